@@ -2,8 +2,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
-#include <random>
-#include <vector>
 
 #include "host_util.h"
 #include "nomad.h"
@@ -38,10 +36,11 @@ extern "C" int nomad_pca_init(const float* X, int64_t n, int32_t d, float std0, 
     KTRY(buf.alloc(&mean_partial, (size_t)mean_blocks * d));
     KTRY(buf.alloc(&mean, (size_t)d));
     hipLaunchKernelGGL(k_pca_colsum, dim3((uint32_t)mean_blocks), dim3(256), 0, st, dX, n, d, mean_partial);
-    hipLaunchKernelGGL(k_pca_mean, dim3(blocks_of(d, 256)), dim3(256), 0, st, (const double*)mean_partial, mean_blocks, d, n, mean);
-    // covariance: enough (tile pair, slab) wavefronts to fill the chip, slabs of at least 256 rows
+    hipLaunchKernelGGL(k_pca_mean, dim3(blocks_of(d, 64)), dim3(64 * kMeanWaves), 0, st, (const double*)mean_partial, mean_blocks, d, n, mean);
+    // covariance: as many (tile pair, slab) wavefronts as the chip holds at once, two per SIMD (every one is a long chain of
+    // matrix instructions, so none is left over for a second round); slabs of at least 256 rows
     const int32_t nb = (d + kColBlock - 1) / kColBlock, n_pairs = nb * (nb + 1) / 2;
-    int64_t slabs64 = std::max<int64_t>(1, (2048 + n_pairs - 1) / n_pairs);
+    int64_t slabs64 = std::max<int64_t>(1, 2048 / n_pairs);
     slabs64 = std::min<int64_t>(slabs64, (n + 255) / 256);
     const int64_t slab_rows = (((n + slabs64 - 1) / slabs64) + 3) / 4 * 4;
     const int32_t slabs = (int32_t)((n + slab_rows - 1) / slab_rows);
@@ -49,61 +48,71 @@ extern "C" int nomad_pca_init(const float* X, int64_t n, int32_t d, float std0, 
     KTRY(buf.alloc(&cov_partial, (size_t)n_pairs * slabs * kColBlock * kColBlock));
     KTRY(buf.alloc(&Cm, (size_t)d * d));
     hipLaunchKernelGGL(k_pca_cov, dim3((uint32_t)(n_pairs * slabs)), dim3(64), 0, st, dX, n, d, (const double*)mean, slabs, slab_rows, cov_partial);
-    hipLaunchKernelGGL(k_pca_cov_reduce, dim3(blocks_of((int64_t)n_pairs * kColBlock * kColBlock, 256)), dim3(256), 0, st,
+    hipLaunchKernelGGL(k_pca_cov_reduce, dim3(blocks_of((int64_t)n_pairs * kColBlock * kColBlock, kReduceEntries)), dim3(256), 0, st,
                        (const double*)cov_partial, n_pairs, slabs, d, n, Cm);
     // leading eigenvectors: subspace iteration from a fixed pseudo-random block
-    double *Q = nullptr, *Z = nullptr, *Z2 = nullptr, *Z3 = nullptr, *lam = nullptr, *resid = nullptr, *factor = nullptr;
+    double *Q = nullptr, *Z = nullptr, *factor = nullptr;
+    RitzState* state = nullptr;
     KTRY(buf.alloc(&Q, (size_t)d * kRitz));
     KTRY(buf.alloc(&Z, (size_t)d * kRitz));
-    KTRY(buf.alloc(&Z2, (size_t)d * kRitz));
-    KTRY(buf.alloc(&Z3, (size_t)d * kRitz));
-    KTRY(buf.alloc(&lam, (size_t)kRitz));
-    KTRY(buf.alloc(&resid, 1));
+    KTRY(buf.alloc(&state, 1));
     KTRY(buf.alloc(&factor, 2));
-    std::vector<double> hQ((size_t)d * kRitz, 0.0);
-    std::mt19937_64 gen(0x6e6f6d6164ULL);
-    for (int32_t r = 0; r < d; ++r)
-        for (int32_t m = 0; m < p; ++m) hQ[(size_t)r * kRitz + m] = (double)(gen() >> 11) * (2.0 / 9007199254740992.0) - 1.0;
-    KTRY(hipMemcpyAsync(Q, hQ.data(), sizeof(double) * hQ.size(), hipMemcpyHostToDevice, st));
-    // kPower applications of C per Rayleigh-Ritz step (that step is one workgroup, an application the whole chip).  Started
-    // from Ritz vectors, column m picks up the directions before it only at rounding level times (lambda_1 / lambda_m)^kPower,
-    // which Gram-Schmidt applied twice removes again.
-    constexpr int kPower = 4;
+    RitzState hstate{};
     const double tol = 1e-12;
-    const int max_iters = 2000, check_every = 4;
-    int iters = 0;
-    double hresid = 1.0, hlam[kRitz] = {0};
-    while (iters < max_iters) {
-        for (int x = 0; x < check_every; ++x) {
-            hipLaunchKernelGGL(k_pca_apply, dim3(blocks_of(d, 4)), dim3(256), 0, st, (const double*)Cm, (const double*)Q, d, Z);
-            double *from = Z, *to = Z2;
-            for (int s = 1; s < kPower; ++s) {
-                hipLaunchKernelGGL(k_pca_apply, dim3(blocks_of(d, 4)), dim3(256), 0, st, (const double*)Cm, (const double*)from, d, to);
-                from = to;
-                to = to == Z2 ? Z3 : Z2;
-            }
-            hipLaunchKernelGGL(k_pca_ritz, dim3(1), dim3(256), 0, st, Q, (const double*)Z, (const double*)from, d, p, lam, resid);
-        }
-        iters += check_every;
-        KTRY(hipMemcpyAsync(&hresid, resid, sizeof(double), hipMemcpyDeviceToHost, st));
+    const int max_steps = 2000;
+    if (d <= kSmallDim) {
+        hipLaunchKernelGGL(k_pca_axes_small, dim3(1), dim3(kSmallThreads), 0, st, (const double*)Cm, Q, d, p, tol, max_steps, state);
+        KTRY(hipMemcpyAsync(&hstate, state, sizeof(hstate), hipMemcpyDeviceToHost, st));
         KTRY(hipStreamSynchronize(st));
-        if (!(hresid > tol)) break;
+    } else {
+        double* Zp = nullptr;
+        KTRY(buf.alloc(&Zp, (size_t)d * kRitz));
+        const size_t lds = (size_t)2 * d * kRitz * sizeof(double);
+        KTRY(hipFuncSetAttribute((const void*)k_pca_ritz, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(k_pca_start, dim3(blocks_of((int64_t)d * kRitz, 256)), dim3(256), 0, st, Q, d, p, state);
+        auto apply = [&](const double* y, const double* prev, double* out) {
+            hipLaunchKernelGGL(k_pca_apply, dim3(blocks_of(d, 16)), dim3(kRitzThreads), 0, st, (const double*)Cm, y, prev, (const RitzState*)state, d, out);
+        };
+        double *block = Q, *image = Z, *spare = Zp;
+        apply(block, nullptr, image);
+        while (true) {
+            hipLaunchKernelGGL(k_pca_ritz, dim3(1), dim3(kRitzThreads), lds, st, (const double*)Cm, block, image, d, p, state);
+            KTRY(hipMemcpyAsync(&hstate, state, sizeof(hstate), hipMemcpyDeviceToHost, st));
+            KTRY(hipStreamSynchronize(st));
+            if (!(hstate.resid > tol) || hstate.steps >= max_steps) break;
+            double *before = block, *now = image;   // T_0 and T_1 of the block
+            for (int k = 1; k < hstate.degree; ++k) {
+                apply(now, before, spare);
+                double* t = before; before = now; now = spare; spare = t;
+            }
+            apply(now, nullptr, before);
+            block = now; image = before;
+        }
+        Q = block;
     }
-    KTRY(hipMemcpyAsync(hlam, lam, sizeof(hlam), hipMemcpyDeviceToHost, st));
-    KTRY(hipStreamSynchronize(st));
-    if (std0 > 0.f && !(hlam[0] > 0.0)) return NOMAD_E_INVALID_ARG;   // no variance to scale
+    KTRY(hipGetLastError());
+    if (std0 > 0.f && !(hstate.lam[0] > 0.0)) return NOMAD_E_INVALID_ARG;   // no variance to scale
     // scores
-    hipLaunchKernelGGL(k_pca_orient, dim3(1), dim3(64), 0, st, (const double*)Q, d, (const double*)lam, std0, factor);
-    hipLaunchKernelGGL(k_pca_project, dim3(blocks_of(n, 4 * kProjectRows)), dim3(256), 0, st, dX, n, d, (const double*)mean, (const double*)Q,
-                       (const double*)factor, (float2*)dTheta);
+    hipLaunchKernelGGL(k_pca_orient, dim3(1), dim3(128), 0, st, (const double*)Q, d, (const RitzState*)state, std0, factor);
+    const auto project = [&](auto kernel, int lanes) {
+        hipLaunchKernelGGL(kernel, dim3(blocks_of(n, 4 * (64 / lanes) * kProjectRows)), dim3(256), 0, st, dX, n, d, (const double*)mean, (const double*)Q,
+                           (const double*)factor, (float2*)dTheta);
+    };
+    if (d % 4 == 0) {   // rows are 16-byte aligned
+        if (d <= 32) project(k_pca_project<4, 8>, 8);
+        else if (d <= 64) project(k_pca_project<4, 16>, 16);
+        else if (d <= 128) project(k_pca_project<4, 32>, 32);
+        else project(k_pca_project<4, 64>, 64);
+    } else if (d <= 16) project(k_pca_project<1, 16>, 16);
+    else project(k_pca_project<1, 64>, 64);
     KTRY(hipGetLastError());
     if (mem == NOMAD_HOST) KTRY(hipMemcpyAsync(theta_out, dTheta, sizeof(float) * (size_t)n * 2, hipMemcpyDeviceToHost, st));
     KTRY(hipStreamSynchronize(st));
     if (stats) {
-        stats[0] = hlam[0];
-        stats[1] = hlam[1];
-        stats[2] = hresid;
-        stats[3] = (double)iters;
+        stats[0] = hstate.lam[0];
+        stats[1] = hstate.lam[1];
+        stats[2] = hstate.resid;
+        stats[3] = (double)hstate.steps;
     }
     return NOMAD_OK;
 }

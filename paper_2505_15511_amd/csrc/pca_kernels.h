@@ -3,9 +3,8 @@
 //   mean        column sums in float64, a slab of rows per block, the slabs added in order
 //   covariance  C = (1/n) sum_i (x_i - mean)(x_i - mean)^T: a dense contraction over the points, on the float64 matrix
 //               cores (v_mfma_f64_16x16x4f64), one wavefront per 64x64 tile of C and slab of rows, slabs added in order
-//   axes        the leading eigenvectors of C by subspace iteration with a Rayleigh-Ritz step per iteration: a block of
-//               kRitz vectors, Z = C Q on the whole chip, the small dense algebra (projected eigenproblem by Jacobi
-//               rotations, re-orthonormalisation by Gram-Schmidt twice) in one workgroup
+//   axes        the leading eigenvectors of C by subspace iteration accelerated with Chebyshev polynomials: a block of
+//               kRitz vectors, a Rayleigh-Ritz step (the 8 x 8 pencil on one wavefront) after every polynomial
 //   scores      theta_i = ((x_i - mean) . axis_1, (x_i - mean) . axis_2), float64, oriented and scaled, rounded once
 #pragma once
 #include <hip/hip_runtime.h>
@@ -18,8 +17,7 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int kMeanRows = 1024;   // rows per partial column sum
 constexpr int kColBlock = 64;     // a wavefront's tile of C is kColBlock x kColBlock (4 x 4 matrix-core tiles)
 constexpr int kRitz = 8;          // vectors iterated together (convergence goes with lambda_9 / lambda_2)
-constexpr int kMaxDim = 768;      // rows of Q per thread of the single-workgroup step: kMaxDim / 256
-constexpr int kRowsPerThread = kMaxDim / 256;
+constexpr int kMaxDim = 768;
 
 __global__ void __launch_bounds__(256) k_pca_colsum(const float* __restrict__ X, int64_t n, int32_t d, double* __restrict__ partial) {
     const int64_t r0 = (int64_t)blockIdx.x * kMeanRows, r1 = min(n, r0 + kMeanRows);
@@ -38,21 +36,32 @@ __global__ void __launch_bounds__(256) k_pca_colsum(const float* __restrict__ X,
     }
 }
 
-__global__ void __launch_bounds__(256) k_pca_mean(const double* __restrict__ partial, int32_t blocks, int32_t d, int64_t n,
-                                                  double* __restrict__ mean) {
-    const int col = blockIdx.x * blockDim.x + threadIdx.x;
-    if (col >= d) return;
+// mean = sum of the partial sums / n; a workgroup per 64 columns, every wavefront its share of the partial sums (eight in
+// flight), the wavefronts' sums added in order.  (One thread per column took 31 us for the 977 slabs of a million rows.)
+constexpr int kMeanWaves = 16;
+__global__ void __launch_bounds__(64 * kMeanWaves) k_pca_mean(const double* __restrict__ partial, int32_t blocks, int32_t d, int64_t n,
+                                                              double* __restrict__ mean) {
+    __shared__ double sum[kMeanWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = blockIdx.x * 64 + lane;
     double s = 0.0;
-    int b = 0;
-    for (; b + 16 <= blocks; b += 16) {   // sixteen partial sums in flight; added in block order
-        double v[16];
+    if (col < d) {
+        int b = wave;
+        for (; b + 7 * kMeanWaves < blocks; b += 8 * kMeanWaves) {
+            double v[8];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = partial[(int64_t)(b + u) * d + col];
+            for (int u = 0; u < 8; ++u) v[u] = partial[(int64_t)(b + u * kMeanWaves) * d + col];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) s += v[u];
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; b < blocks; b += kMeanWaves) s += partial[(int64_t)b * d + col];
     }
-    for (; b < blocks; ++b) s += partial[(int64_t)b * d + col];
-    mean[col] = s / (double)n;
+    sum[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && col < d) {
+        double t = 0.0;
+        for (int w = 0; w < kMeanWaves; ++w) t += sum[w][lane];
+        mean[col] = t / (double)n;
+    }
 }
 
 // column blocks (a, b), a <= b, of tile pair number `pair` when there are nb column blocks
@@ -65,59 +74,85 @@ __host__ __device__ inline void cov_pair(int pair, int nb, int& a, int& b) {
 // One wavefront: tile pair blockIdx.x / slabs, rows slab * slab_rows ...  Operand layout of the 16x16x4 float64
 // instruction: lane l supplies A[i = l % 16][k = l / 16] and B[k = l / 16][j = l % 16]; it receives D[i = l / 16 + 4 v][j = l % 16]
 // in element v.  Here k runs over four consecutive rows of X, i and j over columns: D += Xc^T Xc.
-__global__ void __launch_bounds__(64) k_pca_cov(const float* __restrict__ X, int64_t n, int32_t d, const double* __restrict__ mean,
-                                                int32_t slabs, int64_t slab_rows, double* __restrict__ partial) {
-    const int pair = blockIdx.x / slabs, slab = blockIdx.x % slabs;
-    int a, b;
-    cov_pair(pair, (d + kColBlock - 1) / kColBlock, a, b);
+//
+// Bound by issue: a step of four rows is 16 matrix instructions of 64 cycles, and vector instructions do not overlap float64
+// matrix instructions, so the step carries nothing but its loads (uniform base + 32-bit lane offset), conversions and
+// subtractions.  Columns beyond d are read as the last column (their entries of C are never stored), only the last step of a
+// slab masks rows.  n = 1e6, d = 128: 0.43 ms = 57 TFLOP/s executed (0.56 ms with every element masked); n = 1e5, d = 768:
+// 1.12 ms (2.0 ms).
+template <bool DIAGONAL>
+__device__ __forceinline__ void cov_tile(const float* __restrict__ X, int64_t n, int32_t d, const double* __restrict__ mean, int a, int b,
+                                         int64_t r0, int64_t r1, double* __restrict__ out) {
     const int lane = threadIdx.x, lr = lane >> 4, lc = lane & 15;
-    int cola[4], colb[4];
+    uint32_t offa[4], offb[4];     // elements from the step's first row
     double ma[4], mb[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        cola[u] = a * kColBlock + 16 * u + lc;
-        colb[u] = b * kColBlock + 16 * u + lc;
-        ma[u] = cola[u] < d ? mean[cola[u]] : 0.0;
-        mb[u] = colb[u] < d ? mean[colb[u]] : 0.0;
+        const int ca = min(a * kColBlock + 16 * u + lc, d - 1), cb = min(b * kColBlock + 16 * u + lc, d - 1);
+        offa[u] = (uint32_t)(lr * d + ca);
+        offb[u] = (uint32_t)(lr * d + cb);
+        ma[u] = mean[ca];
+        mb[u] = mean[cb];
     }
     doublex4 acc[4][4];
 #pragma unroll
     for (int x = 0; x < 4; ++x)
 #pragma unroll
         for (int y = 0; y < 4; ++y) acc[x][y] = doublex4{0.0, 0.0, 0.0, 0.0};
-    const int64_t r0 = (int64_t)slab * slab_rows, r1 = min(n, r0 + slab_rows);
-    // loads run kAhead steps (of four rows) ahead of the multiplications: a step is 16 matrix instructions, about half a
-    // microsecond, and the rows come from HBM
+    // loads run kAhead steps ahead of the multiplications: a step is about half a microsecond, and the rows come from HBM
     constexpr int kAhead = 4;
+    const int64_t steps = (r1 - r0) / 4;
     float fa[kAhead][4], fb[kAhead][4];
-    auto fetch = [&](int slot, int64_t r) {   // this lane's row of the step that starts at row r; NaN stands for "no such element"
-        const int64_t row = r + lr;
-        const bool rv = row < r1;
+    auto fetch = [&](int slot, int64_t step) {   // beyond the last step: the last step again (not used)
+        const float* base = X + (r0 + 4 * min(step, steps - 1)) * d;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            fa[slot][u] = (rv && cola[u] < d) ? X[row * d + cola[u]] : __builtin_nanf("");
-            fb[slot][u] = (rv && colb[u] < d) ? X[row * d + colb[u]] : __builtin_nanf("");
+            fa[slot][u] = base[offa[u]];
+            if (!DIAGONAL) fb[slot][u] = base[offb[u]];
         }
     };
+    auto multiply = [&](const float (&va)[4], const float (&vb)[4], bool live) {
+        double xa[4], xb[4];
 #pragma unroll
-    for (int s = 0; s < kAhead; ++s) fetch(s, r0 + 4 * s);
-    for (int64_t r = r0; r < r1; r += 4 * kAhead) {
-#pragma unroll
-        for (int s = 0; s < kAhead; ++s) {   // slot s holds the step at row r + 4 s
-            double xa[4], xb[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {   // an absent element contributes nothing
-                xa[u] = fa[s][u] == fa[s][u] ? (double)fa[s][u] - ma[u] : 0.0;
-                xb[u] = fb[s][u] == fb[s][u] ? (double)fb[s][u] - mb[u] : 0.0;
-            }
-            fetch(s, r + 4 * (s + kAhead));   // beyond the slab: all NaN, no memory access
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int y = 0; y < 4; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[x], xb[y], acc[x][y], 0, 0, 0);
+        for (int u = 0; u < 4; ++u) {
+            xa[u] = live ? (double)va[u] - ma[u] : 0.0;
+            xb[u] = DIAGONAL ? xa[u] : live ? (double)vb[u] - mb[u] : 0.0;
         }
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[x], xb[y], acc[x][y], 0, 0, 0);
+    };
+    if (steps > 0) {
+#pragma unroll
+        for (int s = 0; s < kAhead; ++s) fetch(s, s);
+        int64_t st = 0;
+        for (; st + kAhead <= steps; st += kAhead) {
+#pragma unroll
+            for (int s = 0; s < kAhead; ++s) {   // slot s holds step st + s
+                float va[4], vb[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) { va[u] = fa[s][u]; vb[u] = fb[s][u]; }
+                fetch(s, st + s + kAhead);
+                multiply(va, vb, true);
+                __builtin_amdgcn_sched_barrier(0);   // left to itself the compiler converts four steps at once: one wavefront per SIMD
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kAhead; ++s)
+            if (st + s < steps) multiply(fa[s], fb[s], true);
     }
-    double* out = partial + (int64_t)blockIdx.x * (kColBlock * kColBlock);
+    if (r0 + 4 * steps < r1) {   // one to three rows left
+        const bool live = r0 + 4 * steps + lr < r1;
+        const float* base = X + (r0 + 4 * steps) * d;
+        float va[4], vb[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            va[u] = live ? base[offa[u]] : 0.f;
+            vb[u] = !DIAGONAL && live ? base[offb[u]] : 0.f;
+        }
+        multiply(va, vb, live);
+    }
 #pragma unroll
     for (int x = 0; x < 4; ++x)
 #pragma unroll
@@ -126,314 +161,463 @@ __global__ void __launch_bounds__(64) k_pca_cov(const float* __restrict__ X, int
             for (int v = 0; v < 4; ++v) out[(16 * x + lr + 4 * v) * kColBlock + 16 * y + lc] = acc[x][y][v];
 }
 
-// C = (1/n) sum over the slabs, in slab order; both triangles written
+__global__ void __launch_bounds__(64, 2) k_pca_cov(const float* __restrict__ X, int64_t n, int32_t d, const double* __restrict__ mean,
+                                                int32_t slabs, int64_t slab_rows, double* __restrict__ partial) {
+    const int pair = blockIdx.x / slabs, slab = blockIdx.x % slabs;
+    int a, b;
+    cov_pair(pair, (d + kColBlock - 1) / kColBlock, a, b);
+    const int64_t r0 = (int64_t)slab * slab_rows, r1 = min(n, r0 + slab_rows);
+    double* out = partial + (int64_t)blockIdx.x * (kColBlock * kColBlock);
+    if (a == b) cov_tile<true>(X, n, d, mean, a, b, r0, r1, out);
+    else cov_tile<false>(X, n, d, mean, a, b, r0, r1, out);
+}
+
+// C = (1/n) sum over the slabs; both triangles written.  A workgroup takes 32 consecutive entries of a tile, eight threads
+// each: every eighth slab (eight in flight), the eight sums added in order.  (One thread per entry: 40 us for 683 slabs.)
+constexpr int kReduceEntries = 32;
 __global__ void __launch_bounds__(256) k_pca_cov_reduce(const double* __restrict__ partial, int32_t n_pairs, int32_t slabs, int32_t d,
                                                         int64_t n, double* __restrict__ C) {
-    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= (int64_t)n_pairs * kColBlock * kColBlock) return;
+    __shared__ double part[8][kReduceEntries];
+    const int sub = threadIdx.x / kReduceEntries, lane = threadIdx.x % kReduceEntries;
+    const int64_t x = (int64_t)blockIdx.x * kReduceEntries + lane;   // kReduceEntries divides a tile: one pair per workgroup
     const int pair = (int)(x / (kColBlock * kColBlock)), e = (int)(x % (kColBlock * kColBlock));
+    double s = 0.0;
+    const double* src = partial + (int64_t)pair * slabs * (kColBlock * kColBlock) + e;
+    int sl = sub;
+    for (; sl + 56 < slabs; sl += 64) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(sl + 8 * u) * (kColBlock * kColBlock)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; sl < slabs; sl += 8) s += src[(int64_t)sl * (kColBlock * kColBlock)];
+    part[sub][lane] = s;
+    __syncthreads();
+    if (sub != 0) return;
+    s = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += part[u][lane];
     int a, b;
     cov_pair(pair, (d + kColBlock - 1) / kColBlock, a, b);
     const int gi = a * kColBlock + e / kColBlock, gj = b * kColBlock + e % kColBlock;
     if (gi >= d || gj >= d) return;
-    double s = 0.0;
-    const double* src = partial + (int64_t)pair * slabs * (kColBlock * kColBlock) + e;
-    int sl = 0;
-    for (; sl + 16 <= slabs; sl += 16) {   // sixteen partial tiles in flight; added in slab order
-        double v[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = src[(int64_t)(sl + u) * (kColBlock * kColBlock)];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) s += v[u];
-    }
-    for (; sl < slabs; ++sl) s += src[(int64_t)sl * (kColBlock * kColBlock)];
     s /= (double)n;
     C[(int64_t)gi * d + gj] = s;
     if (a != b) C[(int64_t)gj * d + gi] = s;
 }
 
-// Z = C Q: one wavefront per row of C; Q and Z are [d][kRitz] row-major (columns >= p stay zero)
-__global__ void __launch_bounds__(256) k_pca_apply(const double* __restrict__ C, const double* __restrict__ Q, int32_t d,
-                                                   double* __restrict__ Z) {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= d) return;
-    double s[kRitz];
-#pragma unroll
-    for (int m = 0; m < kRitz; ++m) s[m] = 0.0;
-    for (int col = lane; col < d; col += 64) {
-        const double c = C[(int64_t)row * d + col];
-#pragma unroll
-        for (int m = 0; m < kRitz; ++m) s[m] = fma(c, Q[col * kRitz + m], s[m]);
-    }
-#pragma unroll
-    for (int m = 0; m < kRitz; ++m)
-        for (int w = 32; w > 0; w >>= 1) s[m] += __shfl_xor(s[m], w, 64);
-    if (lane == 0)
-#pragma unroll
-        for (int m = 0; m < kRitz; ++m) Z[row * kRitz + m] = s[m];
-}
+// ---- the leading eigenvectors of C: subspace iteration on a block of kRitz vectors, Chebyshev polynomials of C as the power
+// Rayleigh-Ritz on the block (ritz_step) gives the Ritz vectors R and values lam; the next block is T_deg((C - c) / e) R,
+// T the Chebyshev polynomial of the interval [0, b] (c = e = b / 2) whose upper end b is the smallest Ritz value of the
+// block: components with eigenvalues in the interval stay bounded by 1, those above it grow like cosh(deg acosh(2 lam / b - 1)).
+// Where C^4 per step needed 28 steps of 139 us for a million points in 128 dimensions (and 40 at flatter spectra), five to
+// eight steps of degree up to kMaxDegree do; a step costs about 15 us now that its 8 x 8 algebra runs on a whole wavefront.
+constexpr int kMaxDegree = 20;
+constexpr int kRitzThreads = 1024; // of the step by itself: one row of the block per thread
+constexpr int kSmallDim = 128;     // up to here the whole iteration is one workgroup (k_pca_axes_small) ...
+constexpr int kSmallThreads = 512; // ... of one wavefront per 16-row tile of C
 
-// sums of COUNT per-thread values over the 256 threads of the workgroup, into out[0..COUNT) in LDS (COUNT <= 64)
-template <int COUNT>
-__device__ __forceinline__ void block_sums(const double (&v)[COUNT], double (*scratch)[64], double* out) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int c = 0; c < COUNT; ++c) {
-        double s = v[c];
-        for (int w = 32; w > 0; w >>= 1) s += __shfl_xor(s, w, 64);
-        if (lane == 0) scratch[wave][c] = s;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < COUNT) out[threadIdx.x] = scratch[0][threadIdx.x] + scratch[1][threadIdx.x] + scratch[2][threadIdx.x] + scratch[3][threadIdx.x];
-    __syncthreads();
-}
+struct RitzState {                 // what a step decides, for the host and for the next step
+    double lam[kRitz];
+    double resid;                  // max over the first two pairs of |C w - lam w| / lam_1
+    double c, e;                   // centre and half width of the interval
+    double best;                   // smallest residual so far, for the stall rule
+    int32_t degree;                // of the polynomial that makes the next block
+    int32_t stall;
+    int32_t steps;
+};
 
-// Eigenpairs of the symmetric p x p matrix H (p <= kRitz) by cyclic Jacobi rotations, eigenvalues descending; one thread.
-// W is orthogonal whatever the number of sweeps; lam and W are the eigenpairs to the accuracy the sweeps reached.
-__device__ inline void jacobi_eigen(double (*H)[kRitz], int p, double (*W)[kRitz], double* lam) {
-    for (int i = 0; i < kRitz; ++i)
-        for (int j = 0; j < kRitz; ++j) W[i][j] = i == j ? 1.0 : 0.0;
-    // Two sweeps per call are enough: the caller iterates, and its basis is nearly the Ritz basis from the second
-    // call on (H nearly diagonal, where the rotations converge quadratically).  Rotations that would change nothing at
-    // float64 resolution are skipped.
-    for (int sweep = 0; sweep < 2; ++sweep) {
-        bool rotated = false;
-        for (int i = 0; i < p; ++i)
-            for (int j = i + 1; j < p; ++j) {
-                const double hij = H[i][j];
-                if (hij * hij <= 1e-34 * fabs(H[i][i] * H[j][j]) || hij == 0.0) continue;
-                rotated = true;
-                const double theta = (H[j][j] - H[i][i]) / (2.0 * hij);
-                const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
-                for (int k = 0; k < p; ++k) {   // H <- H J
-                    const double hki = H[k][i], hkj = H[k][j];
-                    H[k][i] = c * hki - s * hkj;
-                    H[k][j] = s * hki + c * hkj;
-                }
-                for (int k = 0; k < p; ++k) {   // H <- J^T H
-                    const double hik = H[i][k], hjk = H[j][k];
-                    H[i][k] = c * hik - s * hjk;
-                    H[j][k] = s * hik + c * hjk;
-                }
-                for (int k = 0; k < p; ++k) {   // W <- W J
-                    const double wki = W[k][i], wkj = W[k][j];
-                    W[k][i] = c * wki - s * wkj;
-                    W[k][j] = s * wki + c * wkj;
-                }
+__device__ __forceinline__ double shfl_f64(double v, int lane) { return __shfl(v, lane, 64); }
+
+// Eigenpairs of the pencil H w = lam G w (both symmetric kRitz x kRitz, G positive semi-definite) on one wavefront, matrix
+// entry (i, j) in lane 8 i + j.  G is scaled to a unit diagonal and factored, G = L L^T; S = L^-1 H L^-T is diagonalised by
+// Jacobi rotations, four disjoint ones at a time (seven rounds per sweep pair every index with every other).  A column
+// whose pivot vanishes (dependent on the ones before it, or absent) is left out: its eigenvalue is 0, its vector zero, and
+// it sorts last.  w_out [kRitz][kRitz] row-major (column m: the m-th Ritz vector's coefficients), lam descending.
+__device__ __forceinline__ void pencil_eigen(double g, double h, double* __restrict__ w_out, double* __restrict__ lam_out,
+                                             int32_t* __restrict__ dead_out) {
+    const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
+    // unit diagonal
+    const double gd = shfl_f64(g, 9 * i), gdj = shfl_f64(g, 9 * j);
+    const double si = gd > 0.0 ? 1.0 / sqrt(gd) : 0.0, sj = gdj > 0.0 ? 1.0 / sqrt(gdj) : 0.0;
+    g *= si * sj;
+    h *= si * sj;
+    // forward elimination of G carried out on the identity as well: E = L^-1
+    double E = i == j ? 1.0 : 0.0;
+    bool dead = false;      // of row i
+#pragma unroll
+    for (int k = 0; k < kRitz; ++k) {
+        const double pivot = shfl_f64(g, 9 * k);
+        const double rs = pivot > 1e-13 ? 1.0 / sqrt(pivot) : 0.0;
+        if (i == k && rs == 0.0) dead = true;
+        const double lik = shfl_f64(g, 8 * i + k) * rs, ljk = shfl_f64(g, 8 * j + k) * rs;   // L[i][k], L[j][k] (i, j > k)
+        const double Ek = shfl_f64(E, 8 * k + j) * rs;                                       // row k of L^-1
+        if (i == k) E = Ek;
+        if (i > k) E = fma(-lik, Ek, E);
+        if (i > k && j > k) g = fma(-lik, ljk, g);
+    }
+    // S = E H E^T
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < kRitz; ++k) t = fma(shfl_f64(E, 8 * i + k), shfl_f64(h, 8 * k + j), t);
+    double S = 0.0;
+#pragma unroll
+    for (int k = 0; k < kRitz; ++k) S = fma(shfl_f64(t, 8 * i + k), shfl_f64(E, 8 * j + k), S);
+    S = 0.5 * (S + shfl_f64(S, 8 * j + i));
+    double U = i == j ? 1.0 : 0.0;
+    for (int sweep = 0; sweep < 12; ++sweep) {
+        const double dii = shfl_f64(S, 9 * i), djj = shfl_f64(S, 9 * j);
+        if (!__any(i != j && S * S > 1e-33 * fabs(dii * djj))) break;
+        for (int round = 0; round < 7; ++round) {
+            // index x < 7 meets (round - x) mod 7, or 7 where that is x itself
+            auto partner = [round](int x) {
+                if (x == 7) return (4 * round) % 7;
+                const int y = (round - x + 7) % 7;
+                return y == x ? 7 : y;
+            };
+            const int ip = partner(i), jp = partner(j);
+            const int lo = min(i, ip), hi = max(i, ip);
+            const double sll = shfl_f64(S, 9 * lo), shh = shfl_f64(S, 9 * hi), slh = shfl_f64(S, 8 * lo + hi);
+            double cs = 1.0, sn = 0.0;
+            if (slh * slh > 1e-34 * fabs(sll * shh) && slh != 0.0) {
+                const double theta = (shh - sll) / (2.0 * slh);
+                const double tt = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(fma(theta, theta, 1.0)));
+                cs = 1.0 / sqrt(fma(tt, tt, 1.0));
+                sn = tt * cs;
             }
-        if (!rotated) break;
-    }
-    for (int i = 0; i < p; ++i) lam[i] = H[i][i];
-    for (int i = 0; i < p; ++i) {   // selection sort, descending
-        int best = i;
-        for (int j = i + 1; j < p; ++j)
-            if (lam[j] > lam[best]) best = j;
-        if (best != i) {
-            const double t = lam[i]; lam[i] = lam[best]; lam[best] = t;
-            for (int k = 0; k < p; ++k) { const double w = W[k][i]; W[k][i] = W[k][best]; W[k][best] = w; }
+            const double sg = i == lo ? -sn : sn;                       // row i <- cs row i + sg row ip
+            const double cj = shfl_f64(cs, 8 * j), sgj = shfl_f64(sg, 8 * j);
+            const double r = fma(sg, shfl_f64(S, 8 * ip + j), cs * S);
+            S = fma(sgj, shfl_f64(r, 8 * i + jp), cj * r);
+            U = fma(sgj, shfl_f64(U, 8 * i + jp), cj * U);
         }
     }
-    for (int i = p; i < kRitz; ++i) lam[i] = 0.0;
+    // W = D E^T U, columns in descending order of the eigenvalues
+    double W = 0.0;
+#pragma unroll
+    for (int k = 0; k < kRitz; ++k) W = fma(shfl_f64(E, 8 * k + i), shfl_f64(U, 8 * k + j), W);
+    W *= si;
+    const int row_dead = dead ? 1 : 0;
+    const int col_dead = __shfl(row_dead, 8 * j, 64);
+    const double lam = col_dead ? 0.0 : shfl_f64(S, 9 * j);
+    if (col_dead) W = 0.0;
+    int rank = 0;
+#pragma unroll
+    for (int k = 0; k < kRitz; ++k) {
+        const double lk = shfl_f64(lam, k);                 // lane k: row 0, column k
+        const int dk = __shfl(col_dead, k, 64);
+        rank += dk != col_dead ? (dk < col_dead) : (lk > lam || (lk == lam && k < j));
+    }
+    w_out[i * kRitz + rank] = W;
+    if (i == 0) { lam_out[rank] = lam; dead_out[rank] = col_dead; }
 }
 
-// One Rayleigh-Ritz step in one workgroup.  In: Q [d][kRitz] (orthonormal columns, or any start block) and Z = C Q.
-// H = Q^T Z, H = W diag(lam) W^T; Ritz vectors Q W with images Z W; residual = max over the first two pairs of
-// |Z w - lam Q w| / lam_1; the next Q = the orthonormalised Z W (Gram-Schmidt, every column projected twice; a column
-// that vanishes -- C of lower rank than the block -- is replaced by a coordinate vector).
-// Znext = C^s Q for some s >= 1 (Z itself when s = 1): the next basis is the orthonormalised Znext W, s power steps at once.
-__global__ void __launch_bounds__(256) k_pca_ritz(double* __restrict__ Q, const double* __restrict__ Z, const double* __restrict__ Znext,
-                                                  int32_t d, int32_t p, double* __restrict__ lam_out, double* __restrict__ resid_out) {
-    __shared__ double scratch[4][64];
-    __shared__ double sums[64];
-    __shared__ double H[kRitz][kRitz], W[kRitz][kRitz], lam[kRitz];
-    const int tid = threadIdx.x;
-    double q[kRowsPerThread][kRitz], z[kRowsPerThread][kRitz];
-#pragma unroll
-    for (int x = 0; x < kRowsPerThread; ++x) {
-        const int row = tid + 256 * x;
-#pragma unroll
-        for (int m = 0; m < kRitz; ++m) {
-            q[x][m] = row < d ? Q[row * kRitz + m] : 0.0;
-            z[x][m] = row < d ? Z[row * kRitz + m] : 0.0;
-        }
-    }
+// LDS of a Rayleigh-Ritz step
+template <int THREADS>
+struct RitzLds {
+    double part[THREADS / 64][2][kRitz * kRitz];   // partial sums of G and H per wavefront
+    double W[kRitz * kRitz], lam[kRitz];
+    double red[THREADS / 64][2];
+    int32_t dead[kRitz];
+};
+
+// One Rayleigh-Ritz step in one workgroup of THREADS >= d.  Q [d][kRitz] any block, Z = C Q (LDS, row-major).  On return
+// Q holds the Ritz vectors, Z the next Chebyshev iterate (C - c) / e Q, and `st` (LDS or global, written by thread 0) what
+// comes next.  A dependent column is replaced by a coordinate vector.
+template <int THREADS>
+__device__ __forceinline__ void ritz_step(double* __restrict__ Q, double* __restrict__ Z, const double* __restrict__ C, int32_t d, int32_t p,
+                                          RitzLds<THREADS>& L, RitzState& st) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int kWaves = THREADS / 64;
     {
-        double h[kRitz * kRitz];
-#pragma unroll
-        for (int a = 0; a < kRitz; ++a)
-#pragma unroll
-            for (int b = 0; b < kRitz; ++b) {
-                double s = 0.0;
-#pragma unroll
-                for (int x = 0; x < kRowsPerThread; ++x) s = fma(q[x][a], z[x][b], s);
-                h[a * kRitz + b] = s;
-            }
-        block_sums<kRitz * kRitz>(h, scratch, sums);
-    }
-    if (tid == 0) {
-        for (int a = 0; a < kRitz; ++a)
-            for (int b = 0; b < kRitz; ++b) H[a][b] = 0.5 * (sums[a * kRitz + b] + sums[b * kRitz + a]);
-        jacobi_eigen(H, p, W, lam);
+        const int a = lane >> 3, b = lane & 7;
+        double g = 0.0, h = 0.0;
+        for (int r = wave; r < d; r += kWaves) {
+            const double qa = Q[r * kRitz + a];
+            g = fma(qa, Q[r * kRitz + b], g);
+            h = fma(qa, Z[r * kRitz + b], h);
+        }
+        L.part[wave][0][lane] = g;
+        L.part[wave][1][lane] = h;
     }
     __syncthreads();
-    // Ritz vectors and their images
-    double rq[kRowsPerThread][kRitz], rz[kRowsPerThread][kRitz];
+    if (wave == 0) {
+        double g = 0.0, h = 0.0;
 #pragma unroll
-    for (int x = 0; x < kRowsPerThread; ++x)
-#pragma unroll
-        for (int m = 0; m < kRitz; ++m) {
-            double sq = 0.0, sz = 0.0;
-#pragma unroll
-            for (int a = 0; a < kRitz; ++a) {
-                sq = fma(q[x][a], W[a][m], sq);
-                sz = fma(z[x][a], W[a][m], sz);
-            }
-            rq[x][m] = sq;
-            rz[x][m] = sz;
-        }
-    {
-        double r[2] = {0.0, 0.0};
-#pragma unroll
-        for (int x = 0; x < kRowsPerThread; ++x)
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const double e = rz[x][m] - lam[m] * rq[x][m];
-                r[m] = fma(e, e, r[m]);
-            }
-        block_sums<2>(r, scratch, sums);
-        if (tid == 0) {
-            const double worst = sqrt(fmax(sums[0], sums[1]));
-            resid_out[0] = lam[0] > 0.0 ? worst / lam[0] : 0.0;
-            for (int m = 0; m < kRitz; ++m) lam_out[m] = lam[m];
-        }
+        for (int w = 0; w < kWaves; ++w) { g += L.part[w][0][lane]; h += L.part[w][1][lane]; }
+        h = 0.5 * (h + shfl_f64(h, 8 * (lane & 7) + (lane >> 3)));
+        pencil_eigen(g, h, L.W, L.lam, L.dead);
     }
-    if (Znext != Z) {
+    __syncthreads();
+    double rq[kRitz], rz[kRitz];
+    double e0 = 0.0, e1 = 0.0;
+    if (tid < d) {
 #pragma unroll
-        for (int x = 0; x < kRowsPerThread; ++x) {
-            const int row = tid + 256 * x;
+        for (int m = 0; m < kRitz; ++m) { rq[m] = 0.0; rz[m] = 0.0; }
 #pragma unroll
-            for (int m = 0; m < kRitz; ++m) z[x][m] = row < d ? Znext[row * kRitz + m] : 0.0;
+        for (int a = 0; a < kRitz; ++a) {
+            const double qa = Q[tid * kRitz + a], za = Z[tid * kRitz + a];
 #pragma unroll
             for (int m = 0; m < kRitz; ++m) {
-                double sz = 0.0;
-#pragma unroll
-                for (int a = 0; a < kRitz; ++a) sz = fma(z[x][a], W[a][m], sz);
-                rz[x][m] = sz;
+                rq[m] = fma(qa, L.W[a * kRitz + m], rq[m]);
+                rz[m] = fma(za, L.W[a * kRitz + m], rz[m]);
             }
         }
+        const double d0 = rz[0] - L.lam[0] * rq[0], d1 = rz[1] - L.lam[1] * rq[1];
+        e0 = d0 * d0;
+        e1 = d1 * d1;
     }
-    // the next basis: orthonormalise the images column by column (q is reused for the finished columns)
-#pragma unroll
-    for (int m = 0; m < kRitz; ++m) {
-        if (m >= p) {
-#pragma unroll
-            for (int x = 0; x < kRowsPerThread; ++x) q[x][m] = 0.0;
-            continue;
+    for (int w = 32; w > 0; w >>= 1) { e0 += __shfl_xor(e0, w, 64); e1 += __shfl_xor(e1, w, 64); }
+    if (lane == 0) { L.red[wave][0] = e0; L.red[wave][1] = e1; }
+    __syncthreads();
+    if (tid == 0) {
+        double s0 = 0.0, s1 = 0.0;
+        for (int w = 0; w < kWaves; ++w) { s0 += L.red[w][0]; s1 += L.red[w][1]; }
+        const double l0 = L.lam[0];
+        const double r0 = l0 > 0.0 ? sqrt(s0) / l0 : 0.0, resid = l0 > 0.0 ? fmax(r0, sqrt(s1) / l0) : 0.0;
+        for (int m = 0; m < kRitz; ++m) st.lam[m] = L.lam[m];
+        st.resid = resid;
+        st.steps += 1;
+        // Upper end of the interval: the block's smallest Ritz value.  Inside a cluster of more than kRitz equal eigenvalues
+        // that end lies in the cluster and nothing is gained on what is below: after four steps without progress, one step
+        // with a lower end.
+        double shrink = 1.0;
+        if (resid > 0.5 * st.best) {
+            if (++st.stall >= 4) { shrink = 0.8; st.stall = 0; }
+        } else {
+            st.best = resid;
+            st.stall = 0;
         }
-        double v[kRowsPerThread];
+        // The first direction leaks into the other columns at the level rho of its error; the polynomial amplifies the leak
+        // by its value at lam_1.  Held at 1e4 relative to 1 the scaled Gram matrix stays factorable with digits to spare.
+        const double rho = fmax(r0, 1e-15), room = 9.2 - log(rho);
+        const double b = fmax(shrink * L.lam[p - 1], 2e-4 * rho * l0);
+        int deg = kMaxDegree;
+        if (b > 0.0) {
+            const double x1 = 2.0 * l0 / b - 1.0, x2 = 2.0 * L.lam[p > 1 ? 1 : 0] / b - 1.0;
+            if (x1 > 1.0 + 1e-9) deg = min(deg, (int)(room / acosh(x1)));
+            if (x2 > 1.0 + 1e-6 && resid > 0.0) deg = min(deg, (int)ceil(log(resid / 1e-13) / acosh(x2)));   // what is left to gain
+        }
+        st.degree = max(1, deg);
+        st.c = 0.5 * b;
+        st.e = 0.5 * b;
+    }
+    __syncthreads();
+    if (tid < d) {
+        const double c = st.c, inv_e = st.e > 0.0 ? 1.0 / st.e : 0.0;
+        const int salt = st.steps * 101;
 #pragma unroll
-        for (int x = 0; x < kRowsPerThread; ++x) v[x] = rz[x][m];   // by now: column m of Znext W
-        for (int attempt = 0; attempt < 4; ++attempt) {
-            double before[1] = {0.0};
+        for (int m = 0; m < kRitz; ++m) {
+            if (m < p && L.dead[m]) {   // a fresh direction; its image is a column of C
+                const int unit = (m * 37 + salt) % d;
+                rq[m] = tid == unit ? 1.0 : 0.0;
+                rz[m] = C[(int64_t)tid * d + unit];
+            }
+            Q[tid * kRitz + m] = rq[m];
+            Z[tid * kRitz + m] = (rz[m] - c * rq[m]) * inv_e;
+        }
+    }
+    __syncthreads();
+}
+
+// entry x of the start block [d][kRitz]: a fixed pseudo-random number in [-1, 1) (the finaliser of a 64-bit mixing function
+// applied to x), zero in the columns >= p
+__device__ __forceinline__ double start_entry(int x, int32_t p) {
+    if (x % kRitz >= p) return 0.0;
+    uint64_t h = ((uint64_t)x + 1u) * 0x9E3779B97F4A7C15ull;
+    h = (h ^ (h >> 30)) * 0xBF58476D1CE4E5B9ull;
+    h = (h ^ (h >> 27)) * 0x94D049BB133111EBull;
+    h ^= h >> 31;
+    return (double)(h >> 11) * (2.0 / 9007199254740992.0) - 1.0;
+}
+
+__global__ void __launch_bounds__(256) k_pca_start(double* __restrict__ Q, int32_t d, int32_t p, RitzState* __restrict__ st) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    if (x < d * kRitz) Q[x] = start_entry(x, p);
+    if (x == 0) { *st = RitzState{}; st->best = 1e300; }
+}
+
+// One 16-row tile of C times a block [d][kRitz] on the float64 matrix cores, by the 16 wavefronts of a workgroup: every
+// wavefront multiplies its share of the columns, the partial tiles are added in wavefront order.  Returns the product for
+// (row, column) = (tid / kRitz, tid % kRitz) in the threads tid < 16 kRitz.
+__device__ __forceinline__ double tile_product(const double* __restrict__ C, const double* __restrict__ Y, int32_t d, int row0,
+                                               double (*part)[16 * kRitz]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane >> 4, lc = lane & 15;
+    const int row = min(row0 + lc, d - 1);
+    constexpr int kSteps = (kMaxDim / 4 + 15) / 16;     // steps of four columns per wavefront, at most
+    double a[kSteps], y[kSteps];
 #pragma unroll
-            for (int x = 0; x < kRowsPerThread; ++x) before[0] = fma(v[x], v[x], before[0]);
-            block_sums<1>(before, scratch, sums);
-            const double norm_before = sums[0];
-            __syncthreads();
-            for (int pass = 0; pass < 2; ++pass) {
-                double dots[kRitz];
+    for (int s = 0; s < kSteps; ++s) {
+        const int k = 4 * (wave + 16 * s) + lr;
+        const bool live = k < d;
+        a[s] = live ? C[(int64_t)row * d + k] : 0.0;
+        y[s] = live && lc < kRitz ? Y[k * kRitz + lc] : 0.0;
+    }
+    doublex4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int j = 0; j < kRitz; ++j) {
-                    double s = 0.0;
-                    if (j < m)
+    for (int s = 0; s < kSteps; ++s)
+        if (4 * (wave + 16 * s) < d) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], y[s], acc, 0, 0, 0);
+    if (lc < kRitz) {
 #pragma unroll
-                        for (int x = 0; x < kRowsPerThread; ++x) s = fma(v[x], q[x][j], s);
-                    dots[j] = s;
+        for (int v = 0; v < 4; ++v) part[wave][(lr + 4 * v) * kRitz + lc] = acc[v];
+    }
+    __syncthreads();
+    double sum = 0.0;
+    if (threadIdx.x < 16 * kRitz)
+#pragma unroll
+        for (int w = 0; w < 16; ++w) sum += part[w][threadIdx.x];
+    return sum;
+}
+
+// out = C y (prev == nullptr) or the Chebyshev step out = 2 (C y - c y) / e - prev; a workgroup per 16 rows
+__global__ void __launch_bounds__(kRitzThreads) k_pca_apply(const double* __restrict__ C, const double* __restrict__ y, const double* __restrict__ prev,
+                                                            const RitzState* __restrict__ st, int32_t d, double* __restrict__ out) {
+    __shared__ double part[16][16 * kRitz];
+    const int row0 = blockIdx.x * 16, x = row0 * kRitz + (int)threadIdx.x;
+    const bool live = threadIdx.x < 16 * kRitz && x < d * kRitz;
+    // what the last line needs is fetched ahead of the product: three memory latencies less in a kernel made of them
+    const double yx = live && prev ? y[x] : 0.0, px = live && prev ? prev[x] : 0.0, c = st->c, e = st->e;
+    const double v = tile_product(C, y, d, row0, part);
+    if (live) out[x] = prev ? 2.0 * (v - c * yx) / e - px : v;
+}
+
+// the Rayleigh-Ritz step on a block in global memory: Q in (the block), out (the Ritz vectors); Z in (C Q), out (the next iterate)
+__global__ void __launch_bounds__(kRitzThreads) k_pca_ritz(const double* __restrict__ C, double* __restrict__ Q, double* __restrict__ Z, int32_t d,
+                                                           int32_t p, RitzState* __restrict__ st) {
+    extern __shared__ double block[];   // Q, Z
+    __shared__ RitzLds<kRitzThreads> L;
+    __shared__ RitzState s;
+    static_assert(kMaxDim <= kRitzThreads && kSmallDim <= kSmallThreads, "one row per thread");
+    double *q = block, *z = block + (size_t)d * kRitz;
+    for (int x = threadIdx.x; x < d * kRitz; x += kRitzThreads) { q[x] = Q[x]; z[x] = Z[x]; }
+    if (threadIdx.x == 0) s = *st;
+    __syncthreads();
+    ritz_step<kRitzThreads>(q, z, C, d, p, L, s);
+    for (int x = threadIdx.x; x < d * kRitz; x += kRitzThreads) { Q[x] = q[x]; Z[x] = z[x]; }
+    if (threadIdx.x == 0) *st = s;
+}
+
+// The whole iteration for d <= kSmallDim in one workgroup: the block stays in LDS, a wavefront keeps its 16 rows of C in
+// registers, so a multiplication by C is at most 32 matrix instructions per wavefront and one barrier, about 2 us where a
+// launch over the chip takes 5.
+__global__ void __launch_bounds__(kSmallThreads) k_pca_axes_small(const double* __restrict__ C, double* __restrict__ Q, int32_t d, int32_t p,
+                                                                  double tol, int32_t max_steps, RitzState* __restrict__ st_out) {
+    __shared__ double Y[2][kSmallDim * kRitz];
+    __shared__ RitzLds<kSmallThreads> L;
+    __shared__ RitzState st;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+    constexpr int kSteps = kSmallDim / 4;
+    double a[kSteps];
+    const int row0 = wave * 16, arow = row0 + lc;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) a[s] = arow < d && 4 * s + lr < d ? C[(int64_t)arow * d + 4 * s + lr] : 0.0;
+    for (int x = tid; x < kSmallDim * kRitz; x += kSmallThreads) {   // rows beyond d stay zero
+        Y[0][x] = x < d * kRitz ? start_entry(x, p) : 0.0;
+        Y[1][x] = 0.0;
+    }
+    if (tid == 0) { st = RitzState{}; st.best = 1e300; }
+    __syncthreads();
+    // Y[to] = C Y[from], or the Chebyshev step with Y[to] holding the iterate before (all threads call)
+    auto multiply = [&](int from, int to, bool step) {
+        if (row0 < d) {
+            doublex4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < kSteps; s += 2) {
+                if (4 * s < d) {
+                    const double y0 = lc < kRitz ? Y[from][(4 * s + lr) * kRitz + lc] : 0.0;
+                    const double y1 = lc < kRitz ? Y[from][(4 * s + 4 + lr) * kRitz + lc] : 0.0;
+                    acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], y0, acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s + 1], y1, acc1, 0, 0, 0);
                 }
-                block_sums<kRitz>(dots, scratch, sums);
-#pragma unroll
-                for (int j = 0; j < kRitz; ++j)
-                    if (j < m)
-#pragma unroll
-                        for (int x = 0; x < kRowsPerThread; ++x) v[x] = fma(-sums[j], q[x][j], v[x]);
-                __syncthreads();
             }
-            double after[1] = {0.0};
+            if (lc < kRitz) {
+                const double c = st.c, inv_e = step ? 1.0 / st.e : 0.0;
 #pragma unroll
-            for (int x = 0; x < kRowsPerThread; ++x) after[0] = fma(v[x], v[x], after[0]);
-            block_sums<1>(after, scratch, sums);
-            const double norm_after = sums[0];
-            __syncthreads();
-            if (norm_after > 1e-24 * norm_before && norm_after > 0.0) {
-                const double inv = 1.0 / sqrt(norm_after);
-#pragma unroll
-                for (int x = 0; x < kRowsPerThread; ++x) q[x][m] = v[x] * inv;
-                break;
-            }
-            // nothing left of this column: start again from a coordinate vector
-            const int unit = (m * 37 + attempt * 101) % d;
-#pragma unroll
-            for (int x = 0; x < kRowsPerThread; ++x) {
-                v[x] = (tid + 256 * x) == unit ? 1.0 : 0.0;
-                q[x][m] = 0.0;
+                for (int v = 0; v < 4; ++v) {
+                    const int x = (row0 + lr + 4 * v) * kRitz + lc;
+                    const double r = acc0[v] + acc1[v];
+                    Y[to][x] = step ? 2.0 * (r - c * Y[from][x]) * inv_e - Y[to][x] : r;
+                }
             }
         }
+        __syncthreads();
+    };
+    int q = 0;      // Y[q] is the block (later the iterate before), Y[q ^ 1] its image (the newest iterate)
+    multiply(q, q ^ 1, false);
+    for (int step = 0; step < max_steps; ++step) {
+        ritz_step<kSmallThreads>(Y[q], Y[q ^ 1], C, d, p, L, st);
+        if (!(st.resid > tol) || step + 1 == max_steps) break;
+        const int degree = st.degree;
+        for (int k = 1; k < degree; ++k) { multiply(q ^ 1, q, true); q ^= 1; }
+        multiply(q ^ 1, q, false);
+        q ^= 1;
     }
-#pragma unroll
-    for (int x = 0; x < kRowsPerThread; ++x) {
-        const int row = tid + 256 * x;
-        if (row < d)
-#pragma unroll
-            for (int m = 0; m < kRitz; ++m) Q[row * kRitz + m] = q[x][m];
-    }
+    for (int x = tid; x < d * kRitz; x += kSmallThreads) Q[x] = Y[q][x];
+    if (tid == 0) *st_out = st;
 }
 
 // factor[m] for m = 0, 1: the sign that makes the axis' entry of largest magnitude (the first among equals) positive,
-// times std0 / sqrt(lam_1) when std0 > 0.  One thread.
-__global__ void k_pca_orient(const double* __restrict__ Q, int32_t d, const double* __restrict__ lam, float std0, double* __restrict__ factor) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const double scale = std0 > 0.f ? (double)std0 / sqrt(lam[0]) : 1.0;
-    for (int m = 0; m < 2; ++m) {
-        int best = 0;
-        for (int r = 1; r < d; ++r)
-            if (fabs(Q[r * kRitz + m]) > fabs(Q[best * kRitz + m])) best = r;
-        factor[m] = (Q[best * kRitz + m] > 0.0 ? 1.0 : -1.0) * scale;
+// times std0 / sqrt(lam_1) when std0 > 0.  One wavefront per axis.
+__global__ void __launch_bounds__(128) k_pca_orient(const double* __restrict__ Q, int32_t d, const RitzState* __restrict__ st, float std0,
+                                                    double* __restrict__ factor) {
+    const int m = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double best = -1.0, value = 0.0;
+    int at = d;
+    for (int r = lane; r < d; r += 64) {
+        const double v = Q[r * kRitz + m];
+        if (fabs(v) > best) { best = fabs(v); value = v; at = r; }
     }
+    for (int w = 32; w > 0; w >>= 1) {
+        const double ob = __shfl_xor(best, w, 64), ov = __shfl_xor(value, w, 64);
+        const int oa = __shfl_xor(at, w, 64);
+        if (ob > best || (ob == best && oa < at)) { best = ob; value = ov; at = oa; }
+    }
+    if (lane == 0) factor[m] = (value > 0.0 ? 1.0 : -1.0) * (std0 > 0.f ? (double)std0 / sqrt(st->lam[0]) : 1.0);
 }
 
-// theta_i = factor * ((x_i - mean) . axis_1, (x_i - mean) . axis_2): a wavefront per row, kProjectRows rows in turn
-constexpr int kProjectRows = 16;
+// theta_i = factor * ((x_i - mean) . axis_1, (x_i - mean) . axis_2).  LANES lanes share a row (a power of two, enough for
+// one VEC-wide chunk of the row each), 64 / LANES rows side by side in a wavefront, kProjectRows such groups in flight: the
+// loop is a stream of X from memory (512 MB at 128 columns: 0.27 ms with four 4-byte loads in flight per lane).
+constexpr int kProjectRows = 8;
+template <int VEC, int LANES>
 __global__ void __launch_bounds__(256) k_pca_project(const float* __restrict__ X, int64_t n, int32_t d, const double* __restrict__ mean,
                                                      const double* __restrict__ Q, const double* __restrict__ factor,
                                                      float2* __restrict__ theta) {
-    const int lane = threadIdx.x & 63;
-    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const double f0 = factor[0], f1 = factor[1];
-    for (int x = 0; x < kProjectRows; x += 4) {   // four rows at a time: their loads are in flight together
-        const int64_t row0 = w * kProjectRows + x;
-        if (row0 >= n) return;
-        double s0[4] = {0.0, 0.0, 0.0, 0.0}, s1[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int col = lane; col < d; col += 64) {
-            const double m = mean[col], q0 = Q[col * kRitz], q1 = Q[col * kRitz + 1];
-            float v[4];
+    constexpr int kSide = 64 / LANES;                 // rows side by side
+    const int lane = threadIdx.x & 63, part = lane % LANES, side = lane / LANES;
+    const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (kSide * kProjectRows) + side;
+    double s0[kProjectRows], s1[kProjectRows];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = row0 + u < n ? X[(row0 + u) * d + col] : 0.f;
+    for (int u = 0; u < kProjectRows; ++u) { s0[u] = 0.0; s1[u] = 0.0; }
+    for (int col = VEC * part; col < d; col += VEC * LANES) {
+        float v[kProjectRows][VEC];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const double c = (double)v[u] - m;
+        for (int u = 0; u < kProjectRows; ++u) {
+            const float* src = X + min(row0 + (int64_t)u * kSide, n - 1) * d + col;
+            if (VEC == 4) { const float4 t = *(const float4*)src; v[u][0] = t.x; v[u][1 % VEC] = t.y; v[u][2 % VEC] = t.z; v[u][3 % VEC] = t.w; }
+            else v[u][0] = *src;
+        }
+#pragma unroll
+        for (int w = 0; w < VEC; ++w) {
+            const double m = mean[col + w], q0 = Q[(col + w) * kRitz], q1 = Q[(col + w) * kRitz + 1];
+#pragma unroll
+            for (int u = 0; u < kProjectRows; ++u) {
+                const double c = (double)v[u][w] - m;
                 s0[u] = fma(c, q0, s0[u]);
                 s1[u] = fma(c, q1, s1[u]);
             }
         }
+    }
+    const double f0 = factor[0], f1 = factor[1];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            for (int o = 32; o > 0; o >>= 1) {
-                s0[u] += __shfl_xor(s0[u], o, 64);
-                s1[u] += __shfl_xor(s1[u], o, 64);
-            }
-            if (lane == 0 && row0 + u < n) theta[row0 + u] = make_float2((float)(s0[u] * f0), (float)(s1[u] * f1));
+    for (int u = 0; u < kProjectRows; ++u) {
+        for (int o = LANES / 2; o > 0; o >>= 1) {
+            s0[u] += __shfl_xor(s0[u], o, 64);
+            s1[u] += __shfl_xor(s1[u], o, 64);
         }
+        const int64_t row = row0 + (int64_t)u * kSide;
+        if (part == 0 && row < n) theta[row] = make_float2((float)(s0[u] * f0), (float)(s1[u] * f1));
     }
 }
 
