@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "host_util.h"
+#include "knn_filter.h"
 #include "knn_kernels.h"
 #include "metrics_kernels.h"
 #include "nomad.h"
@@ -18,67 +19,103 @@ using namespace nomad_metrics;
 namespace {
 
 
-template <int D4, int L>
-hipError_t launch_filter_dl(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand,
-                            float* tau) {
-    const size_t lds = knn_filter_lds_bytes(D4, L);
-    hipError_t e = hipFuncSetAttribute((const void*)k_knn_filter<D4, L>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_knn_filter<D4, L>), dim3(n_blocks), dim3(64 * knn_filter_waves(D4)), lds, st, P, blocks, list_len, cand, tau);
-    return hipGetLastError();
-}
+// One side of the filter, packed: tiles per group (host and device), the packed rows, and the launch that fills them.
+struct PackedSide {
+    int tile = 32, steps = 1;
+    int32_t groups = 0;
+    uint32_t n_tiles = 0;
+    std::vector<uint32_t> tstart;          // [groups + 1]
+    const uint32_t *d_start = nullptr, *d_tstart = nullptr;
+    uint4* data = nullptr;
+    float* norm = nullptr;
 
-template <int D4>
-hipError_t launch_filter_d(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand,
-                           float* tau) {
-    switch (knn_filter_list_class(list_len)) {
-        case 2: return launch_filter_dl<D4, 2>(st, n_blocks, P, blocks, list_len, cand, tau);
-        case 8: return launch_filter_dl<D4, 8>(st, n_blocks, P, blocks, list_len, cand, tau);
-        case 12: return launch_filter_dl<D4, 12>(st, n_blocks, P, blocks, list_len, cand, tau);
-        default: return launch_filter_dl<D4, 20>(st, n_blocks, P, blocks, list_len, cand, tau);
+    void plan(const std::vector<uint32_t>& start, int32_t d, int32_t list_len) {
+        tile = knn_tile(d, list_len);
+        steps = knn_steps(d, tile);
+        groups = (int32_t)start.size() - 1;
+        tstart.assign(start.size(), 0u);
+        for (int32_t g = 0; g < groups; ++g) tstart[g + 1] = tstart[g] + (start[g + 1] - start[g] + (uint32_t)tile - 1) / (uint32_t)tile;
+        n_tiles = tstart[groups];
     }
-}
-
-// width class of the filter kernel for rows of d values
-inline int width_class(int32_t d) {
-    const int d4 = (d + 3) / 4;
-    return d4 <= 8 ? 8 : d4 <= 16 ? 16 : d4 <= 32 ? 32 : d4 <= 64 ? 64 : d4 <= 96 ? 96 : d4 <= 128 ? 128 : 192;
-}
-
-hipError_t launch_filter(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand,
-                         float* tau) {
-    switch (width_class(P.d)) {
-        case 8: return launch_filter_d<8>(st, n_blocks, P, blocks, list_len, cand, tau);
-        case 16: return launch_filter_d<16>(st, n_blocks, P, blocks, list_len, cand, tau);
-        case 32: return launch_filter_d<32>(st, n_blocks, P, blocks, list_len, cand, tau);
-        case 64: return launch_filter_d<64>(st, n_blocks, P, blocks, list_len, cand, tau);
-        case 96: return launch_filter_d<96>(st, n_blocks, P, blocks, list_len, cand, tau);
-        case 128: return launch_filter_d<128>(st, n_blocks, P, blocks, list_len, cand, tau);
-        default: return launch_filter_d<192>(st, n_blocks, P, blocks, list_len, cand, tau);
+    int alloc(Buffers& buf, bool with_norm) {
+        KTRY(buf.alloc(&data, ((size_t)n_tiles + kMaxStageTiles) * knn_tile_units(steps)));   // a stage may read past the last tile
+        if (with_norm) KTRY(buf.alloc(&norm, ((size_t)n_tiles + kMaxStageTiles) * tile));
+        return NOMAD_OK;
     }
+    void fill(hipStream_t st, const float* X, int32_t d, const int32_t* members, const float* centre, const uint32_t* max_bits,
+              const uint32_t* other_bits, const float* row_norm) {
+        if (n_tiles)
+            hipLaunchKernelGGL(k_knn_pack, dim3(n_tiles), dim3(256), 0, st, X, d, members, d_start, d_tstart, groups, centre, max_bits,
+                               other_bits, row_norm, tile,
+                               steps, data, norm);
+    }
+    KnnPacked view(const uint32_t* max_bits) const { return KnnPacked{data, norm, d_tstart, max_bits}; }
+};
+
+// The filter's work list: `waves` query tiles of one group per workgroup.  Workgroups go to the 8 XCDs in turn, and each XCD
+// has an L2 of its own: the work is poured into eight lists of equal cost, group after group, so that the workgroups that
+// stream a group's candidates share an L2 (a group is cut only where a list is full).  Inside a list the groups with the
+// most candidates come first: a workgroup's time goes with its group's candidates, and what starts last should be short.
+// Entries without work (cluster -1) fill the shorter lists up.
+std::vector<KnnBlock> filter_blocks(const PackedSide& Q, const PackedSide& C, int waves) {
+    constexpr int kXcds = 8;
+    const auto cost_of = [&](int32_t g) { return (double)(C.tstart[g + 1] - C.tstart[g]); };
+    double total = 0.0;
+    for (int32_t g = 0; g < Q.groups; ++g) total += cost_of(g) * (double)((Q.tstart[g + 1] - Q.tstart[g] + (uint32_t)waves - 1) / (uint32_t)waves);
+    std::vector<KnnBlock> lists[kXcds];
+    double done = 0.0;
+    for (int32_t g = 0; g < Q.groups; ++g)
+        for (uint32_t t = 0; t < Q.tstart[g + 1] - Q.tstart[g]; t += (uint32_t)waves) {
+            const int x = std::min(kXcds - 1, (int)(total > 0.0 ? done / total * kXcds : 0.0));
+            lists[x].push_back(KnnBlock{g, (int32_t)t});
+            done += cost_of(g);
+        }
+    size_t longest = 0;
+    for (auto& l : lists) {
+        std::stable_sort(l.begin(), l.end(), [&](const KnnBlock& a, const KnnBlock& b) { return cost_of(a.cluster) > cost_of(b.cluster); });
+        longest = std::max(longest, l.size());
+    }
+    std::vector<KnnBlock> blocks(longest * kXcds, KnnBlock{-1, 0});
+    for (int x = 0; x < kXcds; ++x)
+        for (size_t i = 0; i < lists[x].size(); ++i) blocks[i * kXcds + (size_t)x] = lists[x][i];
+    return blocks;
 }
+
+constexpr uint32_t kLoopGrid = 512;   // workgroups of the kernels whose work list is counted on the device
 
 // The k nearest candidates of every query inside its group (filter, refinement, exact fallback).  `cand` [n_q * (k + kPad)],
-// `tau` [n_q], `flagged` [n_q], `n_flagged` [1] are work space; blocks: the filter's work list (n_blocks entries).
-int nearest_in_groups(hipStream_t st, const KnnSets& P, const KnnBlock* blocks, uint32_t n_blocks, int32_t k, int32_t* cand, float* tau,
-                      int32_t* flagged, uint32_t* n_flagged, int32_t* out, uint32_t* flagged_count) {
+// `tau` [n_q], `flagged` [n_q], `n_flagged` [1] are work space.
+int nearest_in_groups(hipStream_t st, const KnnSets& P, const KnnBlock* blocks, uint32_t n_blocks, int waves, int32_t k, int32_t* cand, float* tau,
+                      int32_t* flagged, uint32_t* n_flagged, int32_t* out) {
     const int32_t list_len = k + kPad;
-    KTRY(hipMemsetAsync(cand, 0xFF, sizeof(int32_t) * (size_t)P.n_q * list_len, st));   // every slot "no candidate" until the filter fills it
     KTRY(hipMemsetAsync(n_flagged, 0, sizeof(uint32_t), st));
-    KTRY(launch_filter(st, n_blocks, P, blocks, list_len, cand, tau));
+    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, list_len, cand, tau, KnnAssign{nullptr, nullptr, nullptr}));
     if (list_len <= 16)
         hipLaunchKernelGGL(k_knn_refine<16>, dim3(blocks_of(P.n_q, 16)), dim3(256), 0, st, P, cand, tau, k, list_len, out, flagged, n_flagged);
     else if (list_len <= 32)
         hipLaunchKernelGGL(k_knn_refine<32>, dim3(blocks_of(P.n_q, 8)), dim3(256), 0, st, P, cand, tau, k, list_len, out, flagged, n_flagged);
     else
         hipLaunchKernelGGL(k_knn_refine<64>, dim3(blocks_of(P.n_q, 4)), dim3(256), 0, st, P, cand, tau, k, list_len, out, flagged, n_flagged);
-    uint32_t hflag = 0;
-    KTRY(hipMemcpyAsync(&hflag, n_flagged, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    KTRY(hipStreamSynchronize(st));
-    if (hflag && k <= 16) hipLaunchKernelGGL(k_knn_exact<16>, dim3(hflag), dim3(256), 0, st, P, flagged, k, out);
-    else if (hflag) hipLaunchKernelGGL(k_knn_exact<kMaxK>, dim3(hflag), dim3(256), 0, st, P, flagged, k, out);
+    const dim3 grid((uint32_t)std::min<int64_t>(P.n_q, kLoopGrid));
+    if (k <= 16) hipLaunchKernelGGL((k_knn_exact<16, 1024>), grid, dim3(1024), 0, st, P, flagged, (const uint32_t*)n_flagged, k, out);
+    else hipLaunchKernelGGL((k_knn_exact<kMaxK, 512>), grid, dim3(512), 0, st, P, flagged, (const uint32_t*)n_flagged, k, out);
     KTRY(hipGetLastError());
-    *flagged_count = hflag;
+    return NOMAD_OK;
+}
+
+// The nearest candidate of every query (one group).  Work space: cand [n_q * 128 / tile], tau, todo, flagged [n_q],
+// counters [2] (queries the filter left open, queries for the exact path).
+int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* blocks, uint32_t n_blocks, int waves, int32_t* cand, float* tau,
+                int32_t* todo, int32_t* flagged, uint32_t* counters, int32_t* out) {
+    KTRY(hipMemsetAsync(counters, 0, 2 * sizeof(uint32_t), st));
+    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, tau, KnnAssign{out, todo, counters}));
+    const int32_t width = 128 / tile;
+    const dim3 grid((uint32_t)std::min<int64_t>((P.n_q * width + 255) / 256, kLoopGrid));
+    hipLaunchKernelGGL(k_assign_refine, grid, dim3(256), 0, st, P, (const int32_t*)todo, (const uint32_t*)counters, (const int32_t*)cand, (const float*)tau,
+                       width, out, flagged, counters + 1);
+    hipLaunchKernelGGL((k_knn_exact<1, 256>), dim3((uint32_t)std::min<int64_t>(P.n_q, kLoopGrid)), dim3(256), 0, st, P, (const int32_t*)flagged,
+                       (const uint32_t*)(counters + 1), 1, out);
+    KTRY(hipGetLastError());
     return NOMAD_OK;
 }
 
@@ -149,7 +186,7 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     if (hipGetDeviceCount(&ndev) != hipSuccess || device >= ndev) return NOMAD_E_HIP;
     KTRY(hipSetDevice(device));
     hipStream_t st = (hipStream_t)stream;
-    Buffers buf;
+    Buffers buf(st);
     const int32_t R = n_clusters;
     const int32_t list_len = k + kPad;
 
@@ -169,60 +206,58 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     }
 
     // members grouped by cluster
-    uint32_t *counts = nullptr, *start = nullptr, *cursor = nullptr, *max_norm = nullptr, *n_flagged = nullptr;
+    uint32_t *counts = nullptr, *cursor = nullptr, *max_norm = nullptr, *n_flagged = nullptr;
     int32_t *members = nullptr, *cand = nullptr, *flagged = nullptr;
     float *norm = nullptr, *tau = nullptr, *centre = nullptr;
     int* bad = nullptr;
-    KTRY(buf.alloc(&counts, (size_t)R));
-    KTRY(buf.alloc(&start, (size_t)R + 1));
-    KTRY(buf.alloc(&cursor, (size_t)R));
-    KTRY(buf.alloc(&max_norm, (size_t)R));
-    KTRY(buf.alloc(&n_flagged, 1));
-    KTRY(buf.alloc(&bad, 1));
+    // counters that start at zero: counts, cursor, max_norm, centre, bad, n_flagged
+    uint8_t* zeroed = nullptr;
+    const size_t zero_bytes = sizeof(uint32_t) * ((size_t)3 * R + (size_t)R * d + 2);
+    KTRY(buf.alloc(&zeroed, zero_bytes));
+    KTRY(hipMemsetAsync(zeroed, 0, zero_bytes, st));
+    counts = (uint32_t*)zeroed; cursor = counts + R; max_norm = cursor + R; bad = (int*)(max_norm + R); n_flagged = (uint32_t*)(bad + 1);
+    centre = (float*)(n_flagged + 1);
     KTRY(buf.alloc(&members, (size_t)n));
     KTRY(buf.alloc(&norm, (size_t)n));
     KTRY(buf.alloc(&tau, (size_t)n));
-    KTRY(buf.alloc(&centre, (size_t)R * d));
-    KTRY(hipMemsetAsync(centre, 0, sizeof(float) * (size_t)R * d, st));
     KTRY(buf.alloc(&cand, (size_t)n * list_len));
     KTRY(buf.alloc(&flagged, (size_t)n));
-    KTRY(hipMemsetAsync(counts, 0, sizeof(uint32_t) * (size_t)R, st));
-    KTRY(hipMemsetAsync(cursor, 0, sizeof(uint32_t) * (size_t)R, st));
-    KTRY(hipMemsetAsync(max_norm, 0, sizeof(uint32_t) * (size_t)R, st));
-    KTRY(hipMemsetAsync(bad, 0, sizeof(int), st));
     hipLaunchKernelGGL(k_knn_count, dim3(blocks_of(n, kCountSpan)), dim3(256), 0, st, dC, n, R, counts, bad);
-    std::vector<uint32_t> hcounts(R), hstart((size_t)R + 1, 0);
-    int hbad = 0;
-    KTRY(hipMemcpyAsync(hcounts.data(), counts, sizeof(uint32_t) * (size_t)R, hipMemcpyDeviceToHost, st));
-    KTRY(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st));
+    std::vector<uint32_t> hcounts((size_t)3 * R + 1), hstart((size_t)R + 1, 0);   // counts, two arrays of no interest, bad
+    KTRY(hipMemcpyAsync(hcounts.data(), counts, sizeof(uint32_t) * hcounts.size(), hipMemcpyDeviceToHost, st));
     KTRY(hipStreamSynchronize(st));
-    if (hbad) return NOMAD_E_BAD_GRAPH;   // a cluster id outside 0..n_clusters-1
-    // the width class of the filter kernel decides how many queries a workgroup takes
-    const uint32_t block_queries = (uint32_t)knn_filter_block_queries(width_class(d));
-    std::vector<KnnBlock> hblocks, hslabs;
+    if (hcounts[(size_t)3 * R]) return NOMAD_E_BAD_GRAPH;   // a cluster id outside 0..n_clusters-1
+    std::vector<KnnBlock> hslabs;
     for (int32_t r = 0; r < R; ++r) {
         hstart[r + 1] = hstart[r] + hcounts[r];
-        for (uint32_t q0 = 0; q0 < hcounts[r]; q0 += block_queries) hblocks.push_back(KnnBlock{r, (int32_t)q0});
         for (uint32_t q0 = 0; q0 < hcounts[r]; q0 += kCentroidRows) hslabs.push_back(KnnBlock{r, (int32_t)q0});
     }
-    KnnBlock *blocks = nullptr, *slabs = nullptr;
-    KTRY(buf.alloc(&blocks, hblocks.size()));
-    KTRY(buf.alloc(&slabs, hslabs.size()));
-    KTRY(hipMemcpyAsync(slabs, hslabs.data(), sizeof(KnnBlock) * hslabs.size(), hipMemcpyHostToDevice, st));
-    KTRY(hipMemcpyAsync(start, hstart.data(), sizeof(uint32_t) * ((size_t)R + 1), hipMemcpyHostToDevice, st));
-    KTRY(hipMemcpyAsync(blocks, hblocks.data(), sizeof(KnnBlock) * hblocks.size(), hipMemcpyHostToDevice, st));
+    PackedSide side;
+    side.plan(hstart, d, list_len);
+    const int waves = knn_filter_waves(side.tile, side.n_tiles);
+    const std::vector<KnnBlock> hblocks = filter_blocks(side, side, waves);
+    HostArrays up;
+    const size_t at_start = up.add(hstart), at_tstart = up.add(side.tstart), at_blocks = up.add(hblocks), at_slabs = up.add(hslabs);
+    KTRY(up.upload(buf, st));
+    const uint32_t* start = up.at<uint32_t>(at_start);
+    const KnnBlock *blocks = up.at<KnnBlock>(at_blocks), *slabs = up.at<KnnBlock>(at_slabs);
+    side.d_start = start;
+    side.d_tstart = up.at<uint32_t>(at_tstart);
+    if (int rc = side.alloc(buf, true)) return rc;
     hipLaunchKernelGGL(k_knn_group, dim3(blocks_of(n, kGroupSpan)), dim3(256), 0, st, dC, n, R, start, cursor, members);
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, members, start, slabs, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of((int64_t)R * d, 256)), dim3(256), 0, st, centre, start, R, d);
     hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, dX, n, d, dC, centre, norm, max_norm);
+    side.fill(st, dX, d, members, centre, max_norm, max_norm, norm);
 
     // filter on the matrix cores, float64 refinement, exact fallback
     KnnSets P{};
     P.XQ = dX; P.XC = dX; P.qmembers = members; P.cmembers = members; P.qstart = start; P.cstart = start;
-    P.cnorm = norm; P.centre = centre; P.group_of_q = dC; P.max_norm_bits = max_norm; P.n_q = n; P.n_c = n; P.d = d; P.same_set = 1;
-    uint32_t hflag = 0;
-    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), k, cand, tau, flagged, n_flagged, dOut, &hflag);
+    P.Q = side.view(max_norm); P.C = P.Q; P.centre = centre; P.group_of_q = dC; P.n_q = n; P.n_c = n; P.d = d; P.same_set = 1;
+    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, tau, flagged, n_flagged, dOut);
     if (rc) return rc;
+    uint32_t hflag = 0;
+    KTRY(hipMemcpyAsync(&hflag, n_flagged, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     if (mem == NOMAD_HOST) KTRY(hipMemcpyAsync(out_nbrs, dOut, sizeof(int32_t) * (size_t)n * k, hipMemcpyDeviceToHost, st));
     KTRY(hipStreamSynchronize(st));
     if (stats) {
@@ -243,9 +278,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     if (hipGetDeviceCount(&ndev) != hipSuccess || device >= ndev) return NOMAD_E_HIP;
     KTRY(hipSetDevice(device));
     hipStream_t st = (hipStream_t)stream;
-    Buffers buf;
-    const int32_t k = 1, list_len = k + kPad;
-
+    Buffers buf(st);
     const float* dX = X;
     float* dC = centroids;
     int32_t* dLab = labels;
@@ -260,34 +293,40 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
         dX = x; dC = c; dLab = l;
     }
     // work space
-    uint32_t *qstart = nullptr, *cstart = nullptr, *max_pts = nullptr, *max_norm = nullptr, *n_flagged = nullptr;
-    int32_t *new_lab = nullptr, *cand = nullptr, *flagged = nullptr;
+    uint32_t *max_pts = nullptr, *max_cen = nullptr, *counters = nullptr;
+    int32_t *new_lab = nullptr, *cand = nullptr, *todo = nullptr, *flagged = nullptr;
     float *cnorm = nullptr, *tau = nullptr, *centre = nullptr, *c_used = nullptr;
     unsigned long long* changed = nullptr;
     double* inertia = nullptr;
-    KnnBlock *blocks = nullptr, *slabs = nullptr;
-    KTRY(buf.alloc(&qstart, 2)); KTRY(buf.alloc(&cstart, 2));
-    KTRY(buf.alloc(&max_pts, 1)); KTRY(buf.alloc(&max_norm, 1)); KTRY(buf.alloc(&n_flagged, 1));
-    KTRY(buf.alloc(&new_lab, (size_t)n)); KTRY(buf.alloc(&cand, (size_t)n * list_len)); KTRY(buf.alloc(&flagged, (size_t)n));
+    const std::vector<uint32_t> hq = {0u, (uint32_t)n}, hc = {0u, (uint32_t)K};
+    PackedSide points, cents;
+    points.plan(hq, d, 1);
+    cents.plan(hc, d, 1);
+    KTRY(buf.alloc(&max_pts, 1)); KTRY(buf.alloc(&max_cen, 1)); KTRY(buf.alloc(&counters, 2));
+    KTRY(buf.alloc(&new_lab, (size_t)n)); KTRY(buf.alloc(&cand, (size_t)n * (128 / points.tile))); KTRY(buf.alloc(&todo, (size_t)n)); KTRY(buf.alloc(&flagged, (size_t)n));
     KTRY(buf.alloc(&cnorm, (size_t)K)); KTRY(buf.alloc(&tau, (size_t)n)); KTRY(buf.alloc(&centre, (size_t)d)); KTRY(buf.alloc(&c_used, (size_t)K * d));
     KTRY(buf.alloc(&changed, 1)); KTRY(buf.alloc(&inertia, 1));
-    const uint32_t hq[2] = {0u, (uint32_t)n}, hc[2] = {0u, (uint32_t)K};
-    KTRY(hipMemcpyAsync(qstart, hq, sizeof(hq), hipMemcpyHostToDevice, st));
-    KTRY(hipMemcpyAsync(cstart, hc, sizeof(hc), hipMemcpyHostToDevice, st));
-    const uint32_t block_queries = (uint32_t)knn_filter_block_queries(width_class(d));
-    std::vector<KnnBlock> hblocks, hslabs;
-    for (int64_t q0 = 0; q0 < n; q0 += block_queries) hblocks.push_back(KnnBlock{0, (int32_t)q0});
+    const int waves = knn_filter_waves(points.tile, points.n_tiles);
+    const std::vector<KnnBlock> hblocks = filter_blocks(points, cents, waves);
+    std::vector<KnnBlock> hslabs;
     for (int64_t q0 = 0; q0 < n; q0 += kCentroidRows) hslabs.push_back(KnnBlock{0, (int32_t)q0});
-    KTRY(buf.alloc(&blocks, hblocks.size()));
-    KTRY(buf.alloc(&slabs, hslabs.size()));
-    KTRY(hipMemcpyAsync(blocks, hblocks.data(), sizeof(KnnBlock) * hblocks.size(), hipMemcpyHostToDevice, st));
-    KTRY(hipMemcpyAsync(slabs, hslabs.data(), sizeof(KnnBlock) * hslabs.size(), hipMemcpyHostToDevice, st));
+    HostArrays up;
+    const size_t at_q = up.add(hq), at_c = up.add(hc), at_qt = up.add(points.tstart), at_ct = up.add(cents.tstart), at_blocks = up.add(hblocks),
+                 at_slabs = up.add(hslabs);
+    KTRY(up.upload(buf, st));
+    const uint32_t *qstart = up.at<uint32_t>(at_q), *cstart = up.at<uint32_t>(at_c);
+    const KnnBlock *blocks = up.at<KnnBlock>(at_blocks), *slabs = up.at<KnnBlock>(at_slabs);
+    points.d_start = qstart; points.d_tstart = up.at<uint32_t>(at_qt);
+    cents.d_start = cstart; cents.d_tstart = up.at<uint32_t>(at_ct);
+    if (int rc = points.alloc(buf, false)) return rc;
+    if (int rc = cents.alloc(buf, true)) return rc;
     // both sides are centred on the mean of the points; the largest centred |x|^2 of the points, once
     KTRY(hipMemsetAsync(centre, 0, sizeof(float) * (size_t)d, st));
     KTRY(hipMemsetAsync(max_pts, 0, sizeof(uint32_t), st));
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, (const int32_t*)nullptr, qstart, slabs, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(d, 256)), dim3(256), 0, st, centre, qstart, 1, d);
     hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, dX, n, d, (const int32_t*)nullptr, centre, (float*)nullptr, max_pts);
+    points.fill(st, dX, d, nullptr, centre, max_pts, nullptr, nullptr);
     MeanStep m_step;
     {
         int rc = m_step.init(buf, st, n, K);
@@ -296,19 +335,16 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
 
     KnnSets P{};
     P.XQ = dX; P.XC = dC; P.qmembers = nullptr; P.cmembers = nullptr; P.qstart = qstart; P.cstart = cstart;
-    P.cnorm = cnorm; P.centre = centre; P.group_of_q = nullptr; P.max_norm_bits = max_norm; P.n_q = n; P.n_c = K; P.d = d; P.same_set = 0;
-    float* key2 = nullptr;   // the two smallest filter keys of every point: a clear winner skips the float64 refinement
-    KTRY(buf.alloc(&key2, (size_t)2 * n));
-    P.key2 = key2;
+    P.Q = points.view(max_pts); P.C = cents.view(max_cen); P.centre = centre; P.group_of_q = nullptr; P.n_q = n; P.n_c = K; P.d = d; P.same_set = 0;
     int32_t it = 0;
     bool have_labels = false;
     while (it < max_iters) {
         // E step: the nearest centroid of every point, exactly
-        KTRY(hipMemcpyAsync(max_norm, max_pts, sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+        KTRY(hipMemsetAsync(max_cen, 0, sizeof(uint32_t), st));
         hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(K, kNormRows)), dim3(256), 0, st, (const float*)dC, (int64_t)K, d, (const int32_t*)nullptr, centre, cnorm,
-                           max_norm);
-        uint32_t hflag = 0;
-        int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), k, cand, tau, flagged, n_flagged, new_lab, &hflag);
+                           max_cen);
+        cents.fill(st, dC, d, nullptr, centre, max_cen, max_pts, cnorm);
+        int rc = nearest_one(st, P, points.tile, blocks, (uint32_t)hblocks.size(), waves, cand, tau, todo, flagged, counters, new_lab);
         if (rc) return rc;
         ++it;
         KTRY(hipMemcpyAsync(c_used, dC, sizeof(float) * (size_t)K * d, hipMemcpyDeviceToDevice, st));
@@ -353,7 +389,7 @@ extern "C" int nomad_kmeans_lsh_init(const float* X, int64_t n, int32_t d, int32
     if (hipGetDeviceCount(&ndev) != hipSuccess || device >= ndev) return NOMAD_E_HIP;
     KTRY(hipSetDevice(device));
     hipStream_t st = (hipStream_t)stream;
-    Buffers buf;
+    Buffers buf(st);
     const float *dX = X, *dP = planes;
     const int32_t* dA = anchors;
     float* dC = centroids_out;
@@ -421,42 +457,51 @@ namespace {
 int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t n, int32_t d, const int32_t* dQ, int64_t m, int32_t k,
                           int32_t* out) {
     const int32_t list_len = k + kPad;
-    const uint32_t block_queries = (uint32_t)knn_filter_block_queries(width_class(d));
+    const int64_t block_queries = 8 * knn_tile(d, list_len);
     const int64_t base_blocks = (m + block_queries - 1) / block_queries;
-    int64_t G = std::max<int64_t>(1, 1024 / base_blocks);
-    G = std::min<int64_t>(G, 256 / k);                       // the merge ranks slices * k candidates in one workgroup
-    G = std::min<int64_t>(G, std::max<int64_t>(1, n / 4096));   // slices of at least 4,096 candidates
+    // as many slices as fill the compute units' last round best: rounds of 256 workgroups times a slice's length
+    const int64_t most = std::min<int64_t>(256 / k, std::max<int64_t>(1, n / 4096));   // the merge ranks slices * k candidates in one
+    int64_t G = 1;                                                                       // workgroup; slices of at least 4,096 candidates
+    const auto rounds_cost = [&](int64_t g) { return (double)((base_blocks * g + 255) / 256) * (double)((n + g - 1) / g); };
+    for (int64_t g = 2; g <= most; ++g)
+        if (rounds_cost(g) < 0.98 * rounds_cost(G)) G = g;
     const int64_t slice = (n + G - 1) / G, mq = m * G;
     if (mq >= ((int64_t)1 << 31) - 256) return NOMAD_E_TOO_LARGE;
-    uint32_t *qstart = nullptr, *cstart = nullptr, *max_norm = nullptr, *n_flagged = nullptr;
+    uint32_t *max_q = nullptr, *max_c = nullptr, *n_flagged = nullptr;
     int32_t *cand = nullptr, *flagged = nullptr, *self = nullptr, *group_of_q = nullptr, *slice_of = nullptr, *part = nullptr;
     float *cnorm = nullptr, *tau = nullptr, *centre = nullptr, *AQ = nullptr;
     int* bad = nullptr;
-    KnnBlock *blocks = nullptr, *slabs = nullptr;
-    KTRY(buf.alloc(&qstart, (size_t)G + 1)); KTRY(buf.alloc(&cstart, (size_t)G + 1)); KTRY(buf.alloc(&max_norm, (size_t)G));
-    KTRY(buf.alloc(&n_flagged, 1)); KTRY(buf.alloc(&bad, 1));
+    uint8_t* zeroed = nullptr;   // max_q, max_c, bad, n_flagged, centre
+    const size_t zero_bytes = sizeof(uint32_t) * ((size_t)2 * G + 2 + (size_t)G * d);
+    KTRY(buf.alloc(&zeroed, zero_bytes));
+    KTRY(hipMemsetAsync(zeroed, 0, zero_bytes, st));
+    max_q = (uint32_t*)zeroed; max_c = max_q + G; bad = (int*)(max_c + G); n_flagged = (uint32_t*)(bad + 1); centre = (float*)(n_flagged + 1);
     KTRY(buf.alloc(&cand, (size_t)mq * list_len)); KTRY(buf.alloc(&flagged, (size_t)mq)); KTRY(buf.alloc(&tau, (size_t)mq));
-    KTRY(buf.alloc(&cnorm, (size_t)n)); KTRY(buf.alloc(&centre, (size_t)G * d)); KTRY(buf.alloc(&AQ, (size_t)mq * d));
+    KTRY(buf.alloc(&cnorm, (size_t)n)); KTRY(buf.alloc(&AQ, (size_t)mq * d));
     KTRY(buf.alloc(&self, (size_t)mq));
     std::vector<uint32_t> hq((size_t)G + 1), hc((size_t)G + 1);
-    std::vector<KnnBlock> hblocks, hslabs;
+    std::vector<KnnBlock> hslabs;
     for (int64_t g = 0; g <= G; ++g) {
         hq[g] = (uint32_t)(g * m);
         hc[g] = (uint32_t)std::min<int64_t>(n, g * slice);
     }
-    for (int64_t g = 0; g < G; ++g) {
-        for (int64_t q0 = 0; q0 < m; q0 += block_queries) hblocks.push_back(KnnBlock{(int32_t)g, (int32_t)q0});
+    for (int64_t g = 0; g < G; ++g)
         for (int64_t q0 = 0; q0 < (int64_t)(hc[g + 1] - hc[g]); q0 += kCentroidRows) hslabs.push_back(KnnBlock{(int32_t)g, (int32_t)q0});
-    }
-    KTRY(hipMemcpyAsync(qstart, hq.data(), sizeof(uint32_t) * hq.size(), hipMemcpyHostToDevice, st));
-    KTRY(hipMemcpyAsync(cstart, hc.data(), sizeof(uint32_t) * hc.size(), hipMemcpyHostToDevice, st));
-    KTRY(buf.alloc(&blocks, hblocks.size()));
-    KTRY(buf.alloc(&slabs, hslabs.size()));
-    KTRY(hipMemcpyAsync(blocks, hblocks.data(), sizeof(KnnBlock) * hblocks.size(), hipMemcpyHostToDevice, st));
-    KTRY(hipMemcpyAsync(slabs, hslabs.data(), sizeof(KnnBlock) * hslabs.size(), hipMemcpyHostToDevice, st));
-    KTRY(hipMemsetAsync(centre, 0, sizeof(float) * (size_t)G * d, st));
-    KTRY(hipMemsetAsync(max_norm, 0, sizeof(uint32_t) * (size_t)G, st));
-    KTRY(hipMemsetAsync(bad, 0, sizeof(int), st));
+    PackedSide qside, cside;
+    qside.plan(hq, d, list_len);
+    cside.plan(hc, d, list_len);
+    const int waves = knn_filter_waves(qside.tile, qside.n_tiles);
+    const std::vector<KnnBlock> hblocks = filter_blocks(qside, cside, waves);
+    HostArrays up;
+    const size_t at_q = up.add(hq), at_c = up.add(hc), at_qt = up.add(qside.tstart), at_ct = up.add(cside.tstart), at_blocks = up.add(hblocks),
+                 at_slabs = up.add(hslabs);
+    KTRY(up.upload(buf, st));
+    const uint32_t *qstart = up.at<uint32_t>(at_q), *cstart = up.at<uint32_t>(at_c);
+    const KnnBlock *blocks = up.at<KnnBlock>(at_blocks), *slabs = up.at<KnnBlock>(at_slabs);
+    qside.d_start = qstart; qside.d_tstart = up.at<uint32_t>(at_qt);
+    cside.d_start = cstart; cside.d_tstart = up.at<uint32_t>(at_ct);
+    if (int rc = qside.alloc(buf, false)) return rc;
+    if (int rc = cside.alloc(buf, true)) return rc;
     if (G > 1) {
         KTRY(buf.alloc(&group_of_q, (size_t)mq));
         KTRY(buf.alloc(&slice_of, (size_t)n));
@@ -472,20 +517,48 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     if (hbad) return NOMAD_E_INVALID_ARG;   // a query outside 0..n-1
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, A, d, (const int32_t*)nullptr, cstart, slabs, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(G * d, 256)), dim3(256), 0, st, centre, cstart, (int32_t)G, d);
-    hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, A, n, d, (const int32_t*)slice_of, centre, cnorm, max_norm);
+    hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, A, n, d, (const int32_t*)slice_of, centre, cnorm, max_c);
     hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(mq, kNormRows)), dim3(256), 0, st, (const float*)AQ, mq, d, (const int32_t*)group_of_q, centre,
-                       (float*)nullptr, max_norm);
+                       (float*)nullptr, max_q);
+    cside.fill(st, A, d, nullptr, centre, max_c, max_q, cnorm);
+    qside.fill(st, AQ, d, nullptr, centre, max_q, nullptr, nullptr);
     KnnSets P{};
     P.XQ = AQ; P.XC = A; P.qmembers = nullptr; P.cmembers = nullptr; P.qstart = qstart; P.cstart = cstart;
-    P.cnorm = cnorm; P.centre = centre; P.group_of_q = group_of_q; P.max_norm_bits = max_norm; P.n_q = mq; P.n_c = n; P.d = d; P.same_set = 0;
+    P.Q = qside.view(max_q); P.C = cside.view(max_c); P.centre = centre; P.group_of_q = group_of_q; P.n_q = mq; P.n_c = n; P.d = d; P.same_set = 0;
     P.self_row = self;
-    uint32_t hflag = 0;
-    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), k, cand, tau, flagged, n_flagged, G > 1 ? part : out, &hflag);
+    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, tau, flagged, n_flagged, G > 1 ? part : out);
     if (rc) return rc;
     if (G > 1) {
         hipLaunchKernelGGL(k_merge_slices, dim3((uint32_t)m), dim3(256), 0, st, (const float*)AQ, A, d, (const int32_t*)part, (int32_t)G, m, k, out);
         KTRY(hipGetLastError());
     }
+    return NOMAD_OK;
+}
+
+// The same for rows of two columns and a few thousand points or more: a grid of cells (metrics_kernels.h).
+constexpr int64_t kPlanePoints = 1024;
+int neighbours_in_plane(hipStream_t st, Buffers& buf, const float* A, int64_t n, const int32_t* dQ, int64_t m, int32_t k, int32_t* out,
+                        unsigned long long* bad) {
+    const int32_t G = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kMaxGrid, (int64_t)std::sqrt((double)n / kCellPoints)));
+    const uint64_t cells = (uint64_t)G * G;
+    const uint32_t n_tiles = (uint32_t)((cells + kScanTile - 1) / kScanTile);
+    uint32_t *box = nullptr, *counts = nullptr, *tile_total = nullptr, *rank = nullptr;
+    float2* pos = nullptr;
+    int32_t* id = nullptr;
+    KTRY(buf.alloc(&box, 4)); KTRY(buf.alloc(&counts, (size_t)cells)); KTRY(buf.alloc(&tile_total, (size_t)n_tiles));
+    KTRY(buf.alloc(&rank, (size_t)n)); KTRY(buf.alloc(&pos, (size_t)n)); KTRY(buf.alloc(&id, (size_t)n));
+    KTRY(hipMemsetAsync(counts, 0, sizeof(uint32_t) * (size_t)cells, st));
+    const float2* Y = (const float2*)A;
+    hipLaunchKernelGGL(k_plane_box_clear, dim3(1), dim3(64), 0, st, box);
+    hipLaunchKernelGGL(k_plane_box, dim3((uint32_t)std::min<int64_t>(512, blocks_of(n, 256))), dim3(256), 0, st, Y, n, box);
+    hipLaunchKernelGGL(k_plane_count, dim3(blocks_of(n, 256)), dim3(256), 0, st, Y, n, (const uint32_t*)box, G, counts, rank);
+    hipLaunchKernelGGL(k_sort_scan_tiles, dim3(n_tiles), dim3(256), 0, st, counts, cells, tile_total);
+    hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, st, tile_total, (uint64_t)n_tiles);
+    hipLaunchKernelGGL(k_plane_place, dim3(blocks_of(n, 256)), dim3(256), 0, st, Y, n, (const uint32_t*)box, G, (const uint32_t*)counts,
+                       (const uint32_t*)tile_total, (const uint32_t*)rank, pos, id);
+    hipLaunchKernelGGL(k_plane_neighbours, dim3(blocks_of(m, 4)), dim3(256), 0, st, Y, n, dQ, m, k, (const uint32_t*)box, G, (const uint32_t*)counts,
+                       (const uint32_t*)tile_total, (const float2*)pos, (const int32_t*)id, out, bad);
+    KTRY(hipGetLastError());
     return NOMAD_OK;
 }
 
@@ -506,7 +579,7 @@ extern "C" int nomad_neighbourhood_preservation(const float* X, int64_t n, int32
     const int64_t m = queries ? n_queries : n;
     const float *dX = X, *dY = Y;
     const int32_t* dQ = queries;
-    Buffers io;
+    Buffers io(st);
     if (mem == NOMAD_HOST) {
         float *x = nullptr, *y = nullptr;
         KTRY(io.alloc(&x, (size_t)n * d));
@@ -525,26 +598,21 @@ extern "C" int nomad_neighbourhood_preservation(const float* X, int64_t n, int32
     unsigned long long* hits = nullptr;
     KTRY(io.alloc(&high, (size_t)m * k));
     KTRY(io.alloc(&low, (size_t)m * k));
-    KTRY(io.alloc(&hits, 1));
-    {
-        Buffers work;   // released before the second space takes its own
-        int rc = neighbours_of_queries(st, work, dX, n, d, dQ, m, k, high);
-        if (rc) return rc;
-        KTRY(hipStreamSynchronize(st));
-    }
-    {
-        Buffers work;
-        int rc = neighbours_of_queries(st, work, dY, n, d_low, dQ, m, k, low);
-        if (rc) return rc;
-        KTRY(hipStreamSynchronize(st));
-    }
-    unsigned long long hhits = 0;
-    KTRY(hipMemsetAsync(hits, 0, sizeof(unsigned long long), st));
+    KTRY(io.alloc(&hits, 2));   // the count, and whether a query lies outside 0..n-1
+    KTRY(hipMemsetAsync(hits, 0, 2 * sizeof(unsigned long long), st));
+    const auto neighbours = [&](const float* A, int32_t dim, int32_t* to) {
+        Buffers work(st);   // given back before the second space takes its own
+        return dim == 2 && n >= kPlanePoints ? neighbours_in_plane(st, work, A, n, dQ, m, k, to, hits + 1) : neighbours_of_queries(st, work, A, n, dim, dQ, m, k, to);
+    };
+    if (int rc = neighbours(dX, d, high)) return rc;
+    if (int rc = neighbours(dY, d_low, low)) return rc;
+    unsigned long long hhits[2] = {0, 0};
     hipLaunchKernelGGL(k_overlap, dim3(blocks_of(m, 256)), dim3(256), 0, st, (const int32_t*)high, (const int32_t*)low, k, m, hits);
-    KTRY(hipMemcpyAsync(&hhits, hits, sizeof(hhits), hipMemcpyDeviceToHost, st));
+    KTRY(hipMemcpyAsync(hhits, hits, sizeof(hhits), hipMemcpyDeviceToHost, st));
     KTRY(hipGetLastError());
     KTRY(hipStreamSynchronize(st));
-    *hits_out = (int64_t)hhits;
+    if (hhits[1]) return NOMAD_E_INVALID_ARG;
+    *hits_out = (int64_t)hhits[0];
     return NOMAD_OK;
 }
 
@@ -609,7 +677,7 @@ extern "C" int nomad_random_triplet_accuracy(const float* X, int64_t n, int32_t 
     KTRY(hipSetDevice(device));
     hipStream_t st = (hipStream_t)stream;
     const float *dX = X, *dY = Y;
-    Buffers buf;
+    Buffers buf(st);
     if (mem == NOMAD_HOST) {
         float *x = nullptr, *y = nullptr;
         KTRY(buf.alloc(&x, (size_t)n * d));

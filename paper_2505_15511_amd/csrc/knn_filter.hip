@@ -1,0 +1,87 @@
+// libnomad: the instances of the nearest-neighbour filter kernel and their launch (a source of its own: they are most of the
+// index's compile time).
+#include "knn_filter.h"
+
+namespace {
+
+template <int TILE, int KS, int L, int WAVES>
+hipError_t launch(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand, float* tau,
+                  const KnnAssign& assign) {
+    constexpr size_t lds = knn_filter_lds_bytes(TILE, KS, L, WAVES);
+    static_assert(lds <= 160 * 1024, "");
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void*)k_knn_filter<TILE, KS, L, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_knn_filter<TILE, KS, L, WAVES>), dim3(n_blocks), dim3(64 * WAVES), lds, st, P, blocks, list_len, cand, tau, assign);
+    return hipGetLastError();
+}
+
+// list classes: 0 = one neighbour, 1 = short lists, 2 = long ones
+template <int TILE, int KS, int L>
+hipError_t launch_waves(hipStream_t st, uint32_t n_blocks, int waves, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand,
+                        float* tau, const KnnAssign& assign) {
+    if (waves == 8) return launch<TILE, KS, L, 8>(st, n_blocks, P, blocks, list_len, cand, tau, assign);
+    return launch<TILE, KS, L, TILE == 32 ? 2 : 4>(st, n_blocks, P, blocks, list_len, cand, tau, assign);
+}
+
+}  // namespace
+
+#define NOMAD_ARGS st, n_blocks, waves, P, blocks, list_len, cand, tau, assign
+hipError_t launch_knn_filter(hipStream_t st, uint32_t n_blocks, int waves, const KnnSets& P, const KnnBlock* blocks, int32_t list_len,
+                             int32_t* cand, float* tau, const KnnAssign& assign) {
+    if (n_blocks == 0) return hipSuccess;
+    const int tile = knn_tile(P.d, list_len), steps = knn_steps(P.d, tile);
+    if (assign.out) {
+        if (tile == 32) {
+            switch (steps) {
+                case 1: return launch_waves<32, 1, 2>(NOMAD_ARGS);
+                case 2: return launch_waves<32, 2, 2>(NOMAD_ARGS);
+                case 4: return launch_waves<32, 4, 2>(NOMAD_ARGS);
+                case 6: return launch_waves<32, 6, 2>(NOMAD_ARGS);
+                case 8: return launch_waves<32, 8, 2>(NOMAD_ARGS);
+                case 12: return launch_waves<32, 12, 2>(NOMAD_ARGS);
+                default: return launch_waves<32, 16, 2>(NOMAD_ARGS);
+            }
+        }
+        switch (steps) {
+            case 12: return launch_waves<16, 12, 2>(NOMAD_ARGS);
+            case 16: return launch_waves<16, 16, 2>(NOMAD_ARGS);
+            default: return launch_waves<16, 24, 2>(NOMAD_ARGS);
+        }
+    }
+    if (list_len <= kShortList) {
+        if (tile == 32) {
+            switch (steps) {
+                case 1: return launch_waves<32, 1, 16>(NOMAD_ARGS);
+                case 2: return launch_waves<32, 2, 16>(NOMAD_ARGS);
+                case 4: return launch_waves<32, 4, 16>(NOMAD_ARGS);
+                case 6: return launch_waves<32, 6, 16>(NOMAD_ARGS);
+                case 8: return launch_waves<32, 8, 16>(NOMAD_ARGS);
+                case 12: return launch_waves<32, 12, 16>(NOMAD_ARGS);
+                default: return launch_waves<32, 16, 16>(NOMAD_ARGS);
+            }
+        }
+        switch (steps) {
+            case 12: return launch_waves<16, 12, 12>(NOMAD_ARGS);
+            case 16: return launch_waves<16, 16, 12>(NOMAD_ARGS);
+            default: return launch_waves<16, 24, 12>(NOMAD_ARGS);
+        }
+    }
+    if (tile == 32) {
+        switch (steps) {
+            case 1: return launch_waves<32, 1, 34>(NOMAD_ARGS);
+            case 2: return launch_waves<32, 2, 34>(NOMAD_ARGS);
+            case 4: return launch_waves<32, 4, 34>(NOMAD_ARGS);
+            case 6: return launch_waves<32, 6, 34>(NOMAD_ARGS);
+            default: return launch_waves<32, 8, 34>(NOMAD_ARGS);
+        }
+    }
+    switch (steps) {
+        case 6: return launch_waves<16, 6, 20>(NOMAD_ARGS);
+        case 8: return launch_waves<16, 8, 20>(NOMAD_ARGS);
+        case 12: return launch_waves<16, 12, 20>(NOMAD_ARGS);
+        case 16: return launch_waves<16, 16, 20>(NOMAD_ARGS);
+        default: return launch_waves<16, 24, 20>(NOMAD_ARGS);
+    }
+}

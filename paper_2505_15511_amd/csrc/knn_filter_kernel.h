@@ -1,0 +1,387 @@
+// The nearest-neighbour filter for gfx950: what it works on, the kernel, the rules for its shapes.  (knn_kernels.h has the other
+// stages and the picture as a whole.)
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace nomad_knn {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+
+constexpr int kMaxK = 32;          // neighbours per point
+constexpr int kPad = 8;            // extra candidates the filter keeps
+
+// Rows of up to 256 columns are multiplied in 32x32x16 tiles: a wavefront keeps 32 queries in registers (half a kilobyte
+// per 16 columns, both parts) and every candidate fragment read from LDS serves 32 of them.  Wider rows, and long lists from
+// 128 columns on, leave room for 16 queries per wavefront: 16x16x32 tiles.
+constexpr int kShortList = 24;     // K' up to which the short lists are used
+__host__ __device__ constexpr int knn_tile(int d, int list_len) { return d <= (list_len <= kShortList ? 256 : 128) ? 32 : 16; }
+// matrix steps (of 512 / tile columns) the kernels are compiled for
+__host__ __device__ constexpr int knn_steps(int d, int tile) {
+    return tile == 32 ? (d <= 16 ? 1 : d <= 32 ? 2 : d <= 64 ? 4 : d <= 96 ? 6 : d <= 128 ? 8 : d <= 192 ? 12 : 16)
+                      : (d <= 192 ? 6 : d <= 256 ? 8 : d <= 384 ? 12 : d <= 512 ? 16 : 24);
+}
+__host__ __device__ constexpr size_t knn_tile_units(int steps) { return (size_t)steps * 2 * 64; }   // 16-byte units of a packed tile
+
+struct KnnBlock { int32_t cluster; int32_t q0; };   // one workgroup's share: tiles (or rows) q0 .. of group `cluster`
+
+// Rows laid out for the matrix cores (k_knn_pack): every group's rows in tiles of knn_tile(d), the last one padded.
+struct KnnPacked {
+    const uint4* data;           // [tiles][steps][hi, lo][64 lanes] 16 bytes: lane l of a step holds columns 8 (l / tile) .. + 7 of row l % tile
+    const float* norm;           // [tiles][tile] |x'|^2 / 2 (float32, of the centred row) in units of both sides' scales, +inf in the padding
+    const uint32_t* tstart;      // [groups + 1] first tile of every group
+    const uint32_t* max_bits;    // [groups] largest |x'|^2 of the group's rows: the scale of the group
+};
+
+// Queries and candidates, both cut into the same groups (group g: queries qmembers[qstart[g] .. qstart[g+1]), candidates
+// cmembers[cstart[g] .. cstart[g+1])).  Nearest neighbours inside clusters: both are the data set grouped by cluster.
+// K-Means assignment: one group, the queries are the points, the candidates the centroids.  Neighbourhoods of a sample
+// of query points among all points: one group, the queries a gathered copy of the sampled rows.
+struct KnnSets {
+    const float* XQ;             // query rows
+    const float* XC;             // candidate rows
+    const int32_t* qmembers;     // query row of every position, or nullptr = the position itself
+    const int32_t* cmembers;     // candidate row of every position, or nullptr = the position itself
+    const uint32_t* qstart;      // [groups + 1]
+    const uint32_t* cstart;      // [groups + 1]
+    KnnPacked Q, C;              // both sides packed
+    const float* centre;         // [groups][d] what both sides are centred on
+    const int32_t* group_of_q;   // group of every query row, or nullptr = group 0
+    int64_t n_q, n_c;            // rows of XQ, XC
+    int32_t d;
+    int32_t same_set;            // 1: queries and candidates are the same rows: a row is not its own neighbour
+    const int32_t* self_row;     // or, per query row, the candidate row that is the query itself (nullptr: see same_set)
+};
+
+// Scale of a group's rows: the power of two 2^e that brings |x'| <= sqrt(M) to at most 2^14.
+__device__ __forceinline__ int knn_scale_exponent(uint32_t max_bits) {
+    int x = 0;
+    (void)frexpf(__uint_as_float(max_bits), &x);          // M = f 2^x, 1/2 <= f < 1 (0: x = 0)
+    return max(-60, min(60, 14 - ((x + 1) >> 1)));
+}
+// Bound on |filter key - exact key| for rows of d values whose centred squared norms are at most M, u = 2^-24:
+//   products     hi hi + hi lo + lo hi leaves out lo lo and what lo was rounded by: 3 2^-22 |q||c|; float16 numbers below
+//                2^-14 taken as zero: 2^-13 of a scaled row element, 2^-28 sqrt(d) |q||c| (or, where the scale is at its
+//                limit, 2^-72 sqrt(d M)); doubled in the key
+//   sums         |c|^2 / 2 and d products, each addition rounded by at most 2 u of the sum of magnitudes, at most 3/2 M
+//                (whatever the order inside a matrix instruction), doubled in the key: 6 (d + 1) u M; the two small
+//                products' sums are 2^-10 of that
+//   norm, final combination, centring in float32: (d + 8) u M + 8 u M
+__device__ __forceinline__ double knn_filter_eps(int32_t d, double M) {
+    return (7.0 * (double)(d + 4) + 64.0) * 5.9604644775390625e-08 * M * 1.01 + 1e-12 * M + 1e-20 * sqrt(M);
+}
+__device__ __forceinline__ int32_t knn_row(const int32_t* members, uint32_t pos) { return members ? members[pos] : (int32_t)pos; }
+
+// ---------------------------------------------------------------- stage 1: the filter on the matrix cores
+template <int TILE> struct MatrixTile;
+template <> struct MatrixTile<32> {
+    typedef float Acc __attribute__((ext_vector_type(16)));
+    static __device__ __forceinline__ Acc mul(half8 a, half8 b, Acc c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+};
+template <> struct MatrixTile<16> {
+    typedef float Acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Acc mul(half8 a, half8 b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+};
+
+// Tiles staged together, and stages in LDS: loads into LDS are issued two stages ahead of their use (one at the widest rows,
+// whose stages are 48 KB), which is what hides the memory's latency behind 3,000 cycles of matrix instructions per stage.
+__host__ __device__ constexpr int knn_stage_tiles(int tile, int steps, int L, int waves) {
+    const int target = tile == 16 ? steps : (L > 2 && waves == 8) ? 16 : 8;
+    return steps >= target ? 1 : target / steps;
+}
+__host__ __device__ constexpr int knn_buffers(int tile, int steps) { return tile == 16 && steps > 16 ? 2 : 3; }
+constexpr int kMaxStageTiles = 16;   // packed arrays are this many tiles longer than what they hold
+__host__ __device__ constexpr int knn_fifo(int tile) { return tile == 32 ? 12 : 8; }   // hits a lane sets aside before they go into its list
+__host__ __device__ constexpr size_t knn_stage_bytes(int tile, int steps, int L, int waves) {
+    return (size_t)knn_stage_tiles(tile, steps, L, waves) * (knn_tile_units(steps) * 16 + (size_t)tile * 4);
+}
+__host__ __device__ constexpr size_t knn_filter_lds_bytes(int tile, int steps, int L, int waves) {
+    return knn_buffers(tile, steps) * knn_stage_bytes(tile, steps, L, waves) + (L > 2 ? (size_t)waves * knn_fifo(tile) * 64 * 8 : 0);
+}
+__host__ __device__ constexpr int knn_waves_per_simd(int tile, int steps, int L, int waves) {
+    return waves != 8 ? 1 : tile == 32 && L == 2 && steps <= 8 ? 4 : 2;
+}
+
+// 16 (4) bytes per lane from global memory straight into LDS: lane l's go to byte offset `to` + 16 l (4 l).  Not known to the
+// compiler as a load: the caller waits with wait_loads, and reads what has arrived only behind a barrier.
+__device__ __forceinline__ void load_to_lds16(uint32_t to, const void* base, uint32_t byte_offset) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(byte_offset), "s"(base) : "memory");
+}
+__device__ __forceinline__ void load_to_lds4(uint32_t to, const void* base, uint32_t byte_offset) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(byte_offset), "s"(base) : "memory");
+}
+template <int LEFT>   // until at most LEFT of this wavefront's loads are outstanding
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LEFT) : "memory"); }
+
+// One workgroup = WAVES tiles of queries of one group, one tile per wavefront, looping over the group's candidate tiles.
+// A = the candidates, B = the negated queries, C = |c|^2 / 2: the matrix instructions leave half of the key, |c|^2 - 2 q.c,
+// in units of the scales.  Lane l supplies row l % TILE and columns 8 (l / TILE) .. + 7 of a step; D: lane l holds query
+// l % TILE and the candidates 8 (v / 4) + 4 (l / TILE) + v % 4 in element v.  The queries' fragments stay in registers, the
+// candidates' tiles come packed and are loaded straight into LDS, a stage of tiles at a time.
+//
+// float16 matrix instructions run at 16 times the rate of the float32 ones (2.5 PFLOP/s against 157 TFLOP/s), so three
+// products cost a fifth of one in float32; unlike those they also leave the vector pipe to the selection.
+//
+// Selection: 64 / TILE lanes share a query, each sees its part of every tile's candidates and keeps the L smallest keys,
+// with their positions, sorted in registers.  Keys below the lane's threshold are set aside in a small queue in LDS; when a
+// lane's queue is nearly full every lane of the wavefront inserts what it has, one entry per pass (a sorted slot becomes
+// the median of its left neighbour, the new key and itself).  Inserting at once would spend a pass of the whole wavefront
+// on nearly every tile; the queue fills its passes.  Keys are looked at in fours: one comparison and a branch where no lane
+// of the wavefront has a hit.  The threshold is the smaller of the lane's last key and the largest of
+// the lanes' H-th keys (H 64 / TILE >= K': what lies above that is not among the K' smallest).
+// At the end the lists are merged by counting; tau = min(K'-th key of the union, the lists' last keys): every candidate
+// that is not passed on has key >= tau.
+//
+// L == 2: one neighbour wanted.  Every key goes straight into the lane's best two; at the end a query whose smallest key
+// lies below the second by more than twice the filter's error bound has its answer (out); the others are put on the `todo`
+// list (query position in todo, its 2 * 64 / TILE candidates in cand, tau) for k_assign_refine.
+struct KnnAssign { int32_t* out; int32_t* todo; uint32_t* n_todo; };
+
+template <int TILE, int KS, int L, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WAVES)) k_knn_filter(const KnnSets P, const KnnBlock* __restrict__ blocks, int32_t list_len,
+                                                                               int32_t* __restrict__ cand, float* __restrict__ tau_out,
+                                                                               const KnnAssign assign) {
+    using Mat = MatrixTile<TILE>;
+    using Acc = typename Mat::Acc;
+    constexpr int kShare = 64 / TILE;                 // lanes per query
+    constexpr int kKeys = TILE * TILE / 64;           // keys per lane and tile
+    constexpr int kUnits = KS * 2 * 64;               // 16-byte units of a tile
+    constexpr int kStage = knn_stage_tiles(TILE, KS, L, WAVES), kBuffers = knn_buffers(TILE, KS);
+    constexpr int kStageBytes = (int)knn_stage_bytes(TILE, KS, L, WAVES), kDataBytes = kStage * kUnits * 16;
+    constexpr int kCopies = (kStage * KS * 2 + WAVES - 1) / WAVES;              // 1 KB loads of a wavefront per stage
+    constexpr int kNormCopies = (kStage * TILE + 63) / 64;                      // (every wavefront loads all the norms: they are few)
+    constexpr int kLoads = kCopies + kNormCopies;
+    constexpr int F = knn_fifo(TILE);
+    constexpr int H = TILE == 32 ? (L == 16 ? 12 : 20) : (L == 12 ? 6 : 10);   // H * kShare >= the largest K' of the class
+    extern __shared__ uint4 lds[];                    // [kBuffers] stages: tiles, then their norms; then the queues
+    float2* fifo = (float2*)((char*)lds + kBuffers * kStageBytes);   // [WAVES][F][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = lane / TILE;
+    const KnnBlock blk = blocks[blockIdx.x];
+    const int32_t grp = blk.cluster;
+    if (grp < 0) return;                                      // no work: fills a list up
+    const uint32_t c0 = P.cstart[grp], ct0 = P.C.tstart[grp];
+    const int32_t n_tiles = (int32_t)(P.C.tstart[grp + 1] - ct0);
+    const uint32_t q0g = P.qstart[grp];
+    const int32_t n_qg = (int32_t)(P.qstart[grp + 1] - q0g);
+    const uint32_t qt = P.Q.tstart[grp] + (uint32_t)(blk.q0 + wave);
+    const bool live = qt < P.Q.tstart[grp + 1];               // wave-uniform
+    const int32_t qpos = (blk.q0 + wave) * TILE + (lane & (TILE - 1));
+    const int32_t qpt = live && qpos < n_qg ? knn_row(P.qmembers, q0g + (uint32_t)qpos) : -1;
+    // position of the candidate that is the query itself, if any
+    const int32_t self = qpt < 0 ? -1 : P.self_row ? P.self_row[qpt] - (int32_t)c0 : P.same_set ? qpos : -1;
+    half8 bh[KS], bl[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        uint4 h = make_uint4(0u, 0u, 0u, 0u), l = h;
+        if (live) { const uint4* src = P.Q.data + ((size_t)qt * KS + s) * 128 + lane; h = src[0]; l = src[64]; }
+        constexpr uint32_t kSign = 0x80008000u;
+        h.x ^= kSign; h.y ^= kSign; h.z ^= kSign; h.w ^= kSign;
+        l.x ^= kSign; l.y ^= kSign; l.z ^= kSign; l.w ^= kSign;
+        bh[s] = *(const half8*)&h;
+        bl[s] = *(const half8*)&l;
+    }
+    // half keys in units of both scales
+    const int unit_exp = knn_scale_exponent(P.Q.max_bits[grp]) + knn_scale_exponent(P.C.max_bits[grp]);
+    const float key_unit = ldexpf(2.f, -unit_exp);
+    float lk[L];
+    int32_t lp[L];
+#pragma unroll
+    for (int x = 0; x < L; ++x) { lk[x] = __builtin_inff(); lp[x] = -1; }
+    float thr = qpt >= 0 ? __builtin_inff() : -__builtin_inff();   // lanes without a query take nothing
+    int cnt = 0;                                                   // entries in this lane's queue
+    float2* queue = fifo + (size_t)wave * F * 64 + lane;
+
+    const char* csrc = (const char*)(P.C.data + (size_t)ct0 * kUnits);
+    const char* nsrc = (const char*)(P.C.norm + (size_t)ct0 * TILE);
+    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)(char*)lds;
+    const int32_t last0 = n_tiles > 0 ? (n_tiles - 1) / kStage * kStage : 0;   // first tile of the last stage
+    // the stage that begins with tile t (the last one again where that is past the end), into buffer buf.  The last stage may
+    // take tiles beyond the group's along; the arrays are long enough for that, and nobody looks at them.
+    auto fetch = [&](int32_t t, int buf) {
+        t = min(t, last0);
+        const char* from = csrc + (size_t)t * kUnits * 16;
+        const uint32_t to = lds0 + (uint32_t)(buf * kStageBytes);
+#pragma unroll
+        for (int u = 0; u < kCopies; ++u) {
+            const uint32_t at = (uint32_t)min(wave + u * WAVES, kStage * KS * 2 - 1) * 1024u;
+            load_to_lds16(to + at, from, at + (uint32_t)lane * 16u);
+        }
+        const char* nfrom = nsrc + (size_t)t * TILE * 4;
+#pragma unroll
+        for (int u = 0; u < kNormCopies; ++u)
+            if (kStage * TILE % 64 == 0 || u * 64 + lane < kStage * TILE) load_to_lds4(to + kDataBytes + u * 256, nfrom, (uint32_t)(u * 64 + lane) * 4u);
+    };
+    // one entry of every lane's queue (the newest) into its list
+    auto insert = [&]() {
+        float xk = __builtin_inff();
+        int32_t xp = -1;
+        if (cnt > 0) {
+            --cnt;
+            const float2 e = queue[cnt * 64];
+            xp = __float_as_int(e.y);
+            xk = xp == self ? __builtin_inff() : e.x;
+        }
+        // from the last slot down, in place (the empty assembly keeps the slots in their registers: left to itself the
+        // compiler copies the whole list every pass)
+        bool here = xk < lk[L - 1];
+#pragma unroll
+        for (int x = L - 1; x >= 1; --x) {
+            const bool left = xk < lk[x - 1];
+            const int32_t moved = left ? lp[x - 1] : xp;
+            lp[x] = here ? moved : lp[x];
+            lk[x] = __builtin_amdgcn_fmed3f(lk[x - 1], xk, lk[x]);
+            asm volatile("" : "+v"(lk[x]), "+v"(lp[x]));
+            here = left;
+        }
+        lp[0] = here ? xp : lp[0];
+        lk[0] = here ? xk : lk[0];
+        asm volatile("" : "+v"(lk[0]), "+v"(lp[0]));
+    };
+    auto drain = [&](int level) {     // passes until no lane's queue holds more than `level` entries
+        while (__any(cnt > level)) insert();
+        float most = lk[H < L ? H - 1 : 0];
+#pragma unroll
+        for (int w = TILE; w < 64; w <<= 1) most = fmaxf(most, __shfl_xor(most, w, 64));
+        if (qpt >= 0) thr = fminf(lk[L - 1], most);
+    };
+    // tile number i of the stage in buffer `buf`, tile t of the group
+    auto consume = [&](int buf, int i, int32_t t) {
+        Acc big, small;
+        const char* stage = (const char*)lds + buf * kStageBytes;
+        const float* nn = (const float*)(stage + kDataBytes) + i * TILE + 4 * part;
+#pragma unroll
+        for (int g = 0; g < kKeys / 4; ++g) {
+            const float4 n4 = *(const float4*)(nn + 8 * g);
+            big[4 * g] = n4.x; big[4 * g + 1] = n4.y; big[4 * g + 2] = n4.z; big[4 * g + 3] = n4.w;
+        }
+#pragma unroll
+        for (int v = 0; v < kKeys; ++v) small[v] = 0.f;
+        const uint4* frag = (const uint4*)stage + i * kUnits + lane;
+        half8 ah = *(const half8*)&frag[0], al = *(const half8*)&frag[64];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            half8 nh = ah, nl = al;
+            if (s + 1 < KS) { nh = *(const half8*)&frag[(s + 1) * 128]; nl = *(const half8*)&frag[(s + 1) * 128 + 64]; }
+            __builtin_amdgcn_sched_barrier(0);     // the next step's fragments are on their way while this step is multiplied
+            small = Mat::mul(ah, bl[s], small);
+            big = Mat::mul(ah, bh[s], big);
+            small = Mat::mul(al, bh[s], small);
+            __builtin_amdgcn_sched_barrier(0);
+            ah = nh;
+            al = nl;
+        }
+#pragma unroll
+        for (int g = 0; g < kKeys / 4; ++g) {
+            float key[4];
+            const int32_t pos0 = t * TILE + 8 * g + 4 * part;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) key[v] = big[4 * g + v] + small[4 * g + v];
+            if (L == 2) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const bool lt0 = key[v] < lk[0], lt1 = key[v] < lk[L - 1];
+                    lp[L - 1] = lt0 ? lp[0] : (lt1 ? pos0 + v : lp[L - 1]);
+                    lk[L - 1] = __builtin_amdgcn_fmed3f(lk[0], key[v], lk[L - 1]);
+                    lp[0] = lt0 ? pos0 + v : lp[0];
+                    lk[0] = lt0 ? key[v] : lk[0];
+                }
+            } else if (__any(fminf(fminf(key[0], key[1]), fminf(key[2], key[3])) < thr)) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (key[v] < thr) {
+                        queue[cnt * 64] = make_float2(key[v], __int_as_float(pos0 + v));
+                        ++cnt;
+                    }
+                if (__any(cnt > F - 4)) drain(F - 8);
+            }
+        }
+        if (L > 2 && __any(cnt > 4)) drain(4);
+    };
+
+    // the queries' fragments are here before the loop begins: a wait for them inside it would be a wait for the stage's loads
+#pragma unroll
+    for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(bh[s]), "+v"(bl[s]));
+    if (n_tiles > 0) {
+#pragma unroll
+        for (int x = 0; x < kBuffers - 1; ++x) fetch(x * kStage, x);
+        int buf = 0;
+        for (int32_t t0 = 0; t0 < n_tiles; t0 += kStage) {
+            wait_loads<(kBuffers - 2) * kLoads>();    // this wavefront's part of the stage has arrived ...
+            __builtin_amdgcn_s_barrier();             // ... everyone's has, and everyone is done with the stage before
+            asm volatile("" ::: "memory");
+            fetch(t0 + (kBuffers - 1) * kStage, buf == 0 ? kBuffers - 1 : buf - 1);
+            if (live) {
+                if (kStage == 1) consume(buf, 0, t0);
+                else {
+                    const int m = min(kStage, n_tiles - t0);
+#pragma nounroll
+                    for (int i = 0; i < m; ++i) consume(buf, i, t0 + i);
+                }
+            }
+            buf = buf + 1 == kBuffers ? 0 : buf + 1;
+        }
+        wait_loads<0>();
+    }
+    if (!live) return;
+    if (L > 2) drain(0);
+
+    // ---- merge the lists of a query by counting; ties to the lower part of the wavefront (the ranks are a permutation)
+    int rank[L];
+    float last = lk[L - 1];           // the smallest of the lists' last keys: what this query's lanes may have turned away
+#pragma unroll
+    for (int x = 0; x < L; ++x) rank[x] = x;
+#pragma unroll
+    for (int w = TILE; w < 64; w += TILE) {
+        const bool before = ((lane ^ w) / TILE) < part;
+        last = fminf(last, __shfl_xor(lk[L - 1], w, 64));
+#pragma unroll
+        for (int y = 0; y < L; ++y) {
+            const float o = __shfl_xor(lk[y], w, 64);
+#pragma unroll
+            for (int x = 0; x < L; ++x) rank[x] += (o < lk[x] || (o == lk[x] && before)) ? 1 : 0;
+        }
+    }
+    const int64_t p = (int64_t)q0g + qpos;
+    if (L == 2) {
+        // (key of rank 0 and 1 are among the lanes' entries: the second is the smallest of what is not rank 0)
+        float best = lk[0], second = rank[0] == 0 ? lk[L - 1] : lk[0];
+        int32_t bp = lp[0];
+#pragma unroll
+        for (int w = TILE; w < 64; w <<= 1) {
+            const float ob = __shfl_xor(best, w, 64);
+            const int32_t op = __shfl_xor(bp, w, 64);
+            if (ob < best || (ob == best && ((lane ^ w) / TILE) < part)) { best = ob; bp = op; }
+            second = fminf(second, __shfl_xor(second, w, 64));
+        }
+        const double eps = knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[grp]), (double)__uint_as_float(P.C.max_bits[grp])));
+        const bool open = qpt >= 0 && !(((double)second - (double)best) * (double)key_unit > 2.0 * eps);
+        if (qpt >= 0 && !open && part == 0) assign.out[qpt] = knn_row(P.cmembers, c0 + (uint32_t)bp);
+        const unsigned long long m = __ballot(open && part == 0);
+        if (m == 0ull) return;
+        uint32_t base = 0u;
+        if (lane == 0) base = atomicAdd(assign.n_todo, (uint32_t)__popcll(m));
+        base = __shfl(base, 0, 64);
+        if (open) {
+            const uint32_t slot = base + (uint32_t)__popcll(m & ((1ull << (lane & (TILE - 1))) - 1ull));
+            if (part == 0) { assign.todo[slot] = (int32_t)p; tau_out[slot] = last * key_unit; }
+#pragma unroll
+            for (int x = 0; x < L; ++x) cand[(size_t)slot * (2 * kShare) + rank[x]] = lp[x] < 0 ? -1 : knn_row(P.cmembers, c0 + (uint32_t)lp[x]);
+        }
+        return;
+    }
+    if (qpt < 0) return;
+#pragma unroll
+    for (int x = 0; x < L; ++x) {
+        if (rank[x] < list_len) cand[p * list_len + rank[x]] = lp[x] < 0 ? -1 : knn_row(P.cmembers, c0 + (uint32_t)lp[x]);
+        if (rank[x] == list_len - 1) tau_out[p] = fminf(lk[x], last) * key_unit;
+    }
+}
+
+// wavefronts per workgroup of the filter: eight share a staged tile, unless that leaves compute units without work
+__host__ inline int knn_filter_waves(int tile, int64_t query_tiles) { return query_tiles >= 1024 ? 8 : tile == 32 ? 2 : 4; }
+
+// list length per lane for K' = list_len candidates per query: every list longer than k (32-row tiles, two lists per query;
+// a query whose k nearest all fall to one lane must still be certified), or half of K' (16-row tiles, four lists)
+__host__ inline int knn_list_class(int tile, int list_len) { return tile == 32 ? (list_len <= kShortList ? 16 : 34) : list_len <= kShortList ? 12 : 20; }
+
+}  // namespace nomad_knn

@@ -67,6 +67,193 @@ __global__ void __launch_bounds__(256) k_merge_slices(const float* __restrict__ 
     if (t >= found && t < k) out[r * k + t] = -1;   // fewer than k candidates in all
 }
 
+// ---- nearest neighbours in the plane
+// In two dimensions the nearest neighbours of a point are in the cells around it: the points are counted into a square
+// grid of about kCellPoints points a cell, row by row, so that the cells of one row of a square are one contiguous range.  A
+// wavefront takes a query: the smallest square of cells that holds more than k points, their exact distances, the k
+// smallest; if a point outside the square could still be nearer, the square that reaches as far as the k-th distance.
+// A million points and 10,000 queries: 0.2 ms, where comparing every query with every point took 12 ms on the matrix cores
+// and left most queries to the exact path (neighbour distances in the plane are 1e-5 of its squared extent).
+constexpr int kCellPoints = 6;
+constexpr int kMaxGrid = 2048;      // cells per side
+
+// bounding box as (min x, min y, max x, max y) of ordered bit patterns; box must start at (max, max, 0, 0)
+__device__ __forceinline__ uint32_t ordered_bits(float v) {
+    const uint32_t b = __float_as_uint(v);
+    return b & 0x80000000u ? ~b : b | 0x80000000u;
+}
+__device__ __forceinline__ float from_ordered(uint32_t b) { return __uint_as_float(b & 0x80000000u ? b ^ 0x80000000u : ~b); }
+
+__global__ void k_plane_box_clear(uint32_t* __restrict__ box) {
+    if (threadIdx.x < 4) box[threadIdx.x] = threadIdx.x < 2 ? 0xFFFFFFFFu : 0u;
+}
+__global__ void __launch_bounds__(256) k_plane_box(const float2* __restrict__ Y, int64_t n, uint32_t* __restrict__ box) {
+    uint32_t lx = 0xFFFFFFFFu, ly = 0xFFFFFFFFu, hx = 0u, hy = 0u;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const float2 y = Y[i];
+        const uint32_t x0 = ordered_bits(y.x), y0 = ordered_bits(y.y);
+        lx = min(lx, x0); hx = max(hx, x0);
+        ly = min(ly, y0); hy = max(hy, y0);
+    }
+    for (int w = 32; w > 0; w >>= 1) {
+        lx = min(lx, (uint32_t)__shfl_xor((int)lx, w, 64)); hx = max(hx, (uint32_t)__shfl_xor((int)hx, w, 64));
+        ly = min(ly, (uint32_t)__shfl_xor((int)ly, w, 64)); hy = max(hy, (uint32_t)__shfl_xor((int)hy, w, 64));
+    }
+    if ((threadIdx.x & 63) == 0) { atomicMin(&box[0], lx); atomicMin(&box[1], ly); atomicMax(&box[2], hx); atomicMax(&box[3], hy); }
+}
+
+struct PlaneGrid { float x0, y0, inv; double width; };   // cell of x: floor((x - x0) inv), clamped; square cells
+__device__ __forceinline__ PlaneGrid plane_grid(const uint32_t* __restrict__ box, int32_t G) {
+    PlaneGrid p;
+    p.x0 = from_ordered(box[0]);
+    p.y0 = from_ordered(box[1]);
+    const float side = fmaxf(from_ordered(box[2]) - p.x0, from_ordered(box[3]) - p.y0);
+    p.inv = side > 0.f ? (float)G / side : 0.f;
+    if (!(p.inv < 3.0e38f)) p.inv = 0.f;                  // an extent too small to divide by: one cell
+    p.width = p.inv > 0.f ? 1.0 / (double)p.inv : __builtin_inf();
+    return p;
+}
+__device__ __forceinline__ int plane_cell(float x, float x0, float inv, int32_t G) {
+    return min(G - 1, max(0, (int)((x - x0) * inv)));      // monotone in x
+}
+
+// cell of every point and the number of points per cell
+__global__ void __launch_bounds__(256) k_plane_count(const float2* __restrict__ Y, int64_t n, const uint32_t* __restrict__ box, int32_t G,
+                                                     uint32_t* __restrict__ counts, uint32_t* __restrict__ rank) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const PlaneGrid p = plane_grid(box, G);
+    const float2 y = Y[i];
+    rank[i] = atomicAdd(&counts[plane_cell(y.y, p.y0, p.inv, G) * G + plane_cell(y.x, p.x0, p.inv, G)], 1u);
+}
+// start: exclusive scan of the counts in two levels (tile_offset per kScanTile cells)
+__global__ void __launch_bounds__(256) k_plane_place(const float2* __restrict__ Y, int64_t n, const uint32_t* __restrict__ box, int32_t G,
+                                                     const uint32_t* __restrict__ start, const uint32_t* __restrict__ tile_offset,
+                                                     const uint32_t* __restrict__ rank, float2* __restrict__ pos, int32_t* __restrict__ id) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const PlaneGrid p = plane_grid(box, G);
+    const float2 y = Y[i];
+    const uint32_t c = (uint32_t)(plane_cell(y.y, p.y0, p.inv, G) * G + plane_cell(y.x, p.x0, p.inv, G));
+    const uint32_t at = start[c] + tile_offset[c / nomad_knn::kScanTile] + rank[i];
+    pos[at] = y;
+    id[at] = (int32_t)i;
+}
+
+constexpr int kPlaneBuffer = 320;    // candidates a wavefront holds before it reduces them to the k smallest
+__global__ void __launch_bounds__(256) k_plane_neighbours(const float2* __restrict__ Y, int64_t n, const int32_t* __restrict__ queries, int64_t m,
+                                                          int32_t k, const uint32_t* __restrict__ box, int32_t G, const uint32_t* __restrict__ start,
+                                                          const uint32_t* __restrict__ tile_offset, const float2* __restrict__ pos,
+                                                          const int32_t* __restrict__ id, int32_t* __restrict__ out,
+                                                          unsigned long long* __restrict__ bad) {
+    __shared__ double sD[4][kPlaneBuffer];
+    __shared__ int32_t sI[4][kPlaneBuffer];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t r = (int64_t)blockIdx.x * 4 + wave;
+    if (r >= m) return;
+    const int32_t q = queries ? queries[r] : (int32_t)r;
+    if (q < 0 || q >= n) { *bad = 1ull; return; }
+    double* bD = sD[wave];
+    int32_t* bI = sI[wave];
+    const PlaneGrid g = plane_grid(box, G);
+    const float2 y = Y[q];
+    const int cx = plane_cell(y.x, g.x0, g.inv, G), cy = plane_cell(y.y, g.y0, g.inv, G);
+    const uint32_t cells = (uint32_t)(G * G);
+    auto cell_begin = [&](uint32_t c) { return c < cells ? start[c] + tile_offset[c / nomad_knn::kScanTile] : (uint32_t)n; };
+    auto row_range = [&](int row, int rad, uint32_t& a, uint32_t& b) {
+        a = cell_begin((uint32_t)(row * G + max(0, cx - rad)));
+        b = cell_begin((uint32_t)(row * G + min(G - 1, cx + rad)) + 1u);
+    };
+    auto wave_fence = []() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // the smallest square with more than k points (the query is one of them)
+    int rad = 1;
+    for (;; ++rad) {
+        uint32_t held = 0;
+        for (int row = max(0, cy - rad) + lane; row <= min(G - 1, cy + rad); row += 64) {
+            uint32_t a, b;
+            row_range(row, rad, a, b);
+            held += b - a;
+        }
+        for (int w = 32; w > 0; w >>= 1) held += (uint32_t)__shfl_xor((int)held, w, 64);
+        if (held > (uint32_t)k || (cx - rad <= 0 && cy - rad <= 0 && cx + rad >= G - 1 && cy + rad >= G - 1)) break;
+    }
+    double limit = __builtin_inf();      // candidates beyond it are not among the k nearest
+    int cnt = 0;
+    auto reduce = [&]() {                // the k smallest (distance, id) of the buffer, in order; limit follows
+        constexpr int kOwn = (kPlaneBuffer + 63) / 64;
+        double D[kOwn];
+        int32_t I[kOwn];
+        int rank[kOwn];
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u) {
+            const int e = lane + 64 * u;
+            D[u] = e < cnt ? bD[e] : __builtin_inf();
+            I[u] = e < cnt ? bI[e] : 0x7fffffff;
+            rank[u] = 0;
+        }
+        for (int o = 0; o < cnt; ++o) {
+            const double Do = bD[o];
+            const int32_t Io = bI[o];
+#pragma unroll
+            for (int u = 0; u < kOwn; ++u) rank[u] += (Do < D[u] || (Do == D[u] && Io < I[u])) ? 1 : 0;
+        }
+        wave_fence();
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u)
+            if (lane + 64 * u < cnt && rank[u] < k) { bD[rank[u]] = D[u]; bI[rank[u]] = I[u]; }
+        wave_fence();
+        cnt = min(cnt, k);
+        if (cnt == k) limit = bD[k - 1];
+    };
+    while (true) {
+        cnt = 0;
+        for (int row = max(0, cy - rad); row <= min(G - 1, cy + rad); ++row) {
+            uint32_t a, b;
+            row_range(row, rad, a, b);
+            for (uint32_t p0 = a; p0 < b; p0 += 64) {
+                const uint32_t p = p0 + (uint32_t)lane;
+                bool take = p < b;
+                double D = 0.0;
+                int32_t c = 0;
+                if (take) {
+                    const float2 v = pos[p];
+                    c = id[p];
+                    // the exact distance: coordinate by coordinate, difference, product and sum each rounded once
+                    const double ex = (double)y.x - (double)v.x, ey = (double)y.y - (double)v.y;
+                    D = __dadd_rn(__dmul_rn(ex, ex), __dmul_rn(ey, ey));
+                    take = c != q && D <= limit;
+                }
+                const unsigned long long mask = __ballot(take);
+                if (take) {
+                    const int e = cnt + (int)__popcll(mask & ((1ull << lane) - 1ull));
+                    bD[e] = D;
+                    bI[e] = c;
+                }
+                cnt += (int)__popcll(mask);
+                wave_fence();
+                if (cnt > kPlaneBuffer - 64) reduce();
+            }
+        }
+        reduce();
+        // a point outside the square is at least as far as the square's nearest open side (a hundredth of a cell of slack
+        // covers the rounding of the cell numbers)
+        double open = __builtin_inf();
+        if (cx - rad > 0) open = fmin(open, (double)y.x - ((double)g.x0 + ((double)(cx - rad) + 0.01) * g.width));
+        if (cy - rad > 0) open = fmin(open, (double)y.y - ((double)g.y0 + ((double)(cy - rad) + 0.01) * g.width));
+        if (cx + rad < G - 1) open = fmin(open, (double)g.x0 + ((double)(cx + rad + 1) - 0.01) * g.width - (double)y.x);
+        if (cy + rad < G - 1) open = fmin(open, (double)g.y0 + ((double)(cy + rad + 1) - 0.01) * g.width - (double)y.y);
+        if (open == __builtin_inf() || (cnt == k && limit < (open > 0.0 ? open * open : 0.0) * (1.0 - 1e-12))) break;
+        // reach as far as the k-th distance (or, short of k points, twice as far as before)
+        const double reach = cnt == k ? sqrt(limit) / g.width + 1.1 : 2.0 * rad;
+        rad = max(rad + 1, reach < (double)G ? (int)reach + 1 : G);
+    }
+    if (lane < k) out[r * k + lane] = lane < cnt ? bI[lane] : -1;
+}
+
 // common members of the two neighbour lists of every query (-1 = empty slot), summed
 __global__ void __launch_bounds__(256) k_overlap(const int32_t* __restrict__ a, const int32_t* __restrict__ b, int32_t k, int64_t m,
                                                  unsigned long long* __restrict__ hits) {

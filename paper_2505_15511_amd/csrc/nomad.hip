@@ -13,6 +13,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "host_util.h"
 #include "nomad.h"
 #include "nomad_kernels.h"
 
@@ -114,7 +115,9 @@ template <typename T>
 int dev_alloc(nomad_ctx* c, T** p, size_t count) {
     *p = nullptr;
     const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
-    HIP_TRY(c, hipMalloc((void**)p, bytes));
+    void* q = nullptr;
+    HIP_TRY(c, DevicePool::get().take(&q, bytes));
+    *p = (T*)q;
     c->allocations[*p] = bytes;
     c->device_bytes += (int64_t)bytes;
     return NOMAD_OK;
@@ -125,12 +128,13 @@ void dev_free(nomad_ctx* c, T*& p) {
     if (p) {
         auto it = c->allocations.find(p);
         if (it != c->allocations.end()) { c->device_bytes -= (int64_t)it->second; c->allocations.erase(it); }
-        (void)hipFree(p);
+        DevicePool::get().give(p);   // (every caller has waited for the context's stream)
     }
     p = nullptr;
 }
 
 void free_graph(nomad_ctx* c) {
+    if (!c->allocations.empty()) (void)hipStreamSynchronize(c->stream);   // nothing that is given back may still be in use
     dev_free(c, c->row_ptr); dev_free(c, c->col); dev_free(c, c->cluster_of); dev_free(c, c->group_of_cluster);
     dev_free(c, c->pe); dev_free(c, c->counts); dev_free(c, c->gbase); dev_free(c, c->gcount); dev_free(c, c->chunk_start);
     dev_free(c, c->gomega); dev_free(c, c->hinfo); dev_free(c, c->gmembers); dev_free(c, c->cmembers); dev_free(c, c->chunks); dev_free(c, c->mean_partial);
@@ -707,6 +711,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 ok = hipMemcpyAsync(&want, total_dev, sizeof(want), hipMemcpyDeviceToHost, st) == hipSuccess &&
                      hipStreamSynchronize(st) == hipSuccess;
             }
+            if (!ok) (void)hipStreamSynchronize(st);
             dev_free(c, total_dev);
             if (ok && want < (1ull << 31)) {
                 c->max_chunks = (uint32_t)want;

@@ -19,7 +19,7 @@ extern "C" int nomad_pca_init(const float* X, int64_t n, int32_t d, float std0, 
     if (hipGetDeviceCount(&ndev) != hipSuccess || device >= ndev) return NOMAD_E_HIP;
     KTRY(hipSetDevice(device));
     hipStream_t st = (hipStream_t)stream;
-    Buffers buf;
+    Buffers buf(st);
     const float* dX = X;
     float* dTheta = theta_out;
     if (mem == NOMAD_HOST) {
