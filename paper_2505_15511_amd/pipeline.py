@@ -100,13 +100,35 @@ def project(X: torch.Tensor, n_clusters: int, k: int = 15, n_epochs: int = 200, 
     return theta
 
 
+def sample_without_replacement(n: int, m: int, seed: int) -> torch.Tensor:
+    """torch.randperm(n, generator=torch.Generator().manual_seed(seed))[:m] on the CPU, without the n - m entries that are cut
+    off (5 ms of the host's time at a million).  The permutation is a forward shuffle, step i swapping slots i and
+    i + draw_i % (n - i), so its first m entries follow from the first m draws of the same Mersenne Twister: entry i is the
+    slot it is swapped with, except where two steps touch one slot; those few are replayed in order."""
+    if n >= 1 << 31 or m > n // 8:
+        return torch.randperm(n, generator=torch.Generator().manual_seed(seed))[:m]
+    draws = np.random.RandomState(seed & 0xFFFFFFFF).randint(0, 1 << 32, size=m, dtype=np.uint32).astype(np.int64)
+    step = np.arange(m, dtype=np.int64)
+    slot = step + draws % (n - step)
+    out = slot.copy()
+    slots, count = np.unique(slot, return_counts=True)
+    shared = slots[(count > 1) | (slots < m)]
+    held = {}   # what the touched slots hold by now
+    for i in np.flatnonzero(np.isin(slot, shared) | np.isin(step, shared)).tolist():
+        j = int(slot[i])
+        mine, theirs = held.get(i, i), held.get(j, j)
+        out[i] = theirs
+        held[i], held[j] = theirs, mine
+    return torch.from_numpy(out)
+
+
 def evaluate(X: torch.Tensor, theta: torch.Tensor, k: int = 15, n_queries: int = 10000, n_triplets: int = 1_000_000, seed: int = 0,
              device: int = 0):
     """(neighbourhood preservation at k on a seeded sample of queries, random triplet accuracy), Section 4."""
     n = X.shape[0]
     q = None
     if n_queries < n:
-        q = torch.randperm(n, generator=torch.Generator().manual_seed(seed))[:n_queries].to(torch.int32).to(X.device)
+        q = sample_without_replacement(n, n_queries, seed).to(torch.int32).to(X.device)
     _, preservation = neighbourhood_preservation(X, theta, k, q, device=device)
     _, accuracy = random_triplet_accuracy(X, theta, n_triplets, seed, device=device)
     return preservation, accuracy
