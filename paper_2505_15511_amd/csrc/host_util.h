@@ -118,6 +118,56 @@ struct Buffers {   // device allocations of one call, given back on every path o
     }
 };
 
+// A word that a call reads back while the device goes on: pinned memory and an event, both kept for the next call (making
+// them costs more than a copy).  At most kKeep of them are kept.
+class HostWord {
+public:
+    ~HostWord() {
+        if (!s_.word) return;
+        if (pending_) (void)hipEventSynchronize(s_.event);
+        {
+            std::lock_guard<std::mutex> lock(mutex());
+            if (kept().size() < kKeep) { kept().push_back(s_); return; }
+        }
+        release(s_);
+    }
+    hipError_t take() {
+        int device = 0;
+        hipError_t e = hipGetDevice(&device);
+        if (e != hipSuccess) return e;
+        {
+            std::lock_guard<std::mutex> lock(mutex());
+            for (size_t i = kept().size(); i-- > 0;)
+                if (kept()[i].device == device) {
+                    s_ = kept()[i];
+                    kept().erase(kept().begin() + (long)i);
+                    return hipSuccess;
+                }
+        }
+        Slot s{nullptr, nullptr, device};
+        if ((e = hipEventCreateWithFlags(&s.event, hipEventDisableTiming)) != hipSuccess) return e;
+        if ((e = hipHostMalloc((void**)&s.word, sizeof(unsigned long long), hipHostMallocDefault)) != hipSuccess) { (void)hipEventDestroy(s.event); return e; }
+        s_ = s;
+        return hipSuccess;
+    }
+    hipError_t copy_from(const unsigned long long* src, hipStream_t st) {
+        hipError_t e = hipMemcpyAsync(s_.word, src, sizeof(unsigned long long), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess && (e = hipEventRecord(s_.event, st)) == hipSuccess) pending_ = true;
+        return e;
+    }
+    hipError_t wait() { pending_ = false; return hipEventSynchronize(s_.event); }
+    unsigned long long value() const { return *s_.word; }
+
+private:
+    static constexpr size_t kKeep = 8;
+    struct Slot { unsigned long long* word; hipEvent_t event; int device; };
+    static void release(const Slot& s) { (void)hipHostFree(s.word); (void)hipEventDestroy(s.event); }
+    static std::mutex& mutex() { static std::mutex* m = new std::mutex(); return *m; }   // (both outlive the runtime's own statics)
+    static std::vector<Slot>& kept() { static std::vector<Slot>* k = new std::vector<Slot>(); return *k; }
+    Slot s_{nullptr, nullptr, 0};
+    bool pending_ = false;
+};
+
 struct HostArrays {   // small host arrays that travel to the device in one copy; lives until the copy is done
     std::vector<uint8_t> bytes;
     uint8_t* device = nullptr;

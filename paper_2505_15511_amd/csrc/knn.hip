@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "host_util.h"
@@ -104,10 +105,9 @@ int nearest_in_groups(hipStream_t st, const KnnSets& P, const KnnBlock* blocks, 
 }
 
 // The nearest candidate of every query (one group).  Work space: cand [n_q * 128 / tile], tau, todo, flagged [n_q],
-// counters [2] (queries the filter left open, queries for the exact path).
+// counters [2] (queries the filter left open, queries for the exact path), both zero.
 int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* blocks, uint32_t n_blocks, int waves, int32_t* cand, float* tau,
                 int32_t* todo, int32_t* flagged, uint32_t* counters, int32_t* out) {
-    KTRY(hipMemsetAsync(counters, 0, 2 * sizeof(uint32_t), st));
     KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, tau, KnnAssign{out, todo, counters}));
     const int32_t width = 128 / tile;
     const dim3 grid((uint32_t)std::min<int64_t>((P.n_q * width + 255) / 256, kLoopGrid));
@@ -121,41 +121,39 @@ int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* bloc
 
 // The M step of Lloyd's iteration: the points sorted by label with a stable radix sort (ascending point order inside a
 // cluster), then float64 sums in that order per (centroid, column); a label without points leaves its centroid as it is.
+// sort() and means() only enqueue.
 struct MeanStep {
     int64_t n = 0;
-    int32_t K = 0;
+    int32_t K = 0, d = 0;
     int passes = 1;                 // radix passes of 8 bits that cover the labels 0..K-1
     uint32_t n_blocks = 0;          // workgroups of a sort pass
-    uint32_t *counts = nullptr, *lstart = nullptr, *hist = nullptr, *tile_total = nullptr;
+    bool parallel = false;          // clusters of 128 points and more on average: column sums in parallel (k_mean_partials)
+    uint32_t *lstart = nullptr, *hist = nullptr, *tile_total = nullptr, *list = nullptr;
+    MeanPartial* partial = nullptr;
     uint32_t n_tiles = 0;           // tiles of the scan over the 256 n_blocks digit counters
     int32_t *keys[2] = {nullptr, nullptr}, *ids[2] = {nullptr, nullptr};   // a pass reads one pair of arrays and writes the other
-    int* bad = nullptr;
-    std::vector<uint32_t> hcounts, hstart;
+    const int32_t *sorted_keys = nullptr, *sorted_ids = nullptr;
 
-    int init(Buffers& buf, hipStream_t, int64_t n_, int32_t K_) {
-        n = n_; K = K_;
-        hcounts.assign((size_t)K, 0u);
-        hstart.assign((size_t)K + 1, 0u);
+    int init(Buffers& buf, int64_t n_, int32_t K_, int32_t d_) {
+        n = n_; K = K_; d = d_;
         int bits = 1;
         while (((int64_t)1 << bits) < K) ++bits;
         passes = (bits + 7) / 8;
         n_blocks = blocks_of(n, kSortSpan);
-        KTRY(buf.alloc(&counts, (size_t)K)); KTRY(buf.alloc(&lstart, (size_t)K + 1)); KTRY(buf.alloc(&bad, 1));
+        parallel = n >= (int64_t)128 * K;
+        KTRY(buf.alloc(&lstart, (size_t)K + 1));
         n_tiles = (uint32_t)(((size_t)256 * n_blocks + kScanTile - 1) / kScanTile);
         KTRY(buf.alloc(&hist, (size_t)256 * n_blocks));
         KTRY(buf.alloc(&tile_total, (size_t)n_tiles));
         for (int x = 0; x < (passes > 1 ? 2 : 1); ++x) { KTRY(buf.alloc(&keys[x], (size_t)n)); KTRY(buf.alloc(&ids[x], (size_t)n)); }
+        if (parallel) {
+            KTRY(buf.alloc(&partial, ((size_t)blocks_of(n, kMeanSpan) + (size_t)K) * d));
+            KTRY(buf.alloc(&list, (size_t)K * d));
+        }
         return NOMAD_OK;
     }
-    // labels [n] in 0..K-1 (on the device); dC [K * d] in and out
-    int run(hipStream_t st, const float* dX, int32_t d, const int32_t* labels, float* dC) {
-        KTRY(hipMemsetAsync(counts, 0, sizeof(uint32_t) * (size_t)K, st));
-        KTRY(hipMemsetAsync(bad, 0, sizeof(int), st));
-        hipLaunchKernelGGL(k_knn_count, dim3(blocks_of(n, kCountSpan)), dim3(256), 0, st, labels, n, K, counts, bad);
-        KTRY(hipMemcpyAsync(hcounts.data(), counts, sizeof(uint32_t) * (size_t)K, hipMemcpyDeviceToHost, st));
-        KTRY(hipStreamSynchronize(st));
-        for (int32_t j = 0; j < K; ++j) hstart[j + 1] = hstart[j] + hcounts[j];
-        KTRY(hipMemcpyAsync(lstart, hstart.data(), sizeof(uint32_t) * ((size_t)K + 1), hipMemcpyHostToDevice, st));
+    // labels [n] in 0..K-1 (on the device)
+    void sort(hipStream_t st, const int32_t* labels) {
         const int32_t* kin = labels;
         const int32_t* vin = nullptr;   // first pass: the point at position i is i
         int out = 0;
@@ -168,7 +166,27 @@ struct MeanStep {
             kin = keys[out]; vin = ids[out];
             out ^= 1;
         }
-        hipLaunchKernelGGL(k_kmeans_update, dim3(blocks_of((int64_t)K * d, 256)), dim3(256), 0, st, dX, d, vin, (const uint32_t*)lstart, K, dC);
+        sorted_keys = kin;
+        sorted_ids = vin;
+        hipLaunchKernelGGL(k_label_starts, dim3(blocks_of(n + 1, 256)), dim3(256), 0, st, sorted_keys, n, K, lstart);
+    }
+    // after sort: dC [K * d] in and out; *n_list is zero
+    int means(hipStream_t st, const float* dX, float* dC, uint32_t* n_list) {
+        const uint32_t entries = blocks_of((int64_t)K * d, 256);
+        if (!parallel) {
+            hipLaunchKernelGGL(k_kmeans_update, dim3(entries), dim3(256), 0, st, dX, d, sorted_ids, (const uint32_t*)lstart, K, dC);
+        } else {
+            const auto sums = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(blocks_of(n, kMeanSpan)), dim3(256), 0, st, dX, n, d, sorted_keys, sorted_ids, (const uint32_t*)lstart, partial);
+            };
+            // columns per lane: no lane idle before 16-byte loads, as far as rows are aligned for them
+            if (d % 4 == 0 && d > 128 && ((uintptr_t)dX & 15) == 0) sums(k_mean_partials<4>);
+            else if (d % 2 == 0 && d > 64 && ((uintptr_t)dX & 7) == 0) sums(k_mean_partials<2>);
+            else sums(k_mean_partials<1>);
+            hipLaunchKernelGGL(k_mean_combine, dim3(entries), dim3(256), 0, st, (const MeanPartial*)partial, d, (const uint32_t*)lstart, K, dC, list, n_list);
+            hipLaunchKernelGGL(k_mean_ordered, dim3((uint32_t)std::min<int64_t>(2048, (int64_t)K * d)), dim3(256), 0, st, dX, d, sorted_ids,
+                               (const uint32_t*)lstart, (const uint32_t*)list, (const uint32_t*)n_list, dC);
+        }
         KTRY(hipGetLastError());
         return NOMAD_OK;
     }
@@ -293,19 +311,22 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
         dX = x; dC = c; dLab = l;
     }
     // work space
-    uint32_t *max_pts = nullptr, *max_cen = nullptr, *counters = nullptr;
+    uint32_t *max_pts = nullptr, *zeros = nullptr;
     int32_t *new_lab = nullptr, *cand = nullptr, *todo = nullptr, *flagged = nullptr;
     float *cnorm = nullptr, *tau = nullptr, *centre = nullptr, *c_used = nullptr;
-    unsigned long long* changed = nullptr;
     double* inertia = nullptr;
     const std::vector<uint32_t> hq = {0u, (uint32_t)n}, hc = {0u, (uint32_t)K};
     PackedSide points, cents;
     points.plan(hq, d, 1);
     cents.plan(hc, d, 1);
-    KTRY(buf.alloc(&max_pts, 1)); KTRY(buf.alloc(&max_cen, 1)); KTRY(buf.alloc(&counters, 2));
+    KTRY(buf.alloc(&max_pts, 1)); KTRY(buf.alloc(&zeros, 6));
     KTRY(buf.alloc(&new_lab, (size_t)n)); KTRY(buf.alloc(&cand, (size_t)n * (128 / points.tile))); KTRY(buf.alloc(&todo, (size_t)n)); KTRY(buf.alloc(&flagged, (size_t)n));
     KTRY(buf.alloc(&cnorm, (size_t)K)); KTRY(buf.alloc(&tau, (size_t)n)); KTRY(buf.alloc(&centre, (size_t)d)); KTRY(buf.alloc(&c_used, (size_t)K * d));
-    KTRY(buf.alloc(&changed, 1)); KTRY(buf.alloc(&inertia, 1));
+    KTRY(buf.alloc(&inertia, 1));
+    // what every iteration starts from zero: labels changed (two words), the filter's and the exact path's queries, columns to
+    // add in order, the largest centred |c|^2
+    unsigned long long* changed = (unsigned long long*)zeros;
+    uint32_t *counters = zeros + 2, *n_list = zeros + 4, *max_cen = zeros + 5;
     const int waves = knn_filter_waves(points.tile, points.n_tiles);
     const std::vector<KnnBlock> hblocks = filter_blocks(points, cents, waves);
     std::vector<KnnBlock> hslabs;
@@ -329,41 +350,42 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     points.fill(st, dX, d, nullptr, centre, max_pts, nullptr, nullptr);
     MeanStep m_step;
     {
-        int rc = m_step.init(buf, st, n, K);
+        int rc = m_step.init(buf, n, K, d);
         if (rc) return rc;
     }
 
     KnnSets P{};
     P.XQ = dX; P.XC = dC; P.qmembers = nullptr; P.cmembers = nullptr; P.qstart = qstart; P.cstart = cstart;
     P.Q = points.view(max_pts); P.C = cents.view(max_cen); P.centre = centre; P.group_of_q = nullptr; P.n_q = n; P.n_c = K; P.d = d; P.same_set = 0;
+    // Labels go back and forth between two arrays; the centroids of the last E step are kept for the inertia.
+    int32_t *cur = new_lab, *prev = dLab;
+    HostWord hchanged;
+    KTRY(hchanged.take());
     int32_t it = 0;
-    bool have_labels = false;
     while (it < max_iters) {
         // E step: the nearest centroid of every point, exactly
-        KTRY(hipMemsetAsync(max_cen, 0, sizeof(uint32_t), st));
+        KTRY(hipMemsetAsync(zeros, 0, 6 * sizeof(uint32_t), st));
         hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(K, kNormRows)), dim3(256), 0, st, (const float*)dC, (int64_t)K, d, (const int32_t*)nullptr, centre, cnorm,
                            max_cen);
         cents.fill(st, dC, d, nullptr, centre, max_cen, max_pts, cnorm);
-        int rc = nearest_one(st, P, points.tile, blocks, (uint32_t)hblocks.size(), waves, cand, tau, todo, flagged, counters, new_lab);
+        int rc = nearest_one(st, P, points.tile, blocks, (uint32_t)hblocks.size(), waves, cand, tau, todo, flagged, counters, cur);
         if (rc) return rc;
         ++it;
         KTRY(hipMemcpyAsync(c_used, dC, sizeof(float) * (size_t)K * d, hipMemcpyDeviceToDevice, st));
-        unsigned long long hchanged = 1;
-        if (have_labels) {
-            KTRY(hipMemsetAsync(changed, 0, sizeof(unsigned long long), st));
-            hipLaunchKernelGGL(k_kmeans_changed, dim3(blocks_of(n, 256)), dim3(256), 0, st, (const int32_t*)new_lab, (const int32_t*)dLab, n, changed);
-            KTRY(hipMemcpyAsync(&hchanged, changed, sizeof(hchanged), hipMemcpyDeviceToHost, st));
-            KTRY(hipStreamSynchronize(st));
+        if (it > 1) {
+            hipLaunchKernelGGL(k_kmeans_changed, dim3(std::min<uint32_t>(512, blocks_of(n, 256))), dim3(256), 0, st, (const int32_t*)cur, (const int32_t*)prev, n, changed);
+            KTRY(hchanged.copy_from(changed, st));
         }
-        if (have_labels && hchanged == 0) break;   // nothing moved: the centroids are the means of these labels already
-        KTRY(hipMemcpyAsync(dLab, new_lab, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, st));
-        have_labels = true;
-        // M step
-        {
-            int rc = m_step.run(st, dX, d, (const int32_t*)dLab, dC);
-            if (rc) return rc;
+        m_step.sort(st, cur);   // the device sorts while the host waits for the count; wasted only once, when nothing has changed
+        if (it > 1) {
+            KTRY(hchanged.wait());
+            if (hchanged.value() == 0) break;   // nothing moved: the centroids are the means of these labels already
         }
+        if ((rc = m_step.means(st, dX, dC, n_list))) return rc;
+        std::swap(cur, prev);
     }
+    // (prev holds the last labels: after a break the two arrays are equal)
+    if (prev != dLab) KTRY(hipMemcpyAsync(dLab, prev, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, st));
     // inertia of the labels against the centroids they were computed from
     double hinertia = 0.0;
     KTRY(hipMemsetAsync(inertia, 0, sizeof(double), st));
@@ -419,7 +441,7 @@ extern "C" int nomad_kmeans_lsh_init(const float* X, int64_t n, int32_t d, int32
     if (!anchors) {   // every plane through the median of a sample along its normal
         int32_t* a = nullptr;
         KTRY(buf.alloc(&a, (size_t)n_planes));
-        hipLaunchKernelGGL(k_lsh_median_anchors, dim3((uint32_t)n_planes), dim3(256), 0, st, dX, n, d, dP, a);
+        hipLaunchKernelGGL(k_lsh_median_anchors, dim3((uint32_t)n_planes), dim3(kLshSample), 0, st, dX, n, d, dP, a);
         dA = a;
     }
     if (!dB || mem == NOMAD_HOST) {
@@ -429,14 +451,29 @@ extern "C" int nomad_kmeans_lsh_init(const float* X, int64_t n, int32_t d, int32
     }
     MeanStep m_step;
     {
-        int rc = m_step.init(buf, st, n, K);
+        int rc = m_step.init(buf, n, K, d);
         if (rc) return rc;
     }
-    hipLaunchKernelGGL(k_lsh_buckets, dim3(blocks_of(n, 256)), dim3(256), 0, st, dX, n, d, dP, dA, n_planes, K, dB);
+    double* table = nullptr;   // normals, then offsets
+    KTRY(buf.alloc(&table, (size_t)32 * d + 3 * 32));
+    const auto buckets = [&](auto planes_of) {
+        constexpr int P = decltype(planes_of)::value;
+        double* offset = table + (size_t)P * d;
+        hipLaunchKernelGGL(k_lsh_table<P>, dim3(P), dim3(256), 0, st, dX, d, dP, dA, n_planes, table, offset);
+        hipLaunchKernelGGL(k_lsh_buckets<P>, dim3(blocks_of(n, 256)), dim3(256), 0, st, dX, n, d, dP, dA, (const double*)table, (const double*)offset,
+                           n_planes, K, dB);
+    };
+    if (n_planes <= 8) buckets(std::integral_constant<int, 8>());
+    else if (n_planes <= 16) buckets(std::integral_constant<int, 16>());
+    else buckets(std::integral_constant<int, 32>());
     hipLaunchKernelGGL(k_lsh_fallback, dim3(blocks_of((int64_t)K * d, 256)), dim3(256), 0, st, dX, n, d, K, dC);
     // bucket means: the M step of Lloyd's iteration on the buckets
     {
-        int rc = m_step.run(st, dX, d, (const int32_t*)dB, dC);
+        uint32_t* n_list = nullptr;
+        KTRY(buf.alloc(&n_list, 1));
+        KTRY(hipMemsetAsync(n_list, 0, sizeof(uint32_t), st));
+        m_step.sort(st, (const int32_t*)dB);
+        int rc = m_step.means(st, dX, dC, n_list);
         if (rc) return rc;
     }
     KTRY(hipGetLastError());

@@ -582,24 +582,31 @@ __global__ void __launch_bounds__(256) k_sort_scatter(const int32_t* __restrict_
     }
 }
 
-// how many points changed their cluster
+// first position of every label in the sorted labels (lstart[K] = n)
+__global__ void __launch_bounds__(256) k_label_starts(const int32_t* __restrict__ keys, int64_t n, int32_t K, uint32_t* __restrict__ lstart) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i > n) return;
+    const int32_t cur = i < n ? keys[i] : K, prev = i > 0 ? keys[i - 1] : -1;
+    for (int32_t j = prev + 1; j <= cur; ++j) lstart[j] = (uint32_t)i;
+}
+
+// how many points changed their cluster (one atomic per workgroup: one per wavefront on this single address took 52 us for a
+// million points)
 __global__ void __launch_bounds__(256) k_kmeans_changed(const int32_t* __restrict__ a, const int32_t* __restrict__ b, int64_t n,
                                                         unsigned long long* __restrict__ changed) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool diff = i < n && a[i] != b[i];
-    const unsigned long long m = __ballot(diff);
-    if ((threadIdx.x & 63) == 0 && m) atomicAdd(changed, (unsigned long long)__popcll(m));
+    __shared__ uint32_t part[4];
+    uint32_t count = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) count += a[i] != b[i];
+    for (int w = 32; w > 0; w >>= 1) count += (uint32_t)__shfl_xor((int)count, w, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = count;
+    __syncthreads();
+    if (threadIdx.x == 0 && (count = part[0] + part[1] + part[2] + part[3]) != 0u) atomicAdd(changed, (unsigned long long)count);
 }
 
 // M step: centroid j = float32(sum of its rows / count), the rows added in ascending point order in float64 (ids: the
-// points sorted by cluster, ascending inside a cluster; one thread per (cluster, column)); an empty cluster keeps its row.
-__global__ void __launch_bounds__(256) k_kmeans_update(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ ids,
-                                                       const uint32_t* __restrict__ start, int32_t K, float* __restrict__ C) {
-    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= (int64_t)K * d) return;
-    const int32_t j = (int32_t)(x / d), col = (int32_t)(x % d);
-    const uint32_t r0 = start[j], r1 = start[j + 1];
-    if (r1 == r0) return;
+// points sorted by cluster, ascending inside a cluster); an empty cluster keeps its row.
+__device__ __forceinline__ double ordered_column_sum(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ ids, uint32_t r0,
+                                                     uint32_t r1, int32_t col) {
     double sum = 0.0;
     uint32_t r = r0;
     if (r + 64 <= r1) {   // batches of 64 rows in flight, the additions in order; the next batch's ids travel with this batch's rows
@@ -629,57 +636,276 @@ __global__ void __launch_bounds__(256) k_kmeans_update(const float* __restrict__
         for (int u = 0; u < 8; ++u) sum = __dadd_rn(sum, (double)v[u]);
     }
     for (; r < r1; ++r) sum = __dadd_rn(sum, (double)X[(int64_t)ids[r] * d + col]);
-    C[x] = (float)(sum / (double)(r1 - r0));
+    return sum;
+}
+
+// small clusters: one thread per (cluster, column)
+__global__ void __launch_bounds__(256) k_kmeans_update(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ ids,
+                                                       const uint32_t* __restrict__ start, int32_t K, float* __restrict__ C) {
+    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= (int64_t)K * d) return;
+    const int32_t j = (int32_t)(x / d), col = (int32_t)(x % d);
+    const uint32_t r0 = start[j], r1 = start[j + 1];
+    if (r1 == r0) return;
+    C[x] = (float)(ordered_column_sum(X, d, ids, r0, r1, col) / (double)(r1 - r0));
+}
+
+// Large clusters.  A chain of thousands of ordered additions per thread leaves most of the chip idle (a million points in
+// 256 clusters: 0.33 ms for 512 MB; in parallel 0.11 ms, the card's copy rate).  The centroid is the sum rounded to float32,
+// and the 29 bits less hide the order in nearly every case: every addition errs by at most 2^-53 of its result, so from
+// bounds on the partial sums of both orders follows an interval that holds the ordered sum, and if both its ends divide and
+// round to the same float32, that is the centroid.  The few columns whose interval straddles a rounding boundary (or is not
+// finite) are put on a list and added in order.
+//
+// k_mean_partials: a workgroup takes kMeanSpan positions of the sorted order; the part of span b that lies in cluster j is
+// partial number b + j (b + j grows along the order, so the numbers are distinct and below spans + K).
+constexpr int kMeanSpan = 512;
+struct MeanPartial { double sum; double magnitude; };
+
+template <int VEC>
+__global__ void __launch_bounds__(256) k_mean_partials(const float* __restrict__ X, int64_t n, int32_t d, const int32_t* __restrict__ keys,
+                                                       const int32_t* __restrict__ ids, const uint32_t* __restrict__ lstart,
+                                                       MeanPartial* __restrict__ partial) {
+    __shared__ double s_sum[4][64 * VEC], s_mag[4][64 * VEC];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t b0 = blockIdx.x * (uint32_t)kMeanSpan, b1 = (uint32_t)min(n, (int64_t)b0 + kMeanSpan);
+    for (uint32_t r0 = b0; r0 < b1;) {
+        const int32_t j = __builtin_amdgcn_readfirstlane(keys[r0]);
+        const uint32_t r1 = min(b1, (uint32_t)__builtin_amdgcn_readfirstlane((int)lstart[j + 1]));
+        MeanPartial* out = partial + ((size_t)blockIdx.x + (size_t)j) * d;
+        for (int c0 = 0; c0 < d; c0 += 64 * VEC) {
+            const int col = c0 + lane * VEC;
+            const float* src = X + (col < d ? col : 0);
+            double sum[VEC], mag[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) sum[v] = mag[v] = 0.0;
+            const auto load = [&](uint32_t r, float (&x)[VEC]) {
+                const float* row = src + (int64_t)ids[r] * d;
+                if constexpr (VEC == 4) { const float4 t = *(const float4*)row; x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w; }
+                else if constexpr (VEC == 2) { const float2 t = *(const float2*)row; x[0] = t.x; x[1] = t.y; }
+                else x[0] = *row;
+            };
+            const auto add = [&](const float (&x)[VEC]) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) { sum[v] += (double)x[v]; mag[v] += fabs((double)x[v]); }
+            };
+            uint32_t r = r0 + (uint32_t)wave;
+            for (; r + 60 < r1; r += 64) {   // sixteen rows of this wavefront in flight
+                float x[16][VEC];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) load(r + 4u * u, x[u]);
+#pragma unroll
+                for (int u = 0; u < 16; ++u) add(x[u]);
+            }
+            for (; r < r1; r += 4) {
+                float x[VEC];
+                load(r, x);
+                add(x);
+            }
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) { s_sum[wave][lane * VEC + v] = sum[v]; s_mag[wave][lane * VEC + v] = mag[v]; }
+            __syncthreads();
+            for (int x = threadIdx.x; x < 64 * VEC && c0 + x < d; x += 256)
+                out[c0 + x] = {(s_sum[0][x] + s_sum[1][x]) + (s_sum[2][x] + s_sum[3][x]), (s_mag[0][x] + s_mag[1][x]) + (s_mag[2][x] + s_mag[3][x])};
+            __syncthreads();
+        }
+        r0 = r1;
+    }
+}
+
+// The partials of every (cluster, column); columns whose float32 the order could change go on the list (*n_list of them).
+// With P_b the sum of the spans before b, m_b, M_b the rows and magnitudes of span b and u = 2^-53: a partial sum of the
+// ordered addition inside span b is at most |P_b| + M_b (+ what the earlier roundings moved, below 2 m u M), so it errs by
+// at most u sum_b m_b (|P_b| + M_b + 2 m u M); the parallel sum by u (kMeanSpan / 4 + 4) M inside the spans and u |P_b| at each join.
+__global__ void __launch_bounds__(256) k_mean_combine(const MeanPartial* __restrict__ partial, int32_t d, const uint32_t* __restrict__ lstart, int32_t K,
+                                                      float* __restrict__ C, uint32_t* __restrict__ list, uint32_t* __restrict__ n_list) {
+    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= (int64_t)K * d) return;
+    const int32_t j = (int32_t)(x / d), col = (int32_t)(x % d);
+    const uint32_t r0 = lstart[j], r1 = lstart[j + 1];
+    if (r1 == r0) return;
+    double sum = 0.0, mag = 0.0, ordered = 0.0, joins = 0.0;
+    const uint32_t b1 = (r1 - 1) / kMeanSpan;
+    for (uint32_t b = r0 / kMeanSpan; b <= b1; b += 8) {
+        MeanPartial p[8];   // eight loads in flight
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) p[u] = partial[((size_t)min(b + u, b1) + (size_t)j) * d + col];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u)
+            if (b + u <= b1) {
+                const uint32_t rows = min(r1, (b + u + 1) * kMeanSpan) - max(r0, (b + u) * kMeanSpan);
+                ordered += (double)rows * (fabs(sum) + p[u].magnitude);
+                sum += p[u].sum;
+                mag += p[u].magnitude;
+                joins += fabs(sum);
+            }
+    }
+    const double m = (double)(r1 - r0), err = 0x1p-53 * 1.02 * (ordered + joins + mag * (kMeanSpan / 4 + 4 + 2.0 * m * (m * 0x1p-53)));
+    const float lo = (float)((sum - err) / m), hi = (float)((sum + err) / m);
+    if (lo == hi && mag < 0x1p1000) C[x] = (float)(sum / m);
+    else list[atomicAdd(n_list, 1u)] = (uint32_t)x;
+}
+
+// the columns on the list, a workgroup each: the values come into LDS in parallel, one wavefront adds them in order
+constexpr int kOrderedChunk = 1024;
+__global__ void __launch_bounds__(256) k_mean_ordered(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ ids,
+                                                      const uint32_t* __restrict__ lstart, const uint32_t* __restrict__ list,
+                                                      const uint32_t* __restrict__ n_list, float* __restrict__ C) {
+    __shared__ double v[2][kOrderedChunk];
+    const uint32_t count = *n_list;
+    for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
+        const uint32_t x = list[e];
+        const int32_t j = (int32_t)(x / (uint32_t)d), col = (int32_t)(x % (uint32_t)d);
+        const uint32_t r0 = lstart[j], m = lstart[j + 1] - r0;
+        const auto stage = [&](uint32_t c) {   // past the end: +0.0, which changes no sum that started from +0.0
+#pragma unroll
+            for (int u = 0; u < kOrderedChunk / 256; ++u) {
+                const uint32_t r = c * kOrderedChunk + 256u * u + threadIdx.x;
+                v[c & 1u][256 * u + threadIdx.x] = r < m ? (double)X[(int64_t)ids[r0 + r] * d + col] : 0.0;
+            }
+        };
+        const uint32_t chunks = (m + kOrderedChunk - 1) / kOrderedChunk;
+        stage(0);
+        double sum = 0.0;
+        for (uint32_t c = 0; c < chunks; ++c) {
+            __syncthreads();
+            if (threadIdx.x < 64) {
+                const double* s = v[c & 1u];
+#pragma unroll 16
+                for (int t = 0; t < kOrderedChunk; ++t) sum = __dadd_rn(sum, s[t]);
+            }
+            if (c + 1 < chunks) stage(c + 1);
+        }
+        __syncthreads();   // (the next column's stage overwrites the chunks)
+        if (threadIdx.x == 0) C[x] = (float)(sum / (double)m);
+    }
 }
 
 // The start from a locality-sensitive hash: bit j of a point = [ sum_t h_{j,t} (x_t - a_{j,t}) > 0 ], a_j the anchor row of
 // plane j, the sum over t = 0..d-1 in order with difference, product and running sum each rounded once in float64;
-// bucket = floor(code K / 2^b).  One thread per point, one accumulator per plane, the row read once.
+// bucket = floor(code K / 2^b).  One thread per point, one accumulator per plane.
+//
+// Only the sign of the sum counts, so it is taken from sum_t h_t x_t - sum_t h_t a_t with fused multiply-adds (a third of the
+// operations) wherever that lies outside both sums' roundings, (d + 4) 2^-53 (sum |h_t| |x_t| + sum |h_t| |a_t|) each at most; a point
+// on a plane or nearly so (its anchor) walks its row in the order above.  A workgroup's 256 rows come through LDS kLshCols
+// columns at a time: whole lines from memory, where a thread walking its own row took 2.1 ms for a million rows of 128.
+// P: planes this instance has accumulators for.
 constexpr int kMaxPlanes = 30;
-__global__ void __launch_bounds__(256) k_lsh_buckets(const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ planes,
-                                                     const int32_t* __restrict__ anchors, int32_t b, int32_t K, int32_t* __restrict__ bucket) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double acc[kMaxPlanes];
-#pragma unroll
-    for (int j = 0; j < kMaxPlanes; ++j) acc[j] = 0.0;
-    const float* x = X + i * d;
-    for (int t = 0; t < d; ++t) {
-        const double xt = (double)x[t];
-#pragma unroll
-        for (int j = 0; j < kMaxPlanes; ++j)
-            if (j < b) {
-                const double diff = __dsub_rn(xt, (double)X[(int64_t)anchors[j] * d + t]);
-                acc[j] = __dadd_rn(acc[j], __dmul_rn((double)planes[(int64_t)j * d + t], diff));
-            }
+constexpr int kLshCols = 16;
+// Of every plane j: normals [d][P] as float64 (0 beyond the b planes), and offset [P][3] = sum h a, sum |h| |a|, sum |h|
+template <int P>
+__global__ void __launch_bounds__(256) k_lsh_table(const float* __restrict__ X, int32_t d, const float* __restrict__ planes,
+                                                   const int32_t* __restrict__ anchors, int32_t b, double* __restrict__ normals,
+                                                   double* __restrict__ offset) {
+    __shared__ double part[4][3];
+    const int j = blockIdx.x;
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int t = threadIdx.x; t < d; t += 256) {
+        const double h = j < b ? (double)planes[(int64_t)j * d + t] : 0.0, a = j < b ? (double)X[(int64_t)anchors[j] * d + t] : 0.0;
+        normals[(size_t)t * P + j] = h;
+        s[0] = fma(h, a, s[0]);
+        s[1] = fma(fabs(h), fabs(a), s[1]);
+        s[2] += fabs(h);
     }
-    uint64_t code = 0;
 #pragma unroll
-    for (int j = 0; j < kMaxPlanes; ++j)
-        if (j < b && acc[j] > 0.0) code |= (uint64_t)1 << j;
+    for (int c = 0; c < 3; ++c) {
+        for (int w = 32; w > 0; w >>= 1) s[c] += __shfl_xor(s[c], w, 64);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][c] = s[c];
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) offset[3 * j + threadIdx.x] = part[0][threadIdx.x] + part[1][threadIdx.x] + part[2][threadIdx.x] + part[3][threadIdx.x];
+}
+template <int P>
+__global__ void __launch_bounds__(256) k_lsh_buckets(const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ planes,
+                                                     const int32_t* __restrict__ anchors, const double* __restrict__ normals,
+                                                     const double* __restrict__ offset, int32_t b, int32_t K, int32_t* __restrict__ bucket) {
+    __shared__ float rows[256][kLshCols + 1];
+    const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + threadIdx.x;
+    const int lr = (int)threadIdx.x / kLshCols, lc = (int)threadIdx.x % kLshCols;   // loads: column lc of rows lr + 16 u
+    double acc[P];
+    float big = 0.f;
+#pragma unroll
+    for (int j = 0; j < P; ++j) acc[j] = 0.0;
+    float next[kLshCols];
+    const auto load = [&](int t0) {
+#pragma unroll
+        for (int u = 0; u < kLshCols; ++u) {
+            const int64_t r = i0 + lr + (256 / kLshCols) * u;
+            next[u] = r < n && t0 + lc < d ? X[r * d + t0 + lc] : 0.f;
+        }
+    };
+    load(0);
+    for (int t0 = 0; t0 < d; t0 += kLshCols) {
+        const int cols = min(kLshCols, d - t0);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kLshCols; ++u) rows[lr + (256 / kLshCols) * u][lc] = next[u];
+        __syncthreads();
+        if (t0 + kLshCols < d) load(t0 + kLshCols);
+#pragma unroll 2
+        for (int t = 0; t < cols; ++t) {
+            const float x = rows[threadIdx.x][t];
+            const double* h = normals + (size_t)(t0 + t) * P;
+            big = fmaxf(big, fabsf(x));
+#pragma unroll
+            for (int j = 0; j < P; ++j) acc[j] = fma(h[j], (double)x, acc[j]);
+        }
+    }
+    if (i >= n) return;
+    uint64_t code = 0;
+    uint32_t open = 0;
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+        if (j < b) {
+            const double v = acc[j] - offset[3 * j], bound = (double)(4 * d + 32) * 0x1p-53 * (offset[3 * j + 1] + offset[3 * j + 2] * (double)big);
+            if (v > bound) code |= (uint64_t)1 << j;
+            else if (!(v < -bound)) open |= 1u << j;
+        }
+    for (; open; open &= open - 1u) {
+        const int j = __ffs((int)open) - 1;
+        const float *h = planes + (int64_t)j * d, *a = X + (int64_t)anchors[j] * d, *x = X + i * d;
+        double sum = 0.0;
+        for (int t = 0; t < d; ++t) sum = __dadd_rn(sum, __dmul_rn((double)h[t], __dsub_rn((double)x[t], (double)a[t])));
+        if (sum > 0.0) code |= (uint64_t)1 << j;
+    }
     bucket[i] = (int32_t)((code * (uint64_t)K) >> b);
 }
 
 // Anchors the caller did not draw: plane j goes through the median of a strided sample along its normal.  The sample is the
 // m = min(kLshSample, n) points floor(s n / m); projection = sum_t h_{j,t} x_t over t = 0..d-1 in order (product and
 // running sum each rounded once in float64); the anchor is the sample point of rank floor(m / 2) in ascending
-// (projection, point).  One workgroup per plane: four sample points per thread, ranks by counting.
+// (projection, point).  One workgroup per plane, a sample point per thread, ranks by counting.
 constexpr int kLshSample = 1024;
-__global__ void __launch_bounds__(256) k_lsh_median_anchors(const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ planes,
+__global__ void __launch_bounds__(kLshSample) k_lsh_median_anchors(const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ planes,
                                                             int32_t* __restrict__ anchors) {
     __shared__ double sproj[kLshSample];
     const int j = blockIdx.x;
     const int m = (int)min((int64_t)kLshSample, n);
     const float* h = planes + (int64_t)j * d;
-    for (int s = threadIdx.x; s < m; s += 256) {
+    const int s = threadIdx.x;
+    double p = 0.0;
+    if (s < m) {
         const float* x = X + (((int64_t)s * n) / m) * d;
-        double acc = 0.0;
-        for (int t = 0; t < d; ++t) acc = __dadd_rn(acc, __dmul_rn((double)h[t], (double)x[t]));
-        sproj[s] = acc;
+        int t = 0;
+        if ((d & 3) == 0 && ((uintptr_t)X & 15) == 0) {
+            for (; t + 32 <= d; t += 32) {   // eight 16-byte loads in flight, added one by one in order
+                float4 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(x + t + 4 * u);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u], (double)v[u].x));
+                    p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u + 1], (double)v[u].y));
+                    p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u + 2], (double)v[u].z));
+                    p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u + 3], (double)v[u].w));
+                }
+            }
+        }
+        for (; t < d; ++t) p = __dadd_rn(p, __dmul_rn((double)h[t], (double)x[t]));
+        sproj[s] = p;
     }
     __syncthreads();
-    for (int s = threadIdx.x; s < m; s += 256) {   // sample points are in ascending index order: ties go to the lower s
-        const double p = sproj[s];
+    if (s < m) {   // sample points are in ascending index order: ties go to the lower s
         int rank = 0;
         for (int o = 0; o < m; ++o) rank += (sproj[o] < p || (sproj[o] == p && o < s)) ? 1 : 0;
         if (rank == m / 2) anchors[j] = (int32_t)(((int64_t)s * n) / m);

@@ -1,0 +1,109 @@
+"""Sizes at which the index, initialisation and quality kernels change their shape: the ends of tiles, of list and dimension
+classes, of the parallel sums; against the oracles."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kmeans_oracle as km
+from oracle import knn_oracle as ko
+from oracle import metrics_oracle as mo
+from oracle import pca_oracle as po
+from paper_2505_15511_amd import kmeans_lloyd, kmeans_lsh_init, knn_in_clusters, neighbourhood_preservation, pca_init, pipeline
+
+
+@pytest.mark.parametrize("n,m,seed", [(16, 2, 0), (1000, 125, 3), (80001, 10000, 7), (999, 500, 1), (5000, 5, 2**40 + 9), (1000, 0, 4)])
+def test_sampled_queries_are_the_head_of_the_permutation(n, m, seed):
+    ref = torch.randperm(n, generator=torch.Generator().manual_seed(seed))[:m]
+    assert torch.equal(pipeline.sample_without_replacement(n, m, seed), ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [16, 17, 128, 129, 256, 257, 384, 385])
+@pytest.mark.parametrize("k", [1, 8, 9, 16, 17, 32])
+def test_filter_classes(d, k):
+    rng = np.random.default_rng(d * 100 + k)
+    c = rng.permutation(np.repeat(np.arange(6), [31, 33, 64, 1, 290, 129]))
+    X = (rng.normal(size=(len(c), d)) + 3.0 * rng.normal(size=(6, d))[c]).astype(np.float32)
+    assert np.array_equal(knn_in_clusters(X, c, 6, k).astype(np.int64), ko.in_cluster_knn(X, c, k)[0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,k", [(32 * 1024 + 5, 9, 15), (16 * 1024 + 5, 260, 15), (16 * 1024 + 5, 140, 20)])
+def test_filter_with_the_wide_workgroup(n, d, k):
+    rng = np.random.default_rng(n)
+    c = rng.integers(0, 60, n)
+    X = rng.normal(size=(n, d)).astype(np.float32)
+    out = knn_in_clusters(torch.from_numpy(X).cuda(), torch.from_numpy(c).cuda(), 60, k).cpu().numpy()
+    assert np.array_equal(out.astype(np.int64), ko.in_cluster_knn(X, c, k)[0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,k,layout", [(1023, 15, "normal"), (1024, 15, "normal"), (1500, 32, "normal"), (3000, 1, "grid"), (3000, 15, "grid"),
+                                        (2500, 15, "outliers"), (2500, 15, "line"), (2000, 32, "point")])
+def test_plane_neighbours(n, k, layout):
+    rng = np.random.default_rng(n + k)
+    Y = rng.normal(size=(n, 2)).astype(np.float32)
+    if layout == "grid":
+        Y = rng.integers(0, 12, size=(n, 2)).astype(np.float32)          # ties and duplicates in bulk
+    elif layout == "outliers":
+        Y[:3] = [[1e6, 1e6], [-1e6, 1e6], [1e6, -3e5]]                   # nearly all points in one cell
+    elif layout == "line":
+        Y[:, 1] = 0.25
+    elif layout == "point":
+        Y[:] = 1.5
+        Y[-5:] += 1.0
+    X = np.concatenate([Y, 0.3 * rng.normal(size=(n, 3)).astype(np.float32)], axis=1)
+    q = rng.permutation(n)[:200].astype(np.int32)
+    q[:3] = [0, n - 1, n - 2]
+    q = np.unique(q).astype(np.int32)
+    assert neighbourhood_preservation(X, Y, k, q)[0] == mo.neighbourhood_preservation(X, Y, k, q)[0]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,K", [(513, 64, 4), (1024, 65, 8), (1537, 66, 1), (2000, 128, 15), (2000, 130, 2), (1300, 132, 10), (1300, 260, 3), (127, 6, 1)])
+def test_centroids_of_large_clusters(n, d, K):
+    rng = np.random.default_rng(n + d)
+    X = (rng.normal(size=(n, d)) * 10.0 ** rng.integers(-6, 4, size=(1, d))).astype(np.float32)
+    C0 = X[rng.choice(n, K, replace=False)].copy()
+    C_ref, lab_ref, it_ref, _ = km.lloyd(X, C0, 4)
+    C, lab, it, _ = kmeans_lloyd(X, C0, 4)
+    assert it == it_ref and np.array_equal(lab.astype(np.int64), lab_ref) and np.array_equal(C, C_ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [128, 1024, 1026, 5000])
+def test_means_on_a_rounding_boundary_are_added_in_order(n):
+    rng = np.random.default_rng(n)
+    X = np.full((n, 4), 1.0, np.float32)
+    half = rng.permutation(n)[:n // 2]
+    X[half, 0] = np.float32(1.0 + 2.0**-23)          # the mean lies half way between two float32 values
+    X[:, 1] = rng.normal(size=n)
+    X[half, 2] = -1.0                                # the sum is zero exactly
+    X[half[0], 3] = np.inf
+    C_ref = km.update(X, np.zeros(n, np.int64), X[:1])
+    C, _ = kmeans_lsh_init(X, 1, np.array([[0.0, 1.0, 0.0, 0.0]], np.float32), np.array([3], np.int32), return_buckets=True)
+    assert np.array_equal(C, C_ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("b", [8, 9, 16, 17, 30])
+@pytest.mark.parametrize("n,d", [(255, 15), (257, 16), (600, 33)])
+def test_hash_planes(n, d, b):
+    rng = np.random.default_rng(n + b)
+    X = rng.normal(size=(n, d)).astype(np.float32)
+    planes, anchors = rng.normal(size=(b, d)).astype(np.float32), rng.choice(n, b).astype(np.int32)   # anchors lie on their plane
+    X[n // 2:n // 2 + 20] = X[anchors[rng.integers(0, b, 20)]]
+    C_ref, b_ref = km.lsh_init(X, planes, anchors, 50)
+    C, buckets = kmeans_lsh_init(X, 50, planes, anchors, return_buckets=True)
+    assert np.array_equal(buckets.astype(np.int64), b_ref) and np.array_equal(C, C_ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d", [(70, 3), (500, 9), (1000, 127), (1000, 128), (1000, 129), (900, 257)])
+def test_principal_axes(n, d):
+    rng = np.random.default_rng(d)
+    X = (rng.normal(size=(n, d)) * np.r_[9.0, 5.0, np.ones(d - 2)] + rng.normal(size=d)).astype(np.float32)
+    ref, lam_ref = po.pca_init(X, 0.0)
+    theta, st = pca_init(X, 0.0, return_stats=True)
+    assert np.allclose(st["eigenvalues"], lam_ref, rtol=1e-10) and st["residual"] <= 1e-9
+    assert np.abs(theta - ref).max() <= 1e-5 * np.abs(ref).max()
