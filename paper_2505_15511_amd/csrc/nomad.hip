@@ -246,12 +246,15 @@ void launch_edges(nomad_ctx* c, const EdgeArgs& a) {
     launch_edges_s<MODE, 16>(c, a);
 }
 
+constexpr int64_t kSplitTrafficPoints = (int64_t)4 << 20;   // negatives from all of an embedding larger than the eight L2s together (32 MB)
+
 BinArgs bin_args(nomad_ctx* c) {
     BinArgs q{};
     q.head = c->head; q.pool = c->pool; q.chunk_prev = c->chunk_prev; q.chain_head = c->chain_head; q.chain_fill = c->chain_fill;
     q.wg_pool_begin = c->wg_pool_begin; q.ghead = c->ghead; q.E = c->E; q.e_begin = 0; q.e_end = c->E;
     q.max_chunks = c->max_chunks; q.n_bins = c->n_bins;
     q.tile_bits = c->tile_bits; q.overflow = c->overflow;
+    q.split_traffic = c->n > kSplitTrafficPoints && (!c->grouped || c->cfg.far_field == NOMAD_FAR_FIELD_SAMPLED);
     return q;
 }
 
@@ -260,7 +263,7 @@ size_t edge_pass_lds_bytes(const nomad_ctx* c) {
     if (c->pool_rounds && c->distinct_kernel)
         return distinct_lds_bytes(c->n_bins, (uint32_t)c->cfg.pool_size, (uint32_t)(c->cfg.pool_size / c->cfg.pool_line), c->pool_rounds);
     return c->pool_rounds ? pooled_lds_bytes(c->n_bins, c->cfg.pool_block, (uint32_t)c->cfg.pool_size)
-                          : binned_lds_bytes(c->n_bins, c->cfg.n_neg, c->bin_block, c->sorted_records);
+                          : binned_lds_bytes(c->n_bins, c->cfg.n_neg, c->bin_block, c->sorted_records, c->flush_rounds);
 }
 
 // Calls `fn(kernel)` with the edge-pass kernel that matches the context: number of negatives, sampler, launch shape.
@@ -268,7 +271,9 @@ using EdgePassKernel = void (*)(const EdgeArgs, const BinArgs);
 
 template <int S, typename Fn>
 void with_edge_pass_kernel_s(const nomad_ctx* c, Fn fn) {
-    EdgePassKernel k = k_edges_binned<S, 1024>;
+    const bool plain = !c->grouped && !c->through_means && c->cfg.pool_size == 0;
+    EdgePassKernel k = plain ? k_edges_binned<S, 1024, true, 1, true> : k_edges_binned<S, 1024>;
+    if (c->sorted_records && c->flush_rounds == 2) k = plain ? k_edges_binned<S, 1024, true, 2, true> : k_edges_binned<S, 1024, true, 2>;
     if (c->distinct_kernel && c->pool_rounds == 1) k = k_edges_pooled_distinct<S, 1>;
     else if (c->distinct_kernel && c->pool_rounds == 2) k = k_edges_pooled_distinct<S, 2>;
     else if (c->distinct_kernel && c->pool_rounds == 4) k = k_edges_pooled_distinct<S, 4>;
@@ -277,7 +282,8 @@ void with_edge_pass_kernel_s(const nomad_ctx* c, Fn fn) {
     else if (c->pool_rounds == 2) k = k_edges_pooled<S, 2, 1024>;
     else if (c->pool_rounds == 4) k = k_edges_pooled<S, 4, 1024>;
     else if (c->pool_rounds == 8) k = k_edges_pooled<S, 8, 1024>;
-    else if (c->bin_block == 512) k = c->sorted_records ? k_edges_binned<S, 512, true> : k_edges_binned<S, 512, false>;
+    else if (c->bin_block == 512 && c->sorted_records) k = plain ? k_edges_binned<S, 512, true, 1, true> : k_edges_binned<S, 512, true>;
+    else if (c->bin_block == 512) k = k_edges_binned<S, 512, false>;
     else if (!c->sorted_records && c->flush_rounds == 2) k = k_edges_binned<S, 1024, false, 2>;
     else if (!c->sorted_records) k = k_edges_binned<S, 1024, false, 1>;
     fn(k);
@@ -673,7 +679,11 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         want_plan.tune_edge_block = c->tune_edge_block; want_plan.tune_wg_per_cu = c->tune_wg_per_cu;
         want_plan.tune_pool_kernel = c->tune_pool_kernel; want_plan.tune_record_sort = c->tune_record_sort;
         want_plan.tune_flush_rounds = c->tune_flush_rounds;
-        const EdgePlan plan = plan_edge_pass(want_plan);   // tile size, kernel, launch shape (edge_plan.h)
+        EdgePlan plan = plan_edge_pass(want_plan);   // tile size, kernel, launch shape (edge_plan.h)
+        int compute_units = 0;
+        HTRY(hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, c->cfg.device));
+        compute_units = std::max(1, compute_units);
+        coarsen_tiles(plan, n, s, compute_units);
         const int tile_bits = plan.tile_bits, bin_block = plan.bin_block, wg_per_cu = plan.wg_per_cu, pool_rounds = plan.pool_rounds;
         const uint32_t n_bins = plan.n_bins;
         const bool sorted = plan.sorted, distinct = plan.distinct_kernel;
@@ -682,14 +692,12 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         else if (s > 8) why = "more than 8 negatives per edge: the binned edge pass is built for s <= 8";
         else if (!bin_block) why = "the per-tile tables of the binned edge pass do not fit LDS at this number of points";
         if (E > 0 && why.empty()) {
-            hipDeviceProp_t prop;
-            HTRY(hipGetDeviceProperties(&prop, c->cfg.device));
             c->bin_block = bin_block;
             c->sorted_records = sorted;
             c->flush_rounds = plan.flush_rounds;
             c->pool_rounds = pool_rounds;
             c->distinct_kernel = distinct;
-            c->n_wg = std::max(1, prop.multiProcessorCount) * wg_per_cu;
+            c->n_wg = compute_units * wg_per_cu;
             c->n_bins = n_bins;
             c->tile_bits = tile_bits;
             unsigned long long* total_dev = nullptr;

@@ -15,6 +15,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "edge_plan.h"
 #include "philox.h"
 
@@ -799,6 +801,8 @@ struct BinArgs {
     uint32_t max_chunks;
     uint32_t n_bins;
     int tile_bits;
+    bool split_traffic;           // a round's record stores end before the next gathers start (embedding far beyond the L2s: reads and
+                                  // writes that alternate in bursts measured 3 % faster at 10 M points than mixed, 8 % slower at 1 M)
     int* overflow;                // set if a workgroup's chunk range were ever exceeded (it cannot be)
 };
 
@@ -810,6 +814,41 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// inclusive sum over the 64 lanes; all lanes of a full wavefront must be active
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);    // row_shr:1, 2, 4, 8 inside rows of 16
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, true);    // row_bcast:15 into rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, true);    // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// Chains whose open chunk cannot take the records counted for their tile get new chunks, linked to the chain.  Tables of B
+// tiles in LDS; all lanes of the workgroup must call.  One LDS atomic per wavefront hands the chunks out: a divergent
+// atomicAdd on one address becomes a loop over the lanes (3,000 cycles of a round).
+template <int BS>
+__device__ __forceinline__ void extend_chains(uint32_t B, const uint32_t* cnt, const uint32_t* fill, const uint32_t* chunk, uint32_t* base,
+                                              const BinArgs& Q, uint32_t pool_end, uint32_t* pool_cursor) {
+    for (uint32_t b0 = threadIdx.x & ~63u; b0 < B; b0 += BS) {
+        const uint32_t b = b0 + (threadIdx.x & 63u);
+        const uint32_t c = b < B ? cnt[b] : 0u, fl = b < B ? fill[b] : 0u;
+        const uint32_t k = c != 0 && fl + c > (uint32_t)kChunk ? (fl + c - 1) / kChunk : 0u;
+        const uint32_t incl = wave_prefix(k), all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        if (all == 0) continue;
+        uint32_t nb = 0;
+        if ((threadIdx.x & 63u) == 0) nb = atomicAdd(pool_cursor, all);
+        nb = (uint32_t)__builtin_amdgcn_readfirstlane((int)nb) + incl - k;
+        if (k) {
+            base[b] = nb;
+            if (nb + k > pool_end) *Q.overflow = 1;
+            uint32_t prev = chunk[b];
+            for (uint32_t y = 0; y < k && nb + y < pool_end; ++y) { Q.chunk_prev[nb + y] = prev; prev = nb + y; }
+        }
+    }
 }
 
 // LDS tables of one edge-pass workgroup (see k_edges_binned): per tile the record count of the round
@@ -844,55 +883,96 @@ __device__ __forceinline__ void init_bin_lds(const BinLds& L) {
 // rank of a new record among this round's records of its tile
 __device__ __forceinline__ uint32_t take_rank(const BinLds& L, uint32_t pt) { return atomicAdd(&L.start[pt >> L.tile_bits], 1u); }
 
+// ---- the sorted form of the binned scatter
+// LDS tables of a workgroup: per tile the records it has been given this round, the first sorted slot of this round, and
+// where the round's records go; then the round's records sorted by tile.  Places are record numbers in the workgroup's
+// private range of the pool; a chain's position is the place of its next record (0: no chunk yet; a multiple of kChunk: the
+// last chunk is full).
+struct SortLds {
+    uint2* place;       // [B] what to add to a sorted slot to get its place: while the chunk that is open lasts, and after
+    uint32_t* count;    // [B] low half: records of the round so far; high half: of the round before
+    uint32_t* start;    // [B] first sorted slot
+    uint32_t* rec_pt;   // [nrec] destination point
+    uint32_t* rec_x;    // [nrec] force x (float bits)
+    uint32_t* rec_y;    // [nrec]
+    uint32_t B;
+    int tile_bits;
+};
+
+__device__ __forceinline__ SortLds carve_sort_lds(uint32_t* mem, uint32_t B, uint32_t nrec, int tile_bits) {
+    SortLds L;
+    L.place = (uint2*)mem; L.count = mem + 2 * B; L.start = L.count + B;
+    L.rec_pt = L.start + B; L.rec_x = L.rec_pt + nrec; L.rec_y = L.rec_x + nrec;
+    L.B = B; L.tile_bits = tile_bits;
+    return L;
+}
+
+__device__ __forceinline__ uint32_t take_rank(const SortLds& L, uint32_t pt) { return atomicAdd(&L.count[pt >> L.tile_bits], 1u) & 0xFFFFu; }
+
+// place of sorted slot p of a tile with first slot `start`: chain position start + place.x, the chunk open there lasts to the
+// next multiple of kChunk
+__device__ __forceinline__ uint32_t record_place(uint32_t p, uint32_t start, uint2 place) {
+    const uint32_t last = start + ((0u - (start + place.x)) & ((uint32_t)kChunk - 1u));
+    return p + (p < last ? place.x : place.y);
+}
+// chain position after the round: one past the place of its last record
+__device__ __forceinline__ uint32_t chain_position(uint32_t count, uint32_t start, uint2 place) {
+    return count ? record_place(start + count - 1u, start, place) + 1u : start + place.x;
+}
+
 // One round of the binned scatter for a workgroup of BS lanes.  Every lane brings up to NR records
 // (valid[k], destination pt[k], force (fx[k], fy[k]), rank[k] from take_rank).  The records are
 // counting-sorted by tile in LDS and appended to the (workgroup, tile) chains with consecutive lanes
-// on consecutive records.  FLUSH_ITERS * BS bounds the records of one round.  All lanes must call.
-template <int NR, int BS, int FLUSH_ITERS>
-__device__ __forceinline__ void sort_and_flush(const BinLds& L, const BinArgs& Q, uint32_t pool_end, uint32_t* pool_cursor,
+// on consecutive records.  All lanes must call.
+//
+// A round of a million-point problem takes 11 us without any memory traffic, so its phases are made short: four barriers,
+// none between the writing of one round and the arithmetic of the next (counts are taken over and cleared before the
+// records are placed); chunks are handed out with one LDS atomic per wavefront (a divergent atomicAdd becomes a loop over
+// the lanes); a record's address is its slot plus one of two numbers of its tile, in 32 bits.
+template <int NR, int BS>
+__device__ __forceinline__ void sort_and_flush(const SortLds& L, const BinArgs& Q, uint32_t pool_begin, uint32_t pool_end, uint32_t* pool_cursor,
                                                uint32_t* wave_total, const bool (&valid)[NR], const uint32_t (&pt)[NR],
                                                const uint32_t (&rank)[NR], const float (&fx)[NR], const float (&fy)[NR]) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t B = L.B;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t B = L.B, chunks = pool_end - pool_begin;
     const int tb = L.tile_bits;
     const uint32_t per = (B + BS - 1) / BS;   // tiles owned by one thread, contiguous
-    const uint32_t b0 = min(B, (uint32_t)tid * per), b1 = min(B, b0 + per);
-    lds_barrier();
-    // ---- exclusive scan of the per-tile counts
-    uint32_t cnt_own[kMaxBinsPerThread];
+    const uint32_t b0 = (uint32_t)tid * per;
+    const bool owns = (uint32_t)wave * 64u * per < B;   // this wavefront has tiles
+    lds_barrier();   // the counts are complete; tables and records of the last round have been read
     uint32_t own_sum = 0;
-#pragma unroll
-    for (int x = 0; x < kMaxBinsPerThread; ++x) {
-        cnt_own[x] = (b0 + x < b1) ? L.start[b0 + x] : 0u;
-        own_sum += cnt_own[x];
-    }
-    uint32_t incl = own_sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t u = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += u;
-    }
+    if (owns)
+        for (uint32_t x = 0; x < per; ++x) own_sum += b0 + x < B ? L.count[b0 + x] & 0xFFFFu : 0u;
+    const uint32_t incl = wave_prefix(own_sum);
     if (lane == 63) wave_total[wave] = incl;
     lds_barrier();
-    uint32_t run = incl - own_sum;
-    for (int v = 0; v < wave; ++v) run += wave_total[v];
-    if (tid == BS - 1) L.start[B] = run + own_sum;
-    // tiles whose open chunk cannot take this round's records get new chunks, linked to the chain
-#pragma unroll
-    for (int x = 0; x < kMaxBinsPerThread; ++x) {
-        const uint32_t b = b0 + x;
-        if (b < b1) {
-            const uint32_t c = cnt_own[x];
-            L.start[b] = run;
-            run += c;
-            const uint32_t fl = L.fill[b];
-            if (c != 0 && fl + c > (uint32_t)kChunk) {
-                const uint32_t k = (fl + c - 1) / kChunk;
-                const uint32_t nb = atomicAdd(pool_cursor, k);
-                L.base[b] = nb;
-                if (nb + k > pool_end) *Q.overflow = 1;
-                uint32_t prev = L.chunk[b];
-                for (uint32_t y = 0; y < k && nb + y < pool_end; ++y) { Q.chunk_prev[nb + y] = prev; prev = nb + y; }
+    const uint32_t waves_incl = wave_prefix(lane < BS / 64 ? wave_total[lane] : 0u);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)waves_incl, BS / 64 - 1);
+    if (owns) {
+        uint32_t run = incl - own_sum;
+        if (wave > 0) run += (uint32_t)__builtin_amdgcn_readlane((int)waves_incl, wave - 1);
+        for (uint32_t x = 0; x < per; ++x) {
+            const uint32_t b = b0 + x;
+            const bool own = b < B;
+            const uint32_t both = own ? L.count[b] : 0u, c = both & 0xFFFFu;
+            const uint32_t at = own ? chain_position(both >> 16, L.start[b], L.place[b]) : 0u;
+            const uint32_t room = (0u - at) & ((uint32_t)kChunk - 1u);
+            // a chain whose open chunk cannot take this round's records gets new chunks, linked to it
+            const uint32_t k = c > room ? (c - room + kChunk - 1) / kChunk : 0u;
+            const uint32_t k_incl = wave_prefix(k), k_all = (uint32_t)__builtin_amdgcn_readlane((int)k_incl, 63);
+            uint32_t first = 0;
+            if (k_all) {
+                if (lane == 0) first = atomicAdd(pool_cursor, k_all);
+                first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first) + k_incl - k;
+                if (first + k > chunks) *Q.overflow = 1;
+                uint32_t prev = at ? pool_begin + (at - 1u) / kChunk : kNoChunk;
+                for (uint32_t y = 0; y < k && first + y < chunks; ++y) { Q.chunk_prev[pool_begin + first + y] = prev; prev = pool_begin + first + y; }
+            }
+            if (own) {
+                L.count[b] = c << 16;
+                L.start[b] = run;
+                L.place[b] = make_uint2(at - run, first * kChunk - run - room);
+                run += c;
             }
         }
     }
@@ -908,46 +988,42 @@ __device__ __forceinline__ void sort_and_flush(const BinLds& L, const BinArgs& Q
     }
     lds_barrier();
     // ---- consecutive lanes write consecutive sorted records to the chains
-    const uint32_t total = L.start[B];
-#pragma nounroll
-    for (int it = 0; it < FLUSH_ITERS; ++it) {
-        const uint32_t p = (uint32_t)tid + (uint32_t)it * BS;
-        if (p < total) {
-            const uint32_t dpt = L.rec_pt[p];
-            const uint32_t b = dpt >> tb;
-            const uint32_t pos = L.fill[b] + (p - L.start[b]);
-            uint32_t ch, off;
-            if (pos < (uint32_t)kChunk) { ch = L.chunk[b]; off = pos; }
-            else { ch = L.base[b] + (pos - kChunk) / kChunk; off = (pos - kChunk) % kChunk; }
-            if (ch < pool_end) {   // kNoChunk is above any valid id
-                uint32_t* dst = Q.pool + ((size_t)ch * kChunk + off) * 3;
-                dst[0] = dpt & ((1u << tb) - 1u);
-                dst[1] = L.rec_x[p];
-                dst[2] = L.rec_y[p];
-            }
-        }
-    }
-    lds_barrier();
-    // ---- chain state after this round; counts back to zero
+    char* const out = (char*)(Q.pool + (size_t)pool_begin * kChunk * 3);
+    const uint32_t limit = chunks * kChunk - 1u, mask = (1u << tb) - 1u;
+    const auto write = [&](auto count, uint32_t p0) {   // `count` records per lane, their loads in flight together
+        constexpr int U = decltype(count)::value;
+        uint32_t d[U], x[U], y[U], st[U];
+        uint2 pl[U];
 #pragma unroll
-    for (int x = 0; x < kMaxBinsPerThread; ++x) {
-        const uint32_t b = b0 + x;
-        if (b < b1) {
-            const uint32_t c = cnt_own[x];
-            if (c != 0) {
-                const uint32_t fl = L.fill[b];
-                if (fl + c > (uint32_t)kChunk) {
-                    const uint32_t k = (fl + c - 1) / kChunk;
-                    L.chunk[b] = L.base[b] + k - 1;
-                    L.fill[b] = fl + c - k * kChunk;
-                } else {
-                    L.fill[b] = fl + c;
-                }
-            }
-            L.start[b] = 0;
+        for (int u = 0; u < U; ++u) { d[u] = L.rec_pt[p0 + u * BS]; x[u] = L.rec_x[p0 + u * BS]; y[u] = L.rec_y[p0 + u * BS]; }
+#pragma unroll
+        for (int u = 0; u < U; ++u) { st[u] = L.start[d[u] >> tb]; pl[u] = L.place[d[u] >> tb]; }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t at = min(record_place(p0 + u * BS, st[u], pl[u]), limit);   // (a range that overflowed: flagged, nothing outside it is touched)
+            uint32_t* dst = (uint32_t*)(out + at * 12u);
+            dst[0] = d[u] & mask;
+            dst[1] = x[u];
+            dst[2] = y[u];
         }
+    };
+    uint32_t p = (uint32_t)tid, left = total;
+    for (; left >= 3 * BS; left -= 3 * BS, p += 3 * BS) write(std::integral_constant<int, 3>(), p);
+    for (; left >= BS; left -= BS, p += BS) write(std::integral_constant<int, 1>(), p);
+    if (p < total) write(std::integral_constant<int, 1>(), p);
+    if (Q.split_traffic) lds_barrier();
+}
+
+// the last chunk of every chain and how full it is (end of the edge pass); after the last round's owners have written
+template <int BS>
+__device__ __forceinline__ void publish_sorted_chains(const SortLds& L, const BinArgs& Q, uint32_t pool_begin, uint32_t pool_end) {
+    const uint32_t W = gridDim.x, w = blockIdx.x, per = (L.B + BS - 1) / BS, b0 = min(L.B, threadIdx.x * per), b1 = min(L.B, b0 + per);
+    for (uint32_t b = b0; b < b1; ++b) {
+        const uint32_t at = chain_position(L.count[b] >> 16, L.start[b], L.place[b]), ch = pool_begin + (at - 1u) / kChunk;
+        const bool any = at != 0u && ch < pool_end;
+        Q.chain_head[(size_t)b * W + w] = any ? ch : kNoChunk;
+        Q.chain_fill[(size_t)b * W + w] = any ? at - (at - 1u) / kChunk * kChunk : 0u;
     }
-    lds_barrier();
 }
 
 // The same round without the counting sort, for graphs whose rounds reach few of many tiles (more tiles than a round
@@ -962,17 +1038,7 @@ __device__ __forceinline__ void direct_flush(const BinLds& L, const BinArgs& Q, 
     const uint32_t B = L.B;
     const int tb = L.tile_bits;
     lds_barrier();   // the round's counts are complete
-    for (uint32_t b = threadIdx.x; b < B; b += BS) {
-        const uint32_t c = L.start[b], fl = L.fill[b];
-        if (c != 0 && fl + c > (uint32_t)kChunk) {
-            const uint32_t k = (fl + c - 1) / kChunk;
-            const uint32_t nb = atomicAdd(pool_cursor, k);
-            L.base[b] = nb;
-            if (nb + k > pool_end) *Q.overflow = 1;
-            uint32_t prev = L.chunk[b];
-            for (uint32_t y = 0; y < k && nb + y < pool_end; ++y) { Q.chunk_prev[nb + y] = prev; prev = nb + y; }
-        }
-    }
+    extend_chains<BS>(B, L.start, L.fill, L.chunk, L.base, Q, pool_end, pool_cursor);
     lds_barrier();
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
@@ -1019,7 +1085,16 @@ __device__ __forceinline__ void publish_chains(const BinLds& L, const BinArgs& Q
     }
 }
 
-// Head sum of each row: segmented inclusive scan over the lanes of the row, in lane order.  The last
+// One step of the scan below: what the DPP pattern brings from another lane (0 where it brings nothing), if `take`.
+template <int DPP, int ROWS>
+__device__ __forceinline__ void head_scan_step(float& hx, float& hy, bool take) {
+    const float ux = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(hx), DPP, ROWS, 0xf, true));
+    const float uy = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(hy), DPP, ROWS, 0xf, true));
+    hx += take ? ux : 0.f;
+    hy += take ? uy : 0.f;
+}
+
+// Head sum of each row: segmented inclusive scan over the lanes of the row.  The last
 // lane of a row then holds the row's sum; it is stored directly when the whole row lies inside this
 // wavefront (positions wave_e0 .. wave_e0+63, below e_end), else it has to be handed on as a record
 // (returns true on that lane).  A row is a run of consecutive CSR positions ea .. eb-1, so the first lane of a
@@ -1029,11 +1104,14 @@ __device__ __forceinline__ bool reduce_head_sums(const BinArgs& Q, bool has, int
     const int lane = threadIdx.x & 63;
     const int64_t wave_e0 = e64 - lane;
     const int seg0 = has ? (int)max((int64_t)ea - wave_e0, (int64_t)0) : lane;   // first lane of this lane's row
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const float ux = __shfl_up(hx, d, 64), uy = __shfl_up(hy, d, 64);
-        if (lane - d >= seg0) { hx += ux; hy += uy; }
-    }
+    // inside rows of 16 lanes, then the last lane of row 0 (2) into row 1 (3), then lane 31 into the upper half
+    const int behind = lane - seg0;   // lanes of this row before this one
+    head_scan_step<0x111, 0xf>(hx, hy, behind >= 1);
+    head_scan_step<0x112, 0xf>(hx, hy, behind >= 2);
+    head_scan_step<0x114, 0xf>(hx, hy, behind >= 4);
+    head_scan_step<0x118, 0xf>(hx, hy, behind >= 8);
+    head_scan_step<0x142, 0xa>(hx, hy, behind > (lane & 15));
+    head_scan_step<0x143, 0xc>(hx, hy, behind > (lane & 31));
     const bool row_end = has && (lane == 63 || e64 + 1 >= min((int64_t)eb, e_end));
     const bool inside = (int64_t)ea >= wave_e0 && (int64_t)eb <= min(wave_e0 + 64, e_end);
     if (row_end && inside) Q.ghead[i] = make_float2(hx, hy);
@@ -1041,44 +1119,74 @@ __device__ __forceinline__ bool reduce_head_sums(const BinArgs& Q, bool has, int
 }
 
 // What one lane has in flight for its edge of the next round: issued a round ahead, so that the
-// gathers of round r+1 are served while round r is being sorted and written out.  GATHER: also the
-// rows of the negatives (i.i.d. sampler); the pooled sampler reads them from its pool in LDS.
-template <int S, bool GATHER>
+// gathers of round r+1 are served while round r is being sorted and written out.  Nothing here is computed from another
+// of these loads (the head's constants are, when the round comes: head_of_fetch): an operand would be waited for where
+// it is used, and the round's loads would go out one after the other.
+template <int S>
 struct EdgeFetch {
     bool has;
     int32_t e, i, j, ea, eb;
     float pe;
-    HeadCtx h;
+    float2 ti;
+    float4 hi;                      // groups: the head's hinfo, fetched a round before the rest
+    float A;
+    float2 B;
     int32_t m[S > 0 ? S : 1];
     float2 tj, tm[S > 0 ? S : 1];   // sampled far field: tm[k].x carries the cell of m[k] until the round resolves it
 };
 
-template <int S, bool GATHER>
-__device__ __forceinline__ void issue_edge(const EdgeArgs& P, bool has, int32_t e, int32_t i, int32_t j, EdgeFetch<S, GATHER>& f) {
+template <int S>
+__device__ __forceinline__ void issue_edge(const EdgeArgs& P, bool has, int32_t e, int32_t i, int32_t j, const float4& hi, bool split_traffic, EdgeFetch<S>& f) {
     f.has = has;
-    f.e = e; f.i = has ? i : -1; f.j = j; f.ea = 0; f.eb = 0; f.pe = 0.f;
+    f.e = e; f.i = has ? i : -1; f.j = j; f.ea = 0; f.eb = 0;
     if (!has) return;
     f.ea = P.row_ptr[i];
     f.eb = P.row_ptr[i + 1];
-    f.h = load_head(P, i, f.ea, f.eb);
+    f.ti = P.theta[i];
     f.tj = P.theta[j];
-    f.pe = P.pe ? P.pe[e] : f.h.inv_deg;
-    if (GATHER) {
-        draw_negatives<S>(P, f.h.pop, e, f.m);
-        if (P.far) {
-#pragma unroll
-            for (int k = 0; k < S; ++k) f.tm[k] = make_float2(__int_as_float(P.cluster_of[f.m[k]]), 0.f);
-        } else {
-#pragma unroll
-            for (int k = 0; k < S; ++k) f.tm[k] = P.theta[f.m[k]];
+    if (P.pe) f.pe = P.pe[e];
+    Population pop = {0u, (uint32_t)P.n, nullptr};
+    if (P.group_of_cluster) {
+        f.hi = hi;
+        if (!P.far) {
+            pop = {__float_as_uint(hi.x), __float_as_uint(hi.y), P.gmembers};
+            f.A = P.A[i];
+            f.B = P.B[i];
         }
     }
+    if (split_traffic) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    draw_negatives<S>(P, pop, e, f.m);
+    if (P.far) {
+#pragma unroll
+        for (int k = 0; k < S; ++k) f.tm[k] = make_float2(__int_as_float(P.cluster_of[f.m[k]]), 0.f);
+    } else {
+#pragma unroll
+        for (int k = 0; k < S; ++k) f.tm[k] = P.theta[f.m[k]];
+    }
+}
+
+// the head's constants from what has arrived (load_head's, without its loads)
+template <int S>
+__device__ __forceinline__ HeadCtx head_of_fetch(const EdgeArgs& P, const EdgeFetch<S>& f) {
+    HeadCtx h;
+    h.ti = f.ti;
+    h.inv_deg = f.eb > f.ea ? 1.0f / (float)(f.eb - f.ea) : 0.f;
+    h.MA = h.MBx = h.MBy = 0.f;
+    h.group = P.group_of_cluster ? __float_as_int(f.hi.w) : 0;
+    h.omega = P.omega0;
+    if (P.group_of_cluster && !P.far) {
+        h.omega = f.hi.z;
+        h.MA = P.noise_count * f.A;
+        h.MBx = P.noise_count * f.B.x;
+        h.MBy = P.noise_count * f.B.y;
+    }
+    return h;
 }
 
 // Sampled far field: with the cells of the negatives in hand, fetch what each stands for: the mean of its cell
 // when the cell belongs to another group than the head's (then m = -1: no force goes back), else its own row.
 template <int S>
-__device__ __forceinline__ void resolve_far_negatives(const EdgeArgs& P, EdgeFetch<S, true>& f) {
+__device__ __forceinline__ void resolve_far_negatives(const EdgeArgs& P, int32_t group, EdgeFetch<S>& f) {
     int32_t grp[S > 0 ? S : 1];
     float2 mean[S > 0 ? S : 1];
 #pragma unroll
@@ -1089,27 +1197,37 @@ __device__ __forceinline__ void resolve_far_negatives(const EdgeArgs& P, EdgeFet
     }
 #pragma unroll
     for (int k = 0; k < S; ++k) {
-        if (grp[k] != f.h.group) { f.tm[k] = mean[k]; f.m[k] = -1; }
+        if (grp[k] != group) { f.tm[k] = mean[k]; f.m[k] = -1; }
         else f.tm[k] = P.theta[f.m[k]];
     }
 }
 
-template <int S, int BS, bool SORT = true, int ROUNDS = 1>
-__global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs P, const BinArgs Q) {
-    static_assert(!SORT || ROUNDS == 1, "the sorted form stages one round's records in LDS");
+// PLAIN: one population, i.i.d. negatives, no gradient through the means (what most programs run): the options' registers and branches go.
+template <int S, int BS, bool SORT = true, int ROUNDS = 1, bool PLAIN = false>
+__global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs args, const BinArgs Q) {
+    EdgeArgs P = args;
+    if (PLAIN) { P.pool_size = 0; P.group_of_cluster = nullptr; P.far = 0; P.cS = nullptr; }
     constexpr int SS = S > 0 ? S : 1;
     constexpr int kWaves = BS / 64;
-    constexpr int NREC = BS * (S + 1) + 2 * kWaves;
+    constexpr int NREC = ROUNDS * (BS * (S + 1) + 2 * kWaves);
     constexpr int NR = S + 2;   // per lane and round: the tail, the negatives, and possibly a partial head sum
     extern __shared__ uint32_t lds_bins[];
-    const BinLds L = carve_bin_lds(lds_bins, Q.n_bins, SORT ? NREC : 0, Q.tile_bits);
+    using Tables = std::conditional_t<SORT, SortLds, BinLds>;
+    Tables L;
     __shared__ uint32_t wave_total[kWaves];
     __shared__ uint32_t pool_cursor;
     const int tid = threadIdx.x;
     const uint32_t W = gridDim.x, w = blockIdx.x;
-    const uint32_t pool_end = min(Q.wg_pool_begin[w + 1], Q.max_chunks);
-    init_bin_lds<BS>(L);
-    if (tid == 0) pool_cursor = Q.wg_pool_begin[w];
+    const uint32_t pool_begin = Q.wg_pool_begin[w], pool_end = min(Q.wg_pool_begin[w + 1], Q.max_chunks);
+    if constexpr (SORT) {
+        L = carve_sort_lds(lds_bins, Q.n_bins, NREC, Q.tile_bits);
+        for (uint32_t b = tid; b < 4u * Q.n_bins; b += BS) lds_bins[b] = 0u;   // the tables
+        if (tid == 0) pool_cursor = 0u;
+    } else {
+        L = carve_bin_lds(lds_bins, Q.n_bins, 0, Q.tile_bits);
+        init_bin_lds<BS>(L);
+        if (tid == 0) pool_cursor = pool_begin;
+    }
     lds_barrier();
 
     // The CSR positions are dealt to the workgroups in slabs of BS positions, round-robin: slab w, w + W, ...
@@ -1117,19 +1235,26 @@ __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs P, const Bin
     // graph, which keeps the chains the tile pass walks equally long).
     const int64_t n_slabs = (Q.e_end - Q.e_begin + BS - 1) / BS;
     const int64_t stride = (int64_t)W * BS;
-    // Software pipeline over rounds: (head, tail) indices are read two rounds ahead, the embedding rows
-    // one round ahead.
-    EdgeFetch<S, true> f;
-    int32_t i_next = 0, j_next = 0;
+    // Software pipeline over rounds: (head, tail) indices are read two rounds ahead (with groups three, and the heads' group
+    // information, on which the negatives depend, two), the embedding rows one round ahead.
+    EdgeFetch<S> f;
+    int32_t i1 = 0, j1 = 0, i2 = 0, j2 = 0;   // the next round's; with groups also the one's after
+    float4 hi1 = make_float4(0.f, 0.f, 0.f, 0.f);
     {
-        const int64_t e0 = Q.e_begin + (int64_t)w * BS + tid, e1 = e0 + stride;
+        const int64_t e0 = Q.e_begin + (int64_t)w * BS + tid, e1 = e0 + stride, e2 = e1 + stride;
         int32_t i0 = 0, j0 = 0;
+        float4 hi0 = hi1;
         if (e0 < Q.e_end) { i0 = Q.head[e0]; j0 = P.col[e0]; }
-        if (e1 < Q.e_end) { i_next = Q.head[e1]; j_next = P.col[e1]; }
-        issue_edge<S, true>(P, e0 < Q.e_end, (int32_t)e0, i0, j0, f);
+        if (e1 < Q.e_end) { i1 = Q.head[e1]; j1 = P.col[e1]; }
+        if (P.group_of_cluster) {
+            if (e2 < Q.e_end) { i2 = Q.head[e2]; j2 = P.col[e2]; }
+            hi0 = P.hinfo[i0];
+            hi1 = P.hinfo[i1];
+        }
+        issue_edge<S>(P, e0 < Q.e_end, (int32_t)e0, i0, j0, hi0, false, f);
     }
-    // The unsorted form takes ROUNDS rounds between two flushes (no barrier in between: a record only takes its rank
-    // from the tile's counter when it is made); slabs past the end are empty rounds.
+    // ROUNDS rounds between two flushes (no barrier in between: a record only takes its rank from the tile's counter when
+    // it is made); slabs past the end are empty rounds.
     for (int64_t slab0 = w; slab0 < n_slabs; slab0 += (int64_t)W * ROUNDS) {
         bool valid[NR * ROUNDS];
         uint32_t dst_pt[NR * ROUNDS], rank[NR * ROUNDS];
@@ -1147,9 +1272,10 @@ __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs P, const Bin
             for (int k = 0; k < NR; ++k) { valid[base + k] = k <= S && has; dst_pt[base + k] = 0u; rank[base + k] = 0u; fx[base + k] = 0.f; fy[base + k] = 0.f; }
             float hx = 0.f, hy = 0.f;
             if (has) {
-                if (P.far) resolve_far_negatives<S>(P, f);
+                const HeadCtx h = head_of_fetch(P, f);
+                if (P.far) resolve_far_negatives<S>(P, h.group, f);
                 EdgeOut<SS> o;
-                edge_math<S, false>(f.h, f.pe, f.tj, f.tm, o);
+                edge_math<S, false>(h, P.pe ? f.pe : h.inv_deg, f.tj, f.tm, o);
                 hx = o.hx;
                 hy = o.hy;
                 if (P.cS) P.cS[f.e] = o.c;
@@ -1164,10 +1290,17 @@ __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs P, const Bin
             }
             // the loads of the next round go out before this round is sorted and written
             {
-                const int64_t e1 = e64 + stride, e2 = e1 + stride;
-                const int32_t i1 = i_next, j1 = j_next;
-                if (e2 < Q.e_end) { i_next = Q.head[e2]; j_next = P.col[e2]; }
-                issue_edge<S, true>(P, e1 < Q.e_end, (int32_t)e1, i1, j1, f);
+                const int64_t e1 = e64 + stride, e2 = e1 + stride, e3 = e2 + stride;
+                const int32_t i0 = i1, j0 = j1;
+                const float4 hi0 = hi1;
+                if (P.group_of_cluster) {
+                    i1 = i2; j1 = j2;
+                    hi1 = P.hinfo[i1];
+                    if (e3 < Q.e_end) { i2 = Q.head[e3]; j2 = P.col[e3]; }
+                } else if (e2 < Q.e_end) {
+                    i1 = Q.head[e2]; j1 = P.col[e2];
+                }
+                issue_edge<S>(P, e1 < Q.e_end, (int32_t)e1, i0, j0, hi0, Q.split_traffic, f);
             }
             valid[base + S + 1] = reduce_head_sums(Q, has, i, ea, eb, e64, e_end, hx, hy);
             dst_pt[base + S + 1] = valid[base + S + 1] ? (uint32_t)i : 0u;
@@ -1177,10 +1310,11 @@ __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs P, const Bin
             for (int k = 0; k < NR; ++k)
                 if (valid[base + k]) rank[base + k] = take_rank(L, dst_pt[base + k]);
         }
-        if (SORT) sort_and_flush<NR * ROUNDS, BS, (NREC + BS - 1) / BS>(L, Q, pool_end, &pool_cursor, wave_total, valid, dst_pt, rank, fx, fy);
+        if constexpr (SORT) sort_and_flush<NR * ROUNDS, BS>(L, Q, pool_begin, pool_end, &pool_cursor, wave_total, valid, dst_pt, rank, fx, fy);
         else direct_flush<NR * ROUNDS, BS>(L, Q, pool_end, &pool_cursor, valid, dst_pt, rank, fx, fy);
     }
-    publish_chains<BS>(L, Q, pool_end);
+    if constexpr (SORT) publish_sorted_chains<BS>(L, Q, pool_begin, pool_end);
+    else publish_chains<BS>(L, Q, pool_end);
 }
 
 // ------------------------------------------------------------------ K3 + K4 with the pooled sampler
@@ -1195,22 +1329,24 @@ __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs P, const Bin
 constexpr int kMaxPoolPerLane = 4;   // pool entries one lane fetches and hands on: pool_size <= 4 * workgroup size
 
 
+// Bounds of a row, kept as the pair they are loaded as: taking one of them out of the pair is a use, so a copy of `end` made
+// where the loads are issued (to its register in the next round) waited there for all of them.
+typedef int32_t RowBounds __attribute__((ext_vector_type(2), aligned(4)));
+
 // What a lane of the pooled edge pass has in flight for its next edge (no groups there: one population, no mean field).
 struct PoolFetch {
     bool has;
-    int32_t e, i, j, ea, eb;
+    int32_t e, i, j;
+    RowBounds row;
     float pe;
     float2 ti, tj;
 };
 
 __device__ __forceinline__ void issue_pool_edge(const EdgeArgs& P, bool has, int32_t e, int32_t i, int32_t j, PoolFetch& f) {
     f.has = has;
-    f.e = e; f.i = has ? i : -1; f.j = j; f.ea = 0; f.eb = 0; f.pe = 0.f;
-    f.ti = make_float2(0.f, 0.f);
-    f.tj = make_float2(0.f, 0.f);
+    f.e = e; f.i = has ? i : -1; f.j = j;
     if (!has) return;
-    f.ea = P.row_ptr[i];
-    f.eb = P.row_ptr[i + 1];
+    f.row = *(const RowBounds*)(P.row_ptr + i);
     f.ti = P.theta[i];
     f.tj = P.theta[j];
     if (P.pe) f.pe = P.pe[e];
@@ -1224,7 +1360,8 @@ __global__ void __launch_bounds__(BS) k_edges_pooled(const EdgeArgs P, const Bin
     extern __shared__ unsigned long long lds_pool[];
     const uint32_t PS = P.pool_size, B = Q.n_bins;
     const int tb = Q.tile_bits;
-    unsigned long long* pool_acc = lds_pool;                         // [2 PS] fixed-point force sums
+    unsigned long long* pool_acc = lds_pool;                         // [2 PS] fixed-point force sums: x, then y (side by side
+                                                                     // a wavefront's x sums would share half of the banks)
     float2* pool_th = (float2*)(pool_acc + 2 * (size_t)PS);          // [PS] embedding rows of the pool
     uint32_t* pool_pt = (uint32_t*)(pool_th + PS);                   // [PS] the points
     uint32_t* cnt = pool_pt + PS;                                    // [B] records of this block per tile
@@ -1314,7 +1451,7 @@ __global__ void __launch_bounds__(BS) k_edges_pooled(const EdgeArgs P, const Bin
         for (int r = 0; r < ROUNDS; ++r) {
             const int64_t e64 = blk * G + (int64_t)r * BS + tid;
             const bool has = f.has;
-            const int32_t i = f.i, ea = f.ea, eb = f.eb;
+            const int32_t i = f.i, ea = f.row.x, eb = f.row.y;
             float hx = 0.f, hy = 0.f;
             tv[r] = has; tpt[r] = 0u; trk[r] = 0u; tfx[r] = 0.f; tfy[r] = 0.f;
             if (has) {
@@ -1335,8 +1472,8 @@ __global__ void __launch_bounds__(BS) k_edges_pooled(const EdgeArgs P, const Bin
                 hy = o.hy;
 #pragma unroll
                 for (int k = 0; k < S; ++k) {
-                    atomicAdd(&pool_acc[2 * slot[k]], to_fixed(o.rx[k]));
-                    atomicAdd(&pool_acc[2 * slot[k] + 1], to_fixed(o.ry[k]));
+                    atomicAdd(&pool_acc[slot[k]], to_fixed(o.rx[k]));
+                    atomicAdd(&pool_acc[PS + slot[k]], to_fixed(o.ry[k]));
                 }
                 tpt[r] = (uint32_t)f.j; tfx[r] = -o.a * o.dx; tfy[r] = -o.a * o.dy;
                 trk[r] = atomicAdd(&cnt[tpt[r] >> tb], 1u);
@@ -1363,11 +1500,11 @@ __global__ void __launch_bounds__(BS) k_edges_pooled(const EdgeArgs P, const Bin
             const uint32_t u = (uint32_t)tid + (uint32_t)k * BS;
             pv[k] = false; ppt[k] = 0u; prk[k] = 0u; pfx[k] = 0.f; pfy[k] = 0.f;
             if (u < PS) {
-                const long long ax = (long long)pool_acc[2 * u], ay = (long long)pool_acc[2 * u + 1];
+                const long long ax = (long long)pool_acc[u], ay = (long long)pool_acc[PS + u];
                 pv[k] = (ax | ay) != 0;
                 if (pv[k]) {
-                    pool_acc[2 * u] = 0ull;
-                    pool_acc[2 * u + 1] = 0ull;
+                    pool_acc[u] = 0ull;
+                    pool_acc[PS + u] = 0ull;
                     ppt[k] = pool_pt[u];
                     pfx[k] = (float)((double)ax * kFixInv);
                     pfy[k] = (float)((double)ay * kFixInv);
@@ -1380,18 +1517,7 @@ __global__ void __launch_bounds__(BS) k_edges_pooled(const EdgeArgs P, const Bin
         float sx = 0.f, sy = 0.f;
         if (sv) { spt = side_pt[tid]; sx = side_x[tid]; sy = side_y[tid]; srk = atomicAdd(&cnt[spt >> tb], 1u); }
         lds_barrier();   // the counts are complete
-        // ---- tiles whose open chunk cannot take this block's records get new chunks, linked to the chain
-        for (uint32_t b = tid; b < B; b += BS) {
-            const uint32_t c = cnt[b], fl = fill[b];
-            if (c != 0 && fl + c > (uint32_t)kChunk) {
-                const uint32_t k = (fl + c - 1) / kChunk;
-                const uint32_t nb = atomicAdd(&pool_cursor, k);
-                base[b] = nb;
-                if (nb + k > pool_end) *Q.overflow = 1;
-                uint32_t prev = chunk[b];
-                for (uint32_t y = 0; y < k && nb + y < pool_end; ++y) { Q.chunk_prev[nb + y] = prev; prev = nb + y; }
-            }
-        }
+        extend_chains<BS>(B, cnt, fill, chunk, base, Q, pool_end, &pool_cursor);
         lds_barrier();
         // ---- every lane writes its own records
 #pragma unroll
@@ -1437,7 +1563,8 @@ __global__ void __launch_bounds__(BS) k_edges_pooled(const EdgeArgs P, const Bin
 
 struct DistinctFetch {   // what a lane has in flight for its edge of the next round
     bool has;
-    uint32_t e, i, j, ea, eb;
+    uint32_t e, i, j;
+    RowBounds row;
     float pe;
     float2 ti, tj;
 };
@@ -1458,7 +1585,8 @@ __global__ void __launch_bounds__(1024) k_edges_pooled_distinct(const EdgeArgs P
     const uint32_t line_bits = P.pool_line_bits, seg_bits = P.pool_segment_bits;
     const uint32_t L = PS >> line_bits, lg_lines = 31u - (uint32_t)__clz(L);
     const int tb = Q.tile_bits;
-    unsigned long long* pool_acc = lds_pool;                         // [2 PS] fixed-point force sums
+    unsigned long long* pool_acc = lds_pool;                         // [2 PS] fixed-point force sums: x, then y (side by side
+                                                                     // a wavefront's x sums would share half of the banks)
     float2* pool_th = (float2*)(pool_acc + 2 * (size_t)PS);          // [PS] embedding rows of the pool
     uint32_t* pool_pt = (uint32_t*)(pool_th + PS);                   // [PS] the points
     uint32_t* line_start = pool_pt + PS;                             // [L] first point of every line of the NEXT block
@@ -1524,12 +1652,9 @@ __global__ void __launch_bounds__(1024) k_edges_pooled_distinct(const EdgeArgs P
         return e;
     };
     auto issue = [&](bool has, uint32_t e, uint32_t i, uint32_t j, DistinctFetch& f) {
-        f.has = has; f.e = e; f.i = i; f.j = j; f.ea = 0; f.eb = 0; f.pe = 0.f;
-        f.ti = make_float2(0.f, 0.f);
-        f.tj = make_float2(0.f, 0.f);
+        f.has = has; f.e = e; f.i = i; f.j = j;
         if (!has) return;
-        f.ea = (uint32_t)load_at(P.row_ptr, i);
-        f.eb = (uint32_t)load_at(P.row_ptr + 1, i);
+        f.row = *(const RowBounds*)((const char*)P.row_ptr + (size_t)(i * 4u));
         f.ti = load_at(P.theta, i);
         f.tj = load_at(P.theta, j);
         if (P.pe) f.pe = load_at(P.pe, e);
@@ -1576,7 +1701,7 @@ __global__ void __launch_bounds__(1024) k_edges_pooled_distinct(const EdgeArgs P
         for (int r = 0; r < ROUNDS; ++r) {
             if ((r & 3) == 0) philox4x32_10(blk, kPoolPickStream, P.epoch, tid + 1024u * (uint32_t)(r >> 2), P.key0, P.key1, wd);
             const bool has = f.has;
-            const uint32_t e = f.e, i = f.i, ea = f.ea, eb = f.eb;
+            const uint32_t e = f.e, i = f.i, ea = (uint32_t)f.row.x, eb = (uint32_t)f.row.y;
             float hx = 0.f, hy = 0.f;
             tv[r] = has; tpt[r] = 0u; trk[r] = 0u; tfx[r] = 0.f; tfy[r] = 0.f;
             if (has) {
@@ -1593,8 +1718,8 @@ __global__ void __launch_bounds__(1024) k_edges_pooled_distinct(const EdgeArgs P
                 hy = o.hy;
 #pragma unroll
                 for (int k = 0; k < S; ++k) {
-                    atomicAdd(&pool_acc[2 * slot[k]], to_fixed(o.rx[k]));
-                    atomicAdd(&pool_acc[2 * slot[k] + 1], to_fixed(o.ry[k]));
+                    atomicAdd(&pool_acc[slot[k]], to_fixed(o.rx[k]));
+                    atomicAdd(&pool_acc[PS + slot[k]], to_fixed(o.ry[k]));
                 }
                 tpt[r] = f.j; tfx[r] = -o.a * o.dx; tfy[r] = -o.a * o.dy;
                 trk[r] = atomicAdd(&cnt[tpt[r] >> tb], 1u);
@@ -1624,11 +1749,11 @@ __global__ void __launch_bounds__(1024) k_edges_pooled_distinct(const EdgeArgs P
             pv[k] = false; ppt[k] = 0u; prk[k] = 0u; pfx[k] = 0.f; pfy[k] = 0.f;
             if (idx < PS) {
                 const uint32_t u = entry_of(idx);
-                const long long ax = (long long)pool_acc[2 * u], ay = (long long)pool_acc[2 * u + 1];
+                const long long ax = (long long)pool_acc[u], ay = (long long)pool_acc[PS + u];
                 pv[k] = (ax | ay) != 0;
                 if (pv[k]) {
-                    pool_acc[2 * u] = 0ull;
-                    pool_acc[2 * u + 1] = 0ull;
+                    pool_acc[u] = 0ull;
+                    pool_acc[PS + u] = 0ull;
                     ppt[k] = pool_pt[u];
                     pfx[k] = (float)((double)ax * kFixInv);
                     pfy[k] = (float)((double)ay * kFixInv);
@@ -1642,18 +1767,7 @@ __global__ void __launch_bounds__(1024) k_edges_pooled_distinct(const EdgeArgs P
         if (sv) { spt = side_pt[tid]; sx = side_x[tid]; sy = side_y[tid]; srk = atomicAdd(&cnt[spt >> tb], 1u); }
         fetch_pool(blk + W);
         lds_barrier();   // the counts are complete
-        // ---- tiles whose open chunk cannot take this block's records get new chunks, linked to the chain
-        for (uint32_t b = tid; b < B; b += BS) {
-            const uint32_t c = cnt[b], fl = fill[b];
-            if (c != 0 && fl + c > (uint32_t)kChunk) {
-                const uint32_t k = (fl + c - 1) / kChunk;
-                const uint32_t nb = atomicAdd(&pool_cursor, k);
-                base[b] = nb;
-                if (nb + k > pool_end) *Q.overflow = 1;
-                uint32_t prev = chunk[b];
-                for (uint32_t y = 0; y < k && nb + y < pool_end; ++y) { Q.chunk_prev[nb + y] = prev; prev = nb + y; }
-            }
-        }
+        extend_chains<BS>(B, cnt, fill, chunk, base, Q, pool_end, &pool_cursor);
         lds_barrier();
         // ---- every lane writes its own records
 #pragma unroll
@@ -1840,7 +1954,7 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_accumulate(const BinArgs Q, 
                                                               float2* __restrict__ theta, float eta,
                                                               const int32_t* __restrict__ cluster_of, const float2* __restrict__ gmean,
                                                               unsigned long long* __restrict__ carry, int phase) {
-    extern __shared__ unsigned long long acc[];   // [2 << tile_bits]
+    extern __shared__ unsigned long long acc[];   // [2 << tile_bits]: x, then y
     constexpr int kPerLane = kChunk / 64;         // records one lane takes from a full chunk
     const uint32_t b = blockIdx.x;
     const int tile = 1 << Q.tile_bits;
@@ -1887,8 +2001,8 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_accumulate(const BinArgs Q, 
                         const uint32_t r = (uint32_t)u * 64u + lane;
                         if (r < cnt[k]) {
                             const uint32_t ml = rec[k][u][0] & (uint32_t)(tile - 1);
-                            atomicAdd(&acc[2 * ml], to_fixed(__uint_as_float(rec[k][u][1])));
-                            atomicAdd(&acc[2 * ml + 1], to_fixed(__uint_as_float(rec[k][u][2])));
+                            atomicAdd(&acc[ml], to_fixed(__uint_as_float(rec[k][u][1])));
+                            atomicAdd(&acc[tile + ml], to_fixed(__uint_as_float(rec[k][u][2])));
                         }
                     }
                     ch[k] = __builtin_amdgcn_readfirstlane(prev[k]);
@@ -1903,19 +2017,19 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_accumulate(const BinArgs Q, 
     if (phase == kPhaseFirst || phase == kPhaseMiddle) {   // not the last phase of the step: carry the sums on
         for (int l = threadIdx.x; l < 2 * tile && 2 * p0 + l < 2 * n; l += kBinBlock) {
             const unsigned long long before = phase == kPhaseMiddle ? carry[2 * p0 + l] : 0ull;
-            carry[2 * p0 + l] = before + acc[l];
+            carry[2 * p0 + l] = before + acc[(l & 1) * tile + (l >> 1)];
         }
         return;
     }
     if (phase == kPhaseLast) {
-        for (int l = threadIdx.x; l < 2 * tile && 2 * p0 + l < 2 * n; l += kBinBlock) acc[l] += carry[2 * p0 + l];
+        for (int l = threadIdx.x; l < 2 * tile && 2 * p0 + l < 2 * n; l += kBinBlock) acc[(l & 1) * tile + (l >> 1)] += carry[2 * p0 + l];
         __syncthreads();
     }
     for (int l = threadIdx.x; l < tile && p0 + l < n; l += kBinBlock) {
         const float2 hd = Q.ghead[p0 + l];
         Q.ghead[p0 + l] = make_float2(0.f, 0.f);   // consumed: rows that hand their head sum on as records rely on this
-        float2 gi = make_float2((float)((double)hd.x + (double)(long long)acc[2 * l] * kFixInv),
-                                (float)((double)hd.y + (double)(long long)acc[2 * l + 1] * kFixInv));
+        float2 gi = make_float2((float)((double)hd.x + (double)(long long)acc[l] * kFixInv),
+                                (float)((double)hd.y + (double)(long long)acc[tile + l] * kFixInv));
         if (gmean) {   // gradient through the means: every member's share of its cell's term
             const float2 gm = gmean[cluster_of[p0 + l]];
             gi.x += gm.x;

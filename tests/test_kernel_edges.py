@@ -107,3 +107,62 @@ def test_principal_axes(n, d):
     theta, st = pca_init(X, 0.0, return_stats=True)
     assert np.allclose(st["eigenvalues"], lam_ref, rtol=1e-10) and st["residual"] <= 1e-9
     assert np.abs(theta - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+# ---------------------------------------------------------------- the edge pass
+def test_coarse_tiles(tmp_path):
+    import json
+    import os
+    import subprocess
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src = tmp_path / "plan.cpp"
+    src.write_text(r'''
+#include <stdio.h>
+#include <stdlib.h>
+#include "edge_plan.h"
+using namespace nomad;
+int main(int, char** argv) {
+    EdgePlanRequest q;
+    q.n = atoll(argv[1]); q.E = 30 * q.n; q.s = atoi(argv[2]); q.pool_size = atoi(argv[3]); q.pool_block = 8192; q.pool_line = 16; q.pool_distinct = true;
+    EdgePlan p = plan_edge_pass(q);
+    const uint32_t before = p.n_bins;
+    coarsen_tiles(p, q.n, q.s, 256);
+    printf("[%d, %u, %u, %d, %d, %d, %zu]\n", p.tile_bits, p.n_bins, before, (int)p.sorted, p.pool_rounds, p.flush_rounds,
+           binned_lds_bytes(p.n_bins, q.s, 1024, p.sorted, p.sorted ? p.flush_rounds : 1));
+}
+''')
+    exe = str(tmp_path / "plan")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(root, "paper_2505_15511_amd", "csrc"), str(src), "-o", exe], check=True)
+    for n, s, pool in [(1, 5, 0), (65_535, 5, 0), (65_536, 5, 0), (65_793, 8, 0), (1_000_000, 5, 0), (2_097_152, 2, 0), (2_097_153, 8, 0),
+                       (10_000_000, 5, 0), (10_000_000, 2, 0), (60_000_000, 2, 0), (3_000_017, 5, 4096)]:
+        bits, bins, before, is_sorted, pool_rounds, rounds, lds = json.loads(subprocess.run([exe, str(n), str(s), str(pool)], check=True, capture_output=True, text=True).stdout)
+        assert (bins - 1) << bits < n <= bins << bits and bins <= before
+        if is_sorted and not pool_rounds:
+            assert (n >> bits) <= 256 or bits == 13
+            assert lds <= 160 * 1024 - 256 and rounds in (1, 2)
+        else:
+            assert bins == before
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [255, 257, 65_537, 140_001])
+@pytest.mark.parametrize("s", [0, 1, 5, 7, 8])
+@pytest.mark.parametrize("grouped", [False, True])
+def test_sorted_records_reach_their_points(n, s, grouped):
+    """The binned path against fixed-point atomics: the same sums of the same forces, head sums in another order."""
+    from paper_2505_15511_amd import PATH_BINNED, PATH_FIXED_ATOMICS, Nomad, workloads
+    R = 9
+    g = workloads.planted_knn_graph(n, R, 6, 0.05, 11 + s, device="cuda")
+    groups = torch.arange(R, dtype=torch.int32, device="cuda") if grouped else None
+    theta = 0.1 * torch.randn(n, 2, generator=torch.Generator().manual_seed(n))
+    grads = []
+    for tune in (None, PATH_FIXED_ATOMICS):
+        nm = Nomad(n, R, s, 5.0, 10, 1.0, 3, tune={"scatter_path": tune} if tune else {})
+        nm.set_graph(g["row_ptr"], g["col_idx"], None, g["cluster_of"], groups)
+        assert nm.scatter_path() == (tune or PATH_BINNED)
+        nm.set_embedding(theta)
+        nm.epoch(0)
+        nm.set_embedding(theta)
+        nm.epoch(1)
+        grads.append(np.asarray(nm.get_gradient(), dtype=np.float64))
+    assert np.abs(grads[0] - grads[1]).max() <= 1e-6 * np.abs(grads[1]).max()
