@@ -104,12 +104,13 @@ inline EdgePlan plan_edge_pass(const EdgePlanRequest& q) {
 // plan_edge_pass makes about a thousand tiles.  The sorted form is better off with as few as still give every compute unit one
 // in the tile pass: the records a round brings to a tile are one contiguous run in memory, and runs of 25 records instead of
 // six end in fewer partial lines (1 M points, s = 5, a thousand tiles -> 245: edge pass 1.26 -> 1.12 ms, tile pass 0.32 -> 0.24;
-// 123 tiles: tile pass 0.31).
-inline void coarsen_tiles(EdgePlan& p, int64_t n, int s, int compute_units) {
+// 123 tiles: tile pass 0.31).  two_rounds: two rounds share a flush where their records fit LDS (half the barriers and table
+// passes: 100 k points 0.149 -> 0.142 ms, 6 M points in groups, s = 2, 4.26 -> 4.06).
+inline void coarsen_tiles(EdgePlan& p, int64_t n, int s, int compute_units, bool two_rounds = true) {
     if (!p.sorted || p.pool_rounds) return;
     while (p.tile_bits < kMaxTileBits && (n >> p.tile_bits) > compute_units) ++p.tile_bits;
     p.n_bins = (uint32_t)((n + ((int64_t)1 << p.tile_bits) - 1) >> p.tile_bits);
-    if (p.bin_block == 1024 && binned_lds_bytes(p.n_bins, s, 1024, true, 2) <= kMaxLdsBytes) p.flush_rounds = 2;
+    if (two_rounds && p.bin_block == 1024 && binned_lds_bytes(p.n_bins, s, 1024, true, 2) <= kMaxLdsBytes) p.flush_rounds = 2;
 }
 
 // Record phases: the edge pass of a step runs over `phases` ranges of positions, each followed by the tile pass, so the

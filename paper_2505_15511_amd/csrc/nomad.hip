@@ -266,14 +266,23 @@ size_t edge_pass_lds_bytes(const nomad_ctx* c) {
                           : binned_lds_bytes(c->n_bins, c->cfg.n_neg, c->bin_block, c->sorted_records, c->flush_rounds);
 }
 
+int edge_kind(const nomad_ctx* c) {
+    if (c->through_means || c->cfg.pool_size > 0) return kAnyEdges;
+    if (!c->grouped) return kPlainEdges;
+    if (c->cfg.far_field == NOMAD_FAR_FIELD_SAMPLED) return kFarEdges;
+    return c->gmembers ? kAnyEdges : kGroupedEdges;
+}
+
 // Calls `fn(kernel)` with the edge-pass kernel that matches the context: number of negatives, sampler, launch shape.
 using EdgePassKernel = void (*)(const EdgeArgs, const BinArgs);
 
 template <int S, typename Fn>
 void with_edge_pass_kernel_s(const nomad_ctx* c, Fn fn) {
-    const bool plain = !c->grouped && !c->through_means && c->cfg.pool_size == 0;
-    EdgePassKernel k = plain ? k_edges_binned<S, 1024, true, 1, true> : k_edges_binned<S, 1024>;
-    if (c->sorted_records && c->flush_rounds == 2) k = plain ? k_edges_binned<S, 1024, true, 2, true> : k_edges_binned<S, 1024, true, 2>;
+    const int kind = edge_kind(c);
+    EdgePassKernel k = k_edges_binned<S, 1024>;
+    if (kind == kPlainEdges) k = c->flush_rounds == 2 ? k_edges_binned<S, 1024, true, 2, kPlainEdges> : k_edges_binned<S, 1024, true, 1, kPlainEdges>;
+    if (kind == kGroupedEdges) k = c->flush_rounds == 2 ? k_edges_binned<S, 1024, true, 2, kGroupedEdges> : k_edges_binned<S, 1024, true, 1, kGroupedEdges>;
+    if (kind == kFarEdges) k = c->flush_rounds == 2 ? k_edges_binned<S, 1024, true, 2, kFarEdges> : k_edges_binned<S, 1024, true, 1, kFarEdges>;
     if (c->distinct_kernel && c->pool_rounds == 1) k = k_edges_pooled_distinct<S, 1>;
     else if (c->distinct_kernel && c->pool_rounds == 2) k = k_edges_pooled_distinct<S, 2>;
     else if (c->distinct_kernel && c->pool_rounds == 4) k = k_edges_pooled_distinct<S, 4>;
@@ -282,8 +291,7 @@ void with_edge_pass_kernel_s(const nomad_ctx* c, Fn fn) {
     else if (c->pool_rounds == 2) k = k_edges_pooled<S, 2, 1024>;
     else if (c->pool_rounds == 4) k = k_edges_pooled<S, 4, 1024>;
     else if (c->pool_rounds == 8) k = k_edges_pooled<S, 8, 1024>;
-    else if (c->bin_block == 512 && c->sorted_records) k = plain ? k_edges_binned<S, 512, true, 1, true> : k_edges_binned<S, 512, true>;
-    else if (c->bin_block == 512) k = k_edges_binned<S, 512, false>;
+    else if (c->bin_block == 512) k = c->sorted_records ? k_edges_binned<S, 512, true> : k_edges_binned<S, 512, false>;
     else if (!c->sorted_records && c->flush_rounds == 2) k = k_edges_binned<S, 1024, false, 2>;
     else if (!c->sorted_records) k = k_edges_binned<S, 1024, false, 1>;
     fn(k);
@@ -683,7 +691,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         int compute_units = 0;
         HTRY(hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, c->cfg.device));
         compute_units = std::max(1, compute_units);
-        coarsen_tiles(plan, n, s, compute_units);
+        coarsen_tiles(plan, n, s, compute_units, edge_kind(c) != kAnyEdges);
         const int tile_bits = plan.tile_bits, bin_block = plan.bin_block, wg_per_cu = plan.wg_per_cu, pool_rounds = plan.pool_rounds;
         const uint32_t n_bins = plan.n_bins;
         const bool sorted = plan.sorted, distinct = plan.distinct_kernel;

@@ -787,6 +787,7 @@ __global__ void __launch_bounds__(kBlock) k_edges(const EdgeArgs P) {
 //                    records were appended or read in.  It then adds the head sums and writes g.
 // (tile and chunk sizes and the LDS budgets: edge_plan.h)
 constexpr uint32_t kNoChunk = 0xFFFFFFFFu;
+constexpr uint32_t kNoRank = 0xFFFFFFFFu;
 
 struct BinArgs {
     const int32_t* head;          // [E] head of every CSR position
@@ -1118,14 +1119,20 @@ __device__ __forceinline__ bool reduce_head_sums(const BinArgs& Q, bool has, int
     return row_end && !inside;
 }
 
+// Bounds of a row, kept as the pair they are loaded as: taking one of them out of the pair is a use, so a copy of `end` made
+// where the loads are issued (to its register in the next round) waited there for all of them.
+typedef int32_t RowBounds __attribute__((ext_vector_type(2), aligned(4)));
+
 // What one lane has in flight for its edge of the next round: issued a round ahead, so that the
 // gathers of round r+1 are served while round r is being sorted and written out.  Nothing here is computed from another
 // of these loads (the head's constants are, when the round comes: head_of_fetch): an operand would be waited for where
-// it is used, and the round's loads would go out one after the other.
+// it is used, and the round's loads would go out one after the other.  For the same reason the loads are straight-line
+// code: a lane past the last position loads the last position's edge again.
 template <int S>
 struct EdgeFetch {
     bool has;
-    int32_t e, i, j, ea, eb;
+    int32_t e, i, j;
+    RowBounds row;
     float pe;
     float2 ti;
     float4 hi;                      // groups: the head's hinfo, fetched a round before the rest
@@ -1138,13 +1145,10 @@ struct EdgeFetch {
 template <int S>
 __device__ __forceinline__ void issue_edge(const EdgeArgs& P, bool has, int32_t e, int32_t i, int32_t j, const float4& hi, bool split_traffic, EdgeFetch<S>& f) {
     f.has = has;
-    f.e = e; f.i = has ? i : -1; f.j = j; f.ea = 0; f.eb = 0;
-    if (!has) return;
-    f.ea = P.row_ptr[i];
-    f.eb = P.row_ptr[i + 1];
+    f.e = e; f.i = i; f.j = j;
+    f.row = *(const RowBounds*)(P.row_ptr + i);
     f.ti = P.theta[i];
     f.tj = P.theta[j];
-    if (P.pe) f.pe = P.pe[e];
     Population pop = {0u, (uint32_t)P.n, nullptr};
     if (P.group_of_cluster) {
         f.hi = hi;
@@ -1163,14 +1167,17 @@ __device__ __forceinline__ void issue_edge(const EdgeArgs& P, bool has, int32_t 
 #pragma unroll
         for (int k = 0; k < S; ++k) f.tm[k] = P.theta[f.m[k]];
     }
+    if (P.pe) f.pe = P.pe[e];
 }
 
-// the head's constants from what has arrived (load_head's, without its loads)
+// the head's constants from what has arrived (load_head's, without its loads).  Its products are rounded here, not fused into the
+// sums they enter later: every instance of the edge pass gives the same bits.
 template <int S>
 __device__ __forceinline__ HeadCtx head_of_fetch(const EdgeArgs& P, const EdgeFetch<S>& f) {
+#pragma clang fp contract(off)
     HeadCtx h;
     h.ti = f.ti;
-    h.inv_deg = f.eb > f.ea ? 1.0f / (float)(f.eb - f.ea) : 0.f;
+    h.inv_deg = 1.0f / (float)(f.row.y - f.row.x);
     h.MA = h.MBx = h.MBy = 0.f;
     h.group = P.group_of_cluster ? __float_as_int(f.hi.w) : 0;
     h.omega = P.omega0;
@@ -1202,11 +1209,21 @@ __device__ __forceinline__ void resolve_far_negatives(const EdgeArgs& P, int32_t
     }
 }
 
-// PLAIN: one population, i.i.d. negatives, no gradient through the means (what most programs run): the options' registers and branches go.
-template <int S, int BS, bool SORT = true, int ROUNDS = 1, bool PLAIN = false>
+// KIND: what the options that cost registers and branches are known to be (a kernel with all of them carries 100 scalar spills
+// and the stratified sampler's arithmetic; for 6 M points in groups it took 3.95 ms).  kAnyEdges: whatever the arguments say.
+enum EdgeKind {
+    kAnyEdges = 0,
+    kPlainEdges = 1,     // one population, i.i.d. negatives, no gradient through the means
+    kGroupedEdges = 2,   // groups that are index ranges, the far ones through the mean-field sums; i.i.d. negatives, no gradient through the means
+    kFarEdges = 3        // groups, the far ones through sampled means; i.i.d. negatives, no gradient through the means
+};
+template <int S, int BS, bool SORT = true, int ROUNDS = 1, int KIND = kAnyEdges>
 __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs args, const BinArgs Q) {
     EdgeArgs P = args;
-    if (PLAIN) { P.pool_size = 0; P.group_of_cluster = nullptr; P.far = 0; P.cS = nullptr; }
+    if (KIND != kAnyEdges) { P.pool_size = 0; P.cS = nullptr; P.far = KIND == kFarEdges; }
+    if (KIND == kPlainEdges) P.group_of_cluster = nullptr;
+    if (KIND == kGroupedEdges || KIND == kFarEdges) __builtin_assume(P.group_of_cluster != nullptr);
+    if (KIND == kGroupedEdges) P.gmembers = nullptr;
     constexpr int SS = S > 0 ? S : 1;
     constexpr int kWaves = BS / 64;
     constexpr int NREC = ROUNDS * (BS * (S + 1) + 2 * kWaves);
@@ -1238,20 +1255,20 @@ __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs args, const 
     // Software pipeline over rounds: (head, tail) indices are read two rounds ahead (with groups three, and the heads' group
     // information, on which the negatives depend, two), the embedding rows one round ahead.
     EdgeFetch<S> f;
-    int32_t i1 = 0, j1 = 0, i2 = 0, j2 = 0;   // the next round's; with groups also the one's after
+    int32_t i1, j1, i2 = 0, j2 = 0;   // the next round's; with groups also the one's after
     float4 hi1 = make_float4(0.f, 0.f, 0.f, 0.f);
+    const auto position = [&](int64_t e) { return min(e, Q.e_end - 1); };
     {
-        const int64_t e0 = Q.e_begin + (int64_t)w * BS + tid, e1 = e0 + stride, e2 = e1 + stride;
-        int32_t i0 = 0, j0 = 0;
+        const int64_t e0 = Q.e_begin + (int64_t)w * BS + tid, c0 = position(e0), c1 = position(e0 + stride), c2 = position(e0 + 2 * stride);
+        const int32_t i0 = Q.head[c0], j0 = P.col[c0];
         float4 hi0 = hi1;
-        if (e0 < Q.e_end) { i0 = Q.head[e0]; j0 = P.col[e0]; }
-        if (e1 < Q.e_end) { i1 = Q.head[e1]; j1 = P.col[e1]; }
+        i1 = Q.head[c1]; j1 = P.col[c1];
         if (P.group_of_cluster) {
-            if (e2 < Q.e_end) { i2 = Q.head[e2]; j2 = P.col[e2]; }
+            i2 = Q.head[c2]; j2 = P.col[c2];
             hi0 = P.hinfo[i0];
             hi1 = P.hinfo[i1];
         }
-        issue_edge<S>(P, e0 < Q.e_end, (int32_t)e0, i0, j0, hi0, false, f);
+        issue_edge<S>(P, e0 < Q.e_end, (int32_t)c0, i0, j0, hi0, false, f);
     }
     // ROUNDS rounds between two flushes (no barrier in between: a record only takes its rank from the tile's counter when
     // it is made); slabs past the end are empty rounds.
@@ -1266,7 +1283,7 @@ __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs args, const 
             const int64_t e64 = Q.e_begin + slab * BS + tid;
             const int64_t e_end = min(Q.e_begin + (slab + 1) * BS, Q.e_end);
             const bool has = f.has;
-            const int32_t i = f.i, ea = f.ea, eb = f.eb;
+            const int32_t i = f.i, ea = f.row.x, eb = f.row.y;
             const int base = r * NR;
 #pragma unroll
             for (int k = 0; k < NR; ++k) { valid[base + k] = k <= S && has; dst_pt[base + k] = 0u; rank[base + k] = 0u; fx[base + k] = 0.f; fy[base + k] = 0.f; }
@@ -1290,17 +1307,19 @@ __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs args, const 
             }
             // the loads of the next round go out before this round is sorted and written
             {
-                const int64_t e1 = e64 + stride, e2 = e1 + stride, e3 = e2 + stride;
+                const int64_t e1 = e64 + stride;
                 const int32_t i0 = i1, j0 = j1;
                 const float4 hi0 = hi1;
                 if (P.group_of_cluster) {
+                    const int64_t c3 = position(e1 + 2 * stride);
                     i1 = i2; j1 = j2;
                     hi1 = P.hinfo[i1];
-                    if (e3 < Q.e_end) { i2 = Q.head[e3]; j2 = P.col[e3]; }
-                } else if (e2 < Q.e_end) {
-                    i1 = Q.head[e2]; j1 = P.col[e2];
+                    i2 = Q.head[c3]; j2 = P.col[c3];
+                } else {
+                    const int64_t c2 = position(e1 + stride);
+                    i1 = Q.head[c2]; j1 = P.col[c2];
                 }
-                issue_edge<S>(P, e1 < Q.e_end, (int32_t)e1, i0, j0, hi0, Q.split_traffic, f);
+                issue_edge<S>(P, e1 < Q.e_end, (int32_t)position(e1), i0, j0, hi0, Q.split_traffic, f);
             }
             valid[base + S + 1] = reduce_head_sums(Q, has, i, ea, eb, e64, e_end, hx, hy);
             dst_pt[base + S + 1] = valid[base + S + 1] ? (uint32_t)i : 0u;
@@ -1328,10 +1347,6 @@ __global__ void __launch_bounds__(BS) k_edges_binned(const EdgeArgs args, const 
 // ranks, so their writes still coalesce; a pool entry's record is alone in its tile whichever way it is written.
 constexpr int kMaxPoolPerLane = 4;   // pool entries one lane fetches and hands on: pool_size <= 4 * workgroup size
 
-
-// Bounds of a row, kept as the pair they are loaded as: taking one of them out of the pair is a use, so a copy of `end` made
-// where the loads are issued (to its register in the next round) waited there for all of them.
-typedef int32_t RowBounds __attribute__((ext_vector_type(2), aligned(4)));
 
 // What a lane of the pooled edge pass has in flight for its next edge (no groups there: one population, no mean field).
 struct PoolFetch {
@@ -1739,26 +1754,16 @@ __global__ void __launch_bounds__(1024) k_edges_pooled_distinct(const EdgeArgs P
         }
         draw_lines(blk + W);
         lds_barrier();   // every force of the block is in pool_acc, the side list and the next block's lines are complete
-        // ---- one record per pool entry that received a force, one per partial head sum
-        bool pv[NP];
-        uint32_t ppt[NP], prk[NP];
-        float pfx[NP], pfy[NP];
+        // ---- one record per pool entry that received a force, one per partial head sum (the entry's rank is kept, its sum and
+        // point stay in LDS until it is written: with them in registers the kernel spilled)
+        uint32_t prk[NP];
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
             const uint32_t idx = tid + (uint32_t)k * BS;
-            pv[k] = false; ppt[k] = 0u; prk[k] = 0u; pfx[k] = 0.f; pfy[k] = 0.f;
+            prk[k] = kNoRank;
             if (idx < PS) {
                 const uint32_t u = entry_of(idx);
-                const long long ax = (long long)pool_acc[u], ay = (long long)pool_acc[PS + u];
-                pv[k] = (ax | ay) != 0;
-                if (pv[k]) {
-                    pool_acc[u] = 0ull;
-                    pool_acc[PS + u] = 0ull;
-                    ppt[k] = pool_pt[u];
-                    pfx[k] = (float)((double)ax * kFixInv);
-                    pfy[k] = (float)((double)ay * kFixInv);
-                    prk[k] = atomicAdd(&cnt[ppt[k] >> tb], 1u);
-                }
+                if ((pool_acc[u] | pool_acc[PS + u]) != 0ull) prk[k] = atomicAdd(&cnt[pool_pt[u] >> tb], 1u);
             }
         }
         const bool sv = tid < side_n;
@@ -1773,7 +1778,14 @@ __global__ void __launch_bounds__(1024) k_edges_pooled_distinct(const EdgeArgs P
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) emit(tv[r], tpt[r], trk[r], tfx[r], tfy[r]);
 #pragma unroll
-        for (int k = 0; k < NP; ++k) emit(pv[k], ppt[k], prk[k], pfx[k], pfy[k]);
+        for (int k = 0; k < NP; ++k) {
+            if (prk[k] == kNoRank) continue;
+            const uint32_t u = entry_of(tid + (uint32_t)k * BS);
+            const long long ax = (long long)pool_acc[u], ay = (long long)pool_acc[PS + u];
+            pool_acc[u] = 0ull;
+            pool_acc[PS + u] = 0ull;
+            emit(true, pool_pt[u], prk[k], (float)((double)ax * kFixInv), (float)((double)ay * kFixInv));
+        }
         emit(sv, spt, srk, sx, sy);
         lds_barrier();   // the tables have been read
         // ---- chain state after this block, counts back to zero; the next block's pool into LDS
