@@ -86,17 +86,17 @@ constexpr uint32_t kLoopGrid = 512;   // workgroups of the kernels whose work li
 
 // The k nearest candidates of every query inside its group (filter, refinement, exact fallback).  `cand` [n_q * (k + kPad)],
 // `tau` [n_q], `flagged` [n_q], `n_flagged` [1] are work space.
-int nearest_in_groups(hipStream_t st, const KnnSets& P, const KnnBlock* blocks, uint32_t n_blocks, int waves, int32_t k, int32_t* cand, float* tau,
+int nearest_in_groups(hipStream_t st, const KnnSets& P, const KnnBlock* blocks, uint32_t n_blocks, int waves, int32_t k, int32_t* cand, float* keys, float* tau,
                       int32_t* flagged, uint32_t* n_flagged, int32_t* out) {
     const int32_t list_len = k + kPad;
     KTRY(hipMemsetAsync(n_flagged, 0, sizeof(uint32_t), st));
-    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, list_len, cand, tau, KnnAssign{nullptr, nullptr, nullptr}));
+    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, list_len, cand, keys, tau, KnnAssign{nullptr, nullptr, nullptr}));
     if (list_len <= 16)
-        hipLaunchKernelGGL(k_knn_refine<16>, dim3(blocks_of(P.n_q, 16)), dim3(256), 0, st, P, cand, tau, k, list_len, out, flagged, n_flagged);
+        hipLaunchKernelGGL(k_knn_refine<16>, dim3(blocks_of(P.n_q, 16)), dim3(256), 0, st, P, cand, keys, tau, k, list_len, out, flagged, n_flagged);
     else if (list_len <= 32)
-        hipLaunchKernelGGL(k_knn_refine<32>, dim3(blocks_of(P.n_q, 8)), dim3(256), 0, st, P, cand, tau, k, list_len, out, flagged, n_flagged);
+        hipLaunchKernelGGL(k_knn_refine<32>, dim3(blocks_of(P.n_q, 8)), dim3(256), 0, st, P, cand, keys, tau, k, list_len, out, flagged, n_flagged);
     else
-        hipLaunchKernelGGL(k_knn_refine<64>, dim3(blocks_of(P.n_q, 4)), dim3(256), 0, st, P, cand, tau, k, list_len, out, flagged, n_flagged);
+        hipLaunchKernelGGL(k_knn_refine<64>, dim3(blocks_of(P.n_q, 4)), dim3(256), 0, st, P, cand, keys, tau, k, list_len, out, flagged, n_flagged);
     const dim3 grid((uint32_t)std::min<int64_t>(P.n_q, kLoopGrid));
     if (k <= 16) hipLaunchKernelGGL((k_knn_exact<16, 1024>), grid, dim3(1024), 0, st, P, flagged, (const uint32_t*)n_flagged, k, out);
     else hipLaunchKernelGGL((k_knn_exact<kMaxK, 512>), grid, dim3(512), 0, st, P, flagged, (const uint32_t*)n_flagged, k, out);
@@ -108,7 +108,7 @@ int nearest_in_groups(hipStream_t st, const KnnSets& P, const KnnBlock* blocks, 
 // counters [2] (queries the filter left open, queries for the exact path), both zero.
 int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* blocks, uint32_t n_blocks, int waves, int32_t* cand, float* tau,
                 int32_t* todo, int32_t* flagged, uint32_t* counters, int32_t* out) {
-    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, tau, KnnAssign{out, todo, counters}));
+    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, nullptr, tau, KnnAssign{out, todo, counters}));
     const int32_t width = 128 / tile;
     const dim3 grid((uint32_t)std::min<int64_t>((P.n_q * width + 255) / 256, kLoopGrid));
     hipLaunchKernelGGL(k_assign_refine, grid, dim3(256), 0, st, P, (const int32_t*)todo, (const uint32_t*)counters, (const int32_t*)cand, (const float*)tau,
@@ -226,7 +226,7 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     // members grouped by cluster
     uint32_t *counts = nullptr, *cursor = nullptr, *max_norm = nullptr, *n_flagged = nullptr;
     int32_t *members = nullptr, *cand = nullptr, *flagged = nullptr;
-    float *norm = nullptr, *tau = nullptr, *centre = nullptr;
+    float *norm = nullptr, *keys = nullptr, *tau = nullptr, *centre = nullptr;
     int* bad = nullptr;
     // counters that start at zero: counts, cursor, max_norm, centre, bad, n_flagged
     uint8_t* zeroed = nullptr;
@@ -238,7 +238,7 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     KTRY(buf.alloc(&members, (size_t)n));
     KTRY(buf.alloc(&norm, (size_t)n));
     KTRY(buf.alloc(&tau, (size_t)n));
-    KTRY(buf.alloc(&cand, (size_t)n * list_len));
+    KTRY(buf.alloc(&cand, (size_t)n * list_len)); KTRY(buf.alloc(&keys, (size_t)n * list_len));
     KTRY(buf.alloc(&flagged, (size_t)n));
     hipLaunchKernelGGL(k_knn_count, dim3(blocks_of(n, kCountSpan)), dim3(256), 0, st, dC, n, R, counts, bad);
     std::vector<uint32_t> hcounts((size_t)3 * R + 1), hstart((size_t)R + 1, 0);   // counts, two arrays of no interest, bad
@@ -272,7 +272,7 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     KnnSets P{};
     P.XQ = dX; P.XC = dX; P.qmembers = members; P.cmembers = members; P.qstart = start; P.cstart = start;
     P.Q = side.view(max_norm); P.C = P.Q; P.centre = centre; P.group_of_q = dC; P.n_q = n; P.n_c = n; P.d = d; P.same_set = 1;
-    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, tau, flagged, n_flagged, dOut);
+    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, dOut);
     if (rc) return rc;
     uint32_t hflag = 0;
     KTRY(hipMemcpyAsync(&hflag, n_flagged, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
@@ -506,14 +506,14 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     if (mq >= ((int64_t)1 << 31) - 256) return NOMAD_E_TOO_LARGE;
     uint32_t *max_q = nullptr, *max_c = nullptr, *n_flagged = nullptr;
     int32_t *cand = nullptr, *flagged = nullptr, *self = nullptr, *group_of_q = nullptr, *slice_of = nullptr, *part = nullptr;
-    float *cnorm = nullptr, *tau = nullptr, *centre = nullptr, *AQ = nullptr;
+    float *cnorm = nullptr, *keys = nullptr, *tau = nullptr, *centre = nullptr, *AQ = nullptr;
     int* bad = nullptr;
     uint8_t* zeroed = nullptr;   // max_q, max_c, bad, n_flagged, centre
     const size_t zero_bytes = sizeof(uint32_t) * ((size_t)2 * G + 2 + (size_t)G * d);
     KTRY(buf.alloc(&zeroed, zero_bytes));
     KTRY(hipMemsetAsync(zeroed, 0, zero_bytes, st));
     max_q = (uint32_t*)zeroed; max_c = max_q + G; bad = (int*)(max_c + G); n_flagged = (uint32_t*)(bad + 1); centre = (float*)(n_flagged + 1);
-    KTRY(buf.alloc(&cand, (size_t)mq * list_len)); KTRY(buf.alloc(&flagged, (size_t)mq)); KTRY(buf.alloc(&tau, (size_t)mq));
+    KTRY(buf.alloc(&cand, (size_t)mq * list_len)); KTRY(buf.alloc(&keys, (size_t)mq * list_len)); KTRY(buf.alloc(&flagged, (size_t)mq)); KTRY(buf.alloc(&tau, (size_t)mq));
     KTRY(buf.alloc(&cnorm, (size_t)n)); KTRY(buf.alloc(&AQ, (size_t)mq * d));
     KTRY(buf.alloc(&self, (size_t)mq));
     std::vector<uint32_t> hq((size_t)G + 1), hc((size_t)G + 1);
@@ -563,7 +563,7 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     P.XQ = AQ; P.XC = A; P.qmembers = nullptr; P.cmembers = nullptr; P.qstart = qstart; P.cstart = cstart;
     P.Q = qside.view(max_q); P.C = cside.view(max_c); P.centre = centre; P.group_of_q = group_of_q; P.n_q = mq; P.n_c = n; P.d = d; P.same_set = 0;
     P.self_row = self;
-    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, tau, flagged, n_flagged, G > 1 ? part : out);
+    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, G > 1 ? part : out);
     if (rc) return rc;
     if (G > 1) {
         hipLaunchKernelGGL(k_merge_slices, dim3((uint32_t)m), dim3(256), 0, st, (const float*)AQ, A, d, (const int32_t*)part, (int32_t)G, m, k, out);

@@ -5,7 +5,7 @@
 namespace {
 
 template <int TILE, int KS, int L, int WAVES>
-hipError_t launch(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand, float* tau,
+hipError_t launch(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand, float* keys, float* tau,
                   const KnnAssign& assign) {
     constexpr size_t lds = knn_filter_lds_bytes(TILE, KS, L, WAVES);
     static_assert(lds <= 160 * 1024, "");
@@ -13,23 +13,23 @@ hipError_t launch(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const Knn
         hipError_t e = hipFuncSetAttribute((const void*)k_knn_filter<TILE, KS, L, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_knn_filter<TILE, KS, L, WAVES>), dim3(n_blocks), dim3(64 * WAVES), lds, st, P, blocks, list_len, cand, tau, assign);
+    hipLaunchKernelGGL((k_knn_filter<TILE, KS, L, WAVES>), dim3(n_blocks), dim3(64 * WAVES), lds, st, P, blocks, list_len, cand, keys, tau, assign);
     return hipGetLastError();
 }
 
 // list classes: 0 = one neighbour, 1 = short lists, 2 = long ones
 template <int TILE, int KS, int L>
 hipError_t launch_waves(hipStream_t st, uint32_t n_blocks, int waves, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand,
-                        float* tau, const KnnAssign& assign) {
-    if (waves == 8) return launch<TILE, KS, L, 8>(st, n_blocks, P, blocks, list_len, cand, tau, assign);
-    return launch<TILE, KS, L, TILE == 32 ? 2 : 4>(st, n_blocks, P, blocks, list_len, cand, tau, assign);
+                        float* keys, float* tau, const KnnAssign& assign) {
+    if (waves == 8) return launch<TILE, KS, L, 8>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+    return launch<TILE, KS, L, TILE == 32 ? 2 : 4>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
 }
 
 }  // namespace
 
-#define NOMAD_ARGS st, n_blocks, waves, P, blocks, list_len, cand, tau, assign
+#define NOMAD_ARGS st, n_blocks, waves, P, blocks, list_len, cand, keys, tau, assign
 hipError_t launch_knn_filter(hipStream_t st, uint32_t n_blocks, int waves, const KnnSets& P, const KnnBlock* blocks, int32_t list_len,
-                             int32_t* cand, float* tau, const KnnAssign& assign) {
+                             int32_t* cand, float* keys, float* tau, const KnnAssign& assign) {
     if (n_blocks == 0) return hipSuccess;
     const int tile = knn_tile(P.d, list_len), steps = knn_steps(P.d, tile);
     if (assign.out) {

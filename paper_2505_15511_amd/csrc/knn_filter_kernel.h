@@ -129,7 +129,7 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // on nearly every tile; the queue fills its passes.  Keys are looked at in fours: one comparison and a branch where no lane
 // of the wavefront has a hit.  The threshold is the smaller of the lane's last key and the largest of
 // the lanes' H-th keys (H 64 / TILE >= K': what lies above that is not among the K' smallest).
-// At the end the lists are merged by counting; tau = min(K'-th key of the union, the lists' last keys): every candidate
+// At the end the lists are merged by counting, smallest key first; tau = min(K'-th key of the union, the lists' last keys): every candidate
 // that is not passed on has key >= tau.
 //
 // L == 2: one neighbour wanted.  Every key goes straight into the lane's best two; at the end a query whose smallest key
@@ -139,7 +139,7 @@ struct KnnAssign { int32_t* out; int32_t* todo; uint32_t* n_todo; };
 
 template <int TILE, int KS, int L, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WAVES)) k_knn_filter(const KnnSets P, const KnnBlock* __restrict__ blocks, int32_t list_len,
-                                                                               int32_t* __restrict__ cand, float* __restrict__ tau_out,
+                                                                               int32_t* __restrict__ cand, float* __restrict__ key_out, float* __restrict__ tau_out,
                                                                                const KnnAssign assign) {
     using Mat = MatrixTile<TILE>;
     using Acc = typename Mat::Acc;
@@ -372,7 +372,10 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     if (qpt < 0) return;
 #pragma unroll
     for (int x = 0; x < L; ++x) {
-        if (rank[x] < list_len) cand[p * list_len + rank[x]] = lp[x] < 0 ? -1 : knn_row(P.cmembers, c0 + (uint32_t)lp[x]);
+        if (rank[x] < list_len) {
+            cand[p * list_len + rank[x]] = lp[x] < 0 ? -1 : knn_row(P.cmembers, c0 + (uint32_t)lp[x]);
+            key_out[p * list_len + rank[x]] = lk[x] * key_unit;
+        }
         if (rank[x] == list_len - 1) tau_out[p] = fminf(lk[x], last) * key_unit;
     }
 }

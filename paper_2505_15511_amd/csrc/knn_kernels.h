@@ -6,9 +6,9 @@
 //                  laid out tile by tile in the order the matrix instructions read their operands;
 //   k_knn_filter   float16 matrix cores (hi hi + hi lo + lo hi, float32 accumulation): for every query the K' = k + pad
 //                  candidates with the smallest key |c|^2 - 2 q.c, and tau (every point left out has key >= tau);
-//   k_knn_refine   the exact distances of those candidates, sum_t (x_t - y_t)^2 in float64 in the order t = 0..d-1,
-//                  sorted by (distance, index); the first k are the answer if the k-th exact key lies below
-//                  tau by more than the error bound of the filter -- otherwise the query is flagged;
+//   k_knn_refine   sorts those candidates by (distance, index), distance = sum_t (x_t - y_t)^2 in float64 in the order
+//                  t = 0..d-1, worked out where the filter's error bound leaves the order open; the first k are the answer
+//                  if the k-th lies below tau by more than that bound -- otherwise the query is flagged;
 //   k_knn_exact    flagged queries (near-ties beyond the pad, duplicates in bulk): exact distances to the whole cluster.
 // The result therefore does not depend on the filter's rounding: it is the float64 definition, tie-broken by index.
 #pragma once
@@ -262,14 +262,19 @@ __device__ __forceinline__ double exact_distance(const float* __restrict__ x, co
     return acc;
 }
 
-// ---------------------------------------------------------------- stage 2: exact distances of the candidates
-// One lane per candidate.  rank = number of candidates that come before in (distance, point).
-// The answer is certified when the k-th exact key, D_k - |q|^2, lies below tau by more than eps (knn_filter_eps): every
-// point the filter left out has filter key >= tau, hence exact key >= tau - eps.
-// G lanes per query (16, 32 or 64, at least the list length): short lists share a wavefront between several queries.
+// ---------------------------------------------------------------- stage 2: the order of the candidates
+// The candidates arrive in the order of their filter keys.  Where a key lies below the next by more than twice the filter's
+// error bound the exact distances stand in that order too; only the members of a run of closer keys need their exact
+// distances to be ordered (by distance, then point), and of those only the runs that begin among the first k.  The
+// kernel is bound by the rows it gathers: a million queries with 23 candidates of 128 columns, all exact, took 2.0 ms
+// (5.9 TB/s out of the caches); with few of them exact: 0.89 ms.
+// Certified, i.e. no point that the filter left out (key >= tau, exact key >= tau - eps) is nearer than the k-th, when the
+// k-th key lies below tau by more than twice the bound (k candidates have exact keys up to key + eps), or else the k-th
+// exact key, D_k - |q|^2, does by more than the bound; otherwise the query is flagged.
+// G lanes per query (16, 32 or 64, at least the list length), one per candidate: short lists share a wavefront.
 template <int G>
-__global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32_t* __restrict__ cand, const float* __restrict__ tau,
-                                                    int32_t k, int32_t list_len, int32_t* __restrict__ out,
+__global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32_t* __restrict__ cand, const float* __restrict__ keys,
+                                                    const float* __restrict__ tau, int32_t k, int32_t list_len, int32_t* __restrict__ out,
                                                     int32_t* __restrict__ flagged, uint32_t* __restrict__ n_flagged) {
     const int64_t p = (int64_t)blockIdx.x * (256 / G) + (threadIdx.x / G);   // position in the grouped query order
     const int lane = threadIdx.x % G;
@@ -280,36 +285,42 @@ __global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32
     const float* xq = P.XQ + (int64_t)q * d;
     int32_t c = lane < list_len ? cand[p * list_len + lane] : -1;
     if (c >= P.n_c) c = -1;   // never an address outside the candidate rows, whatever the list holds
-    const double D = c >= 0 ? exact_distance(xq, P.XC + (int64_t)c * d, d) : __builtin_inf();
-    int rank = 0, cnt = 0;
-    for (int o = 0; o < list_len; ++o) {
-        const double Do = __shfl(D, o, G);
-        const int32_t co = __shfl(c, o, G);
-        if (co >= 0) {
-            ++cnt;
-            if (Do < D || (Do == D && co < c)) ++rank;
-        }
+    const double key = c >= 0 ? (double)keys[p * list_len + lane] : __builtin_inf();
+    const float t = tau[p];
+    const int32_t g = P.group_of_q ? P.group_of_q[q] : 0;
+    const double eps = knn_filter_eps(d, fmax((double)__uint_as_float(P.Q.max_bits[g]), (double)__uint_as_float(P.C.max_bits[g])));
+    const int first = (int)(threadIdx.x & 63u) - lane;   // of this query's lanes in the wavefront
+    const auto votes = [&](bool v) { return (__ballot(v) >> first) & (~0ull >> (64 - G)); };
+    const double next = __shfl_down(key, 1, G);
+    const int cnt = __popcll(votes(c >= 0));
+    // (negated comparisons: a key that is not a number counts as close to everything)
+    const unsigned long long links = votes(lane + 1 < cnt && !(next - key > 2.0 * eps));
+    const unsigned long long breaks = ~links & ((1ull << lane) - 1ull);
+    const int run0 = breaks ? 64 - __clzll((long long)breaks) : 0, run1 = lane + __ffsll((long long)(~links >> lane)) - 1;   // this lane's run
+    const bool left_out = t < __builtin_inff() && cnt >= k;   // the same for every lane of the group
+    const bool open = left_out && votes(lane == k - 1 && !(key + 2.0 * eps < (double)t)) != 0ull;
+    const bool exact = c >= 0 && ((run1 > run0 && run0 < k) || (open && lane == k - 1));
+    const double D = exact ? exact_distance(xq, P.XC + (int64_t)c * d, d) : 0.0;
+    int rank = run0;
+    for (int r = 1; __any(lane - r >= run0 || lane + r <= run1); ++r) {
+        const double Dl = __shfl(D, lane - r, G), Dr = __shfl(D, lane + r, G);
+        const int32_t cl = __shfl(c, lane - r, G), cr = __shfl(c, lane + r, G);
+        if (lane - r >= run0 && (Dl < D || (Dl == D && cl < c))) ++rank;
+        if (lane + r <= run1 && (Dr < D || (Dr == D && cr < c))) ++rank;
     }
     if (c >= 0 && rank < k) out[(int64_t)q * k + rank] = c;
     if (lane >= cnt && lane < k) out[(int64_t)q * k + lane] = -1;   // fewer than k candidates in the group
-    // certification by the lane that holds the k-th neighbour (only needed when something was left out).  |q'|^2 of the
-    // centred query as the filter saw it: the group's lanes add a strided share each (the order is free: the value only
-    // enters an inequality with slack).
-    const float t = tau[p];
-    const int32_t g = P.group_of_q ? P.group_of_q[q] : 0;
+    if (!open) return;
+    // |q'|^2 of the centred query as the filter saw it: the group's lanes add a strided share each (the order is free: the
+    // value only enters an inequality with slack)
     double qn = 0.0;
-    if (t < __builtin_inff() && cnt >= k) {   // the same for every lane of the group
-        const float* ctr = P.centre + (int64_t)g * d;
-        for (int x = lane; x < d; x += G) {
-            const double v = (double)(xq[x] - ctr[x]);
-            qn = fma(v, v, qn);
-        }
-        for (int w = G / 2; w > 0; w >>= 1) qn += __shfl_xor(qn, w, G);
+    const float* ctr = P.centre + (int64_t)g * d;
+    for (int x = lane; x < d; x += G) {
+        const double v = (double)(xq[x] - ctr[x]);
+        qn = fma(v, v, qn);
     }
-    if (c >= 0 && rank == min(k, cnt) - 1 && t < __builtin_inff() && cnt >= k) {
-        const double eps = knn_filter_eps(d, fmax((double)__uint_as_float(P.Q.max_bits[g]), (double)__uint_as_float(P.C.max_bits[g])));
-        if (!(D - qn + eps < (double)t)) flagged[atomicAdd(n_flagged, 1u)] = q;
-    }
+    for (int w = G / 2; w > 0; w >>= 1) qn += __shfl_xor(qn, w, G);
+    if (c >= 0 && rank == k - 1 && !(D - qn + eps < (double)t)) flagged[atomicAdd(n_flagged, 1u)] = q;
 }
 
 // ---------------------------------------------------------------- stage 3: flagged queries, exactly, against the whole cluster
