@@ -16,9 +16,11 @@ namespace nomad {
 
 constexpr int kMaxTileBits = 13;        // 8192 points: 128 KB of accumulators in the tile pass
 constexpr int kMinTileBits = 8;
+constexpr int kMinFittedTileBits = 4;  // the smallest tile fit_tiles makes
 constexpr int kChunk = 128;             // records per chunk (1.5 KB): every (workgroup, tile) chain ends in a partly filled
                                         // chunk, so the pool carries workgroups x tiles x kChunk records of slack
 constexpr int kBinBlock = 1024;         // threads of the tile pass and of the large edge-pass workgroup
+constexpr int kSmallBinBlock = 256;     // threads of the small one (fit_tiles)
 constexpr int kMaxBinsPerThread = 8;    // tiles one thread owns in the per-round scan of the sorted form
 constexpr size_t kMaxLdsBytes = 160 * 1024 - 256;   // per workgroup on gfx950, less the kernels' static LDS
 constexpr int kDefaultFlushRounds = 2;  // unsorted binned edge pass: rounds between two flushes (5 % faster than one at
@@ -101,16 +103,42 @@ inline EdgePlan plan_edge_pass(const EdgePlanRequest& q) {
     return p;
 }
 
-// plan_edge_pass makes about a thousand tiles.  The sorted form is better off with as few as still give every compute unit one
-// in the tile pass: the records a round brings to a tile are one contiguous run in memory, and runs of 25 records instead of
-// six end in fewer partial lines (1 M points, s = 5, a thousand tiles -> 245: edge pass 1.26 -> 1.12 ms, tile pass 0.32 -> 0.24;
-// 123 tiles: tile pass 0.31).  two_rounds: two rounds share a flush where their records fit LDS (half the barriers and table
-// passes: 100 k points 0.149 -> 0.142 ms, 6 M points in groups, s = 2, 4.26 -> 4.06).
-inline void coarsen_tiles(EdgePlan& p, int64_t n, int s, int compute_units, bool two_rounds = true) {
-    if (!p.sorted || p.pool_rounds) return;
-    while (p.tile_bits < kMaxTileBits && (n >> p.tile_bits) > compute_units) ++p.tile_bits;
-    p.n_bins = (uint32_t)((n + ((int64_t)1 << p.tile_bits) - 1) >> p.tile_bits);
-    if (two_rounds && p.bin_block == 1024 && binned_lds_bytes(p.n_bins, s, 1024, true, 2) <= kMaxLdsBytes) p.flush_rounds = 2;
+// plan_edge_pass makes up to a thousand tiles of at least 256 points.  What serves the tile pass is one tile per compute unit:
+//   fewer points a tile in small problems (2,000 points in 8 tiles left 248 units idle: tile pass 32 us a step; 125 tiles of 16: 10.5 us);
+//   in the sorted form more points a tile in large ones: the records a round brings to a tile are one contiguous run in memory,
+//   and runs of 25 records instead of six end in fewer partial lines (1 M points, s = 5, a thousand tiles -> 245: edge pass
+//   1.26 -> 1.12 ms, tile pass 0.32 -> 0.24; 123 tiles: tile pass 0.31).
+// special_kernel: the edge pass is one of the kernels that know their options.  Those also come
+//   with two rounds to a flush, where the records fit LDS (half the barriers and table passes: 100 k points 0.149 -> 0.142 ms,
+//   6 M points in groups, s = 2, 4.26 -> 4.06);
+//   with 256 lanes, for graphs of no more positions than give every compute unit one such workgroup: one round is all there
+//   is, and its length goes with the lanes that share its barriers and LDS (whole epoch, 14 k edges: 22.0 -> 12.7 us, 58 k:
+//   22.4 -> 18.8; with two such workgroups per compute unit 87 k: 24.0 -> 25.8, 116 k: 25.7 -> 29.9).
+inline bool edge_tables_fit(const EdgePlan& p, const EdgePlanRequest& q) {
+    const size_t lds = p.distinct_kernel ? distinct_lds_bytes(p.n_bins, (uint32_t)q.pool_size, (uint32_t)(q.pool_size / q.pool_line), p.pool_rounds)
+                       : p.pool_rounds  ? pooled_lds_bytes(p.n_bins, q.pool_block, (uint32_t)q.pool_size)
+                                        : p.wg_per_cu * binned_lds_bytes(p.n_bins, q.s, p.bin_block, p.sorted, p.flush_rounds);
+    return lds <= kMaxLdsBytes;
+}
+inline void fit_tiles(EdgePlan& p, const EdgePlanRequest& q, int compute_units, bool special_kernel = true) {
+    if (!p.bin_block) return;
+    const auto tiles = [&](int bits) { return (uint32_t)((q.n + ((int64_t)1 << bits) - 1) >> bits); };
+    if (p.sorted && !p.pool_rounds)
+        while (p.tile_bits < kMaxTileBits && (q.n >> p.tile_bits) > compute_units) ++p.tile_bits;
+    p.n_bins = tiles(p.tile_bits);
+    while (p.tile_bits > kMinFittedTileBits && tiles(p.tile_bits - 1) <= (uint32_t)compute_units) {
+        EdgePlan finer = p;
+        finer.n_bins = tiles(--finer.tile_bits);
+        if (!edge_tables_fit(finer, q)) break;
+        p = finer;
+    }
+    if (!p.sorted || p.pool_rounds || !special_kernel) return;
+    if (q.tune_edge_block == 0 && q.tune_wg_per_cu == 0 && q.E <= (int64_t)compute_units * kSmallBinBlock) {
+        p.bin_block = kSmallBinBlock;
+        p.wg_per_cu = 1;
+    }
+    if (p.bin_block == 1024 && binned_lds_bytes(p.n_bins, q.s, 1024, true, 2) <= kMaxLdsBytes)
+        p.flush_rounds = 2;
 }
 
 // Record phases: the edge pass of a step runs over `phases` ranges of positions, each followed by the tile pass, so the

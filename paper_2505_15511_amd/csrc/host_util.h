@@ -157,6 +157,8 @@ public:
     }
     hipError_t wait() { pending_ = false; return hipEventSynchronize(s_.event); }
     unsigned long long value() const { return *s_.word; }
+    // for a kernel to write and the host to read once it has waited for the stream: no copy on the way
+    unsigned long long* word() const { return s_.word; }
 
 private:
     static constexpr size_t kKeep = 8;

@@ -68,8 +68,8 @@ struct nomad_ctx {
     int tile_bits = kMaxTileBits;
     uint32_t *pool = nullptr, *chunk_prev = nullptr, *chain_head = nullptr, *chain_fill = nullptr, *wg_pool_begin = nullptr;
     int32_t* head = nullptr;
-    int* overflow = nullptr;
-    double *loss_partial = nullptr, *loss_out = nullptr;
+    HostWord overflow, loss_out;    // written by kernels, read once the stream has been waited for
+    double* loss_partial = nullptr;
     uint32_t edge_grid = 0;
     int* flags = nullptr;
     // launch-shape knobs (nomad_tune) and what set_graph made of them
@@ -140,12 +140,12 @@ void free_graph(nomad_ctx* c) {
     dev_free(c, c->gomega); dev_free(c, c->hinfo); dev_free(c, c->gmembers); dev_free(c, c->cmembers); dev_free(c, c->chunks); dev_free(c, c->mean_partial);
     dev_free(c, c->theta); dev_free(c, c->g); dev_free(c, c->ghead); dev_free(c, c->mu); dev_free(c, c->B); dev_free(c, c->cinfo);
     dev_free(c, c->cell_slot); dev_free(c, c->group_slots);
-    dev_free(c, c->A); dev_free(c, c->gfix); dev_free(c, c->loss_partial); dev_free(c, c->loss_out);
+    dev_free(c, c->A); dev_free(c, c->gfix); dev_free(c, c->loss_partial);
     dev_free(c, c->cS); dev_free(c, c->chead); dev_free(c, c->Gfix); dev_free(c, c->gmean);
     c->through_means = false;
     dev_free(c, c->flags);
     dev_free(c, c->pool); dev_free(c, c->chunk_prev); dev_free(c, c->chain_head); dev_free(c, c->chain_fill); dev_free(c, c->wg_pool_begin);
-    dev_free(c, c->head); dev_free(c, c->overflow); dev_free(c, c->carry); dev_free(c, c->pool_keys);
+    dev_free(c, c->head); dev_free(c, c->carry); dev_free(c, c->pool_keys);
     c->phases = 1;
     c->binned = false;
     c->pool_rounds = 0;
@@ -253,7 +253,7 @@ BinArgs bin_args(nomad_ctx* c) {
     q.head = c->head; q.pool = c->pool; q.chunk_prev = c->chunk_prev; q.chain_head = c->chain_head; q.chain_fill = c->chain_fill;
     q.wg_pool_begin = c->wg_pool_begin; q.ghead = c->ghead; q.E = c->E; q.e_begin = 0; q.e_end = c->E;
     q.max_chunks = c->max_chunks; q.n_bins = c->n_bins;
-    q.tile_bits = c->tile_bits; q.overflow = c->overflow;
+    q.tile_bits = c->tile_bits; q.overflow = (int*)c->overflow.word();
     q.split_traffic = c->n > kSplitTrafficPoints && (!c->grouped || c->cfg.far_field == NOMAD_FAR_FIELD_SAMPLED);
     return q;
 }
@@ -292,6 +292,9 @@ void with_edge_pass_kernel_s(const nomad_ctx* c, Fn fn) {
     else if (c->pool_rounds == 4) k = k_edges_pooled<S, 4, 1024>;
     else if (c->pool_rounds == 8) k = k_edges_pooled<S, 8, 1024>;
     else if (c->bin_block == 512) k = c->sorted_records ? k_edges_binned<S, 512, true> : k_edges_binned<S, 512, false>;
+    else if (c->bin_block == kSmallBinBlock && kind == kPlainEdges) k = k_edges_binned<S, kSmallBinBlock, true, 1, kPlainEdges>;
+    else if (c->bin_block == kSmallBinBlock && kind == kGroupedEdges) k = k_edges_binned<S, kSmallBinBlock, true, 1, kGroupedEdges>;
+    else if (c->bin_block == kSmallBinBlock) k = k_edges_binned<S, kSmallBinBlock, true, 1, kFarEdges>;
     else if (!c->sorted_records && c->flush_rounds == 2) k = k_edges_binned<S, 1024, false, 2>;
     else if (!c->sorted_records) k = k_edges_binned<S, 1024, false, 1>;
     fn(k);
@@ -380,15 +383,16 @@ int check_ready(nomad_ctx* c, bool need_theta) {
     return NOMAD_OK;
 }
 
-int copy_out(nomad_ctx* c, void* dst, const void* src, size_t bytes, int mem) {
+// Waits for the stream; fails if a workgroup's chunk range was exceeded in what ran.
+int finish(nomad_ctx* c) {
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (c->overflow) {
-        int ov = 0;
-        HIP_TRY(c, hipMemcpy(&ov, c->overflow, sizeof(int), hipMemcpyDeviceToHost));
-        if (ov) return fail(c, NOMAD_E_HIP, "internal error: record pool bound exceeded");
-    }
-    HIP_TRY(c, hipMemcpy(dst, src, bytes, out_kind(mem)));
+    if (c->overflow.word() && *(const volatile int*)c->overflow.word()) return fail(c, NOMAD_E_HIP, "internal error: record pool bound exceeded");
     return NOMAD_OK;
+}
+
+int copy_out(nomad_ctx* c, void* dst, const void* src, size_t bytes, int mem) {
+    HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, out_kind(mem), c->stream));
+    return finish(c);
 }
 
 }  // namespace
@@ -674,7 +678,9 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
     TRY(dev_alloc(c, &c->mu, (size_t)R));
     TRY(dev_alloc(c, &c->cinfo, (size_t)R));
     TRY(dev_alloc(c, &c->loss_partial, (size_t)c->edge_grid));
-    TRY(dev_alloc(c, &c->loss_out, 1));
+    if (!c->loss_out.word()) HTRY(c->loss_out.take());
+    if (!c->overflow.word()) HTRY(c->overflow.take());
+    *c->overflow.word() = 0ull;   // (nothing of this context is running)
     if (c->cfg.scatter_mode == NOMAD_SCATTER_DETERMINISTIC) {
         TRY(dev_alloc(c, &c->ghead, (size_t)n));
         // Binned scatter of the tail and negative forces: needs a compile-time s and per-tile tables
@@ -691,7 +697,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         int compute_units = 0;
         HTRY(hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, c->cfg.device));
         compute_units = std::max(1, compute_units);
-        coarsen_tiles(plan, n, s, compute_units, edge_kind(c) != kAnyEdges);
+        fit_tiles(plan, want_plan, compute_units, edge_kind(c) != kAnyEdges);
         const int tile_bits = plan.tile_bits, bin_block = plan.bin_block, wg_per_cu = plan.wg_per_cu, pool_rounds = plan.pool_rounds;
         const uint32_t n_bins = plan.n_bins;
         const bool sorted = plan.sorted, distinct = plan.distinct_kernel;
@@ -705,7 +711,10 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
             c->flush_rounds = plan.flush_rounds;
             c->pool_rounds = pool_rounds;
             c->distinct_kernel = distinct;
-            c->n_wg = compute_units * wg_per_cu;
+            // one workgroup per compute unit, fewer where there is less work (the tile pass reads a chain of each)
+            const int64_t units = distinct && pool_rounds ? (int64_t)c->pool_blocks : pool_rounds ? (E + c->cfg.pool_block - 1) / c->cfg.pool_block + 1
+                                                                                              : (E + bin_block - 1) / bin_block;
+            c->n_wg = (int)std::min<int64_t>((int64_t)compute_units * wg_per_cu, units);
             c->n_bins = n_bins;
             c->tile_bits = tile_bits;
             unsigned long long* total_dev = nullptr;
@@ -735,10 +744,9 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 ok = dev_alloc(c, &c->pool, (size_t)c->max_chunks * kChunk * 3) == NOMAD_OK &&
                      dev_alloc(c, &c->chunk_prev, c->max_chunks) == NOMAD_OK && dev_alloc(c, &c->chain_head, chains) == NOMAD_OK &&
                      dev_alloc(c, &c->chain_fill, chains) == NOMAD_OK && dev_alloc(c, &c->head, (size_t)E) == NOMAD_OK &&
-                     dev_alloc(c, &c->overflow, 1) == NOMAD_OK && (c->phases == 1 || dev_alloc(c, &c->carry, (size_t)n * 2) == NOMAD_OK);
+                     (c->phases == 1 || dev_alloc(c, &c->carry, (size_t)n * 2) == NOMAD_OK);
                 if (ok) ok = prepare_binned(c) == NOMAD_OK;
                 if (ok) {
-                    HTRY(hipMemsetAsync(c->overflow, 0, sizeof(int), st));
                     hipLaunchKernelGGL(k_edge_heads, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, n, c->head);
                     hipLaunchKernelGGL(k_zero_f2, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->ghead, n);
                     c->binned = true;
@@ -753,7 +761,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 why = buf;
                 (void)hipGetLastError();
                 dev_free(c, c->pool); dev_free(c, c->chunk_prev); dev_free(c, c->chain_head); dev_free(c, c->chain_fill); dev_free(c, c->wg_pool_begin);
-                dev_free(c, c->head); dev_free(c, c->overflow); dev_free(c, c->carry);
+                dev_free(c, c->head); dev_free(c, c->carry);
                 c->phases = 1;
                 c->pool_rounds = 0;
                 c->distinct_kernel = false;
@@ -898,9 +906,11 @@ int nomad_loss(nomad_ctx* c, int32_t t_sample, double* out_host) {
     { Timed tm(c, NOMAD_K_LOSS);
       launch_edges<kModeLoss>(c, a);
       hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(kBlock), 0, c->stream, c->loss_partial, c->edge_grid, 1.0 / (double)c->n,
-                         c->loss_out); }
+                         (double*)c->loss_out.word()); }
     HIP_TRY(c, hipGetLastError());
-    return copy_out(c, out_host, c->loss_out, sizeof(double), NOMAD_HOST);
+    rc = finish(c);
+    if (rc == NOMAD_OK) *out_host = *(const volatile double*)c->loss_out.word();
+    return rc;
 }
 
 int nomad_get_embedding(nomad_ctx* c, float* out, int mem) {

@@ -110,7 +110,7 @@ def test_principal_axes(n, d):
 
 
 # ---------------------------------------------------------------- the edge pass
-def test_coarse_tiles(tmp_path):
+def test_fitted_tiles(tmp_path):
     import json
     import os
     import subprocess
@@ -126,26 +126,27 @@ int main(int, char** argv) {
     q.n = atoll(argv[1]); q.E = 30 * q.n; q.s = atoi(argv[2]); q.pool_size = atoi(argv[3]); q.pool_block = 8192; q.pool_line = 16; q.pool_distinct = true;
     EdgePlan p = plan_edge_pass(q);
     const uint32_t before = p.n_bins;
-    coarsen_tiles(p, q.n, q.s, 256);
-    printf("[%d, %u, %u, %d, %d, %d, %zu]\n", p.tile_bits, p.n_bins, before, (int)p.sorted, p.pool_rounds, p.flush_rounds,
-           binned_lds_bytes(p.n_bins, q.s, 1024, p.sorted, p.sorted ? p.flush_rounds : 1));
+    fit_tiles(p, q, 256);
+    printf("[%d, %u, %u, %d, %d, %d, %d, %d]\n", p.tile_bits, p.n_bins, before, (int)p.sorted, p.pool_rounds, p.flush_rounds, p.bin_block,
+           (int)edge_tables_fit(p, q));
 }
 ''')
     exe = str(tmp_path / "plan")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(root, "paper_2505_15511_amd", "csrc"), str(src), "-o", exe], check=True)
-    for n, s, pool in [(1, 5, 0), (65_535, 5, 0), (65_536, 5, 0), (65_793, 8, 0), (1_000_000, 5, 0), (2_097_152, 2, 0), (2_097_153, 8, 0),
+    for n, s, pool in [(1, 5, 0), (17, 5, 0), (2_000, 5, 0), (2_184, 8, 0), (2_185, 8, 0), (4_097, 2, 0), (3_001, 5, 4096), (65_535, 5, 0), (65_536, 5, 0), (65_793, 8, 0), (1_000_000, 5, 0), (2_097_152, 2, 0), (2_097_153, 8, 0),
                        (10_000_000, 5, 0), (10_000_000, 2, 0), (60_000_000, 2, 0), (3_000_017, 5, 4096)]:
-        bits, bins, before, is_sorted, pool_rounds, rounds, lds = json.loads(subprocess.run([exe, str(n), str(s), str(pool)], check=True, capture_output=True, text=True).stdout)
-        assert (bins - 1) << bits < n <= bins << bits and bins <= before
+        bits, bins, before, is_sorted, pool_rounds, rounds, block, fits = json.loads(subprocess.run([exe, str(n), str(s), str(pool)], check=True, capture_output=True, text=True).stdout)
+        assert (bins - 1) << bits < n <= bins << bits and fits
+        assert bins <= max(before, 256) and bits >= 4
         if is_sorted and not pool_rounds:
             assert (n >> bits) <= 256 or bits == 13
-            assert lds <= 160 * 1024 - 256 and rounds in (1, 2)
-        else:
+            assert rounds in (1, 2) and (block == 256) == (30 * n <= 256 * 256)
+        elif n > 65_536:
             assert bins == before
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [255, 257, 65_537, 140_001])
+@pytest.mark.parametrize("n", [255, 257, 4_097, 7_000, 65_537, 140_001])
 @pytest.mark.parametrize("s", [0, 1, 5, 7, 8])
 @pytest.mark.parametrize("grouped", [False, True])
 def test_sorted_records_reach_their_points(n, s, grouped):
