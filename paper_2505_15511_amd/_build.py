@@ -11,7 +11,7 @@ LIB_PATH = os.environ.get("NOMAD_LIBRARY_PATH") or os.path.join(_PKG, "libnomad.
 SOURCES = [os.path.join(_PKG, "csrc", "nomad.hip"), os.path.join(_PKG, "csrc", "knn.hip"), os.path.join(_PKG, "csrc", "knn_filter.hip"),
            os.path.join(_PKG, "csrc", "pca.hip"), os.path.join(_PKG, "csrc", "probes.hip")]
 HEADERS = [os.path.join(_PKG, "csrc", "nomad_kernels.h"), os.path.join(_PKG, "csrc", "knn_kernels.h"),
-           os.path.join(_PKG, "csrc", "knn_filter.h"), os.path.join(_PKG, "csrc", "knn_filter_kernel.h"),
+           os.path.join(_PKG, "csrc", "knn_filter.h"), os.path.join(_PKG, "csrc", "knn_filter_kernel.h"), os.path.join(_PKG, "csrc", "filter_scale.h"),
            os.path.join(_PKG, "csrc", "metrics_kernels.h"), os.path.join(_PKG, "csrc", "philox.h"),
            os.path.join(_PKG, "csrc", "pca_kernels.h"), os.path.join(_PKG, "csrc", "host_util.h"),
            os.path.join(_PKG, "csrc", "edge_plan.h"),

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "filter_scale.h"
+
 namespace nomad_knn {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -53,23 +55,6 @@ struct KnnSets {
     const int32_t* self_row;     // or, per query row, the candidate row that is the query itself (nullptr: see same_set)
 };
 
-// Scale of a group's rows: the power of two 2^e that brings |x'| <= sqrt(M) to at most 2^14.
-__device__ __forceinline__ int knn_scale_exponent(uint32_t max_bits) {
-    int x = 0;
-    (void)frexpf(__uint_as_float(max_bits), &x);          // M = f 2^x, 1/2 <= f < 1 (0: x = 0)
-    return max(-60, min(60, 14 - ((x + 1) >> 1)));
-}
-// Bound on |filter key - exact key| for rows of d values whose centred squared norms are at most M, u = 2^-24:
-//   products     hi hi + hi lo + lo hi leaves out lo lo and what lo was rounded by: 3 2^-22 |q||c|; float16 numbers below
-//                2^-14 taken as zero: 2^-13 of a scaled row element, 2^-28 sqrt(d) |q||c| (or, where the scale is at its
-//                limit, 2^-72 sqrt(d M)); doubled in the key
-//   sums         |c|^2 / 2 and d products, each addition rounded by at most 2 u of the sum of magnitudes, at most 3/2 M
-//                (whatever the order inside a matrix instruction), doubled in the key: 6 (d + 1) u M; the two small
-//                products' sums are 2^-10 of that
-//   norm, final combination, centring in float32: (d + 8) u M + 8 u M
-__device__ __forceinline__ double knn_filter_eps(int32_t d, double M) {
-    return (7.0 * (double)(d + 4) + 64.0) * 5.9604644775390625e-08 * M * 1.01 + 1e-12 * M + 1e-20 * sqrt(M);
-}
 __device__ __forceinline__ int32_t knn_row(const int32_t* members, uint32_t pos) { return members ? members[pos] : (int32_t)pos; }
 
 // ---------------------------------------------------------------- stage 1: the filter on the matrix cores
@@ -160,7 +145,8 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     const int32_t grp = blk.cluster;
     if (grp < 0) return;                                      // no work: fills a list up
     const uint32_t c0 = P.cstart[grp], ct0 = P.C.tstart[grp];
-    const int32_t n_tiles = (int32_t)(P.C.tstart[grp + 1] - ct0);
+    // a group whose keys are not all finite (knn_filter_usable) passes nothing on: its queries are the exact path's
+    const int32_t n_tiles = knn_filter_usable(P.Q.max_bits[grp], P.C.max_bits[grp]) ? (int32_t)(P.C.tstart[grp + 1] - ct0) : 0;
     const uint32_t q0g = P.qstart[grp];
     const int32_t n_qg = (int32_t)(P.qstart[grp + 1] - q0g);
     const uint32_t qt = P.Q.tstart[grp] + (uint32_t)(blk.q0 + wave);

@@ -270,7 +270,8 @@ __device__ __forceinline__ double exact_distance(const float* __restrict__ x, co
 // (5.9 TB/s out of the caches); with few of them exact: 0.89 ms.
 // Certified, i.e. no point that the filter left out (key >= tau, exact key >= tau - eps) is nearer than the k-th, when the
 // k-th key lies below tau by more than twice the bound (k candidates have exact keys up to key + eps), or else the k-th
-// exact key, D_k - |q|^2, does by more than the bound; otherwise the query is flagged.
+// exact key, D_k - |q|^2, does by more than the bound; otherwise the query is flagged.  So is every query of a group that the
+// filter cannot work on.
 // G lanes per query (16, 32 or 64, at least the list length), one per candidate: short lists share a wavefront.
 template <int G>
 __global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32_t* __restrict__ cand, const float* __restrict__ keys,
@@ -288,6 +289,10 @@ __global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32
     const double key = c >= 0 ? (double)keys[p * list_len + lane] : __builtin_inf();
     const float t = tau[p];
     const int32_t g = P.group_of_q ? P.group_of_q[q] : 0;
+    if (!knn_filter_usable(P.Q.max_bits[g], P.C.max_bits[g])) {   // the same for every lane of the query
+        if (lane == 0) flagged[atomicAdd(n_flagged, 1u)] = q;
+        return;
+    }
     const double eps = knn_filter_eps(d, fmax((double)__uint_as_float(P.Q.max_bits[g]), (double)__uint_as_float(P.C.max_bits[g])));
     const int first = (int)(threadIdx.x & 63u) - lane;   // of this query's lanes in the wavefront
     const auto votes = [&](bool v) { return (__ballot(v) >> first) & (~0ull >> (64 - G)); };
@@ -375,7 +380,7 @@ __device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (c[u] < 0 || c[u] == self) continue;
-            double xD = D[u];
+            double xD = D[u] == D[u] ? D[u] : __builtin_inf();   // no number: as far as can be, so that every candidate has a place in the order
             int32_t xP = c[u];
             // slot k - 1 is the list's last used slot: what does not come before it cannot be among this thread's k smallest
             if (!(wP < 0 || xD < wD || (xD == wD && xP < wP))) continue;
@@ -451,6 +456,10 @@ __global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const in
     const uint32_t count = *n_todo, per = 256u / (uint32_t)width, lane = threadIdx.x % (uint32_t)width;
     for (uint32_t x = blockIdx.x * per + threadIdx.x / (uint32_t)width; x < count; x += gridDim.x * per) {
         const int32_t q = knn_row(P.qmembers, (uint32_t)todo[x]), g = P.group_of_q ? P.group_of_q[q] : 0;
+        if (!knn_filter_usable(P.Q.max_bits[g], P.C.max_bits[g])) {
+            if (lane == 0u) flagged[atomicAdd(n_flagged, 1u)] = q;
+            continue;
+        }
         const float* xq = P.XQ + (int64_t)q * P.d;
         const int32_t c = cand[(size_t)x * width + lane];
         double D = c >= 0 ? exact_distance(xq, P.XC + (int64_t)c * P.d, P.d) : __builtin_inf();
@@ -468,10 +477,11 @@ __global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const in
             if (oD < D || (oD == D && oc < best)) { D = oD; best = oc; }
         }
         if (lane != 0u) continue;
-        out[q] = best;
+        const bool found = best != 0x7fffffff;
+        if (found) out[q] = best;
         const double eps = knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[g]), (double)__uint_as_float(P.C.max_bits[g])));
         const float t = tau[x];
-        if (t < __builtin_inff() && !(D - qn + eps < (double)t)) flagged[atomicAdd(n_flagged, 1u)] = q;
+        if (!found || (t < __builtin_inff() && !(D - qn + eps < (double)t))) flagged[atomicAdd(n_flagged, 1u)] = q;
     }
 }
 
@@ -593,11 +603,11 @@ __global__ void __launch_bounds__(256) k_sort_scatter(const int32_t* __restrict_
     }
 }
 
-// first position of every label in the sorted labels (lstart[K] = n)
+// first position of every label in the sorted labels (lstart[K] = n); never a store outside lstart, whatever the labels hold
 __global__ void __launch_bounds__(256) k_label_starts(const int32_t* __restrict__ keys, int64_t n, int32_t K, uint32_t* __restrict__ lstart) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i > n) return;
-    const int32_t cur = i < n ? keys[i] : K, prev = i > 0 ? keys[i - 1] : -1;
+    const int32_t cur = i < n ? min(keys[i], K) : K, prev = i > 0 ? max(keys[i - 1], -1) : -1;
     for (int32_t j = prev + 1; j <= cur; ++j) lstart[j] = (uint32_t)i;
 }
 

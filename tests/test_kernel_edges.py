@@ -167,3 +167,60 @@ def test_sorted_records_reach_their_points(n, s, grouped):
         nm.epoch(1)
         grads.append(np.asarray(nm.get_gradient(), dtype=np.float64))
     assert np.abs(grads[0] - grads[1]).max() <= 1e-6 * np.abs(grads[1]).max()
+
+
+# ---------------------------------------------------------------- rows whose filter keys are not finite
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,k", [(20, 8), (260, 15), (140, 20)])
+@pytest.mark.parametrize("outlier", [2e18, 1e20, 3e38])
+def test_neighbours_next_to_a_sentinel(d, k, outlier):
+    rng = np.random.default_rng(d)
+    c = rng.permutation(np.repeat(np.arange(4), [12, 200, 90, 1]))
+    X = (rng.normal(size=(len(c), d)) + 3.0 * rng.normal(size=(4, d))[c]).astype(np.float32)
+    X[np.flatnonzero(c == 0)[0], 3] = outlier
+    X[np.flatnonzero(c == 1)[:2], 0] = [outlier, -outlier]
+    out, stats = knn_in_clusters(X, c, 4, k, return_stats=True)
+    assert np.array_equal(out.astype(np.int64), ko.in_cluster_knn(X, c, k)[0])
+    assert outlier < 1e19 or stats["fallback_queries"] >= 212
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,K", [(20, 7), (260, 40), (400, 3)])
+@pytest.mark.parametrize("outlier", [1e20, -3e38])
+def test_partition_next_to_a_sentinel(d, K, outlier):
+    rng = np.random.default_rng(d + K)
+    X = rng.normal(size=(1200, d)).astype(np.float32)
+    X[7, 2] = outlier
+    C0 = X[rng.choice(1200, K, replace=False)].copy()
+    C_ref, lab_ref, it_ref, _ = km.lloyd(X, C0, 3)
+    C, lab, it, _ = kmeans_lloyd(X, C0, 3)
+    assert it == it_ref and np.array_equal(lab.astype(np.int64), lab_ref) and np.array_equal(C, C_ref)
+
+
+@pytest.mark.gpu
+def test_partition_far_from_its_starting_centroids():
+    X = (1e-15 * np.random.default_rng(1).normal(size=(1200, 16))).astype(np.float32)   # the points' scale times the centroids' norms overflows
+    C0 = np.stack([X[0], X[1] + np.float32(3e17), X[2] - np.float32(1e17)]).astype(np.float32)
+    C_ref, lab_ref, it_ref, _ = km.lloyd(X, C0, 3)
+    C, lab, it, _ = kmeans_lloyd(X, C0, 3)
+    assert it == it_ref and np.array_equal(lab.astype(np.int64), lab_ref) and np.array_equal(C, C_ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_labels_stay_in_range_whatever_the_rows_hold(value):
+    X = np.random.default_rng(2).normal(size=(700, 20)).astype(np.float32)
+    C0 = X[:300].copy()
+    X[[0, 5, 699]] = value
+    _, lab, _, _ = kmeans_lloyd(X, C0, 3)
+    assert lab.min() >= 0 and lab.max() < 300
+
+
+@pytest.mark.gpu
+def test_preservation_next_to_a_sentinel():
+    rng = np.random.default_rng(3)
+    X = rng.normal(size=(9000, 12)).astype(np.float32)
+    Y = rng.normal(size=(9000, 3)).astype(np.float32)
+    X[8999, 1], Y[0, 2] = 1e20, -1e20
+    q = np.r_[0, 8999, rng.choice(8000, 60, replace=False) + 1].astype(np.int32)
+    assert neighbourhood_preservation(X, Y, 15, q)[0] == mo.neighbourhood_preservation(X, Y, 15, q)[0]
