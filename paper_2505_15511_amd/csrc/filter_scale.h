@@ -44,8 +44,11 @@ NOMAD_BOTH bool knn_filter_usable(uint32_t q_bits, uint32_t c_bits) {
 //                (whatever the order inside a matrix instruction), doubled in the key: 6 (d + 1) u M; the two small
 //                products' sums are 2^-10 of that
 //   norm, final combination, centring in float32: (d + 8) u M + 8 u M
+//   underflow    a square is a multiple of 2^-149 and zero below 2^-150: norms miss up to d 2^-150 each, and a side whose M
+//                came out as zero is multiplied as zero: at most 4 d 2^-150 < 1e-40 in the key (next to a larger side:
+//                2 sqrt(d) 2^-75 sqrt(M), inside the products' term)
 NOMAD_BOTH double knn_filter_eps(int32_t d, double M) {
-    return (7.0 * (double)(d + 4) + 64.0) * 5.9604644775390625e-08 * M * 1.01 + 1e-12 * M + 1e-20 * sqrt(M);
+    return (7.0 * (double)(d + 4) + 64.0) * 5.9604644775390625e-08 * M * 1.01 + 1e-12 * M + 1e-20 * sqrt(M) + 1e-40;
 }
 
 }  // namespace nomad_knn

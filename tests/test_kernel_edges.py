@@ -224,3 +224,16 @@ def test_preservation_next_to_a_sentinel():
     X[8999, 1], Y[0, 2] = 1e20, -1e20
     q = np.r_[0, 8999, rng.choice(8000, 60, replace=False) + 1].astype(np.int32)
     assert neighbourhood_preservation(X, Y, 15, q)[0] == mo.neighbourhood_preservation(X, Y, 15, q)[0]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scale", [1e-20, 1e-22, 1e-24, 1e-30])
+def test_neighbours_of_rows_whose_squares_underflow(scale):
+    rng = np.random.default_rng(4)
+    X = (scale * rng.normal(size=(400, 18))).astype(np.float32)
+    c = rng.integers(0, 3, 400)
+    assert np.array_equal(knn_in_clusters(X, c, 3, 5).astype(np.int64), ko.in_cluster_knn(X, c, 5)[0])
+    C0 = X[:9].copy()
+    C_ref, lab_ref, it_ref, _ = km.lloyd(X, C0, 3)
+    C, lab, it, _ = kmeans_lloyd(X, C0, 3)
+    assert it == it_ref and np.array_equal(lab.astype(np.int64), lab_ref) and np.array_equal(C, C_ref)
