@@ -122,6 +122,19 @@ def _marshal(x, np_dtype, count=None):
     return a.ctypes.data_as(C.c_void_p), NOMAD_HOST, a
 
 
+def _call_stream(device, stream):
+    """The stream of a call on device tensors: `stream`, or the current one (None).  Where it is not the current one, what
+    the current stream still has to do comes first: it may be making the inputs, or working on what a result's memory
+    belonged to before (the caching allocator hands that out in the current stream's order)."""
+    import torch
+    current = torch.cuda.current_stream(device)
+    if stream is None:
+        return current.cuda_stream
+    if current.cuda_stream != int(stream):
+        current.synchronize()
+    return stream
+
+
 def copy_probe(dst, src, stream=None):
     """Enqueue the library's streaming copy kernel between two device tensors of equal size."""
     import torch
@@ -180,8 +193,7 @@ def knn_in_clusters(X, cluster_of, n_clusters, k, device=0, stream=None, return_
         import torch
         out = torch.empty((n, int(k)), dtype=torch.int32, device=keep_x.device)
         po = C.c_void_p(out.data_ptr())
-        if stream is None:
-            stream = torch.cuda.current_stream(device).cuda_stream
+        stream = _call_stream(device, stream)
     else:
         out = np.empty((n, int(k)), dtype=np.int32)
         po = out.ctypes.data_as(C.c_void_p)
@@ -212,8 +224,7 @@ def kmeans_lloyd(X, centroids, max_iters, device=0, stream=None):
         import torch
         labels = torch.empty(n, dtype=torch.int32, device=keep_x.device)
         pl = C.c_void_p(labels.data_ptr())
-        if stream is None:
-            stream = torch.cuda.current_stream(device).cuda_stream
+        stream = _call_stream(device, stream)
     else:
         labels = np.empty(n, dtype=np.int32)
         pl = labels.ctypes.data_as(C.c_void_p)
@@ -233,9 +244,8 @@ def _two_spaces(X, Y, stream, device):
     py, m1, keep_y = _marshal(Y, np.float32, n * d_low)
     if m0 != m1:
         raise ValueError("X and Y must live in the same memory space")
-    if m0 == NOMAD_DEVICE and stream is None:
-        import torch
-        stream = torch.cuda.current_stream(device).cuda_stream
+    if m0 == NOMAD_DEVICE:
+        stream = _call_stream(device, stream)
     return n, d, d_low, px, py, m0, C.c_void_p(int(stream) if stream else None), (keep_x, keep_y)
 
 
@@ -290,8 +300,7 @@ def pca_init(X, std0=0.0, device=0, stream=None, return_stats=False):
         import torch
         theta = torch.empty(n, 2, dtype=torch.float32, device=keep.device)
         pt = C.c_void_p(theta.data_ptr())
-        if stream is None:
-            stream = torch.cuda.current_stream(device).cuda_stream
+        stream = _call_stream(device, stream)
     else:
         theta = np.empty((n, 2), dtype=np.float32)
         pt = theta.ctypes.data_as(C.c_void_p)
@@ -323,8 +332,7 @@ def kmeans_lsh_init(X, K, planes, anchors=None, device=0, stream=None, return_bu
         cen = torch.empty(int(K), d, dtype=torch.float32, device=keep_x.device)
         buckets = torch.empty(n, dtype=torch.int32, device=keep_x.device)
         pc, pb = C.c_void_p(cen.data_ptr()), C.c_void_p(buckets.data_ptr())
-        if stream is None:
-            stream = torch.cuda.current_stream(device).cuda_stream
+        stream = _call_stream(device, stream)
     else:
         cen = np.empty((int(K), d), dtype=np.float32)
         buckets = np.empty(n, dtype=np.int32)
@@ -405,10 +413,14 @@ class Nomad:
         mems = {m for m in (m0, m1, m2, m3, m4) if m is not None}
         if len(mems) > 1:
             raise ValueError("all graph buffers must live in the same memory space")
+        if NOMAD_DEVICE in mems:
+            _call_stream(self.device, self.cfg.stream or 0)
         self._check(self.lib.nomad_set_graph(self.ctx, rp, ci, w, co, cg, mems.pop()))
 
     def set_embedding(self, theta):
         p, mem, keep = _marshal(theta, np.float32, 2 * self.n)
+        if mem == NOMAD_DEVICE:
+            _call_stream(self.device, self.cfg.stream or 0)
         self._check(self.lib.nomad_set_embedding(self.ctx, p, mem))
 
     # ---- the path
@@ -426,6 +438,7 @@ class Nomad:
             import torch
             tdt = {np.float32: torch.float32, np.int32: torch.int32}[np_dtype]
             t = torch.empty(shape, dtype=tdt, device=f"cuda:{self.device}")
+            _call_stream(self.device, self.cfg.stream or 0)
             self._check(fn(self.ctx, *pre, C.c_void_p(t.data_ptr()), NOMAD_DEVICE))
             return t
         a = np.empty(shape, dtype=np_dtype)

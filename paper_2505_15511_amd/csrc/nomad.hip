@@ -390,7 +390,10 @@ int finish(nomad_ctx* c) {
     return NOMAD_OK;
 }
 
+// A device destination may be a block that work on the null stream still writes (an allocator hands out what was freed there):
+// the copy, on the context's stream, waits for that work.
 int copy_out(nomad_ctx* c, void* dst, const void* src, size_t bytes, int mem) {
+    if (mem == NOMAD_DEVICE && c->stream) HIP_TRY(c, hipStreamSynchronize(nullptr));
     HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, out_kind(mem), c->stream));
     return finish(c);
 }

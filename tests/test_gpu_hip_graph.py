@@ -73,3 +73,28 @@ def test_recorded_epochs_in_atomic_mode_stay_within_the_bar():
             assert np.abs(nm.get_embedding() - ref.get_embedding()).max() < 1e-4
         nm.close()
         ref.close()
+
+
+def test_results_wait_for_the_work_their_memory_still_has():
+    """A context on a side stream, called outside of it: the result's block was freed with work on the default stream pending."""
+    w = workloads.make_config(3, scale=0.2)
+    side = torch.cuda.Stream()
+    nm = Nomad.from_workload(w, SCATTER_DETERMINISTIC, stream=side.cuda_stream)
+    nm.epoch(0)
+    theta, g = nm.get_embedding(), nm.get_gradient()
+    nodes = torch.empty(1 << 26, device="cuda")
+    for get, want in ((nm.get_embedding, theta), (nm.get_gradient, g)):
+        block = torch.empty(w.n, 2, device="cuda")
+        for _ in range(40):
+            nodes.normal_()                      # some milliseconds ahead of the write below
+        block.fill_(7.0)
+        del block
+        out = get(device=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), want)
+    # inputs made on the current stream: a conversion that has not run yet
+    for _ in range(40):
+        nodes.normal_()
+    nm.set_embedding(torch.from_numpy(theta).cuda().double() + 1.0)
+    assert np.array_equal(nm.get_embedding(), theta + np.float32(1.0))
+    nm.close()
