@@ -58,8 +58,12 @@ def test_recorded_epochs_in_atomic_mode_stay_within_the_bar():
     with torch.cuda.stream(side):
         ref = Nomad.from_workload(w, SCATTER_DETERMINISTIC, stream=side.cuda_stream)
         nm = Nomad.from_workload(w, SCATTER_ATOMIC, stream=side.cuda_stream)
+        # The bar: every epoch's gradient within 1e-5 of its largest component (the atomic path's bar), so positions within the
+        # sum of eta_t times that: 2.8e-4 here.  Forty eager runs ended 1.9e-5 to 7.4e-5 apart, a later one 1.04e-4.
+        bar = 0.0
         for t in range(T):
             ref.epoch(t)
+            bar += 1e-5 * w.lr0 * (1.0 - t / w.n_epochs) * float(np.abs(ref.get_gradient()).max())
         nm.epoch(0)
         nm.set_embedding(theta0)
         graph = torch.cuda.CUDAGraph()
@@ -70,7 +74,7 @@ def test_recorded_epochs_in_atomic_mode_stay_within_the_bar():
             nm.set_embedding(theta0)
             graph.replay()
             side.synchronize()
-            assert np.abs(nm.get_embedding() - ref.get_embedding()).max() < 1e-4
+            assert np.abs(nm.get_embedding() - ref.get_embedding()).max() < bar
         nm.close()
         ref.close()
 
