@@ -128,13 +128,14 @@ void dev_free(nomad_ctx* c, T*& p) {
     if (p) {
         auto it = c->allocations.find(p);
         if (it != c->allocations.end()) { c->device_bytes -= (int64_t)it->second; c->allocations.erase(it); }
-        DevicePool::get().give(p);   // (every caller has waited for the context's stream)
+        DevicePool::get().give(p);   // (every caller has waited for the work that uses it)
     }
     p = nullptr;
 }
 
 void free_graph(nomad_ctx* c) {
-    if (!c->allocations.empty()) (void)hipStreamSynchronize(c->stream);   // nothing that is given back may still be in use
+    // nothing that is given back may still be in use, on any stream: epochs recorded into a graph run where it is replayed
+    if (!c->allocations.empty()) (void)hipDeviceSynchronize();
     dev_free(c, c->row_ptr); dev_free(c, c->col); dev_free(c, c->cluster_of); dev_free(c, c->group_of_cluster);
     dev_free(c, c->pe); dev_free(c, c->counts); dev_free(c, c->gbase); dev_free(c, c->gcount); dev_free(c, c->chunk_start);
     dev_free(c, c->gomega); dev_free(c, c->hinfo); dev_free(c, c->gmembers); dev_free(c, c->cmembers); dev_free(c, c->chunks); dev_free(c, c->mean_partial);
@@ -535,7 +536,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
     if (rc == NOMAD_OK) rc = dev_alloc(c, &first, (size_t)R);
     if (rc == NOMAD_OK) rc = dev_alloc(c, &gfirst, (size_t)R);
     if (rc == NOMAD_OK) rc = dev_alloc(c, &boundaries, 2);
-    auto cleanup_tmp = [&]() { dev_free(c, wdev); dev_free(c, first); dev_free(c, gfirst); dev_free(c, boundaries); };
+    auto cleanup_tmp = [&]() { (void)hipStreamSynchronize(st); dev_free(c, wdev); dev_free(c, first); dev_free(c, gfirst); dev_free(c, boundaries); };
     if (rc != NOMAD_OK) { cleanup_tmp(); free_graph(c); return rc; }
 #define HTRY2(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) { cleanup_tmp(); free_graph(c); return fail(c, e_ == hipErrorOutOfMemory ? NOMAD_E_OOM : NOMAD_E_HIP, "%s: %s", #call, hipGetErrorString(e_)); } } while (0)
     HTRY2(hipMemsetAsync(c->flags, 0, sizeof(int) * kFlagCount, st));
@@ -557,7 +558,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                      : hflags[kFlagWeight] ? "weights must be finite, >= 0, with a positive sum on every non-empty row"
                      : hflags[kFlagCluster] ? "cluster_of entry outside 0..|R|-1" : nullptr;
     if (what) { cleanup_tmp(); free_graph(c); return fail(c, NOMAD_E_BAD_GRAPH, "%s", what); }
-    dev_free(c, wdev);
+    dev_free(c, wdev);   // (the check has been waited for)
 
     // ---- partition tables (host arithmetic on |R|-sized arrays only)
     std::vector<uint32_t> hcounts(R), hfirst(R), hgfirst(R);

@@ -102,3 +102,30 @@ def test_results_wait_for_the_work_their_memory_still_has():
     nm.set_embedding(torch.from_numpy(theta).cuda().double() + 1.0)
     assert np.array_equal(nm.get_embedding(), theta + np.float32(1.0))
     nm.close()
+
+
+@pytest.mark.parametrize("ending", ["close", "set_graph"])
+def test_memory_is_given_back_when_replays_on_other_streams_have_ended(ending):
+    w = workloads.make_config(3, scale=0.02)
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        nm = Nomad.from_workload(w, SCATTER_DETERMINISTIC, stream=side.cuda_stream)
+        nm.epoch(0)
+        want = nm.get_embedding()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            nm.epoch(1)
+        side.synchronize()
+    with torch.cuda.stream(other):
+        for _ in range(300):
+            graph.replay()
+        if ending == "close":
+            nm.close()
+        else:
+            nm.set_graph(w.row_ptr, w.col_idx, w.weights, w.cluster_of, w.cluster_group)
+        assert other.query()
+    fresh = Nomad.from_workload(w, SCATTER_DETERMINISTIC)
+    fresh.epoch(0)
+    assert np.array_equal(fresh.get_embedding(), want)
+    fresh.close()
+    nm.close()
