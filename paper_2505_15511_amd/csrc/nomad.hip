@@ -507,7 +507,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         TRY(dev_alloc(c, &c->pe, (size_t)E));
         TRY(dev_alloc(c, &wdev, (size_t)E));
         hipError_t e_ = E ? hipMemcpy(wdev, weights, sizeof(float) * (size_t)E, in_kind(mem)) : hipSuccess;
-        if (e_ != hipSuccess) { dev_free(c, wdev); free_graph(c); return fail(c, NOMAD_E_HIP, "copy of weights: %s", hipGetErrorString(e_)); }
+        if (e_ != hipSuccess) { free_graph(c); dev_free(c, wdev); return fail(c, NOMAD_E_HIP, "copy of weights: %s", hipGetErrorString(e_)); }
     }
     std::vector<int32_t> hgroup;
     c->grouped = false;
@@ -515,16 +515,16 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         hgroup.resize(R);
         hipError_t e_ = hipMemcpy(hgroup.data(), cluster_group, sizeof(int32_t) * (size_t)R,
                                   mem == NOMAD_DEVICE ? hipMemcpyDeviceToHost : hipMemcpyHostToHost);
-        if (e_ != hipSuccess) { dev_free(c, wdev); free_graph(c); return fail(c, NOMAD_E_HIP, "copy of cluster_group: %s", hipGetErrorString(e_)); }
+        if (e_ != hipSuccess) { free_graph(c); dev_free(c, wdev); return fail(c, NOMAD_E_HIP, "copy of cluster_group: %s", hipGetErrorString(e_)); }
         for (int32_t r = 0; r < R; ++r)
-            if (hgroup[r] < 0 || hgroup[r] >= R) { dev_free(c, wdev); free_graph(c); return fail(c, NOMAD_E_BAD_GRAPH, "cluster_group[%d] = %d is outside 0..|R|-1", r, hgroup[r]); }
+            if (hgroup[r] < 0 || hgroup[r] >= R) { free_graph(c); dev_free(c, wdev); return fail(c, NOMAD_E_BAD_GRAPH, "cluster_group[%d] = %d is outside 0..|R|-1", r, hgroup[r]); }
         for (int32_t r = 1; r < R; ++r)
             if (hgroup[r] != hgroup[0]) c->grouped = true;   // one label everywhere == nothing approximated
-        if (c->grouped && c->cfg.pool_size > 0) { dev_free(c, wdev); free_graph(c); return fail(c, NOMAD_E_INVALID_ARG, "the pooled sampler needs a single sampling population (cluster_group = NULL)"); }
+        if (c->grouped && c->cfg.pool_size > 0) { free_graph(c); dev_free(c, wdev); return fail(c, NOMAD_E_INVALID_ARG, "the pooled sampler needs a single sampling population (cluster_group = NULL)"); }
         if (c->grouped) {
             rc = dev_alloc(c, &c->group_of_cluster, (size_t)R);
             if (rc == NOMAD_OK && hipMemcpy(c->group_of_cluster, hgroup.data(), sizeof(int32_t) * (size_t)R, hipMemcpyHostToDevice) != hipSuccess) rc = fail(c, NOMAD_E_HIP, "upload of cluster_group failed");
-            if (rc != NOMAD_OK) { dev_free(c, wdev); free_graph(c); return rc; }
+            if (rc != NOMAD_OK) { free_graph(c); dev_free(c, wdev); return rc; }
         }
     }
 
@@ -539,6 +539,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
     auto cleanup_tmp = [&]() { (void)hipStreamSynchronize(st); dev_free(c, wdev); dev_free(c, first); dev_free(c, gfirst); dev_free(c, boundaries); };
     if (rc != NOMAD_OK) { cleanup_tmp(); free_graph(c); return rc; }
 #define HTRY2(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) { cleanup_tmp(); free_graph(c); return fail(c, e_ == hipErrorOutOfMemory ? NOMAD_E_OOM : NOMAD_E_HIP, "%s: %s", #call, hipGetErrorString(e_)); } } while (0)
+    HTRY2(hipStreamSynchronize(nullptr));   // the copies above: between device buffers they may still be on their way on the null stream
     HTRY2(hipMemsetAsync(c->flags, 0, sizeof(int) * kFlagCount, st));
     HTRY2(hipMemsetAsync(c->counts, 0, sizeof(uint32_t) * (size_t)R, st));
     HTRY2(hipMemsetAsync(first, 0xFF, sizeof(uint32_t) * (size_t)R, st));
@@ -966,8 +967,8 @@ int nomad_get_means(nomad_ctx* c, float* mu, int64_t* counts, int mem) {
     if ((!mu && !counts) || (mem != NOMAD_HOST && mem != NOMAD_DEVICE)) return fail(c, NOMAD_E_INVALID_ARG, "null pointer or bad mem");
     HIP_TRY(c, hipSetDevice(c->cfg.device));
     run_means(c);
+    if (mu && (rc = copy_out(c, mu, c->mu, sizeof(float2) * (size_t)c->R, mem))) return rc;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (mu) HIP_TRY(c, hipMemcpy(mu, c->mu, sizeof(float2) * (size_t)c->R, out_kind(mem)));
     if (counts) {
         std::vector<uint32_t> h32(c->R);
         std::vector<int64_t> h64(c->R);
@@ -985,11 +986,13 @@ int nomad_get_mean_field(nomad_ctx* c, float* A, float* B, int mem) {
     if (!A || !B || (mem != NOMAD_HOST && mem != NOMAD_DEVICE)) return fail(c, NOMAD_E_INVALID_ARG, "null pointer or bad mem");
     HIP_TRY(c, hipSetDevice(c->cfg.device));
     if (!c->grouped || c->cfg.far_field == NOMAD_FAR_FIELD_SAMPLED) {
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
         if (mem == NOMAD_DEVICE) {
-            HIP_TRY(c, hipMemset(A, 0, sizeof(float) * (size_t)c->n));
-            HIP_TRY(c, hipMemset(B, 0, sizeof(float2) * (size_t)c->n));
+            HIP_TRY(c, hipStreamSynchronize(nullptr));   // (see copy_out)
+            HIP_TRY(c, hipMemsetAsync(A, 0, sizeof(float) * (size_t)c->n, c->stream));
+            HIP_TRY(c, hipMemsetAsync(B, 0, sizeof(float2) * (size_t)c->n, c->stream));
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
         } else {
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
             memset(A, 0, sizeof(float) * (size_t)c->n);
             memset(B, 0, sizeof(float2) * (size_t)c->n);
         }
@@ -997,10 +1000,8 @@ int nomad_get_mean_field(nomad_ctx* c, float* A, float* B, int mem) {
     }
     run_means(c);
     run_mean_field(c, 0, c->n);
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    HIP_TRY(c, hipMemcpy(A, c->A, sizeof(float) * (size_t)c->n, out_kind(mem)));
-    HIP_TRY(c, hipMemcpy(B, c->B, sizeof(float2) * (size_t)c->n, out_kind(mem)));
-    return NOMAD_OK;
+    if ((rc = copy_out(c, A, c->A, sizeof(float) * (size_t)c->n, mem))) return rc;
+    return copy_out(c, B, c->B, sizeof(float2) * (size_t)c->n, mem);
 }
 
 int nomad_profile(nomad_ctx* c, int enable) {

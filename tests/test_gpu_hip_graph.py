@@ -129,3 +129,30 @@ def test_memory_is_given_back_when_replays_on_other_streams_have_ended(ending):
     assert np.array_equal(fresh.get_embedding(), want)
     fresh.close()
     nm.close()
+
+
+@pytest.mark.parametrize("grouped", [False, True])
+def test_device_buffers_of_a_context_on_a_side_stream(grouped):
+    """Graph, embedding, means and mean-field sums as device buffers: copies complete before they are used or returned."""
+    import ctypes as C
+    w = workloads.make_config(3, scale=0.02, n_groups=4 if grouped else None)
+    side = torch.cuda.Stream()
+    dev = {k: None if getattr(w, k) is None else torch.as_tensor(getattr(w, k)).cuda() for k in ("row_ptr", "col_idx", "weights", "cluster_of", "cluster_group")}
+    theta = torch.as_tensor(w.theta0).cuda()
+    ref = Nomad.from_workload(w)
+    nm = Nomad.from_workload(w, stream=side.cuda_stream)
+    nm.set_graph(*dev.values())
+    nm.set_embedding(theta)
+    mu, A, B = (torch.full(shape, 7.0, device="cuda") for shape in ((nm.R, 2), (nm.n,), (nm.n, 2)))
+    counts = torch.zeros(nm.R, dtype=torch.int64, device="cuda")
+    nm._check(nm.lib.nomad_get_means(nm.ctx, C.c_void_p(mu.data_ptr()), C.c_void_p(counts.data_ptr()), 1))
+    nm._check(nm.lib.nomad_get_mean_field(nm.ctx, C.c_void_p(A.data_ptr()), C.c_void_p(B.data_ptr()), 1))
+    with torch.cuda.stream(torch.cuda.Stream()):         # a reader that no stream of the calls is ordered with
+        got = [t.cpu().numpy() for t in (mu, counts, A, B)]
+    for a, b in zip(got, (*ref.get_means(), *ref.get_mean_field())):
+        assert np.array_equal(a, b)
+    nm.epoch(0)
+    ref.epoch(0)
+    assert np.array_equal(nm.get_embedding(), ref.get_embedding())
+    nm.close()
+    ref.close()
