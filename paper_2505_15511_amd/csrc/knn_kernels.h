@@ -923,6 +923,7 @@ __global__ void __launch_bounds__(kLshSample) k_lsh_median_anchors(const float* 
             }
         }
         for (; t < d; ++t) p = __dadd_rn(p, __dmul_rn((double)h[t], (double)x[t]));
+        if (!(p == p)) p = __builtin_inf();   // no number: last in the order, so that one point has the median's rank
         sproj[s] = p;
     }
     __syncthreads();

@@ -51,6 +51,7 @@ __global__ void __launch_bounds__(256) k_merge_slices(const float* __restrict__ 
     if (t < total) {
         c = part_nbrs[((int64_t)(t / k) * m + r) * k + t % k];
         if (c >= 0) D = nomad_knn::exact_distance(AQ + r * d, A + (int64_t)c * d, d);
+        if (!(D == D)) D = __builtin_inf();   // no number: as in the slices' own order
     }
     sD[t] = D;
     sC[t] = c;
@@ -114,7 +115,8 @@ __device__ __forceinline__ PlaneGrid plane_grid(const uint32_t* __restrict__ box
     return p;
 }
 __device__ __forceinline__ int plane_cell(float x, float x0, float inv, int32_t G) {
-    return min(G - 1, max(0, (int)((x - x0) * inv)));      // monotone in x
+    const float t = (x - x0) * inv;
+    return t >= 1.f ? (int)fminf(t, (float)(G - 1)) : 0;   // monotone in x; what is no number goes to cell 0
 }
 
 // cell of every point and the number of points per cell

@@ -237,3 +237,17 @@ def test_neighbours_of_rows_whose_squares_underflow(scale):
     C_ref, lab_ref, it_ref, _ = km.lloyd(X, C0, 3)
     C, lab, it, _ = kmeans_lloyd(X, C0, 3)
     assert it == it_ref and np.array_equal(lab.astype(np.int64), lab_ref) and np.array_equal(C, C_ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [5, 700])
+def test_hash_planes_find_an_anchor_whatever_the_rows_hold(rows):
+    rng = np.random.default_rng(5)
+    X, planes = rng.normal(size=(700, 12)).astype(np.float32), rng.normal(size=(5, 12)).astype(np.float32)
+    X[rng.permutation(700)[:rows], 3] = np.nan           # their projections have no place in the order
+    _, buckets = kmeans_lsh_init(X, 20, planes, None, return_buckets=True)
+    assert buckets.min() >= 0 and buckets.max() < 20
+    Y = rng.normal(size=(9000, 3)).astype(np.float32)
+    Y[::3] = np.nan                                      # slices of candidates: the merge has a place for every one of them
+    q = np.arange(64, dtype=np.int32)
+    assert neighbourhood_preservation(Y, Y, 5, q)[0] == 5 * 64
