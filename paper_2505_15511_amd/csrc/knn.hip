@@ -180,7 +180,7 @@ struct MeanStep {
                 hipLaunchKernelGGL(kernel, dim3(blocks_of(n, kMeanSpan)), dim3(256), 0, st, dX, n, d, sorted_keys, sorted_ids, (const uint32_t*)lstart, partial);
             };
             // columns per lane: no lane idle before 16-byte loads, as far as rows are aligned for them
-            if (d % 4 == 0 && d > 128 && ((uintptr_t)dX & 15) == 0) sums(k_mean_partials<4>);
+            if (d > 128 && rows_by_16(dX, d)) sums(k_mean_partials<4>);
             else if (d % 2 == 0 && d > 64 && ((uintptr_t)dX & 7) == 0) sums(k_mean_partials<2>);
             else sums(k_mean_partials<1>);
             hipLaunchKernelGGL(k_mean_combine, dim3(entries), dim3(256), 0, st, (const MeanPartial*)partial, d, (const uint32_t*)lstart, K, dC, list, n_list);
@@ -230,11 +230,12 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     int* bad = nullptr;
     // counters that start at zero: counts, cursor, max_norm, centre, bad, n_flagged
     uint8_t* zeroed = nullptr;
-    const size_t zero_bytes = sizeof(uint32_t) * ((size_t)3 * R + (size_t)R * d + 2);
+    const size_t zero_words = ((size_t)3 * R + 2 + 3) / 4 * 4;   // ahead of the centres, whose rows are read 16 bytes at a time
+    const size_t zero_bytes = sizeof(uint32_t) * (zero_words + (size_t)R * d);
     KTRY(buf.alloc(&zeroed, zero_bytes));
     KTRY(hipMemsetAsync(zeroed, 0, zero_bytes, st));
     counts = (uint32_t*)zeroed; cursor = counts + R; max_norm = cursor + R; bad = (int*)(max_norm + R); n_flagged = (uint32_t*)(bad + 1);
-    centre = (float*)(n_flagged + 1);
+    centre = (float*)zeroed + zero_words;
     KTRY(buf.alloc(&members, (size_t)n));
     KTRY(buf.alloc(&norm, (size_t)n));
     KTRY(buf.alloc(&tau, (size_t)n));
@@ -509,10 +510,11 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     float *cnorm = nullptr, *keys = nullptr, *tau = nullptr, *centre = nullptr, *AQ = nullptr;
     int* bad = nullptr;
     uint8_t* zeroed = nullptr;   // max_q, max_c, bad, n_flagged, centre
-    const size_t zero_bytes = sizeof(uint32_t) * ((size_t)2 * G + 2 + (size_t)G * d);
+    const size_t zero_words = ((size_t)2 * G + 2 + 3) / 4 * 4;   // ahead of the centres, whose rows are read 16 bytes at a time
+    const size_t zero_bytes = sizeof(uint32_t) * (zero_words + (size_t)G * d);
     KTRY(buf.alloc(&zeroed, zero_bytes));
     KTRY(hipMemsetAsync(zeroed, 0, zero_bytes, st));
-    max_q = (uint32_t*)zeroed; max_c = max_q + G; bad = (int*)(max_c + G); n_flagged = (uint32_t*)(bad + 1); centre = (float*)(n_flagged + 1);
+    max_q = (uint32_t*)zeroed; max_c = max_q + G; bad = (int*)(max_c + G); n_flagged = (uint32_t*)(bad + 1); centre = (float*)zeroed + zero_words;
     KTRY(buf.alloc(&cand, (size_t)mq * list_len)); KTRY(buf.alloc(&keys, (size_t)mq * list_len)); KTRY(buf.alloc(&flagged, (size_t)mq)); KTRY(buf.alloc(&tau, (size_t)mq));
     KTRY(buf.alloc(&cnorm, (size_t)n)); KTRY(buf.alloc(&AQ, (size_t)mq * d));
     KTRY(buf.alloc(&self, (size_t)mq));
@@ -585,15 +587,14 @@ int neighbours_in_plane(hipStream_t st, Buffers& buf, const float* A, int64_t n,
     KTRY(buf.alloc(&box, 4)); KTRY(buf.alloc(&counts, (size_t)cells)); KTRY(buf.alloc(&tile_total, (size_t)n_tiles));
     KTRY(buf.alloc(&rank, (size_t)n)); KTRY(buf.alloc(&pos, (size_t)n)); KTRY(buf.alloc(&id, (size_t)n));
     KTRY(hipMemsetAsync(counts, 0, sizeof(uint32_t) * (size_t)cells, st));
-    const float2* Y = (const float2*)A;
     hipLaunchKernelGGL(k_plane_box_clear, dim3(1), dim3(64), 0, st, box);
-    hipLaunchKernelGGL(k_plane_box, dim3((uint32_t)std::min<int64_t>(512, blocks_of(n, 256))), dim3(256), 0, st, Y, n, box);
-    hipLaunchKernelGGL(k_plane_count, dim3(blocks_of(n, 256)), dim3(256), 0, st, Y, n, (const uint32_t*)box, G, counts, rank);
+    hipLaunchKernelGGL(k_plane_box, dim3((uint32_t)std::min<int64_t>(512, blocks_of(n, 256))), dim3(256), 0, st, A, n, box);
+    hipLaunchKernelGGL(k_plane_count, dim3(blocks_of(n, 256)), dim3(256), 0, st, A, n, (const uint32_t*)box, G, counts, rank);
     hipLaunchKernelGGL(k_sort_scan_tiles, dim3(n_tiles), dim3(256), 0, st, counts, cells, tile_total);
     hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, st, tile_total, (uint64_t)n_tiles);
-    hipLaunchKernelGGL(k_plane_place, dim3(blocks_of(n, 256)), dim3(256), 0, st, Y, n, (const uint32_t*)box, G, (const uint32_t*)counts,
+    hipLaunchKernelGGL(k_plane_place, dim3(blocks_of(n, 256)), dim3(256), 0, st, A, n, (const uint32_t*)box, G, (const uint32_t*)counts,
                        (const uint32_t*)tile_total, (const uint32_t*)rank, pos, id);
-    hipLaunchKernelGGL(k_plane_neighbours, dim3(blocks_of(m, 4)), dim3(256), 0, st, Y, n, dQ, m, k, (const uint32_t*)box, G, (const uint32_t*)counts,
+    hipLaunchKernelGGL(k_plane_neighbours, dim3(blocks_of(m, 4)), dim3(256), 0, st, A, n, dQ, m, k, (const uint32_t*)box, G, (const uint32_t*)counts,
                        (const uint32_t*)tile_total, (const float2*)pos, (const int32_t*)id, out, bad);
     KTRY(hipGetLastError());
     return NOMAD_OK;

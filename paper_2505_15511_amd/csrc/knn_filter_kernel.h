@@ -90,10 +90,10 @@ __host__ __device__ constexpr int knn_waves_per_simd(int tile, int steps, int L,
 // 16 (4) bytes per lane from global memory straight into LDS: lane l's go to byte offset `to` + 16 l (4 l).  Not known to the
 // compiler as a load: the caller waits with wait_loads, and reads what has arrived only behind a barrier.
 __device__ __forceinline__ void load_to_lds16(uint32_t to, const void* base, uint32_t byte_offset) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(byte_offset), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(byte_offset), "s"(base) : "m0", "memory");
 }
 __device__ __forceinline__ void load_to_lds4(uint32_t to, const void* base, uint32_t byte_offset) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(byte_offset), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(byte_offset), "s"(base) : "m0", "memory");
 }
 template <int LEFT>   // until at most LEFT of this wavefront's loads are outstanding
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LEFT) : "memory"); }

@@ -16,6 +16,7 @@
 #include <stdint.h>
 
 #include "knn_filter_kernel.h"
+#include "rows.h"
 
 namespace nomad_knn {
 
@@ -71,7 +72,7 @@ __global__ void __launch_bounds__(256) k_knn_norms(const float* __restrict__ X, 
         const float* x = X + i * d;
         g = cluster_of ? cluster_of[i] : 0;
         const float* c = centre + (int64_t)g * d;
-        if ((d & 3) == 0) {
+        if (rows_by_16(X, d)) {   // (the centres are the library's own, see knn.hip)
             for (int t = 4 * part; t < d; t += 4 * kNormLanes) {
                 const float4 xv = *(const float4*)(x + t), cv = *(const float4*)(c + t);
                 float v = xv.x - cv.x;
@@ -184,7 +185,7 @@ __global__ void __launch_bounds__(256) k_knn_pack(const float* __restrict__ X, i
     const float scale = ldexpf(1.f, knn_scale_exponent(max_bits[g]));
     const float* c = centre + (int64_t)g * d;
     const int tshift = tile == 32 ? 5 : 4, per_step = 64 >> tshift;   // chunks of eight columns per step
-    const bool vec = (d & 3) == 0;
+    const bool vec = rows_by_16(X, d);
     for (int x = threadIdx.x; x < (steps * 64); x += 256) {
         const int row = x & (tile - 1), chunk = x >> tshift, col = 8 * chunk;
         const uint32_t pos = pos0 + (uint32_t)row;
@@ -222,10 +223,11 @@ __global__ void __launch_bounds__(256) k_knn_pack(const float* __restrict__ X, i
 }
 
 // the oracle's distance: difference, product and running sum each rounded once, in float64, t = 0..d-1 in order
-__device__ __forceinline__ double exact_distance(const float* __restrict__ x, const float* __restrict__ y, int32_t d) {
+// (by16: rows_by_16 of both sides' arrays)
+__device__ __forceinline__ double exact_distance(const float* __restrict__ x, const float* __restrict__ y, int32_t d, bool by16) {
     double acc = 0.0;
     int t = 0;
-    if ((d & 3) == 0) {   // rows are 16-byte aligned: four values per load, still added one by one in order
+    if (by16) {   // four values per load, still added one by one in order
         for (; t + 16 <= d; t += 16) {   // eight loads in flight before the first dependent addition
             float4 a[4], b[4];
 #pragma unroll
@@ -305,7 +307,7 @@ __global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32
     const bool left_out = t < __builtin_inff() && cnt >= k;   // the same for every lane of the group
     const bool open = left_out && votes(lane == k - 1 && !(key + 2.0 * eps < (double)t)) != 0ull;
     const bool exact = c >= 0 && ((run1 > run0 && run0 < k) || (open && lane == k - 1));
-    const double D = exact ? exact_distance(xq, P.XC + (int64_t)c * d, d) : 0.0;
+    const double D = exact ? exact_distance(xq, P.XC + (int64_t)c * d, d, rows_by_16(P.XQ, d) && rows_by_16(P.XC, d)) : 0.0;
     int rank = run0;
     for (int r = 1; __any(lane - r >= run0 || lane + r <= run1); ++r) {
         const double Dl = __shfl(D, lane - r, G), Dr = __shfl(D, lane + r, G);
@@ -330,10 +332,10 @@ __global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32
 
 // ---------------------------------------------------------------- stage 3: flagged queries, exactly, against the whole cluster
 // exact distances of four rows at once (the chains side by side)
-__device__ __forceinline__ void exact_distances4(const float* __restrict__ x, const float* const (&y)[4], int32_t d, double (&D)[4]) {
+__device__ __forceinline__ void exact_distances4(const float* __restrict__ x, const float* const (&y)[4], int32_t d, bool by16, double (&D)[4]) {
     if (d > 32) {   // long rows keep enough loads in flight by themselves
 #pragma unroll
-        for (int u = 0; u < 4; ++u) D[u] = exact_distance(x, y[u], d);
+        for (int u = 0; u < 4; ++u) D[u] = exact_distance(x, y[u], d, by16);
         return;
     }
     double a[4] = {0.0, 0.0, 0.0, 0.0};
@@ -360,6 +362,7 @@ __device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t
     const int32_t r = P.group_of_q ? P.group_of_q[q] : 0;
     const uint32_t c0 = P.cstart[r], c1 = P.cstart[r + 1];
     const float* xq = P.XQ + (int64_t)q * d;
+    const bool by16 = rows_by_16(P.XQ, d) && rows_by_16(P.XC, d);
     const int32_t self = P.self_row ? P.self_row[q] : P.same_set ? q : -1;
     double lD[KL];      // ascending in (distance, point); empty slots: (inf, -1) at the end
     int32_t lP[KL];
@@ -376,7 +379,7 @@ __device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t
             c[u] = pos + u * THREADS < c1 ? knn_row(P.cmembers, pos + u * THREADS) : -1;
             row[u] = P.XC + (int64_t)(c[u] < 0 ? knn_row(P.cmembers, pos) : c[u]) * d;
         }
-        exact_distances4(xq, row, d, D);
+        exact_distances4(xq, row, d, by16, D);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (c[u] < 0 || c[u] == self) continue;
@@ -462,7 +465,7 @@ __global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const in
         }
         const float* xq = P.XQ + (int64_t)q * P.d;
         const int32_t c = cand[(size_t)x * width + lane];
-        double D = c >= 0 ? exact_distance(xq, P.XC + (int64_t)c * P.d, P.d) : __builtin_inf();
+        double D = c >= 0 ? exact_distance(xq, P.XC + (int64_t)c * P.d, P.d, rows_by_16(P.XQ, P.d) && rows_by_16(P.XC, P.d)) : __builtin_inf();
         int32_t best = c >= 0 ? c : 0x7fffffff;
         double qn = 0.0;
         const float* ctr = P.centre + (int64_t)g * P.d;
@@ -908,7 +911,7 @@ __global__ void __launch_bounds__(kLshSample) k_lsh_median_anchors(const float* 
     if (s < m) {
         const float* x = X + (((int64_t)s * n) / m) * d;
         int t = 0;
-        if ((d & 3) == 0 && ((uintptr_t)X & 15) == 0) {
+        if (rows_by_16(X, d)) {
             for (; t + 32 <= d; t += 32) {   // eight 16-byte loads in flight, added one by one in order
                 float4 v[8];
 #pragma unroll
@@ -947,7 +950,7 @@ __global__ void __launch_bounds__(256) k_kmeans_inertia(const float* __restrict_
                                                         const int32_t* __restrict__ labels, int64_t n, double* __restrict__ out) {
     __shared__ double part[256];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    part[threadIdx.x] = i < n ? exact_distance(X + i * d, C + (int64_t)labels[i] * d, d) : 0.0;
+    part[threadIdx.x] = i < n ? exact_distance(X + i * d, C + (int64_t)labels[i] * d, d, rows_by_16(X, d) && rows_by_16(C, d)) : 0.0;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];

@@ -9,6 +9,7 @@
 
 #include "knn_kernels.h"
 #include "philox.h"
+#include "rows.h"
 
 namespace nomad_metrics {
 
@@ -50,7 +51,7 @@ __global__ void __launch_bounds__(256) k_merge_slices(const float* __restrict__ 
     double D = __builtin_inf();
     if (t < total) {
         c = part_nbrs[((int64_t)(t / k) * m + r) * k + t % k];
-        if (c >= 0) D = nomad_knn::exact_distance(AQ + r * d, A + (int64_t)c * d, d);
+        if (c >= 0) D = nomad_knn::exact_distance(AQ + r * d, A + (int64_t)c * d, d, rows_by_16(AQ, d) && rows_by_16(A, d));
         if (!(D == D)) D = __builtin_inf();   // no number: as in the slices' own order
     }
     sD[t] = D;
@@ -88,10 +89,10 @@ __device__ __forceinline__ float from_ordered(uint32_t b) { return __uint_as_flo
 __global__ void k_plane_box_clear(uint32_t* __restrict__ box) {
     if (threadIdx.x < 4) box[threadIdx.x] = threadIdx.x < 2 ? 0xFFFFFFFFu : 0u;
 }
-__global__ void __launch_bounds__(256) k_plane_box(const float2* __restrict__ Y, int64_t n, uint32_t* __restrict__ box) {
+__global__ void __launch_bounds__(256) k_plane_box(const float* __restrict__ Y, int64_t n, uint32_t* __restrict__ box) {
     uint32_t lx = 0xFFFFFFFFu, ly = 0xFFFFFFFFu, hx = 0u, hy = 0u;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const float2 y = Y[i];
+        const float2 y = pair_at(Y, i);
         const uint32_t x0 = ordered_bits(y.x), y0 = ordered_bits(y.y);
         lx = min(lx, x0); hx = max(hx, x0);
         ly = min(ly, y0); hy = max(hy, y0);
@@ -120,22 +121,22 @@ __device__ __forceinline__ int plane_cell(float x, float x0, float inv, int32_t 
 }
 
 // cell of every point and the number of points per cell
-__global__ void __launch_bounds__(256) k_plane_count(const float2* __restrict__ Y, int64_t n, const uint32_t* __restrict__ box, int32_t G,
+__global__ void __launch_bounds__(256) k_plane_count(const float* __restrict__ Y, int64_t n, const uint32_t* __restrict__ box, int32_t G,
                                                      uint32_t* __restrict__ counts, uint32_t* __restrict__ rank) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     const PlaneGrid p = plane_grid(box, G);
-    const float2 y = Y[i];
+    const float2 y = pair_at(Y, i);
     rank[i] = atomicAdd(&counts[plane_cell(y.y, p.y0, p.inv, G) * G + plane_cell(y.x, p.x0, p.inv, G)], 1u);
 }
 // start: exclusive scan of the counts in two levels (tile_offset per kScanTile cells)
-__global__ void __launch_bounds__(256) k_plane_place(const float2* __restrict__ Y, int64_t n, const uint32_t* __restrict__ box, int32_t G,
+__global__ void __launch_bounds__(256) k_plane_place(const float* __restrict__ Y, int64_t n, const uint32_t* __restrict__ box, int32_t G,
                                                      const uint32_t* __restrict__ start, const uint32_t* __restrict__ tile_offset,
                                                      const uint32_t* __restrict__ rank, float2* __restrict__ pos, int32_t* __restrict__ id) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     const PlaneGrid p = plane_grid(box, G);
-    const float2 y = Y[i];
+    const float2 y = pair_at(Y, i);
     const uint32_t c = (uint32_t)(plane_cell(y.y, p.y0, p.inv, G) * G + plane_cell(y.x, p.x0, p.inv, G));
     const uint32_t at = start[c] + tile_offset[c / nomad_knn::kScanTile] + rank[i];
     pos[at] = y;
@@ -143,7 +144,7 @@ __global__ void __launch_bounds__(256) k_plane_place(const float2* __restrict__ 
 }
 
 constexpr int kPlaneBuffer = 320;    // candidates a wavefront holds before it reduces them to the k smallest
-__global__ void __launch_bounds__(256) k_plane_neighbours(const float2* __restrict__ Y, int64_t n, const int32_t* __restrict__ queries, int64_t m,
+__global__ void __launch_bounds__(256) k_plane_neighbours(const float* __restrict__ Y, int64_t n, const int32_t* __restrict__ queries, int64_t m,
                                                           int32_t k, const uint32_t* __restrict__ box, int32_t G, const uint32_t* __restrict__ start,
                                                           const uint32_t* __restrict__ tile_offset, const float2* __restrict__ pos,
                                                           const int32_t* __restrict__ id, int32_t* __restrict__ out,
@@ -158,7 +159,7 @@ __global__ void __launch_bounds__(256) k_plane_neighbours(const float2* __restri
     double* bD = sD[wave];
     int32_t* bI = sI[wave];
     const PlaneGrid g = plane_grid(box, G);
-    const float2 y = Y[q];
+    const float2 y = pair_at(Y, q);
     const int cx = plane_cell(y.x, g.x0, g.inv, G), cy = plane_cell(y.y, g.y0, g.inv, G);
     const uint32_t cells = (uint32_t)(G * G);
     auto cell_begin = [&](uint32_t c) { return c < cells ? start[c] + tile_offset[c / nomad_knn::kScanTile] : (uint32_t)n; };
@@ -275,10 +276,10 @@ __global__ void __launch_bounds__(256) k_overlap(const int32_t* __restrict__ a, 
 // squared distances from row a to rows b and c: difference, product and running sum each rounded once in float64,
 // t = 0..d-1 in order (two independent chains)
 __device__ __forceinline__ void anchor_distances(const float* __restrict__ a, const float* __restrict__ b, const float* __restrict__ c,
-                                                 int32_t d, double& Dab, double& Dac) {
+                                                 int32_t d, bool by16, double& Dab, double& Dac) {
     double s1 = 0.0, s2 = 0.0;
     int t = 0;
-    if ((d & 3) == 0) {
+    if (by16) {
         for (; t + 8 <= d; t += 8) {   // six loads in flight
             const float4 a0 = *(const float4*)(a + t), a1 = *(const float4*)(a + t + 4);
             const float4 b0 = *(const float4*)(b + t), b1 = *(const float4*)(b + t + 4);
@@ -323,8 +324,8 @@ __global__ void __launch_bounds__(256) k_triplets(const float* __restrict__ X, i
         k += k >= lo;
         k += k >= hi;
         double hij, hik, lij, lik;
-        anchor_distances(X + (int64_t)i * d, X + (int64_t)j * d, X + (int64_t)k * d, d, hij, hik);
-        anchor_distances(Y + (int64_t)i * d_low, Y + (int64_t)j * d_low, Y + (int64_t)k * d_low, d_low, lij, lik);
+        anchor_distances(X + (int64_t)i * d, X + (int64_t)j * d, X + (int64_t)k * d, d, rows_by_16(X, d), hij, hik);
+        anchor_distances(Y + (int64_t)i * d_low, Y + (int64_t)j * d_low, Y + (int64_t)k * d_low, d_low, rows_by_16(Y, d_low), lij, lik);
         same = (hij < hik) == (lij < lik);
     }
     const unsigned long long m = __ballot(same);

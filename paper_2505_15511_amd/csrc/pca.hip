@@ -6,6 +6,7 @@
 #include "host_util.h"
 #include "nomad.h"
 #include "pca_kernels.h"
+#include "rows.h"
 
 using namespace nomad_pca;
 
@@ -96,9 +97,9 @@ extern "C" int nomad_pca_init(const float* X, int64_t n, int32_t d, float std0, 
     hipLaunchKernelGGL(k_pca_orient, dim3(1), dim3(128), 0, st, (const double*)Q, d, (const RitzState*)state, std0, factor);
     const auto project = [&](auto kernel, int lanes) {
         hipLaunchKernelGGL(kernel, dim3(blocks_of(n, 4 * (64 / lanes) * kProjectRows)), dim3(256), 0, st, dX, n, d, (const double*)mean, (const double*)Q,
-                           (const double*)factor, (float2*)dTheta);
+                           (const double*)factor, dTheta);
     };
-    if (d % 4 == 0) {   // rows are 16-byte aligned
+    if (rows_by_16(dX, d)) {
         if (d <= 32) project(k_pca_project<4, 8>, 8);
         else if (d <= 64) project(k_pca_project<4, 16>, 16);
         else if (d <= 128) project(k_pca_project<4, 32>, 32);

@@ -421,8 +421,8 @@ __device__ __forceinline__ void ritz_step(double* __restrict__ Q, double* __rest
     __syncthreads();
 }
 
-// entry x of the start block [d][kRitz]: a fixed pseudo-random number in [-1, 1) (the finaliser of a 64-bit mixing function
-// applied to x), zero in the columns >= p
+// entry x of the start block [d][kRitz]: a fixed pseudo-random number in [-1, 1) (SplitMix64, G. L. Steele, D. Lea and C. H. Flood 2014, of
+// the counter x), zero in the columns >= p
 __device__ __forceinline__ double start_entry(int x, int32_t p) {
     if (x % kRitz >= p) return 0.0;
     uint64_t h = ((uint64_t)x + 1u) * 0x9E3779B97F4A7C15ull;
@@ -583,7 +583,7 @@ constexpr int kProjectRows = 8;
 template <int VEC, int LANES>
 __global__ void __launch_bounds__(256) k_pca_project(const float* __restrict__ X, int64_t n, int32_t d, const double* __restrict__ mean,
                                                      const double* __restrict__ Q, const double* __restrict__ factor,
-                                                     float2* __restrict__ theta) {
+                                                     float* __restrict__ theta) {
     constexpr int kSide = 64 / LANES;                 // rows side by side
     const int lane = threadIdx.x & 63, part = lane % LANES, side = lane / LANES;
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (kSide * kProjectRows) + side;
@@ -617,7 +617,7 @@ __global__ void __launch_bounds__(256) k_pca_project(const float* __restrict__ X
             s1[u] += __shfl_xor(s1[u], o, 64);
         }
         const int64_t row = row0 + (int64_t)u * kSide;
-        if (part == 0 && row < n) theta[row] = make_float2((float)(s0[u] * f0), (float)(s1[u] * f1));
+        if (part == 0 && row < n) { theta[2 * row] = (float)(s0[u] * f0); theta[2 * row + 1] = (float)(s1[u] * f1); }
     }
 }
 

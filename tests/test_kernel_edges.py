@@ -251,3 +251,35 @@ def test_hash_planes_find_an_anchor_whatever_the_rows_hold(rows):
     Y[::3] = np.nan                                      # slices of candidates: the merge has a place for every one of them
     q = np.arange(64, dtype=np.int32)
     assert neighbourhood_preservation(Y, Y, 5, q)[0] == 5 * 64
+
+
+# ---------------------------------------------------------------- arrays that begin anywhere
+@pytest.mark.gpu
+@pytest.mark.parametrize("offset", [1, 2, 3])
+@pytest.mark.parametrize("d", [12, 132])
+def test_views_at_any_offset(d, offset):
+    from paper_2505_15511_amd import random_triplet_accuracy
+    rng = np.random.default_rng(d + offset)
+
+    def shifted(a):
+        t = torch.empty(a.size + 4, device="cuda")[offset:offset + a.size].view(a.shape)
+        t.copy_(torch.from_numpy(a))
+        assert t.data_ptr() % 16 == 4 * offset and t.is_contiguous()
+        return t
+
+    n, K = 1500, 3
+    c = torch.from_numpy(rng.integers(0, 4, n).astype(np.int32)).cuda()
+    Xh, Yh = rng.normal(size=(n, d)).astype(np.float32), rng.normal(size=(n, 2)).astype(np.float32)
+    planes = rng.normal(size=(3, d)).astype(np.float32)
+    results = []
+    for put in (lambda a: torch.from_numpy(a).cuda(), shifted):
+        X, Y = put(Xh), put(Yh)
+        C, lab, it, inertia = kmeans_lloyd(X, put(Xh[:K].copy()), 3)
+        cen, buckets = kmeans_lsh_init(X, K, put(planes), None, return_buckets=True)
+        results.append([knn_in_clusters(X, c, 4, 9), C, lab, cen, buckets, pca_init(X, 0.0),
+                        neighbourhood_preservation(X, Y, 7)[0], random_triplet_accuracy(X, Y, 20_000, 3)[0], it])
+    for a, b in zip(*results):
+        if isinstance(a, torch.Tensor) and a.shape == (n, 2):      # the scores' sums are added in another order
+            assert torch.allclose(a, b, rtol=0.0, atol=1e-6 * float(a.abs().max()))
+        else:
+            assert torch.equal(a, b) if isinstance(a, torch.Tensor) else a == b
