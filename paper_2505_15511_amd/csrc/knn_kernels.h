@@ -331,11 +331,12 @@ __global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32
 }
 
 // ---------------------------------------------------------------- stage 3: flagged queries, exactly, against the whole cluster
-// exact distances of four rows at once (the chains side by side)
-__device__ __forceinline__ void exact_distances4(const float* __restrict__ x, const float* const (&y)[4], int32_t d, bool by16, double (&D)[4]) {
+// exact distances of four rows at once (the chains side by side); rows without a candidate (c < 0) can be read and count for nothing
+__device__ __forceinline__ void exact_distances4(const float* __restrict__ x, const float* const (&y)[4], const int32_t (&c)[4], int32_t d, bool by16,
+                                                 double (&D)[4]) {
     if (d > 32) {   // long rows keep enough loads in flight by themselves
 #pragma unroll
-        for (int u = 0; u < 4; ++u) D[u] = exact_distance(x, y[u], d, by16);
+        for (int u = 0; u < 4; ++u) D[u] = c[u] >= 0 ? exact_distance(x, y[u], d, by16) : 0.0;
         return;
     }
     double a[4] = {0.0, 0.0, 0.0, 0.0};
@@ -352,15 +353,15 @@ __device__ __forceinline__ void exact_distances4(const float* __restrict__ x, co
     for (int u = 0; u < 4; ++u) D[u] = a[u];
 }
 
-// One workgroup per flagged query at a time.  Every thread walks its share of the group once, four candidates at a time, and
-// keeps its own k smallest (distance, point) pairs sorted in registers (KL >= k slots); the k smallest of the group are among
-// those, and k rounds pick them: each thread offers its smallest pair above the one picked before, the workgroup takes the
-// smallest offer.  There are usually a few dozen such queries: the time is one query's chain of memory latencies.
+// A team of THREADS lanes, a workgroup or one wavefront of it, per flagged query at a time.  Every lane walks its share of the
+// group once, four candidates at a time, and keeps its own k smallest (distance, point) pairs sorted in registers (KL >= k
+// slots); the k smallest of the group are among those, and k rounds pick them: each lane offers its smallest pair above the
+// one picked before, the team takes the smallest offer.
 template <int KL, int THREADS>
 __device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t k, int32_t* __restrict__ out, double* sD, int32_t* sP) {
     const int32_t d = P.d;
     const int32_t r = P.group_of_q ? P.group_of_q[q] : 0;
-    const uint32_t c0 = P.cstart[r], c1 = P.cstart[r + 1];
+    const uint32_t c0 = P.cstart[r], c1 = P.cstart[r + 1], tid = threadIdx.x % THREADS;
     const float* xq = P.XQ + (int64_t)q * d;
     const bool by16 = rows_by_16(P.XQ, d) && rows_by_16(P.XC, d);
     const int32_t self = P.self_row ? P.self_row[q] : P.same_set ? q : -1;
@@ -370,7 +371,7 @@ __device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t
     for (int x = 0; x < KL; ++x) { lD[x] = __builtin_inf(); lP[x] = -1; }
     double wD = __builtin_inf();   // the pair in slot k - 1 (point -1 while the list is not full)
     int32_t wP = -1;
-    for (uint32_t pos = c0 + threadIdx.x; pos < c1; pos += 4 * THREADS) {
+    for (uint32_t pos = c0 + tid; pos < c1; pos += 4 * THREADS) {
         int32_t c[4];
         const float* row[4];
         double D[4];
@@ -379,7 +380,7 @@ __device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t
             c[u] = pos + u * THREADS < c1 ? knn_row(P.cmembers, pos + u * THREADS) : -1;
             row[u] = P.XC + (int64_t)(c[u] < 0 ? knn_row(P.cmembers, pos) : c[u]) * d;
         }
-        exact_distances4(xq, row, d, by16, D);
+        exact_distances4(xq, row, c, d, by16, D);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (c[u] < 0 || c[u] == self) continue;
@@ -422,29 +423,43 @@ __device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t
             bestP = take ? Po : bestP;
         };
         for (int w = 32; w > 0; w >>= 1) take_smaller(__shfl_xor(bestD, w, 64), __shfl_xor(bestP, w, 64));
-        if ((threadIdx.x & 63) == 0) { sD[threadIdx.x >> 6] = bestD; sP[threadIdx.x >> 6] = bestP; }
-        __syncthreads();
-        bestD = __builtin_inf();
-        bestP = -1;
-        for (int w = 0; w < THREADS / 64; ++w) take_smaller(sD[w], sP[w]);
+        if (THREADS > 64) {
+            if ((tid & 63) == 0) { sD[tid >> 6] = bestD; sP[tid >> 6] = bestP; }
+            __syncthreads();
+            bestD = __builtin_inf();
+            bestP = -1;
+            for (int w = 0; w < THREADS / 64; ++w) take_smaller(sD[w], sP[w]);
+        }
         lastD = bestD;
         lastP = bestP;
-        if (threadIdx.x == 0) out[(int64_t)q * k + m] = lastP;   // -1 once the group is exhausted
-        __syncthreads();
+        if (tid == 0) out[(int64_t)q * k + m] = lastP;   // -1 once the group is exhausted
+        if (THREADS > 64) __syncthreads();
         if (lastP < 0) {   // nothing left: the remaining slots stay empty
-            for (int x = m + 1 + threadIdx.x; x < k; x += THREADS) out[(int64_t)q * k + x] = -1;
+            for (int x = m + 1 + (int)tid; x < k; x += THREADS) out[(int64_t)q * k + x] = -1;
             break;
         }
     }
 }
 
-// the workgroups take the flagged queries in turn (how many there are is known on the device only)
+// The teams take the flagged queries in turn (how many there are is known on the device only).  Usually there are a few dozen: a
+// workgroup each, the time is one query's chain of memory latencies.  From four a workgroup on (data with far outliers, groups
+// the filter cannot work on) a wavefront each: the k rounds then need no barriers and short groups leave fewer lanes without
+// a candidate.  Whole calls, a workgroup each -> a wavefront each: 200,000 x 64 in 64 clusters, k = 15, 62,000 and 145,000
+// flagged 29 -> 12.5 and 64 -> 27 ms, 3,100 flagged 2.35 -> 1.6; 20,000 x 768, 7,300 flagged 14.8 -> 7.0; five iterations of
+// 300,000 x 128 on 128 centroids, all flagged, 59 -> 14; one cluster of 100,000 x 128, 9,600 flagged 78 -> 81 (both bound by the
+// rows' way from the last cache).
 template <int KL, int THREADS>
 __global__ void __launch_bounds__(THREADS) k_knn_exact(const KnnSets P, const int32_t* __restrict__ flagged, const uint32_t* __restrict__ n_flagged,
                                                        int32_t k, int32_t* __restrict__ out) {
     __shared__ double sD[THREADS / 64];
     __shared__ int32_t sP[THREADS / 64];
+    constexpr uint32_t kWaves = THREADS / 64;
     const uint32_t count = *n_flagged;
+    if (count >= 4u * gridDim.x) {
+        for (uint32_t f = blockIdx.x * kWaves + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6); f < count; f += gridDim.x * kWaves)
+            exact_query<KL, 64>(P, flagged[f], k, out, sD, sP);
+        return;
+    }
     for (uint32_t f = blockIdx.x; f < count; f += gridDim.x) {
         exact_query<KL, THREADS>(P, flagged[f], k, out, sD, sP);
         __syncthreads();

@@ -283,3 +283,28 @@ def test_views_at_any_offset(d, offset):
             assert torch.allclose(a, b, rtol=0.0, atol=1e-6 * float(a.abs().max()))
         else:
             assert torch.equal(a, b) if isinstance(a, torch.Tensor) else a == b
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size,k", [(2047, 3), (2048, 3), (2061, 16), (8195, 16), (2047, 17), (2048, 17), (2055, 32)])
+def test_exact_path_by_workgroups_and_by_wavefronts(size, k):
+    """A sentinel sends its whole cluster of `size` points to the exact path: too few for a wavefront each, and enough."""
+    rng = np.random.default_rng(size)
+    c = rng.permutation(np.repeat([0, 1], [size, 9]))
+    X = rng.integers(-9, 9, size=(len(c), 5)).astype(np.float32)
+    X[np.flatnonzero(c == 0)[0], 0] = 1e20
+    out, stats = knn_in_clusters(X, c, 2, k, return_stats=True)
+    assert size <= stats["fallback_queries"] <= size + 9
+    assert np.array_equal(out.astype(np.int64), ko.in_cluster_knn(X, c, k)[0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [2047, 2048, 2100])
+def test_exact_assignment_by_workgroups_and_by_wavefronts(n):
+    rng = np.random.default_rng(n)
+    X = rng.integers(-3, 3, size=(n, 36)).astype(np.float32)
+    X[3, 0] = 1e20
+    C0 = X[rng.choice(n, 300, replace=False)].copy()
+    C_ref, lab_ref, it_ref, _ = km.lloyd(X, C0, 2)
+    C, lab, it, _ = kmeans_lloyd(X, C0, 2)
+    assert it == it_ref and np.array_equal(lab.astype(np.int64), lab_ref) and np.array_equal(C, C_ref)
