@@ -100,12 +100,17 @@ def project(X: torch.Tensor, n_clusters: int, k: int = 15, n_epochs: int = 200, 
     return theta
 
 
+#: Below this many entries torch.randperm draws 32-bit numbers (it bounds their bias by n < (2^32 - 1) / 20), 64-bit from there on.
+kShuffle32 = 0xFFFFFFFF // 20
+
+
 def sample_without_replacement(n: int, m: int, seed: int) -> torch.Tensor:
     """torch.randperm(n, generator=torch.Generator().manual_seed(seed))[:m] on the CPU, without the n - m entries that are cut
     off (5 ms of the host's time at a million).  The permutation is a forward shuffle, step i swapping slots i and
     i + draw_i % (n - i), so its first m entries follow from the first m draws of the same Mersenne Twister: entry i is the
-    slot it is swapped with, except where two steps touch one slot; those few are replayed in order."""
-    if n >= 1 << 31 or m > n // 8:
+    slot it is swapped with, except where two steps touch one slot; those few are replayed in order.  torch shuffles that way
+    with 32-bit draws below kShuffle32 entries; longer permutations are torch's own."""
+    if n >= kShuffle32 or m > n // 8:
         return torch.randperm(n, generator=torch.Generator().manual_seed(seed))[:m]
     draws = np.random.RandomState(seed & 0xFFFFFFFF).randint(0, 1 << 32, size=m, dtype=np.uint32).astype(np.int64)
     step = np.arange(m, dtype=np.int64)

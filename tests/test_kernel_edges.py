@@ -17,6 +17,14 @@ def test_sampled_queries_are_the_head_of_the_permutation(n, m, seed):
     assert torch.equal(pipeline.sample_without_replacement(n, m, seed), ref)
 
 
+def test_long_permutations_are_torch_s_own(monkeypatch):
+    asked = []
+    monkeypatch.setattr(pipeline.torch, "randperm", lambda n, generator: asked.append(n) or torch.arange(5))
+    for n in (214_748_363, 214_748_364, 214_748_370, 1 << 31):      # 32-bit draws up to (2^32 - 1) / 20 entries
+        pipeline.sample_without_replacement(n, 4, 1)
+    assert asked == [214_748_364, 214_748_370, 1 << 31]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [16, 17, 128, 129, 256, 257, 384, 385])
 @pytest.mark.parametrize("k", [1, 8, 9, 16, 17, 32])
