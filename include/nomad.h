@@ -23,7 +23,11 @@
  *     points 0..n-1 and CSR positions 0..E-1 as passed to nomad_set_graph.
  *   - One context = one device + one stream.  A context is not thread-safe; different contexts
  *     are independent.  nomad_epoch only enqueues work on the stream; get_* and nomad_loss wait
- *     for it.
+ *     for it.  A get_* into device memory is ordered behind the work of the null stream, and
+ *     complete on return; buffers that another stream still works on are the caller's to wait for.
+ *   - Device memory that contexts and calls give back is kept for the next one, at most 2 GiB per
+ *     process; see nomad_release_memory.  nomad_set_graph and nomad_destroy give a context's
+ *     memory back after waiting for the whole device (recorded epochs may run on any stream).
  */
 #ifndef NOMAD_H
 #define NOMAD_H
@@ -258,8 +262,14 @@ int64_t nomad_num_edges(const nomad_ctx* ctx);
 #define NOMAD_PATH_FIXED_ATOMICS 4
 int nomad_scatter_path(const nomad_ctx* ctx);
 
-/* Device memory the context holds, in bytes (graph, embedding, work space; 0 before nomad_set_graph). */
+/* Device memory the context holds, in bytes (graph, embedding, work space; 0 before nomad_set_graph).  Blocks taken over
+ * from earlier contexts and calls count at their full size, up to half as large again as what was needed. */
 int64_t nomad_device_bytes(const nomad_ctx* ctx);
+
+/* Frees the device memory the library keeps between calls (what no context and no running call holds): at most 2 GiB, none
+ * of its blocks larger than 1 GiB.  The library frees it by itself when one of its own allocations fails or 1,024 requests have
+ * passed a block by; other allocators of the process, torch's among them, cannot ask for it.  Any thread, any time. */
+int nomad_release_memory(void);
 
 /*
  * Launch-shape knobs for experiments and tests; results do not depend on them beyond rounding order (every setting
@@ -356,10 +366,13 @@ int nomad_scatter_probe(int kind, void* table, uint64_t table_bytes, uint64_t n_
  *   stats      NULL, or [2] host int64: queries that needed the exact fallback, point pairs the filter evaluated
  *
  * Distance: sum over t = 0..d-1, in that order, of (x_t - y_t)^2 with every operation in float64.  The result is that
- * definition exactly: a float32 pass on the matrix cores only selects k + 8 candidates per point, their distances are
- * recomputed in float64, and a point whose candidates cannot be proven complete (the float32 error bound against
- * the first key left out) is redone against its whole cluster.  Inputs must be finite.  Stand-alone: needs no context;
- * allocates its work space on `device` and frees it before it returns; waits for `stream`.
+ * definition exactly: a pass on the float16 matrix cores (every value in two parts, float32 sums) only selects k + 8
+ * candidates per point; distances are recomputed in float64 wherever the pass's error bound leaves the order open, and a point
+ * whose candidates cannot be proven complete (that bound against the first key left out) is redone against its whole cluster,
+ * as is every point of a cluster whose squared norms are too large for the pass (about 1e36; a sentinel of 1e20 among the
+ * rows).  The bound goes with the cluster's largest squared distance from its mean: far outliers send more points that way.
+ * Inputs must be finite.  Stand-alone: needs no context; takes its work space on `device` and gives it back before it
+ * returns (up to 2 GiB are kept for later calls, see nomad_release_memory); waits for `stream`.
  * Errors: NOMAD_E_INVALID_ARG, NOMAD_E_TOO_LARGE (n >= 2^31 - 256), NOMAD_E_BAD_GRAPH (cluster id out of range), NOMAD_E_OOM,
  * NOMAD_E_HIP.
  */

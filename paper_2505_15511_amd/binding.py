@@ -23,7 +23,7 @@ ERRORS = {-1: "NOMAD_E_INVALID_ARG", -2: "NOMAD_E_BAD_GRAPH", -3: "NOMAD_E_ORDER
 
 EXPORTS = ["nomad_create", "nomad_destroy", "nomad_set_graph", "nomad_set_embedding", "nomad_epoch", "nomad_loss",
            "nomad_get_embedding", "nomad_get_gradient", "nomad_get_negatives", "nomad_get_means",
-           "nomad_get_mean_field", "nomad_num_edges", "nomad_scatter_path", "nomad_device_bytes", "nomad_tune", "nomad_profile", "nomad_profile_read", "nomad_last_error",
+           "nomad_get_mean_field", "nomad_num_edges", "nomad_scatter_path", "nomad_device_bytes", "nomad_release_memory", "nomad_tune", "nomad_profile", "nomad_profile_read", "nomad_last_error",
            "nomad_copy_probe", "nomad_gather_probe", "nomad_scatter_probe", "nomad_knn_in_clusters", "nomad_kmeans_lloyd", "nomad_neighbourhood_preservation",
            "nomad_random_triplet_accuracy", "nomad_random_triplet_accuracy_noalloc", "nomad_pca_init", "nomad_kmeans_lsh_init"]
 
@@ -82,6 +82,7 @@ def load_library():
     lib.nomad_scatter_path.argtypes = [vp]
     lib.nomad_device_bytes.argtypes = [vp]
     lib.nomad_device_bytes.restype = i64
+    lib.nomad_release_memory.argtypes = []
     lib.nomad_tune.argtypes = [vp, C.c_int, C.c_int]
     lib.nomad_profile.argtypes = [vp, C.c_int]
     lib.nomad_profile_read.argtypes = [vp, C.c_int, C.POINTER(C.c_double), C.POINTER(i64)]
@@ -133,6 +134,13 @@ def _call_stream(device, stream):
     if current.cuda_stream != int(stream):
         current.synchronize()
     return stream
+
+
+def release_memory():
+    """nomad_release_memory: free the device memory (at most 2 GiB) that the library keeps between calls."""
+    rc = load_library().nomad_release_memory()
+    if rc:
+        raise NomadError(rc, "nomad_release_memory")
 
 
 def copy_probe(dst, src, stream=None):

@@ -14,11 +14,13 @@
 // Device memory that calls and contexts have given back, kept for the next one that asks for about as much.  hipMalloc and
 // hipFree of work space cost a call on small inputs more than its kernels (and 1.5 ms a call for the half gigabyte of a
 // million points: page tables).  Bounded: at most kKeepBytes in all, nothing larger than half of that, and what 1,024 requests
-// in a row have not taken is freed; when the device runs out of memory everything kept is freed before the request fails.
-// A block comes back only after the stream that used it has been waited for, so any thread and stream may take it next.
+// in a row have not taken is freed; when the device runs out of memory everything kept is freed before the request fails, and
+// nomad_release_memory frees it for others (torch's allocator cannot ask for it).
+// A block comes back only after the work that used it has been waited for, so any thread and stream may take it next.
 class DevicePool {
 public:
-    hipError_t take(void** p, size_t bytes) {
+    // held: the block's size, which may be half as large again as what was asked for
+    hipError_t take(void** p, size_t bytes, size_t* held = nullptr) {
         *p = nullptr;
         const size_t want = (std::max<size_t>(bytes, 1) + kGrain - 1) / kGrain * kGrain;
         int device = 0;
@@ -35,6 +37,7 @@ public:
             if (best < kept_.size()) {
                 *p = kept_[best].p;
                 sizes_[*p] = {kept_[best].bytes, device};
+                if (held) *held = kept_[best].bytes;
                 bytes_ -= kept_[best].bytes;
                 kept_.erase(kept_.begin() + (long)best);
                 return hipSuccess;
@@ -47,6 +50,7 @@ public:
             e = hipMalloc(p, want);
         }
         if (e != hipSuccess) { *p = nullptr; return e; }
+        if (held) *held = want;
         std::lock_guard<std::mutex> lock(mutex_);
         sizes_[*p] = {want, device};
         return hipSuccess;

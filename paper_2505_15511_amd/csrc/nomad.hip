@@ -116,10 +116,11 @@ int dev_alloc(nomad_ctx* c, T** p, size_t count) {
     *p = nullptr;
     const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
     void* q = nullptr;
-    HIP_TRY(c, DevicePool::get().take(&q, bytes));
+    size_t held = 0;
+    HIP_TRY(c, DevicePool::get().take(&q, bytes, &held));
     *p = (T*)q;
-    c->allocations[*p] = bytes;
-    c->device_bytes += (int64_t)bytes;
+    c->allocations[*p] = held;
+    c->device_bytes += (int64_t)held;
     return NOMAD_OK;
 }
 
@@ -794,6 +795,11 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
 int nomad_scatter_path(const nomad_ctx* c) { return c ? c->path : 0; }
 
 int64_t nomad_device_bytes(const nomad_ctx* c) { return c ? c->device_bytes : 0; }
+
+int nomad_release_memory(void) {
+    DevicePool::get().trim(0);
+    return NOMAD_OK;
+}
 
 int nomad_tune(nomad_ctx* c, int knob, int value) {
     if (!c) return NOMAD_E_INVALID_ARG;

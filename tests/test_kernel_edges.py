@@ -316,3 +316,31 @@ def test_exact_assignment_by_workgroups_and_by_wavefronts(n):
     C_ref, lab_ref, it_ref, _ = km.lloyd(X, C0, 2)
     C, lab, it, _ = kmeans_lloyd(X, C0, 2)
     assert it == it_ref and np.array_equal(lab.astype(np.int64), lab_ref) and np.array_equal(C, C_ref)
+
+
+# ---------------------------------------------------------------- memory kept between calls
+@pytest.mark.gpu
+def test_kept_memory_is_freed_on_request():
+    from paper_2505_15511_amd import Nomad, release_memory, workloads
+    X = torch.randn(200_000, 64, device="cuda")
+    c = torch.randint(0, 50, (200_000,), device="cuda", dtype=torch.int32)
+    first = knn_in_clusters(X, c, 50, 15)
+    release_memory()
+    free0 = torch.cuda.mem_get_info()[0]
+    again = knn_in_clusters(X, c, 50, 15)
+    free1 = torch.cuda.mem_get_info()[0]
+    assert torch.equal(first, again) and free0 - free1 > 4 * 200_000 * 23 * 2     # candidates and keys at least are kept
+    w = workloads.make_config(3, scale=0.02)
+    release_memory()
+    with Nomad.from_workload(w) as nm:
+        held = nm.device_bytes()
+        nm.set_graph(w.row_ptr, w.col_idx, w.weights, w.cluster_of, w.cluster_group)   # its own blocks, taken again
+        assert held <= nm.device_bytes() <= 2 * held
+        release_memory()                                                              # what the context holds stays
+        nm.set_embedding(w.theta0)
+        nm.epoch(0)
+        theta = nm.get_embedding()
+    release_memory()
+    release_memory()
+    assert torch.cuda.mem_get_info()[0] >= free0 and np.isfinite(theta).all()
+    assert torch.equal(knn_in_clusters(X, c, 50, 15), first)
