@@ -128,11 +128,11 @@ def _call_stream(device, stream):
     the current stream still has to do comes first: it may be making the inputs, or working on what a result's memory
     belonged to before (the caching allocator hands that out in the current stream's order)."""
     import torch
-    current = torch.cuda.current_stream(device)
+    current = torch._C._cuda_getCurrentRawStream(device)   # the handle alone: a Stream object takes as long as a small copy
     if stream is None:
-        return current.cuda_stream
-    if current.cuda_stream != int(stream):
-        current.synchronize()
+        return current
+    if current != int(stream):
+        torch.cuda.current_stream(device).synchronize()
     return stream
 
 
@@ -369,6 +369,7 @@ class Nomad:
                                FAR_FIELD_SAMPLED if sampled_far_field else FAR_FIELD_EXACT, int(bool(mean_gradient)),
                                int(pool_mode), int(pool_line), int(pool_segment), int(bool(inverse_rank_weights)))
         self.n, self.R, self.s = int(n_points), int(n_clusters), int(n_neg)
+        self._stream = int(stream or 0)
         self.device = int(device)
         self.ctx = C.c_void_p()
         rc = self.lib.nomad_create(C.byref(self.cfg), C.byref(self.ctx))
@@ -422,13 +423,13 @@ class Nomad:
         if len(mems) > 1:
             raise ValueError("all graph buffers must live in the same memory space")
         if NOMAD_DEVICE in mems:
-            _call_stream(self.device, self.cfg.stream or 0)
+            _call_stream(self.device, self._stream)
         self._check(self.lib.nomad_set_graph(self.ctx, rp, ci, w, co, cg, mems.pop()))
 
     def set_embedding(self, theta):
         p, mem, keep = _marshal(theta, np.float32, 2 * self.n)
         if mem == NOMAD_DEVICE:
-            _call_stream(self.device, self.cfg.stream or 0)
+            _call_stream(self.device, self._stream)
         self._check(self.lib.nomad_set_embedding(self.ctx, p, mem))
 
     # ---- the path
@@ -446,7 +447,7 @@ class Nomad:
             import torch
             tdt = {np.float32: torch.float32, np.int32: torch.int32}[np_dtype]
             t = torch.empty(shape, dtype=tdt, device=f"cuda:{self.device}")
-            _call_stream(self.device, self.cfg.stream or 0)
+            _call_stream(self.device, self._stream)
             self._check(fn(self.ctx, *pre, C.c_void_p(t.data_ptr()), NOMAD_DEVICE))
             return t
         a = np.empty(shape, dtype=np_dtype)
