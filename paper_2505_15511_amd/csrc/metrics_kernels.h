@@ -76,6 +76,9 @@ __global__ void __launch_bounds__(256) k_merge_slices(const float* __restrict__ 
 // smallest; if a point outside the square could still be nearer, the square that reaches as far as the k-th distance.
 // A million points and 10,000 queries: 0.2 ms, where comparing every query with every point took 12 ms on the matrix cores
 // and left most queries to the exact path (neighbour distances in the plane are 1e-5 of its squared extent).
+// The grid follows the bounding box: a few far points put nearly all others into one cell, and every query reads them all.
+// Same sizes with three points 10,000 deviations out: 20 ms (the matrix cores and the exact path: 31), with Cauchy
+// coordinates 24 (209), with half of the points in a ten-thousandth of the extent 12 (99).
 constexpr int kCellPoints = 6;
 constexpr int kMaxGrid = 2048;      // cells per side
 
