@@ -1031,7 +1031,7 @@ __device__ __forceinline__ void publish_sorted_chains(const SortLds& L, const Bi
 // has records, and negatives drawn near the head): a record's place in its chain is the chain's fill plus the rank
 // it took from the tile's counter, so once the chains have been extended every lane writes its own records.  The
 // records of one tile still land side by side; what is given up is that consecutive lanes write them, what is saved
-// are the scan over all tiles, the staging in LDS and two of the round's six barriers.  All lanes must call.
+// are the scan over all tiles and the staging in LDS (both forms have four barriers a round).  All lanes must call.
 template <int NR, int BS>
 __device__ __forceinline__ void direct_flush(const BinLds& L, const BinArgs& Q, uint32_t pool_end, uint32_t* pool_cursor,
                                              const bool (&valid)[NR], const uint32_t (&pt)[NR], const uint32_t (&rank)[NR],
