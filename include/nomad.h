@@ -263,12 +263,13 @@ int64_t nomad_num_edges(const nomad_ctx* ctx);
 int nomad_scatter_path(const nomad_ctx* ctx);
 
 /* Device memory the context holds, in bytes (graph, embedding, work space; 0 before nomad_set_graph).  Blocks taken over
- * from earlier contexts and calls count at their full size, up to half as large again as what was needed. */
+ * from earlier contexts and calls count at their full size, up to half as large again (and 64 KB) as what was needed. */
 int64_t nomad_device_bytes(const nomad_ctx* ctx);
 
 /* Frees the device memory the library keeps between calls (what no context and no running call holds): at most 2 GiB, none
  * of its blocks larger than 1 GiB.  The library frees it by itself when one of its own allocations fails or 1,024 requests have
- * passed a block by; other allocators of the process, torch's among them, cannot ask for it.  Any thread, any time. */
+ * passed a block by; other allocators of the process, torch's among them, cannot ask for it.  Any thread; like hipFree, not
+ * while a graph is being recorded. */
 int nomad_release_memory(void);
 
 /*

@@ -19,7 +19,7 @@
 // A block comes back only after the work that used it has been waited for, so any thread and stream may take it next.
 class DevicePool {
 public:
-    // held: the block's size, which may be half as large again as what was asked for
+    // held: the block's size, which may be half as large again (and 64 KB) as what was asked for
     hipError_t take(void** p, size_t bytes, size_t* held = nullptr) {
         *p = nullptr;
         const size_t want = (std::max<size_t>(bytes, 1) + kGrain - 1) / kGrain * kGrain;

@@ -136,7 +136,11 @@ void dev_free(nomad_ctx* c, T*& p) {
 
 void free_graph(nomad_ctx* c) {
     // nothing that is given back may still be in use, on any stream: epochs recorded into a graph run where it is replayed
-    if (!c->allocations.empty()) (void)hipDeviceSynchronize();
+    // (refused while another thread records a graph: then at least what this context's own stream does)
+    if (!c->allocations.empty() && hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipStreamSynchronize(c->stream);
+    }
     dev_free(c, c->row_ptr); dev_free(c, c->col); dev_free(c, c->cluster_of); dev_free(c, c->group_of_cluster);
     dev_free(c, c->pe); dev_free(c, c->counts); dev_free(c, c->gbase); dev_free(c, c->gcount); dev_free(c, c->chunk_start);
     dev_free(c, c->gomega); dev_free(c, c->hinfo); dev_free(c, c->gmembers); dev_free(c, c->cmembers); dev_free(c, c->chunks); dev_free(c, c->mean_partial);
@@ -957,6 +961,8 @@ int nomad_get_negatives(nomad_ctx* c, int32_t t, int64_t e_begin, int64_t e_end,
         rc = dev_alloc(c, &tmp, (size_t)cnt * s);
         if (rc) return rc;
         dst = tmp;
+    } else if (c->stream) {
+        HIP_TRY(c, hipStreamSynchronize(nullptr));   // (see copy_out)
     }
     const EdgeArgs a = edge_args(c, (uint32_t)t);
     hipLaunchKernelGGL(k_negatives, dim3(blocks_for(cnt)), dim3(kBlock), 0, c->stream, a, e_begin, e_end, dst);

@@ -154,5 +154,6 @@ def test_device_buffers_of_a_context_on_a_side_stream(grouped):
     nm.epoch(0)
     ref.epoch(0)
     assert np.array_equal(nm.get_embedding(), ref.get_embedding())
+    assert np.array_equal(nm.get_negatives(3, 10, 5_000, device=True).cpu().numpy(), ref.get_negatives(3, 10, 5_000))
     nm.close()
     ref.close()
