@@ -174,9 +174,11 @@ private:
     bool pending_ = false;
 };
 
-struct HostArrays {   // small host arrays that travel to the device in one copy; lives until the copy is done
+struct HostArrays {   // small host arrays that travel to the device in one copy, which has been waited for when they go
     std::vector<uint8_t> bytes;
     uint8_t* device = nullptr;
+    hipStream_t stream = nullptr;
+    ~HostArrays() { if (device) (void)hipStreamSynchronize(stream); }   // (a call that has run to its end has waited already)
     template <typename T>
     size_t add(const std::vector<T>& v) {   // -> offset
         const size_t at = (bytes.size() + 15) / 16 * 16;
@@ -185,6 +187,7 @@ struct HostArrays {   // small host arrays that travel to the device in one copy
         return at;
     }
     hipError_t upload(Buffers& buf, hipStream_t st) {
+        stream = st;
         hipError_t e = buf.alloc(&device, bytes.size());
         return e != hipSuccess ? e : hipMemcpyAsync(device, bytes.data(), bytes.size(), hipMemcpyHostToDevice, st);
     }
