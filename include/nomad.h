@@ -287,6 +287,9 @@ int nomad_release_memory(void);
  *                              lane writes its own records
  *   NOMAD_TUNE_FLUSH_ROUNDS    0 (default: 2), 1 or 2: rounds of 1024 positions the unsorted form takes between two
  *                              flushes of its records (1024-lane workgroups only)
+ *   NOMAD_TUNE_EXCHANGE        0 (default: large embeddings of one population with i.i.d. negatives, unless a knob above asks for
+ *                              a shape of the sorted edge pass), 1: the exchanged edge pass wherever it can run, 2: never; the
+ *                              two give the same bits
  */
 #define NOMAD_TUNE_EDGE_BLOCK 1
 #define NOMAD_TUNE_WORKGROUPS_PER_CU 2
@@ -295,6 +298,7 @@ int nomad_release_memory(void);
 #define NOMAD_TUNE_RECORD_PHASES 5
 #define NOMAD_TUNE_RECORD_SORT 6
 #define NOMAD_TUNE_FLUSH_ROUNDS 7
+#define NOMAD_TUNE_EXCHANGE 8
 int nomad_tune(nomad_ctx* ctx, int knob, int value);
 
 /* ---- kernel timing (HIP events on the context's stream, around each launch) ---- */

@@ -44,6 +44,26 @@ NOMAD_HOST_DEVICE inline size_t distinct_lds_bytes(uint32_t n_bins, uint32_t poo
     return (size_t)pool_size * 28 + ((size_t)lines + (size_t)4 * n_bins + 3 * (size_t)(32 * rounds)) * sizeof(uint32_t);
 }
 
+// exchanged edge pass (exchange_kernels.h): blocks of kExchangeLanes * R edges, whose references fit half of a compute unit's LDS.
+// (All of it, one workgroup of 1,024 lanes that fetches the next block while it computes one: runs twice as long, but k_exchange_edges took
+// 2.29 ms for 75 M edges where two workgroups take turns in 1.79, and 0.129 for 0.054 at 100 k points.)
+constexpr int kExchangeLanes = 768;
+constexpr uint32_t kExchangeSpare = 4096;        // slots that mean nothing, for lanes without a reference
+constexpr uint32_t kExchangeTilesTogether = 16;  // neighbouring tiles that go to one XCD (32: the same; 64: 2.58 ms for 2.11, the XCDs' shares differ)
+NOMAD_HOST_DEVICE constexpr uint32_t exchange_padded_tiles(uint32_t n) {
+    return (n + 8 * kExchangeTilesTogether - 1) / (8 * kExchangeTilesTogether) * (8 * kExchangeTilesTogether);
+}
+NOMAD_HOST_DEVICE constexpr int exchange_edges_per_lane(int s) {
+    const int r = (int)(78 * 1024 / (8 * (s + 1) * kExchangeLanes));
+    return r < 1 ? 1 : r > 4 ? 4 : r;
+}
+NOMAD_HOST_DEVICE constexpr int exchange_block_edges(int s) { return kExchangeLanes * exchange_edges_per_lane(s); }
+NOMAD_HOST_DEVICE constexpr size_t exchange_slots(int s) {   // one per reference, two per wavefront of head sums; a multiple of 64
+    return ((size_t)exchange_block_edges(s) * (s + 1) + 2 * (exchange_block_edges(s) / 64) + 63) / 64 * 64;
+}
+NOMAD_HOST_DEVICE constexpr size_t exchange_deal_lds_bytes(int s, uint32_t n_tiles) { return exchange_slots(s) * 2 + (size_t)n_tiles * 4; }
+NOMAD_HOST_DEVICE constexpr size_t exchange_edges_lds_bytes(int s) { return exchange_slots(s) * 8; }
+
 // ---- the plan
 struct EdgePlanRequest {
     int64_t n = 0, E = 0;
@@ -52,7 +72,8 @@ struct EdgePlanRequest {
     int32_t pool_size = 0, pool_block = 0, pool_line = 1;
     bool pool_distinct = false;
     // nomad_tune (0 = the library's choice, except pool_kernel: 1 = use the pooled kernels)
-    int tune_edge_block = 0, tune_wg_per_cu = 0, tune_pool_kernel = 1, tune_record_sort = 0, tune_flush_rounds = 0;
+    int tune_edge_block = 0, tune_wg_per_cu = 0, tune_pool_kernel = 1, tune_record_sort = 0, tune_flush_rounds = 0,
+        tune_exchange = 0;
 };
 
 struct EdgePlan {
@@ -157,6 +178,40 @@ inline int plan_record_phases(int64_t E, int s, int bin_block, int tune_phases) 
     const int64_t blocks = (E + bin_block - 1) / bin_block;
     if (phases > blocks) phases = (int)blocks;
     return phases < 1 ? 1 : phases;
+}
+
+// Whether a problem of one population takes the exchanged edge pass (exchange_kernels.h), and its tile kernels' shapes.
+//   Which: embeddings beyond two L2s.  The sorted pass gathers a row per negative, and once most gathers miss the L2s they end
+//   at 58 G lines/s; the exchange moves 42 bytes a reference in streams instead.  ms per epoch, sorted -> exchanged: 15 out-neighbours,
+//   symmetrised, s = 5: 100 k points 0.198 -> 0.201, 300 k 0.65 -> 0.78, 700 k 1.59 -> 1.73, 1 M 2.55 -> 2.27, 2 M 6.15 -> 4.56, 5 M 15.3 -> 10.5,
+//   10 M 41.1 -> 29.8; s = 2: 1 M 1.307 -> 1.277, 1.3 M 1.76 -> 1.78, 2 M 2.91 -> 2.53 (fewer gathers an edge, the same streams of
+//   heads and tails).  Up to where a run is shorter than two references: s = 2 at 40 M points 28.9 -> 28.4, s = 5 62.5 -> 55.5.
+//   Rows: runs of about seven references (10 M points) leave as partial sectors; two neighbouring tiles in LDS make them twice
+//   as long (2.79 -> 2.45 ms for 75 M edges; at 5 M points a tile alone is as fast).
+//   Lanes: as many as most runs have references (75 M edges, rows and sums, 16 / 32 / 64 lanes: runs of 7.5 in pairs 2.67 / 2.47 / 2.76 and
+//   2.11 / 2.37 / 3.98 ms, of 15 4.02 / 2.13 / 2.28 and 2.14 / 1.65 / 2.61, of 25 - / 1.99 / 1.95 and 4.45 / 1.44 / 1.95).
+struct ExchangePlan {
+    bool use = false;
+    bool pairs = false;                     // k_exchange_rows holds two neighbouring tiles
+    int rows_lanes = 64, sums_lanes = 64;   // lanes that take one run
+    uint32_t parts = 1;                     // workgroups per tile (or pair) that answer
+    int tile_bits = 0;
+};
+inline size_t exchange_rows_lds_bytes(const ExchangePlan& x) { return (size_t)8 << (x.tile_bits + (x.pairs ? 1 : 0)); }
+inline ExchangePlan plan_exchange(const EdgePlanRequest& q, const EdgePlan& p) {
+    ExchangePlan x;
+    if (q.s < 1 || q.s > 8 || q.E < 1 || q.pool_size || !p.bin_block || q.tune_exchange == 2) return x;
+    const double run = (double)exchange_block_edges(q.s) * (q.s + 1) / p.n_bins;   // mean length of a run
+    const bool sorted_asked = q.tune_edge_block || q.tune_wg_per_cu || q.tune_record_sort || q.tune_flush_rounds;
+    x.use = q.tune_exchange == 1 || (!sorted_asked && q.n >= (q.s < 3 ? 1500000 : 1000000) && run >= 2);
+    if (exchange_deal_lds_bytes(q.s, p.n_bins) > kMaxLdsBytes) x.use = false;
+    x.tile_bits = p.tile_bits;
+    x.pairs = run < 12;
+    x.rows_lanes = x.pairs ? (2 * run < 9 ? 16 : 32) : run < 26 ? 32 : 64;
+    x.sums_lanes = run < 11 ? 16 : run < 26 ? 32 : 64;
+    const uint32_t units = x.pairs ? (p.n_bins + 1) / 2 : p.n_bins;
+    x.parts = units >= 512 ? 2 : (1024 + units - 1) / units;   // (four workgroups per compute unit and more at a few hundred tiles)
+    return x;
 }
 
 }  // namespace nomad

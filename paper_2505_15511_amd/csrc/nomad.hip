@@ -15,6 +15,7 @@
 
 #include "host_util.h"
 #include "nomad.h"
+#include "exchange_kernels.h"
 #include "nomad_kernels.h"
 
 using namespace nomad;
@@ -73,7 +74,13 @@ struct nomad_ctx {
     uint32_t edge_grid = 0;
     int* flags = nullptr;
     // launch-shape knobs (nomad_tune) and what set_graph made of them
-    int tune_edge_block = 0, tune_wg_per_cu = 0, tune_path = 0, tune_pool_kernel = 1, tune_phases = 0, tune_record_sort = 0, tune_flush_rounds = 0;
+    int tune_edge_block = 0, tune_wg_per_cu = 0, tune_path = 0, tune_pool_kernel = 1, tune_phases = 0, tune_record_sort = 0, tune_flush_rounds = 0, tune_exchange = 0;
+    bool exchange = false;          // the edge pass is the exchanged one (exchange_kernels.h)
+    float2* ex_rec = nullptr;
+    uint16_t *ex_idx = nullptr, *ex_side = nullptr;
+    uint32_t *ex_pos = nullptr, *ex_runs = nullptr;
+    uint32_t ex_spare = 0;          // first of the spare slots
+    ExchangePlan ex;
     int path = 0;                   // NOMAD_PATH_* in use
     int phases = 1;                 // record phases of the binned edge pass
     unsigned long long* carry = nullptr;   // [2 n] fixed-point sums carried from phase to phase (phases > 1)
@@ -134,6 +141,11 @@ void dev_free(nomad_ctx* c, T*& p) {
     p = nullptr;
 }
 
+void free_exchange(nomad_ctx* c) {
+    dev_free(c, c->ex_rec); dev_free(c, c->ex_idx); dev_free(c, c->ex_pos); dev_free(c, c->ex_side); dev_free(c, c->ex_runs);
+    c->exchange = false;
+}
+
 void free_graph(nomad_ctx* c) {
     // nothing that is given back may still be in use, on any stream: epochs recorded into a graph run where it is replayed
     // (refused while another thread records a graph: then at least what this context's own stream does)
@@ -152,6 +164,7 @@ void free_graph(nomad_ctx* c) {
     dev_free(c, c->flags);
     dev_free(c, c->pool); dev_free(c, c->chunk_prev); dev_free(c, c->chain_head); dev_free(c, c->chain_fill); dev_free(c, c->wg_pool_begin);
     dev_free(c, c->head); dev_free(c, c->carry); dev_free(c, c->pool_keys);
+    free_exchange(c);
     c->phases = 1;
     c->binned = false;
     c->pool_rounds = 0;
@@ -341,6 +354,63 @@ void launch_edges_binned(nomad_ctx* c, const EdgeArgs& a, int64_t e_begin, int64
     const dim3 grid(c->n_wg), block(c->bin_block);
     const size_t lds = edge_pass_lds_bytes(c);
     with_edge_pass_kernel(c, [&](EdgePassKernel kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, c->stream, a, q); });
+}
+
+// ---- the exchanged edge pass
+template <typename Fn>
+void with_exchange_s(const nomad_ctx* c, Fn fn) {
+    switch (c->cfg.n_neg) {
+#define NOMAD_CASE(S) case S: fn(std::integral_constant<int, S>()); break;
+        NOMAD_CASE(1) NOMAD_CASE(2) NOMAD_CASE(3) NOMAD_CASE(4) NOMAD_CASE(5) NOMAD_CASE(6) NOMAD_CASE(7) NOMAD_CASE(8)
+#undef NOMAD_CASE
+    }
+}
+// the tile kernels for the length of this problem's runs (exchange_kernels.h)
+using ExchangeRowsKernel = void (*)(const ExchangeArgs, const float2*, int64_t, uint32_t, uint32_t);
+using ExchangeSumsKernel = void (*)(const ExchangeArgs, uint32_t, float2*, int64_t, float2*, float, unsigned long long*, int);
+ExchangeRowsKernel exchange_rows_kernel(const ExchangePlan& p) {
+    if (p.pairs) return p.rows_lanes == 16 ? k_exchange_rows<16, true> : k_exchange_rows<32, true>;
+    return p.rows_lanes == 32 ? k_exchange_rows<32, false> : k_exchange_rows<64, false>;
+}
+ExchangeSumsKernel exchange_sums_kernel(const ExchangePlan& p) {
+    return p.sums_lanes == 16 ? k_exchange_sums<16> : p.sums_lanes == 32 ? k_exchange_sums<32> : k_exchange_sums<64>;
+}
+
+ExchangeArgs exchange_args(const nomad_ctx* c, int64_t e_begin, int64_t e_end) {
+    ExchangeArgs x{};
+    x.head = c->head; x.rec = c->ex_rec; x.idx = c->ex_idx; x.pos = c->ex_pos; x.side = c->ex_side; x.runs = c->ex_runs; x.ghead = c->ghead;
+    x.e_begin = e_begin; x.e_end = e_end;
+    const int eb = exchange_block_edges(c->cfg.n_neg);
+    x.n_blocks = (uint32_t)((e_end - e_begin + eb - 1) / eb);
+    x.n_tiles = c->n_bins; x.tile_bits = c->tile_bits; x.spare = c->ex_spare;
+    return x;
+}
+
+int prepare_exchange(nomad_ctx* c) {
+    hipError_t err = hipSuccess;
+    const auto allow = [&](const void* k, size_t lds) { if (err == hipSuccess) err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); };
+    with_exchange_s(c, [&](auto s) {
+        allow((const void*)k_exchange_deal<decltype(s)::value>, exchange_deal_lds_bytes(c->cfg.n_neg, c->n_bins));
+        allow((const void*)k_exchange_edges<decltype(s)::value>, exchange_edges_lds_bytes(c->cfg.n_neg));
+    });
+    allow((const void*)exchange_rows_kernel(c->ex), exchange_rows_lds_bytes(c->ex));
+    allow((const void*)exchange_sums_kernel(c->ex), sizeof(unsigned long long) * 2 << c->tile_bits);
+    HIP_TRY(c, err);
+    return NOMAD_OK;
+}
+
+void launch_exchange_edges(nomad_ctx* c, const EdgeArgs& a, const ExchangeArgs& x) {
+    const int s = c->cfg.n_neg;
+    const dim3 grid(x.n_blocks), block(kExchangeLanes);
+    with_exchange_s(c, [&](auto S) { hipLaunchKernelGGL(k_exchange_deal<decltype(S)::value>, grid, block, exchange_deal_lds_bytes(s, x.n_tiles), c->stream, a, x); });
+    hipLaunchKernelGGL(exchange_rows_kernel(c->ex), dim3(exchange_padded_tiles(c->ex.pairs ? (x.n_tiles + 1) / 2 : x.n_tiles) * c->ex.parts), dim3(1024),
+                       exchange_rows_lds_bytes(c->ex), c->stream, x, c->theta, c->n, (uint32_t)exchange_slots(s), c->ex.parts);
+    with_exchange_s(c, [&](auto S) { hipLaunchKernelGGL(k_exchange_edges<decltype(S)::value>, grid, block, exchange_edges_lds_bytes(s), c->stream, a, x); });
+}
+
+void launch_exchange_sums(nomad_ctx* c, const ExchangeArgs& x, float eta, int phase) {
+    hipLaunchKernelGGL(exchange_sums_kernel(c->ex), dim3(exchange_padded_tiles(x.n_tiles)), dim3(kBinBlock), sizeof(unsigned long long) * 2 << c->tile_bits,
+                       c->stream, x, (uint32_t)exchange_slots(c->cfg.n_neg), c->g, c->n, c->theta, eta, c->carry, phase);
 }
 
 // cell means of the current embedding -> mu, cinfo
@@ -702,7 +772,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         want_plan.pool_distinct = c->cfg.pool_mode != NOMAD_POOL_PICKS16;
         want_plan.tune_edge_block = c->tune_edge_block; want_plan.tune_wg_per_cu = c->tune_wg_per_cu;
         want_plan.tune_pool_kernel = c->tune_pool_kernel; want_plan.tune_record_sort = c->tune_record_sort;
-        want_plan.tune_flush_rounds = c->tune_flush_rounds;
+        want_plan.tune_flush_rounds = c->tune_flush_rounds; want_plan.tune_exchange = c->tune_exchange;
         EdgePlan plan = plan_edge_pass(want_plan);   // tile size, kernel, launch shape (edge_plan.h)
         int compute_units = 0;
         HTRY(hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, c->cfg.device));
@@ -715,7 +785,33 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         if (c->tune_path == NOMAD_PATH_FIXED_ATOMICS) why = "the fixed-point atomics path was asked for (nomad_tune)";
         else if (s > 8) why = "more than 8 negatives per edge: the binned edge pass is built for s <= 8";
         else if (!bin_block) why = "the per-tile tables of the binned edge pass do not fit LDS at this number of points";
-        if (E > 0 && why.empty()) {
+        const ExchangePlan ex = edge_kind(c) == kPlainEdges && why.empty() ? plan_exchange(want_plan, plan) : ExchangePlan{};
+        if (ex.use) {
+            c->ex = ex;
+            c->n_bins = n_bins;
+            c->tile_bits = tile_bits;
+            const int eb = exchange_block_edges(s);
+            c->phases = plan_record_phases(E, s, eb, c->tune_phases);
+            // (sub-steps and phases are cut into blocks of their own: at most one more each than the positions fill)
+            const size_t blocks = (size_t)((E + eb - 1) / eb + c->phases - 1) / c->phases + 1, slots = exchange_slots(s) * blocks;
+            c->ex_spare = (uint32_t)slots;
+            bool ok = slots + kExchangeSpare < ((size_t)1 << 32) && dev_alloc(c, &c->ex_rec, slots + kExchangeSpare) == NOMAD_OK &&
+                      dev_alloc(c, &c->ex_idx, slots + kExchangeSpare) == NOMAD_OK && dev_alloc(c, &c->ex_pos, (size_t)(s + 2) / 2 * eb * blocks) == NOMAD_OK &&
+                      dev_alloc(c, &c->ex_side, (size_t)(eb / 32) * blocks) == NOMAD_OK && dev_alloc(c, &c->ex_runs, (size_t)n_bins * blocks) == NOMAD_OK &&
+                      dev_alloc(c, &c->head, (size_t)E) == NOMAD_OK && (c->phases == 1 || dev_alloc(c, &c->carry, (size_t)n * 2) == NOMAD_OK);
+            ok = ok && prepare_exchange(c) == NOMAD_OK;
+            if (ok) {
+                hipLaunchKernelGGL(k_edge_heads, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, n, c->head);
+                hipLaunchKernelGGL(k_zero_f2, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->ghead, n);
+                c->binned = c->exchange = true;
+            } else {   // the sorted edge pass remains
+                (void)hipGetLastError();
+                free_exchange(c);
+                dev_free(c, c->head); dev_free(c, c->carry);
+                c->phases = 1;
+            }
+        }
+        if (E > 0 && why.empty() && !c->exchange) {
             c->bin_block = bin_block;
             c->sorted_records = sorted;
             c->flush_rounds = plan.flush_rounds;
@@ -830,6 +926,9 @@ int nomad_tune(nomad_ctx* c, int knob, int value) {
         case NOMAD_TUNE_FLUSH_ROUNDS:
             if (value < 0 || value > 2) break;
             c->tune_flush_rounds = value; return NOMAD_OK;
+        case NOMAD_TUNE_EXCHANGE:
+            if (value < 0 || value > 2) break;
+            c->tune_exchange = value; return NOMAD_OK;
     }
     return fail(c, NOMAD_E_INVALID_ARG, "nomad_tune: unknown knob %d or value %d out of range", knob, value);
 }
@@ -870,17 +969,20 @@ int nomad_epoch(nomad_ctx* c, int32_t t) {
         if (c->cfg.scatter_mode == NOMAD_SCATTER_DETERMINISTIC && c->binned) {
             // the positions of this step in `phases` ranges cut at multiples of the workgroup size; every range's
             // records are accumulated before the next range reuses the pool, the last accumulation takes the step
-            const int phases = c->pool_rounds ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(c->phases, (e1 - e0 + c->bin_block - 1) / c->bin_block));
+            const int64_t cut = c->exchange ? exchange_block_edges(c->cfg.n_neg) : c->bin_block;
+            const int phases = c->pool_rounds ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(c->phases, (e1 - e0 + cut - 1) / cut));
             for (int ph = 0; ph < phases; ++ph) {
-                const int64_t blocks = (e1 - e0 + c->bin_block - 1) / c->bin_block;
-                const int64_t p0 = e0 + blocks * ph / phases * c->bin_block, p1 = ph + 1 == phases ? e1 : e0 + blocks * (ph + 1) / phases * c->bin_block;
+                const int64_t blocks = (e1 - e0 + cut - 1) / cut;
+                const int64_t p0 = e0 + blocks * ph / phases * cut, p1 = ph + 1 == phases ? e1 : e0 + blocks * (ph + 1) / phases * cut;
                 { Timed tm(c, NOMAD_K_EDGES);
-                  launch_edges_binned(c, a, p0, p1); }
+                  if (c->exchange) launch_exchange_edges(c, a, exchange_args(c, p0, p1));
+                  else launch_edges_binned(c, a, p0, p1); }
                 const bool last = ph + 1 == phases;
                 if (last) run_mean_gradient(c, r0, r1);
                 const int kind = phases == 1 ? kPhaseOnly : ph == 0 ? kPhaseFirst : last ? kPhaseLast : kPhaseMiddle;
                 Timed tm(c, NOMAD_K_TILES);   // accumulates the records of every tile; the last one takes the SGD step for its points
-                hipLaunchKernelGGL(k_tile_accumulate, dim3(c->n_bins), dim3(kBinBlock), sizeof(unsigned long long) * 2 << c->tile_bits,
+                if (c->exchange) launch_exchange_sums(c, exchange_args(c, p0, p1), eta, kind);
+                else hipLaunchKernelGGL(k_tile_accumulate, dim3(c->n_bins), dim3(kBinBlock), sizeof(unsigned long long) * 2 << c->tile_bits,
                                    c->stream, bin_args(c), (uint32_t)c->n_wg, c->g, n, c->theta, eta,
                                    c->through_means ? c->cluster_of : nullptr, c->through_means ? c->gmean : nullptr, c->carry, kind);
             }

@@ -1962,6 +1962,41 @@ __global__ void __launch_bounds__(kBlock) k_add_mean_gradient(float2* __restrict
 // it goes on as the single-phase form (kPhaseOnly) does.  Integer sums: the result does not depend on the phases.
 enum TilePhase { kPhaseOnly = 0, kPhaseFirst = 1, kPhaseMiddle = 2, kPhaseLast = 3 };
 
+// What follows the sums of a tile of points p0 .. (acc: x, then y): carried to the next phase, or with the head sums the gradient and the step.
+__device__ __forceinline__ void finish_tile(unsigned long long* acc, int64_t p0, int tile, float2* __restrict__ ghead, float2* __restrict__ g, int64_t n,
+                                            float2* __restrict__ theta, float eta, const int32_t* __restrict__ cluster_of,
+                                            const float2* __restrict__ gmean, unsigned long long* __restrict__ carry, int phase) {
+    if (phase == kPhaseFirst || phase == kPhaseMiddle) {   // not the last phase of the step: carry the sums on
+        for (int l = threadIdx.x; l < 2 * tile && 2 * p0 + l < 2 * n; l += kBinBlock) {
+            const unsigned long long before = phase == kPhaseMiddle ? carry[2 * p0 + l] : 0ull;
+            carry[2 * p0 + l] = before + acc[(l & 1) * tile + (l >> 1)];
+        }
+        return;
+    }
+    if (phase == kPhaseLast) {
+        for (int l = threadIdx.x; l < 2 * tile && 2 * p0 + l < 2 * n; l += kBinBlock) acc[(l & 1) * tile + (l >> 1)] += carry[2 * p0 + l];
+        __syncthreads();
+    }
+    for (int l = threadIdx.x; l < tile && p0 + l < n; l += kBinBlock) {
+        const float2 hd = ghead[p0 + l];
+        ghead[p0 + l] = make_float2(0.f, 0.f);   // consumed: rows that hand their head sum on as records rely on this
+        float2 gi = make_float2((float)((double)hd.x + (double)(long long)acc[l] * kFixInv),
+                                (float)((double)hd.y + (double)(long long)acc[tile + l] * kFixInv));
+        if (gmean) {   // gradient through the means: every member's share of its cell's term
+            const float2 gm = gmean[cluster_of[p0 + l]];
+            gi.x += gm.x;
+            gi.y += gm.y;
+        }
+        g[p0 + l] = gi;
+        if (theta) {
+            float2 t = theta[p0 + l];
+            t.x = fmaf(-eta, gi.x, t.x);
+            t.y = fmaf(-eta, gi.y, t.y);
+            theta[p0 + l] = t;
+        }
+    }
+}
+
 __global__ void __launch_bounds__(kBinBlock) k_tile_accumulate(const BinArgs Q, uint32_t n_wg, float2* __restrict__ g, int64_t n,
                                                               float2* __restrict__ theta, float eta,
                                                               const int32_t* __restrict__ cluster_of, const float2* __restrict__ gmean,
@@ -2025,36 +2060,7 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_accumulate(const BinArgs Q, 
         }
     }
     __syncthreads();
-    const int64_t p0 = (int64_t)b << Q.tile_bits;
-    if (phase == kPhaseFirst || phase == kPhaseMiddle) {   // not the last phase of the step: carry the sums on
-        for (int l = threadIdx.x; l < 2 * tile && 2 * p0 + l < 2 * n; l += kBinBlock) {
-            const unsigned long long before = phase == kPhaseMiddle ? carry[2 * p0 + l] : 0ull;
-            carry[2 * p0 + l] = before + acc[(l & 1) * tile + (l >> 1)];
-        }
-        return;
-    }
-    if (phase == kPhaseLast) {
-        for (int l = threadIdx.x; l < 2 * tile && 2 * p0 + l < 2 * n; l += kBinBlock) acc[(l & 1) * tile + (l >> 1)] += carry[2 * p0 + l];
-        __syncthreads();
-    }
-    for (int l = threadIdx.x; l < tile && p0 + l < n; l += kBinBlock) {
-        const float2 hd = Q.ghead[p0 + l];
-        Q.ghead[p0 + l] = make_float2(0.f, 0.f);   // consumed: rows that hand their head sum on as records rely on this
-        float2 gi = make_float2((float)((double)hd.x + (double)(long long)acc[l] * kFixInv),
-                                (float)((double)hd.y + (double)(long long)acc[tile + l] * kFixInv));
-        if (gmean) {   // gradient through the means: every member's share of its cell's term
-            const float2 gm = gmean[cluster_of[p0 + l]];
-            gi.x += gm.x;
-            gi.y += gm.y;
-        }
-        g[p0 + l] = gi;
-        if (theta) {
-            float2 t = theta[p0 + l];
-            t.x = fmaf(-eta, gi.x, t.x);
-            t.y = fmaf(-eta, gi.y, t.y);
-            theta[p0 + l] = t;
-        }
-    }
+    finish_tile(acc, (int64_t)b << Q.tile_bits, tile, Q.ghead, g, n, theta, eta, cluster_of, gmean, carry, phase);
 }
 
 // fixed-order sum of the per-block loss partials (one block)

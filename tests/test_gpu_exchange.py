@@ -1,0 +1,79 @@
+"""The exchanged edge pass against the sorted one: the same lanes take the same edges, products are rounded alike and forces are
+summed as integers, so gradient and embedding agree bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import c_oracle
+from paper_2505_15511_amd import Nomad
+from tests.test_gpu_parity import GRAD_TOL, grad_err
+
+pytestmark = pytest.mark.gpu
+BLOCK = {1: 3072, 2: 3072, 3: 2304, 4: 1536, 5: 1536, 6: 768, 7: 768, 8: 768}     # positions of a block
+
+
+def graph(n, E, seed, hub=0):
+    """E edges with random heads (rows of every length, empty ones too) and tails; with `hub`, that many of them leave one point."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    head = torch.randint(0, n, (E,), generator=g, device="cuda")
+    head[:hub] = n // 3
+    head = head.sort().values
+    col = (head + 1 + torch.randint(0, max(1, n - 1), (E,), generator=g, device="cuda")) % n
+    near = torch.rand(E, generator=g, device="cuda") < 0.5                # half of the tails close by: long runs of one tile
+    col = torch.where(near, (head + 1 + torch.randint(0, min(40, n - 1), (E,), generator=g, device="cuda")) % n, col)
+    row_ptr = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    row_ptr[1:] = torch.cumsum(torch.bincount(head, minlength=n), 0).to(torch.int32)
+    return row_ptr, col.to(torch.int32), 0.5 * torch.randn(n, 2, generator=g, device="cuda")
+
+
+def epochs(n, s, row_ptr, col, theta, exchange, tune=None, weights=None, n_epochs=2, **kw):
+    nm = Nomad(n, 1, s, 5.0, 10, 1.0, 77, tune=dict(tune or {}, exchange=exchange), **kw)
+    nm.set_graph(row_ptr, col, weights, torch.zeros(n, dtype=torch.int32, device="cuda"), None)
+    nm.set_embedding(theta)
+    for t in range(n_epochs):
+        nm.epoch(t)
+    return nm.get_gradient(device=True), nm.get_embedding(device=True)
+
+
+def same(a, b):
+    assert torch.equal(a[0].view(torch.int32), b[0].view(torch.int32)) and torch.equal(a[1].view(torch.int32), b[1].view(torch.int32))
+
+
+@pytest.mark.parametrize("s", range(1, 9))
+@pytest.mark.parametrize("blocks,edges", [(0, 1), (0, 63), (1, -1), (1, 0), (1, 1), (9, 77)])
+def test_blocks(s, blocks, edges):
+    E = blocks * BLOCK[s] + edges
+    args = graph(2_000, E, 100 * s + E % 97, hub=5_000 if blocks == 9 else 0)
+    same(epochs(2_000, s, *args, exchange=1), epochs(2_000, s, *args, exchange=2))
+
+
+@pytest.mark.parametrize("n", [2, 17, 256, 4_097, 65_536, 300_001])
+def test_points(n):
+    args = graph(n, 40_000, n)
+    same(epochs(n, 5, *args, exchange=1), epochs(n, 5, *args, exchange=2))
+
+
+# tile kernels: 64 lanes a run; 32; pairs of tiles and 32, 16 for the sums; pairs and 16
+@pytest.mark.parametrize("n,E", [(1_200_000, 3_000_001), (3_100_000, 3_200_000), (7_000_003, 9_000_000), (17_500_001, 9_000_000)])
+def test_lanes_and_pairs(n, E):
+    args = graph(n, E, n % 1000, hub=20_000)
+    same(epochs(n, 5, *args, exchange=1, n_epochs=1), epochs(n, 5, *args, exchange=2, n_epochs=1))
+
+
+@pytest.mark.parametrize("tune,kw", [({}, {"batches_per_epoch": 4}), ({"record_phases": 3}, {}), ({"record_phases": 64}, {"batches_per_epoch": 3}),
+                                     ({}, {"inverse_rank_weights": True})], ids=["sub-steps", "phases", "both", "ranks"])
+def test_steps_and_weights(tune, kw):
+    args = graph(30_000, 200_000, 5, hub=3_000)
+    same(epochs(30_000, 5, *args, exchange=1, tune=tune, **kw), epochs(30_000, 5, *args, exchange=2, tune=tune, **kw))
+
+
+def test_against_the_oracle():
+    n, s = 5_000, 5
+    row_ptr, col, theta = graph(n, 60_000, 9, hub=2_000)
+    w = torch.rand(60_000, device="cuda") + 0.1
+    got = epochs(n, s, row_ptr, col, theta, exchange=1, weights=w, n_epochs=1)
+    O = c_oracle.COracle(row_ptr=row_ptr.cpu().numpy(), col_idx=col.cpu().numpy(), weights=w.cpu().numpy(), cluster_of=np.zeros(n, np.int32), 
+                         n=n, n_clusters=1, n_neg=s, noise_count=5.0, n_epochs=10, lr0=1.0, seed=77)
+    _, g_ref, _ = O.epoch(theta.cpu().numpy(), 0)
+    assert grad_err(got[0].cpu().numpy(), g_ref) < GRAD_TOL
