@@ -73,7 +73,7 @@ struct EdgePlanRequest {
     bool pool_distinct = false;
     // nomad_tune (0 = the library's choice, except pool_kernel: 1 = use the pooled kernels)
     int tune_edge_block = 0, tune_wg_per_cu = 0, tune_pool_kernel = 1, tune_record_sort = 0, tune_flush_rounds = 0,
-        tune_exchange = 0;
+        tune_exchange = 0, tune_phases = 0;
 };
 
 struct EdgePlan {
@@ -178,6 +178,22 @@ inline int plan_record_phases(int64_t E, int s, int bin_block, int tune_phases) 
     const int64_t blocks = (E + bin_block - 1) / bin_block;
     if (phases > blocks) phases = (int)blocks;
     return phases < 1 ? 1 : phases;
+}
+
+// Whether a problem takes the edge pass that sums in LDS (small_kernels.h), and its workgroups (0: no).  Every embedding whose sums fit
+// one workgroup's LDS: whole epoch, records -> sums in LDS, us: 2,000 points and 47 k positions 19.1 -> 10.4 (s = 2: 17.0 -> 9.8, s = 8: 21.6 -> 11.8),
+// 5,000 29.7 -> 17.4, 8,000 33.2 -> 21.5, 10,000 39.6 -> 26.0 (80 k positions, s = 2: 22.5 -> 18.1).
+// Workgroups: a round of 1,024 positions costs 3.8 us, a megabyte of sums written and read back half of one: as many workgroups as there are
+// rounds until their sums are 12 MB (8,000 points: 6 MB 25.8 us, 12 MB 21.5, 16 MB 21.9; 5,000: 16.8, 17.4, 17.6).
+constexpr int kSmallLanes = 1024;
+NOMAD_HOST_DEVICE inline size_t small_lds_bytes(int64_t n) { return (size_t)n * 16; }
+inline int plan_small(const EdgePlanRequest& q, const EdgePlan& p, int compute_units) {
+    const bool sorted_asked = q.tune_edge_block || q.tune_wg_per_cu || q.tune_record_sort || q.tune_flush_rounds || q.tune_phases || q.tune_exchange;
+    if (q.s < 0 || q.s > 8 || q.E < 1 || q.pool_size || !p.bin_block || sorted_asked || q.n < 1 || small_lds_bytes(q.n) > kMaxLdsBytes) return 0;
+    const int64_t rounds = (q.E + kSmallLanes - 1) / kSmallLanes, room = (int64_t)(12 << 20) / (int64_t)small_lds_bytes(q.n);
+    int64_t wg = rounds < compute_units ? rounds : compute_units;
+    if (wg > room) wg = room;
+    return wg < 1 ? 1 : (int)wg;
 }
 
 // Whether a problem of one population takes the exchanged edge pass (exchange_kernels.h), and its tile kernels' shapes.

@@ -17,6 +17,7 @@
 #include "nomad.h"
 #include "exchange_kernels.h"
 #include "nomad_kernels.h"
+#include "small_kernels.h"
 
 using namespace nomad;
 
@@ -75,6 +76,8 @@ struct nomad_ctx {
     int* flags = nullptr;
     // launch-shape knobs (nomad_tune) and what set_graph made of them
     int tune_edge_block = 0, tune_wg_per_cu = 0, tune_path = 0, tune_pool_kernel = 1, tune_phases = 0, tune_record_sort = 0, tune_flush_rounds = 0, tune_exchange = 0;
+    int small_wg = 0;               // > 0: the edge pass sums in LDS (small_kernels.h), at most this many workgroups
+    unsigned long long* small_sums = nullptr;
     bool exchange = false;          // the edge pass is the exchanged one (exchange_kernels.h)
     float2* ex_rec = nullptr;
     uint16_t *ex_idx = nullptr, *ex_side = nullptr;
@@ -165,6 +168,8 @@ void free_graph(nomad_ctx* c) {
     dev_free(c, c->pool); dev_free(c, c->chunk_prev); dev_free(c, c->chain_head); dev_free(c, c->chain_fill); dev_free(c, c->wg_pool_begin);
     dev_free(c, c->head); dev_free(c, c->carry); dev_free(c, c->pool_keys);
     free_exchange(c);
+    dev_free(c, c->small_sums);
+    c->small_wg = 0;
     c->phases = 1;
     c->binned = false;
     c->pool_rounds = 0;
@@ -354,6 +359,27 @@ void launch_edges_binned(nomad_ctx* c, const EdgeArgs& a, int64_t e_begin, int64
     const dim3 grid(c->n_wg), block(c->bin_block);
     const size_t lds = edge_pass_lds_bytes(c);
     with_edge_pass_kernel(c, [&](EdgePassKernel kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, c->stream, a, q); });
+}
+
+// ---- the edge pass of small embeddings
+template <typename Fn>
+void with_small_kernel(const nomad_ctx* c, Fn fn) {
+    const int kind = edge_kind(c);
+    switch (c->cfg.n_neg) {
+#define NOMAD_CASE(S) case S: fn(kind == kPlainEdges ? k_edges_small<S, kPlainEdges> : kind == kGroupedEdges ? k_edges_small<S, kGroupedEdges> : k_edges_small<S, kFarEdges>); break;
+        NOMAD_CASE(0) NOMAD_CASE(1) NOMAD_CASE(2) NOMAD_CASE(3) NOMAD_CASE(4) NOMAD_CASE(5) NOMAD_CASE(6) NOMAD_CASE(7) NOMAD_CASE(8)
+#undef NOMAD_CASE
+    }
+}
+
+// edge pass and step of the positions e_begin .. e_end-1
+void launch_small(nomad_ctx* c, const EdgeArgs& a, int64_t e_begin, int64_t e_end, float eta) {
+    const SmallArgs x{c->head, c->small_sums, c->ghead, e_begin, e_end};
+    const uint32_t wg = (uint32_t)std::min<int64_t>(c->small_wg, (e_end - e_begin + kSmallLanes - 1) / kSmallLanes);
+    { Timed tm(c, NOMAD_K_EDGES);
+      with_small_kernel(c, [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(wg), dim3(kSmallLanes), small_lds_bytes(c->n), c->stream, a, x); }); }
+    Timed tm(c, NOMAD_K_TILES);
+    hipLaunchKernelGGL(k_small_finish, dim3(blocks_for(c->n, 32)), dim3(256), 0, c->stream, c->small_sums, wg, c->ghead, c->g, (uint32_t)c->n, c->theta, eta);
 }
 
 // ---- the exchanged edge pass
@@ -772,7 +798,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         want_plan.pool_distinct = c->cfg.pool_mode != NOMAD_POOL_PICKS16;
         want_plan.tune_edge_block = c->tune_edge_block; want_plan.tune_wg_per_cu = c->tune_wg_per_cu;
         want_plan.tune_pool_kernel = c->tune_pool_kernel; want_plan.tune_record_sort = c->tune_record_sort;
-        want_plan.tune_flush_rounds = c->tune_flush_rounds; want_plan.tune_exchange = c->tune_exchange;
+        want_plan.tune_flush_rounds = c->tune_flush_rounds; want_plan.tune_exchange = c->tune_exchange; want_plan.tune_phases = c->tune_phases;
         EdgePlan plan = plan_edge_pass(want_plan);   // tile size, kernel, launch shape (edge_plan.h)
         int compute_units = 0;
         HTRY(hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, c->cfg.device));
@@ -785,8 +811,22 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         if (c->tune_path == NOMAD_PATH_FIXED_ATOMICS) why = "the fixed-point atomics path was asked for (nomad_tune)";
         else if (s > 8) why = "more than 8 negatives per edge: the binned edge pass is built for s <= 8";
         else if (!bin_block) why = "the per-tile tables of the binned edge pass do not fit LDS at this number of points";
+        const int small_wg = edge_kind(c) != kAnyEdges && why.empty() ? plan_small(want_plan, plan, compute_units) : 0;
+        if (small_wg && dev_alloc(c, &c->small_sums, (size_t)small_wg * 2 * n) == NOMAD_OK && dev_alloc(c, &c->head, (size_t)E) == NOMAD_OK) {
+            hipError_t allowed = hipSuccess;
+            with_small_kernel(c, [&](auto kernel) { allowed = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_lds_bytes(n)); });
+            HTRY(allowed);
+            hipLaunchKernelGGL(k_edge_heads, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, n, c->head);
+            hipLaunchKernelGGL(k_zero_f2, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->ghead, n);
+            c->small_wg = small_wg;
+            c->binned = true;
+        } else if (small_wg) {   // records remain
+            (void)hipGetLastError();
+            dev_free(c, c->small_sums);
+            dev_free(c, c->head);
+        }
         const ExchangePlan ex = edge_kind(c) == kPlainEdges && why.empty() ? plan_exchange(want_plan, plan) : ExchangePlan{};
-        if (ex.use) {
+        if (ex.use && !c->small_wg) {
             c->ex = ex;
             c->n_bins = n_bins;
             c->tile_bits = tile_bits;
@@ -811,7 +851,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 c->phases = 1;
             }
         }
-        if (E > 0 && why.empty() && !c->exchange) {
+        if (E > 0 && why.empty() && !c->exchange && !c->small_wg) {
             c->bin_block = bin_block;
             c->sorted_records = sorted;
             c->flush_rounds = plan.flush_rounds;
@@ -966,6 +1006,10 @@ int nomad_epoch(nomad_ctx* c, int32_t t) {
         a.row_begin = r0;
         a.row_end = r1;
         if (c->through_means) a.cS = c->cS;
+        if (c->small_wg) {
+            launch_small(c, a, e0, e1, eta);
+            continue;
+        }
         if (c->cfg.scatter_mode == NOMAD_SCATTER_DETERMINISTIC && c->binned) {
             // the positions of this step in `phases` ranges cut at multiples of the workgroup size; every range's
             // records are accumulated before the next range reuses the pool, the last accumulation takes the step
@@ -1017,12 +1061,12 @@ int nomad_loss(nomad_ctx* c, int32_t t_sample, double* out_host) {
     if (rc) return rc;
     if (!out_host || t_sample < 0) return fail(c, NOMAD_E_INVALID_ARG, "null output or negative epoch index");
     HIP_TRY(c, hipSetDevice(c->cfg.device));
-    run_means(c);
+    if (c->grouped) run_means(c);
     run_mean_field(c, 0, c->n);
     const EdgeArgs a = edge_args(c, (uint32_t)t_sample);
     { Timed tm(c, NOMAD_K_LOSS);
       launch_edges<kModeLoss>(c, a);
-      hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(kBlock), 0, c->stream, c->loss_partial, c->edge_grid, 1.0 / (double)c->n,
+      hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(kLossBlock), 0, c->stream, c->loss_partial, c->edge_grid, 1.0 / (double)c->n,
                          (double*)c->loss_out.word()); }
     HIP_TRY(c, hipGetLastError());
     rc = finish(c);

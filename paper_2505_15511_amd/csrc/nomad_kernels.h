@@ -437,10 +437,12 @@ struct EdgeOut {
     float rx[S], ry[S];
 };
 
-// The arithmetic of one edge, given the embedding rows it touches (tj the tail, tm[k] the negatives).
+// The arithmetic of one edge, given the embedding rows it touches (tj the tail, tm[k] the negatives).  Every product is rounded by
+// itself (the fused ones are written out): which ones the compiler would fuse depends on the kernel around it.
 template <int S, bool LOSS>
 __device__ __forceinline__ void edge_math(const HeadCtx& h, float pe, float2 tj, const float2 (&tm)[S > 0 ? S : 1],
                                           EdgeOut<(S > 0 ? S : 1)>& o) {
+#pragma clang fp contract(off)
     o.dx = h.ti.x - tj.x;
     o.dy = h.ti.y - tj.y;
     const float qij = cauchy(o.dx, o.dy);
@@ -1962,6 +1964,12 @@ __global__ void __launch_bounds__(kBlock) k_add_mean_gradient(float2* __restrict
 // it goes on as the single-phase form (kPhaseOnly) does.  Integer sums: the result does not depend on the phases.
 enum TilePhase { kPhaseOnly = 0, kPhaseFirst = 1, kPhaseMiddle = 2, kPhaseLast = 3 };
 
+// a point's gradient from its head sum and the fixed-point sums of what it receives, and the SGD step of Section 3.4
+__device__ __forceinline__ float2 point_gradient(float2 hd, unsigned long long sx, unsigned long long sy) {
+    return make_float2((float)((double)hd.x + (double)(long long)sx * kFixInv), (float)((double)hd.y + (double)(long long)sy * kFixInv));
+}
+__device__ __forceinline__ float2 stepped(float2 t, float2 gi, float eta) { return make_float2(fmaf(-eta, gi.x, t.x), fmaf(-eta, gi.y, t.y)); }
+
 // What follows the sums of a tile of points p0 .. (acc: x, then y): carried to the next phase, or with the head sums the gradient and the step.
 __device__ __forceinline__ void finish_tile(unsigned long long* acc, int64_t p0, int tile, float2* __restrict__ ghead, float2* __restrict__ g, int64_t n,
                                             float2* __restrict__ theta, float eta, const int32_t* __restrict__ cluster_of,
@@ -1980,20 +1988,14 @@ __device__ __forceinline__ void finish_tile(unsigned long long* acc, int64_t p0,
     for (int l = threadIdx.x; l < tile && p0 + l < n; l += kBinBlock) {
         const float2 hd = ghead[p0 + l];
         ghead[p0 + l] = make_float2(0.f, 0.f);   // consumed: rows that hand their head sum on as records rely on this
-        float2 gi = make_float2((float)((double)hd.x + (double)(long long)acc[l] * kFixInv),
-                                (float)((double)hd.y + (double)(long long)acc[tile + l] * kFixInv));
+        float2 gi = point_gradient(hd, acc[l], acc[tile + l]);
         if (gmean) {   // gradient through the means: every member's share of its cell's term
             const float2 gm = gmean[cluster_of[p0 + l]];
             gi.x += gm.x;
             gi.y += gm.y;
         }
         g[p0 + l] = gi;
-        if (theta) {
-            float2 t = theta[p0 + l];
-            t.x = fmaf(-eta, gi.x, t.x);
-            t.y = fmaf(-eta, gi.y, t.y);
-            theta[p0 + l] = t;
-        }
+        if (theta) theta[p0 + l] = stepped(theta[p0 + l], gi, eta);
     }
 }
 
@@ -2063,18 +2065,26 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_accumulate(const BinArgs Q, 
     finish_tile(acc, (int64_t)b << Q.tile_bits, tile, Q.ghead, g, n, theta, eta, cluster_of, gmean, carry, phase);
 }
 
-// fixed-order sum of the per-block loss partials (one block)
-__global__ void __launch_bounds__(kBlock) k_loss_finish(const double* __restrict__ partial, uint32_t count, double inv_n,
-                                                        double* __restrict__ out) {
-    __shared__ double sl[kBlock / 64];
+// fixed-order sum of the per-block loss partials (one block; eight loads of a lane in flight: 6,250 partials took 7.7 us one by one
+// in 256 lanes)
+constexpr int kLossBlock = 1024;
+__global__ void __launch_bounds__(kLossBlock) k_loss_finish(const double* __restrict__ partial, uint32_t count, double inv_n,
+                                                            double* __restrict__ out) {
+    __shared__ double sl[kLossBlock / 64];
     double acc = 0.0;
-    for (uint32_t b = threadIdx.x; b < count; b += kBlock) acc += partial[b];
+    for (uint32_t b0 = threadIdx.x; b0 < count; b0 += 8 * kLossBlock) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = partial[min(b0 + u * kLossBlock, count - 1u)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += b0 + u * kLossBlock < count ? v[u] : 0.0;
+    }
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) sl[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         double t = 0.0;
-        for (int w = 0; w < kBlock / 64; ++w) t += sl[w];
+        for (int w = 0; w < kLossBlock / 64; ++w) t += sl[w];
         *out = t * inv_n;
     }
 }

@@ -66,3 +66,37 @@ def test_shapes_fit(planner, s):
         assert 2 * p["edges_lds"] <= 160 * 1024
         assert max(p["deal_lds"], p["rows_lds"], p["sums_lds"]) <= p["max_lds"]
         assert 1 <= p["parts"] <= 1024
+
+
+SMALL = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "edge_plan.h"
+using namespace nomad;
+int main(int argc, char** argv) {
+    EdgePlanRequest q;
+    q.n = atoll(argv[1]); q.E = atoll(argv[2]); q.s = atoi(argv[3]); q.pool_size = atoi(argv[4]); q.pool_block = q.pool_size ? 4096 : 0; q.tune_phases = atoi(argv[5]);
+    EdgePlan p = plan_edge_pass(q);
+    fit_tiles(p, q, 256, true);
+    printf("%d %zu %zu\n", plan_small(q, p, 256), small_lds_bytes(q.n), kMaxLdsBytes);
+    return 0;
+}
+"""
+
+
+def test_sums_in_lds(tmp_path):
+    """Embeddings whose sums fit a workgroup's LDS, the workgroups they get, and what keeps them on the other passes."""
+    (tmp_path / "small.cpp").write_text(SMALL)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2505_15511_amd", "csrc"), str(tmp_path / "small.cpp"), "-o",
+                    str(tmp_path / "small")], check=True, capture_output=True, text=True)
+
+    def plan(n, E, s=5, pool=0, phases=0):
+        wg, lds, most = map(int, subprocess.run([str(tmp_path / "small")] + [str(v) for v in (n, E, s, pool, phases)], check=True, capture_output=True,
+                                                text=True).stdout.split())
+        assert wg == 0 or lds <= most
+        return wg
+    assert plan(2_000, 46_734) == 46 and plan(1, 1) == 1 and plan(2, 10 ** 7) == 256
+    assert plan(10_224, 300_000) > 0 and plan(10_225, 300_000) == 0
+    for n in (5_000, 8_000, 10_224):
+        assert plan(n, 10 ** 6) * 16 * n <= 12 << 20
+    assert plan(2_000, 46_734, s=9) == plan(2_000, 46_734, pool=1024) == plan(2_000, 46_734, phases=2) == plan(2_000, 0) == 0
