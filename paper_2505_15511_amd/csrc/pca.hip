@@ -31,26 +31,29 @@ extern "C" int nomad_pca_init(const float* X, int64_t n, int32_t d, float std0, 
         dX = x; dTheta = t;
     }
     const int32_t p = std::min<int32_t>(kRitz, d);
-    // mean
-    const int32_t mean_blocks = (int32_t)blocks_of(n, kMeanRows);
-    double *mean_partial = nullptr, *mean = nullptr;
-    KTRY(buf.alloc(&mean_partial, (size_t)mean_blocks * d));
-    KTRY(buf.alloc(&mean, (size_t)d));
-    hipLaunchKernelGGL(k_pca_colsum, dim3((uint32_t)mean_blocks), dim3(256), 0, st, dX, n, d, mean_partial);
-    hipLaunchKernelGGL(k_pca_mean, dim3(blocks_of(d, 64)), dim3(64 * kMeanWaves), 0, st, (const double*)mean_partial, mean_blocks, d, n, mean);
-    // covariance: as many (tile pair, slab) wavefronts as the chip holds at once, two per SIMD (every one is a long chain of
-    // matrix instructions, so none is left over for a second round); slabs of at least 256 rows
-    const int32_t nb = (d + kColBlock - 1) / kColBlock, n_pairs = nb * (nb + 1) / 2;
-    int64_t slabs64 = std::max<int64_t>(1, 2048 / n_pairs);
-    slabs64 = std::min<int64_t>(slabs64, (n + 255) / 256);
-    const int64_t slab_rows = (((n + slabs64 - 1) / slabs64) + 3) / 4 * 4;
-    const int32_t slabs = (int32_t)((n + slab_rows - 1) / slab_rows);
-    double *cov_partial = nullptr, *Cm = nullptr;
-    KTRY(buf.alloc(&cov_partial, (size_t)n_pairs * slabs * kColBlock * kColBlock));
+    // covariance about a shift, and the mean with it: as many (tile pair, slab) wavefronts as the chip holds at once, two per SIMD
+    // (every one is a long chain of matrix instructions, so none is left over for a second round); slabs of at least 256 rows
+    const int32_t nb = (d + kColBlock - 1) / kColBlock, n_off = nb * (nb - 1) / 2, n_pairs = nb + n_off;
+    const auto cut = [&](double want, int32_t& count, int64_t& rows) {
+        const int64_t slabs64 = std::max<int64_t>(1, std::min<int64_t>((int64_t)want, (n + 255) / 256));
+        rows = (((n + slabs64 - 1) / slabs64) + 3) / 4 * 4;
+        count = (int32_t)((n + rows - 1) / rows);
+    };
+    CovSlabs slabs;
+    const double off_slabs = 2048.0 / (n_off + kDiagonalShare * nb);
+    cut(off_slabs, slabs.off, slabs.off_rows);
+    cut(kDiagonalShare * off_slabs, slabs.diag, slabs.diag_rows);
+    const size_t tiles = (size_t)nb * slabs.diag + (size_t)n_off * slabs.off;
+    double *cov_partial = nullptr, *Cm = nullptr, *sums = nullptr, *shift = nullptr, *delta = nullptr, *mean = nullptr;
+    KTRY(buf.alloc(&cov_partial, tiles * kColBlock * kColBlock));
     KTRY(buf.alloc(&Cm, (size_t)d * d));
-    hipLaunchKernelGGL(k_pca_cov, dim3((uint32_t)(n_pairs * slabs)), dim3(64), 0, st, dX, n, d, (const double*)mean, slabs, slab_rows, cov_partial);
+    KTRY(buf.alloc(&sums, (size_t)slabs.diag * d));
+    KTRY(buf.alloc(&shift, (size_t)d)); KTRY(buf.alloc(&delta, (size_t)d)); KTRY(buf.alloc(&mean, (size_t)d));
+    hipLaunchKernelGGL(k_pca_shift, dim3(blocks_of(d, 64)), dim3(64 * kMeanWaves), 0, st, dX, n, d, shift);
+    hipLaunchKernelGGL(k_pca_cov, dim3((uint32_t)tiles), dim3(64), 0, st, dX, n, d, (const double*)shift, slabs, cov_partial, sums);
+    hipLaunchKernelGGL(k_pca_mean, dim3(blocks_of(d, 64)), dim3(64 * kMeanWaves), 0, st, (const double*)sums, slabs.diag, d, n, (const double*)shift, delta, mean);
     hipLaunchKernelGGL(k_pca_cov_reduce, dim3(blocks_of((int64_t)n_pairs * kColBlock * kColBlock, kReduceEntries)), dim3(256), 0, st,
-                       (const double*)cov_partial, n_pairs, slabs, d, n, Cm);
+                       (const double*)cov_partial, slabs, d, n, (const double*)delta, Cm);
     // leading eigenvectors: subspace iteration from a fixed pseudo-random block
     double *Q = nullptr, *Z = nullptr, *factor = nullptr;
     RitzState* state = nullptr;

@@ -1,8 +1,11 @@
 // Device code of the PCA initialisation (Section 3.5: the projection starts from a PCA of the data).
 //
-//   mean        column sums in float64, a slab of rows per block, the slabs added in order
-//   covariance  C = (1/n) sum_i (x_i - mean)(x_i - mean)^T: a dense contraction over the points, on the float64 matrix
-//               cores (v_mfma_f64_16x16x4f64), one wavefront per 64x64 tile of C and slab of rows, slabs added in order
+//   shift       a = the mean of up to kShiftRows rows spread over the set, in float64: near the mean, so that
+//   covariance  C = (1/n) sum_i (x_i - a)(x_i - a)^T - (mean - a)(mean - a)^T loses nothing: |mean - a|^2 is of the order of the
+//               variance over the sampled rows, n / kShiftRows times the variance at the very worst (four digits of the sixteen).  A dense
+//               contraction over the points, on the float64 matrix cores (v_mfma_f64_16x16x4f64), one wavefront per 64x64 tile
+//               of C and slab of rows, slabs added in order; the tiles on the diagonal also add up the columns, for
+//   mean        = a + (1/n) sum_i (x_i - a)
 //   axes        the leading eigenvectors of C by subspace iteration accelerated with Chebyshev polynomials: a block of
 //               kRitz vectors, a Rayleigh-Ritz step (the 8 x 8 pencil on one wavefront) after every polynomial
 //   scores      theta_i = ((x_i - mean) . axis_1, (x_i - mean) . axis_2), float64, oriented and scaled, rounded once
@@ -14,33 +17,38 @@ namespace nomad_pca {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-constexpr int kMeanRows = 1024;   // rows per partial column sum
+constexpr int kShiftRows = 256;   // rows of the shift
 constexpr int kColBlock = 64;     // a wavefront's tile of C is kColBlock x kColBlock (4 x 4 matrix-core tiles)
 constexpr int kRitz = 8;          // vectors iterated together (convergence goes with lambda_9 / lambda_2)
 constexpr int kMaxDim = 768;
 
-__global__ void __launch_bounds__(256) k_pca_colsum(const float* __restrict__ X, int64_t n, int32_t d, double* __restrict__ partial) {
-    const int64_t r0 = (int64_t)blockIdx.x * kMeanRows, r1 = min(n, r0 + kMeanRows);
-    for (int col = threadIdx.x; col < d; col += 256) {
-        double s = 0.0;
-        int64_t r = r0;
-        for (; r + 16 <= r1; r += 16) {   // sixteen rows in flight; added in row order
-            float v[16];
+// shift = mean of the m rows floor(i n / m); a workgroup per 64 columns, every wavefront its share of the rows (eight in flight)
+constexpr int kMeanWaves = 16;
+__global__ void __launch_bounds__(64 * kMeanWaves) k_pca_shift(const float* __restrict__ X, int64_t n, int32_t d, double* __restrict__ shift) {
+    __shared__ double sum[kMeanWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = blockIdx.x * 64 + lane, c = min(col, d - 1);
+    const int m = (int)min((int64_t)kShiftRows, n);
+    double s = 0.0;
+    for (int i = wave; i < m; i += 8 * kMeanWaves) {
+        float v[8];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = X[(r + u) * d + col];
+        for (int u = 0; u < 8; ++u) v[u] = X[(int64_t)min(i + u * kMeanWaves, m - 1) * n / m * d + c];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) s += (double)v[u];
-        }
-        for (; r < r1; ++r) s += (double)X[r * d + col];
-        partial[(int64_t)blockIdx.x * d + col] = s;
+        for (int u = 0; u < 8; ++u) s += i + u * kMeanWaves < m ? (double)v[u] : 0.0;
+    }
+    sum[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && col < d) {
+        double t = 0.0;
+        for (int w = 0; w < kMeanWaves; ++w) t += sum[w][lane];
+        shift[col] = t / (double)m;
     }
 }
 
-// mean = sum of the partial sums / n; a workgroup per 64 columns, every wavefront its share of the partial sums (eight in
-// flight), the wavefronts' sums added in order.  (One thread per column took 31 us for the 977 slabs of a million rows.)
-constexpr int kMeanWaves = 16;
-__global__ void __launch_bounds__(64 * kMeanWaves) k_pca_mean(const double* __restrict__ partial, int32_t blocks, int32_t d, int64_t n,
-                                                              double* __restrict__ mean) {
+// delta = sum of the slabs' column sums of x - shift / n, mean = shift + delta; a workgroup per 64 columns, every wavefront its share of
+// the partial sums (eight in flight), the wavefronts' sums added in order.  (One thread per column took 31 us for 977 slabs.)
+__global__ void __launch_bounds__(64 * kMeanWaves) k_pca_mean(const double* __restrict__ partial, int32_t blocks, int32_t d, int64_t n, const double* __restrict__ shift,
+                                                              double* __restrict__ delta, double* __restrict__ mean) {
     __shared__ double sum[kMeanWaves][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = blockIdx.x * 64 + lane;
     double s = 0.0;
@@ -60,16 +68,25 @@ __global__ void __launch_bounds__(64 * kMeanWaves) k_pca_mean(const double* __re
     if (wave == 0 && col < d) {
         double t = 0.0;
         for (int w = 0; w < kMeanWaves; ++w) t += sum[w][lane];
-        mean[col] = t / (double)n;
+        t /= (double)n;
+        delta[col] = t;
+        mean[col] = shift[col] + t;
     }
 }
 
-// column blocks (a, b), a <= b, of tile pair number `pair` when there are nb column blocks
+// column blocks (a, b), a <= b, of tile pair number `pair` when there are nb column blocks: the diagonal first
 __host__ __device__ inline void cov_pair(int pair, int nb, int& a, int& b) {
+    if (pair < nb) { a = b = pair; return; }
+    pair -= nb;
     a = 0;
-    while (pair >= nb - a) { pair -= nb - a; ++a; }
-    b = a + pair;
+    while (pair >= nb - 1 - a) { pair -= nb - 1 - a; ++a; }
+    b = a + 1 + pair;
 }
+
+// Slabs of rows of a tile pair.  A tile on the diagonal takes 10 of the 16 products (the others are their mirror images), kDiagonalShare of the time:
+// its slabs are longer, so that all the wavefronts end together.
+constexpr double kDiagonalShare = 0.7;   // (with the columns' sums; million x 128: 0.56 0.343 ms, 0.62 0.341, 0.68 0.325, 0.75 0.329)
+struct CovSlabs { int32_t diag, off; int64_t diag_rows, off_rows; };
 
 // One wavefront: tile pair blockIdx.x / slabs, rows slab * slab_rows ...  Operand layout of the 16x16x4 float64
 // instruction: lane l supplies A[i = l % 16][k = l / 16] and B[k = l / 16][j = l % 16]; it receives D[i = l / 16 + 4 v][j = l % 16]
@@ -78,11 +95,11 @@ __host__ __device__ inline void cov_pair(int pair, int nb, int& a, int& b) {
 // Bound by issue: a step of four rows is 16 matrix instructions of 64 cycles, and vector instructions do not overlap float64
 // matrix instructions, so the step carries nothing but its loads (uniform base + 32-bit lane offset), conversions and
 // subtractions.  Columns beyond d are read as the last column (their entries of C are never stored), only the last step of a
-// slab masks rows.  n = 1e6, d = 128: 0.43 ms = 57 TFLOP/s executed (0.56 ms with every element masked); n = 1e5, d = 768:
-// 1.12 ms (2.0 ms).
+// slab masks rows.  n = 1e6, d = 128: 0.43 ms = 57 TFLOP/s executed (0.56 ms with every element masked), 0.325 without the mirrored
+// products and with the columns' sums (a pass of 0.083 ms before); n = 1e5, d = 768: 1.12 ms, now 1.06.
 template <bool DIAGONAL>
 __device__ __forceinline__ void cov_tile(const float* __restrict__ X, int64_t n, int32_t d, const double* __restrict__ mean, int a, int b,
-                                         int64_t r0, int64_t r1, double* __restrict__ out) {
+                                         int64_t r0, int64_t r1, double* __restrict__ out, double* __restrict__ sums) {
     const int lane = threadIdx.x, lr = lane >> 4, lc = lane & 15;
     uint32_t offa[4], offb[4];     // elements from the step's first row
     double ma[4], mb[4];
@@ -95,6 +112,7 @@ __device__ __forceinline__ void cov_tile(const float* __restrict__ X, int64_t n,
         mb[u] = mean[cb];
     }
     doublex4 acc[4][4];
+    double colsum[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int x = 0; x < 4; ++x)
 #pragma unroll
@@ -117,11 +135,12 @@ __device__ __forceinline__ void cov_tile(const float* __restrict__ X, int64_t n,
         for (int u = 0; u < 4; ++u) {
             xa[u] = live ? (double)va[u] - ma[u] : 0.0;
             xb[u] = DIAGONAL ? xa[u] : live ? (double)vb[u] - mb[u] : 0.0;
+            if (DIAGONAL) colsum[u] += xa[u];
         }
 #pragma unroll
         for (int x = 0; x < 4; ++x)
 #pragma unroll
-            for (int y = 0; y < 4; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[x], xb[y], acc[x][y], 0, 0, 0);
+            for (int y = DIAGONAL ? x : 0; y < 4; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[x], xb[y], acc[x][y], 0, 0, 0);
     };
     if (steps > 0) {
 #pragma unroll
@@ -156,34 +175,50 @@ __device__ __forceinline__ void cov_tile(const float* __restrict__ X, int64_t n,
 #pragma unroll
     for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int y = 0; y < 4; ++y)
+        for (int y = DIAGONAL ? x : 0; y < 4; ++y)
 #pragma unroll
             for (int v = 0; v < 4; ++v) out[(16 * x + lr + 4 * v) * kColBlock + 16 * y + lc] = acc[x][y][v];
+    if (DIAGONAL) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            double t = colsum[u];
+            t += __shfl_xor(t, 16, 64);
+            t += __shfl_xor(t, 32, 64);
+            const int c = a * kColBlock + 16 * u + lc;
+            if (lr == 0 && c < d) sums[c] = t;
+        }
+    }
 }
 
-__global__ void __launch_bounds__(64, 2) k_pca_cov(const float* __restrict__ X, int64_t n, int32_t d, const double* __restrict__ mean,
-                                                int32_t slabs, int64_t slab_rows, double* __restrict__ partial) {
-    const int pair = blockIdx.x / slabs, slab = blockIdx.x % slabs;
+// partial: [diagonal tiles][slabs.diag], then [the others][slabs.off] tiles; sums [slabs.diag][d]
+__global__ void __launch_bounds__(64, 2) k_pca_cov(const float* __restrict__ X, int64_t n, int32_t d, const double* __restrict__ shift,
+                                                CovSlabs slabs, double* __restrict__ partial, double* __restrict__ sums) {
+    const int nb = (d + kColBlock - 1) / kColBlock, on_diag = nb * slabs.diag, rest = (int)blockIdx.x - on_diag;
+    const int pair = rest < 0 ? (int)blockIdx.x / slabs.diag : nb + rest / slabs.off, slab = rest < 0 ? (int)blockIdx.x % slabs.diag : rest % slabs.off;
     int a, b;
-    cov_pair(pair, (d + kColBlock - 1) / kColBlock, a, b);
-    const int64_t r0 = (int64_t)slab * slab_rows, r1 = min(n, r0 + slab_rows);
+    cov_pair(pair, nb, a, b);
+    const int64_t rows = rest < 0 ? slabs.diag_rows : slabs.off_rows, r0 = min(n, (int64_t)slab * rows), r1 = min(n, r0 + rows);
     double* out = partial + (int64_t)blockIdx.x * (kColBlock * kColBlock);
-    if (a == b) cov_tile<true>(X, n, d, mean, a, b, r0, r1, out);
-    else cov_tile<false>(X, n, d, mean, a, b, r0, r1, out);
+    if (a == b) cov_tile<true>(X, n, d, shift, a, b, r0, r1, out, sums + (int64_t)slab * d);
+    else cov_tile<false>(X, n, d, shift, a, b, r0, r1, out, nullptr);
 }
 
-// C = (1/n) sum over the slabs; both triangles written.  A workgroup takes 32 consecutive entries of a tile, eight threads
+// C = (1/n) sum over the slabs - delta delta^T; both triangles written.  A workgroup takes 32 consecutive entries of a tile, eight threads
 // each: every eighth slab (eight in flight), the eight sums added in order.  (One thread per entry: 40 us for 683 slabs.)
 constexpr int kReduceEntries = 32;
-__global__ void __launch_bounds__(256) k_pca_cov_reduce(const double* __restrict__ partial, int32_t n_pairs, int32_t slabs, int32_t d,
-                                                        int64_t n, double* __restrict__ C) {
+__global__ void __launch_bounds__(256) k_pca_cov_reduce(const double* __restrict__ partial, CovSlabs cut, int32_t d, int64_t n, const double* __restrict__ delta,
+                                                        double* __restrict__ C) {
     __shared__ double part[8][kReduceEntries];
     const int sub = threadIdx.x / kReduceEntries, lane = threadIdx.x % kReduceEntries;
     const int64_t x = (int64_t)blockIdx.x * kReduceEntries + lane;   // kReduceEntries divides a tile: one pair per workgroup
     const int pair = (int)(x / (kColBlock * kColBlock)), e = (int)(x % (kColBlock * kColBlock));
+    const int nb = (d + kColBlock - 1) / kColBlock, slabs = pair < nb ? cut.diag : cut.off;
+    const int64_t first = pair < nb ? (int64_t)pair * cut.diag : (int64_t)nb * cut.diag + (int64_t)(pair - nb) * cut.off;
+    const int row = e / kColBlock, column = e % kColBlock;
+    const bool mirrored = pair < nb && row / 16 > column / 16;   // not computed: written with its mirror image
     double s = 0.0;
-    const double* src = partial + (int64_t)pair * slabs * (kColBlock * kColBlock) + e;
-    int sl = sub;
+    const double* src = partial + first * (kColBlock * kColBlock) + e;
+    int sl = mirrored ? slabs : sub;
     for (; sl + 56 < slabs; sl += 64) {
         double v[8];
 #pragma unroll
@@ -194,17 +229,17 @@ __global__ void __launch_bounds__(256) k_pca_cov_reduce(const double* __restrict
     for (; sl < slabs; sl += 8) s += src[(int64_t)sl * (kColBlock * kColBlock)];
     part[sub][lane] = s;
     __syncthreads();
-    if (sub != 0) return;
+    if (sub != 0 || mirrored) return;
     s = 0.0;
 #pragma unroll
     for (int u = 0; u < 8; ++u) s += part[u][lane];
     int a, b;
-    cov_pair(pair, (d + kColBlock - 1) / kColBlock, a, b);
-    const int gi = a * kColBlock + e / kColBlock, gj = b * kColBlock + e % kColBlock;
+    cov_pair(pair, nb, a, b);
+    const int gi = a * kColBlock + row, gj = b * kColBlock + column;
     if (gi >= d || gj >= d) return;
-    s /= (double)n;
+    s = s / (double)n - delta[gi] * delta[gj];
     C[(int64_t)gi * d + gj] = s;
-    if (a != b) C[(int64_t)gj * d + gi] = s;
+    if (a != b || row / 16 < column / 16) C[(int64_t)gj * d + gi] = s;
 }
 
 // ---- the leading eigenvectors of C: subspace iteration on a block of kRitz vectors, Chebyshev polynomials of C as the power
@@ -578,7 +613,8 @@ __global__ void __launch_bounds__(128) k_pca_orient(const double* __restrict__ Q
 
 // theta_i = factor * ((x_i - mean) . axis_1, (x_i - mean) . axis_2).  LANES lanes share a row (a power of two, enough for
 // one VEC-wide chunk of the row each), 64 / LANES rows side by side in a wavefront, kProjectRows such groups in flight: the
-// loop is a stream of X from memory (512 MB at 128 columns: 0.27 ms with four 4-byte loads in flight per lane).
+// loop is a stream of X from memory (512 MB at 128 columns: 0.27 ms with four 4-byte loads in flight per lane, 0.134 with eight of 16
+// bytes; halving the sums a lane holds at every step of the reduction, 16 exchanges for 80, takes 0.205).
 constexpr int kProjectRows = 8;
 template <int VEC, int LANES>
 __global__ void __launch_bounds__(256) k_pca_project(const float* __restrict__ X, int64_t n, int32_t d, const double* __restrict__ mean,
