@@ -631,20 +631,18 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
 
     // ---- validate on the device
     rc = dev_alloc(c, &c->flags, kFlagCount);
-    uint32_t *first = nullptr, *gfirst = nullptr;
+    uint32_t* first = nullptr;
     unsigned long long* boundaries = nullptr;
     if (rc == NOMAD_OK) rc = dev_alloc(c, &c->counts, (size_t)R);
     if (rc == NOMAD_OK) rc = dev_alloc(c, &first, (size_t)R);
-    if (rc == NOMAD_OK) rc = dev_alloc(c, &gfirst, (size_t)R);
     if (rc == NOMAD_OK) rc = dev_alloc(c, &boundaries, 2);
-    auto cleanup_tmp = [&]() { (void)hipStreamSynchronize(st); dev_free(c, wdev); dev_free(c, first); dev_free(c, gfirst); dev_free(c, boundaries); };
+    auto cleanup_tmp = [&]() { (void)hipStreamSynchronize(st); dev_free(c, wdev); dev_free(c, first); dev_free(c, boundaries); };
     if (rc != NOMAD_OK) { cleanup_tmp(); free_graph(c); return rc; }
 #define HTRY2(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) { cleanup_tmp(); free_graph(c); return fail(c, e_ == hipErrorOutOfMemory ? NOMAD_E_OOM : NOMAD_E_HIP, "%s: %s", #call, hipGetErrorString(e_)); } } while (0)
     HTRY2(hipStreamSynchronize(nullptr));   // the copies above: between device buffers they may still be on their way on the null stream
     HTRY2(hipMemsetAsync(c->flags, 0, sizeof(int) * kFlagCount, st));
     HTRY2(hipMemsetAsync(c->counts, 0, sizeof(uint32_t) * (size_t)R, st));
     HTRY2(hipMemsetAsync(first, 0xFF, sizeof(uint32_t) * (size_t)R, st));
-    HTRY2(hipMemsetAsync(gfirst, 0xFF, sizeof(uint32_t) * (size_t)R, st));
     HTRY2(hipMemsetAsync(boundaries, 0, sizeof(unsigned long long) * 2, st));
     hipLaunchKernelGGL(k_check_row_ptr, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, n, c->flags);
     int hflags[kFlagCount];
@@ -652,8 +650,8 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
     HTRY2(hipStreamSynchronize(st));
     if (hflags[kFlagRowPtr]) { cleanup_tmp(); free_graph(c); return fail(c, NOMAD_E_BAD_GRAPH, "row_ptr must start at 0 and be non-decreasing"); }
     hipLaunchKernelGGL(k_check_rows, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, c->col, wdev, c->pe, n, by_rank ? 1 : 0, c->flags);
-    hipLaunchKernelGGL(k_cluster_census, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->cluster_of,
-                       c->grouped ? c->group_of_cluster : nullptr, n, R, c->counts, first, gfirst, boundaries, c->flags);
+    hipLaunchKernelGGL(k_cluster_census, dim3(blocks_for(n, kCensusSpan)), dim3(kBlock), 0, st, c->cluster_of,
+                       c->grouped ? c->group_of_cluster : nullptr, n, R, c->counts, first, boundaries, c->flags);
     HTRY2(hipMemcpyAsync(hflags, c->flags, sizeof(hflags), hipMemcpyDeviceToHost, st));
     HTRY2(hipStreamSynchronize(st));
     const char* what = hflags[kFlagCol] ? "col_idx entry outside 0..n-1" : hflags[kFlagSelfLoop] ? "self loop in the graph"
@@ -663,13 +661,14 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
     dev_free(c, wdev);   // (the check has been waited for)
 
     // ---- partition tables (host arithmetic on |R|-sized arrays only)
-    std::vector<uint32_t> hcounts(R), hfirst(R), hgfirst(R);
+    std::vector<uint32_t> hcounts(R), hfirst(R), hgfirst(R, 0xFFFFFFFFu);
     unsigned long long hb[2];
     HTRY2(hipMemcpy(hcounts.data(), c->counts, sizeof(uint32_t) * (size_t)R, hipMemcpyDeviceToHost));
     HTRY2(hipMemcpy(hfirst.data(), first, sizeof(uint32_t) * (size_t)R, hipMemcpyDeviceToHost));
-    HTRY2(hipMemcpy(hgfirst.data(), gfirst, sizeof(uint32_t) * (size_t)R, hipMemcpyDeviceToHost));
     HTRY2(hipMemcpy(hb, boundaries, sizeof(hb), hipMemcpyDeviceToHost));
     cleanup_tmp();
+    if (c->grouped)
+        for (int32_t r = 0; r < R; ++r) hgfirst[hgroup[r]] = std::min(hgfirst[hgroup[r]], hfirst[r]);
     int64_t nonempty = 0;
     for (int32_t r = 0; r < R; ++r) nonempty += hcounts[r] > 0;
     const bool clusters_contiguous = (int64_t)hb[0] == nonempty - 1;
