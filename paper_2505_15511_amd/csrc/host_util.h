@@ -159,6 +159,12 @@ public:
         if (e == hipSuccess && (e = hipEventRecord(s_.event, st)) == hipSuccess) pending_ = true;
         return e;
     }
+    // the word is written by a kernel that has been enqueued
+    hipError_t record(hipStream_t st) {
+        const hipError_t e = hipEventRecord(s_.event, st);
+        if (e == hipSuccess) pending_ = true;
+        return e;
+    }
     hipError_t wait() { pending_ = false; return hipEventSynchronize(s_.event); }
     unsigned long long value() const { return *s_.word; }
     // for a kernel to write and the host to read once it has waited for the stream: no copy on the way

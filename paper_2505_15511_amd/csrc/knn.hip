@@ -105,19 +105,24 @@ int nearest_in_groups(hipStream_t st, const KnnSets& P, const KnnBlock* blocks, 
 }
 
 // The nearest candidate of every query (one group).  Work space: cand [n_q * 128 / tile], tau, todo, flagged [n_q],
-// counters [2] (queries the filter left open, queries for the exact path), both zero.
-int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* blocks, uint32_t n_blocks, int waves, int32_t* cand, float* tau,
+// counters [2] (queries the filter left open, queries for the exact path), both zero.  few: what the filter leaves open goes to
+// the exact path at once (a launch less; of a few thousand queries a few hundred).  Query positions are query rows here.
+int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* blocks, uint32_t n_blocks, int waves, bool few, int32_t* cand, float* tau,
                 int32_t* todo, int32_t* flagged, uint32_t* counters, int32_t* out) {
-    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, nullptr, tau, KnnAssign{out, todo, counters}));
-    const int32_t width = 128 / tile;
-    const dim3 grid((uint32_t)std::min<int64_t>((P.n_q * width + 255) / 256, kLoopGrid));
-    hipLaunchKernelGGL(k_assign_refine, grid, dim3(256), 0, st, P, (const int32_t*)todo, (const uint32_t*)counters, (const int32_t*)cand, (const float*)tau,
-                       width, out, flagged, counters + 1);
+    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, nullptr, tau, few ? KnnAssign{out, flagged, counters + 1} : KnnAssign{out, todo, counters}));
+    if (!few) {
+        const int32_t width = 128 / tile;
+        const dim3 grid((uint32_t)std::min<int64_t>((P.n_q * width + 255) / 256, kLoopGrid));
+        hipLaunchKernelGGL(k_assign_refine, grid, dim3(256), 0, st, P, (const int32_t*)todo, (const uint32_t*)counters, (const int32_t*)cand, (const float*)tau,
+                           width, out, flagged, counters + 1);
+    }
     hipLaunchKernelGGL((k_knn_exact<1, 256>), dim3((uint32_t)std::min<int64_t>(P.n_q, kLoopGrid)), dim3(256), 0, st, P, (const int32_t*)flagged,
                        (const uint32_t*)(counters + 1), 1, out);
     KTRY(hipGetLastError());
     return NOMAD_OK;
 }
+
+constexpr int32_t kZeroWords = 6;   // counters of an iteration, then the centroids' largest norm
 
 // The M step of Lloyd's iteration: the points sorted by label with a stable radix sort (ascending point order inside a
 // cluster), then float64 sums in that order per (centroid, column); a label without points leaves its centroid as it is.
@@ -130,45 +135,61 @@ struct MeanStep {
     bool parallel = false;          // clusters of 128 points and more on average: column sums in parallel (k_mean_partials)
     uint32_t *lstart = nullptr, *hist = nullptr, *tile_total = nullptr, *list = nullptr;
     MeanPartial* partial = nullptr;
+    int32_t span = 0;               // positions of a partial sum
     uint32_t n_tiles = 0;           // tiles of the scan over the 256 n_blocks digit counters
     int32_t *keys[2] = {nullptr, nullptr}, *ids[2] = {nullptr, nullptr};   // a pass reads one pair of arrays and writes the other
     const int32_t *sorted_keys = nullptr, *sorted_ids = nullptr;
 
+    bool small = false;             // everything in one launch (k_mean_small)
+
     int init(Buffers& buf, int64_t n_, int32_t K_, int32_t d_) {
         n = n_; K = K_; d = d_;
+        small = n <= kSmallMeanPoints && n * K <= ((int64_t)1 << 25);   // (every workgroup reads all labels)
+        if (small) return NOMAD_OK;
         int bits = 1;
         while (((int64_t)1 << bits) < K) ++bits;
         passes = (bits + 7) / 8;
         n_blocks = blocks_of(n, kSortSpan);
         parallel = n >= (int64_t)128 * K;
+        span = mean_span(n);
         KTRY(buf.alloc(&lstart, (size_t)K + 1));
         n_tiles = (uint32_t)(((size_t)256 * n_blocks + kScanTile - 1) / kScanTile);
         KTRY(buf.alloc(&hist, (size_t)256 * n_blocks));
         KTRY(buf.alloc(&tile_total, (size_t)n_tiles));
         for (int x = 0; x < (passes > 1 ? 2 : 1); ++x) { KTRY(buf.alloc(&keys[x], (size_t)n)); KTRY(buf.alloc(&ids[x], (size_t)n)); }
         if (parallel) {
-            KTRY(buf.alloc(&partial, ((size_t)blocks_of(n, kMeanSpan) + (size_t)K) * d));
+            KTRY(buf.alloc(&partial, ((size_t)blocks_of(n, span) + (size_t)K) * d));
             KTRY(buf.alloc(&list, (size_t)K * d));
         }
         return NOMAD_OK;
     }
-    // labels [n] in 0..K-1 (on the device)
-    void sort(hipStream_t st, const int32_t* labels) {
+    // labels [n] in 0..K-1 (on the device); with prev the labels that differ are counted (*changed: zero) and handed to `host`
+    int sort(hipStream_t st, const int32_t* labels, const int32_t* prev = nullptr, unsigned long long* changed = nullptr, HostWord* host = nullptr) {
         const int32_t* kin = labels;
         const int32_t* vin = nullptr;   // first pass: the point at position i is i
         int out = 0;
         for (int p = 0; p < passes; ++p) {
-            hipLaunchKernelGGL(k_sort_count, dim3(n_blocks), dim3(256), 0, st, kin, n, 8 * p, n_blocks, hist);
+            const bool report = p == 0 && prev;
+            hipLaunchKernelGGL(k_sort_count, dim3(n_blocks), dim3(256), 0, st, kin, n, 8 * p, n_blocks, hist,
+                               report ? prev : (const int32_t*)nullptr, changed, report ? host->word() : (unsigned long long*)nullptr);
+            if (report) KTRY(host->record(st));
             hipLaunchKernelGGL(k_sort_scan_tiles, dim3(n_tiles), dim3(256), 0, st, hist, (uint64_t)256 * n_blocks, tile_total);
             hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, st, tile_total, (uint64_t)n_tiles);
             hipLaunchKernelGGL(k_sort_scatter, dim3(n_blocks), dim3(256), 0, st, kin, vin, n, 8 * p, n_blocks, (const uint32_t*)hist,
-                               (const uint32_t*)tile_total, keys[out], ids[out]);
+                               (const uint32_t*)tile_total, keys[out], ids[out], K, passes == 1 ? lstart : (uint32_t*)nullptr);
             kin = keys[out]; vin = ids[out];
             out ^= 1;
         }
         sorted_keys = kin;
         sorted_ids = vin;
-        hipLaunchKernelGGL(k_label_starts, dim3(blocks_of(n + 1, 256)), dim3(256), 0, st, sorted_keys, n, K, lstart);
+        if (passes > 1) hipLaunchKernelGGL(k_label_starts, dim3(blocks_of(n + 1, 256)), dim3(256), 0, st, sorted_keys, n, K, lstart);
+        return NOMAD_OK;
+    }
+    // small sets: dC [K * d] in and out, and the labels that differ from prev's; *changed: zero
+    int small_means(hipStream_t st, const float* dX, const int32_t* labels, const int32_t* prev, float* dC, unsigned long long* changed, unsigned long long* changed_host) {
+        hipLaunchKernelGGL(k_mean_small, dim3((uint32_t)K, blocks_of(d, 64)), dim3(256), sizeof(uint16_t) * (size_t)n, st, dX, (int32_t)n, d, labels, prev, dC, changed, changed_host);
+        KTRY(hipGetLastError());
+        return NOMAD_OK;
     }
     // after sort: dC [K * d] in and out; *n_list is zero
     int means(hipStream_t st, const float* dX, float* dC, uint32_t* n_list) {
@@ -177,13 +198,13 @@ struct MeanStep {
             hipLaunchKernelGGL(k_kmeans_update, dim3(entries), dim3(256), 0, st, dX, d, sorted_ids, (const uint32_t*)lstart, K, dC);
         } else {
             const auto sums = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(blocks_of(n, kMeanSpan)), dim3(256), 0, st, dX, n, d, sorted_keys, sorted_ids, (const uint32_t*)lstart, partial);
+                hipLaunchKernelGGL(kernel, dim3(blocks_of(n, span)), dim3(256), 0, st, dX, n, d, sorted_keys, sorted_ids, (const uint32_t*)lstart, span, partial);
             };
             // columns per lane: no lane idle before 16-byte loads, as far as rows are aligned for them
             if (d > 128 && rows_by_16(dX, d)) sums(k_mean_partials<4>);
             else if (d % 2 == 0 && d > 64 && ((uintptr_t)dX & 7) == 0) sums(k_mean_partials<2>);
             else sums(k_mean_partials<1>);
-            hipLaunchKernelGGL(k_mean_combine, dim3(entries), dim3(256), 0, st, (const MeanPartial*)partial, d, (const uint32_t*)lstart, K, dC, list, n_list);
+            hipLaunchKernelGGL(k_mean_combine, dim3(entries), dim3(256), 0, st, (const MeanPartial*)partial, d, (const uint32_t*)lstart, K, span, dC, list, n_list);
             hipLaunchKernelGGL(k_mean_ordered, dim3((uint32_t)std::min<int64_t>(2048, (int64_t)K * d)), dim3(256), 0, st, dX, d, sorted_ids,
                                (const uint32_t*)lstart, (const uint32_t*)list, (const uint32_t*)n_list, dC);
         }
@@ -246,10 +267,11 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     KTRY(hipMemcpyAsync(hcounts.data(), counts, sizeof(uint32_t) * hcounts.size(), hipMemcpyDeviceToHost, st));
     KTRY(hipStreamSynchronize(st));
     if (hcounts[(size_t)3 * R]) return NOMAD_E_BAD_GRAPH;   // a cluster id outside 0..n_clusters-1
+    const int32_t slab_rows = centroid_rows(n);
     std::vector<KnnBlock> hslabs;
     for (int32_t r = 0; r < R; ++r) {
         hstart[r + 1] = hstart[r] + hcounts[r];
-        for (uint32_t q0 = 0; q0 < hcounts[r]; q0 += kCentroidRows) hslabs.push_back(KnnBlock{r, (int32_t)q0});
+        for (uint32_t q0 = 0; q0 < hcounts[r]; q0 += (uint32_t)slab_rows) hslabs.push_back(KnnBlock{r, (int32_t)q0});
     }
     PackedSide side;
     side.plan(hstart, d, list_len);
@@ -264,7 +286,7 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     side.d_tstart = up.at<uint32_t>(at_tstart);
     if (int rc = side.alloc(buf, true)) return rc;
     hipLaunchKernelGGL(k_knn_group, dim3(blocks_of(n, kGroupSpan)), dim3(256), 0, st, dC, n, R, start, cursor, members);
-    hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, members, start, slabs, centre);
+    hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, members, start, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of((int64_t)R * d, 256)), dim3(256), 0, st, centre, start, R, d);
     hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, dX, n, d, dC, centre, norm, max_norm);
     side.fill(st, dX, d, members, centre, max_norm, max_norm, norm);
@@ -320,18 +342,19 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     PackedSide points, cents;
     points.plan(hq, d, 1);
     cents.plan(hc, d, 1);
-    KTRY(buf.alloc(&max_pts, 1)); KTRY(buf.alloc(&zeros, 6));
+    KTRY(buf.alloc(&max_pts, 1)); KTRY(buf.alloc(&zeros, kZeroWords));
     KTRY(buf.alloc(&new_lab, (size_t)n)); KTRY(buf.alloc(&cand, (size_t)n * (128 / points.tile))); KTRY(buf.alloc(&todo, (size_t)n)); KTRY(buf.alloc(&flagged, (size_t)n));
     KTRY(buf.alloc(&cnorm, (size_t)K)); KTRY(buf.alloc(&tau, (size_t)n)); KTRY(buf.alloc(&centre, (size_t)d)); KTRY(buf.alloc(&c_used, (size_t)K * d));
     KTRY(buf.alloc(&inertia, 1));
-    // what every iteration starts from zero: labels changed (two words), the filter's and the exact path's queries, columns to
-    // add in order, the largest centred |c|^2
-    unsigned long long* changed = (unsigned long long*)zeros;
+    // what every iteration starts from zero: labels changed, the filter's and the exact path's
+    // queries, columns to add in order; and the largest centred |c|^2
+    unsigned long long* changed = (unsigned long long*)zeros;   // (and the workgroups that have counted theirs)
     uint32_t *counters = zeros + 2, *n_list = zeros + 4, *max_cen = zeros + 5;
     const int waves = knn_filter_waves(points.tile, points.n_tiles);
     const std::vector<KnnBlock> hblocks = filter_blocks(points, cents, waves);
+    const int32_t slab_rows = centroid_rows(n);
     std::vector<KnnBlock> hslabs;
-    for (int64_t q0 = 0; q0 < n; q0 += kCentroidRows) hslabs.push_back(KnnBlock{0, (int32_t)q0});
+    for (int64_t q0 = 0; q0 < n; q0 += slab_rows) hslabs.push_back(KnnBlock{0, (int32_t)q0});
     HostArrays up;
     const size_t at_q = up.add(hq), at_c = up.add(hc), at_qt = up.add(points.tstart), at_ct = up.add(cents.tstart), at_blocks = up.add(hblocks),
                  at_slabs = up.add(hslabs);
@@ -345,7 +368,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     // both sides are centred on the mean of the points; the largest centred |x|^2 of the points, once
     KTRY(hipMemsetAsync(centre, 0, sizeof(float) * (size_t)d, st));
     KTRY(hipMemsetAsync(max_pts, 0, sizeof(uint32_t), st));
-    hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, (const int32_t*)nullptr, qstart, slabs, centre);
+    hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, (const int32_t*)nullptr, qstart, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(d, 256)), dim3(256), 0, st, centre, qstart, 1, d);
     hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, dX, n, d, (const int32_t*)nullptr, centre, (float*)nullptr, max_pts);
     points.fill(st, dX, d, nullptr, centre, max_pts, nullptr, nullptr);
@@ -360,30 +383,47 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     P.Q = points.view(max_pts); P.C = cents.view(max_cen); P.centre = centre; P.group_of_q = nullptr; P.n_q = n; P.n_c = K; P.d = d; P.same_set = 0;
     // Labels go back and forth between two arrays; the centroids of the last E step are kept for the inertia.
     int32_t *cur = new_lab, *prev = dLab;
-    HostWord hchanged;
-    KTRY(hchanged.take());
+    HostWord hchanged[2];
+    for (auto& h : hchanged) KTRY(h.take());
+    const bool prepare = (int64_t)K * d <= kPrepareValues;
     int32_t it = 0;
     while (it < max_iters) {
         // E step: the nearest centroid of every point, exactly
-        KTRY(hipMemsetAsync(zeros, 0, 6 * sizeof(uint32_t), st));
-        hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(K, kNormRows)), dim3(256), 0, st, (const float*)dC, (int64_t)K, d, (const int32_t*)nullptr, centre, cnorm,
-                           max_cen);
-        cents.fill(st, dC, d, nullptr, centre, max_cen, max_pts, cnorm);
-        int rc = nearest_one(st, P, points.tile, blocks, (uint32_t)hblocks.size(), waves, cand, tau, todo, flagged, counters, cur);
+        if (prepare) {
+            hipLaunchKernelGGL(k_kmeans_prepare, dim3(cents.n_tiles), dim3(1024), 0, st, (const float*)dC, K, d, (const float*)centre, (const uint32_t*)max_pts,
+                               cents.tile, cents.steps, cents.data, cents.norm, c_used, zeros, kZeroWords - 1, max_cen);
+        } else {
+            KTRY(hipMemsetAsync(zeros, 0, kZeroWords * sizeof(uint32_t), st));
+            hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(K, kNormRows)), dim3(256), 0, st, (const float*)dC, (int64_t)K, d, (const int32_t*)nullptr, centre, cnorm,
+                               max_cen);
+            cents.fill(st, dC, d, nullptr, centre, max_cen, max_pts, cnorm);
+            KTRY(hipMemcpyAsync(c_used, dC, sizeof(float) * (size_t)K * d, hipMemcpyDeviceToDevice, st));
+        }
+        int rc = nearest_one(st, P, points.tile, blocks, (uint32_t)hblocks.size(), waves, m_step.small, cand, tau, todo, flagged, counters, cur);
         if (rc) return rc;
         ++it;
-        KTRY(hipMemcpyAsync(c_used, dC, sizeof(float) * (size_t)K * d, hipMemcpyDeviceToDevice, st));
-        if (it > 1) {
-            hipLaunchKernelGGL(k_kmeans_changed, dim3(std::min<uint32_t>(512, blocks_of(n, 256))), dim3(256), 0, st, (const int32_t*)cur, (const int32_t*)prev, n, changed);
-            KTRY(hchanged.copy_from(changed, st));
+        const int32_t* before = it > 1 ? prev : nullptr;
+        if (m_step.small) {
+            // The host runs an iteration ahead: what it has enqueued by the time it learns that nothing moved gives the same centroids
+            // and labels again.
+            HostWord& h = hchanged[it & 1];
+            if ((rc = m_step.small_means(st, dX, cur, before, dC, changed, before ? h.word() : nullptr))) return rc;
+            if (before) KTRY(h.record(st));
+            std::swap(cur, prev);
+            if (it > 2) {
+                HostWord& last = hchanged[(it - 1) & 1];
+                KTRY(last.wait());
+                if (last.value() == 0) { --it; break; }
+            }
+        } else {
+            if ((rc = m_step.sort(st, cur, before, changed, &hchanged[0]))) return rc;
+            if (before) {   // the device sorts while the host waits for the count; wasted only once, when nothing has changed
+                KTRY(hchanged[0].wait());
+                if (hchanged[0].value() == 0) break;   // nothing moved: the centroids are the means of these labels already
+            }
+            if ((rc = m_step.means(st, dX, dC, n_list))) return rc;
+            std::swap(cur, prev);
         }
-        m_step.sort(st, cur);   // the device sorts while the host waits for the count; wasted only once, when nothing has changed
-        if (it > 1) {
-            KTRY(hchanged.wait());
-            if (hchanged.value() == 0) break;   // nothing moved: the centroids are the means of these labels already
-        }
-        if ((rc = m_step.means(st, dX, dC, n_list))) return rc;
-        std::swap(cur, prev);
     }
     // (prev holds the last labels: after a break the two arrays are equal)
     if (prev != dLab) KTRY(hipMemcpyAsync(dLab, prev, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, st));
@@ -442,7 +482,10 @@ extern "C" int nomad_kmeans_lsh_init(const float* X, int64_t n, int32_t d, int32
     if (!anchors) {   // every plane through the median of a sample along its normal
         int32_t* a = nullptr;
         KTRY(buf.alloc(&a, (size_t)n_planes));
-        hipLaunchKernelGGL(k_lsh_median_anchors, dim3((uint32_t)n_planes), dim3(kLshSample), 0, st, dX, n, d, dP, a);
+        double* proj = nullptr;
+        KTRY(buf.alloc(&proj, (size_t)n_planes * kLshSample));
+        hipLaunchKernelGGL(k_lsh_projections, dim3((uint32_t)n_planes, kLshSample / 64), dim3(64), 0, st, dX, n, d, dP, proj);
+        hipLaunchKernelGGL(k_lsh_median_anchors, dim3((uint32_t)n_planes), dim3(kLshSample), 0, st, (const double*)proj, n, a);
         dA = a;
     }
     if (!dB || mem == NOMAD_HOST) {
@@ -473,8 +516,9 @@ extern "C" int nomad_kmeans_lsh_init(const float* X, int64_t n, int32_t d, int32
         uint32_t* n_list = nullptr;
         KTRY(buf.alloc(&n_list, 1));
         KTRY(hipMemsetAsync(n_list, 0, sizeof(uint32_t), st));
-        m_step.sort(st, (const int32_t*)dB);
-        int rc = m_step.means(st, dX, dC, n_list);
+        int rc = m_step.small ? NOMAD_OK : m_step.sort(st, (const int32_t*)dB);
+        if (rc) return rc;
+        rc = m_step.small ? m_step.small_means(st, dX, (const int32_t*)dB, nullptr, dC, nullptr, nullptr) : m_step.means(st, dX, dC, n_list);
         if (rc) return rc;
     }
     KTRY(hipGetLastError());
@@ -519,13 +563,14 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     KTRY(buf.alloc(&cnorm, (size_t)n)); KTRY(buf.alloc(&AQ, (size_t)mq * d));
     KTRY(buf.alloc(&self, (size_t)mq));
     std::vector<uint32_t> hq((size_t)G + 1), hc((size_t)G + 1);
+    const int32_t slab_rows = centroid_rows(n);
     std::vector<KnnBlock> hslabs;
     for (int64_t g = 0; g <= G; ++g) {
         hq[g] = (uint32_t)(g * m);
         hc[g] = (uint32_t)std::min<int64_t>(n, g * slice);
     }
     for (int64_t g = 0; g < G; ++g)
-        for (int64_t q0 = 0; q0 < (int64_t)(hc[g + 1] - hc[g]); q0 += kCentroidRows) hslabs.push_back(KnnBlock{(int32_t)g, (int32_t)q0});
+        for (int64_t q0 = 0; q0 < (int64_t)(hc[g + 1] - hc[g]); q0 += slab_rows) hslabs.push_back(KnnBlock{(int32_t)g, (int32_t)q0});
     PackedSide qside, cside;
     qside.plan(hq, d, list_len);
     cside.plan(hc, d, list_len);
@@ -554,7 +599,7 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     KTRY(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st));
     KTRY(hipStreamSynchronize(st));
     if (hbad) return NOMAD_E_INVALID_ARG;   // a query outside 0..n-1
-    hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, A, d, (const int32_t*)nullptr, cstart, slabs, centre);
+    hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, A, d, (const int32_t*)nullptr, cstart, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(G * d, 256)), dim3(256), 0, st, centre, cstart, (int32_t)G, d);
     hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, A, n, d, (const int32_t*)slice_of, centre, cnorm, max_c);
     hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(mq, kNormRows)), dim3(256), 0, st, (const float*)AQ, mq, d, (const int32_t*)group_of_q, centre,

@@ -22,14 +22,19 @@ namespace nomad_knn {
 
 // Distances do not change when a cluster is moved as a whole, and the float32 error of the filter grows with |x|^2:
 // the filter therefore works on rows centred on their cluster, x' = fl(x - c_r), c_r = the cluster's mean in float32.
-// Column sums of a cluster, a slab of rows per block, one thread per column:
-constexpr int kCentroidRows = 1024;
+// Column sums of a cluster, a slab of rows per block, one thread per column.  Slabs are cut so that there are a few for every
+// compute unit (3,001 x 50: three slabs of 1,024 rows took 38 us; 100,003 x 768: 98 of them 191 us), 32 to 1,024 rows.
+inline int32_t centroid_rows(int64_t n) {
+    int32_t rows = 32;
+    while (rows < 1024 && n / rows > 1024) rows *= 2;
+    return rows;
+}
 __global__ void __launch_bounds__(256) k_knn_centroid_sums(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ members,
                                                            const uint32_t* __restrict__ start, const KnnBlock* __restrict__ slabs,
-                                                           float* __restrict__ centre) {
-    const KnnBlock sl = slabs[blockIdx.x];   // rows q0 .. q0 + kCentroidRows of cluster sl.cluster
+                                                           int32_t rows, float* __restrict__ centre) {
+    const KnnBlock sl = slabs[blockIdx.x];   // rows q0 .. q0 + rows of cluster sl.cluster
     const uint32_t c0 = start[sl.cluster], c1 = start[sl.cluster + 1];
-    const uint32_t r0 = c0 + (uint32_t)sl.q0, r1 = min(c1, r0 + (uint32_t)kCentroidRows);
+    const uint32_t r0 = c0 + (uint32_t)sl.q0, r1 = min(c1, r0 + (uint32_t)rows);
     for (int col = threadIdx.x; col < d; col += 256) {
         float s = 0.f;
         uint32_t r = r0;
@@ -168,25 +173,13 @@ __global__ void __launch_bounds__(256) k_knn_group(const int32_t* __restrict__ c
 }
 
 // ---------------------------------------------------------------- stage 0: rows for the matrix cores
-// Packs the rows of a set: one workgroup per tile; a thread takes eight columns of one row at a time (adjacent threads
-// adjacent rows: 16-byte stores side by side, the rows' lines shared inside the workgroup).
-__global__ void __launch_bounds__(256) k_knn_pack(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ members,
-                                                  const uint32_t* __restrict__ start, const uint32_t* __restrict__ tstart, int32_t groups,
-                                                  const float* __restrict__ centre, const uint32_t* __restrict__ max_bits,
-                                                  const uint32_t* __restrict__ other_bits, const float* __restrict__ row_norm, int32_t tile, int32_t steps, uint4* __restrict__ data,
-                                                  float* __restrict__ norm) {
-    const uint32_t t = blockIdx.x;
-    int32_t g = 0, hi = groups;      // the group of this tile
-    while (hi - g > 1) {
-        const int32_t mid = (g + hi) >> 1;
-        if (tstart[mid] <= t) g = mid; else hi = mid;
-    }
-    const uint32_t r0 = start[g], n_g = start[g + 1] - r0, pos0 = (t - tstart[g]) * (uint32_t)tile;
-    const float scale = ldexpf(1.f, knn_scale_exponent(max_bits[g]));
-    const float* c = centre + (int64_t)g * d;
+// Packs one tile of rows (positions pos0 .. of the n_g that begin at r0): a thread takes eight columns of one row at a time
+// (adjacent threads adjacent rows: 16-byte stores side by side, the rows' lines shared inside the workgroup).  data: the tile's.
+__device__ __forceinline__ void pack_tile(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ members, uint32_t r0, uint32_t n_g, uint32_t pos0,
+                                          const float* __restrict__ c, float scale, int32_t tile, int32_t steps, uint4* __restrict__ data) {
     const int tshift = tile == 32 ? 5 : 4, per_step = 64 >> tshift;   // chunks of eight columns per step
     const bool vec = rows_by_16(X, d);
-    for (int x = threadIdx.x; x < (steps * 64); x += 256) {
+    for (int x = threadIdx.x; x < (steps * 64); x += (int)blockDim.x) {
         const int row = x & (tile - 1), chunk = x >> tshift, col = 8 * chunk;
         const uint32_t pos = pos0 + (uint32_t)row;
         const bool live = pos < n_g;
@@ -211,14 +204,80 @@ __global__ void __launch_bounds__(256) k_knn_pack(const float* __restrict__ X, i
             vl[h] = (_Float16)(y - (float)vh[h]);
         }
         const int step = chunk / per_step, l = ((chunk % per_step) << tshift) + row;
-        uint4* dst = data + ((size_t)t * steps + step) * 128 + l;
+        uint4* dst = data + (size_t)step * 128 + l;
         dst[0] = *(const uint4*)&vh;
         dst[64] = *(const uint4*)&vl;
     }
+}
+
+// the rows of a set, one workgroup per tile
+__global__ void __launch_bounds__(256) k_knn_pack(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ members,
+                                                  const uint32_t* __restrict__ start, const uint32_t* __restrict__ tstart, int32_t groups,
+                                                  const float* __restrict__ centre, const uint32_t* __restrict__ max_bits,
+                                                  const uint32_t* __restrict__ other_bits, const float* __restrict__ row_norm, int32_t tile, int32_t steps, uint4* __restrict__ data,
+                                                  float* __restrict__ norm) {
+    const uint32_t t = blockIdx.x;
+    int32_t g = 0, hi = groups;      // the group of this tile
+    while (hi - g > 1) {
+        const int32_t mid = (g + hi) >> 1;
+        if (tstart[mid] <= t) g = mid; else hi = mid;
+    }
+    const uint32_t r0 = start[g], n_g = start[g + 1] - r0, pos0 = (t - tstart[g]) * (uint32_t)tile;
+    pack_tile(X, d, members, r0, n_g, pos0, centre + (int64_t)g * d, ldexpf(1.f, knn_scale_exponent(max_bits[g])), tile, steps,
+              data + (size_t)t * steps * 128);
     if (norm && threadIdx.x < (uint32_t)tile) {
         const uint32_t pos = pos0 + threadIdx.x;
         const float half_unit = ldexpf(0.5f, knn_scale_exponent(max_bits[g]) + knn_scale_exponent(other_bits[g]));
         norm[(size_t)t * tile + threadIdx.x] = pos < n_g ? row_norm[knn_row(members, r0 + pos)] * half_unit : __builtin_inff();
+    }
+}
+
+// What an E step of Lloyd's iterations starts with, one workgroup per tile of centroids: the words that count from zero, the
+// centroids' norms and the largest of them, the packed tile, and the copy the inertia is computed from.  Every workgroup reads all K rows
+// for the largest norm, so this is for up to kPrepareValues values; beyond, the norms, the packing, the clearing and the copy are
+// launches of their own (four of 3 to 4 us and their gaps; one of 5).
+constexpr int64_t kPrepareValues = 65536;
+__global__ void __launch_bounds__(1024) k_kmeans_prepare(const float* __restrict__ C, int32_t K, int32_t d, const float* __restrict__ centre,
+                                                        const uint32_t* __restrict__ point_bits, int32_t tile, int32_t steps, uint4* __restrict__ data,
+                                                        float* __restrict__ norm, float* __restrict__ c_used, uint32_t* __restrict__ zeros, int32_t n_zeros,
+                                                        uint32_t* __restrict__ max_cen) {
+    __shared__ float own[32];          // |c'|^2 of this tile's rows
+    __shared__ uint32_t largest;
+    const uint32_t pos0 = blockIdx.x * (uint32_t)tile;
+    if (threadIdx.x == 0) largest = 0u;
+    if (threadIdx.x < 32u) own[threadIdx.x] = 0.f;
+    __syncthreads();
+    const int part = threadIdx.x % kNormLanes;
+    uint32_t bits = 0u;
+    for (int32_t r = threadIdx.x / kNormLanes; r < K; r += 1024 / kNormLanes) {
+        float s = 0.f;
+        for (int t = part; t < d; t += 8 * kNormLanes) {   // eight values in flight
+            float x[8], c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) { const int at = min(t + u * kNormLanes, d - 1); x[u] = C[(int64_t)r * d + at]; c[u] = centre[at]; }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float v = t + u * kNormLanes < d ? x[u] - c[u] : 0.f;
+                s = fmaf(v, v, s);
+            }
+        }
+        for (int w = kNormLanes / 2; w > 0; w >>= 1) s += __shfl_xor(s, w, kNormLanes);
+        bits = max(bits, __float_as_uint(s));
+        if (part == 0 && (uint32_t)r >= pos0 && (uint32_t)r < pos0 + (uint32_t)tile) own[(uint32_t)r - pos0] = s;
+    }
+    atomicMax(&largest, bits);
+    __syncthreads();
+    const uint32_t top = largest;
+    pack_tile(C, d, nullptr, 0u, (uint32_t)K, pos0, centre, ldexpf(1.f, knn_scale_exponent(top)), tile, steps, data + (size_t)blockIdx.x * steps * 128);
+    if (threadIdx.x < (uint32_t)tile) {
+        const float half_unit = ldexpf(0.5f, knn_scale_exponent(top) + knn_scale_exponent(point_bits[0]));
+        norm[(size_t)blockIdx.x * tile + threadIdx.x] = pos0 + threadIdx.x < (uint32_t)K ? own[threadIdx.x] * half_unit : __builtin_inff();
+    }
+    const int64_t v0 = (int64_t)pos0 * d, v1 = min((int64_t)K * d, v0 + (int64_t)tile * d);
+    for (int64_t v = v0 + threadIdx.x; v < v1; v += 1024) c_used[v] = C[v];
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < (uint32_t)n_zeros) zeros[threadIdx.x] = 0u;
+        if (threadIdx.x == 0) *max_cen = top;
     }
 }
 
@@ -514,18 +573,36 @@ __global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const in
 // point order.
 constexpr int kSortSpan = 2048;
 
+// One lane of every workgroup adds what the workgroup counted; the last of them hands the sum to the host.  Count and workgroups share
+// a word (sum in the high half), so that one atomic does and nothing has to be fenced (a fence writes the XCD's L2 back: the
+// count of a million labels took 11.5 us with one, 5.4 without).
+__device__ __forceinline__ void report_changed(uint32_t count, uint32_t workgroups, unsigned long long* __restrict__ changed,
+                                               unsigned long long* __restrict__ changed_host) {
+    const unsigned long long before = atomicAdd(changed, ((unsigned long long)count << 32) + 1ull);
+    if ((uint32_t)before + 1u == workgroups) *(volatile unsigned long long*)changed_host = (before >> 32) + count;
+}
+
+// With prev it also counts the keys that differ from prev's; the last workgroup hands the count to the host, which waits for it while the
+// sort goes on.
 __global__ void __launch_bounds__(256) k_sort_count(const int32_t* __restrict__ keys, int64_t n, int shift, uint32_t n_blocks,
-                                                    uint32_t* __restrict__ hist) {   // hist [256][n_blocks]
-    __shared__ uint32_t h[256];
+                                                    uint32_t* __restrict__ hist, const int32_t* __restrict__ prev,   // hist [256][n_blocks]
+                                                    unsigned long long* __restrict__ changed, unsigned long long* __restrict__ changed_host) {
+    __shared__ uint32_t h[256], moved;
     h[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) moved = 0u;
     __syncthreads();
     const int64_t i0 = (int64_t)blockIdx.x * kSortSpan;
     for (int u = 0; u < kSortSpan / 256; ++u) {
         const int64_t i = i0 + u * 256 + threadIdx.x;
         if (i < n) atomicAdd(&h[((uint32_t)keys[i] >> shift) & 255u], 1u);
+        if (prev) {
+            const unsigned long long differ = __ballot(i < n && keys[i] != prev[i]);
+            if (differ && (threadIdx.x & 63) == 0) atomicAdd(&moved, (uint32_t)__popcll(differ));
+        }
     }
     __syncthreads();
     hist[(size_t)threadIdx.x * n_blocks + blockIdx.x] = h[threadIdx.x];
+    if (prev && threadIdx.x == 0) report_changed(moved, gridDim.x, changed, changed_host);
 }
 
 // Exclusive scan of the m counters in two levels: every workgroup scans a tile of kScanTile consecutive counters in
@@ -578,17 +655,21 @@ __global__ void __launch_bounds__(1024) k_sort_scan(uint32_t* __restrict__ hist,
     for (uint64_t x = a; x < b; ++x) { const uint32_t c = hist[x]; hist[x] = run; run += c; }
 }
 
-// vals_in == nullptr: the value of position i is i (first pass)
+// vals_in == nullptr: the value of position i is i (first pass); lstart: see k_label_starts (a single pass only)
 __global__ void __launch_bounds__(256) k_sort_scatter(const int32_t* __restrict__ keys_in, const int32_t* __restrict__ vals_in, int64_t n,
                                                       int shift, uint32_t n_blocks, const uint32_t* __restrict__ first_slot,
                                                       const uint32_t* __restrict__ tile_offset, int32_t* __restrict__ keys_out,
-                                                      int32_t* __restrict__ vals_out) {
+                                                      int32_t* __restrict__ vals_out, int32_t K, uint32_t* __restrict__ lstart) {
     __shared__ uint32_t running[256];       // next output slot of every digit for this workgroup
     __shared__ uint32_t wave_cnt[4][256];   // pairs of the chunk with each digit, per wavefront
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     {
         const size_t x = (size_t)threadIdx.x * n_blocks + blockIdx.x;   // the counters in (digit, workgroup) order
         running[threadIdx.x] = first_slot[x] + tile_offset[x / kScanTile];
+        if (lstart && blockIdx.x == 0) {   // the only pass: a digit's first slot is its label's
+            if ((int32_t)threadIdx.x < K) lstart[threadIdx.x] = running[threadIdx.x];
+            if (threadIdx.x == 0) lstart[K] = (uint32_t)n;
+        }
     }
     const int64_t i0 = (int64_t)blockIdx.x * kSortSpan;
     for (int u = 0; u < kSortSpan / 256; ++u) {
@@ -627,19 +708,6 @@ __global__ void __launch_bounds__(256) k_label_starts(const int32_t* __restrict_
     if (i > n) return;
     const int32_t cur = i < n ? min(keys[i], K) : K, prev = i > 0 ? max(keys[i - 1], -1) : -1;
     for (int32_t j = prev + 1; j <= cur; ++j) lstart[j] = (uint32_t)i;
-}
-
-// how many points changed their cluster (one atomic per workgroup: one per wavefront on this single address took 52 us for a
-// million points)
-__global__ void __launch_bounds__(256) k_kmeans_changed(const int32_t* __restrict__ a, const int32_t* __restrict__ b, int64_t n,
-                                                        unsigned long long* __restrict__ changed) {
-    __shared__ uint32_t part[4];
-    uint32_t count = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) count += a[i] != b[i];
-    for (int w = 32; w > 0; w >>= 1) count += (uint32_t)__shfl_xor((int)count, w, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = count;
-    __syncthreads();
-    if (threadIdx.x == 0 && (count = part[0] + part[1] + part[2] + part[3]) != 0u) atomicAdd(changed, (unsigned long long)count);
 }
 
 // M step: centroid j = float32(sum of its rows / count), the rows added in ascending point order in float64 (ids: the
@@ -689,6 +757,78 @@ __global__ void __launch_bounds__(256) k_kmeans_update(const float* __restrict__
     C[x] = (float)(ordered_column_sum(X, d, ids, r0, r1, col) / (double)(r1 - r0));
 }
 
+// The M step of a small set in one launch, a workgroup per centroid and 64 columns: it finds the centroid's points among the labels
+// itself, in order; four wavefronts bring 64 rows to LDS at a time, one adds them, a column a lane.  With prev it also counts the
+// labels that changed; the last workgroup hands the count to the host.  Against the sort, its scans and the sums as launches of their
+// own: eight for one.
+constexpr int64_t kSmallMeanPoints = 16384;
+__global__ void __launch_bounds__(256) k_mean_small(const float* __restrict__ X, int32_t n, int32_t d, const int32_t* __restrict__ labels, const int32_t* __restrict__ prev,
+                                                    float* __restrict__ C, unsigned long long* __restrict__ changed, unsigned long long* __restrict__ changed_host) {
+    extern __shared__ uint16_t ids[];   // [n] the points of this centroid, ascending
+    constexpr int V = 64;               // rows of a stage
+    __shared__ float stage[2][V][64];
+    __shared__ uint32_t wave_count[4], n_changed;
+    const int32_t j = (int32_t)blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int U = 8;                // consecutive labels of a lane
+    if (threadIdx.x == 0) n_changed = 0u;
+    uint32_t m = 0, moved = 0;
+    for (int32_t i0 = 0; i0 < n; i0 += 256 * U) {
+        const int32_t first = i0 + (int32_t)threadIdx.x * U;
+        uint32_t mine = 0;              // a bit per label that is j
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t i = min(first + u, n - 1);
+            const bool is = first + u < n && labels[i] == j;
+            mine |= is ? 1u << u : 0u;
+            if (prev) moved += is && prev[i] != j ? 1u : 0u;
+        }
+        uint32_t incl = (uint32_t)__popc(mine);
+        const uint32_t own = incl;
+#pragma unroll
+        for (int dlt = 1; dlt < 64; dlt <<= 1) {
+            const uint32_t up = __shfl_up(incl, dlt, 64);
+            if (lane >= dlt) incl += up;
+        }
+        if (lane == 63) wave_count[wave] = incl;
+        __syncthreads();
+        uint32_t at = m + incl - own;
+        for (int w = 0; w < wave; ++w) at += wave_count[w];
+        for (; mine; mine &= mine - 1u) ids[at++] = (uint16_t)(first + __ffs((int)mine) - 1);
+        m += wave_count[0] + wave_count[1] + wave_count[2] + wave_count[3];
+        __syncthreads();
+    }
+    if (moved && blockIdx.y == 0) atomicAdd(&n_changed, moved);
+    if (m) {
+        const int32_t col = (int32_t)blockIdx.y * 64 + lane, c = min(col, d - 1);
+        float v[V / 4];                 // rows wave, wave + 4, ... of the next stage
+        const auto load = [&](uint32_t r0) {   // rows past the end: the last again, not added
+#pragma unroll
+            for (int u = 0; u < V / 4; ++u) v[u] = X[(int64_t)ids[min(r0 + 4u * u + (uint32_t)wave, m - 1u)] * d + c];
+        };
+        load(0u);
+        double sum = 0.0;
+        for (uint32_t r0 = 0, buf = 0; r0 < m; r0 += V, buf ^= 1u) {
+#pragma unroll
+            for (int u = 0; u < V / 4; ++u) stage[buf][4 * u + wave][lane] = v[u];
+            if (r0 + V < m) load(r0 + V);
+            __syncthreads();            // (a stage is written again only after the barrier of the one between)
+            if (wave == 0) {
+                if (r0 + V <= m) {
+#pragma unroll
+                    for (int u = 0; u < V; ++u) sum = __dadd_rn(sum, (double)stage[buf][u][lane]);
+                } else {
+                    for (uint32_t u = 0; r0 + u < m; ++u) sum = __dadd_rn(sum, (double)stage[buf][u][lane]);
+                }
+            }
+        }
+        if (wave == 0 && col < d) C[(int64_t)j * d + col] = (float)(sum / (double)m);
+    }
+    if (!changed_host) return;
+    __syncthreads();
+    if (threadIdx.x == 0) report_changed(n_changed, gridDim.x * gridDim.y, changed, changed_host);
+}
+
 // Large clusters.  A chain of thousands of ordered additions per thread leaves most of the chip idle (a million points in
 // 256 clusters: 0.33 ms for 512 MB; in parallel 0.11 ms, the card's copy rate).  The centroid is the sum rounded to float32,
 // and the 29 bits less hide the order in nearly every case: every addition errs by at most 2^-53 of its result, so from
@@ -696,18 +836,20 @@ __global__ void __launch_bounds__(256) k_kmeans_update(const float* __restrict__
 // round to the same float32, that is the centroid.  The few columns whose interval straddles a rounding boundary (or is not
 // finite) are put on a list and added in order.
 //
-// k_mean_partials: a workgroup takes kMeanSpan positions of the sorted order; the part of span b that lies in cluster j is
+// k_mean_partials: a workgroup takes `span` positions of the sorted order; the part of span b that lies in cluster j is
 // partial number b + j (b + j grows along the order, so the numbers are distinct and below spans + K).
+// (512 positions, fewer where that leaves compute units idle: 100,003 x 768, 196 spans of 512 98 us)
 constexpr int kMeanSpan = 512;
+inline int32_t mean_span(int64_t n) { return n >= 512 * 1024 ? kMeanSpan : n >= 256 * 512 ? 256 : 128; }
 struct MeanPartial { double sum; double magnitude; };
 
 template <int VEC>
 __global__ void __launch_bounds__(256) k_mean_partials(const float* __restrict__ X, int64_t n, int32_t d, const int32_t* __restrict__ keys,
-                                                       const int32_t* __restrict__ ids, const uint32_t* __restrict__ lstart,
+                                                       const int32_t* __restrict__ ids, const uint32_t* __restrict__ lstart, int32_t span,
                                                        MeanPartial* __restrict__ partial) {
     __shared__ double s_sum[4][64 * VEC], s_mag[4][64 * VEC];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t b0 = blockIdx.x * (uint32_t)kMeanSpan, b1 = (uint32_t)min(n, (int64_t)b0 + kMeanSpan);
+    const uint32_t b0 = blockIdx.x * (uint32_t)span, b1 = (uint32_t)min(n, (int64_t)b0 + span);
     for (uint32_t r0 = b0; r0 < b1;) {
         const int32_t j = __builtin_amdgcn_readfirstlane(keys[r0]);
         const uint32_t r1 = min(b1, (uint32_t)__builtin_amdgcn_readfirstlane((int)lstart[j + 1]));
@@ -755,8 +897,8 @@ __global__ void __launch_bounds__(256) k_mean_partials(const float* __restrict__
 // The partials of every (cluster, column); columns whose float32 the order could change go on the list (*n_list of them).
 // With P_b the sum of the spans before b, m_b, M_b the rows and magnitudes of span b and u = 2^-53: a partial sum of the
 // ordered addition inside span b is at most |P_b| + M_b (+ what the earlier roundings moved, below 2 m u M), so it errs by
-// at most u sum_b m_b (|P_b| + M_b + 2 m u M); the parallel sum by u (kMeanSpan / 4 + 4) M inside the spans and u |P_b| at each join.
-__global__ void __launch_bounds__(256) k_mean_combine(const MeanPartial* __restrict__ partial, int32_t d, const uint32_t* __restrict__ lstart, int32_t K,
+// at most u sum_b m_b (|P_b| + M_b + 2 m u M); the parallel sum by u (span / 4 + 4) M inside the spans and u |P_b| at each join.
+__global__ void __launch_bounds__(256) k_mean_combine(const MeanPartial* __restrict__ partial, int32_t d, const uint32_t* __restrict__ lstart, int32_t K, int32_t span,
                                                       float* __restrict__ C, uint32_t* __restrict__ list, uint32_t* __restrict__ n_list) {
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= (int64_t)K * d) return;
@@ -764,22 +906,22 @@ __global__ void __launch_bounds__(256) k_mean_combine(const MeanPartial* __restr
     const uint32_t r0 = lstart[j], r1 = lstart[j + 1];
     if (r1 == r0) return;
     double sum = 0.0, mag = 0.0, ordered = 0.0, joins = 0.0;
-    const uint32_t b1 = (r1 - 1) / kMeanSpan;
-    for (uint32_t b = r0 / kMeanSpan; b <= b1; b += 8) {
+    const uint32_t b1 = (r1 - 1) / span;
+    for (uint32_t b = r0 / span; b <= b1; b += 8) {
         MeanPartial p[8];   // eight loads in flight
 #pragma unroll
         for (uint32_t u = 0; u < 8; ++u) p[u] = partial[((size_t)min(b + u, b1) + (size_t)j) * d + col];
 #pragma unroll
         for (uint32_t u = 0; u < 8; ++u)
             if (b + u <= b1) {
-                const uint32_t rows = min(r1, (b + u + 1) * kMeanSpan) - max(r0, (b + u) * kMeanSpan);
+                const uint32_t rows = min(r1, (b + u + 1) * span) - max(r0, (b + u) * span);
                 ordered += (double)rows * (fabs(sum) + p[u].magnitude);
                 sum += p[u].sum;
                 mag += p[u].magnitude;
                 joins += fabs(sum);
             }
     }
-    const double m = (double)(r1 - r0), err = 0x1p-53 * 1.02 * (ordered + joins + mag * (kMeanSpan / 4 + 4 + 2.0 * m * (m * 0x1p-53)));
+    const double m = (double)(r1 - r0), err = 0x1p-53 * 1.02 * (ordered + joins + mag * (span / 4 + 4 + 2.0 * m * (m * 0x1p-53)));
     const float lo = (float)((sum - err) / m), hi = (float)((sum + err) / m);
     if (lo == hi && mag < 0x1p1000) C[x] = (float)(sum / m);
     else list[atomicAdd(n_list, 1u)] = (uint32_t)x;
@@ -913,43 +1055,65 @@ __global__ void __launch_bounds__(256) k_lsh_buckets(const float* __restrict__ X
 // Anchors the caller did not draw: plane j goes through the median of a strided sample along its normal.  The sample is the
 // m = min(kLshSample, n) points floor(s n / m); projection = sum_t h_{j,t} x_t over t = 0..d-1 in order (product and
 // running sum each rounded once in float64); the anchor is the sample point of rank floor(m / 2) in ascending
-// (projection, point).  One workgroup per plane, a sample point per thread, ranks by counting.
+// (projection, point).  A wavefront takes 64 of the projections of a plane (k_lsh_projections), a workgroup per plane the median, from a
+// bitonic sort.  (One workgroup per plane for both, every thread counting its rank among 1,024: 59 us at 128 columns and 136 at
+// 768; now 23 and 39.)
 constexpr int kLshSample = 1024;
-__global__ void __launch_bounds__(kLshSample) k_lsh_median_anchors(const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ planes,
-                                                            int32_t* __restrict__ anchors) {
-    __shared__ double sproj[kLshSample];
-    const int j = blockIdx.x;
+__global__ void __launch_bounds__(64) k_lsh_projections(const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ planes, double* __restrict__ proj) {
+    const int j = blockIdx.x, s = (int)blockIdx.y * 64 + (int)threadIdx.x;
     const int m = (int)min((int64_t)kLshSample, n);
     const float* h = planes + (int64_t)j * d;
-    const int s = threadIdx.x;
+    const float* x = X + (((int64_t)min(s, m - 1) * n) / m) * d;
     double p = 0.0;
-    if (s < m) {
-        const float* x = X + (((int64_t)s * n) / m) * d;
-        int t = 0;
-        if (rows_by_16(X, d)) {
-            for (; t + 32 <= d; t += 32) {   // eight 16-byte loads in flight, added one by one in order
-                float4 v[8];
+    int t = 0;
+    if (rows_by_16(X, d)) {
+        for (; t + 32 <= d; t += 32) {   // eight 16-byte loads in flight, added one by one in order
+            float4 v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(x + t + 4 * u);
+            for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(x + t + 4 * u);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u], (double)v[u].x));
-                    p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u + 1], (double)v[u].y));
-                    p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u + 2], (double)v[u].z));
-                    p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u + 3], (double)v[u].w));
+            for (int u = 0; u < 8; ++u) {
+                p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u], (double)v[u].x));
+                p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u + 1], (double)v[u].y));
+                p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u + 2], (double)v[u].z));
+                p = __dadd_rn(p, __dmul_rn((double)h[t + 4 * u + 3], (double)v[u].w));
+            }
+        }
+    }
+    for (; t + 16 <= d; t += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = x[t + u];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) p = __dadd_rn(p, __dmul_rn((double)h[t + u], (double)v[u]));
+    }
+    for (; t < d; ++t) p = __dadd_rn(p, __dmul_rn((double)h[t], (double)x[t]));
+    if (!(p == p)) p = __builtin_inf();   // no number: last in the order, so that one point has the median's rank
+    proj[(size_t)j * kLshSample + s] = s < m ? p : __builtin_inf();
+}
+
+__global__ void __launch_bounds__(kLshSample) k_lsh_median_anchors(const double* __restrict__ proj, int64_t n, int32_t* __restrict__ anchors) {
+    __shared__ double sproj[kLshSample];
+    __shared__ uint16_t sidx[kLshSample];
+    const int j = blockIdx.x, s = threadIdx.x;
+    const int m = (int)min((int64_t)kLshSample, n);
+    sproj[s] = proj[(size_t)j * kLshSample + s];
+    // ascending in (projection, sample); sample points are in ascending index order, the places past them come last
+    sidx[s] = (uint16_t)s;
+    for (int size = 2; size <= kLshSample; size <<= 1)
+        for (int dist = size >> 1; dist > 0; dist >>= 1) {
+            __syncthreads();
+            const int a = 2 * s - (s & (dist - 1)), b = a + dist;   // pair number s of this step
+            if (s < kLshSample / 2) {
+                const bool up = (a & size) == 0, after = sproj[a] > sproj[b] || (sproj[a] == sproj[b] && sidx[a] > sidx[b]);
+                if (after == up) {
+                    const double t = sproj[a]; sproj[a] = sproj[b]; sproj[b] = t;
+                    const uint16_t u = sidx[a]; sidx[a] = sidx[b]; sidx[b] = u;
                 }
             }
         }
-        for (; t < d; ++t) p = __dadd_rn(p, __dmul_rn((double)h[t], (double)x[t]));
-        if (!(p == p)) p = __builtin_inf();   // no number: last in the order, so that one point has the median's rank
-        sproj[s] = p;
-    }
     __syncthreads();
-    if (s < m) {   // sample points are in ascending index order: ties go to the lower s
-        int rank = 0;
-        for (int o = 0; o < m; ++o) rank += (sproj[o] < p || (sproj[o] == p && o < s)) ? 1 : 0;
-        if (rank == m / 2) anchors[j] = (int32_t)(((int64_t)s * n) / m);
-    }
+    if (s == 0) anchors[j] = (int32_t)(((int64_t)sidx[m / 2] * n) / m);
 }
 
 // centroid j starts as the data point floor(j n / K): what an empty bucket keeps
