@@ -701,7 +701,7 @@ extern "C" int nomad_neighbourhood_preservation(const float* X, int64_t n, int32
 
 namespace {
 
-// One launch covers at most kTripletsPerLaunch triplets (65,536 workgroups), so that any count up to the documented
+// One launch covers at most kTripletsPerLaunch triplets (262,144 workgroups), so that any count up to the documented
 // 2^40 stays inside the grid limits; the launches add into the same counter.
 constexpr int64_t kTripletsPerLaunch = (int64_t)1 << 24;
 
@@ -717,9 +717,10 @@ int check_triplet_arguments(const float* X, int64_t n, int32_t d, const float* Y
 int enqueue_triplets(hipStream_t st, const float* dX, int32_t d, const float* dY, int32_t d_low, int64_t n, int64_t n_triplets,
                      uint64_t seed, unsigned long long* agree) {
     hipLaunchKernelGGL(k_store_u64, dim3(1), dim3(64), 0, st, agree, 0ull);
+    const auto kernel = d >= kStagedColumns ? k_triplets<true> : k_triplets<false>;
     for (int64_t t0 = 0; t0 < n_triplets; t0 += kTripletsPerLaunch) {
         const int64_t t1 = std::min(n_triplets, t0 + kTripletsPerLaunch);
-        hipLaunchKernelGGL(k_triplets, dim3(blocks_of(t1 - t0, 256)), dim3(256), 0, st, dX, d, dY, d_low, (uint32_t)n, t0, t1,
+        hipLaunchKernelGGL(kernel, dim3(blocks_of(t1 - t0, 64)), dim3(64), 0, st, dX, d, dY, d_low, (uint32_t)n, t0, t1,
                            (uint32_t)seed, (uint32_t)(seed >> 32), agree);
     }
     KTRY(hipGetLastError());

@@ -307,32 +307,85 @@ __device__ __forceinline__ void anchor_distances(const float* __restrict__ a, co
     Dac = s2;
 }
 
+// The same with the wavefront's rows read together, for rows of 128 bytes and more: eight lanes take 128 consecutive bytes of one
+// of the 192 rows, 24 such loads a round for the next 32 columns while the present ones go through LDS to the lanes that own
+// them.  A lane that reads its own three rows 16 bytes at a time finds their lines gone from the first cache when it comes to
+// their next bytes: a million triplets of 1,000,000 x 128 took 0.76 ms, now 0.29; the 1.2e7 lines alone are 0.21 at the rate
+// of gathers from memory.  Every lane of the wavefront takes part; i, j, k are rows of X.
+constexpr int32_t kStagedColumns = 32, kStagedPitch = kStagedColumns / 4 + 1;   // (a pitch of nine pieces: no bank conflicts)
+struct StagedRows { float4 piece[3 * 64][kStagedPitch]; };
+__device__ __forceinline__ void staged_distances(StagedRows& lds, const float* __restrict__ X, int32_t d, uint32_t i, uint32_t j, uint32_t k, double& Dij, double& Dik) {
+    const int lane = threadIdx.x & 63, sub = lane & 7, owner = lane >> 3;
+    const bool by16 = rows_by_16(X, d);
+    uint32_t row[24];
+#pragma unroll
+    for (int u = 0; u < 24; ++u) row[u] = (uint32_t)__shfl((int)(u < 8 ? i : u < 16 ? j : k), (u & 7) * 8 + owner, 64);
+    float4 next[24];
+    const auto fetch = [&](int32_t c0) {
+        const int32_t col = c0 + 4 * sub;
+        if (by16) {
+#pragma unroll
+            for (int u = 0; u < 24; ++u) next[u] = col < d ? *(const float4*)(X + (int64_t)row[u] * d + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 24; ++u) {
+                const float* x = X + (int64_t)row[u] * d;
+                next[u] = make_float4(col < d ? x[col] : 0.f, col + 1 < d ? x[col + 1] : 0.f, col + 2 < d ? x[col + 2] : 0.f, col + 3 < d ? x[col + 3] : 0.f);
+            }
+        }
+    };
+    double s1 = 0.0, s2 = 0.0;
+    fetch(0);
+    for (int32_t c0 = 0; c0 < d; c0 += kStagedColumns) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 24; ++u) lds.piece[(u >> 3) * 64 + (u & 7) * 8 + owner][sub] = next[u];
+        __syncthreads();
+        if (c0 + kStagedColumns < d) fetch(c0 + kStagedColumns);
+        // (columns past the last one are zeros in all three rows: they add +0 to sums that are not below it)
+#pragma unroll
+        for (int p = 0; p < kStagedColumns / 4; ++p) {
+            const float4 a = lds.piece[lane][p], b = lds.piece[64 + lane][p], c = lds.piece[128 + lane][p];
+            const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w}, cv[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double e1 = (double)av[u] - (double)bv[u], e2 = (double)av[u] - (double)cv[u];
+                s1 = __dadd_rn(s1, __dmul_rn(e1, e1));
+                s2 = __dadd_rn(s2, __dmul_rn(e2, e2));
+            }
+        }
+    }
+    Dij = s1;
+    Dik = s2;
+}
+
 // Triplet number t (one per thread): anchor i and two other points j, k, all distinct and uniform, from the words of
 // Philox(counter = (lo32 t, hi32 t, stream, 0), key = seed) by multiply-high range reduction over n, n - 1 and n - 2
 // values, stepping over the points already taken.  It agrees when [D_X(i,j) < D_X(i,k)] == [D_Y(i,j) < D_Y(i,k)].
-// A launch covers the triplets t_begin .. t_end-1 and adds its count to *agree.
-__global__ void __launch_bounds__(256) k_triplets(const float* __restrict__ X, int32_t d, const float* __restrict__ Y, int32_t d_low,
-                                                  uint32_t n, int64_t t_begin, int64_t t_end, uint32_t key0, uint32_t key1,
-                                                  unsigned long long* __restrict__ agree) {
+// A launch covers the triplets t_begin .. t_end-1 and adds its count to *agree.  Workgroups of one wavefront.
+template <bool STAGED>
+__global__ void __launch_bounds__(64) k_triplets(const float* __restrict__ X, int32_t d, const float* __restrict__ Y, int32_t d_low,
+                                                 uint32_t n, int64_t t_begin, int64_t t_end, uint32_t key0, uint32_t key1,
+                                                 unsigned long long* __restrict__ agree) {
+    __shared__ uint4 space[STAGED ? sizeof(StagedRows) / 16 : 1];
     const int64_t t = t_begin + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool same = false;
-    if (t < t_end) {
-        uint32_t w[4];
-        philox4x32_10((uint32_t)t, (uint32_t)((uint64_t)t >> 32), kTripletStream, 0u, key0, key1, w);
-        const uint32_t i = __umulhi(w[0], n);
-        uint32_t j = __umulhi(w[1], n - 1u);
-        j += j >= i;
-        uint32_t k = __umulhi(w[2], n - 2u);
-        const uint32_t lo = min(i, j), hi = max(i, j);
-        k += k >= lo;
-        k += k >= hi;
-        double hij, hik, lij, lik;
-        anchor_distances(X + (int64_t)i * d, X + (int64_t)j * d, X + (int64_t)k * d, d, rows_by_16(X, d), hij, hik);
-        anchor_distances(Y + (int64_t)i * d_low, Y + (int64_t)j * d_low, Y + (int64_t)k * d_low, d_low, rows_by_16(Y, d_low), lij, lik);
-        same = (hij < hik) == (lij < lik);
-    }
+    // (lanes past the end draw a triplet too, and do not count it)
+    uint32_t w[4];
+    philox4x32_10((uint32_t)t, (uint32_t)((uint64_t)t >> 32), kTripletStream, 0u, key0, key1, w);
+    const uint32_t i = __umulhi(w[0], n);
+    uint32_t j = __umulhi(w[1], n - 1u);
+    j += j >= i;
+    uint32_t k = __umulhi(w[2], n - 2u);
+    const uint32_t lo = min(i, j), hi = max(i, j);
+    k += k >= lo;
+    k += k >= hi;
+    double hij, hik, lij, lik;
+    anchor_distances(Y + (int64_t)i * d_low, Y + (int64_t)j * d_low, Y + (int64_t)k * d_low, d_low, rows_by_16(Y, d_low), lij, lik);
+    if (STAGED) staged_distances(*(StagedRows*)space, X, d, i, j, k, hij, hik);
+    else anchor_distances(X + (int64_t)i * d, X + (int64_t)j * d, X + (int64_t)k * d, d, rows_by_16(X, d), hij, hik);
+    const bool same = t < t_end && (hij < hik) == (lij < lik);
     const unsigned long long m = __ballot(same);
-    if ((threadIdx.x & 63) == 0 && m) atomicAdd(agree, (unsigned long long)__popcll(m));
+    if (threadIdx.x == 0 && m) atomicAdd(agree, (unsigned long long)__popcll(m));
 }
 
 // *p = v (one lane): clears a counter without a memset node, so that a caller may record the call into a HIP graph
