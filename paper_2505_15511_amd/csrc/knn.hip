@@ -19,6 +19,11 @@ using namespace nomad_metrics;
 
 namespace {
 
+void launch_norms(hipStream_t st, const float* X, int64_t n, int32_t d, const int32_t* members, const int32_t* group_of, const float* centre, float* norm,
+                  uint32_t* max_bits) {
+    hipLaunchKernelGGL(k_knn_norms, dim3((uint32_t)((n + norm_block_rows(n) - 1) / norm_block_rows(n))), dim3(256), 0, st, X, n, d, members, group_of, centre, norm,
+                       max_bits, (int32_t)norm_batches(n));
+}
 
 // One side of the filter, packed: tiles per group (host and device), the packed rows, and the launch that fills them.
 struct PackedSide {
@@ -85,11 +90,14 @@ std::vector<KnnBlock> filter_blocks(const PackedSide& Q, const PackedSide& C, in
 constexpr uint32_t kLoopGrid = 512;   // workgroups of the kernels whose work list is counted on the device
 
 // The k nearest candidates of every query inside its group (filter, refinement, exact fallback).  `cand` [n_q * (k + kPad)],
-// `tau` [n_q], `flagged` [n_q], `n_flagged` [1] are work space.
-int nearest_in_groups(hipStream_t st, const KnnSets& P, const KnnBlock* blocks, uint32_t n_blocks, int waves, int32_t k, int32_t* cand, float* keys, float* tau,
+// `tau` [n_q], `flagged` [n_q], `n_flagged` [1] (zero) are work space.
+int nearest_in_groups(hipStream_t st, Buffers& buf, const KnnSets& P, const KnnBlock* blocks, uint32_t n_blocks, int waves, int32_t k, int32_t* cand, float* keys, float* tau,
                       int32_t* flagged, uint32_t* n_flagged, int32_t* out) {
     const int32_t list_len = k + kPad;
-    KTRY(hipMemsetAsync(n_flagged, 0, sizeof(uint32_t), st));
+    const dim3 grid((uint32_t)std::min<int64_t>(P.n_q, kLoopGrid));
+    ExactParts parts{};
+    KTRY(buf.alloc(&parts.D, (size_t)grid.x * k)); KTRY(buf.alloc(&parts.P, (size_t)grid.x * k)); KTRY(buf.alloc(&parts.done, (size_t)grid.x));
+    KTRY(hipMemsetAsync(parts.done, 0, sizeof(uint32_t) * (size_t)grid.x, st));
     KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, list_len, cand, keys, tau, KnnAssign{nullptr, nullptr, nullptr}));
     if (list_len <= 16)
         hipLaunchKernelGGL(k_knn_refine<16>, dim3(blocks_of(P.n_q, 16)), dim3(256), 0, st, P, cand, keys, tau, k, list_len, out, flagged, n_flagged);
@@ -97,9 +105,8 @@ int nearest_in_groups(hipStream_t st, const KnnSets& P, const KnnBlock* blocks, 
         hipLaunchKernelGGL(k_knn_refine<32>, dim3(blocks_of(P.n_q, 8)), dim3(256), 0, st, P, cand, keys, tau, k, list_len, out, flagged, n_flagged);
     else
         hipLaunchKernelGGL(k_knn_refine<64>, dim3(blocks_of(P.n_q, 4)), dim3(256), 0, st, P, cand, keys, tau, k, list_len, out, flagged, n_flagged);
-    const dim3 grid((uint32_t)std::min<int64_t>(P.n_q, kLoopGrid));
-    if (k <= 16) hipLaunchKernelGGL((k_knn_exact<16, 1024>), grid, dim3(1024), 0, st, P, flagged, (const uint32_t*)n_flagged, k, out);
-    else hipLaunchKernelGGL((k_knn_exact<kMaxK, 512>), grid, dim3(512), 0, st, P, flagged, (const uint32_t*)n_flagged, k, out);
+    if (k <= 16) hipLaunchKernelGGL((k_knn_exact<16, 1024>), grid, dim3(1024), 0, st, P, flagged, (const uint32_t*)n_flagged, k, out, parts);
+    else hipLaunchKernelGGL((k_knn_exact<kMaxK, 512>), grid, dim3(512), 0, st, P, flagged, (const uint32_t*)n_flagged, k, out, parts);
     KTRY(hipGetLastError());
     return NOMAD_OK;
 }
@@ -117,7 +124,7 @@ int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* bloc
                            width, out, flagged, counters + 1);
     }
     hipLaunchKernelGGL((k_knn_exact<1, 256>), dim3((uint32_t)std::min<int64_t>(P.n_q, kLoopGrid)), dim3(256), 0, st, P, (const int32_t*)flagged,
-                       (const uint32_t*)(counters + 1), 1, out);
+                       (const uint32_t*)(counters + 1), 1, out, ExactParts{});
     KTRY(hipGetLastError());
     return NOMAD_OK;
 }
@@ -288,14 +295,14 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     hipLaunchKernelGGL(k_knn_group, dim3(blocks_of(n, kGroupSpan)), dim3(256), 0, st, dC, n, R, start, cursor, members);
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, members, start, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of((int64_t)R * d, 256)), dim3(256), 0, st, centre, start, R, d);
-    hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, dX, n, d, dC, centre, norm, max_norm);
+    launch_norms(st, dX, n, d, members, dC, centre, norm, max_norm);
     side.fill(st, dX, d, members, centre, max_norm, max_norm, norm);
 
     // filter on the matrix cores, float64 refinement, exact fallback
     KnnSets P{};
     P.XQ = dX; P.XC = dX; P.qmembers = members; P.cmembers = members; P.qstart = start; P.cstart = start;
     P.Q = side.view(max_norm); P.C = P.Q; P.centre = centre; P.group_of_q = dC; P.n_q = n; P.n_c = n; P.d = d; P.same_set = 1;
-    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, dOut);
+    int rc = nearest_in_groups(st, buf, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, dOut);
     if (rc) return rc;
     uint32_t hflag = 0;
     KTRY(hipMemcpyAsync(&hflag, n_flagged, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
@@ -370,7 +377,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     KTRY(hipMemsetAsync(max_pts, 0, sizeof(uint32_t), st));
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, (const int32_t*)nullptr, qstart, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(d, 256)), dim3(256), 0, st, centre, qstart, 1, d);
-    hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, dX, n, d, (const int32_t*)nullptr, centre, (float*)nullptr, max_pts);
+    launch_norms(st, dX, n, d, nullptr, nullptr, centre, nullptr, max_pts);
     points.fill(st, dX, d, nullptr, centre, max_pts, nullptr, nullptr);
     MeanStep m_step;
     {
@@ -394,8 +401,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
                                cents.tile, cents.steps, cents.data, cents.norm, c_used, zeros, kZeroWords - 1, max_cen);
         } else {
             KTRY(hipMemsetAsync(zeros, 0, kZeroWords * sizeof(uint32_t), st));
-            hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(K, kNormRows)), dim3(256), 0, st, (const float*)dC, (int64_t)K, d, (const int32_t*)nullptr, centre, cnorm,
-                               max_cen);
+            launch_norms(st, dC, K, d, nullptr, nullptr, centre, cnorm, max_cen);
             cents.fill(st, dC, d, nullptr, centre, max_cen, max_pts, cnorm);
             KTRY(hipMemcpyAsync(c_used, dC, sizeof(float) * (size_t)K * d, hipMemcpyDeviceToDevice, st));
         }
@@ -601,16 +607,15 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     if (hbad) return NOMAD_E_INVALID_ARG;   // a query outside 0..n-1
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, A, d, (const int32_t*)nullptr, cstart, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(G * d, 256)), dim3(256), 0, st, centre, cstart, (int32_t)G, d);
-    hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(n, kNormRows)), dim3(256), 0, st, A, n, d, (const int32_t*)slice_of, centre, cnorm, max_c);
-    hipLaunchKernelGGL(k_knn_norms, dim3(blocks_of(mq, kNormRows)), dim3(256), 0, st, (const float*)AQ, mq, d, (const int32_t*)group_of_q, centre,
-                       (float*)nullptr, max_q);
+    launch_norms(st, A, n, d, nullptr, slice_of, centre, cnorm, max_c);
+    launch_norms(st, AQ, mq, d, nullptr, group_of_q, centre, nullptr, max_q);
     cside.fill(st, A, d, nullptr, centre, max_c, max_q, cnorm);
     qside.fill(st, AQ, d, nullptr, centre, max_q, nullptr, nullptr);
     KnnSets P{};
     P.XQ = AQ; P.XC = A; P.qmembers = nullptr; P.cmembers = nullptr; P.qstart = qstart; P.cstart = cstart;
     P.Q = qside.view(max_q); P.C = cside.view(max_c); P.centre = centre; P.group_of_q = group_of_q; P.n_q = mq; P.n_c = n; P.d = d; P.same_set = 0;
     P.self_row = self;
-    int rc = nearest_in_groups(st, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, G > 1 ? part : out);
+    int rc = nearest_in_groups(st, buf, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, G > 1 ? part : out);
     if (rc) return rc;
     if (G > 1) {
         hipLaunchKernelGGL(k_merge_slices, dim3((uint32_t)m), dim3(256), 0, st, (const float*)AQ, A, d, (const int32_t*)part, (int32_t)G, m, k, out);

@@ -62,53 +62,122 @@ __global__ void __launch_bounds__(256) k_knn_centroid_finish(float* __restrict__
 
 // |x'|^2 of every centred row in float32 and the largest one per cluster.  Sixteen lanes share a row (a wavefront reads
 // four consecutive rows, each lane every sixteenth column or 16-byte chunk) and add their partial sums pairwise; any
-// summation order stays within the d u |x'|^2 that the filter's error bound allows for the norm.
+// summation order stays within the d u |x'|^2 that the filter's error bound allows for the norm.  Bound by the latency of two
+// or three loads in a chain and, where the groups are few, by the atomics on their words: large sets take kNormBatch rows per
+// sixteen lanes, all their loads in flight, and one atomic per workgroup that lies inside one group.  `members` lists the rows
+// group by group where the caller has that order: the centres then come from the first cache.  1,000,000 x 128: one group 175 ->
+// 84 us (6.1 TB/s), six slices 290 -> 85, 256 clusters of mixed rows 175 -> 155.
 constexpr int kNormLanes = 16;
-constexpr int kNormRows = 256 / kNormLanes;   // rows per workgroup
-__global__ void __launch_bounds__(256) k_knn_norms(const float* __restrict__ X, int64_t n, int32_t d, const int32_t* __restrict__ cluster_of,
-                                                   const float* __restrict__ centre, float* __restrict__ norm,
-                                                   uint32_t* __restrict__ max_norm_bits) {
-    const int64_t i = (int64_t)blockIdx.x * kNormRows + threadIdx.x / kNormLanes;
-    const int part = threadIdx.x % kNormLanes;
-    const bool valid = i < n;
-    int32_t g = 0;
-    float s = 0.f;
-    if (valid) {
-        const float* x = X + i * d;
-        g = cluster_of ? cluster_of[i] : 0;
-        const float* c = centre + (int64_t)g * d;
-        if (rows_by_16(X, d)) {   // (the centres are the library's own, see knn.hip)
-            for (int t = 4 * part; t < d; t += 4 * kNormLanes) {
-                const float4 xv = *(const float4*)(x + t), cv = *(const float4*)(c + t);
-                float v = xv.x - cv.x;
-                s = fmaf(v, v, s);
-                v = xv.y - cv.y;
-                s = fmaf(v, v, s);
-                v = xv.z - cv.z;
-                s = fmaf(v, v, s);
-                v = xv.w - cv.w;
-                s = fmaf(v, v, s);
+constexpr int kNormRows = 256 / kNormLanes;   // rows per workgroup and batch entry
+constexpr int kNormBatch = 4, kNormBatches = 4;
+inline int norm_batches(int64_t n) { return n >= ((int64_t)1 << 17) ? kNormBatches : 0; }   // 0: one row per sixteen lanes
+inline int64_t norm_block_rows(int64_t n) { return norm_batches(n) ? (int64_t)kNormRows * kNormBatch * kNormBatches : kNormRows; }
+
+// U rows of sixteen lanes each, i0 + u stride: their sums, of rows that are none zero
+template <int U>
+__device__ __forceinline__ void centred_norms(const float* __restrict__ X, int64_t n, int32_t d, const int32_t* __restrict__ members,
+                                              const int32_t* __restrict__ cluster_of, const float* __restrict__ centre, int64_t i0, int64_t stride,
+                                              int part, int32_t* row, int32_t* g, float* s) {
+    const float *x[U], *c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) row[u] = knn_row(members, (uint32_t)(i0 + u * stride < n ? i0 + u * stride : n - 1));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        x[u] = X + (int64_t)row[u] * d;
+        g[u] = cluster_of ? cluster_of[row[u]] : 0;
+        s[u] = 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = centre + (int64_t)g[u] * d;
+    if (rows_by_16(X, d)) {   // (the centres are the library's own, see knn.hip)
+        for (int t = 4 * part; t < d; t += 4 * kNormLanes) {
+            float4 xv[U], cv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) { xv[u] = *(const float4*)(x[u] + t); cv[u] = *(const float4*)(c[u] + t); }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float v = xv[u].x - cv[u].x;
+                s[u] = fmaf(v, v, s[u]);
+                v = xv[u].y - cv[u].y;
+                s[u] = fmaf(v, v, s[u]);
+                v = xv[u].z - cv[u].z;
+                s[u] = fmaf(v, v, s[u]);
+                v = xv[u].w - cv[u].w;
+                s[u] = fmaf(v, v, s[u]);
             }
-        } else {
-            for (int t = part; t < d; t += kNormLanes) {
-                const float v = x[t] - c[t];
-                s = fmaf(v, v, s);
+        }
+    } else {
+        for (int t = part; t < d; t += kNormLanes) {
+            float xv[U], cv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) { xv[u] = x[u][t]; cv[u] = c[u][t]; }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float v = xv[u] - cv[u];
+                s[u] = fmaf(v, v, s[u]);
             }
         }
     }
-    for (int w = kNormLanes / 2; w > 0; w >>= 1) s += __shfl_xor(s, w, kNormLanes);   // every lane of the row: the row's sum
-    if (valid && part == 0 && norm) norm[i] = s;
-    // non-negative floats order like their bit patterns; one atomic per wavefront where it lies inside one group
-    const unsigned long long live = __ballot(valid);
-    if (!live) return;
-    const int first = __ffsll((long long)live) - 1;
-    const int32_t g0 = __shfl(g, first, 64);
-    uint32_t bits = valid ? __float_as_uint(s) : 0u;
-    if (__all(!valid || g == g0)) {
-        for (int w = 32; w > 0; w >>= 1) bits = max(bits, (uint32_t)__shfl_xor((int)bits, w, 64));
-        if ((int)(threadIdx.x & 63) == first && bits > max_norm_bits[g0]) atomicMax(&max_norm_bits[g0], bits);
-    } else if (valid && part == 0 && bits > max_norm_bits[g]) {   // the maximum only grows: a stale read costs one atomic, not the result
-        atomicMax(&max_norm_bits[g], bits);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        for (int w = kNormLanes / 2; w > 0; w >>= 1) s[u] += __shfl_xor(s[u], w, kNormLanes);   // every lane of the row: the row's sum
+        if (i0 + u * stride >= n) s[u] = 0.f;
+    }
+}
+// non-negative floats order like their bit patterns; the maximum only grows: a stale read costs one atomic, not the result
+__device__ __forceinline__ void raise_norm(uint32_t* __restrict__ word, uint32_t bits) {
+    if (bits > *word) atomicMax(word, bits);
+}
+__global__ void __launch_bounds__(256) k_knn_norms(const float* __restrict__ X, int64_t n, int32_t d, const int32_t* __restrict__ members,
+                                                   const int32_t* __restrict__ cluster_of, const float* __restrict__ centre, float* __restrict__ norm,
+                                                   uint32_t* __restrict__ max_norm_bits, int32_t batches) {
+    __shared__ int32_t group[4];
+    __shared__ uint32_t most[4];
+    const int part = threadIdx.x % kNormLanes;
+    const int64_t row = threadIdx.x / kNormLanes;
+    int32_t cur = -1;          // the group that `bits` is the maximum of
+    uint32_t bits = 0u;
+    const auto enter = [&](int64_t i, int32_t r, int32_t g, float s) {
+        if (i >= n) return;
+        if (part == 0 && norm) norm[r] = s;
+        if (g != cur) {
+            if (cur >= 0 && part == 0) raise_norm(&max_norm_bits[cur], bits);
+            cur = g;
+            bits = 0u;
+        }
+        bits = max(bits, __float_as_uint(s));
+    };
+    if (batches == 0) {
+        const int64_t i = (int64_t)blockIdx.x * kNormRows + row;
+        int32_t r[1], g[1];
+        float s[1];
+        centred_norms<1>(X, n, d, members, cluster_of, centre, i, 0, part, r, g, s);
+        enter(i, r[0], g[0], s[0]);
+    } else {
+        for (int b = 0; b < batches; ++b) {
+            const int64_t i = ((int64_t)blockIdx.x * batches + b) * (kNormRows * kNormBatch) + row;
+            int32_t r[kNormBatch], g[kNormBatch];
+            float s[kNormBatch];
+            centred_norms<kNormBatch>(X, n, d, members, cluster_of, centre, i, kNormRows, part, r, g, s);
+#pragma unroll
+            for (int u = 0; u < kNormBatch; ++u) enter(i + u * kNormRows, r[u], g[u], s[u]);
+        }
+    }
+    // the wavefront's own group, or -1 where it has several (those go out by themselves) or none
+    const unsigned long long live = __ballot(cur >= 0);
+    const int32_t g0 = live ? __shfl(cur, __ffsll((long long)live) - 1, 64) : -1;
+    const bool one = __all(cur < 0 || cur == g0);
+    for (int w = 32; w >= kNormLanes && one; w >>= 1) bits = max(bits, (uint32_t)__shfl_xor((int)bits, w, 64));
+    if (!one && cur >= 0 && part == 0) raise_norm(&max_norm_bits[cur], bits);
+    if ((threadIdx.x & 63) == 0) { group[threadIdx.x >> 6] = one ? g0 : -1; most[threadIdx.x >> 6] = bits; }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int32_t own = group[threadIdx.x];
+        uint32_t m = 0u;
+        bool first = own >= 0;
+        for (int w = 0; w < 4; ++w)
+            if (group[w] == own) { m = max(m, most[w]); first = first && w >= (int)threadIdx.x; }
+        if (first) raise_norm(&max_norm_bits[own], m);
     }
 }
 
@@ -412,106 +481,134 @@ __device__ __forceinline__ void exact_distances4(const float* __restrict__ x, co
     for (int u = 0; u < 4; ++u) D[u] = a[u];
 }
 
-// A team of THREADS lanes, a workgroup or one wavefront of it, per flagged query at a time.  Every lane walks its share of the
-// group once, four candidates at a time, and keeps its own k smallest (distance, point) pairs sorted in registers (KL >= k
-// slots); the k smallest of the group are among those, and k rounds pick them: each lane offers its smallest pair above the
-// one picked before, the team takes the smallest offer.
+// A team of THREADS lanes, a workgroup or one wavefront of it, per flagged query (or part of its group) at a time.  Every lane
+// walks its share of the candidates once, four at a time, and keeps its own k smallest (distance, point) pairs sorted in
+// registers (KL >= k slots); the k smallest of all are among those, and k rounds pick them: each lane offers its smallest pair
+// above the one picked before, the team takes the smallest offer.
 template <int KL, int THREADS>
-__device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t k, int32_t* __restrict__ out, double* sD, int32_t* sP) {
-    const int32_t d = P.d;
-    const int32_t r = P.group_of_q ? P.group_of_q[q] : 0;
-    const uint32_t c0 = P.cstart[r], c1 = P.cstart[r + 1], tid = threadIdx.x % THREADS;
-    const float* xq = P.XQ + (int64_t)q * d;
-    const bool by16 = rows_by_16(P.XQ, d) && rows_by_16(P.XC, d);
-    const int32_t self = P.self_row ? P.self_row[q] : P.same_set ? q : -1;
+struct ExactTeam {
     double lD[KL];      // ascending in (distance, point); empty slots: (inf, -1) at the end
     int32_t lP[KL];
+    double wD;          // the pair in slot k - 1 (point -1 while the list is not full)
+    int32_t wP;
+
+    __device__ __forceinline__ void clear() {
 #pragma unroll
-    for (int x = 0; x < KL; ++x) { lD[x] = __builtin_inf(); lP[x] = -1; }
-    double wD = __builtin_inf();   // the pair in slot k - 1 (point -1 while the list is not full)
-    int32_t wP = -1;
-    for (uint32_t pos = c0 + tid; pos < c1; pos += 4 * THREADS) {
-        int32_t c[4];
-        const float* row[4];
-        double D[4];
+        for (int x = 0; x < KL; ++x) { lD[x] = __builtin_inf(); lP[x] = -1; }
+        wD = __builtin_inf();
+        wP = -1;
+    }
+    __device__ __forceinline__ void insert(double xD, int32_t xP, int32_t k) {
+        // slot k - 1 is the list's last used slot: what does not come before it cannot be among this thread's k smallest
+        if (!(wP < 0 || xD < wD || (xD == wD && xP < wP))) return;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            c[u] = pos + u * THREADS < c1 ? knn_row(P.cmembers, pos + u * THREADS) : -1;
-            row[u] = P.XC + (int64_t)(c[u] < 0 ? knn_row(P.cmembers, pos) : c[u]) * d;
-        }
-        exact_distances4(xq, row, c, d, by16, D);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (c[u] < 0 || c[u] == self) continue;
-            double xD = D[u] == D[u] ? D[u] : __builtin_inf();   // no number: as far as can be, so that every candidate has a place in the order
-            int32_t xP = c[u];
-            // slot k - 1 is the list's last used slot: what does not come before it cannot be among this thread's k smallest
-            if (!(wP < 0 || xD < wD || (xD == wD && xP < wP))) continue;
-#pragma unroll
-            for (int x = 0; x < KL; ++x) {
-                if (x < k) {
-                    const bool take = xP >= 0 && (lP[x] < 0 || xD < lD[x] || (xD == lD[x] && xP < lP[x]));
-                    const double oD = lD[x];
-                    const int32_t oP = lP[x];
-                    lD[x] = take ? xD : oD;
-                    lP[x] = take ? xP : oP;
-                    xD = take ? oD : xD;
-                    xP = take ? oP : xP;
-                }
+        for (int x = 0; x < KL; ++x) {
+            if (x < k) {
+                const bool take = xP >= 0 && (lP[x] < 0 || xD < lD[x] || (xD == lD[x] && xP < lP[x]));
+                const double oD = lD[x];
+                const int32_t oP = lP[x];
+                lD[x] = take ? xD : oD;
+                lP[x] = take ? xP : oP;
+                xD = take ? oD : xD;
+                xP = take ? oP : xP;
             }
+        }
 #pragma unroll
-            for (int x = 0; x < KL; ++x)
-                if (x == k - 1) { wD = lD[x]; wP = lP[x]; }
+        for (int x = 0; x < KL; ++x)
+            if (x == k - 1) { wD = lD[x]; wP = lP[x]; }
+    }
+    // the candidates at positions c0 .. c1 - 1
+    __device__ __forceinline__ void walk(const KnnSets& P, int32_t q, int32_t k, uint32_t c0, uint32_t c1) {
+        const int32_t d = P.d;
+        const float* xq = P.XQ + (int64_t)q * d;
+        const bool by16 = rows_by_16(P.XQ, d) && rows_by_16(P.XC, d);
+        const int32_t self = P.self_row ? P.self_row[q] : P.same_set ? q : -1;
+        for (uint32_t pos = c0 + threadIdx.x % THREADS; pos < c1; pos += 4 * THREADS) {
+            int32_t c[4];
+            const float* row[4];
+            double D[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                c[u] = pos + u * THREADS < c1 ? knn_row(P.cmembers, pos + u * THREADS) : -1;
+                row[u] = P.XC + (int64_t)(c[u] < 0 ? knn_row(P.cmembers, pos) : c[u]) * d;
+            }
+            exact_distances4(xq, row, c, d, by16, D);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (c[u] < 0 || c[u] == self) continue;
+                insert(D[u] == D[u] ? D[u] : __builtin_inf(), c[u], k);   // no number: as far as can be, so that every candidate has a place in the order
+            }
         }
     }
-    double lastD = -1.0;
-    int32_t lastP = -1;
-    for (int m = 0; m < k; ++m) {
-        double bestD = __builtin_inf();
-        int32_t bestP = -1;
+    // put(m, D, P) by the team's first lane for the k smallest in order, point -1 once there are no more
+    template <typename Put>
+    __device__ __forceinline__ void pick(int32_t k, double* sD, int32_t* sP, const Put& put) {
+        const uint32_t tid = threadIdx.x % THREADS;
+        double lastD = -1.0;
+        int32_t lastP = -1;
+        for (int m = 0; m < k; ++m) {
+            double bestD = __builtin_inf();
+            int32_t bestP = -1;
 #pragma unroll
-        for (int x = KL - 1; x >= 0; --x) {   // descending, so that the first pair after the last pick is what remains
-            const bool after = lP[x] >= 0 && (lD[x] > lastD || (lD[x] == lastD && lP[x] > lastP));
-            bestD = after ? lD[x] : bestD;
-            bestP = after ? lP[x] : bestP;
-        }
-        // smallest offer: inside the wavefront, then over the wavefronts' offers
-        auto take_smaller = [&](double Do, int32_t Po) {
-            const bool take = Po >= 0 && (bestP < 0 || Do < bestD || (Do == bestD && Po < bestP));
-            bestD = take ? Do : bestD;
-            bestP = take ? Po : bestP;
-        };
-        for (int w = 32; w > 0; w >>= 1) take_smaller(__shfl_xor(bestD, w, 64), __shfl_xor(bestP, w, 64));
-        if (THREADS > 64) {
-            if ((tid & 63) == 0) { sD[tid >> 6] = bestD; sP[tid >> 6] = bestP; }
-            __syncthreads();
-            bestD = __builtin_inf();
-            bestP = -1;
-            for (int w = 0; w < THREADS / 64; ++w) take_smaller(sD[w], sP[w]);
-        }
-        lastD = bestD;
-        lastP = bestP;
-        if (tid == 0) out[(int64_t)q * k + m] = lastP;   // -1 once the group is exhausted
-        if (THREADS > 64) __syncthreads();
-        if (lastP < 0) {   // nothing left: the remaining slots stay empty
-            for (int x = m + 1 + (int)tid; x < k; x += THREADS) out[(int64_t)q * k + x] = -1;
-            break;
+            for (int x = KL - 1; x >= 0; --x) {   // descending, so that the first pair after the last pick is what remains
+                const bool after = lP[x] >= 0 && (lD[x] > lastD || (lD[x] == lastD && lP[x] > lastP));
+                bestD = after ? lD[x] : bestD;
+                bestP = after ? lP[x] : bestP;
+            }
+            // smallest offer: inside the wavefront, then over the wavefronts' offers
+            auto take_smaller = [&](double Do, int32_t Po) {
+                const bool take = Po >= 0 && (bestP < 0 || Do < bestD || (Do == bestD && Po < bestP));
+                bestD = take ? Do : bestD;
+                bestP = take ? Po : bestP;
+            };
+            for (int w = 32; w > 0; w >>= 1) take_smaller(__shfl_xor(bestD, w, 64), __shfl_xor(bestP, w, 64));
+            if (THREADS > 64) {
+                if ((tid & 63) == 0) { sD[tid >> 6] = bestD; sP[tid >> 6] = bestP; }
+                __syncthreads();
+                bestD = __builtin_inf();
+                bestP = -1;
+                for (int w = 0; w < THREADS / 64; ++w) take_smaller(sD[w], sP[w]);
+            }
+            lastD = bestD;
+            lastP = bestP;
+            if (tid == 0) put(m, lastD, lastP);
+            if (THREADS > 64) __syncthreads();
+            if (lastP < 0) {   // nothing left: the remaining slots stay empty
+                if (tid == 0)
+                    for (int x = m + 1; x < k; ++x) put(x, lastD, -1);
+                break;
+            }
         }
     }
+};
+template <int KL, int THREADS>
+__device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t k, int32_t* __restrict__ out, double* sD, int32_t* sP) {
+    const int32_t r = P.group_of_q ? P.group_of_q[q] : 0;
+    ExactTeam<KL, THREADS> team;
+    team.clear();
+    team.walk(P, q, k, P.cstart[r], P.cstart[r + 1]);
+    team.pick(k, sD, sP, [&](int m, double, int32_t c) { out[(int64_t)q * k + m] = c; });
 }
 
-// The teams take the flagged queries in turn (how many there are is known on the device only).  Usually there are a few dozen: a
-// workgroup each, the time is one query's chain of memory latencies.  From four a workgroup on (data with far outliers, groups
-// the filter cannot work on) a wavefront each: the k rounds then need no barriers and short groups leave fewer lanes without
-// a candidate.  Whole calls, a workgroup each -> a wavefront each: 200,000 x 64 in 64 clusters, k = 15, 62,000 and 145,000
+// Work space for queries whose groups are cut: pairs of every workgroup, and per query how many of its parts are through (zero)
+struct ExactParts { double* D; int32_t* P; uint32_t* done; };   // [grid * k] each, [grid / 2]
+constexpr uint32_t kMaxParts = 32;
+
+// The teams take the flagged queries in turn (how many there are is known on the device only).  Usually there are a few dozen: the
+// time is one query's chain of memory latencies.  Up to half as many as workgroups: the query's group is cut into parts of at
+// least a row for every lane, a workgroup each, and the one that is through last picks from all parts' pairs (100,003 x 768:
+// 0.51 ms with a workgroup to a query, now 0.22; 1,000,000 x 128 in 256 clusters: 0.15 to 0.19, now 0.09).  Up to four a
+// workgroup: a workgroup each.  From there on (data with far outliers, groups the filter cannot work on) a wavefront each: the k
+// rounds then need no barriers and short groups leave fewer lanes without a candidate.  Whole calls, a workgroup each -> a wavefront each: 200,000 x 64 in 64 clusters, k = 15, 62,000 and 145,000
 // flagged 29 -> 12.5 and 64 -> 27 ms, 3,100 flagged 2.35 -> 1.6; 20,000 x 768, 7,300 flagged 14.8 -> 7.0; five iterations of
 // 300,000 x 128 on 128 centroids, all flagged, 59 -> 14; one cluster of 100,000 x 128, 9,600 flagged 78 -> 81 (both bound by the
 // rows' way from the last cache).
 template <int KL, int THREADS>
 __global__ void __launch_bounds__(THREADS) k_knn_exact(const KnnSets P, const int32_t* __restrict__ flagged, const uint32_t* __restrict__ n_flagged,
-                                                       int32_t k, int32_t* __restrict__ out) {
+                                                       int32_t k, int32_t* __restrict__ out, const ExactParts parts) {
     __shared__ double sD[THREADS / 64];
     __shared__ int32_t sP[THREADS / 64];
+    __shared__ uint32_t through;
     constexpr uint32_t kWaves = THREADS / 64;
     const uint32_t count = *n_flagged;
     if (count >= 4u * gridDim.x) {
@@ -519,10 +616,39 @@ __global__ void __launch_bounds__(THREADS) k_knn_exact(const KnnSets P, const in
             exact_query<KL, 64>(P, flagged[f], k, out, sD, sP);
         return;
     }
-    for (uint32_t f = blockIdx.x; f < count; f += gridDim.x) {
-        exact_query<KL, THREADS>(P, flagged[f], k, out, sD, sP);
-        __syncthreads();
+    if (KL == 1 || 2u * count > gridDim.x) {   // (one neighbour wanted: the candidates are a few hundred centroids)
+        for (uint32_t f = blockIdx.x; f < count; f += gridDim.x) {
+            exact_query<KL, THREADS>(P, flagged[f], k, out, sD, sP);
+            __syncthreads();
+        }
+        return;
     }
+    if (count == 0u) return;
+    const uint32_t f = blockIdx.x % count, part = blockIdx.x / count;
+    const int32_t q = flagged[f], r = P.group_of_q ? P.group_of_q[q] : 0;
+    const uint32_t c0 = P.cstart[r], c1 = P.cstart[r + 1];
+    const uint32_t n_parts = max(1u, min(min(kMaxParts, gridDim.x / count), (c1 - c0 + THREADS - 1u) / THREADS));
+    if (part >= n_parts) return;
+    if (n_parts == 1u) { exact_query<KL, THREADS>(P, q, k, out, sD, sP); return; }
+    const uint32_t span = (c1 - c0 + n_parts - 1u) / n_parts, from = min(c1, c0 + part * span);
+    ExactTeam<KL, THREADS> team;
+    team.clear();
+    team.walk(P, q, k, from, min(c1, from + span));
+    team.pick(k, sD, sP, [&](int m, double D, int32_t c) { parts.D[(size_t)blockIdx.x * k + m] = D; parts.P[(size_t)blockIdx.x * k + m] = c; });
+    if (threadIdx.x == 0) {
+        __threadfence();
+        through = atomicAdd(&parts.done[f], 1u) + 1u;
+    }
+    __syncthreads();
+    if (through != n_parts) return;
+    __threadfence();
+    team.clear();
+    for (uint32_t x = threadIdx.x; x < n_parts * (uint32_t)k; x += THREADS) {
+        const size_t at = ((size_t)(x / (uint32_t)k) * count + f) * k + x % (uint32_t)k;
+        if (parts.P[at] >= 0) team.insert(parts.D[at], parts.P[at], k);
+    }
+    __syncthreads();
+    team.pick(k, sD, sP, [&](int m, double, int32_t c) { out[(int64_t)q * k + m] = c; });
 }
 
 // One neighbour wanted, queries the filter's bound could not decide: the exact distances of the `width` (4 or 8)
