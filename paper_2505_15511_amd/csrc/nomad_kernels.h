@@ -472,7 +472,7 @@ __device__ __forceinline__ void edge_math(const HeadCtx& h, float pe, float2 tj,
         qm[k] = cauchy(o.rx[k], o.ry[k]);
         qsum += qm[k];
     }
-    const float rest = h.MA + h.omega * qsum;   // S_e - q_ij: the noise part of the denominator
+    const float rest = fmaf(h.omega, qsum, h.MA);   // S_e - q_ij: the noise part of the denominator
     const float Se = qij + rest;
     if (LOSS) {
         o.log_term = pe * logf(Se / qij);   // -log q + log S = log(S (1 + d^2))
@@ -491,8 +491,8 @@ __device__ __forceinline__ void edge_math(const HeadCtx& h, float pe, float2 tj,
         fy -= o.ry[k];
     }
     o.c = 2.0f * pe * inv_S;
-    o.hx = fx - o.c * h.MBx;
-    o.hy = fy - o.c * h.MBy;
+    o.hx = fmaf(-o.c, h.MBx, fx);
+    o.hy = fmaf(-o.c, h.MBy, fy);
 }
 
 // Pooled sampler: pool entry of slot k given the four words of the per-edge Philox call k >> 3
