@@ -301,7 +301,7 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     // filter on the matrix cores, float64 refinement, exact fallback
     KnnSets P{};
     P.XQ = dX; P.XC = dX; P.qmembers = members; P.cmembers = members; P.qstart = start; P.cstart = start;
-    P.Q = side.view(max_norm); P.C = P.Q; P.centre = centre; P.group_of_q = dC; P.n_q = n; P.n_c = n; P.d = d; P.same_set = 1;
+    P.Q = side.view(max_norm); P.C = P.Q; P.centre = centre; P.group_of_q = dC; P.n_q = n; P.n_c = n; P.d = d; P.same_set = 1; P.chunk = knn_chunk_columns(d, list_len);
     int rc = nearest_in_groups(st, buf, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, dOut);
     if (rc) return rc;
     uint32_t hflag = 0;
@@ -387,7 +387,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
 
     KnnSets P{};
     P.XQ = dX; P.XC = dC; P.qmembers = nullptr; P.cmembers = nullptr; P.qstart = qstart; P.cstart = cstart;
-    P.Q = points.view(max_pts); P.C = cents.view(max_cen); P.centre = centre; P.group_of_q = nullptr; P.n_q = n; P.n_c = K; P.d = d; P.same_set = 0;
+    P.Q = points.view(max_pts); P.C = cents.view(max_cen); P.centre = centre; P.group_of_q = nullptr; P.n_q = n; P.n_c = K; P.d = d; P.same_set = 0; P.chunk = knn_chunk_columns(d, 1);
     // Labels go back and forth between two arrays; the centroids of the last E step are kept for the inertia.
     int32_t *cur = new_lab, *prev = dLab;
     HostWord hchanged[2];
@@ -613,7 +613,7 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     qside.fill(st, AQ, d, nullptr, centre, max_q, nullptr, nullptr);
     KnnSets P{};
     P.XQ = AQ; P.XC = A; P.qmembers = nullptr; P.cmembers = nullptr; P.qstart = qstart; P.cstart = cstart;
-    P.Q = qside.view(max_q); P.C = cside.view(max_c); P.centre = centre; P.group_of_q = group_of_q; P.n_q = mq; P.n_c = n; P.d = d; P.same_set = 0;
+    P.Q = qside.view(max_q); P.C = cside.view(max_c); P.centre = centre; P.group_of_q = group_of_q; P.n_q = mq; P.n_c = n; P.d = d; P.same_set = 0; P.chunk = knn_chunk_columns(d, list_len);
     P.self_row = self;
     int rc = nearest_in_groups(st, buf, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, G > 1 ? part : out);
     if (rc) return rc;

@@ -52,6 +52,7 @@ struct KnnSets {
     int64_t n_q, n_c;            // rows of XQ, XC
     int32_t d;
     int32_t same_set;            // 1: queries and candidates are the same rows: a row is not its own neighbour
+    int32_t chunk;               // columns that the filter sums at a time (knn_chunk_columns): its error bound depends on it
     const int32_t* self_row;     // or, per query row, the candidate row that is the query itself (nullptr: see same_set)
 };
 
@@ -74,6 +75,17 @@ template <> struct MatrixTile<16> {
 // wavefronts per unit, which wait for each other less but stage every tile twice, are 10 and 5 % slower.  Otherwise loads into
 // LDS are issued two stages ahead of their use (one at the widest rows, whose stages are 48 KB), which is what hides the
 // memory's latency behind 3,000 cycles of matrix instructions per stage.
+// Steps of the large products that are summed by themselves (0: all of them in one sum): 64 columns.  The bound on a sum's
+// rounding grows with its length, and with the bound the number of candidates whose order the keys leave open and whose rows
+// k_knn_refine has to read, and of queries left to the exact path.  1,000,000 x 128 in clusters of 4,000, sums of all columns /
+// 64 / 32: filter 5.33 / 5.42 / 5.4 ms, refinement 0.91 / 0.74 / 0.65, exact path 0.09 / 0.05 / 0.04; but over slices of the
+// whole set the additions cost more than they save (7.9 / 7.9 / 8.2 ms a call).  One neighbour wanted: the lists hold two and the
+// bound decides few (partition of 1,000,000 x 128: no gain).  Not where registers would spill: the widest rows with one neighbour
+// (95 -> 123 us of filter for 8 us of exact path), long lists and more than 192 columns in 32-row tiles.
+__host__ __device__ constexpr int knn_chunk_steps(int tile, int steps, int L) {
+    const int chunk = 64 * tile / 512;
+    return steps <= chunk ? 0 : (tile == 16 ? L > 2 || steps <= 16 : L == 16 && steps <= 12) ? chunk : 0;
+}
 constexpr int kMaxStageTiles = 16;   // packed arrays are this many tiles longer than what they hold
 __host__ __device__ constexpr int knn_stage_tiles(int tile, int steps, int L, int waves) {
     const int target = tile == 16 ? steps : (L > 2 && waves == 8) ? 24 : 8;
@@ -144,6 +156,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     constexpr int kShare = 64 / TILE;                 // lanes per query
     constexpr int kKeys = TILE * TILE / 64;           // keys per lane and tile
     constexpr int kUnits = KS * 2 * 64;               // 16-byte units of a tile
+    constexpr int kChunk = knn_chunk_steps(TILE, KS, L);
     constexpr int kStage = knn_stage_tiles(TILE, KS, L, WAVES), kBuffers = knn_buffers(TILE, KS, L, WAVES);
     constexpr int kStageBytes = (int)knn_stage_bytes(TILE, KS, L, WAVES), kDataBytes = kStage * kUnits * 16;
     constexpr int kCopies = (kStage * KS * 2 + WAVES - 1) / WAVES;              // 1 KB loads of a wavefront per stage
@@ -244,6 +257,16 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         if (qpt >= 0) thr = fminf(lk[L - 1], most);
     };
     constexpr bool kSift = L > 2 && !(TILE == 16 && KS > 16);     // (the widest rows' queries fill the registers as it is)
+    // step s of the large product: big = the norms and the chunks before, chunk = the present one
+    const auto large = [&](Acc& big, Acc& chunk, half8 a, int s) {
+        if (kChunk == 0 || s < kChunk) { big = Mat::mul(a, bh[s], big); return; }
+        if (s % (kChunk ? kChunk : 1) == 0) {
+            if (s > kChunk) big += chunk;
+            chunk = Acc{};
+        }
+        chunk = Mat::mul(a, bh[s], chunk);
+        if (s == KS - 1) big += chunk;
+    };
     const int32_t sift_from = kSift ? list_len * TILE / 2 : n_tiles;
     float slack = 0.f;             // >= |hi lo + lo hi| of this query with any candidate, as summed below
     if (kSift && n_tiles > sift_from) {
@@ -265,7 +288,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     }
     // tile number i of the stage in buffer `buf`, tile t of the group
     auto consume = [&](int buf, int i, int32_t t) {
-        Acc big, small;
+        Acc big, small, chunk;
         const char* stage = (const char*)lds + buf * kStageBytes;
         const float* nn = (const float*)(stage + kDataBytes) + i * TILE + 4 * part;
 #pragma unroll
@@ -284,7 +307,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
                 __builtin_amdgcn_sched_barrier(0);
-                big = Mat::mul(a[s % kAhead], bh[s], big);
+                large(big, chunk, a[s % kAhead], s);
                 __builtin_amdgcn_sched_barrier(0);
                 if (s + kAhead < KS) a[s % kAhead] = *(const half8*)&frag[(s + kAhead) * 128];
             }
@@ -312,7 +335,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                 if (s + 1 < KS) { nh = *(const half8*)&frag[(s + 1) * 128]; nl = *(const half8*)&frag[(s + 1) * 128 + 64]; }
                 __builtin_amdgcn_sched_barrier(0);     // the next step's fragments are on their way while this step is multiplied
                 small = Mat::mul(ah, bl[s], small);
-                big = Mat::mul(ah, bh[s], big);
+                large(big, chunk, ah, s);
                 small = Mat::mul(al, bh[s], small);
                 __builtin_amdgcn_sched_barrier(0);
                 ah = nh;
@@ -402,7 +425,8 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
             if (ob < best || (ob == best && ((lane ^ w) / TILE) < part)) { best = ob; bp = op; }
             second = fminf(second, __shfl_xor(second, w, 64));
         }
-        const double eps = knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[grp]), (double)__uint_as_float(P.C.max_bits[grp])));
+        const double eps = knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[grp]), (double)__uint_as_float(P.C.max_bits[grp])),
+                                          kChunk * 512 / TILE);
         const bool open = qpt >= 0 && !(((double)second - (double)best) * (double)key_unit > 2.0 * eps);
         if (qpt >= 0 && !open && part == 0) assign.out[qpt] = knn_row(P.cmembers, c0 + (uint32_t)bp);
         const unsigned long long m = __ballot(open && part == 0);
@@ -435,5 +459,11 @@ __host__ inline int knn_filter_waves(int tile, int64_t query_tiles) { return que
 // list length per lane for K' = list_len candidates per query: every list longer than k (32-row tiles, two lists per query;
 // a query whose k nearest all fall to one lane must still be certified), or half of K' (16-row tiles, four lists)
 __host__ inline int knn_list_class(int tile, int list_len) { return tile == 32 ? (list_len <= kShortList ? 16 : 34) : list_len <= kShortList ? 12 : 20; }
+
+// columns that the filter sums at a time for K' = list_len (1: one neighbour wanted); 0: all of them
+__host__ inline int32_t knn_chunk_columns(int d, int list_len) {
+    const int tile = knn_tile(d, list_len);
+    return knn_chunk_steps(tile, knn_steps(d, tile), list_len == 1 ? 2 : knn_list_class(tile, list_len)) * 512 / tile;
+}
 
 }  // namespace nomad_knn

@@ -70,8 +70,9 @@ __global__ void __launch_bounds__(256) k_knn_centroid_finish(float* __restrict__
 constexpr int kNormLanes = 16;
 constexpr int kNormRows = 256 / kNormLanes;   // rows per workgroup and batch entry
 constexpr int kNormBatch = 4, kNormBatches = 4;
-inline int norm_batches(int64_t n) { return n >= ((int64_t)1 << 17) ? kNormBatches : 0; }   // 0: one row per sixteen lanes
-inline int64_t norm_block_rows(int64_t n) { return norm_batches(n) ? (int64_t)kNormRows * kNormBatch * kNormBatches : kNormRows; }
+// batches of a workgroup: as many as leave 2,048 of them; 0: one row per sixteen lanes, where batches would leave units without work
+inline int norm_batches(int64_t n) { return n < 65536 ? 0 : n < ((int64_t)1 << 18) ? 1 : n < ((int64_t)1 << 19) ? 2 : kNormBatches; }
+inline int64_t norm_block_rows(int64_t n) { return (int64_t)kNormRows * (norm_batches(n) ? kNormBatch * norm_batches(n) : 1); }
 
 // U rows of sixteen lanes each, i0 + u stride: their sums, of rows that are none zero
 template <int U>
@@ -397,7 +398,8 @@ __device__ __forceinline__ double exact_distance(const float* __restrict__ x, co
 // error bound the exact distances stand in that order too; only the members of a run of closer keys need their exact
 // distances to be ordered (by distance, then point), and of those only the runs that begin among the first k.  The
 // kernel is bound by the rows it gathers: a million queries with 23 candidates of 128 columns, all exact, took 2.0 ms
-// (5.9 TB/s out of the caches); with few of them exact: 0.89 ms.
+// (5.9 TB/s out of the caches); with those whose order the bound leaves open 0.91 ms when the filter's sums were whole
+// rows, 0.74 with sums of 64 columns and half the bound (100,003 x 768: a tenth of it, 0.79 -> 0.51).
 // Certified, i.e. no point that the filter left out (key >= tau, exact key >= tau - eps) is nearer than the k-th, when the
 // k-th key lies below tau by more than twice the bound (k candidates have exact keys up to key + eps), or else the k-th
 // exact key, D_k - |q|^2, does by more than the bound; otherwise the query is flagged.  So is every query of a group that the
@@ -423,7 +425,7 @@ __global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32
         if (lane == 0) flagged[atomicAdd(n_flagged, 1u)] = q;
         return;
     }
-    const double eps = knn_filter_eps(d, fmax((double)__uint_as_float(P.Q.max_bits[g]), (double)__uint_as_float(P.C.max_bits[g])));
+    const double eps = knn_filter_eps(d, fmax((double)__uint_as_float(P.Q.max_bits[g]), (double)__uint_as_float(P.C.max_bits[g])), P.chunk);
     const int first = (int)(threadIdx.x & 63u) - lane;   // of this query's lanes in the wavefront
     const auto votes = [&](bool v) { return (__ballot(v) >> first) & (~0ull >> (64 - G)); };
     const double next = __shfl_down(key, 1, G);
@@ -682,7 +684,7 @@ __global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const in
         if (lane != 0u) continue;
         const bool found = best != 0x7fffffff;
         if (found) out[q] = best;
-        const double eps = knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[g]), (double)__uint_as_float(P.C.max_bits[g])));
+        const double eps = knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[g]), (double)__uint_as_float(P.C.max_bits[g])), P.chunk);
         const float t = tau[x];
         if (!found || (t < __builtin_inff() && !(D - qn + eps < (double)t))) flagged[atomicAdd(n_flagged, 1u)] = q;
     }
