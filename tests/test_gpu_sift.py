@@ -28,3 +28,18 @@ def test_neighbours_late_in_a_long_group(n, d, k, outlier):
     D = ko.pair_distances(X[q], X)
     D[np.arange(len(q)), q] = np.inf
     assert np.array_equal(out[q].astype(np.int64), np.argsort(D, axis=1, kind="stable")[:, :k])
+
+
+@pytest.mark.parametrize("d,k", [(16, 15), (40, 20), (140, 30), (300, 10)])
+def test_a_key_of_zero_keeps_its_position(d, k):
+    """A row that is its group's mean has the key 0 for every query: the smallest numbers a list's entries can be."""
+    print(f"d={d} k={k}", flush=True)
+    rng = np.random.default_rng(d)
+    half = rng.integers(-60, 61, size=(700, d)).astype(np.float32)
+    half[:20] = np.sign(half[:20]) * (np.abs(half[:20]) > 45)        # a few rows close to the middle: it is among their nearest
+    X = np.concatenate([half, -half, np.zeros((1, d), np.float32)])
+    X = X[rng.permutation(len(X))]
+    out, st = knn_in_clusters(torch.from_numpy(X).cuda(), torch.zeros(len(X), dtype=torch.int32, device="cuda"), 1, k, return_stats=True)
+    print(f"  flagged {st['fallback_queries']}", flush=True)
+    ref, _ = ko.in_cluster_knn(X, np.zeros(len(X), np.int32), k)
+    assert np.array_equal(out.cpu().numpy().astype(np.int64), ref)
