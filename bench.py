@@ -550,7 +550,7 @@ def main():
     out["config"]["scatter_path"] = path_name
     out["copy_probe_gbs"] = round(copy_probe_gbs(torch, gib=2, steps=5)["gbs_read_plus_write"], 1)
     # the rate at which this machine serves independent 8-byte gathers from a table the size of the embedding at
-    # 10 M points: E * s such gathers per epoch bound the i.i.d. sampler's edge pass from below (E s / rate)
+    # 10 M points, and what E * s of them would take: an epoch with a gather per negative (the exchange of large embeddings makes none)
     gp = gather_probe_glines(torch, table_mb=80, steps=3)
     out["gather_probe_glines"] = round(gp["g_requests_per_s"], 2)
     out["gather_probe"] = {"table_mb": 80, "requests": gp["requests"], "ms": round(gp["ms"], 3),

@@ -7,7 +7,8 @@
 // Two mappings of edges to lanes:
 //   k_edges_binned / k_edges_pooled (the deterministic epoch): one directed edge per lane, consecutive
 //     lanes on consecutive CSR positions; forces to tails and negatives leave as records binned by
-//     destination tile; head sums are segmented scans in lane order.
+//     destination tile; head sums are segmented scans in lane order.  Large embeddings with the plain sampler:
+//     exchange_kernels.h, small ones: small_kernels.h, with the same arithmetic (edge_math) and the same bits.
 //   k_edges (atomic mode, the loss, and the fallback without binning): a *row group* of LPR adjacent
 //     lanes walks the CSR row of one head i, LPR edges at a time; head sums are reduced inside the
 //     row group with a fixed xor butterfly.
