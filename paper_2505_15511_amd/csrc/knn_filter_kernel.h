@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                      "s_mov_b64 exec, %[all]"
                      : [at] "+v"(at), [all] "=&s"(all)
                      : [key] "v"(key), [thr] "v"(thr), [pos] "v"(pos), [entry] "s"(kEntry)
-                     : "vcc", "memory");
+                     : "vcc", "scc", "memory");
     };
     constexpr bool kSift = L > 2 && !(TILE == 16 && KS > 16);     // (the widest rows' queries fill the registers as it is)
     // step s of the large product: big = the norms and the chunks before, chunk = the present one
