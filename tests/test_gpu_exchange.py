@@ -77,3 +77,29 @@ def test_against_the_oracle():
                          n=n, n_clusters=1, n_neg=s, noise_count=5.0, n_epochs=10, lr0=1.0, seed=77)
     _, g_ref, _ = O.epoch(theta.cpu().numpy(), 0)
     assert grad_err(got[0].cpu().numpy(), g_ref) < GRAD_TOL
+
+
+@pytest.mark.parametrize("kw", [{"tune": {"record_phases": 3}}, {"batches_per_epoch": 2}], ids=["phases", "sub-steps"])
+def test_recorded_epochs(kw):
+    """Every replay of a recorded epoch gives what the eager epochs give, with eager work in between."""
+    n, s = 30_000, 5
+    row_ptr, col, theta = graph(n, 100_000, 6, hub=3_000)
+    want = epochs(n, s, row_ptr, col, theta, exchange=1, **kw)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        tune = dict(kw.get("tune", {}), exchange=1)
+        nm = Nomad(n, 1, s, 5.0, 10, 1.0, 77, tune=tune, stream=side.cuda_stream, batches_per_epoch=kw.get("batches_per_epoch", 1))
+        nm.set_graph(row_ptr, col, None, torch.zeros(n, dtype=torch.int32, device="cuda"), None)
+        nm.set_embedding(theta)
+        recorded = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(recorded, stream=side):
+            nm.epoch(0)
+            nm.epoch(1)
+        for _ in range(3):
+            nm.epoch(2)
+            nm.set_embedding(theta)
+            recorded.replay()
+            side.synchronize()
+            same((nm.get_gradient(device=True), nm.get_embedding(device=True)), want)
+        nm.close()
