@@ -65,7 +65,8 @@ extern "C" int nomad_pca_init(const float* X, int64_t n, int32_t d, float std0, 
     const double tol = 1e-12;
     const int max_steps = 2000;
     if (d <= kSmallDim) {
-        hipLaunchKernelGGL(k_pca_axes_small, dim3(1), dim3(kSmallThreads), 0, st, (const double*)Cm, Q, d, p, tol, max_steps, state);
+        const auto kernel = d <= 32 ? k_pca_axes_small<8> : d <= 64 ? k_pca_axes_small<16> : d <= 96 ? k_pca_axes_small<24> : k_pca_axes_small<kSmallDim / 4>;
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallThreads), 0, st, (const double*)Cm, Q, d, p, tol, max_steps, state);
         KTRY(hipMemcpyAsync(&hstate, state, sizeof(hstate), hipMemcpyDeviceToHost, st));
         KTRY(hipStreamSynchronize(st));
     } else {

@@ -534,19 +534,24 @@ __global__ void __launch_bounds__(kRitzThreads) k_pca_ritz(const double* __restr
 }
 
 // The whole iteration for d <= kSmallDim in one workgroup: the block stays in LDS, a wavefront keeps its 16 rows of C in
-// registers, so a multiplication by C is at most 32 matrix instructions per wavefront and one barrier, about 2 us where a
-// launch over the chip takes 5.
+// registers (STEPS of four columns).  A chain of multiplications by C, each waiting for the one before: all that a wavefront reads of the
+// block is on its way before the first matrix instruction, nothing is behind a branch and no division is left in it.
+// The 4x4x4 instruction works on four blocks, lane l: row (of A) or column (of B) l % 4 of block l / 4 % 4, k = l / 16; it receives
+// row l / 16, column l % 4.  Two blocks of rows and two of columns make 8 x 8 of the product, where half of the 16x16x4 one's
+// columns would be idle.  Five steps at 128 columns 289 -> 246 us (270 with the instruction alone), at 96 231 -> 178, four at 50 139 -> 130.
+template <int STEPS>
 __global__ void __launch_bounds__(kSmallThreads) k_pca_axes_small(const double* __restrict__ C, double* __restrict__ Q, int32_t d, int32_t p,
                                                                   double tol, int32_t max_steps, RitzState* __restrict__ st_out) {
     __shared__ double Y[2][kSmallDim * kRitz];
     __shared__ RitzLds<kSmallThreads> L;
     __shared__ RitzState st;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
-    constexpr int kSteps = kSmallDim / 4;
-    double a[kSteps];
-    const int row0 = wave * 16, arow = row0 + lc;
+    double a[2][STEPS];
+    const int row0 = wave * 16, arow = row0 + 4 * (lc >> 3) + (lc & 3), col = lc & 7, drow = row0 + 4 * (lc >> 3) + lr;
 #pragma unroll
-    for (int s = 0; s < kSteps; ++s) a[s] = arow < d && 4 * s + lr < d ? C[(int64_t)arow * d + 4 * s + lr] : 0.0;
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) a[u][s] = arow + 8 * u < d && 4 * s + lr < d ? C[(int64_t)(arow + 8 * u) * d + 4 * s + lr] : 0.0;
     for (int x = tid; x < kSmallDim * kRitz; x += kSmallThreads) {   // rows beyond d stay zero
         Y[0][x] = x < d * kRitz ? start_entry(x, p) : 0.0;
         Y[1][x] = 0.0;
@@ -554,26 +559,26 @@ __global__ void __launch_bounds__(kSmallThreads) k_pca_axes_small(const double* 
     if (tid == 0) { st = RitzState{}; st.best = 1e300; }
     __syncthreads();
     // Y[to] = C Y[from], or the Chebyshev step with Y[to] holding the iterate before (all threads call)
+    double c = 0.0, inv_e = 0.0;
     auto multiply = [&](int from, int to, bool step) {
         if (row0 < d) {
-            doublex4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
+            double y[STEPS], now[2], before[2];
 #pragma unroll
-            for (int s = 0; s < kSteps; s += 2) {
-                if (4 * s < d) {
-                    const double y0 = lc < kRitz ? Y[from][(4 * s + lr) * kRitz + lc] : 0.0;
-                    const double y1 = lc < kRitz ? Y[from][(4 * s + 4 + lr) * kRitz + lc] : 0.0;
-                    acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], y0, acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s + 1], y1, acc1, 0, 0, 0);
-                }
+            for (int s = 0; s < STEPS; ++s) y[s] = Y[from][(4 * s + lr) * kRitz + col];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                now[u] = Y[from][(drow + 8 * u) * kRitz + col];
+                before[u] = Y[to][(drow + 8 * u) * kRitz + col];
             }
-            if (lc < kRitz) {
-                const double c = st.c, inv_e = step ? 1.0 / st.e : 0.0;
+            double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int x = (row0 + lr + 4 * v) * kRitz + lc;
-                    const double r = acc0[v] + acc1[v];
-                    Y[to][x] = step ? 2.0 * (r - c * Y[from][x]) * inv_e - Y[to][x] : r;
-                }
+            for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) acc[u][s & 1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[u][s], y[s], acc[u][s & 1], 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const double r = acc[u][0] + acc[u][1];
+                Y[to][(drow + 8 * u) * kRitz + col] = step ? 2.0 * (r - c * now[u]) * inv_e - before[u] : r;
             }
         }
         __syncthreads();
@@ -584,6 +589,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_pca_axes_small(const double* 
         ritz_step<kSmallThreads>(Y[q], Y[q ^ 1], C, d, p, L, st);
         if (!(st.resid > tol) || step + 1 == max_steps) break;
         const int degree = st.degree;
+        c = st.c;
+        inv_e = 1.0 / st.e;
         for (int k = 1; k < degree; ++k) { multiply(q ^ 1, q, true); q ^= 1; }
         multiply(q ^ 1, q, false);
         q ^= 1;
