@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(256) k_pca_cov_reduce(const double* __restrict
 // T the Chebyshev polynomial of the interval [0, b] (c = e = b / 2) whose upper end b is the smallest Ritz value of the
 // block: components with eigenvalues in the interval stay bounded by 1, those above it grow like cosh(deg acosh(2 lam / b - 1)).
 // Where C^4 per step needed 28 steps of 139 us for a million points in 128 dimensions (and 40 at flatter spectra), five to
-// eight steps of degree up to kMaxDegree do; a step costs about 15 us now that its 8 x 8 algebra runs on a whole wavefront.
+// eight steps of degree up to kMaxDegree do, with their 8 x 8 algebra on a whole wavefront.
 constexpr int kMaxDegree = 20;
 constexpr int kRitzThreads = 1024; // of the step by itself: one row of the block per thread
 constexpr int kSmallDim = 128;     // up to here the whole iteration is one workgroup (k_pca_axes_small) ...
