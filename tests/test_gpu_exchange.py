@@ -61,6 +61,20 @@ def test_lanes_and_pairs(n, E):
     same(epochs(n, 5, *args, exchange=1, n_epochs=1), epochs(n, 5, *args, exchange=2, n_epochs=1))
 
 
+# runs of about as many references as lanes take of one (64; in the mean 63 and 71), of fewer (53) and of more than twice as many (288)
+@pytest.mark.parametrize("n,s,blocks", [(300_000, 5, 90), (1_060_000, 3, 300), (1_060_000, 5, 300), (1_060_000, 8, 300), (500, 5, 40)])
+def test_runs_longer_than_lanes(n, s, blocks):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + s)
+    E = blocks * BLOCK[s] + 321
+    head = torch.randint(0, n, (E,), generator=g, device="cuda").sort().values
+    col = ((head + 1 + torch.randint(0, n - 1, (E,), generator=g, device="cuda")) % n).to(torch.int32)   # tails anywhere: all runs alike
+    row_ptr = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    row_ptr[1:] = torch.cumsum(torch.bincount(head, minlength=n), 0).to(torch.int32)
+    args = row_ptr, col, 0.5 * torch.randn(n, 2, generator=g, device="cuda")
+    same(epochs(n, s, *args, exchange=1, n_epochs=1), epochs(n, s, *args, exchange=2, n_epochs=1))
+
+
 @pytest.mark.parametrize("tune,kw", [({}, {"batches_per_epoch": 4}), ({"record_phases": 3}, {}), ({"record_phases": 64}, {"batches_per_epoch": 3}),
                                      ({}, {"inverse_rank_weights": True})], ids=["sub-steps", "phases", "both", "ranks"])
 def test_steps_and_weights(tune, kw):
