@@ -71,6 +71,7 @@ struct EdgePlanRequest {
     // pooled sampler (pool_size 0: none); distinct: picks in different lines (modes 1 and 2)
     int32_t pool_size = 0, pool_block = 0, pool_line = 1;
     bool pool_distinct = false;
+    int batches = 1;            // sub-steps of an epoch
     // nomad_tune (0 = the library's choice, except pool_kernel: 1 = use the pooled kernels)
     int tune_edge_block = 0, tune_wg_per_cu = 0, tune_pool_kernel = 1, tune_record_sort = 0, tune_flush_rounds = 0,
         tune_exchange = 0, tune_phases = 0;
@@ -198,10 +199,19 @@ inline int plan_small(const EdgePlanRequest& q, const EdgePlan& p, int compute_u
 
 // Whether a problem of one population takes the exchanged edge pass (exchange_kernels.h), and its tile kernels' shapes.
 //   Which: embeddings beyond two L2s.  The sorted pass gathers a row per negative, and once most gathers miss the L2s they end
-//   at 58 G lines/s; the exchange moves 42 bytes a reference in streams instead.  ms per epoch, sorted -> exchanged: 15 out-neighbours,
-//   symmetrised, s = 5: 100 k points 0.198 -> 0.201, 300 k 0.65 -> 0.78, 700 k 1.59 -> 1.73, 1 M 2.55 -> 2.27, 2 M 6.15 -> 4.56, 5 M 15.3 -> 10.5,
-//   10 M 41.1 -> 29.8; s = 2: 1 M 1.307 -> 1.277, 1.3 M 1.76 -> 1.78, 2 M 2.91 -> 2.53 (fewer gathers an edge, the same streams of
-//   heads and tails).  Up to where a run is shorter than two references: s = 2 at 40 M points 28.9 -> 28.4, s = 5 62.5 -> 55.5.
+//   at 58 G lines/s; the exchange moves 42 bytes a reference in streams instead.  Time of an epoch, exchange over sorted, of the slowest
+//   order of points (numbered cluster by cluster, 15 out-neighbours, symmetrised or not) and of a random one: s = 3, 5, 6, 8 at 800 k points
+//   0.98, 0.97, 1.11, 1.02 (random 0.86 to 0.99), 900 k 0.95, 0.91, 0.99, 0.96 (0.79 to 0.90), 1 M 0.90, 0.87, 0.93, 0.91 (0.76 to 0.84), 1.06 M
+//   0.97, 0.94, 0.97, 0.90 (0.84 to 0.88), 1.2 M 0.93, 0.91, 0.99, 0.91, 2 M 0.79, 0.73, -, 0.74.  s = 2 (fewer gathers an edge, the same
+//   streams of heads and tails) 1 M 0.95 (0.76), 1.2 M 1.01 (0.91), 1.4 M 0.93 (0.80), 1.5 M 0.91 (0.76), 2 M 0.82; s = 1 1.2 M 1.09 (0.84), 1.5 M
+//   1.04 (0.77), 1.8 M 1.01 (0.71), 2 M 0.95.  Smaller ones lose, s = 5 and 8: 100 k 1.07 and
+//   1.13, 300 k 1.16 and 1.21, 600 k 1.08 and 1.12.  Up to where a run is shorter than two
+//   references: s = 2 at 40 M points 28.9 -> 28.4 ms, s = 5 62.5 -> 55.5.
+//   Sub-steps: where points are numbered cluster by cluster the tails of a sub-step lie in a stretch of the tiles, one workgroup of
+//   k_exchange_sums each, and few blocks leave compute units idle.  Exchange over sorted by millions of references a sub-step,
+//   s = 2: 1 M points 1.4 / 1.08 / 1.03 at 2 / 5.6 / 6.4, 2 M 1.18 / 1.01 / 0.83 at 3.2 / 6.4 / 11; s = 3: 1 M 1.25 / 1.05 / 0.9 at 3.2 / 6.3 / 9.2;
+//   s = 5: 1 M 1.24 / 1.07 / 0.81 at 1.9 / 4.6 / 11, 5 M 0.86 / 0.73 at 7.5 / 22; s = 8: 5 M 1.28 / 1.04 / 0.83 at 6.9 / 8.4 / 17; s = 1: 2 M 1.27 / 1.04 / 0.90 at
+//   5 / 10 / 15.  (Random order: 2 M, s = 2 0.91 at 3.8, 1.42 at 1.4.)  The line is at 8.
 //   Rows: runs of about seven references (10 M points) leave as partial sectors; two neighbouring tiles in LDS make them twice
 //   as long (2.79 -> 2.45 ms for 75 M edges; at 5 M points a tile alone is as fast).
 //   Lanes: as many as most runs have references (75 M edges, rows and sums, 16 / 32 / 64 lanes: runs of 7.5 in pairs 2.67 / 2.47 / 2.76 and
@@ -214,12 +224,14 @@ struct ExchangePlan {
     int tile_bits = 0;
 };
 inline size_t exchange_rows_lds_bytes(const ExchangePlan& x) { return (size_t)8 << (x.tile_bits + (x.pairs ? 1 : 0)); }
+constexpr double kExchangeStepReferences = 8e6;
 inline ExchangePlan plan_exchange(const EdgePlanRequest& q, const EdgePlan& p) {
     ExchangePlan x;
     if (q.s < 1 || q.s > 8 || q.E < 1 || q.pool_size || !p.bin_block || q.tune_exchange == 2) return x;
     const double run = (double)exchange_block_edges(q.s) * (q.s + 1) / p.n_bins;   // mean length of a run
     const bool sorted_asked = q.tune_edge_block || q.tune_wg_per_cu || q.tune_record_sort || q.tune_flush_rounds;
-    x.use = q.tune_exchange == 1 || (!sorted_asked && q.n >= (q.s < 3 ? 1500000 : 1000000) && run >= 2);
+    const bool long_steps = q.batches <= 1 || (double)q.E * (q.s + 1) >= kExchangeStepReferences * q.batches;
+    x.use = q.tune_exchange == 1 || (!sorted_asked && q.n >= (q.s < 3 ? 1500000 : 1000000) && long_steps && run >= 2);
     if (exchange_deal_lds_bytes(q.s, p.n_bins) > kMaxLdsBytes) x.use = false;
     x.tile_bits = p.tile_bits;
     x.pairs = run < 12;

@@ -13,12 +13,13 @@ DRIVER = r"""
 #include <stdlib.h>
 #include "edge_plan.h"
 using namespace nomad;
-// argv: n E s pool_size tune_exchange tune_record_sort
+// argv: n E s pool_size tune_exchange tune_record_sort [batches]
 int main(int argc, char** argv) {
-    if (argc != 7) return 2;
+    if (argc != 7 && argc != 8) return 2;
     EdgePlanRequest q;
     q.n = atoll(argv[1]); q.E = atoll(argv[2]); q.s = atoi(argv[3]); q.pool_size = atoi(argv[4]); q.pool_block = q.pool_size ? 4096 : 0;
     q.tune_exchange = atoi(argv[5]); q.tune_record_sort = atoi(argv[6]);
+    if (argc == 8) q.batches = atoi(argv[7]);
     EdgePlan p = plan_edge_pass(q);
     fit_tiles(p, q, 256, true);
     const ExchangePlan x = plan_exchange(q, p);
@@ -39,8 +40,8 @@ def planner(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2505_15511_amd", "csrc"), str(src), "-o", str(exe)],
                    check=True, capture_output=True, text=True)
 
-    def plan(n, s=5, E=None, pool=0, exchange=0, sort=0):
-        out = subprocess.run([str(exe)] + [str(int(v)) for v in (n, 15 * n if E is None else E, s, pool, exchange, sort)], check=True, capture_output=True, text=True)
+    def plan(n, s=5, E=None, pool=0, exchange=0, sort=0, batches=1):
+        out = subprocess.run([str(exe)] + [str(int(v)) for v in (n, 15 * n if E is None else E, s, pool, exchange, sort, batches)], check=True, capture_output=True, text=True)
         return json.loads(out.stdout)
     return plan
 
@@ -53,6 +54,15 @@ def test_the_line(planner):
     assert planner(60_000_000, s=2)["use"] == 0                      # runs shorter than two references
     assert planner(10_000_000, sort=1)["use"] == 0 and planner(10_000_000, exchange=2)["use"] == 0
     assert planner(2_000, exchange=1)["use"] == 1 and planner(10_000_000, exchange=1, sort=1)["use"] == 1
+
+
+@pytest.mark.parametrize("s", range(1, 9))
+def test_short_sub_steps_stay_on_the_sorted_pass(planner, s):
+    n, E = 4_000_000, 60_000_000
+    most = E * (s + 1) // 8_000_000                                  # sub-steps of eight million references
+    assert planner(n, s, E, batches=1)["use"] == planner(n, s, E, batches=most)["use"] == 1
+    assert planner(n, s, E, batches=most + 1)["use"] == 0
+    assert planner(n, s, 3_000_000, batches=1)["use"] == 1 and planner(n, s, E, exchange=1, batches=10_000)["use"] == 1
 
 
 @pytest.mark.parametrize("s", range(1, 9))
