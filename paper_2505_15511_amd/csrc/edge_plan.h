@@ -71,6 +71,7 @@ struct EdgePlanRequest {
     // pooled sampler (pool_size 0: none); distinct: picks in different lines (modes 1 and 2)
     int32_t pool_size = 0, pool_block = 0, pool_line = 1;
     bool pool_distinct = false;
+    bool far = false;           // groups whose far cells are sampled
     int batches = 1;            // sub-steps of an epoch
     // nomad_tune (0 = the library's choice, except pool_kernel: 1 = use the pooled kernels)
     int tune_edge_block = 0, tune_wg_per_cu = 0, tune_pool_kernel = 1, tune_record_sort = 0, tune_flush_rounds = 0,
@@ -181,20 +182,35 @@ inline int plan_record_phases(int64_t E, int s, int bin_block, int tune_phases) 
     return phases < 1 ? 1 : phases;
 }
 
-// Whether a problem takes the edge pass that sums in LDS (small_kernels.h), and its workgroups (0: no).  Every embedding whose sums fit
+// Whether a problem takes the edge pass that sums in LDS (small_kernels.h), and its workgroups (0: no).  Embeddings whose sums fit
 // one workgroup's LDS: whole epoch, records -> sums in LDS, us: 2,000 points and 47 k positions 19.1 -> 10.4 (s = 2: 17.0 -> 9.8, s = 8: 21.6 -> 11.8),
 // 5,000 29.7 -> 17.4, 8,000 33.2 -> 21.5, 10,000 39.6 -> 26.0 (80 k positions, s = 2: 22.5 -> 18.1).
 // Workgroups: a round of 1,024 positions costs 3.8 us, a megabyte of sums written and read back half of one: as many workgroups as there are
-// rounds until their sums are 12 MB (8,000 points: 6 MB 25.8 us, 12 MB 21.5, 16 MB 21.9; 5,000: 16.8, 17.4, 17.6).
+// rounds until their sums are 12 MB (8,000 points: 6 MB 25.8 us, 12 MB 21.5, 16 MB 21.9; 5,000: 16.8, 17.4, 17.6).  Where that makes some
+// do two rounds, half as many as there are rounds do two each, with half the sums (0.85 to 0.96 of an epoch of 5,000 to 10,200 points).
+// Not where so few workgroups (fewer than 150: from 5,243 points on) have more to do than what records cost on all compute units:
+//   sampled far field, whose rounds are long (negatives are resolved one by one).  Rounds of a workgroup here / with records, time over that
+//   of records, s = 2: 8,000 points 3 / 1 0.84, 10 / 4 0.99, 20 / 8 1.06, 10,200 8 / 3 0.96, 6 / 2 1.04, 26 / 9 1.26, 33 / 10 1.44; s = 5: 6,000 6 / 3
+//   0.89, 8,000 4 / 2 0.96, 5 / 2 1.04, 20 / 8 1.25; s = 8: 6,000 3 / 2 0.86, 8,000 4 / 2 0.98, 5 / 2 1.11, 20 / 8 1.32; with fewer than 96 workgroups
+//   (from 8,192 points) s = 5 and 8 2 / 1 1.01 to 1.24, 4 / 2 0.97 to 1.03;
+//   no negatives, where records are one an edge: one round a workgroup, sums of up to 8 MB 0.71 to 0.92, 9 to 14 MB 1.04 to 1.13; two
+//   rounds 0.75 to 0.92, with fewer than 96 workgroups 1.00 to 1.19; more 0.85 to 1.0.
+// (All others: 0.45 to 0.99; s = 1 at 10,200 points up to 1.05.)
 constexpr int kSmallLanes = 1024;
 NOMAD_HOST_DEVICE inline size_t small_lds_bytes(int64_t n) { return (size_t)n * 16; }
 inline int plan_small(const EdgePlanRequest& q, const EdgePlan& p, int compute_units) {
     const bool sorted_asked = q.tune_edge_block || q.tune_wg_per_cu || q.tune_record_sort || q.tune_flush_rounds || q.tune_phases || q.tune_exchange;
     if (q.s < 0 || q.s > 8 || q.E < 1 || q.pool_size || !p.bin_block || sorted_asked || q.n < 1 || small_lds_bytes(q.n) > kMaxLdsBytes) return 0;
     const int64_t rounds = (q.E + kSmallLanes - 1) / kSmallLanes, room = (int64_t)(12 << 20) / (int64_t)small_lds_bytes(q.n);
-    int64_t wg = rounds < compute_units ? rounds : compute_units;
-    if (wg > room) wg = room;
-    return wg < 1 ? 1 : (int)wg;
+    const int64_t per = (rounds + room - 1) / room, records_per = (rounds + compute_units - 1) / compute_units;   // rounds of a workgroup
+    if (room < 150) {
+        if (q.far && q.s <= 3 && records_per > 4 && 2 * per >= 5 * records_per) return 0;
+        if (q.far && q.s > 3 && (per > 2 * records_per || (room < 96 && per == 2))) return 0;
+        if (q.s == 0 && rounds * (int64_t)small_lds_bytes(q.n) > (8 << 20) && (per == 1 || (room < 96 && per == 2))) return 0;
+    }
+    int64_t wg = rounds < room ? rounds : room;
+    if (per == 2 && room < compute_units) wg = (rounds + 1) / 2;
+    return (int)(wg < compute_units ? wg : compute_units);
 }
 
 // Whether a problem of one population takes the exchanged edge pass (exchange_kernels.h), and its tile kernels' shapes.

@@ -795,6 +795,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         want_plan.n = n; want_plan.E = E; want_plan.s = s;
         want_plan.pool_size = c->cfg.pool_size; want_plan.pool_block = c->cfg.pool_block; want_plan.pool_line = std::max(1, c->cfg.pool_line);
         want_plan.pool_distinct = c->cfg.pool_mode != NOMAD_POOL_PICKS16;
+        want_plan.far = edge_kind(c) == kFarEdges;
         want_plan.batches = c->cfg.batches_per_epoch;
         want_plan.tune_edge_block = c->tune_edge_block; want_plan.tune_wg_per_cu = c->tune_wg_per_cu;
         want_plan.tune_pool_kernel = c->tune_pool_kernel; want_plan.tune_record_sort = c->tune_record_sort;

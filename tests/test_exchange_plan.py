@@ -85,7 +85,7 @@ SMALL = r"""
 using namespace nomad;
 int main(int argc, char** argv) {
     EdgePlanRequest q;
-    q.n = atoll(argv[1]); q.E = atoll(argv[2]); q.s = atoi(argv[3]); q.pool_size = atoi(argv[4]); q.pool_block = q.pool_size ? 4096 : 0; q.tune_phases = atoi(argv[5]);
+    q.n = atoll(argv[1]); q.E = atoll(argv[2]); q.s = atoi(argv[3]); q.pool_size = atoi(argv[4]); q.pool_block = q.pool_size ? 4096 : 0; q.tune_phases = atoi(argv[5]); q.far = argc > 6 && atoi(argv[6]);
     EdgePlan p = plan_edge_pass(q);
     fit_tiles(p, q, 256, true);
     printf("%d %zu %zu\n", plan_small(q, p, 256), small_lds_bytes(q.n), kMaxLdsBytes);
@@ -100,8 +100,8 @@ def test_sums_in_lds(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2505_15511_amd", "csrc"), str(tmp_path / "small.cpp"), "-o",
                     str(tmp_path / "small")], check=True, capture_output=True, text=True)
 
-    def plan(n, E, s=5, pool=0, phases=0):
-        wg, lds, most = map(int, subprocess.run([str(tmp_path / "small")] + [str(v) for v in (n, E, s, pool, phases)], check=True, capture_output=True,
+    def plan(n, E, s=5, pool=0, phases=0, far=0):
+        wg, lds, most = map(int, subprocess.run([str(tmp_path / "small")] + [str(v) for v in (n, E, s, pool, phases, far)], check=True, capture_output=True,
                                                 text=True).stdout.split())
         assert wg == 0 or lds <= most
         return wg
@@ -110,3 +110,12 @@ def test_sums_in_lds(tmp_path):
     for n in (5_000, 8_000, 10_224):
         assert plan(n, 10 ** 6) * 16 * n <= 12 << 20
     assert plan(2_000, 46_734, s=9) == plan(2_000, 46_734, pool=1024) == plan(2_000, 46_734, phases=2) == plan(2_000, 0) == 0
+    # one round more than there is room for: all do two, with half the sums
+    assert plan(10_200, 77 * 1024) == 77 and plan(10_200, 77 * 1024 + 1) == 39 and plan(10_200, 3 * 77 * 1024) == 77 and plan(2_000, 300 * 1024) == 256
+    # sampled far field: records where a workgroup had too many rounds
+    for n, s, records, lds in ((8_000, 2, 20 * 8_000, 250 * 8_000), (8_000, 8, 45 * 8_000, 60 * 8_000), (9_000, 8, 4 * 9_000, 12 * 9_000), (10_200, 5, 4 * 10_200, 45 * 10_200)):
+        assert plan(n, records, s, far=1) > 0 and plan(n, lds, s, far=1) == 0 and plan(n, lds, s) > 0
+    assert all(plan(5_242, k * 5_242, s, far=1) > 0 for k in (1, 30, 500) for s in range(9))
+    # no negatives
+    assert plan(9_000, 4 * 9_000, 0) > 0 and plan(9_000, 8 * 9_000, 0) == 0 and plan(9_000, 12 * 9_000, 0) == 0 and plan(9_000, 30 * 9_000, 0) > 0
+    assert plan(7_000, 12 * 7_000, 0) == 0 and plan(7_000, 20 * 7_000, 0) > 0 and plan(5_000, 20 * 5_000, 0) > 0
