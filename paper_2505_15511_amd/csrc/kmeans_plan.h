@@ -1,0 +1,29 @@
+// libnomad: which steps of Lloyd's iterations take one launch, plain C++ (a test compiles it with the host compiler).
+// Times in this file: per iteration, one launch less the launches it stands for, one MI355X, Gaussian mixtures.
+#pragma once
+#include <stdint.h>
+
+namespace nomad_knn {
+
+// The M step in one launch (k_mean_small) instead of a sort by label, its scans and the sums.  It saves 10 to 30 us where
+//   clusters are short, because a workgroup adds its centroid's rows one after the other: 512 points a cluster on average (16,000 points, K = 32
+//   -10 to +5 us, K = 10 +4 to +68; 8,000, K = 10 -19 to +12, K = 2 +67 to +86; 4,000, K = 10 -8 to -26, K = 2 +30 to +41);
+//   the workgroups, one a centroid and 64 columns, are not many rounds of the chip: 1,024 (4,000 points, K = 512, d = 128 -23, K = 256, d = 300
+//   +2, K = 512, d = 768 +36; 2,000 points, K = 128, d = 768 -2);
+//   the labels, which every workgroup reads, are not much: 2^23 of them (16,000 points, d <= 64, K = 512 -17 to -21, K = 1,024 +2 to +6; K = 256, d = 128
+//   +2, d = 300 +33; K = 64, d = 300 -14, d = 768 +4; 16,000 points, K = 2,000, d = 768 +900: 6.8 ms a call for 2.0).
+constexpr int64_t kSmallMeanPoints = 16384;   // (the workgroup's list of them is 16-bit, in LDS)
+inline bool mean_in_one_launch(int64_t n, int64_t K, int64_t d) {
+    const int64_t workgroups = K * ((d + 63) / 64);
+    return n <= kSmallMeanPoints && n <= 512 * K && workgroups <= 1024 && n * workgroups <= ((int64_t)1 << 23);
+}
+
+// Clearing, norms, packing and the copy of the centroids in one launch (k_kmeans_prepare)
+constexpr int64_t kPrepareValues = 65536;
+inline bool prepare_in_one_launch(int64_t K, int64_t d) { return K * d <= kPrepareValues; }
+
+// What the filter leaves open goes to the exact path at once, over all K centroids, instead of to the candidates' refinement first: a
+// launch less.  Up to 16,384 points -2 to -10 us, wide rows to -40; from K = 1,024 on -10 to +55.
+inline bool open_points_are_few(int64_t n, int64_t K) { return n <= 16384 && K <= 512; }
+
+}  // namespace nomad_knn

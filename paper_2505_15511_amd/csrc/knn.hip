@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "host_util.h"
+#include "kmeans_plan.h"
 #include "knn_filter.h"
 #include "knn_kernels.h"
 #include "metrics_kernels.h"
@@ -113,7 +114,7 @@ int nearest_in_groups(hipStream_t st, Buffers& buf, const KnnSets& P, const KnnB
 
 // The nearest candidate of every query (one group).  Work space: cand [n_q * 128 / tile], tau, todo, flagged [n_q],
 // counters [2] (queries the filter left open, queries for the exact path), both zero.  few: what the filter leaves open goes to
-// the exact path at once (a launch less; of a few thousand queries a few hundred).  Query positions are query rows here.
+// the exact path at once (kmeans_plan.h).  Query positions are query rows here.
 int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* blocks, uint32_t n_blocks, int waves, bool few, int32_t* cand, float* tau,
                 int32_t* todo, int32_t* flagged, uint32_t* counters, int32_t* out) {
     KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, nullptr, tau, few ? KnnAssign{out, flagged, counters + 1} : KnnAssign{out, todo, counters}));
@@ -151,7 +152,7 @@ struct MeanStep {
 
     int init(Buffers& buf, int64_t n_, int32_t K_, int32_t d_) {
         n = n_; K = K_; d = d_;
-        small = n <= kSmallMeanPoints && n * K <= ((int64_t)1 << 25);   // (every workgroup reads all labels)
+        small = mean_in_one_launch(n, K, d);
         if (small) return NOMAD_OK;
         int bits = 1;
         while (((int64_t)1 << bits) < K) ++bits;
@@ -392,7 +393,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     int32_t *cur = new_lab, *prev = dLab;
     HostWord hchanged[2];
     for (auto& h : hchanged) KTRY(h.take());
-    const bool prepare = (int64_t)K * d <= kPrepareValues;
+    const bool prepare = prepare_in_one_launch(K, d), few = open_points_are_few(n, K);
     int32_t it = 0;
     while (it < max_iters) {
         // E step: the nearest centroid of every point, exactly
@@ -405,7 +406,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
             cents.fill(st, dC, d, nullptr, centre, max_cen, max_pts, cnorm);
             KTRY(hipMemcpyAsync(c_used, dC, sizeof(float) * (size_t)K * d, hipMemcpyDeviceToDevice, st));
         }
-        int rc = nearest_one(st, P, points.tile, blocks, (uint32_t)hblocks.size(), waves, m_step.small, cand, tau, todo, flagged, counters, cur);
+        int rc = nearest_one(st, P, points.tile, blocks, (uint32_t)hblocks.size(), waves, few, cand, tau, todo, flagged, counters, cur);
         if (rc) return rc;
         ++it;
         const int32_t* before = it > 1 ? prev : nullptr;

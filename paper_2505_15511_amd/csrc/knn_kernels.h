@@ -304,9 +304,8 @@ __global__ void __launch_bounds__(256) k_knn_pack(const float* __restrict__ X, i
 
 // What an E step of Lloyd's iterations starts with, one workgroup per tile of centroids: the words that count from zero, the
 // centroids' norms and the largest of them, the packed tile, and the copy the inertia is computed from.  Every workgroup reads all K rows
-// for the largest norm, so this is for up to kPrepareValues values; beyond, the norms, the packing, the clearing and the copy are
-// launches of their own (four of 3 to 4 us and their gaps; one of 5).
-constexpr int64_t kPrepareValues = 65536;
+// for the largest norm, so this is for few and short ones (prepare_in_one_launch); beyond, the norms, the packing, the clearing and the copy
+// are launches of their own (four of 3 to 4 us and their gaps; one of 5).
 __global__ void __launch_bounds__(1024) k_kmeans_prepare(const float* __restrict__ C, int32_t K, int32_t d, const float* __restrict__ centre,
                                                         const uint32_t* __restrict__ point_bits, int32_t tile, int32_t steps, uint4* __restrict__ data,
                                                         float* __restrict__ norm, float* __restrict__ c_used, uint32_t* __restrict__ zeros, int32_t n_zeros,
@@ -888,8 +887,7 @@ __global__ void __launch_bounds__(256) k_kmeans_update(const float* __restrict__
 // The M step of a small set in one launch, a workgroup per centroid and 64 columns: it finds the centroid's points among the labels
 // itself, in order; four wavefronts bring 64 rows to LDS at a time, one adds them, a column a lane.  With prev it also counts the
 // labels that changed; the last workgroup hands the count to the host.  Against the sort, its scans and the sums as launches of their
-// own: eight for one.
-constexpr int64_t kSmallMeanPoints = 16384;
+// own: eight for one (mean_in_one_launch says where that pays).
 __global__ void __launch_bounds__(256) k_mean_small(const float* __restrict__ X, int32_t n, int32_t d, const int32_t* __restrict__ labels, const int32_t* __restrict__ prev,
                                                     float* __restrict__ C, unsigned long long* __restrict__ changed, unsigned long long* __restrict__ changed_host) {
     extern __shared__ uint16_t ids[];   // [n] the points of this centroid, ascending

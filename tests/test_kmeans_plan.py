@@ -1,0 +1,50 @@
+"""Where steps of Lloyd's iterations take one launch (csrc/kmeans_plan.h, compiled on the host): both sides of every line."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PROGRAM = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "kmeans_plan.h"
+using namespace nomad_knn;
+int main(int argc, char** argv) {   // triples n K d
+    for (int a = 1; a + 2 < argc; a += 3) {
+        const int64_t n = atoll(argv[a]), K = atoll(argv[a + 1]), d = atoll(argv[a + 2]);
+        printf("%d %d %d\n", (int)mean_in_one_launch(n, K, d), (int)prepare_in_one_launch(K, d), (int)open_points_are_few(n, K));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("kmeans_plan")
+    (d / "plan.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2505_15511_amd", "csrc"), str(d / "plan.cpp"), "-o", str(d / "plan")],
+                   check=True, capture_output=True, text=True)
+
+    def of(n, K, d_):
+        out = subprocess.run([str(d / "plan"), str(n), str(K), str(d_)], check=True, capture_output=True, text=True).stdout.split()
+        return [bool(int(x)) for x in out]
+    return of
+
+
+def test_means(rules):
+    assert rules(3_001, 10, 50)[0] and rules(1, 1, 1)[0]
+    assert rules(16_384, 32, 64)[0] and not rules(16_385, 64, 64)[0]                  # points
+    assert rules(5_120, 10, 64)[0] and not rules(5_121, 10, 64)[0]                    # points a cluster
+    assert rules(4_000, 512, 128)[0] and not rules(4_000, 512, 129)[0]                # workgroups
+    assert rules(2_048, 1_024, 64)[0] and not rules(2_048, 1_025, 64)[0]
+    assert rules(16_384, 512, 64)[0] and not rules(16_384, 513, 64)[0]                # labels read
+    assert not rules(16_384, 2_000, 768)[0] and not rules(16_384, 2_147_483_647, 768)[0]
+
+
+def test_centroids(rules):
+    assert rules(5_000, 85, 768)[1] and not rules(5_000, 86, 768)[1]                  # values
+
+
+def test_open_points(rules):
+    assert rules(16_384, 512, 768)[2] and not rules(16_385, 2, 2)[2] and not rules(16_384, 513, 2)[2]
