@@ -18,9 +18,10 @@ inline bool mean_in_one_launch(int64_t n, int64_t K, int64_t d) {
     return n <= kSmallMeanPoints && n <= 512 * K && workgroups <= 1024 && n * workgroups <= ((int64_t)1 << 23);
 }
 
-// Clearing, norms, packing and the copy of the centroids in one launch (k_kmeans_prepare)
-constexpr int64_t kPrepareValues = 65536;
-inline bool prepare_in_one_launch(int64_t K, int64_t d) { return K * d <= kPrepareValues; }
+// Clearing, norms, packing and the copy of the centroids in one launch (k_kmeans_prepare), whose every workgroup reads all K rows, 64
+// at a time: -6 to -13 us up to K = 128, -1 to -8 at 512, +4 at 1,024, +15 at 2,048, +38 at 4,096 (d = 2 to 64), +83 at 8,192.
+constexpr int64_t kPrepareValues = 65536;     // (128 x 768 -4, 256 x 300 -3: there by a margin)
+inline bool prepare_in_one_launch(int64_t K, int64_t d) { return K <= 512 && K * d <= kPrepareValues; }
 
 // What the filter leaves open goes to the exact path at once, over all K centroids, instead of to the candidates' refinement first: a
 // launch less.  Up to 16,384 points -2 to -10 us, wide rows to -40; from K = 1,024 on -10 to +55.

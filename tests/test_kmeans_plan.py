@@ -43,6 +43,7 @@ def test_means(rules):
 
 
 def test_centroids(rules):
+    assert rules(5_000, 512, 128)[1] and not rules(5_000, 513, 2)[1]                  # rows
     assert rules(5_000, 85, 768)[1] and not rules(5_000, 86, 768)[1]                  # values
 
 
