@@ -262,6 +262,21 @@ int64_t nomad_num_edges(const nomad_ctx* ctx);
 #define NOMAD_PATH_FIXED_ATOMICS 4
 int nomad_scatter_path(const nomad_ctx* ctx);
 
+/* Which edge pass nomad_epoch runs after nomad_set_graph (0 before it):
+ *   NOMAD_EDGES_ROWS      a group of lanes per row, global atomics (NOMAD_PATH_ATOMIC_FP32, NOMAD_PATH_FIXED_ATOMICS)
+ *   NOMAD_EDGES_RECORDS   an edge per lane, forces as records by tile (NOMAD_PATH_BINNED)
+ *   NOMAD_EDGES_POOLED    the pooled samplers' own (NOMAD_PATH_BINNED_POOLED)
+ *   NOMAD_EDGES_EXCHANGED embedding rows and forces exchanged tile by tile (NOMAD_PATH_BINNED, the same bits as records)
+ *   NOMAD_EDGES_LDS_SUMS  the forces of a small embedding summed in LDS (NOMAD_PATH_BINNED, the same bits as records)
+ * Where one of the last two could not get its memory, nomad_set_graph goes on with records and nomad_last_error says so.
+ */
+#define NOMAD_EDGES_ROWS 1
+#define NOMAD_EDGES_RECORDS 2
+#define NOMAD_EDGES_POOLED 3
+#define NOMAD_EDGES_EXCHANGED 4
+#define NOMAD_EDGES_LDS_SUMS 5
+int nomad_edge_pass(const nomad_ctx* ctx);
+
 /* Device memory the context holds, in bytes (graph, embedding, work space; 0 before nomad_set_graph).  Blocks taken over
  * from earlier contexts and calls count at their full size, up to half as large again (and 64 KB) as what was needed. */
 int64_t nomad_device_bytes(const nomad_ctx* ctx);
@@ -501,7 +516,7 @@ int nomad_pca_init(const float* X, int64_t n, int32_t d, float std0, float* thet
                    void* stream);
 
 /* Text of the last error of this context ("" if none), or, after a successful nomad_set_graph that had to take a
- * slower path, the reason (see nomad_scatter_path).  Valid until the next call on it. */
+ * slower path, the reason (see nomad_scatter_path, nomad_edge_pass).  Valid until the next call on it. */
 const char* nomad_last_error(const nomad_ctx* ctx);
 
 #ifdef __cplusplus

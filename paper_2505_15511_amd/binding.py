@@ -23,7 +23,7 @@ ERRORS = {-1: "NOMAD_E_INVALID_ARG", -2: "NOMAD_E_BAD_GRAPH", -3: "NOMAD_E_ORDER
 
 EXPORTS = ["nomad_create", "nomad_destroy", "nomad_set_graph", "nomad_set_embedding", "nomad_epoch", "nomad_loss",
            "nomad_get_embedding", "nomad_get_gradient", "nomad_get_negatives", "nomad_get_means",
-           "nomad_get_mean_field", "nomad_num_edges", "nomad_scatter_path", "nomad_device_bytes", "nomad_release_memory", "nomad_tune", "nomad_profile", "nomad_profile_read", "nomad_last_error",
+           "nomad_get_mean_field", "nomad_num_edges", "nomad_scatter_path", "nomad_edge_pass", "nomad_device_bytes", "nomad_release_memory", "nomad_tune", "nomad_profile", "nomad_profile_read", "nomad_last_error",
            "nomad_copy_probe", "nomad_gather_probe", "nomad_scatter_probe", "nomad_knn_in_clusters", "nomad_kmeans_lloyd", "nomad_neighbourhood_preservation",
            "nomad_random_triplet_accuracy", "nomad_random_triplet_accuracy_noalloc", "nomad_pca_init", "nomad_kmeans_lsh_init"]
 
@@ -38,6 +38,7 @@ class NomadConfig(C.Structure):
 
 
 PATH_ATOMIC_FP32, PATH_BINNED, PATH_BINNED_POOLED, PATH_FIXED_ATOMICS = 1, 2, 3, 4
+EDGES_ROWS, EDGES_RECORDS, EDGES_POOLED, EDGES_EXCHANGED, EDGES_LDS_SUMS = 1, 2, 3, 4, 5
 PATH_NAMES = {0: "none", 1: "atomic_fp32", 2: "binned", 3: "binned_pooled", 4: "fixed_point_atomics"}
 TUNE = {"edge_block": 1, "workgroups_per_cu": 2, "scatter_path": 3, "pool_kernel": 4, "record_phases": 5, "record_sort": 6, "flush_rounds": 7, "exchange": 8}
 POOL_PICKS16, POOL_DISTINCT, POOL_STRATIFIED = 0, 1, 2
@@ -80,6 +81,7 @@ def load_library():
     lib.nomad_num_edges.argtypes = [vp]
     lib.nomad_num_edges.restype = i64
     lib.nomad_scatter_path.argtypes = [vp]
+    lib.nomad_edge_pass.argtypes = [vp]
     lib.nomad_device_bytes.argtypes = [vp]
     lib.nomad_device_bytes.restype = i64
     lib.nomad_release_memory.argtypes = []
@@ -482,6 +484,10 @@ class Nomad:
     def scatter_path(self):
         """nomad_scatter_path: one of the PATH_* constants."""
         return int(self.lib.nomad_scatter_path(self.ctx))
+
+    def edge_pass(self):
+        """nomad_edge_pass: one of the EDGES_* constants."""
+        return int(self.lib.nomad_edge_pass(self.ctx))
 
     def device_bytes(self):
         return int(self.lib.nomad_device_bytes(self.ctx))

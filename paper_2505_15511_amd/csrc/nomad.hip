@@ -823,6 +823,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
             c->binned = true;
         } else if (small_wg) {   // records remain
             (void)hipGetLastError();
+            fallback_note = "records in place of sums in LDS, whose work space could not be allocated: " + c->err;
             dev_free(c, c->small_sums);
             dev_free(c, c->head);
         }
@@ -847,6 +848,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 c->binned = c->exchange = true;
             } else {   // the sorted edge pass remains
                 (void)hipGetLastError();
+                fallback_note = "the sorted edge pass in place of the exchanged one, whose work space could not be set up: " + (c->err.empty() ? "size out of range" : c->err);
                 free_exchange(c);
                 dev_free(c, c->head); dev_free(c, c->carry);
                 c->phases = 1;
@@ -934,6 +936,12 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
 }
 
 int nomad_scatter_path(const nomad_ctx* c) { return c ? c->path : 0; }
+
+int nomad_edge_pass(const nomad_ctx* c) {
+    if (!c || !c->path) return 0;
+    return !c->binned ? NOMAD_EDGES_ROWS : c->small_wg ? NOMAD_EDGES_LDS_SUMS : c->exchange ? NOMAD_EDGES_EXCHANGED
+           : c->pool_rounds ? NOMAD_EDGES_POOLED : NOMAD_EDGES_RECORDS;
+}
 
 int64_t nomad_device_bytes(const nomad_ctx* c) { return c ? c->device_bytes : 0; }
 

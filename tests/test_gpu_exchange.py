@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from oracle import c_oracle
-from paper_2505_15511_amd import Nomad
+from paper_2505_15511_amd import EDGES_EXCHANGED, EDGES_LDS_SUMS, EDGES_POOLED, EDGES_RECORDS, EDGES_ROWS, SCATTER_ATOMIC, Nomad
 from tests.test_gpu_parity import GRAD_TOL, grad_err
 
 pytestmark = pytest.mark.gpu
@@ -30,6 +30,7 @@ def graph(n, E, seed, hub=0):
 def epochs(n, s, row_ptr, col, theta, exchange, tune=None, weights=None, n_epochs=2, **kw):
     nm = Nomad(n, 1, s, 5.0, 10, 1.0, 77, tune=dict(tune or {}, exchange=exchange), **kw)
     nm.set_graph(row_ptr, col, weights, torch.zeros(n, dtype=torch.int32, device="cuda"), None)
+    assert nm.edge_pass() == (EDGES_EXCHANGED if exchange == 1 else EDGES_RECORDS) and nm.note() == ""
     nm.set_embedding(theta)
     for t in range(n_epochs):
         nm.epoch(t)
@@ -80,6 +81,20 @@ def test_runs_longer_than_lanes(n, s, blocks):
 def test_steps_and_weights(tune, kw):
     args = graph(30_000, 200_000, 5, hub=3_000)
     same(epochs(30_000, 5, *args, exchange=1, tune=tune, **kw), epochs(30_000, 5, *args, exchange=2, tune=tune, **kw))
+
+
+@pytest.mark.parametrize("n,s,kw,want", [
+    (2_000, 5, {}, EDGES_LDS_SUMS), (10_225, 5, {}, EDGES_RECORDS), (300_000, 5, {}, EDGES_RECORDS), (1_000_000, 5, {}, EDGES_EXCHANGED),
+    (1_000_000, 2, {}, EDGES_RECORDS), (1_500_000, 2, {}, EDGES_EXCHANGED), (1_000_000, 5, {"batches_per_epoch": 3}, EDGES_RECORDS),
+    (1_000_000, 9, {}, EDGES_ROWS), (1_000_000, 5, {"scatter_mode": SCATTER_ATOMIC}, EDGES_ROWS),
+    (1_000_000, 5, {"pool_size": 1024, "pool_block": 4096}, EDGES_POOLED), (1_000_000, 5, {"tune": {"record_sort": 1}}, EDGES_RECORDS)])
+def test_which_pass(n, s, kw, want):
+    row_ptr, col, _ = graph(n, 3_000_000, n)
+    nm = Nomad(n, 1, s, 5.0, 10, 1.0, 77, **kw)
+    assert nm.edge_pass() == 0
+    nm.set_graph(row_ptr, col, None, torch.zeros(n, dtype=torch.int32, device="cuda"), None)
+    assert nm.edge_pass() == want
+    nm.close()
 
 
 def test_against_the_oracle():

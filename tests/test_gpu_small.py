@@ -2,7 +2,7 @@
 import pytest
 import torch
 
-from paper_2505_15511_amd import Nomad
+from paper_2505_15511_amd import EDGES_LDS_SUMS, EDGES_RECORDS, Nomad
 from tests.test_gpu_exchange import graph, same
 
 pytestmark = pytest.mark.gpu
@@ -13,6 +13,7 @@ def epochs(n, s, args, tune, R=1, groups=None, n_epochs=2, **kw):
     nm = Nomad(n, R, s, 5.0, 10, 1.0, 77, tune=tune, **kw)
     cluster = (torch.arange(n, device="cuda") * R // n).to(torch.int32)
     nm.set_graph(row_ptr, col, None, cluster, groups)
+    assert nm.edge_pass() == (EDGES_RECORDS if tune else EDGES_LDS_SUMS) and nm.note() == ""
     nm.set_embedding(theta)
     for t in range(n_epochs):
         nm.epoch(t)
