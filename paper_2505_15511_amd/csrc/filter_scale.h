@@ -48,14 +48,15 @@ NOMAD_BOTH bool knn_filter_usable(uint32_t q_bits, uint32_t c_bits) {
 //                came out as zero is multiplied as zero: at most 4 d 2^-150 < 1e-40 in the key (next to a larger side:
 //                2 sqrt(d) 2^-75 sqrt(M), inside the products' term)
 // chunk > 0: the large products are summed `chunk` columns at a time, the first chunk on top of |c|^2 / 2, and the chunks' sums
-// added up; the norm is sixteen sums side by side.  Then
+// added up; the norm is kNormLanes sums side by side, each of at most 4 ceil(d / 64) squares, added pairwise.  Then
 //   sums         inside a chunk `chunk` additions of at most 2 u of the chunk's own magnitudes, which add up to 3/2 M at most over
 //                the chunks (Cauchy-Schwarz); a rounding of u 3/2 M a chunk and one for the small products; doubled in the key:
 //                6 chunk u M + 3 (d / chunk + 2) u M; the two small products' own sums are 2^-10 of 8 d u M
-//   norm         (d / 16 + 10) u M
+//   norm         4 ceil(d / 64) + 4 additions: (d / 16 + 10) u M
 // which for 768 columns in chunks of 64 is a tenth of the bound for one sum, for 128 columns half of it.
+constexpr int kNormLanes = 16;   // lanes that share a row's norm
 NOMAD_BOTH double knn_filter_eps(int32_t d, double M, int32_t chunk = 0) {
-    const double units = chunk > 0 ? 6.0 * (double)(chunk + 1) + 3.0 * ((double)d / (double)chunk + 2.0) + (double)d / 16.0 + 10.0 + (double)d / 64.0 + 64.0
+    const double units = chunk > 0 ? 6.0 * (double)(chunk + 1) + 3.0 * ((double)d / (double)chunk + 2.0) + (double)d / (double)kNormLanes + 10.0 + (double)d / 64.0 + 64.0
                                    : 7.0 * (double)(d + 4) + 64.0;
     return units * 5.9604644775390625e-08 * M * 1.01 + 1e-12 * M + 1e-20 * sqrt(M) + 1e-40;
 }

@@ -154,11 +154,6 @@ public:
         s_ = s;
         return hipSuccess;
     }
-    hipError_t copy_from(const unsigned long long* src, hipStream_t st) {
-        hipError_t e = hipMemcpyAsync(s_.word, src, sizeof(unsigned long long), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess && (e = hipEventRecord(s_.event, st)) == hipSuccess) pending_ = true;
-        return e;
-    }
     // the word is written by a kernel that has been enqueued
     hipError_t record(hipStream_t st) {
         const hipError_t e = hipEventRecord(s_.event, st);

@@ -61,13 +61,13 @@ __global__ void __launch_bounds__(256) k_knn_centroid_finish(float* __restrict__
 }
 
 // |x'|^2 of every centred row in float32 and the largest one per cluster.  Sixteen lanes share a row (a wavefront reads
-// four consecutive rows, each lane every sixteenth column or 16-byte chunk) and add their partial sums pairwise; any
-// summation order stays within the d u |x'|^2 that the filter's error bound allows for the norm.  Bound by the latency of two
+// four consecutive rows, each lane every sixteenth column or 16-byte chunk) and add their partial sums pairwise: at most 4 ceil(d / 64)
+// additions one after the other and four pairwise ones, which is what knn_filter_eps allows the norm for.  Bound by the latency of two
 // or three loads in a chain and, where the groups are few, by the atomics on their words: large sets take kNormBatch rows per
 // sixteen lanes, all their loads in flight, and one atomic per workgroup that lies inside one group.  `members` lists the rows
 // group by group where the caller has that order: the centres then come from the first cache.  1,000,000 x 128: one group 175 ->
 // 84 us (6.1 TB/s), six slices 290 -> 85, 256 clusters of mixed rows 175 -> 155.
-constexpr int kNormLanes = 16;
+static_assert(kNormLanes == 16, "four pairwise additions");
 constexpr int kNormRows = 256 / kNormLanes;   // rows per workgroup and batch entry
 constexpr int kNormBatch = 4, kNormBatches = 4;
 // batches of a workgroup: as many as leave 2,048 of them; 0: one row per sixteen lanes, where batches would leave units without work
@@ -303,9 +303,9 @@ __global__ void __launch_bounds__(256) k_knn_pack(const float* __restrict__ X, i
 }
 
 // What an E step of Lloyd's iterations starts with, one workgroup per tile of centroids: the words that count from zero, the
-// centroids' norms and the largest of them, the packed tile, and the copy the inertia is computed from.  Every workgroup reads all K rows
-// for the largest norm, so this is for few and short ones (prepare_in_one_launch); beyond, the norms, the packing, the clearing and the copy
-// are launches of their own (four of 3 to 4 us and their gaps; one of 5).
+// centroids' norms (kNormLanes sums a row, as in k_knn_norms) and the largest of them, the packed tile, and the copy the inertia
+// is computed from.  Every workgroup reads all K rows for the largest norm, so this is for few and short ones (prepare_in_one_launch);
+// beyond, the norms, the packing, the clearing and the copy are launches of their own (four of 3 to 4 us and their gaps; one of 5).
 __global__ void __launch_bounds__(1024) k_kmeans_prepare(const float* __restrict__ C, int32_t K, int32_t d, const float* __restrict__ centre,
                                                         const uint32_t* __restrict__ point_bits, int32_t tile, int32_t steps, uint4* __restrict__ data,
                                                         float* __restrict__ norm, float* __restrict__ c_used, uint32_t* __restrict__ zeros, int32_t n_zeros,
@@ -592,7 +592,7 @@ __device__ __forceinline__ void exact_query(const KnnSets& P, int32_t q, int32_t
 }
 
 // Work space for queries whose groups are cut: pairs of every workgroup, and per query how many of its parts are through (zero)
-struct ExactParts { double* D; int32_t* P; uint32_t* done; };   // [grid * k] each, [grid / 2]
+struct ExactParts { double* D; int32_t* P; uint32_t* done; };   // [grid * k] each, [grid] (one per query, at most half of them used)
 constexpr uint32_t kMaxParts = 32;
 
 // The teams take the flagged queries in turn (how many there are is known on the device only).  Usually there are a few dozen: the
