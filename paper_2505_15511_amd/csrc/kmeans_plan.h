@@ -6,8 +6,9 @@
 namespace nomad_knn {
 
 // The M step in one launch (k_mean_small) instead of a sort by label, its scans and the sums.  It saves 10 to 30 us where
-//   clusters are short, because a workgroup adds its centroid's rows one after the other: 512 points a cluster on average (16,000 points, K = 32
-//   -10 to +5 us, K = 10 +4 to +68; 8,000, K = 10 -19 to +12, K = 2 +67 to +86; 4,000, K = 10 -8 to -26, K = 2 +30 to +41);
+//   clusters are short and points few, because a workgroup reads all labels and adds its centroid's rows one after the other, 1.4 ns a label
+//   and 16 a row: n + 12 n / K up to 20,000 (d = 4 to 116: 1,040 points, K = 2 -19 us; 3,000, K = 2 -4 to 0; 4,800, K = 6 -7; 7,200, K = 6 -1 to +2;
+//   9,000, K = 10 -1; 10,000, K = 10 +2; 11,200, K = 16 -6 to -1; 15,000, K = 10 +17; 16,000, K = 16 +6 to +11, K = 64 -4 to -8; d = 768 10 to 20 us less);
 //   the workgroups, one a centroid and 64 columns, are not many rounds of the chip: 1,024 (4,000 points, K = 512, d = 128 -23, K = 256, d = 300
 //   +2, K = 512, d = 768 +36; 2,000 points, K = 128, d = 768 -2);
 //   the labels, which every workgroup reads, are not much: 2^23 of them (16,000 points, d <= 64, K = 512 -17 to -21, K = 1,024 +2 to +6; K = 256, d = 128
@@ -15,16 +16,16 @@ namespace nomad_knn {
 constexpr int64_t kSmallMeanPoints = 16384;   // (the workgroup's list of them is 16-bit, in LDS)
 inline bool mean_in_one_launch(int64_t n, int64_t K, int64_t d) {
     const int64_t workgroups = K * ((d + 63) / 64);
-    return n <= kSmallMeanPoints && n <= 512 * K && workgroups <= 1024 && n * workgroups <= ((int64_t)1 << 23);
+    return n <= kSmallMeanPoints && n * K + 12 * n <= 20000 * K && workgroups <= 1024 && n * workgroups <= ((int64_t)1 << 23);
 }
 
 // Clearing, norms, packing and the copy of the centroids in one launch (k_kmeans_prepare), whose every workgroup reads all K rows, 64
-// at a time: -6 to -13 us up to K = 128, -1 to -8 at 512, +4 at 1,024, +15 at 2,048, +38 at 4,096 (d = 2 to 64), +83 at 8,192.
+// at a time: -6 to -13 us up to K = 128, -1 to -8 at 512, about 0 at 640, +4 at 1,024, +15 at 2,048, +38 at 4,096 (d = 2 to 64), +83 at 8,192.
 constexpr int64_t kPrepareValues = 65536;     // (128 x 768 -4, 256 x 300 -3: there by a margin)
-inline bool prepare_in_one_launch(int64_t K, int64_t d) { return K <= 512 && K * d <= kPrepareValues; }
+inline bool prepare_in_one_launch(int64_t K, int64_t d) { return K <= 640 && K * d <= kPrepareValues; }
 
 // What the filter leaves open goes to the exact path at once, over all K centroids, instead of to the candidates' refinement first: a
-// launch less.  Up to 16,384 points -2 to -10 us, wide rows to -40; from K = 1,024 on -10 to +55.
-inline bool open_points_are_few(int64_t n, int64_t K) { return n <= 16384 && K <= 512; }
+// launch less.  Up to 16,384 points -2 to -10 us, wide rows to -40; from K = 1,024 on -24 to +55.
+inline bool open_points_are_few(int64_t n, int64_t K) { return n <= 16384 && K <= 768; }
 
 }  // namespace nomad_knn

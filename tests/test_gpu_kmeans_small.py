@@ -25,8 +25,8 @@ def test_points(n, d, K):
 
 
 # the one-launch sums at their lines: the longest lists, the most workgroups, the first sets past either; more centroids than are prepared in one launch
-@pytest.mark.parametrize("n,d,K", [(16_384, 5, 32), (16_385, 5, 33), (5_121, 3, 10), (2_100, 64, 1_024), (2_100, 65, 1_024), (4_096, 128, 512), (4_096, 129, 512),
-                                   (3_000, 4, 513)])
+@pytest.mark.parametrize("n,d,K", [(16_384, 5, 64), (16_385, 5, 64), (9_090, 3, 10), (9_091, 3, 10), (1_538, 3, 1), (2_100, 64, 1_024), (2_100, 65, 1_024), (4_096, 128, 512), (4_096, 129, 512),
+                                   (3_000, 4, 641), (3_000, 70, 769)])
 def test_lines(n, d, K):
     rng = np.random.default_rng(n + d + K)
     X = (rng.normal(size=(n, d)) + 3.0 * rng.integers(0, 3, size=(n, 1))).astype(np.float32)

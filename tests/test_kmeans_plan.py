@@ -34,8 +34,9 @@ def rules(tmp_path_factory):
 
 def test_means(rules):
     assert rules(3_001, 10, 50)[0] and rules(1, 1, 1)[0]
-    assert rules(16_384, 32, 64)[0] and not rules(16_385, 64, 64)[0]                  # points
-    assert rules(5_120, 10, 64)[0] and not rules(5_121, 10, 64)[0]                    # points a cluster
+    assert rules(16_384, 64, 64)[0] and not rules(16_385, 64, 64)[0]                  # points
+    assert rules(9_090, 10, 64)[0] and not rules(9_091, 10, 64)[0]                    # points and points a cluster
+    assert rules(2_857, 2, 64)[0] and not rules(2_858, 2, 64)[0] and rules(1_538, 1, 64)[0] and not rules(1_539, 1, 64)[0]
     assert rules(4_000, 512, 128)[0] and not rules(4_000, 512, 129)[0]                # workgroups
     assert rules(2_048, 1_024, 64)[0] and not rules(2_048, 1_025, 64)[0]
     assert rules(16_384, 512, 64)[0] and not rules(16_384, 513, 64)[0]                # labels read
@@ -43,9 +44,9 @@ def test_means(rules):
 
 
 def test_centroids(rules):
-    assert rules(5_000, 512, 128)[1] and not rules(5_000, 513, 2)[1]                  # rows
+    assert rules(5_000, 640, 102)[1] and not rules(5_000, 641, 2)[1]                  # rows
     assert rules(5_000, 85, 768)[1] and not rules(5_000, 86, 768)[1]                  # values
 
 
 def test_open_points(rules):
-    assert rules(16_384, 512, 768)[2] and not rules(16_385, 2, 2)[2] and not rules(16_384, 513, 2)[2]
+    assert rules(16_384, 768, 768)[2] and not rules(16_385, 2, 2)[2] and not rules(16_384, 769, 2)[2]
