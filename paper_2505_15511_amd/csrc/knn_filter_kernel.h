@@ -131,6 +131,10 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // follow only where some lane's smallest key comes within slack of its threshold.  The keys are the same bits, and what is
 // passed over would not have been looked at.  10,000 queries among 1,000,000 x 128 in six slices: 63 % of the tiles end there,
 // the filter takes 5.8 ms instead of 7.6 (sifting from the first tile on: the same, and 3 % more for clusters of 4,000).
+// Workgroups of fewer wavefronts (few queries, one wavefront a SIMD) have nobody to multiply while a chain of dependent products is
+// waited for, and a tile with a hit then waits for two chains in turn: they sift from tile 2 TILE K' on.  50 queries, 30 neighbours,
+// 300,000 x 400: filter 2.18 ms without sifting and chunks, 2.53 with both, 2.41 with the later start and 2.38 with a chunk's sum
+// added while the next one is multiplied.
 //
 // Selection: 64 / TILE lanes share a query, each sees its part of every tile's candidates and keeps the L smallest keys,
 // with their positions, sorted in registers.  Keys below the lane's threshold are set aside in a small queue in LDS; when a
@@ -285,13 +289,20 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     const auto large = [&](Acc& big, Acc& chunk, half8 a, int s) {
         if (kChunk == 0 || s < kChunk) { big = Mat::mul(a, bh[s], big); return; }
         if (s % (kChunk ? kChunk : 1) == 0) {
-            if (s > kChunk) big += chunk;
+            const Acc before = chunk;
             chunk = Acc{};
+            if (WAVES == 8 && s > kChunk) big += before;
+            chunk = Mat::mul(a, bh[s], chunk);
+            if (WAVES != 8 && s > kChunk) {
+                __builtin_amdgcn_sched_barrier(0);     // the chunk before is added while this one is multiplied
+                big += before;
+            }
+        } else {
+            chunk = Mat::mul(a, bh[s], chunk);
         }
-        chunk = Mat::mul(a, bh[s], chunk);
         if (s == KS - 1) big += chunk;
     };
-    const int32_t sift_from = kSift ? list_len * TILE / 2 : n_tiles;
+    const int32_t sift_from = kSift ? (WAVES == 8 ? list_len * TILE / 2 : list_len * TILE * 2) : n_tiles;
     float slack = 0.f;             // >= |hi lo + lo hi| of this query with any candidate, as summed below
     if (kSift && n_tiles > sift_from) {
         float h2 = 0.f, l2 = 0.f;

@@ -9,10 +9,12 @@ from paper_2505_15511_amd import knn_in_clusters
 pytestmark = pytest.mark.gpu
 
 
-# (n, d, k): 32-row tiles with short lists (sifting from row 512 (k + 8) on) just at the line, one row past it and far beyond it,
-# with two and with eight wavefronts a workgroup; long lists; 16-row tiles (from row 128 (k + 8) on) with both list lengths
+# (n, d, k): 32-row tiles with short lists, eight wavefronts a workgroup (from 32,768 rows on; sifting from row 512 (k + 8) on) and two (from row
+# 2,048 (k + 8) on: just at the line, one row past it, beyond it); long lists; 16-row tiles with both list lengths, eight wavefronts (from
+# 16,384 rows on; sifting from row 128 (k + 8) on) and four (from row 512 (k + 8) on: at the line, past it)
 @pytest.mark.parametrize("n,d,k", [(11776, 20, 15), (11777, 20, 15), (9000, 128, 5), (34001, 40, 15), (33333, 128, 1), (33000, 10, 12), (34000, 64, 20),
-                                   (18001, 300, 15), (17000, 200, 20), (5003, 768, 15)])
+                                   (18001, 300, 15), (17000, 200, 20), (5003, 768, 15),
+                                   (26624, 20, 5), (26625, 20, 5), (30001, 128, 5), (11776, 300, 15), (11777, 300, 15), (15001, 400, 15), (16301, 200, 20)])
 @pytest.mark.parametrize("outlier", [False, True])
 def test_neighbours_late_in_a_long_group(n, d, k, outlier):
     print(f"n={n} d={d} k={k} outlier={outlier}", flush=True)
