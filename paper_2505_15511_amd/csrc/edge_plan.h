@@ -134,8 +134,8 @@ inline EdgePlan plan_edge_pass(const EdgePlanRequest& q) {
 // special_kernel: the edge pass is one of the kernels that know their options.  Those also come
 //   with two rounds to a flush, where the records fit LDS (half the barriers and table passes: 100 k points 0.149 -> 0.142 ms,
 //   6 M points in groups, s = 2, 4.26 -> 4.06);
-//   with 256 lanes, for graphs of no more positions than give every compute unit one such workgroup (few now: embeddings of up to
-//   10,224 points take plan_small's pass): one round is all there is, and its length goes with the lanes that share its
+//   with 256 lanes, for graphs of no more positions than give every compute unit one such workgroup (few now: most embeddings of
+//   up to 10,224 points take plan_small's pass): one round is all there is, and its length goes with the lanes that share its
 //   barriers and LDS (whole epoch, 14 k edges: 22.0 -> 12.7 us, 58 k: 22.4 -> 18.8; with two such workgroups per compute unit 87 k: 24.0 -> 25.8, 116 k: 25.7 -> 29.9).
 inline bool edge_tables_fit(const EdgePlan& p, const EdgePlanRequest& q) {
     const size_t lds = p.distinct_kernel ? distinct_lds_bytes(p.n_bins, (uint32_t)q.pool_size, (uint32_t)(q.pool_size / q.pool_line), p.pool_rounds)
