@@ -19,6 +19,17 @@ inline bool mean_in_one_launch(int64_t n, int64_t K, int64_t d) {
     return n <= kSmallMeanPoints && n * K + 12 * n <= 20000 * K && workgroups <= 1024 && n * workgroups <= ((int64_t)1 << 23);
 }
 
+// Positions of a partial sum in the parallel M step: 512, fewer where that leaves compute units idle (100,003 x 768, 196 workgroups: 98 us), but not
+// where clusters are long: k_mean_combine adds a cluster's partial sums one after the other, which short rows hide less of.  128 / 256 positions
+// against 512, us, d = 64: 20,000 points, K = 32 -3 / -2, K = 8 0 / 0, K = 2 +3 / +2; 50,000, K = 16 0 / -2, K = 4 +6 / 0; 100,000, K = 32 0 / -3, K = 8 +7 / 0,
+// K = 2 +24 / +6; 300,000, K = 64 +7 / +2, K = 4 +72 / +25 (and d = 16: 960 us a call of five iterations for 887); d = 768: 20,000, K = 8 -16 / -11, K = 2 -8 / -7;
+// 50,000, K = 8 -23 / -21, K = 2 -2 / -9; 100,000, K = 64 -9 / -14, K = 8 +16 / 0, K = 4 +10 / -3, K = 2 +26 / +6.
+inline int32_t mean_span(int64_t n, int64_t K, int64_t d) {
+    if (n < 65536 && n <= (16 + d / 32) * 128 * K) return 128;
+    if (n < 512 * 1024 && n <= (32 + d / 12) * 256 * K) return 256;
+    return 512;
+}
+
 // Clearing, norms, packing and the copy of the centroids in one launch (k_kmeans_prepare), whose every workgroup reads all K rows, 64
 // at a time: -6 to -13 us up to K = 128, -1 to -8 at 512, about 0 at 640, +4 at 1,024, +15 at 2,048, +38 at 4,096 (d = 2 to 64), +83 at 8,192.
 constexpr int64_t kPrepareValues = 65536;     // (128 x 768 -4, 256 x 300 -3: there by a margin)

@@ -159,7 +159,7 @@ struct MeanStep {
         passes = (bits + 7) / 8;
         n_blocks = blocks_of(n, kSortSpan);
         parallel = n >= (int64_t)128 * K;
-        span = mean_span(n);
+        span = mean_span(n, K, d);
         KTRY(buf.alloc(&lstart, (size_t)K + 1));
         n_tiles = (uint32_t)(((size_t)256 * n_blocks + kScanTile - 1) / kScanTile);
         KTRY(buf.alloc(&hist, (size_t)256 * n_blocks));

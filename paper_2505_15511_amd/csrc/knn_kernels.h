@@ -964,9 +964,7 @@ __global__ void __launch_bounds__(256) k_mean_small(const float* __restrict__ X,
 //
 // k_mean_partials: a workgroup takes `span` positions of the sorted order; the part of span b that lies in cluster j is
 // partial number b + j (b + j grows along the order, so the numbers are distinct and below spans + K).
-// (512 positions, fewer where that leaves compute units idle: 100,003 x 768, 196 spans of 512 98 us)
-constexpr int kMeanSpan = 512;
-inline int32_t mean_span(int64_t n) { return n >= 512 * 1024 ? kMeanSpan : n >= 256 * 512 ? 256 : 128; }
+// (mean_span, kmeans_plan.h)
 struct MeanPartial { double sum; double magnitude; };
 
 template <int VEC>

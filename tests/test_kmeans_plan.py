@@ -13,7 +13,7 @@ using namespace nomad_knn;
 int main(int argc, char** argv) {   // triples n K d
     for (int a = 1; a + 2 < argc; a += 3) {
         const int64_t n = atoll(argv[a]), K = atoll(argv[a + 1]), d = atoll(argv[a + 2]);
-        printf("%d %d %d\n", (int)mean_in_one_launch(n, K, d), (int)prepare_in_one_launch(K, d), (int)open_points_are_few(n, K));
+        printf("%d %d %d %d\n", (int)mean_in_one_launch(n, K, d), (int)prepare_in_one_launch(K, d), (int)open_points_are_few(n, K), (int)mean_span(n, K, d));
     }
 }
 """
@@ -28,7 +28,7 @@ def rules(tmp_path_factory):
 
     def of(n, K, d_):
         out = subprocess.run([str(d / "plan"), str(n), str(K), str(d_)], check=True, capture_output=True, text=True).stdout.split()
-        return [bool(int(x)) for x in out]
+        return [bool(int(x)) for x in out[:3]] + [int(out[3])]
     return of
 
 
@@ -50,3 +50,9 @@ def test_centroids(rules):
 
 def test_open_points(rules):
     assert rules(16_384, 768, 768)[2] and not rules(16_385, 2, 2)[2] and not rules(16_384, 769, 2)[2]
+
+
+def test_spans(rules):
+    assert [rules(n, 1_000, 64)[3] for n in (65_535, 65_536, 524_287, 524_288)] == [128, 256, 256, 512]       # compute units
+    assert [rules(20_736, K, 64)[3] for K in (9, 8, 3, 2)] == [128, 256, 256, 512]                             # partial sums of a cluster
+    assert [rules(20_736, K, 768)[3] for K in (5, 4, 1)] == [128, 256, 256] and [rules(300_000, K, 64)[3] for K in (32, 31, 1)] == [256, 512, 512]
