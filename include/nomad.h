@@ -302,8 +302,8 @@ int nomad_release_memory(void);
  *                              lane writes its own records
  *   NOMAD_TUNE_FLUSH_ROUNDS    0 (default: 2), 1 or 2: rounds of 1024 positions the unsorted form takes between two
  *                              flushes of its records (1024-lane workgroups only)
- *   NOMAD_TUNE_EXCHANGE        0 (default: large embeddings of one population with i.i.d. negatives, unless a knob above asks for
- *                              a shape of the sorted edge pass), 1: the exchanged edge pass wherever it can run, 2: never; the
+ *   NOMAD_TUNE_EXCHANGE        0 (default: large embeddings of one population with i.i.d. negatives and no short sub-steps, unless a
+ *                              knob above asks for a shape of the sorted edge pass), 1: the exchanged edge pass wherever it can run, 2: never; the
  *                              two give the same bits
  */
 #define NOMAD_TUNE_EDGE_BLOCK 1
