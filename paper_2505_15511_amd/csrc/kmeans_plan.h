@@ -22,10 +22,10 @@ inline bool mean_in_one_launch(int64_t n, int64_t K, int64_t d) {
 // Positions of a partial sum in the parallel M step: 512, fewer where that leaves compute units idle (100,003 x 768, 196 workgroups: 98 us), but not
 // where clusters are long: k_mean_combine adds a cluster's partial sums one after the other, which short rows hide less of.  128 / 256 positions
 // against 512, us, d = 64: 20,000 points, K = 32 -3 / -2, K = 8 0 / 0, K = 2 +3 / +2; 50,000, K = 16 0 / -2, K = 4 +6 / 0; 100,000, K = 32 0 / -3, K = 8 +7 / 0,
-// K = 2 +24 / +6; 300,000, K = 64 +7 / +2, K = 4 +72 / +25 (and d = 16: 960 us a call of five iterations for 887); d = 768: 20,000, K = 8 -16 / -11, K = 2 -8 / -7;
+// K = 128 -6 / -5, K = 2 +24 / +6; 300,000, K = 64 +7 / +2, K = 4 +72 / +25 (and d = 16: 960 us a call of five iterations for 887); d = 768: 20,000, K = 8 -16 / -11, K = 2 -8 / -7;
 // 50,000, K = 8 -23 / -21, K = 2 -2 / -9; 100,000, K = 64 -9 / -14, K = 8 +16 / 0, K = 4 +10 / -3, K = 2 +26 / +6.
 inline int32_t mean_span(int64_t n, int64_t K, int64_t d) {
-    if (n < 65536 && n <= (16 + d / 32) * 128 * K) return 128;
+    if (n < (d < 256 ? 98304 : 65536) && n <= (16 + d / 32) * 128 * K) return 128;
     if (n < 512 * 1024 && n <= (32 + d / 12) * 256 * K) return 256;
     return 512;
 }

@@ -53,6 +53,7 @@ def test_open_points(rules):
 
 
 def test_spans(rules):
-    assert [rules(n, 1_000, 64)[3] for n in (65_535, 65_536, 524_287, 524_288)] == [128, 256, 256, 512]       # compute units
+    assert [rules(n, 1_000, 255)[3] for n in (98_303, 98_304, 524_287, 524_288)] == [128, 256, 256, 512]      # compute units
+    assert [rules(n, 1_000, 256)[3] for n in (65_535, 65_536)] == [128, 256]
     assert [rules(20_736, K, 64)[3] for K in (9, 8, 3, 2)] == [128, 256, 256, 512]                             # partial sums of a cluster
     assert [rules(20_736, K, 768)[3] for K in (5, 4, 1)] == [128, 256, 256] and [rules(300_000, K, 64)[3] for K in (32, 31, 1)] == [256, 512, 512]
