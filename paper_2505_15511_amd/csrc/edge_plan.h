@@ -230,12 +230,14 @@ inline int plan_small(const EdgePlanRequest& q, const EdgePlan& p, int compute_u
 //   5 / 10 / 15.  (Random order: 2 M, s = 2 0.91 at 3.8, 1.42 at 1.4.)  The line is at 8.
 //   Rows: runs of about seven references (10 M points) leave as partial sectors; two neighbouring tiles in LDS make them twice
 //   as long (2.79 -> 2.45 ms for 75 M edges; at 5 M points a tile alone is as fast).
-//   Lanes: as many as most runs have references (75 M edges, rows and sums, 16 / 32 / 64 lanes: runs of 7.5 in pairs 2.67 / 2.47 / 2.76 and
-//   2.11 / 2.37 / 3.98 ms, of 15 4.02 / 2.13 / 2.28 and 2.14 / 1.65 / 2.61, of 25 - / 1.99 / 1.95 and 4.45 / 1.44 / 1.95).
+//   Lanes: as many as most runs have references (75 M edges, rows, 16 / 32 / 64 lanes: runs of 7.5 in pairs 2.67 / 2.47 / 2.76 ms, of 15
+//   4.02 / 2.13 / 2.28, of 25 - / 1.99 / 1.95).  Sums, lanes of two references: runs of 7.5 4 / 8 / 16 lanes 2.32 / 2.14 / 2.18 ms; of 37 8 / 16
+//   lanes 0.327 / 0.268 (a run is one segment or two).
 struct ExchangePlan {
     bool use = false;
     bool pairs = false;                     // k_exchange_rows holds two neighbouring tiles
-    int rows_lanes = 64, sums_lanes = 64;   // lanes that take one run
+    int rows_lanes = 64;                    // lanes that take one run
+    int sums_lanes = 16;                    // lanes that take a segment of twice as many references
     uint32_t parts = 1;                     // workgroups per tile (or pair) that answer
     int tile_bits = 0;
 };
@@ -252,7 +254,7 @@ inline ExchangePlan plan_exchange(const EdgePlanRequest& q, const EdgePlan& p) {
     x.tile_bits = p.tile_bits;
     x.pairs = run < 12;
     x.rows_lanes = x.pairs ? (2 * run < 9 ? 16 : 32) : run < 26 ? 32 : 64;
-    x.sums_lanes = run < 11 ? 16 : run < 26 ? 32 : 64;
+    x.sums_lanes = run < 12 ? 8 : 16;
     const uint32_t units = x.pairs ? (p.n_bins + 1) / 2 : p.n_bins;
     x.parts = units >= 512 ? 2 : (1024 + units - 1) / units;   // (four workgroups per compute unit and more at a few hundred tiles)
     return x;

@@ -393,13 +393,17 @@ void with_exchange_s(const nomad_ctx* c, Fn fn) {
 }
 // the tile kernels for the length of this problem's runs (exchange_kernels.h)
 using ExchangeRowsKernel = void (*)(const ExchangeArgs, const float2*, int64_t, uint32_t, uint32_t);
-using ExchangeSumsKernel = void (*)(const ExchangeArgs, uint32_t, float2*, int64_t, float2*, float, unsigned long long*, int);
 ExchangeRowsKernel exchange_rows_kernel(const ExchangePlan& p) {
     if (p.pairs) return p.rows_lanes == 16 ? k_exchange_rows<16, true> : k_exchange_rows<32, true>;
     return p.rows_lanes == 32 ? k_exchange_rows<32, false> : k_exchange_rows<64, false>;
 }
-ExchangeSumsKernel exchange_sums_kernel(const ExchangePlan& p) {
-    return p.sums_lanes == 16 ? k_exchange_sums<16> : p.sums_lanes == 32 ? k_exchange_sums<32> : k_exchange_sums<64>;
+// the sums of a tile, for the length of this problem's runs
+using TileSumsKernel = void (*)(const TileSums, float2*, int64_t, float2*, float, unsigned long long*, int);
+TileSumsKernel tile_sums_kernel(int lanes) { return lanes == 8 ? k_tile_sums<8> : k_tile_sums<16>; }
+
+void launch_tile_sums(nomad_ctx* c, int lanes, const TileSums& x, float eta, int phase) {
+    hipLaunchKernelGGL(tile_sums_kernel(lanes), dim3(exchange_padded_tiles(x.n_tiles)), dim3(kBinBlock), 16 * (size_t)x.points, c->stream, x, c->g, c->n, c->theta, eta,
+                       c->carry, phase);
 }
 
 ExchangeArgs exchange_args(const nomad_ctx* c, int64_t e_begin, int64_t e_end) {
@@ -420,7 +424,7 @@ int prepare_exchange(nomad_ctx* c) {
         allow((const void*)k_exchange_edges<decltype(s)::value>, exchange_edges_lds_bytes(c->cfg.n_neg));
     });
     allow((const void*)exchange_rows_kernel(c->ex), exchange_rows_lds_bytes(c->ex));
-    allow((const void*)exchange_sums_kernel(c->ex), sizeof(unsigned long long) * 2 << c->tile_bits);
+    allow((const void*)tile_sums_kernel(c->ex.sums_lanes), (size_t)16 << c->tile_bits);
     HIP_TRY(c, err);
     return NOMAD_OK;
 }
@@ -435,8 +439,8 @@ void launch_exchange_edges(nomad_ctx* c, const EdgeArgs& a, const ExchangeArgs& 
 }
 
 void launch_exchange_sums(nomad_ctx* c, const ExchangeArgs& x, float eta, int phase) {
-    hipLaunchKernelGGL(exchange_sums_kernel(c->ex), dim3(exchange_padded_tiles(x.n_tiles)), dim3(kBinBlock), sizeof(unsigned long long) * 2 << c->tile_bits,
-                       c->stream, x, (uint32_t)exchange_slots(c->cfg.n_neg), c->g, c->n, c->theta, eta, c->carry, phase);
+    const uint32_t points = 1u << c->tile_bits;
+    launch_tile_sums(c, c->ex.sums_lanes, TileSums{x.rec, x.idx, x.runs, x.ghead, x.n_blocks, (uint32_t)exchange_slots(c->cfg.n_neg), x.n_tiles, points, points - 1u, x.spare}, eta, phase);
 }
 
 // cell means of the current embedding -> mu, cinfo
