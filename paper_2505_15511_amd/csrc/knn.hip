@@ -283,7 +283,7 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     }
     PackedSide side;
     side.plan(hstart, d, list_len);
-    const int waves = knn_filter_waves(side.tile, side.n_tiles);
+    const int waves = knn_filter_waves(side.tile, side.n_tiles, knn_most_waves(side.tile, side.steps, knn_list_class(side.tile, list_len)));
     const std::vector<KnnBlock> hblocks = filter_blocks(side, side, waves);
     HostArrays up;
     const size_t at_start = up.add(hstart), at_tstart = up.add(side.tstart), at_blocks = up.add(hblocks), at_slabs = up.add(hslabs);
@@ -296,13 +296,30 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     hipLaunchKernelGGL(k_knn_group, dim3(blocks_of(n, kGroupSpan)), dim3(256), 0, st, dC, n, R, start, cursor, members);
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, members, start, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of((int64_t)R * d, 256)), dim3(256), 0, st, centre, start, R, d);
-    launch_norms(st, dX, n, d, members, dC, centre, norm, max_norm);
+    const bool ordered = knn_ordered(n, d, R);   // the order of the rows inside a cluster, and the norms with it
+    if (ordered) {
+        uint32_t* cells = nullptr;      // [2][R][kCells] counts, cursors
+        uint8_t* cell_of = nullptr;
+        int32_t* placed = nullptr;
+        KTRY(buf.alloc(&cells, (size_t)2 * R * kCells));
+        KTRY(buf.alloc(&cell_of, (size_t)n));
+        KTRY(buf.alloc(&placed, (size_t)n));
+        KTRY(hipMemsetAsync(cells, 0, sizeof(uint32_t) * (size_t)2 * R * kCells, st));
+        const size_t lds = sizeof(float) * (size_t)(kCells + 1) * ((d + 3) / 4 * 4);
+        hipLaunchKernelGGL(k_knn_cells, dim3((uint32_t)hslabs.size()), dim3(256), lds, st, dX, d, (const int32_t*)members, start, slabs, slab_rows,
+                           (const float*)centre, norm, max_norm, cell_of, cells);
+        hipLaunchKernelGGL(k_knn_place, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, (const int32_t*)members, (const uint8_t*)cell_of, start, slabs, slab_rows,
+                           (const uint32_t*)cells, cells + (size_t)R * kCells, placed);
+        members = placed;
+    } else {
+        launch_norms(st, dX, n, d, members, dC, centre, norm, max_norm);
+    }
     side.fill(st, dX, d, members, centre, max_norm, max_norm, norm);
 
     // filter on the matrix cores, float64 refinement, exact fallback
     KnnSets P{};
     P.XQ = dX; P.XC = dX; P.qmembers = members; P.cmembers = members; P.qstart = start; P.cstart = start;
-    P.Q = side.view(max_norm); P.C = P.Q; P.centre = centre; P.group_of_q = dC; P.n_q = n; P.n_c = n; P.d = d; P.same_set = 1; P.chunk = knn_chunk_columns(d, list_len);
+    P.Q = side.view(max_norm); P.C = P.Q; P.centre = centre; P.group_of_q = dC; P.n_q = n; P.n_c = n; P.d = d; P.same_set = 1; P.ordered = ordered; P.chunk = knn_chunk_columns(d, list_len);
     int rc = nearest_in_groups(st, buf, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, dOut);
     if (rc) return rc;
     uint32_t hflag = 0;

@@ -4,16 +4,16 @@
 
 namespace {
 
-template <int TILE, int KS, int L, int WAVES>
+template <int TILE, int KS, int L, int WAVES, bool SIFT = true>
 hipError_t launch(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand, float* keys, float* tau,
                   const KnnAssign& assign) {
     constexpr size_t lds = knn_filter_lds_bytes(TILE, KS, L, WAVES);
     static_assert(lds <= 160 * 1024, "");
     if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_knn_filter<TILE, KS, L, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void*)k_knn_filter<TILE, KS, L, WAVES, SIFT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_knn_filter<TILE, KS, L, WAVES>), dim3(n_blocks), dim3(64 * WAVES), lds, st, P, blocks, list_len, cand, keys, tau, assign);
+    hipLaunchKernelGGL((k_knn_filter<TILE, KS, L, WAVES, SIFT>), dim3(n_blocks), dim3(64 * WAVES), lds, st, P, blocks, list_len, cand, keys, tau, assign);
     return hipGetLastError();
 }
 
@@ -21,8 +21,14 @@ hipError_t launch(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const Knn
 template <int TILE, int KS, int L>
 hipError_t launch_waves(hipStream_t st, uint32_t n_blocks, int waves, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand,
                         float* keys, float* tau, const KnnAssign& assign) {
+    constexpr int kMost = knn_most_waves(TILE, KS, L), kFew = TILE == 32 ? 2 : 4;
+    if (kMost > 8 && waves == kMost) return launch<TILE, KS, L, kMost>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+    if (L > 2 && !knn_both_ways(TILE, KS, 8) && !P.ordered) {
+        if (waves == 8) return launch<TILE, KS, L, 8, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+        return launch<TILE, KS, L, kFew, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+    }
     if (waves == 8) return launch<TILE, KS, L, 8>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
-    return launch<TILE, KS, L, TILE == 32 ? 2 : 4>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+    return launch<TILE, KS, L, kFew>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
 }
 
 }  // namespace

@@ -54,6 +54,7 @@ struct KnnSets {
     int32_t same_set;            // 1: queries and candidates are the same rows: a row is not its own neighbour
     int32_t chunk;               // columns that the filter sums at a time (knn_chunk_columns): its error bound depends on it
     const int32_t* self_row;     // or, per query row, the candidate row that is the query itself (nullptr: see same_set)
+    int32_t ordered;             // 1: the rows of a group lie cell by cell (k_knn_place): near rows are near in the list
 };
 
 __device__ __forceinline__ int32_t knn_row(const int32_t* members, uint32_t pos) { return members ? members[pos] : (int32_t)pos; }
@@ -74,7 +75,7 @@ template <> struct MatrixTile<16> {
 // the same LDS) are 1.5 % of a filter over large clusters and 1 % of one over slices of the whole set; two workgroups of four
 // wavefronts per unit, which wait for each other less but stage every tile twice, are 10 and 5 % slower.  Otherwise loads into
 // LDS are issued two stages ahead of their use (one at the widest rows, whose stages are 48 KB), which is what hides the
-// memory's latency behind 3,000 cycles of matrix instructions per stage.
+// memory's latency behind 3,000 cycles of matrix instructions per stage.  Twelve and sixteen wavefronts leave LDS for two stages of 16 and 8 steps.
 // Steps of the large products that are summed by themselves (0: all of them in one sum): 64 columns.  The bound on a sum's
 // rounding grows with its length, and with the bound the number of candidates whose order the keys leave open and whose rows
 // k_knn_refine has to read, and of queries left to the exact path.  1,000,000 x 128 in clusters of 4,000, sums of all columns /
@@ -88,11 +89,11 @@ __host__ __device__ constexpr int knn_chunk_steps(int tile, int steps, int L) {
 }
 constexpr int kMaxStageTiles = 16;   // packed arrays are this many tiles longer than what they hold
 __host__ __device__ constexpr int knn_stage_tiles(int tile, int steps, int L, int waves) {
-    const int target = tile == 16 ? steps : (L > 2 && waves == 8) ? 24 : 8;
+    const int target = tile == 16 ? steps : waves > 12 ? 8 : waves > 8 ? 16 : (L > 2 && waves == 8) ? 24 : 8;
     return steps >= target ? 1 : target / steps < kMaxStageTiles ? target / steps : kMaxStageTiles;
 }
 __host__ __device__ constexpr int knn_buffers(int tile, int steps, int L, int waves) {
-    return (tile == 16 && steps > 16) || (L > 2 && waves == 8 && knn_stage_tiles(tile, steps, L, waves) > 1) ? 2 : 3;
+    return (tile == 16 && steps > 16) || (L > 2 && waves >= 8 && knn_stage_tiles(tile, steps, L, waves) > 1) ? 2 : 3;
 }
 __host__ __device__ constexpr int knn_fifo(int tile) { return tile == 32 ? 12 : 8; }   // hits a lane sets aside before they go into its list
 __host__ __device__ constexpr size_t knn_stage_bytes(int tile, int steps, int L, int waves) {
@@ -101,8 +102,10 @@ __host__ __device__ constexpr size_t knn_stage_bytes(int tile, int steps, int L,
 __host__ __device__ constexpr size_t knn_filter_lds_bytes(int tile, int steps, int L, int waves) {
     return knn_buffers(tile, steps, L, waves) * knn_stage_bytes(tile, steps, L, waves) + (L > 2 ? (size_t)waves * knn_fifo(tile) * 64 * 8 : 0);
 }
+// whether a filter that sifts has the other way of multiplying a tile too (see below): not where registers are short
+__host__ __device__ constexpr bool knn_both_ways(int tile, int steps, int waves) { return waves <= 8 && !(tile == 16 && steps > 16); }
 __host__ __device__ constexpr int knn_waves_per_simd(int tile, int steps, int L, int waves) {
-    return waves != 8 ? 1 : tile == 32 && L == 2 && steps <= 8 ? 4 : 2;
+    return waves > 8 ? waves / 4 : waves != 8 ? 1 : tile == 32 && L == 2 && steps <= 8 ? 4 : 2;
 }
 
 // 16 (4) bytes per lane from global memory straight into LDS: lane l's go to byte offset `to` + 16 l (4 l).  Not known to the
@@ -126,15 +129,20 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // products cost a fifth of one in float32; unlike those they also leave the vector pipe to the selection.
 //
 // Sifting: the products hi lo + lo hi, two thirds of the matrix work, are at most `slack` in size (Cauchy-Schwarz, from the
-// query's own parts and the largest candidate).  Far into a long group few tiles hold a hit at all, TILE K' of TILE t
-// candidates' keys after t tiles in random order, so from tile TILE K' / 2 on the large product comes first and the others
-// follow only where some lane's smallest key comes within slack of its threshold.  The keys are the same bits, and what is
-// passed over would not have been looked at.  10,000 queries among 1,000,000 x 128 in six slices: 63 % of the tiles end there,
-// the filter takes 5.8 ms instead of 7.6 (sifting from the first tile on: the same, and 3 % more for clusters of 4,000).
+// query's own parts and the largest candidate).  The large product comes first and the others follow only where some lane's smallest
+// key comes within slack of its threshold.  The keys are the same bits, and what is passed over would not have been looked at.
+// Where the rows of a group lie cell by cell (P.ordered) the scan begins at the queries' own tiles, whose candidates bring the
+// thresholds down, and of the other cells' tiles few are left: 1,000,000 x 128 in clusters of 4,000, 47 % of the tiles end there.
+// Multiplying the large product first also needs a third accumulator less, and with it three wavefronts a SIMD fit the registers (four of
+// the shortest rows), which is worth as much: filter 4.9 ms, ordered 4.2, with twelve wavefronts a workgroup 3.8.  In random order
+// few tiles hold no hit until far into a long group (TILE K' of TILE t candidates' keys after t tiles): there workgroups of eight
+// wavefronts multiply all three products side by side up to tile TILE K' / 2, which saves a chain of dependent products a tile.
+// 10,000 queries among 1,000,000 x 128 in six slices: 63 % of the tiles end after the large product, the filter takes 5.8 ms instead of 7.6.
 // Workgroups of fewer wavefronts (few queries, one wavefront a SIMD) have nobody to multiply while a chain of dependent products is
 // waited for, and a tile with a hit then waits for two chains in turn: they sift from tile 2 TILE K' on.  50 queries, 30 neighbours,
 // 300,000 x 400: filter 2.18 ms without sifting and chunks, 2.53 with both, 2.41 with the later start and 2.38 with a chunk's sum
-// added while the next one is multiplied.
+// added while the next one is multiplied.  Rows of more than 512 columns have registers for one way only (both: 32 to 63 spilled, call
+// +10 %): sifting where the rows are ordered, side by side otherwise.
 //
 // Selection: 64 / TILE lanes share a query, each sees its part of every tile's candidates and keeps the L smallest keys,
 // with their positions, sorted in registers.  Keys below the lane's threshold are set aside in a small queue in LDS; when a
@@ -151,7 +159,7 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // list (query position in todo, its 2 * 64 / TILE candidates in cand, tau) for k_assign_refine.
 struct KnnAssign { int32_t* out; int32_t* todo; uint32_t* n_todo; };
 
-template <int TILE, int KS, int L, int WAVES>
+template <int TILE, int KS, int L, int WAVES, bool SIFT = true>
 __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WAVES)) k_knn_filter(const KnnSets P, const KnnBlock* __restrict__ blocks, int32_t list_len,
                                                                                int32_t* __restrict__ cand, float* __restrict__ key_out, float* __restrict__ tau_out,
                                                                                const KnnAssign assign) {
@@ -213,11 +221,17 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     const uint32_t queue0 = lds0 + (uint32_t)(kBuffers * kStageBytes) + (uint32_t)wave * (F * kEntry);
     uint32_t at = queue0 + 4u * (uint32_t)lane;
     const auto holds_more_than = [&](int x) { return at > queue0 + (uint32_t)x * kEntry + 255u; };
-    const int32_t last0 = n_tiles > 0 ? (n_tiles - 1) / kStage * kStage : 0;   // first tile of the last stage
-    // the stage that begins with tile t (the last one again where that is past the end), into buffer buf.  The last stage may
+    const int32_t n_stages = (n_tiles + kStage - 1) / kStage;
+    // first stage: the one the queries themselves are in, where what is near them is there too
+    const int32_t stage0 = P.ordered ? min(blk.q0 / kStage, max(n_stages - 1, 0)) : 0;
+    const auto first_tile = [&](int32_t x) {   // of the x-th stage, all of them in turn from stage0 on
+        x += stage0;
+        return (x >= n_stages ? x - n_stages : x) * kStage;
+    };
+    // the x-th stage (the last one again where that is past the end), into buffer buf.  The group's last stage may
     // take tiles beyond the group's along; the arrays are long enough for that, and nobody looks at them.
-    auto fetch = [&](int32_t t, int buf) {
-        t = min(t, last0);
+    auto fetch = [&](int32_t x, int buf) {
+        const int32_t t = first_tile(min(x, n_stages - 1));
         const char* from = csrc + (size_t)t * kUnits * 16;
         const uint32_t to = lds0 + (uint32_t)(buf * kStageBytes);
 #pragma unroll
@@ -284,16 +298,16 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                      : [key] "v"(key), [thr] "v"(thr), [pos] "v"(pos), [entry] "s"(kEntry)
                      : "vcc", "scc", "memory");
     };
-    constexpr bool kSift = L > 2 && !(TILE == 16 && KS > 16);     // (the widest rows' queries fill the registers as it is)
+    constexpr bool kSift = L > 2 && SIFT, kTogether = knn_both_ways(TILE, KS, WAVES) || !SIFT;
     // step s of the large product: big = the norms and the chunks before, chunk = the present one
     const auto large = [&](Acc& big, Acc& chunk, half8 a, int s) {
         if (kChunk == 0 || s < kChunk) { big = Mat::mul(a, bh[s], big); return; }
         if (s % (kChunk ? kChunk : 1) == 0) {
             const Acc before = chunk;
             chunk = Acc{};
-            if (WAVES == 8 && s > kChunk) big += before;
+            if (WAVES >= 8 && s > kChunk) big += before;
             chunk = Mat::mul(a, bh[s], chunk);
-            if (WAVES != 8 && s > kChunk) {
+            if (WAVES < 8 && s > kChunk) {
                 __builtin_amdgcn_sched_barrier(0);     // the chunk before is added while this one is multiplied
                 big += before;
             }
@@ -302,9 +316,9 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         }
         if (s == KS - 1) big += chunk;
     };
-    const int32_t sift_from = kSift ? (WAVES == 8 ? list_len * TILE / 2 : list_len * TILE * 2) : n_tiles;
+    const int32_t sift_from = !kSift ? n_tiles : !kTogether || P.ordered ? 0 : WAVES == 8 ? list_len * TILE / 2 : list_len * TILE * 2;
     float slack = 0.f;             // >= |hi lo + lo hi| of this query with any candidate, as summed below
-    if (kSift && n_tiles > sift_from) {
+    if (kSift && sift_from < n_tiles) {
         float h2 = 0.f, l2 = 0.f;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
@@ -321,20 +335,18 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         const float least = sqrtf((float)P.d) * 0x1p-25f;
         slack = 1.01f * (sqrtf(l2) * (1.001f * longest + least) + sqrtf(h2) * (0x1p-11f * longest + least));
     }
-    // tile number i of the stage in buffer `buf`, tile t of the group
-    auto consume = [&](int buf, int i, int32_t t) {
-        Acc big, small, chunk;
+    // tile number i of the stage in buffer `buf`, tile t of the group, `before` tiles after the first
+    auto consume = [&](int buf, int i, int32_t t, int32_t before) {
         const char* stage = (const char*)lds + buf * kStageBytes;
         const float* nn = (const float*)(stage + kDataBytes) + i * TILE + 4 * part;
+        const uint4* frag = (const uint4*)stage + i * kUnits + lane;
+        Acc big, small;
 #pragma unroll
         for (int g = 0; g < kKeys / 4; ++g) {
             const float4 n4 = *(const float4*)(nn + 8 * g);
             big[4 * g] = n4.x; big[4 * g + 1] = n4.y; big[4 * g + 2] = n4.z; big[4 * g + 3] = n4.w;
         }
-#pragma unroll
-        for (int v = 0; v < kKeys; ++v) small[v] = 0.f;
-        const uint4* frag = (const uint4*)stage + i * kUnits + lane;
-        if (kSift && t >= sift_from) {
+        if (kSift && (!kTogether || before >= sift_from)) {
             constexpr int kAhead = KS < 4 ? KS : 4;    // steps whose fragments are on their way
             half8 a[kAhead];
 #pragma unroll
@@ -342,7 +354,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
                 __builtin_amdgcn_sched_barrier(0);
-                large(big, chunk, a[s % kAhead], s);
+                large(big, small, a[s % kAhead], s);
                 __builtin_amdgcn_sched_barrier(0);
                 if (s + kAhead < KS) a[s % kAhead] = *(const half8*)&frag[(s + kAhead) * 128];
             }
@@ -350,6 +362,8 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
 #pragma unroll
             for (int v = 1; v < kKeys; ++v) low = fminf(low, big[v]);
             if (!__any(low <= thr + slack)) return;    // (a key below thr, big + small rounded, has big <= thr + |small|)
+#pragma unroll
+            for (int v = 0; v < kKeys; ++v) small[v] = 0.f;
             half8 ah = *(const half8*)&frag[0], al = *(const half8*)&frag[64];
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
@@ -363,6 +377,9 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                 al = nl;
             }
         } else {
+            Acc chunk;
+#pragma unroll
+            for (int v = 0; v < kKeys; ++v) small[v] = 0.f;
             half8 ah = *(const half8*)&frag[0], al = *(const half8*)&frag[64];
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
@@ -406,19 +423,20 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(bh[s]), "+v"(bl[s]));
     if (n_tiles > 0) {
 #pragma unroll
-        for (int x = 0; x < kBuffers - 1; ++x) fetch(x * kStage, x);
+        for (int x = 0; x < kBuffers - 1; ++x) fetch(x, x);
         int buf = 0;
-        for (int32_t t0 = 0; t0 < n_tiles; t0 += kStage) {
+        for (int32_t x = 0; x < n_stages; ++x) {
             wait_loads<(kBuffers - 2) * kLoads>();    // this wavefront's part of the stage has arrived ...
             __builtin_amdgcn_s_barrier();             // ... everyone's has, and everyone is done with the stage before
             asm volatile("" ::: "memory");
-            fetch(t0 + (kBuffers - 1) * kStage, buf == 0 ? kBuffers - 1 : buf - 1);
+            fetch(x + kBuffers - 1, buf == 0 ? kBuffers - 1 : buf - 1);
             if (live) {
-                if (kStage == 1) consume(buf, 0, t0);
+                const int32_t t0 = first_tile(x);
+                if (kStage == 1) consume(buf, 0, t0, x);
                 else {
                     const int m = min(kStage, n_tiles - t0);
 #pragma nounroll
-                    for (int i = 0; i < m; ++i) consume(buf, i, t0 + i);
+                    for (int i = 0; i < m; ++i) consume(buf, i, t0 + i, x * kStage + i);
                 }
             }
             buf = buf + 1 == kBuffers ? 0 : buf + 1;
@@ -484,8 +502,13 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     }
 }
 
-// wavefronts per workgroup of the filter: eight share a staged tile, unless that leaves compute units without work
-__host__ inline int knn_filter_waves(int tile, int64_t query_tiles) { return query_tiles >= 1024 ? 8 : tile == 32 ? 2 : 4; }
+// Wavefronts per workgroup of the filter: eight share a staged tile, unless that leaves compute units without work.  Inside clusters as
+// many as the registers allow (`most`): 600,000 x 64 in clusters of 4,000, k = 10, unordered, 2.82 -> 2.40 ms.  Over slices of
+// the whole set eight: twelve leave fewer workgroups, and fewer of them stage the tiles, which comes out the same (7.7 ms a call).
+__host__ __device__ constexpr int knn_most_waves(int tile, int steps, int L) {
+    return tile == 32 ? (L == 16 ? (steps <= 2 ? 16 : steps <= 8 ? 12 : 8) : L > 16 && steps <= 2 ? 12 : 8) : L > 2 && steps <= (L == 12 ? 12 : 8) ? 12 : 8;
+}
+__host__ inline int knn_filter_waves(int tile, int64_t query_tiles, int most = 8) { return query_tiles >= 1024 ? most : tile == 32 ? 2 : 4; }
 
 // list length per lane for K' = list_len candidates per query: every list longer than k (32-row tiles, two lists per query;
 // a query whose k nearest all fall to one lane must still be certified), or half of K' (16-row tiles, four lists)

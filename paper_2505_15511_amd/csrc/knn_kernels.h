@@ -1,7 +1,8 @@
 // Device kernels of the in-cluster exact nearest-neighbour index for gfx950 (Section 3.2 of arxiv 2505.15511: the
 // candidates for a point's neighbours are the points of its own cluster; among those the neighbours are exact).
 //
-// A dense contraction: all pairwise dot products inside a cluster.  Four stages:
+// A dense contraction: all pairwise dot products inside a cluster.  The stages:
+//   k_knn_cells    long groups of wide rows only: the rows of a group in the order of cells (k_knn_place), near rows together;
 //   k_knn_pack     every row centred, scaled by a power of two and split into two float16 parts, x' = hi + lo to 2^-22 of x',
 //                  laid out tile by tile in the order the matrix instructions read their operands;
 //   k_knn_filter   float16 matrix cores (hi hi + hi lo + lo hi, float32 accumulation): for every query the K' = k + pad
@@ -240,6 +241,163 @@ __global__ void __launch_bounds__(256) k_knn_group(const int32_t* __restrict__ c
 #pragma unroll
     for (int u = 0; u < kPer; ++u)
         if (cl[u] >= 0) members[h[cl[u]] + rk[u]] = (int32_t)(i0 + u * 256 + threadIdx.x);
+}
+
+// ---------------------------------------------------------------- the order of the rows inside a group
+// The filter passes over a tile of candidates after a third of its products where none of them can be among the nearest of any of the
+// tile's queries.  In random order hardly a tile of a short group is so; where the rows of a group lie cell by cell, most are, as far as
+// the rows of a group differ by more than noise.  A group's cells are the nearest of kCells of its rows.  The order has no part in the answers.
+constexpr int kCells = 16;
+// Mean rows of a group times columns from which the filter gains more than the order costs (the cells' products beside the norms, 0.05 ms
+// for 1,000,000 x 128, and two launches).  Mixtures with four components a cluster, k = 10 to 32, calls without and with the order: clusters of 500 x 128
+// 1.18 / 1.26 to 2.13 / 2.27 ms, 500 x 250 2.32 / 2.35 to 3.46 / 3.41, 500 x 400 1.15 / 1.11, 1,500 x 64 1.54 / 1.55 to 2.66 / 2.81,
+// 1,500 x 128 1.63 / 1.55 to 2.80 / 2.84, 4,000 x 30 2.04 / 1.90 to 3.43 / 3.54, 4,000 x 64 2.34 / 2.12 to 3.87 / 3.71, 4,000 x 256 2.72 / 2.29 to 4.28 / 3.59;
+// isotropic rows, which have no cells worth the name: 3,900 x 128 5.86 / 5.99.
+inline bool knn_ordered(int64_t n, int32_t d, int32_t groups) { return n * d >= (int64_t)200000 * groups; }
+
+// the sum over the sixteen lanes of a row of lanes, in all of them
+template <int CTRL> __device__ __forceinline__ float add_lanes(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float sum_of_16(float v) { return add_lanes<0x140>(add_lanes<0x141>(add_lanes<0x4E>(add_lanes<0xB1>(v)))); }
+
+// k_knn_norms for rows in the order of their groups, with the cell of every row, and how many of the group each cell has.  A slab of a group's rows
+// per workgroup, its cells' rows in LDS.  Bound by the one read of the rows and, nearly as much, the vector pipe: 1,000,000 x 128 0.20 ms, the
+// norms alone 0.16.
+__global__ void __launch_bounds__(256) k_knn_cells(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ members, const uint32_t* __restrict__ start,
+                                                   const KnnBlock* __restrict__ slabs, int32_t rows, const float* __restrict__ centre, float* __restrict__ norm,
+                                                   uint32_t* __restrict__ max_norm_bits, uint8_t* __restrict__ cell_of, uint32_t* __restrict__ counts) {
+    extern __shared__ float4 lds_pivots[];     // [kCells][width / 4] rows, then the centre's
+    __shared__ float half_norm[kCells];
+    __shared__ uint32_t hist[kCells], most;
+    const KnnBlock sl = slabs[blockIdx.x];
+    const uint32_t c0 = start[sl.cluster], n_g = start[sl.cluster + 1] - c0;
+    const uint32_t r0 = c0 + (uint32_t)sl.q0, r1 = min(c0 + n_g, r0 + (uint32_t)rows);
+    const int width = (d + 3) / 4 * 4, part = threadIdx.x % kNormLanes, mine = threadIdx.x / kNormLanes;
+    float* const pivots = (float*)lds_pivots;
+    float* const middle = pivots + kCells * width;
+    if (threadIdx.x < kCells) hist[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) most = 0u;
+    for (int t = threadIdx.x; t < width; t += 256) middle[t] = t < d ? centre[(int64_t)sl.cluster * d + t] : 0.f;
+    __syncthreads();
+    {   // (kCells = 256 / kNormLanes: sixteen lanes a row)
+        const float* x = X + (int64_t)knn_row(members, c0 + (uint32_t)((uint64_t)n_g * (uint32_t)mine / kCells)) * d;
+        float s = 0.f;
+        for (int t = part; t < width; t += kNormLanes) {
+            const float v = t < d ? x[t] - middle[t] : 0.f;
+            pivots[mine * width + t] = v;
+            s = fmaf(v, v, s);
+        }
+        s = sum_of_16(s);
+        if (part == 0) half_norm[mine] = 0.5f * s;
+    }
+    __syncthreads();
+    const bool vec = rows_by_16(X, d);
+    uint32_t bits = 0u;
+    for (uint32_t i0 = r0 + (uint32_t)mine; i0 - (uint32_t)mine < r1; i0 += kNormRows * kNormBatch) {
+        int32_t row[kNormBatch];
+        const float* x[kNormBatch];
+        float s[kNormBatch], dot[kNormBatch][kCells];
+#pragma unroll
+        for (int u = 0; u < kNormBatch; ++u) row[u] = members[min(i0 + u * kNormRows, r1 - 1u)];
+#pragma unroll
+        for (int u = 0; u < kNormBatch; ++u) {
+            x[u] = X + (int64_t)row[u] * d;
+            s[u] = 0.f;
+#pragma unroll
+            for (int p = 0; p < kCells; ++p) dot[u][p] = 0.f;
+        }
+        if (vec) {
+            for (int t = 4 * part; t < d; t += 4 * kNormLanes) {
+                float4 v[kNormBatch];
+#pragma unroll
+                for (int u = 0; u < kNormBatch; ++u) v[u] = *(const float4*)(x[u] + t);
+                const float4 c = *(const float4*)(middle + t);
+#pragma unroll
+                for (int u = 0; u < kNormBatch; ++u) {
+                    v[u].x -= c.x; v[u].y -= c.y; v[u].z -= c.z; v[u].w -= c.w;
+                    s[u] = fmaf(v[u].w, v[u].w, fmaf(v[u].z, v[u].z, fmaf(v[u].y, v[u].y, fmaf(v[u].x, v[u].x, s[u]))));
+                }
+#pragma unroll
+                for (int p = 0; p < kCells; ++p) {
+                    const float4 y = *(const float4*)(pivots + p * width + t);
+#pragma unroll
+                    for (int u = 0; u < kNormBatch; ++u) dot[u][p] = fmaf(v[u].w, y.w, fmaf(v[u].z, y.z, fmaf(v[u].y, y.y, fmaf(v[u].x, y.x, dot[u][p]))));
+                }
+            }
+        } else {
+            for (int t = part; t < d; t += kNormLanes) {
+                float v[kNormBatch];
+#pragma unroll
+                for (int u = 0; u < kNormBatch; ++u) v[u] = x[u][t];
+#pragma unroll
+                for (int u = 0; u < kNormBatch; ++u) {
+                    v[u] -= middle[t];
+                    s[u] = fmaf(v[u], v[u], s[u]);
+                }
+#pragma unroll
+                for (int p = 0; p < kCells; ++p) {
+                    const float y = pivots[p * width + t];
+#pragma unroll
+                    for (int u = 0; u < kNormBatch; ++u) dot[u][p] = fmaf(v[u], y, dot[u][p]);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kNormBatch; ++u) {
+            s[u] = sum_of_16(s[u]);
+            float best = 0.f;
+            int cell = 0;
+#pragma unroll
+            for (int p = 0; p < kCells; ++p) {
+                const float key = half_norm[p] - sum_of_16(dot[u][p]);
+                if (p == 0 || key < best) { best = key; cell = p; }
+            }
+            const uint32_t i = i0 + u * kNormRows;
+            if (part == 0 && i < r1) {
+                norm[row[u]] = s[u];
+                cell_of[i] = (uint8_t)cell;
+                atomicAdd(&hist[cell], 1u);
+                bits = max(bits, __float_as_uint(s[u]));
+            }
+        }
+    }
+    atomicMax(&most, bits);
+    __syncthreads();
+    if (threadIdx.x < kCells && hist[threadIdx.x]) atomicAdd(&counts[(size_t)sl.cluster * kCells + threadIdx.x], hist[threadIdx.x]);
+    if (threadIdx.x == 0) raise_norm(&max_norm_bits[sl.cluster], most);
+}
+
+// the members of every group cell by cell; cursor [groups][kCells] begins at zero
+__global__ void __launch_bounds__(256) k_knn_place(const int32_t* __restrict__ members, const uint8_t* __restrict__ cell_of, const uint32_t* __restrict__ start,
+                                                   const KnnBlock* __restrict__ slabs, int32_t rows, const uint32_t* __restrict__ counts,
+                                                   uint32_t* __restrict__ cursor, int32_t* __restrict__ out) {
+    __shared__ uint32_t hist[kCells], base[kCells];
+    const KnnBlock sl = slabs[blockIdx.x];
+    const uint32_t c0 = start[sl.cluster], c1 = start[sl.cluster + 1];
+    const uint32_t r0 = c0 + (uint32_t)sl.q0, r1 = min(c1, r0 + (uint32_t)rows);
+    if (threadIdx.x < kCells) hist[threadIdx.x] = 0u;
+    __syncthreads();
+    constexpr int kPer = 4;                    // (slabs have up to 1,024 rows)
+    uint32_t cell[kPer], rank[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const uint32_t i = r0 + u * 256 + threadIdx.x;
+        cell[u] = i < r1 ? cell_of[i] : 0u;
+        rank[u] = i < r1 ? atomicAdd(&hist[cell[u]], 1u) : 0u;
+    }
+    __syncthreads();
+    if (threadIdx.x < kCells) {
+        uint32_t before = c0;
+        for (int p = 0; p < (int)threadIdx.x; ++p) before += counts[(size_t)sl.cluster * kCells + p];
+        base[threadIdx.x] = before + atomicAdd(&cursor[(size_t)sl.cluster * kCells + threadIdx.x], hist[threadIdx.x]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const uint32_t i = r0 + u * 256 + threadIdx.x;
+        if (i < r1) out[base[cell[u]] + rank[u]] = members[i];
+    }
 }
 
 // ---------------------------------------------------------------- stage 0: rows for the matrix cores
