@@ -145,6 +145,9 @@ struct MeanStep {
     MeanPartial* partial = nullptr;
     int32_t span = 0;               // positions of a partial sum
     uint32_t n_tiles = 0;           // tiles of the scan over the 256 n_blocks digit counters
+    int32_t* stamp_of = nullptr;    // [K] sort with prev that last saw the cluster change
+    int32_t stamp = 0;
+    ChangedClusters clusters{nullptr, 0};   // of the last sort
     int32_t *keys[2] = {nullptr, nullptr}, *ids[2] = {nullptr, nullptr};   // a pass reads one pair of arrays and writes the other
     const int32_t *sorted_keys = nullptr, *sorted_ids = nullptr;
 
@@ -161,6 +164,8 @@ struct MeanStep {
         parallel = n >= (int64_t)128 * K;
         span = mean_span(n, K, d);
         KTRY(buf.alloc(&lstart, (size_t)K + 1));
+        KTRY(buf.alloc(&stamp_of, (size_t)K));
+        KTRY(hipMemsetAsync(stamp_of, 0, sizeof(int32_t) * (size_t)K, buf.stream));
         n_tiles = (uint32_t)(((size_t)256 * n_blocks + kScanTile - 1) / kScanTile);
         KTRY(buf.alloc(&hist, (size_t)256 * n_blocks));
         KTRY(buf.alloc(&tile_total, (size_t)n_tiles));
@@ -171,15 +176,17 @@ struct MeanStep {
         }
         return NOMAD_OK;
     }
-    // labels [n] in 0..K-1 (on the device); with prev the labels that differ are counted (*changed: zero) and handed to `host`
+    // labels [n] in 0..K-1 (on the device); with prev the labels that differ are counted (*changed: zero) and handed to `host`, and means() leaves
+    // the centroids of clusters that have not changed alone: they are the means of prev's
     int sort(hipStream_t st, const int32_t* labels, const int32_t* prev = nullptr, unsigned long long* changed = nullptr, HostWord* host = nullptr) {
         const int32_t* kin = labels;
         const int32_t* vin = nullptr;   // first pass: the point at position i is i
         int out = 0;
+        clusters = prev ? ChangedClusters{stamp_of, ++stamp} : ChangedClusters{nullptr, 0};
         for (int p = 0; p < passes; ++p) {
             const bool report = p == 0 && prev;
             hipLaunchKernelGGL(k_sort_count, dim3(n_blocks), dim3(256), 0, st, kin, n, 8 * p, n_blocks, hist,
-                               report ? prev : (const int32_t*)nullptr, changed, report ? host->word() : (unsigned long long*)nullptr);
+                               report ? prev : (const int32_t*)nullptr, changed, report ? host->word() : (unsigned long long*)nullptr, clusters);
             if (report) KTRY(host->record(st));
             hipLaunchKernelGGL(k_sort_scan_tiles, dim3(n_tiles), dim3(256), 0, st, hist, (uint64_t)256 * n_blocks, tile_total);
             hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, st, tile_total, (uint64_t)n_tiles);
@@ -203,16 +210,16 @@ struct MeanStep {
     int means(hipStream_t st, const float* dX, float* dC, uint32_t* n_list) {
         const uint32_t entries = blocks_of((int64_t)K * d, 256);
         if (!parallel) {
-            hipLaunchKernelGGL(k_kmeans_update, dim3(entries), dim3(256), 0, st, dX, d, sorted_ids, (const uint32_t*)lstart, K, dC);
+            hipLaunchKernelGGL(k_kmeans_update, dim3(entries), dim3(256), 0, st, dX, d, sorted_ids, (const uint32_t*)lstart, K, clusters, dC);
         } else {
             const auto sums = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(blocks_of(n, span)), dim3(256), 0, st, dX, n, d, sorted_keys, sorted_ids, (const uint32_t*)lstart, span, partial);
+                hipLaunchKernelGGL(kernel, dim3(blocks_of(n, span)), dim3(256), 0, st, dX, n, d, sorted_keys, sorted_ids, (const uint32_t*)lstart, span, clusters, partial);
             };
             // columns per lane: no lane idle before 16-byte loads, as far as rows are aligned for them
             if (d > 128 && rows_by_16(dX, d)) sums(k_mean_partials<4>);
             else if (d % 2 == 0 && d > 64 && ((uintptr_t)dX & 7) == 0) sums(k_mean_partials<2>);
             else sums(k_mean_partials<1>);
-            hipLaunchKernelGGL(k_mean_combine, dim3(entries), dim3(256), 0, st, (const MeanPartial*)partial, d, (const uint32_t*)lstart, K, span, dC, list, n_list);
+            hipLaunchKernelGGL(k_mean_combine, dim3(entries), dim3(256), 0, st, (const MeanPartial*)partial, d, (const uint32_t*)lstart, K, span, clusters, dC, list, n_list);
             hipLaunchKernelGGL(k_mean_ordered, dim3((uint32_t)std::min<int64_t>(2048, (int64_t)K * d)), dim3(256), 0, st, dX, d, sorted_ids,
                                (const uint32_t*)lstart, (const uint32_t*)list, (const uint32_t*)n_list, dC);
         }

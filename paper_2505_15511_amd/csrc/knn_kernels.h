@@ -867,11 +867,22 @@ __device__ __forceinline__ void report_changed(uint32_t count, uint32_t workgrou
     if ((uint32_t)before + 1u == workgroups) *(volatile unsigned long long*)changed_host = (before >> 32) + count;
 }
 
-// With prev it also counts the keys that differ from prev's; the last workgroup hands the count to the host, which waits for it while the
-// sort goes on.
+// Which clusters the M step computes: those that a point has entered or left since the step before.  The others' means are what they were, bit for
+// bit, for a centroid is its members' sum in ascending order.  The stamp of an iteration stands for "changed", so that nothing has to be cleared
+// between two; nullptr: all of them.  In Gaussian mixtures (1,000,000 x 128 in 256 clusters) the share of the points in such clusters goes 0.99, 0.48,
+// 0.21, 0.10, 0.07, .. by iteration, in rows without structure it stays 1.  There, ten iterations: partial sums 1.19 -> 0.52 ms, a call 5.49 -> 4.68.
+struct ChangedClusters {
+    int32_t* stamp_of;
+    int32_t stamp;
+    __device__ __forceinline__ bool has(int32_t j) const { return !stamp_of || stamp_of[j] == stamp; }
+    __device__ __forceinline__ void add(int32_t j) const { if (stamp_of[j] != stamp) stamp_of[j] = stamp; }   // (whoever writes it writes the same)
+};
+
+// With prev it also counts the keys that differ from prev's, and marks their clusters; the last workgroup hands the count to the host, which
+// waits for it while the sort goes on.
 __global__ void __launch_bounds__(256) k_sort_count(const int32_t* __restrict__ keys, int64_t n, int shift, uint32_t n_blocks,
                                                     uint32_t* __restrict__ hist, const int32_t* __restrict__ prev,   // hist [256][n_blocks]
-                                                    unsigned long long* __restrict__ changed, unsigned long long* __restrict__ changed_host) {
+                                                    unsigned long long* __restrict__ changed, unsigned long long* __restrict__ changed_host, ChangedClusters clusters) {
     __shared__ uint32_t h[256], moved;
     h[threadIdx.x] = 0u;
     if (threadIdx.x == 0) moved = 0u;
@@ -881,7 +892,9 @@ __global__ void __launch_bounds__(256) k_sort_count(const int32_t* __restrict__ 
         const int64_t i = i0 + u * 256 + threadIdx.x;
         if (i < n) atomicAdd(&h[((uint32_t)keys[i] >> shift) & 255u], 1u);
         if (prev) {
-            const unsigned long long differ = __ballot(i < n && keys[i] != prev[i]);
+            const bool other = i < n && keys[i] != prev[i];
+            if (other) { clusters.add(keys[i]); clusters.add(prev[i]); }
+            const unsigned long long differ = __ballot(other);
             if (differ && (threadIdx.x & 63) == 0) atomicAdd(&moved, (uint32_t)__popcll(differ));
         }
     }
@@ -1033,12 +1046,12 @@ __device__ __forceinline__ double ordered_column_sum(const float* __restrict__ X
 
 // small clusters: one thread per (cluster, column)
 __global__ void __launch_bounds__(256) k_kmeans_update(const float* __restrict__ X, int32_t d, const int32_t* __restrict__ ids,
-                                                       const uint32_t* __restrict__ start, int32_t K, float* __restrict__ C) {
+                                                       const uint32_t* __restrict__ start, int32_t K, ChangedClusters clusters, float* __restrict__ C) {
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= (int64_t)K * d) return;
     const int32_t j = (int32_t)(x / d), col = (int32_t)(x % d);
     const uint32_t r0 = start[j], r1 = start[j + 1];
-    if (r1 == r0) return;
+    if (r1 == r0 || !clusters.has(j)) return;
     C[x] = (float)(ordered_column_sum(X, d, ids, r0, r1, col) / (double)(r1 - r0));
 }
 
@@ -1128,13 +1141,14 @@ struct MeanPartial { double sum; double magnitude; };
 template <int VEC>
 __global__ void __launch_bounds__(256) k_mean_partials(const float* __restrict__ X, int64_t n, int32_t d, const int32_t* __restrict__ keys,
                                                        const int32_t* __restrict__ ids, const uint32_t* __restrict__ lstart, int32_t span,
-                                                       MeanPartial* __restrict__ partial) {
+                                                       ChangedClusters clusters, MeanPartial* __restrict__ partial) {
     __shared__ double s_sum[4][64 * VEC], s_mag[4][64 * VEC];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t b0 = blockIdx.x * (uint32_t)span, b1 = (uint32_t)min(n, (int64_t)b0 + span);
     for (uint32_t r0 = b0; r0 < b1;) {
         const int32_t j = __builtin_amdgcn_readfirstlane(keys[r0]);
         const uint32_t r1 = min(b1, (uint32_t)__builtin_amdgcn_readfirstlane((int)lstart[j + 1]));
+        if (!clusters.has(j)) { r0 = r1; continue; }
         MeanPartial* out = partial + ((size_t)blockIdx.x + (size_t)j) * d;
         for (int c0 = 0; c0 < d; c0 += 64 * VEC) {
             const int col = c0 + lane * VEC;
@@ -1181,12 +1195,12 @@ __global__ void __launch_bounds__(256) k_mean_partials(const float* __restrict__
 // ordered addition inside span b is at most |P_b| + M_b (+ what the earlier roundings moved, below 2 m u M), so it errs by
 // at most u sum_b m_b (|P_b| + M_b + 2 m u M); the parallel sum by u (span / 4 + 4) M inside the spans and u |P_b| at each join.
 __global__ void __launch_bounds__(256) k_mean_combine(const MeanPartial* __restrict__ partial, int32_t d, const uint32_t* __restrict__ lstart, int32_t K, int32_t span,
-                                                      float* __restrict__ C, uint32_t* __restrict__ list, uint32_t* __restrict__ n_list) {
+                                                      ChangedClusters clusters, float* __restrict__ C, uint32_t* __restrict__ list, uint32_t* __restrict__ n_list) {
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= (int64_t)K * d) return;
     const int32_t j = (int32_t)(x / d), col = (int32_t)(x % d);
     const uint32_t r0 = lstart[j], r1 = lstart[j + 1];
-    if (r1 == r0) return;
+    if (r1 == r0 || !clusters.has(j)) return;
     double sum = 0.0, mag = 0.0, ordered = 0.0, joins = 0.0;
     const uint32_t b1 = (r1 - 1) / span;
     for (uint32_t b = r0 / span; b <= b1; b += 8) {
