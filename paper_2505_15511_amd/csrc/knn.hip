@@ -563,6 +563,9 @@ extern "C" int nomad_kmeans_lsh_init(const float* X, int64_t n, int32_t d, int32
 
 namespace {
 
+// Slices up to which they tell each other their distances (a wavefront reads one word a query and slice each time).
+constexpr int64_t kSharingSlices = 32;
+
 // Exact k nearest other points, among all n rows of A, of the rows listed in dQ (m of them; nullptr: every row).
 // out [m * k] on the device.  A workgroup of the filter scans every candidate of its group, so few queries would leave
 // most of the chip idle: the candidates are then cut into slices, every slice is a group of its own with a copy of the
@@ -582,7 +585,7 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     if (mq >= ((int64_t)1 << 31) - 256) return NOMAD_E_TOO_LARGE;
     uint32_t *max_q = nullptr, *max_c = nullptr, *n_flagged = nullptr;
     int32_t *cand = nullptr, *flagged = nullptr, *self = nullptr, *group_of_q = nullptr, *slice_of = nullptr, *part = nullptr;
-    float *cnorm = nullptr, *keys = nullptr, *tau = nullptr, *centre = nullptr, *AQ = nullptr;
+    float *cnorm = nullptr, *qnorm = nullptr, *shared = nullptr, *keys = nullptr, *tau = nullptr, *centre = nullptr, *AQ = nullptr;
     int* bad = nullptr;
     uint8_t* zeroed = nullptr;   // max_q, max_c, bad, n_flagged, centre
     const size_t zero_words = ((size_t)2 * G + 2 + 3) / 4 * 4;   // ahead of the centres, whose rows are read 16 bytes at a time
@@ -617,6 +620,12 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     cside.d_start = cstart; cside.d_tstart = up.at<uint32_t>(at_ct);
     if (int rc = qside.alloc(buf, false)) return rc;
     if (int rc = cside.alloc(buf, true)) return rc;
+    const bool share = G > 1 && G <= kSharingSlices;
+    if (share) {
+        KTRY(buf.alloc(&qnorm, (size_t)mq));
+        KTRY(buf.alloc(&shared, (size_t)mq));
+        KTRY(hipMemsetAsync(shared, 0x7f, sizeof(float) * (size_t)mq, st));   // 3.4e38: bounds nothing
+    }
     if (G > 1) {
         KTRY(buf.alloc(&group_of_q, (size_t)mq));
         KTRY(buf.alloc(&slice_of, (size_t)n));
@@ -633,13 +642,17 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, A, d, (const int32_t*)nullptr, cstart, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(G * d, 256)), dim3(256), 0, st, centre, cstart, (int32_t)G, d);
     launch_norms(st, A, n, d, nullptr, slice_of, centre, cnorm, max_c);
-    launch_norms(st, AQ, mq, d, nullptr, group_of_q, centre, nullptr, max_q);
+    launch_norms(st, AQ, mq, d, nullptr, group_of_q, centre, qnorm, max_q);
     cside.fill(st, A, d, nullptr, centre, max_c, max_q, cnorm);
     qside.fill(st, AQ, d, nullptr, centre, max_q, nullptr, nullptr);
     KnnSets P{};
     P.XQ = AQ; P.XC = A; P.qmembers = nullptr; P.cmembers = nullptr; P.qstart = qstart; P.cstart = cstart;
     P.Q = qside.view(max_q); P.C = cside.view(max_c); P.centre = centre; P.group_of_q = group_of_q; P.n_q = mq; P.n_c = n; P.d = d; P.same_set = 0; P.chunk = knn_chunk_columns(d, list_len);
     P.self_row = self;
+    if (share) {
+        const int32_t lists = (int32_t)G * (64 / qside.tile);   // lanes that hold candidates of one query
+        P.shared = shared; P.q_norm = qnorm; P.slices = (int32_t)G; P.share_rank = (list_len + lists - 1) / lists - 1;
+    }
     int rc = nearest_in_groups(st, buf, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, G > 1 ? part : out);
     if (rc) return rc;
     if (G > 1) {

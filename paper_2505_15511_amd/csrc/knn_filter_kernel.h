@@ -55,6 +55,11 @@ struct KnnSets {
     int32_t chunk;               // columns that the filter sums at a time (knn_chunk_columns): its error bound depends on it
     const int32_t* self_row;     // or, per query row, the candidate row that is the query itself (nullptr: see same_set)
     int32_t ordered;             // 1: the rows of a group lie cell by cell (k_knn_place): near rows are near in the list
+    // The groups are slices of one set, each with the same queries in the same order, and the answer is the nearest of all slices: what the others
+    // have found bounds what a slice has to find (nullptr: the groups have nothing to do with each other).
+    float* shared;               // [slices][queries] squared distance that share_rank + 1 candidates of every lane of the slice are within; large at first
+    const float* q_norm;         // [n_q] |x'|^2 of the queries
+    int32_t slices, share_rank;
 };
 
 __device__ __forceinline__ int32_t knn_row(const int32_t* members, uint32_t pos) { return members ? members[pos] : (int32_t)pos; }
@@ -151,6 +156,11 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // on nearly every tile; the queue fills its passes.  Keys are looked at in fours: one comparison and a branch where no lane
 // of the wavefront has a hit.  The threshold is the smaller of the lane's last key and the largest of
 // the lanes' H-th keys (H 64 / TILE >= K': what lies above that is not among the K' smallest).
+// Slices of one set (P.shared) tell each other how far their (share_rank + 1)-th keys are, which are K' candidates together: what lies above all of these is
+// not among the K' nearest of the set, and a slice need not look at it.  As distances, for the slices' centres differ; raised by twice the
+// filter's error bound where they are written and where they are read, and by more than the conversion's roundings, so that what is turned away on
+// their account is farther than the K'-th nearest for certain, and `tau` speaks of the rest only.  Every wavefront writes its queries' and reads
+// the others' whenever it has seen an eighth more (some forty times; what others have not written yet bounds nothing, nobody waits).
 // At the end the lists are merged by counting, smallest key first; tau = min(K'-th key of the union, the lists' last keys): every candidate
 // that is not passed on has key >= tau.
 //
@@ -211,6 +221,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
 #pragma unroll
     for (int x = 0; x < L; ++x) { lk[x] = __builtin_inff(); lp[x] = -1; }
     float thr = qpt >= 0 ? __builtin_inff() : -__builtin_inff();   // lanes without a query take nothing
+    float others_thr = __builtin_inff();                           // what the other slices have made of it
 
     const char* csrc = (const char*)(P.C.data + (size_t)ct0 * kUnits);
     const char* nsrc = (const char*)(P.C.norm + (size_t)ct0 * TILE);
@@ -282,7 +293,32 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         float most = lk[H < L ? H - 1 : 0];
 #pragma unroll
         for (int w = TILE; w < 64; w <<= 1) most = fmaxf(most, __shfl_xor(most, w, 64));
-        if (qpt >= 0) thr = fminf(lk[L - 1], most);
+        if (qpt >= 0) thr = fminf(fminf(lk[L - 1], most), others_thr);
+    };
+    const auto share = [&]() {
+        float v = lk[0];
+#pragma unroll
+        for (int x = 1; x < L; ++x) v = x == P.share_rank ? lk[x] : v;
+#pragma unroll
+        for (int w = TILE; w < 64; w <<= 1) v = fmaxf(v, __shfl_xor(v, w, 64));
+        const float eps2 = 2.01f * (float)knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[grp]), (double)__uint_as_float(P.C.max_bits[grp])), kChunk * 512 / TILE);
+        if (qpt < 0) return;
+        const float qn = P.q_norm[qpt], least = fmaf(qn, 1e-4f, eps2);
+        const float own = fmaf(v, key_unit, qn) + least;
+        if (part == 0) __hip_atomic_store(P.shared + (q0g + (uint32_t)qpos), own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        float far = own;
+        for (int32_t h = 0; h < P.slices; h += 8) {
+            float o[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                o[u] = __hip_atomic_load(P.shared + ((size_t)min(h + u, P.slices - 1) * (uint32_t)n_qg + (uint32_t)qpos), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) far = fmaxf(far, o[u]);
+        }
+        if (far > 1e-30f && far < 1e30f) {   // (elsewhere roundings are not what `least` covers)
+            others_thr = fminf(others_thr, ldexpf(fmaf(far, 1.000001f, least - qn), unit_exp - 1));
+            thr = fminf(thr, others_thr);
+        }
     };
     // key and position into the queues of the lanes whose key lies below their threshold: a mask and no branch.  (A branch a key,
     // two jumps on most keys of short groups, and reading a queue's entry only when its pass begins: calls with 1,000,000 x 128 in
@@ -298,6 +334,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                      : [key] "v"(key), [thr] "v"(thr), [pos] "v"(pos), [entry] "s"(kEntry)
                      : "vcc", "scc", "memory");
     };
+    constexpr bool kShares = L > 2 && knn_both_ways(TILE, KS, WAVES);   // (elsewhere registers are short, or the groups are no slices)
     constexpr bool kSift = L > 2 && SIFT, kTogether = knn_both_ways(TILE, KS, WAVES) || !SIFT;
     // step s of the large product: big = the norms and the chunks before, chunk = the present one
     const auto large = [&](Acc& big, Acc& chunk, half8 a, int s) {
@@ -316,7 +353,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         }
         if (s == KS - 1) big += chunk;
     };
-    const int32_t sift_from = !kSift ? n_tiles : !kTogether || P.ordered ? 0 : WAVES == 8 ? list_len * TILE / 2 : list_len * TILE * 2;
+    const int32_t sift_from = !kSift ? n_tiles : !kTogether || P.ordered ? 0 : (WAVES == 8 ? list_len * TILE / 2 : list_len * TILE * 2) / (kShares && P.shared ? P.slices : 1);
     float slack = 0.f;             // >= |hi lo + lo hi| of this query with any candidate, as summed below
     if (kSift && sift_from < n_tiles) {
         float h2 = 0.f, l2 = 0.f;
@@ -425,6 +462,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
 #pragma unroll
         for (int x = 0; x < kBuffers - 1; ++x) fetch(x, x);
         int buf = 0;
+        int32_t next_share = 8;                       // tiles
         for (int32_t x = 0; x < n_stages; ++x) {
             wait_loads<(kBuffers - 2) * kLoads>();    // this wavefront's part of the stage has arrived ...
             __builtin_amdgcn_s_barrier();             // ... everyone's has, and everyone is done with the stage before
@@ -437,6 +475,10 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                     const int m = min(kStage, n_tiles - t0);
 #pragma nounroll
                     for (int i = 0; i < m; ++i) consume(buf, i, t0 + i, x * kStage + i);
+                }
+                if (kShares && P.shared && (x + 1) * kStage >= next_share) {
+                    share();
+                    next_share = (x + 1) * kStage * 9 / 8 + 8;
                 }
             }
             buf = buf + 1 == kBuffers ? 0 : buf + 1;

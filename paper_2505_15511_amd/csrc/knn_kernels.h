@@ -609,7 +609,9 @@ __global__ void __launch_bounds__(256) k_knn_refine(const KnnSets P, const int32
         if (lane + r <= run1 && (Dr < D || (Dr == D && cr < c))) ++rank;
     }
     if (c >= 0 && rank < k) out[(int64_t)q * k + rank] = c;
-    if (lane >= cnt && lane < k) out[(int64_t)q * k + lane] = -1;   // fewer than k candidates in the group
+    if (lane >= cnt && lane < k) out[(int64_t)q * k + lane] = -1;   // fewer than k candidates in the group, or in the slice fewer near enough
+    // (of a slice with fewer, a lane's list may have run over all the same: 16-row tiles, lists of 12)
+    if (P.shared && lane == 0 && cnt < k && t < __builtin_inff()) flagged[atomicAdd(n_flagged, 1u)] = q;
     if (!open) return;
     // |q'|^2 of the centred query as the filter saw it: the group's lanes add a strided share each (the order is free: the
     // value only enters an inequality with slack)
