@@ -585,7 +585,7 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     if (mq >= ((int64_t)1 << 31) - 256) return NOMAD_E_TOO_LARGE;
     uint32_t *max_q = nullptr, *max_c = nullptr, *n_flagged = nullptr;
     int32_t *cand = nullptr, *flagged = nullptr, *self = nullptr, *group_of_q = nullptr, *slice_of = nullptr, *part = nullptr;
-    float *cnorm = nullptr, *qnorm = nullptr, *shared = nullptr, *keys = nullptr, *tau = nullptr, *centre = nullptr, *AQ = nullptr;
+    float *cnorm = nullptr, *qnorm = nullptr, *keys = nullptr, *tau = nullptr, *centre = nullptr, *AQ = nullptr;
     int* bad = nullptr;
     uint8_t* zeroed = nullptr;   // max_q, max_c, bad, n_flagged, centre
     const size_t zero_words = ((size_t)2 * G + 2 + 3) / 4 * 4;   // ahead of the centres, whose rows are read 16 bytes at a time
@@ -620,11 +620,15 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     cside.d_start = cstart; cside.d_tstart = up.at<uint32_t>(at_ct);
     if (int rc = qside.alloc(buf, false)) return rc;
     if (int rc = cside.alloc(buf, true)) return rc;
-    const bool share = G > 1 && G <= kSharingSlices;
+    const int64_t lists = G * (64 / qside.tile);   // lanes that hold candidates of one query
+    const int32_t share_rank = (int32_t)((list_len + 2 * lists - 1) / (2 * lists));
+    const bool share = G > 1 && G <= kSharingSlices && 4 * share_rank <= knn_list_class(qside.tile, list_len);
+    float4* shared = nullptr;
     if (share) {
         KTRY(buf.alloc(&qnorm, (size_t)mq));
-        KTRY(buf.alloc(&shared, (size_t)mq));
-        KTRY(hipMemsetAsync(shared, 0x7f, sizeof(float) * (size_t)mq, st));   // 3.4e38: bounds nothing
+        const size_t words = (size_t)mq * (64 / qside.tile);
+        KTRY(buf.alloc(&shared, words));
+        KTRY(hipMemsetAsync(shared, 0x7f, sizeof(float4) * words, st));   // 3.4e38: bounds nothing
     }
     if (G > 1) {
         KTRY(buf.alloc(&group_of_q, (size_t)mq));
@@ -650,8 +654,7 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     P.Q = qside.view(max_q); P.C = cside.view(max_c); P.centre = centre; P.group_of_q = group_of_q; P.n_q = mq; P.n_c = n; P.d = d; P.same_set = 0; P.chunk = knn_chunk_columns(d, list_len);
     P.self_row = self;
     if (share) {
-        const int32_t lists = (int32_t)G * (64 / qside.tile);   // lanes that hold candidates of one query
-        P.shared = shared; P.q_norm = qnorm; P.slices = (int32_t)G; P.share_rank = (list_len + lists - 1) / lists - 1;
+        P.shared = shared; P.q_norm = qnorm; P.slices = (int32_t)G; P.share_rank = share_rank;
     }
     int rc = nearest_in_groups(st, buf, P, blocks, (uint32_t)hblocks.size(), waves, k, cand, keys, tau, flagged, n_flagged, G > 1 ? part : out);
     if (rc) return rc;

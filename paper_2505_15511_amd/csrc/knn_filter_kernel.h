@@ -57,7 +57,7 @@ struct KnnSets {
     int32_t ordered;             // 1: the rows of a group lie cell by cell (k_knn_place): near rows are near in the list
     // The groups are slices of one set, each with the same queries in the same order, and the answer is the nearest of all slices: what the others
     // have found bounds what a slice has to find (nullptr: the groups have nothing to do with each other).
-    float* shared;               // [slices][queries] squared distance that share_rank + 1 candidates of every lane of the slice are within; large at first
+    void* shared;                // [slices][queries][lanes of a query][4] squared distances that share_rank, 2, 3, 4 share_rank candidates of the lane are within; large at first
     const float* q_norm;         // [n_q] |x'|^2 of the queries
     int32_t slices, share_rank;
 };
@@ -142,7 +142,8 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // the shortest rows), which is worth as much: filter 4.9 ms, ordered 4.2, with twelve wavefronts a workgroup 3.8.  In random order
 // few tiles hold no hit until far into a long group (TILE K' of TILE t candidates' keys after t tiles): there workgroups of eight
 // wavefronts multiply all three products side by side up to tile TILE K' / 2, which saves a chain of dependent products a tile.
-// 10,000 queries among 1,000,000 x 128 in six slices: 63 % of the tiles end after the large product, the filter takes 5.8 ms instead of 7.6.
+// 10,000 queries among 1,000,000 x 128 in six slices: 63 % of the tiles end after the large product, the filter takes 5.96 ms instead of 7.6, and 4.5 since
+// the slices tell each other their distances (5.1 with one rank a list; 3.1 is what it takes without any hit).
 // Workgroups of fewer wavefronts (few queries, one wavefront a SIMD) have nobody to multiply while a chain of dependent products is
 // waited for, and a tile with a hit then waits for two chains in turn: they sift from tile 2 TILE K' on.  50 queries, 30 neighbours,
 // 300,000 x 400: filter 2.18 ms without sifting and chunks, 2.53 with both, 2.41 with the later start and 2.38 with a chunk's sum
@@ -156,11 +157,12 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // on nearly every tile; the queue fills its passes.  Keys are looked at in fours: one comparison and a branch where no lane
 // of the wavefront has a hit.  The threshold is the smaller of the lane's last key and the largest of
 // the lanes' H-th keys (H 64 / TILE >= K': what lies above that is not among the K' smallest).
-// Slices of one set (P.shared) tell each other how far their (share_rank + 1)-th keys are, which are K' candidates together: what lies above all of these is
-// not among the K' nearest of the set, and a slice need not look at it.  As distances, for the slices' centres differ; raised by twice the
-// filter's error bound where they are written and where they are read, and by more than the conversion's roundings, so that what is turned away on
-// their account is farther than the K'-th nearest for certain, and `tau` speaks of the rest only.  Every wavefront writes its queries' and reads
-// the others' whenever it has seen an eighth more (some forty times; what others have not written yet bounds nothing, nobody waits).
+// Slices of one set (P.shared) tell each other how far their lists reach: every lane's r-th, 2 r-th, 3 r-th and 4 r-th keys, with r so that the 2 r-th of all
+// lists together are K' candidates.  The least distance within which these hold K' of them (up to 8 slices; the largest 2 r-th
+// otherwise) is not below the K'-th nearest of the set, and a slice need not look at what lies above it.  As distances, for the slices' centres
+// differ; raised by twice the filter's error bound where they are written and where they are read, and by more than the conversion's roundings, so that what is
+// turned away on their account is farther than the K'-th nearest for certain, and `tau` speaks of the rest only.  Every wavefront writes its
+// queries' and reads the others' whenever it has seen an eighth more (some forty times; what others have not written yet bounds nothing, nobody waits).
 // At the end the lists are merged by counting, smallest key first; tau = min(K'-th key of the union, the lists' last keys): every candidate
 // that is not passed on has key >= tau.
 //
@@ -295,27 +297,64 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         for (int w = TILE; w < 64; w <<= 1) most = fmaxf(most, __shfl_xor(most, w, 64));
         if (qpt >= 0) thr = fminf(fminf(lk[L - 1], most), others_thr);
     };
+    // ranks published of every lane's list: r, 2 r, 3 r, 4 r, r = P.share_rank
+    constexpr int kBisect = 8, kFine = 8;
     const auto share = [&]() {
-        float v = lk[0];
-#pragma unroll
-        for (int x = 1; x < L; ++x) v = x == P.share_rank ? lk[x] : v;
-#pragma unroll
-        for (int w = TILE; w < 64; w <<= 1) v = fmaxf(v, __shfl_xor(v, w, 64));
         const float eps2 = 2.01f * (float)knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[grp]), (double)__uint_as_float(P.C.max_bits[grp])), kChunk * 512 / TILE);
-        if (qpt < 0) return;
-        const float qn = P.q_norm[qpt], least = fmaf(qn, 1e-4f, eps2);
-        const float own = fmaf(v, key_unit, qn) + least;
-        if (part == 0) __hip_atomic_store(P.shared + (q0g + (uint32_t)qpos), own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        float far = own;
-        for (int32_t h = 0; h < P.slices; h += 8) {
-            float o[8];
+        const int32_t row = max(qpt, 0), m = n_qg * kShare, mine = min(qpos, n_qg - 1) * kShare + part;   // (lanes without a query go along)
+        const float qn = P.q_norm[row], least = fmaf(qn, 1e-4f, eps2);
+        float own[4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                o[u] = __hip_atomic_load(P.shared + ((size_t)min(h + u, P.slices - 1) * (uint32_t)n_qg + (uint32_t)qpos), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int y = 0; y < 4; ++y) {
+            const int at_rank = (y + 1) * P.share_rank - 1;
+            float v = lk[0];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) far = fmaxf(far, o[u]);
+            for (int x = 1; x < L; ++x) v = x == at_rank ? lk[x] : v;
+            own[y] = fminf(fmaf(v, key_unit, qn) + least, 3e38f);
         }
-        if (far > 1e-30f && far < 1e30f) {   // (elsewhere roundings are not what `least` covers)
+        unsigned long long* const lists = (unsigned long long*)P.shared;
+        const auto both = [](float a, float b) { return (unsigned long long)__float_as_uint(b) << 32 | __float_as_uint(a); };
+        if (qpt >= 0) {
+            unsigned long long* const to = lists + ((size_t)grp * m + mine) * 2;
+            __hip_atomic_store(to, both(own[0], own[1]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(to + 1, both(own[2], own[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // 2 r of every list are within `far`
+        float far = own[1], near = own[0], o[kFine][4];
+        for (int32_t h0 = 0; h0 < P.slices; h0 += kFine) {
+            unsigned long long lo[kFine], hi[kFine];
+#pragma unroll
+            for (int u = 0; u < kFine; ++u) {
+                const unsigned long long* const from = lists + ((size_t)min(h0 + u, P.slices - 1) * m + mine) * 2;
+                lo[u] = __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                hi[u] = __hip_atomic_load(from + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int u = 0; u < kFine; ++u) {
+                o[u][0] = __uint_as_float((uint32_t)lo[u]); o[u][1] = __uint_as_float((uint32_t)(lo[u] >> 32));
+                o[u][2] = __uint_as_float((uint32_t)hi[u]); o[u][3] = __uint_as_float((uint32_t)(hi[u] >> 32));
+                far = fmaxf(far, o[u][1]);
+                near = fminf(near, o[u][0]);
+                if (h0 + u >= P.slices) o[u][0] = o[u][1] = o[u][2] = o[u][3] = 3e38f;
+            }
+        }
+#pragma unroll
+        for (int w = TILE; w < 64; w <<= 1) { far = fmaxf(far, __shfl_xor(far, w, 64)); near = fminf(near, __shfl_xor(near, w, 64)); }
+        if (P.slices <= kFine) {   // the lists are all in registers: the least distance that K' candidates are within, or a little more
+            for (int y = 0; y < kBisect; ++y) {
+                const float mid = 0.5f * (near + far);
+                int within = 0;
+#pragma unroll
+                for (int u = 0; u < kFine; ++u)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) within += o[u][v] <= mid ? 1 : 0;
+#pragma unroll
+                for (int w = TILE; w < 64; w <<= 1) within += __shfl_xor(within, w, 64);
+                if (within * P.share_rank >= list_len) far = mid;
+                else near = mid;
+            }
+        }
+        if (qpt >= 0 && far > 1e-30f && far < 1e30f) {   // (elsewhere roundings are not what `least` covers)
             others_thr = fminf(others_thr, ldexpf(fmaf(far, 1.000001f, least - qn), unit_exp - 1));
             thr = fminf(thr, others_thr);
         }
@@ -334,7 +373,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                      : [key] "v"(key), [thr] "v"(thr), [pos] "v"(pos), [entry] "s"(kEntry)
                      : "vcc", "scc", "memory");
     };
-    constexpr bool kShares = L > 2 && knn_both_ways(TILE, KS, WAVES);   // (elsewhere registers are short, or the groups are no slices)
+    constexpr bool kShares = L > 2 && knn_both_ways(TILE, KS, WAVES) && !(TILE == 32 && KS > 12);   // (elsewhere registers are short, or the groups are no slices)
     constexpr bool kSift = L > 2 && SIFT, kTogether = knn_both_ways(TILE, KS, WAVES) || !SIFT;
     // step s of the large product: big = the norms and the chunks before, chunk = the present one
     const auto large = [&](Acc& big, Acc& chunk, half8 a, int s) {
