@@ -99,7 +99,7 @@ int nearest_in_groups(hipStream_t st, Buffers& buf, const KnnSets& P, const KnnB
     ExactParts parts{};
     KTRY(buf.alloc(&parts.D, (size_t)grid.x * k)); KTRY(buf.alloc(&parts.P, (size_t)grid.x * k)); KTRY(buf.alloc(&parts.done, (size_t)grid.x));
     KTRY(hipMemsetAsync(parts.done, 0, sizeof(uint32_t) * (size_t)grid.x, st));
-    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, list_len, cand, keys, tau, KnnAssign{nullptr, nullptr, nullptr}));
+    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, list_len, cand, keys, tau, KnnAssign{}));
     if (list_len <= 16)
         hipLaunchKernelGGL(k_knn_refine<16>, dim3(blocks_of(P.n_q, 16)), dim3(256), 0, st, P, cand, keys, tau, k, list_len, out, flagged, n_flagged);
     else if (list_len <= 32)
@@ -112,25 +112,24 @@ int nearest_in_groups(hipStream_t st, Buffers& buf, const KnnSets& P, const KnnB
     return NOMAD_OK;
 }
 
-// The nearest candidate of every query (one group).  Work space: cand [n_q * 128 / tile], tau, todo, flagged [n_q],
-// counters [2] (queries the filter left open, queries for the exact path), both zero.  few: what the filter leaves open goes to
-// the exact path at once (kmeans_plan.h).  Query positions are query rows here.
+// The nearest candidate of every query (one group).  Work space: cand [n_q * 128 / tile], tau, flagged [n_q], open [tiles of queries],
+// n_flagged (zero).  few: what the filter leaves open goes to the exact path at once (kmeans_plan.h).  Query positions are query rows here.
 int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* blocks, uint32_t n_blocks, int waves, bool few, int32_t* cand, float* tau,
-                int32_t* todo, int32_t* flagged, uint32_t* counters, int32_t* out) {
-    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, nullptr, tau, few ? KnnAssign{out, flagged, counters + 1} : KnnAssign{out, todo, counters}));
+                uint32_t* open, int32_t* flagged, uint32_t* n_flagged, int32_t* out) {
+    KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, nullptr, tau, few ? KnnAssign{out, flagged, n_flagged, nullptr} : KnnAssign{out, nullptr, nullptr, open}));
     if (!few) {
-        const int32_t width = 128 / tile;
-        const dim3 grid((uint32_t)std::min<int64_t>((P.n_q * width + 255) / 256, kLoopGrid));
-        hipLaunchKernelGGL(k_assign_refine, grid, dim3(256), 0, st, P, (const int32_t*)todo, (const uint32_t*)counters, (const int32_t*)cand, (const float*)tau,
-                           width, out, flagged, counters + 1);
+        const int64_t n_tiles = (P.n_q + tile - 1) / tile;
+        hipLaunchKernelGGL(k_assign_refine, dim3(blocks_of(n_tiles, 4 * kRefineTiles)), dim3(256), 0, st, P, (const uint32_t*)open, n_tiles, tile, (const int32_t*)cand,
+                           (const float*)tau, 128 / tile, out, flagged, n_flagged);
     }
     hipLaunchKernelGGL((k_knn_exact<1, 256>), dim3((uint32_t)std::min<int64_t>(P.n_q, kLoopGrid)), dim3(256), 0, st, P, (const int32_t*)flagged,
-                       (const uint32_t*)(counters + 1), 1, out, ExactParts{});
+                       (const uint32_t*)n_flagged, 1, out, ExactParts{});
     KTRY(hipGetLastError());
     return NOMAD_OK;
 }
 
 constexpr int32_t kZeroWords = 6;   // counters of an iteration, then the centroids' largest norm
+constexpr int64_t kOpenShare = 16;  // the filter's large products decide alone where they leave fewer than one query in this many open
 
 // The M step of Lloyd's iteration: the points sorted by label with a stable radix sort (ascending point order inside a
 // cluster), then float64 sums in that order per (centroid, column); a label without points leaves its centroid as it is.
@@ -176,17 +175,18 @@ struct MeanStep {
         }
         return NOMAD_OK;
     }
-    // labels [n] in 0..K-1 (on the device); with prev the labels that differ are counted (*changed: zero) and handed to `host`, and means() leaves
-    // the centroids of clusters that have not changed alone: they are the means of prev's
-    int sort(hipStream_t st, const int32_t* labels, const int32_t* prev = nullptr, unsigned long long* changed = nullptr, HostWord* host = nullptr) {
+    // labels [n] in 0..K-1 (on the device); with prev the labels that differ are counted (*changed: zero), and means() leaves the centroids of
+    // clusters that have not changed alone: they are the means of prev's.  host: is handed that count, and *open_count in the high half
+    int sort(hipStream_t st, const int32_t* labels, const int32_t* prev = nullptr, unsigned long long* changed = nullptr, HostWord* host = nullptr,
+             const uint32_t* open_count = nullptr) {
         const int32_t* kin = labels;
         const int32_t* vin = nullptr;   // first pass: the point at position i is i
         int out = 0;
         clusters = prev ? ChangedClusters{stamp_of, ++stamp} : ChangedClusters{nullptr, 0};
         for (int p = 0; p < passes; ++p) {
-            const bool report = p == 0 && prev;
+            const bool report = p == 0 && host;
             hipLaunchKernelGGL(k_sort_count, dim3(n_blocks), dim3(256), 0, st, kin, n, 8 * p, n_blocks, hist,
-                               report ? prev : (const int32_t*)nullptr, changed, report ? host->word() : (unsigned long long*)nullptr, clusters);
+                               p == 0 ? prev : (const int32_t*)nullptr, changed, report ? host->word() : (unsigned long long*)nullptr, open_count, clusters);
             if (report) KTRY(host->record(st));
             hipLaunchKernelGGL(k_sort_scan_tiles, dim3(n_tiles), dim3(256), 0, st, hist, (uint64_t)256 * n_blocks, tile_total);
             hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, st, tile_total, (uint64_t)n_tiles);
@@ -367,21 +367,22 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     }
     // work space
     uint32_t *max_pts = nullptr, *zeros = nullptr;
-    int32_t *new_lab = nullptr, *cand = nullptr, *todo = nullptr, *flagged = nullptr;
-    float *cnorm = nullptr, *tau = nullptr, *centre = nullptr, *c_used = nullptr;
+    uint32_t* open = nullptr;
+    int32_t *new_lab = nullptr, *cand = nullptr, *flagged = nullptr;
+    float *cnorm = nullptr, *xnorm = nullptr, *tau = nullptr, *centre = nullptr, *c_used = nullptr;
     double* inertia = nullptr;
     const std::vector<uint32_t> hq = {0u, (uint32_t)n}, hc = {0u, (uint32_t)K};
     PackedSide points, cents;
     points.plan(hq, d, 1);
     cents.plan(hc, d, 1);
     KTRY(buf.alloc(&max_pts, 1)); KTRY(buf.alloc(&zeros, kZeroWords));
-    KTRY(buf.alloc(&new_lab, (size_t)n)); KTRY(buf.alloc(&cand, (size_t)n * (128 / points.tile))); KTRY(buf.alloc(&todo, (size_t)n)); KTRY(buf.alloc(&flagged, (size_t)n));
+    KTRY(buf.alloc(&new_lab, (size_t)n)); KTRY(buf.alloc(&cand, (size_t)n * (128 / points.tile))); KTRY(buf.alloc(&open, (size_t)points.n_tiles)); KTRY(buf.alloc(&flagged, (size_t)n));
     KTRY(buf.alloc(&cnorm, (size_t)K)); KTRY(buf.alloc(&tau, (size_t)n)); KTRY(buf.alloc(&centre, (size_t)d)); KTRY(buf.alloc(&c_used, (size_t)K * d));
     KTRY(buf.alloc(&inertia, 1));
-    // what every iteration starts from zero: labels changed, the filter's and the exact path's
-    // queries, columns to add in order; and the largest centred |c|^2
+    // what every iteration starts from zero: labels changed, the exact path's queries, those the large products leave open (of a sample),
+    // columns to add in order; and the largest centred |c|^2
     unsigned long long* changed = (unsigned long long*)zeros;   // (and the workgroups that have counted theirs)
-    uint32_t *counters = zeros + 2, *n_list = zeros + 4, *max_cen = zeros + 5;
+    uint32_t *n_flagged = zeros + 2, *open_count = zeros + 3, *n_list = zeros + 4, *max_cen = zeros + 5;
     const int waves = knn_filter_waves(points.tile, points.n_tiles);
     const std::vector<KnnBlock> hblocks = filter_blocks(points, cents, waves);
     const int32_t slab_rows = centroid_rows(n);
@@ -402,7 +403,10 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     KTRY(hipMemsetAsync(max_pts, 0, sizeof(uint32_t), st));
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, (const int32_t*)nullptr, qstart, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(d, 256)), dim3(256), 0, st, centre, qstart, 1, d);
-    launch_norms(st, dX, n, d, nullptr, nullptr, centre, nullptr, max_pts);
+    // (where what is left open goes to the exact path, and where the M step is too short for the host to hear of it, always all three products)
+    const bool few = open_points_are_few(n, K), may_be_alone = !few && !mean_in_one_launch(n, K, d);
+    if (may_be_alone) KTRY(buf.alloc(&xnorm, (size_t)n));
+    launch_norms(st, dX, n, d, nullptr, nullptr, centre, xnorm, max_pts);
     points.fill(st, dX, d, nullptr, centre, max_pts, nullptr, nullptr);
     MeanStep m_step;
     {
@@ -417,7 +421,8 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     int32_t *cur = new_lab, *prev = dLab;
     HostWord hchanged[2];
     for (auto& h : hchanged) KTRY(h.take());
-    const bool prepare = prepare_in_one_launch(K, d), few = open_points_are_few(n, K);
+    const bool prepare = prepare_in_one_launch(K, d);
+    P.q_norm = xnorm; P.open_count = may_be_alone ? open_count : nullptr;
     int32_t it = 0;
     while (it < max_iters) {
         // E step: the nearest centroid of every point, exactly
@@ -430,7 +435,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
             cents.fill(st, dC, d, nullptr, centre, max_cen, max_pts, cnorm);
             KTRY(hipMemcpyAsync(c_used, dC, sizeof(float) * (size_t)K * d, hipMemcpyDeviceToDevice, st));
         }
-        int rc = nearest_one(st, P, points.tile, blocks, (uint32_t)hblocks.size(), waves, few, cand, tau, todo, flagged, counters, cur);
+        int rc = nearest_one(st, P, points.tile, blocks, (uint32_t)hblocks.size(), waves, few, cand, tau, open, flagged, n_flagged, cur);
         if (rc) return rc;
         ++it;
         const int32_t* before = it > 1 ? prev : nullptr;
@@ -447,11 +452,11 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
                 if (last.value() == 0) { --it; break; }
             }
         } else {
-            if ((rc = m_step.sort(st, cur, before, changed, &hchanged[0]))) return rc;
-            if (before) {   // the device sorts while the host waits for the count; wasted only once, when nothing has changed
-                KTRY(hchanged[0].wait());
-                if (hchanged[0].value() == 0) break;   // nothing moved: the centroids are the means of these labels already
-            }
+            if ((rc = m_step.sort(st, cur, before, changed, &hchanged[0], P.open_count))) return rc;
+            KTRY(hchanged[0].wait());   // the device sorts meanwhile; wasted only once, when nothing has changed
+            const unsigned long long counts = hchanged[0].value();
+            if (before && (uint32_t)counts == 0) break;   // nothing moved: the centroids are the means of these labels already
+            P.alone = may_be_alone && (int64_t)(counts >> 32) * kOpenSample * kOpenShare < n;
             if ((rc = m_step.means(st, dX, dC, n_list))) return rc;
             std::swap(cur, prev);
         }

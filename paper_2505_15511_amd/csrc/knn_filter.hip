@@ -7,7 +7,7 @@ namespace {
 template <int TILE, int KS, int L, int WAVES, bool SIFT = true>
 hipError_t launch(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand, float* keys, float* tau,
                   const KnnAssign& assign) {
-    constexpr size_t lds = knn_filter_lds_bytes(TILE, KS, L, WAVES);
+    constexpr size_t lds = knn_filter_lds_bytes(TILE, KS, L, WAVES, L == 2 && !SIFT ? 1 : 2);
     static_assert(lds <= 160 * 1024, "");
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)k_knn_filter<TILE, KS, L, WAVES, SIFT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -24,6 +24,10 @@ hipError_t launch_waves(hipStream_t st, uint32_t n_blocks, int waves, const KnnS
     constexpr int kMost = knn_most_waves(TILE, KS, L), kFew = TILE == 32 ? 2 : 4;
     if (kMost > 8 && waves == kMost) return launch<TILE, KS, L, kMost>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
     if (L > 2 && !knn_both_ways(TILE, KS, 8) && !P.ordered) {
+        if (waves == 8) return launch<TILE, KS, L, 8, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+        return launch<TILE, KS, L, kFew, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+    }
+    if (L == 2 && P.alone) {
         if (waves == 8) return launch<TILE, KS, L, 8, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
         return launch<TILE, KS, L, kFew, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
     }

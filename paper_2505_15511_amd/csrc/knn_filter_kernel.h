@@ -60,6 +60,10 @@ struct KnnSets {
     void* shared;                // [slices][queries][lanes of a query][4] squared distances that share_rank, 2, 3, 4 share_rank candidates of the lane are within; large at first
     const float* q_norm;         // [n_q] |x'|^2 of the queries
     int32_t slices, share_rank;
+    // One neighbour wanted: the large products alone (k_knn_filter), and where the queries are counted that these leave open, or would (nullptr:
+    // nowhere); q_norm is there then
+    int32_t alone;
+    uint32_t* open_count;
 };
 
 __device__ __forceinline__ int32_t knn_row(const int32_t* members, uint32_t pos) { return members ? members[pos] : (int32_t)pos; }
@@ -93,19 +97,20 @@ __host__ __device__ constexpr int knn_chunk_steps(int tile, int steps, int L) {
     return steps <= chunk ? 0 : (tile == 16 ? L > 2 || steps <= 16 : L == 16 && steps <= 12) ? chunk : 0;
 }
 constexpr int kMaxStageTiles = 16;   // packed arrays are this many tiles longer than what they hold
-__host__ __device__ constexpr int knn_stage_tiles(int tile, int steps, int L, int waves) {
-    const int target = tile == 16 ? steps : waves > 12 ? 8 : waves > 8 ? 16 : (L > 2 && waves == 8) ? 24 : 8;
+__host__ __device__ constexpr int knn_stage_tiles(int tile, int steps, int L, int waves, int parts = 2) {
+    const int target = tile == 16 ? steps : parts == 1 ? 16 : waves > 12 ? 8 : waves > 8 ? 16 : (L > 2 && waves == 8) ? 24 : 8;
     return steps >= target ? 1 : target / steps < kMaxStageTiles ? target / steps : kMaxStageTiles;
 }
 __host__ __device__ constexpr int knn_buffers(int tile, int steps, int L, int waves) {
     return (tile == 16 && steps > 16) || (L > 2 && waves >= 8 && knn_stage_tiles(tile, steps, L, waves) > 1) ? 2 : 3;
 }
 __host__ __device__ constexpr int knn_fifo(int tile) { return tile == 32 ? 12 : 8; }   // hits a lane sets aside before they go into its list
-__host__ __device__ constexpr size_t knn_stage_bytes(int tile, int steps, int L, int waves) {
-    return (size_t)knn_stage_tiles(tile, steps, L, waves) * (knn_tile_units(steps) * 16 + (size_t)tile * 4);
+// (parts: 2, or 1 where only the high halves are staged)
+__host__ __device__ constexpr size_t knn_stage_bytes(int tile, int steps, int L, int waves, int parts) {
+    return (size_t)knn_stage_tiles(tile, steps, L, waves, parts) * (knn_tile_units(steps) / 2 * parts * 16 + (size_t)tile * 4);
 }
-__host__ __device__ constexpr size_t knn_filter_lds_bytes(int tile, int steps, int L, int waves) {
-    return knn_buffers(tile, steps, L, waves) * knn_stage_bytes(tile, steps, L, waves) + (L > 2 ? (size_t)waves * knn_fifo(tile) * 64 * 8 : 0);
+__host__ __device__ constexpr size_t knn_filter_lds_bytes(int tile, int steps, int L, int waves, int parts) {
+    return knn_buffers(tile, steps, L, waves) * knn_stage_bytes(tile, steps, L, waves, parts) + (L > 2 ? (size_t)waves * knn_fifo(tile) * 64 * 8 : 0);
 }
 // whether a filter that sifts has the other way of multiplying a tile too (see below): not where registers are short
 __host__ __device__ constexpr bool knn_both_ways(int tile, int steps, int waves) { return waves <= 8 && !(tile == 16 && steps > 16); }
@@ -169,7 +174,15 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // L == 2: one neighbour wanted.  Every key goes straight into the lane's best two; at the end a query whose smallest key
 // lies below the second by more than twice the filter's error bound has its answer (out); the others are put on the `todo`
 // list (query position in todo, its 2 * 64 / TILE candidates in cand, tau) for k_assign_refine.
-struct KnnAssign { int32_t* out; int32_t* todo; uint32_t* n_todo; };
+//
+// Large products alone: the nearest centroid is usually nearer than the second by more than 2 slack, and then hi hi decides: a third of the
+// products, and half of what is read of the queries.  A step of Lloyd's iterations does without the others where the one before has
+// left (or, with all three products, would have left) fewer than a sixteenth of the queries open (kOpenShare); the first one does not.  What is open goes to
+// k_assign_refine as ever, with slack in the margin and in tau.  1,000,000 x 128 and 256 centroids: 227 -> 132 us a step, a call of ten 4.64 -> 3.76 ms.
+// Or, with `open`, a word of bits a tile of queries says which those are, and what goes with them lies at their positions (a list's one counter was what
+// the step waited for: a step of a million points with one in every second wavefront, 150 us for 132).
+struct KnnAssign { int32_t* out; int32_t* todo; uint32_t* n_todo; uint32_t* open; };
+constexpr uint32_t kOpenSample = 64;   // workgroups of which one counts, for the host, what the large products leave open
 
 template <int TILE, int KS, int L, int WAVES, bool SIFT = true>
 __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WAVES)) k_knn_filter(const KnnSets P, const KnnBlock* __restrict__ blocks, int32_t list_len,
@@ -179,11 +192,13 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     using Acc = typename Mat::Acc;
     constexpr int kShare = 64 / TILE;                 // lanes per query
     constexpr int kKeys = TILE * TILE / 64;           // keys per lane and tile
-    constexpr int kUnits = KS * 2 * 64;               // 16-byte units of a tile
+    constexpr bool kAlone = L == 2 && !SIFT;          // large products alone
+    constexpr int kParts = kAlone ? 1 : 2;
+    constexpr int kUnits = KS * 2 * 64, kStaged = KS * kParts * 64;   // 16-byte units of a tile, of what is staged of it
     constexpr int kChunk = knn_chunk_steps(TILE, KS, L);
-    constexpr int kStage = knn_stage_tiles(TILE, KS, L, WAVES), kBuffers = knn_buffers(TILE, KS, L, WAVES);
-    constexpr int kStageBytes = (int)knn_stage_bytes(TILE, KS, L, WAVES), kDataBytes = kStage * kUnits * 16;
-    constexpr int kCopies = (kStage * KS * 2 + WAVES - 1) / WAVES;              // 1 KB loads of a wavefront per stage
+    constexpr int kStage = knn_stage_tiles(TILE, KS, L, WAVES, kParts), kBuffers = knn_buffers(TILE, KS, L, WAVES);
+    constexpr int kStageBytes = (int)knn_stage_bytes(TILE, KS, L, WAVES, kParts), kDataBytes = kStage * kStaged * 16;
+    constexpr int kCopies = (kStage * KS * kParts + WAVES - 1) / WAVES;              // 1 KB loads of a wavefront per stage
     constexpr int kNormCopies = (kStage * TILE + 63) / 64;                      // (every wavefront loads all the norms: they are few)
     constexpr int kLoads = kCopies + kNormCopies;
     constexpr int F = knn_fifo(TILE);
@@ -204,11 +219,16 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     const int32_t qpt = live && qpos < n_qg ? knn_row(P.qmembers, q0g + (uint32_t)qpos) : -1;
     // position of the candidate that is the query itself, if any
     const int32_t self = qpt < 0 ? -1 : P.self_row ? P.self_row[qpt] - (int32_t)c0 : P.same_set ? qpos : -1;
+    const bool counts = L == 2 && P.open_count;
     half8 bh[KS], bl[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         uint4 h = make_uint4(0u, 0u, 0u, 0u), l = h;
-        if (live) { const uint4* src = P.Q.data + ((size_t)qt * KS + s) * 128 + lane; h = src[0]; l = src[64]; }
+        if (live) {
+            const uint4* src = P.Q.data + ((size_t)qt * KS + s) * 128 + lane;
+            h = src[0];
+            if (!kAlone) l = src[64];
+        }
         constexpr uint32_t kSign = 0x80008000u;
         h.x ^= kSign; h.y ^= kSign; h.z ^= kSign; h.w ^= kSign;
         l.x ^= kSign; l.y ^= kSign; l.z ^= kSign; l.w ^= kSign;
@@ -249,8 +269,8 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         const uint32_t to = lds0 + (uint32_t)(buf * kStageBytes);
 #pragma unroll
         for (int u = 0; u < kCopies; ++u) {
-            const uint32_t at = (uint32_t)min(wave + u * WAVES, kStage * KS * 2 - 1) * 1024u;
-            load_to_lds16(to + at, from, at + (uint32_t)lane * 16u);
+            const uint32_t at = (uint32_t)min(wave + u * WAVES, kStage * KS * kParts - 1) * 1024u;
+            load_to_lds16(to + at, from, at * (uint32_t)(2 / kParts) + (uint32_t)lane * 16u);
         }
         const char* nfrom = nsrc + (size_t)t * TILE * 4;
 #pragma unroll
@@ -394,6 +414,10 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     };
     const int32_t sift_from = !kSift ? n_tiles : !kTogether || P.ordered ? 0 : (WAVES == 8 ? list_len * TILE / 2 : list_len * TILE * 2) / (kShares && P.shared ? P.slices : 1);
     float slack = 0.f;             // >= |hi lo + lo hi| of this query with any candidate, as summed below
+    // |hi| <= |c| (1 + 2^-11), |lo| <= 2^-11 |c|, below float16's normal numbers 2^-25 an element; one part in a hundred for
+    // the roundings of the sums (2 768 terms of 2^-23 at most) and of max_bits
+    const auto longest_candidate = [&]() { return ldexpf(sqrtf(__uint_as_float(P.C.max_bits[grp])), knn_scale_exponent(P.C.max_bits[grp])); };
+    const auto least_part = [&]() { return sqrtf((float)P.d) * 0x1p-25f; };
     if (kSift && sift_from < n_tiles) {
         float h2 = 0.f, l2 = 0.f;
 #pragma unroll
@@ -405,17 +429,14 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
             }
 #pragma unroll
         for (int w = TILE; w < 64; w <<= 1) { h2 += __shfl_xor(h2, w, 64); l2 += __shfl_xor(l2, w, 64); }
-        // |hi| <= |c| (1 + 2^-11), |lo| <= 2^-11 |c|, below float16's normal numbers 2^-25 an element; one part in a hundred for
-        // the roundings of the sums (2 768 terms of 2^-23 at most) and of max_bits
-        const float longest = ldexpf(sqrtf(__uint_as_float(P.C.max_bits[grp])), knn_scale_exponent(P.C.max_bits[grp]));
-        const float least = sqrtf((float)P.d) * 0x1p-25f;
+        const float longest = longest_candidate(), least = least_part();
         slack = 1.01f * (sqrtf(l2) * (1.001f * longest + least) + sqrtf(h2) * (0x1p-11f * longest + least));
     }
     // tile number i of the stage in buffer `buf`, tile t of the group, `before` tiles after the first
     auto consume = [&](int buf, int i, int32_t t, int32_t before) {
         const char* stage = (const char*)lds + buf * kStageBytes;
         const float* nn = (const float*)(stage + kDataBytes) + i * TILE + 4 * part;
-        const uint4* frag = (const uint4*)stage + i * kUnits + lane;
+        const uint4* frag = (const uint4*)stage + i * kStaged + lane;
         Acc big, small;
 #pragma unroll
         for (int g = 0; g < kKeys / 4; ++g) {
@@ -452,6 +473,18 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                 ah = nh;
                 al = nl;
             }
+        } else if (kAlone) {
+            constexpr int kAhead = KS < 4 ? KS : 4;
+            half8 a[kAhead];
+#pragma unroll
+            for (int s = 0; s < kAhead; ++s) a[s] = *(const half8*)&frag[s * 64];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                __builtin_amdgcn_sched_barrier(0);
+                large(big, small, a[s % kAhead], s);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + kAhead < KS) a[s % kAhead] = *(const half8*)&frag[(s + kAhead) * 64];
+            }
         } else {
             Acc chunk;
 #pragma unroll
@@ -469,13 +502,14 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                 ah = nh;
                 al = nl;
             }
+            if (L == 2) big += small;
         }
 #pragma unroll
         for (int g = 0; g < kKeys / 4; ++g) {
             float key[4];
             const int32_t pos0 = t * TILE + 8 * g + 4 * part;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) key[v] = big[4 * g + v] + small[4 * g + v];
+            for (int v = 0; v < 4; ++v) key[v] = L == 2 ? big[4 * g + v] : big[4 * g + v] + small[4 * g + v];
             if (L == 2) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
@@ -557,16 +591,27 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         }
         const double eps = knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[grp]), (double)__uint_as_float(P.C.max_bits[grp])),
                                           kChunk * 512 / TILE);
-        const bool open = qpt >= 0 && !(((double)second - (double)best) * (double)key_unit > 2.0 * eps);
+        if (counts) {   // from the query's norm
+            const float least = least_part(), longest = longest_candidate();
+            const float length = ldexpf(sqrtf(P.q_norm[max(qpt, 0)]), knn_scale_exponent(P.Q.max_bits[grp])), lo = fmaf(length, 0x1p-11f, least);
+            slack = 1.01f * (lo * (1.001f * longest + least) + (1.001f * length + least) * (0x1p-11f * longest + least));
+        }
+        const double gap = ((double)second - (double)best) * (double)key_unit, unsure = 2.0 * (double)slack * (double)key_unit;
+        const bool open = qpt >= 0 && !(gap > 2.0 * eps + (kAlone ? unsure : 0.0));
+        if (counts && blockIdx.x % kOpenSample == 0) {
+            const unsigned long long left = __ballot(qpt >= 0 && part == 0 && !(gap > 2.0 * eps + unsure));
+            if (lane == 0 && left) atomicAdd(P.open_count, (uint32_t)__popcll(left));
+        }
         if (qpt >= 0 && !open && part == 0) assign.out[qpt] = knn_row(P.cmembers, c0 + (uint32_t)bp);
         const unsigned long long m = __ballot(open && part == 0);
+        if (assign.open && lane == 0) assign.open[qt - P.Q.tstart[grp]] = (uint32_t)m;
         if (m == 0ull) return;
         uint32_t base = 0u;
-        if (lane == 0) base = atomicAdd(assign.n_todo, (uint32_t)__popcll(m));
+        if (!assign.open && lane == 0) base = atomicAdd(assign.n_todo, (uint32_t)__popcll(m));
         base = __shfl(base, 0, 64);
         if (open) {
-            const uint32_t slot = base + (uint32_t)__popcll(m & ((1ull << (lane & (TILE - 1))) - 1ull));
-            if (part == 0) { assign.todo[slot] = (int32_t)p; tau_out[slot] = last * key_unit; }
+            const uint32_t slot = assign.open ? (uint32_t)p : base + (uint32_t)__popcll(m & ((1ull << (lane & (TILE - 1))) - 1ull));
+            if (part == 0) { if (!assign.open) assign.todo[slot] = (int32_t)p; tau_out[slot] = (kAlone ? last - slack : last) * key_unit; }
 #pragma unroll
             for (int x = 0; x < L; ++x) cand[(size_t)slot * (2 * kShare) + rank[x]] = lp[x] < 0 ? -1 : knn_row(P.cmembers, c0 + (uint32_t)lp[x]);
         }

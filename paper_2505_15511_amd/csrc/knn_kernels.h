@@ -819,13 +819,28 @@ __global__ void __launch_bounds__(THREADS) k_knn_exact(const KnnSets P, const in
 }
 
 // One neighbour wanted, queries the filter's bound could not decide: the exact distances of the `width` (4 or 8)
-// candidates the filter kept, one lane each; certified as in k_knn_refine.
-__global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const int32_t* __restrict__ todo, const uint32_t* __restrict__ n_todo,
+// candidates the filter kept, one lane each; certified as in k_knn_refine.  One group of queries, which are rows; the filter's bits say which of a tile are
+// open: a wavefront takes kRefineTiles tiles, queues theirs in LDS, and then 64 / width queries at a time.
+constexpr int kRefineTiles = 16;
+__global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const uint32_t* __restrict__ open, int64_t n_tiles, int32_t tile,
                                                        const int32_t* __restrict__ cand, const float* __restrict__ tau, int32_t width,
                                                        int32_t* __restrict__ out, int32_t* __restrict__ flagged, uint32_t* __restrict__ n_flagged) {
-    const uint32_t count = *n_todo, per = 256u / (uint32_t)width, lane = threadIdx.x % (uint32_t)width;
-    for (uint32_t x = blockIdx.x * per + threadIdx.x / (uint32_t)width; x < count; x += gridDim.x * per) {
-        const int32_t q = knn_row(P.qmembers, (uint32_t)todo[x]), g = P.group_of_q ? P.group_of_q[q] : 0;
+    __shared__ int32_t queues[4][kRefineTiles * 32];
+    int32_t* const queue = queues[threadIdx.x >> 6];
+    const int64_t t0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kRefineTiles;
+    const uint32_t in_wave = threadIdx.x & 63u, lane = threadIdx.x % (uint32_t)width, per = 64u / (uint32_t)width;
+    uint32_t bits = in_wave < (uint32_t)kRefineTiles && t0 + in_wave < n_tiles ? open[t0 + in_wave] : 0u;
+    uint32_t incl = (uint32_t)__popc(bits);
+    for (int w = 1; w < kRefineTiles; w <<= 1) {
+        const uint32_t up = __shfl_up(incl, w, 64);
+        if (in_wave >= (uint32_t)w) incl += up;
+    }
+    uint32_t at = incl - (uint32_t)__popc(bits);
+    const uint32_t count = __shfl(incl, kRefineTiles - 1, 64);
+    for (; bits; bits &= bits - 1u) queue[at++] = (int32_t)((t0 + in_wave) * tile) + __ffs((int)bits) - 1;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");   // (the queue is the wavefront's own)
+    for (uint32_t y = in_wave / (uint32_t)width; y < count; y += per) {
+        const int32_t x = queue[y], q = x, g = 0;
         if (!knn_filter_usable(P.Q.max_bits[g], P.C.max_bits[g])) {
             if (lane == 0u) flagged[atomicAdd(n_flagged, 1u)] = q;
             continue;
@@ -870,9 +885,10 @@ constexpr int kSortSpan = 2048;
 // a word (sum in the high half), so that one atomic does and nothing has to be fenced (a fence writes the XCD's L2 back: the
 // count of a million labels took 11.5 us with one, 5.4 without).
 __device__ __forceinline__ void report_changed(uint32_t count, uint32_t workgroups, unsigned long long* __restrict__ changed,
-                                               unsigned long long* __restrict__ changed_host) {
+                                               unsigned long long* __restrict__ changed_host, const uint32_t* __restrict__ open_count = nullptr) {
     const unsigned long long before = atomicAdd(changed, ((unsigned long long)count << 32) + 1ull);
-    if ((uint32_t)before + 1u == workgroups) *(volatile unsigned long long*)changed_host = (before >> 32) + count;
+    if ((uint32_t)before + 1u == workgroups)
+        *(volatile unsigned long long*)changed_host = (before >> 32) + count + (open_count ? (unsigned long long)*open_count << 32 : 0ull);
 }
 
 // Which clusters the M step computes: those that a point has entered or left since the step before.  The others' means are what they were, bit for
@@ -886,11 +902,12 @@ struct ChangedClusters {
     __device__ __forceinline__ void add(int32_t j) const { if (stamp_of[j] != stamp) stamp_of[j] = stamp; }   // (whoever writes it writes the same)
 };
 
-// With prev it also counts the keys that differ from prev's, and marks their clusters; the last workgroup hands the count to the host, which
-// waits for it while the sort goes on.
+// With prev it also counts the keys that differ from prev's, and marks their clusters; with changed_host the last workgroup hands the count to the
+// host, which waits for it while the sort goes on, and in the high half what the filter has counted (open_count).
 __global__ void __launch_bounds__(256) k_sort_count(const int32_t* __restrict__ keys, int64_t n, int shift, uint32_t n_blocks,
                                                     uint32_t* __restrict__ hist, const int32_t* __restrict__ prev,   // hist [256][n_blocks]
-                                                    unsigned long long* __restrict__ changed, unsigned long long* __restrict__ changed_host, ChangedClusters clusters) {
+                                                    unsigned long long* __restrict__ changed, unsigned long long* __restrict__ changed_host, const uint32_t* __restrict__ open_count,
+                                                    ChangedClusters clusters) {
     __shared__ uint32_t h[256], moved;
     h[threadIdx.x] = 0u;
     if (threadIdx.x == 0) moved = 0u;
@@ -908,7 +925,7 @@ __global__ void __launch_bounds__(256) k_sort_count(const int32_t* __restrict__ 
     }
     __syncthreads();
     hist[(size_t)threadIdx.x * n_blocks + blockIdx.x] = h[threadIdx.x];
-    if (prev && threadIdx.x == 0) report_changed(moved, gridDim.x, changed, changed_host);
+    if (changed_host && threadIdx.x == 0) report_changed(moved, gridDim.x, changed, changed_host, open_count);
 }
 
 // Exclusive scan of the m counters in two levels: every workgroup scans a tile of kScanTile consecutive counters in
