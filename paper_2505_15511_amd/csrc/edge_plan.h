@@ -224,7 +224,7 @@ inline int plan_small(const EdgePlanRequest& q, const EdgePlan& p, int compute_u
 //   1.13, 300 k 1.16 and 1.21, 600 k 1.08 and 1.12.  Up to where a run is shorter than two
 //   references: s = 2 at 40 M points 28.9 -> 28.4 ms, s = 5 62.5 -> 55.5.
 //   Sub-steps: where points are numbered cluster by cluster the tails of a sub-step lie in a stretch of the tiles, one workgroup of
-//   k_exchange_sums each, and few blocks leave compute units idle.  Exchange over sorted by millions of references a sub-step,
+//   k_tile_sums each, and few blocks leave compute units idle.  Exchange over sorted by millions of references a sub-step,
 //   s = 2: 1 M points 1.4 / 1.08 / 1.03 at 2 / 5.6 / 6.4, 2 M 1.18 / 1.01 / 0.83 at 3.2 / 6.4 / 11; s = 3: 1 M 1.25 / 1.05 / 0.9 at 3.2 / 6.3 / 9.2;
 //   s = 5: 1 M 1.24 / 1.07 / 0.81 at 1.9 / 4.6 / 11, 5 M 0.86 / 0.73 at 7.5 / 22; s = 8: 5 M 1.28 / 1.04 / 0.83 at 6.9 / 8.4 / 17; s = 1: 2 M 1.27 / 1.04 / 0.90 at
 //   5 / 10 / 15.  (Random order: 2 M, s = 2 0.91 at 3.8, 1.42 at 1.4.)  The line is at 8.

@@ -19,8 +19,8 @@
 //
 // A reference costs 42 bytes in streams (2 + 2 out, 2 in and 8 out, 10 in and 8 out, 10 in) where the sorted pass fetches a line of
 // 128 and moves 24.  Ten million points, 3.0e8 positions, s = 5, a quarter of the epoch's positions a launch: edge pass 9.2 ms and
-// tile pass 1.1 before; deal 0.66 (vector pipe and LDS counters), rows 2.49, edges 1.82 (5.0 TB/s: a copy's rate), sums 2.27; the
-// epoch 41.3 -> 29.1 ms.  A million points, directed: 1.33 -> 1.17 ms an epoch.  What holds rows and sums is the short run:
+// tile pass 1.1 before; deal 0.66 (vector pipe and LDS counters), rows 2.49, edges 1.82 (5.0 TB/s: a copy's rate), sums 2.15; the
+// epoch 41.3 -> 28.7 ms.  A million points, directed: 1.33 -> 1.15 ms an epoch.  What holds rows and sums is the short run:
 // without its stores k_exchange_rows takes 0.6 of 2.1 ms, and pieces of 120 bytes at any 8-byte boundary are written at 1.7 TB/s
 // where whole 64-byte sectors go at 3.4 and a stream at 5.4.  Tried: answers laid out tile by tile, staged in LDS and written in whole
 // sectors, read piecewise by the edges (rows 2.4, but its short reads then fetch 7.2 GB for 1.4; edges 2.06); non-temporal

@@ -39,4 +39,8 @@ inline bool prepare_in_one_launch(int64_t K, int64_t d) { return K <= 640 && K *
 // launch less.  Up to 16,384 points -2 to -10 us, wide rows to -40; from K = 1,024 on -24 to +55.
 inline bool open_points_are_few(int64_t n, int64_t K) { return n <= 16384 && K <= 768; }
 
+// Whether the filter may do without the small products where the large ones decide.  The host has to hear how many they leave open after the first
+// step too, when it would not wait otherwise: some 5 us a call, where a step saves 95 at 1,000,000 x 128, K = 256, and less than one below this line.
+inline bool products_may_be_alone(int64_t n) { return n >= 65536; }
+
 }  // namespace nomad_knn

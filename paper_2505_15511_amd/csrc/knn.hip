@@ -164,7 +164,6 @@ struct MeanStep {
         span = mean_span(n, K, d);
         KTRY(buf.alloc(&lstart, (size_t)K + 1));
         KTRY(buf.alloc(&stamp_of, (size_t)K));
-        KTRY(hipMemsetAsync(stamp_of, 0, sizeof(int32_t) * (size_t)K, buf.stream));
         n_tiles = (uint32_t)(((size_t)256 * n_blocks + kScanTile - 1) / kScanTile);
         KTRY(buf.alloc(&hist, (size_t)256 * n_blocks));
         KTRY(buf.alloc(&tile_total, (size_t)n_tiles));
@@ -182,11 +181,14 @@ struct MeanStep {
         const int32_t* kin = labels;
         const int32_t* vin = nullptr;   // first pass: the point at position i is i
         int out = 0;
-        clusters = prev ? ChangedClusters{stamp_of, ++stamp} : ChangedClusters{nullptr, 0};
+        if (!prev) stamp = 0;
+        const ChangedClusters stamps{stamp_of, prev ? ++stamp : 0};
+        clusters = prev ? stamps : ChangedClusters{nullptr, 0};
         for (int p = 0; p < passes; ++p) {
             const bool report = p == 0 && host;
             hipLaunchKernelGGL(k_sort_count, dim3(n_blocks), dim3(256), 0, st, kin, n, 8 * p, n_blocks, hist,
-                               p == 0 ? prev : (const int32_t*)nullptr, changed, report ? host->word() : (unsigned long long*)nullptr, open_count, clusters);
+                               p == 0 ? prev : (const int32_t*)nullptr, changed, report ? host->word() : (unsigned long long*)nullptr, open_count, stamps,
+                               p == 0 && !prev ? K : 0);
             if (report) KTRY(host->record(st));
             hipLaunchKernelGGL(k_sort_scan_tiles, dim3(n_tiles), dim3(256), 0, st, hist, (uint64_t)256 * n_blocks, tile_total);
             hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, st, tile_total, (uint64_t)n_tiles);
@@ -403,8 +405,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     KTRY(hipMemsetAsync(max_pts, 0, sizeof(uint32_t), st));
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, (const int32_t*)nullptr, qstart, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(d, 256)), dim3(256), 0, st, centre, qstart, 1, d);
-    // (where what is left open goes to the exact path, and where the M step is too short for the host to hear of it, always all three products)
-    const bool few = open_points_are_few(n, K), may_be_alone = !few && !mean_in_one_launch(n, K, d);
+    const bool few = open_points_are_few(n, K), may_be_alone = products_may_be_alone(n);
     if (may_be_alone) KTRY(buf.alloc(&xnorm, (size_t)n));
     launch_norms(st, dX, n, d, nullptr, nullptr, centre, xnorm, max_pts);
     points.fill(st, dX, d, nullptr, centre, max_pts, nullptr, nullptr);
@@ -452,9 +453,10 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
                 if (last.value() == 0) { --it; break; }
             }
         } else {
-            if ((rc = m_step.sort(st, cur, before, changed, &hchanged[0], P.open_count))) return rc;
-            KTRY(hchanged[0].wait());   // the device sorts meanwhile; wasted only once, when nothing has changed
-            const unsigned long long counts = hchanged[0].value();
+            const bool wait = before || may_be_alone;
+            if ((rc = m_step.sort(st, cur, before, changed, wait ? &hchanged[0] : nullptr, P.open_count))) return rc;
+            if (wait) KTRY(hchanged[0].wait());   // the device sorts meanwhile; wasted only once, when nothing has changed
+            const unsigned long long counts = wait ? hchanged[0].value() : 0;
             if (before && (uint32_t)counts == 0) break;   // nothing moved: the centroids are the means of these labels already
             P.alone = may_be_alone && (int64_t)(counts >> 32) * kOpenSample * kOpenShare < n;
             if ((rc = m_step.means(st, dX, dC, n_list))) return rc;

@@ -903,12 +903,14 @@ struct ChangedClusters {
 };
 
 // With prev it also counts the keys that differ from prev's, and marks their clusters; with changed_host the last workgroup hands the count to the
-// host, which waits for it while the sort goes on, and in the high half what the filter has counted (open_count).
+// host, which waits for it while the sort goes on, and in the high half what the filter has counted (open_count).  Without prev the stamps of
+// n_clear clusters are cleared.
 __global__ void __launch_bounds__(256) k_sort_count(const int32_t* __restrict__ keys, int64_t n, int shift, uint32_t n_blocks,
                                                     uint32_t* __restrict__ hist, const int32_t* __restrict__ prev,   // hist [256][n_blocks]
                                                     unsigned long long* __restrict__ changed, unsigned long long* __restrict__ changed_host, const uint32_t* __restrict__ open_count,
-                                                    ChangedClusters clusters) {
+                                                    ChangedClusters clusters, int32_t n_clear) {
     __shared__ uint32_t h[256], moved;
+    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; !prev && j < n_clear; j += (int64_t)gridDim.x * 256) clusters.stamp_of[j] = 0;
     h[threadIdx.x] = 0u;
     if (threadIdx.x == 0) moved = 0u;
     __syncthreads();
