@@ -1,19 +1,21 @@
 // libnomad: the instances of the nearest-neighbour filter kernel and their launch (a source of its own: they are most of the
 // index's compile time).
+#include <type_traits>
+
 #include "knn_filter.h"
 
 namespace {
 
-template <int TILE, int KS, int L, int WAVES, bool SIFT = true>
+template <int TILE, int KS, int L, int WAVES, int WAY = kWaySift>
 hipError_t launch(hipStream_t st, uint32_t n_blocks, const KnnSets& P, const KnnBlock* blocks, int32_t list_len, int32_t* cand, float* keys, float* tau,
                   const KnnAssign& assign) {
-    constexpr size_t lds = knn_filter_lds_bytes(TILE, KS, L, WAVES, L == 2 && !SIFT ? 1 : 2);
+    constexpr size_t lds = knn_filter_lds_bytes(TILE, KS, L, WAVES, WAY == kWayAlone ? 1 : 2);
     static_assert(lds <= 160 * 1024, "");
     if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_knn_filter<TILE, KS, L, WAVES, SIFT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void*)k_knn_filter<TILE, KS, L, WAVES, WAY>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_knn_filter<TILE, KS, L, WAVES, SIFT>), dim3(n_blocks), dim3(64 * WAVES), lds, st, P, blocks, list_len, cand, keys, tau, assign);
+    hipLaunchKernelGGL((k_knn_filter<TILE, KS, L, WAVES, WAY>), dim3(n_blocks), dim3(64 * WAVES), lds, st, P, blocks, list_len, cand, keys, tau, assign);
     return hipGetLastError();
 }
 
@@ -23,16 +25,17 @@ hipError_t launch_waves(hipStream_t st, uint32_t n_blocks, int waves, const KnnS
                         float* keys, float* tau, const KnnAssign& assign) {
     constexpr int kMost = knn_most_waves(TILE, KS, L), kFew = TILE == 32 ? 2 : 4;
     if (kMost > 8 && waves == kMost) return launch<TILE, KS, L, kMost>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
-    if (L > 2 && !knn_both_ways(TILE, KS, 8) && !P.ordered) {
-        if (waves == 8) return launch<TILE, KS, L, 8, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
-        return launch<TILE, KS, L, kFew, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
-    }
-    if (L == 2 && P.alone) {
-        if (waves == 8) return launch<TILE, KS, L, 8, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
-        return launch<TILE, KS, L, kFew, false>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
-    }
-    if (waves == 8) return launch<TILE, KS, L, 8>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
-    return launch<TILE, KS, L, kFew>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+    const auto way = [&](auto w) {
+        if (waves == 8) return launch<TILE, KS, L, 8, decltype(w)::value>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+        return launch<TILE, KS, L, kFew, decltype(w)::value>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign);
+    };
+    if constexpr (knn_shares(TILE, KS, L))
+        if (P.shared) return way(std::integral_constant<int, kWayShare>());
+    if constexpr (L > 2 && !knn_both_ways(TILE, KS, 8))
+        if (!P.ordered) return way(std::integral_constant<int, kWayBeside>());
+    if constexpr (L == 2)
+        if (P.alone) return way(std::integral_constant<int, kWayAlone>());
+    return way(std::integral_constant<int, kWaySift>());
 }
 
 }  // namespace

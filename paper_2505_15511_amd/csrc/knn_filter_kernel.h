@@ -184,7 +184,18 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 struct KnnAssign { int32_t* out; int32_t* todo; uint32_t* n_todo; uint32_t* open; };
 constexpr uint32_t kOpenSample = 64;   // workgroups of which one counts, for the host, what the large products leave open
 
-template <int TILE, int KS, int L, int WAVES, bool SIFT = true>
+// What an instance does beside the common part; each is compiled for itself, since scalar registers and the code before the loop count in short groups
+// (6,582 x 84 in 25 clusters with the slices' exchange compiled in: a call 169 -> 178 us)
+enum FilterWay : int {
+    kWaySift,      // several neighbours: sifts
+    kWayBeside,    // several neighbours: all three products side by side
+    kWayShare,     // several neighbours: sifts, and the groups are slices that share their distances
+    kWayAlone      // one neighbour: the large products alone
+};
+// whether an instance for slices exists: not where registers are short
+__host__ __device__ constexpr bool knn_shares(int tile, int steps, int L) { return L > 2 && knn_both_ways(tile, steps, 8) && !(tile == 32 && steps > 12); }
+
+template <int TILE, int KS, int L, int WAVES, int WAY = kWaySift>
 __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WAVES)) k_knn_filter(const KnnSets P, const KnnBlock* __restrict__ blocks, int32_t list_len,
                                                                                int32_t* __restrict__ cand, float* __restrict__ key_out, float* __restrict__ tau_out,
                                                                                const KnnAssign assign) {
@@ -192,7 +203,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     using Acc = typename Mat::Acc;
     constexpr int kShare = 64 / TILE;                 // lanes per query
     constexpr int kKeys = TILE * TILE / 64;           // keys per lane and tile
-    constexpr bool kAlone = L == 2 && !SIFT;          // large products alone
+    constexpr bool kAlone = WAY == kWayAlone;          // large products alone
     constexpr int kParts = kAlone ? 1 : 2;
     constexpr int kUnits = KS * 2 * 64, kStaged = KS * kParts * 64;   // 16-byte units of a tile, of what is staged of it
     constexpr int kChunk = knn_chunk_steps(TILE, KS, L);
@@ -393,8 +404,8 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
                      : [key] "v"(key), [thr] "v"(thr), [pos] "v"(pos), [entry] "s"(kEntry)
                      : "vcc", "scc", "memory");
     };
-    constexpr bool kShares = L > 2 && knn_both_ways(TILE, KS, WAVES) && !(TILE == 32 && KS > 12);   // (elsewhere registers are short, or the groups are no slices)
-    constexpr bool kSift = L > 2 && SIFT, kTogether = knn_both_ways(TILE, KS, WAVES) || !SIFT;
+    constexpr bool kShares = WAY == kWayShare;
+    constexpr bool kSift = L > 2 && WAY != kWayBeside, kTogether = knn_both_ways(TILE, KS, WAVES) || WAY == kWayBeside;
     // step s of the large product: big = the norms and the chunks before, chunk = the present one
     const auto large = [&](Acc& big, Acc& chunk, half8 a, int s) {
         if (kChunk == 0 || s < kChunk) { big = Mat::mul(a, bh[s], big); return; }
@@ -412,7 +423,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         }
         if (s == KS - 1) big += chunk;
     };
-    const int32_t sift_from = !kSift ? n_tiles : !kTogether || P.ordered ? 0 : (WAVES == 8 ? list_len * TILE / 2 : list_len * TILE * 2) / (kShares && P.shared ? P.slices : 1);
+    const int32_t sift_from = !kSift ? n_tiles : !kTogether || P.ordered ? 0 : (WAVES == 8 ? list_len * TILE / 2 : list_len * TILE * 2) / (kShares ? P.slices : 1);
     float slack = 0.f;             // >= |hi lo + lo hi| of this query with any candidate, as summed below
     // |hi| <= |c| (1 + 2^-11), |lo| <= 2^-11 |c|, below float16's normal numbers 2^-25 an element; one part in a hundred for
     // the roundings of the sums (2 768 terms of 2^-23 at most) and of max_bits
@@ -549,7 +560,7 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
 #pragma nounroll
                     for (int i = 0; i < m; ++i) consume(buf, i, t0 + i, x * kStage + i);
                 }
-                if (kShares && P.shared && (x + 1) * kStage >= next_share) {
+                if (kShares && (x + 1) * kStage >= next_share) {
                     share();
                     next_share = (x + 1) * kStage * 9 / 8 + 8;
                 }
