@@ -39,6 +39,15 @@ inline bool prepare_in_one_launch(int64_t K, int64_t d) { return K <= 640 && K *
 // launch less.  Up to 16,384 points -2 to -10 us, wide rows to -40; from K = 1,024 on -24 to +55.
 inline bool open_points_are_few(int64_t n, int64_t K) { return n <= 16384 && K <= 768; }
 
+// Tiles of points whose open points a wavefront of k_assign_refine takes: few, for it takes them 16 at a time (8 in 16-row tiles), a chain of d float64 additions each; but a
+// wavefront's start is not free either.  Calls of five steps on rows without structure, 2 / 4 / 8 / 16 tiles, ms: 1,250 tiles (20,000 x 768) 1.07 / 1.15 / 1.27 / 1.50,
+// 6,251 (100,003 x 768) 2.64 / 2.66 / 2.75 / 3.18, 9,375 (300,000 x 64) 0.98 / 0.95 / 0.94 / 0.94, 31,250 (1,000,000 x 128) 3.89 / 3.84 / 3.81 / 3.75; one tile 4 % slower than two.
+constexpr int kRefineTiles = 16;      // at most (a wavefront's queue in LDS)
+inline int32_t refine_tiles(int64_t n_tiles) {
+    const int64_t tiles = (n_tiles + 2047) / 2048;
+    return (int32_t)(tiles < 2 ? 2 : tiles < kRefineTiles ? tiles : kRefineTiles);
+}
+
 // Whether the filter may do without the small products where the large ones decide.  The host has to hear how many they leave open after the first
 // step too, when it would not wait otherwise: some 5 us a call, where a step saves 95 at 1,000,000 x 128, K = 256, and less than one below this line.
 inline bool products_may_be_alone(int64_t n) { return n >= 65536; }

@@ -119,7 +119,8 @@ int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* bloc
     KTRY(launch_knn_filter(st, n_blocks, waves, P, blocks, 1, cand, nullptr, tau, few ? KnnAssign{out, flagged, n_flagged, nullptr} : KnnAssign{out, nullptr, nullptr, open}));
     if (!few) {
         const int64_t n_tiles = (P.n_q + tile - 1) / tile;
-        hipLaunchKernelGGL(k_assign_refine, dim3(blocks_of(n_tiles, 4 * kRefineTiles)), dim3(256), 0, st, P, (const uint32_t*)open, n_tiles, tile, (const int32_t*)cand,
+        const int32_t tiles = refine_tiles(n_tiles);
+        hipLaunchKernelGGL(k_assign_refine, dim3(blocks_of(n_tiles, 4 * tiles)), dim3(256), 0, st, P, (const uint32_t*)open, n_tiles, tile, tiles, (const int32_t*)cand,
                            (const float*)tau, 128 / tile, out, flagged, n_flagged);
     }
     hipLaunchKernelGGL((k_knn_exact<1, 256>), dim3((uint32_t)std::min<int64_t>(P.n_q, kLoopGrid)), dim3(256), 0, st, P, (const int32_t*)flagged,

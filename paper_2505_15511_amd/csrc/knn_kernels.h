@@ -820,16 +820,17 @@ __global__ void __launch_bounds__(THREADS) k_knn_exact(const KnnSets P, const in
 
 // One neighbour wanted, queries the filter's bound could not decide: the exact distances of the `width` (4 or 8)
 // candidates the filter kept, one lane each; certified as in k_knn_refine.  One group of queries, which are rows; the filter's bits say which of a tile are
-// open: a wavefront takes kRefineTiles tiles, queues theirs in LDS, and then 64 / width queries at a time.
-constexpr int kRefineTiles = 16;
-__global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const uint32_t* __restrict__ open, int64_t n_tiles, int32_t tile,
+// open.  A wavefront takes `tiles` tiles (refine_tiles), queues their open queries in LDS, and then 64 / width of them at a time, each a chain of d
+// additions: as many wavefronts as there can be, and the tiles of one as far apart as can be, for open queries lie together where the rows are in
+// the order of their classes.
+__global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const uint32_t* __restrict__ open, int64_t n_tiles, int32_t tile, int32_t tiles,
                                                        const int32_t* __restrict__ cand, const float* __restrict__ tau, int32_t width,
                                                        int32_t* __restrict__ out, int32_t* __restrict__ flagged, uint32_t* __restrict__ n_flagged) {
     __shared__ int32_t queues[4][kRefineTiles * 32];
     int32_t* const queue = queues[threadIdx.x >> 6];
-    const int64_t t0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kRefineTiles;
     const uint32_t in_wave = threadIdx.x & 63u, lane = threadIdx.x % (uint32_t)width, per = 64u / (uint32_t)width;
-    uint32_t bits = in_wave < (uint32_t)kRefineTiles && t0 + in_wave < n_tiles ? open[t0 + in_wave] : 0u;
+    const int64_t t = (int64_t)in_wave * gridDim.x * 4 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // this lane's tile
+    uint32_t bits = in_wave < (uint32_t)tiles && t < n_tiles ? open[t] : 0u;
     uint32_t incl = (uint32_t)__popc(bits);
     for (int w = 1; w < kRefineTiles; w <<= 1) {
         const uint32_t up = __shfl_up(incl, w, 64);
@@ -837,7 +838,7 @@ __global__ void __launch_bounds__(256) k_assign_refine(const KnnSets P, const ui
     }
     uint32_t at = incl - (uint32_t)__popc(bits);
     const uint32_t count = __shfl(incl, kRefineTiles - 1, 64);
-    for (; bits; bits &= bits - 1u) queue[at++] = (int32_t)((t0 + in_wave) * tile) + __ffs((int)bits) - 1;
+    for (; bits; bits &= bits - 1u) queue[at++] = (int32_t)(t * tile) + __ffs((int)bits) - 1;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");   // (the queue is the wavefront's own)
     for (uint32_t y = in_wave / (uint32_t)width; y < count; y += per) {
         const int32_t x = queue[y], q = x, g = 0;

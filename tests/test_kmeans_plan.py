@@ -57,3 +57,33 @@ def test_spans(rules):
     assert [rules(n, 1_000, 256)[3] for n in (65_535, 65_536)] == [128, 256]
     assert [rules(20_736, K, 64)[3] for K in (9, 8, 3, 2)] == [128, 256, 256, 512]                             # partial sums of a cluster
     assert [rules(20_736, K, 768)[3] for K in (5, 4, 1)] == [128, 256, 256] and [rules(300_000, K, 64)[3] for K in (32, 31, 1)] == [256, 512, 512]
+
+
+PARTS = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+#include "kmeans_plan.h"
+using namespace nomad_knn;
+int main(int argc, char** argv) {
+    if (!strcmp(argv[1], "refine"))                       // tiles of points
+        for (int a = 2; a < argc; ++a) printf("%d\n", (int)refine_tiles(atoll(argv[a])));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("kmeans_parts")
+    (d / "parts.cpp").write_text(PARTS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2505_15511_amd", "csrc"), str(d / "parts.cpp"), "-o", str(d / "parts")],
+                   check=True, capture_output=True, text=True)
+    return lambda *a: [int(x) for x in subprocess.run([str(d / "parts")] + [str(x) for x in a], check=True, capture_output=True, text=True).stdout.split()]
+
+
+def test_what_is_open_is_refined_by_the_whole_chip(ask):
+    for tiles in (1, 3, 625, 1_250, 2_048, 4_096, 4_097, 6_251, 9_375, 18_750, 31_250, 1 << 20, 1 << 27):
+        t, = ask("refine", tiles)
+        assert 1 <= t <= 16                                           # the queue in LDS
+        wavefronts = -(-tiles // t)
+        assert wavefronts >= min(tiles // 2, 1_024)                   # (four to a workgroup, 256 compute units)
