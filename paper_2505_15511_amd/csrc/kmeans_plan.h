@@ -3,6 +3,8 @@
 #pragma once
 #include <stdint.h>
 
+#include "filter_scale.h"
+
 namespace nomad_knn {
 
 // The M step in one launch (k_mean_small) instead of a sort by label, its scans and the sums.  It saves 10 to 30 us where
@@ -46,6 +48,16 @@ constexpr int kRefineTiles = 16;      // at most (a wavefront's queue in LDS)
 inline int32_t refine_tiles(int64_t n_tiles) {
     const int64_t tiles = (n_tiles + 2047) / 2048;
     return (int32_t)(tiles < 2 ? 2 : tiles < kRefineTiles ? tiles : kRefineTiles);
+}
+
+// Which wavefronts count, for the host, what the large products leave open of their tile of points: one in kOpenSample.  The workgroups' points lie in eight
+// lists, an eighth of all points each, in turn (filter_blocks): tile t of list x is counted where t comes to a place among 64 that differs from list to list and
+// from 64 tiles to the next, so that rows in any order of their own, classes one after the other or a period, are met as often as they are there.  (One workgroup in
+// 64 is always the first list's: 1,000,000 x 128 with an eighth in clusters, which come first, and the rest without structure, 13.1 ms a call of six steps, now 4.7.)
+constexpr uint32_t kOpenSample = 64;
+NOMAD_BOTH bool open_is_counted(uint32_t workgroup, uint32_t wave) {
+    const uint32_t list = workgroup % 8u, tile = workgroup / 8u * 8u + wave;   // (eight wavefronts a workgroup)
+    return tile % kOpenSample == (9u * list + 37u * (tile / kOpenSample)) % kOpenSample;
 }
 
 // Whether the filter may do without the small products where the large ones decide.  The host has to hear how many they leave open after the first

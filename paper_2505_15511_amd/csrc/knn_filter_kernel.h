@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "filter_scale.h"
+#include "kmeans_plan.h"
 
 namespace nomad_knn {
 
@@ -182,7 +183,6 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // Or, with `open`, a word of bits a tile of queries says which those are, and what goes with them lies at their positions (a list's one counter was what
 // the step waited for: a step of a million points with one in every second wavefront, 150 us for 132).
 struct KnnAssign { int32_t* out; int32_t* todo; uint32_t* n_todo; uint32_t* open; };
-constexpr uint32_t kOpenSample = 64;   // workgroups of which one counts, for the host, what the large products leave open
 
 // What an instance does beside the common part; each is compiled for itself, since scalar registers and the code before the loop count in short groups
 // (6,582 x 84 in 25 clusters with the slices' exchange compiled in: a call 169 -> 178 us)
@@ -230,7 +230,6 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     const int32_t qpt = live && qpos < n_qg ? knn_row(P.qmembers, q0g + (uint32_t)qpos) : -1;
     // position of the candidate that is the query itself, if any
     const int32_t self = qpt < 0 ? -1 : P.self_row ? P.self_row[qpt] - (int32_t)c0 : P.same_set ? qpos : -1;
-    const bool counts = L == 2 && P.open_count;
     half8 bh[KS], bl[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -602,14 +601,15 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         }
         const double eps = knn_filter_eps(P.d, fmax((double)__uint_as_float(P.Q.max_bits[grp]), (double)__uint_as_float(P.C.max_bits[grp])),
                                           kChunk * 512 / TILE);
-        if (counts) {   // from the query's norm
+        const bool counted = P.open_count && open_is_counted(blockIdx.x, (uint32_t)wave);
+        if (kAlone || counted) {   // from the query's norm
             const float least = least_part(), longest = longest_candidate();
             const float length = ldexpf(sqrtf(P.q_norm[max(qpt, 0)]), knn_scale_exponent(P.Q.max_bits[grp])), lo = fmaf(length, 0x1p-11f, least);
             slack = 1.01f * (lo * (1.001f * longest + least) + (1.001f * length + least) * (0x1p-11f * longest + least));
         }
         const double gap = ((double)second - (double)best) * (double)key_unit, unsure = 2.0 * (double)slack * (double)key_unit;
         const bool open = qpt >= 0 && !(gap > 2.0 * eps + (kAlone ? unsure : 0.0));
-        if (counts && blockIdx.x % kOpenSample == 0) {
+        if (counted) {
             const unsigned long long left = __ballot(qpt >= 0 && part == 0 && !(gap > 2.0 * eps + unsure));
             if (lane == 0 && left) atomicAdd(P.open_count, (uint32_t)__popcll(left));
         }

@@ -68,6 +68,10 @@ using namespace nomad_knn;
 int main(int argc, char** argv) {
     if (!strcmp(argv[1], "refine"))                       // tiles of points
         for (int a = 2; a < argc; ++a) printf("%d\n", (int)refine_tiles(atoll(argv[a])));
+    if (!strcmp(argv[1], "counted"))                      // workgroups: those of their wavefronts that count, as list and tile
+        for (int g = 0; g < atoi(argv[2]); ++g)
+            for (int w = 0; w < 8; ++w)
+                if (open_is_counted((uint32_t)g, (uint32_t)w)) printf("%d %d\n", g % 8, g / 8 * 8 + w);
 }
 """
 
@@ -87,3 +91,14 @@ def test_what_is_open_is_refined_by_the_whole_chip(ask):
         assert 1 <= t <= 16                                           # the queue in LDS
         wavefronts = -(-tiles // t)
         assert wavefronts >= min(tiles // 2, 1_024)                   # (four to a workgroup, 256 compute units)
+
+
+def test_the_sample_of_open_points_is_fair(ask):
+    for groups in (128, 131, 256, 300, 1_000, 4_096, 31_250):
+        v = ask("counted", groups)
+        lists, tiles = v[0::2], v[1::2]
+        per_list = [lists.count(x) for x in range(8)]
+        share = groups / 64                                           # of a list's groups eight tiles each, one in 64 counted
+        assert all(abs(c - share) <= 2 for c in per_list) and min(per_list) >= 1
+        if groups == 4_096:                                           # every place among 64 equally often: rows with a period
+            assert [sum(t % 64 == p for t in tiles) for p in range(64)] == [8] * 64
