@@ -60,8 +60,22 @@ NOMAD_BOTH bool open_is_counted(uint32_t workgroup, uint32_t wave) {
     return tile % kOpenSample == (9u * list + 37u * (tile / kOpenSample)) % kOpenSample;
 }
 
-// Whether the filter may do without the small products where the large ones decide.  The host has to hear how many they leave open after the first
-// step too, when it would not wait otherwise: some 5 us a call, where a step saves 95 at 1,000,000 x 128, K = 256, and less than one below this line.
-inline bool products_may_be_alone(int64_t n) { return n >= 65536; }
+// Whether the filter may do without the small products where the large ones decide, in steps after one that has left few points open: a step saves
+// 3e-6 ns of filter a product (n K d of them) and pays for the points that are open then, counting them costs a few us a call.  Calls of five steps, never / always
+// alone, ms: n K d = 2.7e8 (65,536, K = 64, d = 64) 0.588 / 0.597, 8.2e8 (100,003, K = 128, d = 64) 0.614 / 0.627, 1.1e9 (66,000, K = 256, d = 64) 0.608 / 0.606, 1.7e9
+// (35,000, K = 64, d = 768) 1.072 / 1.033, 3.2e9 (50,000, K = 500, d = 128) 0.827 / 0.793, 1.2e10 (300,000, K = 128, d = 300) 2.21 / 1.82, 7.7e10 (50,000, K = 2,000,
+// d = 768) 3.83 / 3.56; short rows of many points, whose filter the additional operand of a query is as much as: 1,000,000, K = 16, d = 16 0.996 / 1.083.  Fewer than
+// eight wavefronts a workgroup (n_tiles tiles of points) have no such instance.
+inline bool products_may_be_alone(int64_t n, int64_t K, int64_t d, int64_t n_tiles, int64_t steps) {
+    return steps > 1 && n_tiles >= 1024 && K * d >= 8192 && n * K * d >= (int64_t)1 << 30 && !open_points_are_few(n, K);
+}
+// The share of the points, at most, that a step may leave open for the next to do so: what is open costs a row of each of its candidates, and of all centroids where
+// these don't decide, which is as much as the step saves at about K d / 2^20: 300,000, K = 128, d = 64, saved 9 us, paid at a share of 0.016 3, 0.027 18, 0.045 49;
+// 1,000,000, K = 256, d = 128, saved 90, paid at 0.014 20, 0.034 73.
+inline bool products_alone(int64_t open, int64_t n, int64_t K, int64_t d) {
+    const int64_t products = K * d * (d > 256 ? 3 : 1);      // (16-row tiles: 2.5 to 3 times as long a product)
+    const int64_t share = products < 65536 ? (((int64_t)1 << 20) + products - 1) / products : 16;
+    return open * share < n;
+}
 
 }  // namespace nomad_knn

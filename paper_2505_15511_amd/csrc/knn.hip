@@ -130,7 +130,6 @@ int nearest_one(hipStream_t st, const KnnSets& P, int tile, const KnnBlock* bloc
 }
 
 constexpr int32_t kZeroWords = 6;   // counters of an iteration, then the centroids' largest norm
-constexpr int64_t kOpenShare = 16;  // the filter's large products decide alone where they leave fewer than one query in this many open
 
 // The M step of Lloyd's iteration: the points sorted by label with a stable radix sort (ascending point order inside a
 // cluster), then float64 sums in that order per (centroid, column); a label without points leaves its centroid as it is.
@@ -406,7 +405,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     KTRY(hipMemsetAsync(max_pts, 0, sizeof(uint32_t), st));
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, (const int32_t*)nullptr, qstart, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(d, 256)), dim3(256), 0, st, centre, qstart, 1, d);
-    const bool few = open_points_are_few(n, K), may_be_alone = products_may_be_alone(n);
+    const bool few = open_points_are_few(n, K), may_be_alone = products_may_be_alone(n, K, d, points.n_tiles, max_iters);
     if (may_be_alone) KTRY(buf.alloc(&xnorm, (size_t)n));
     launch_norms(st, dX, n, d, nullptr, nullptr, centre, xnorm, max_pts);
     points.fill(st, dX, d, nullptr, centre, max_pts, nullptr, nullptr);
@@ -456,11 +455,15 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
         } else {
             const bool wait = before || may_be_alone;
             if ((rc = m_step.sort(st, cur, before, changed, wait ? &hchanged[0] : nullptr, P.open_count))) return rc;
-            if (wait) KTRY(hchanged[0].wait());   // the device sorts meanwhile; wasted only once, when nothing has changed
-            const unsigned long long counts = wait ? hchanged[0].value() : 0;
-            if (before && (uint32_t)counts == 0) break;   // nothing moved: the centroids are the means of these labels already
-            P.alone = may_be_alone && (int64_t)(counts >> 32) * kOpenSample * kOpenShare < n;
+            if (before) {   // the device sorts while the host waits for the count; wasted only once, when nothing has changed
+                KTRY(hchanged[0].wait());
+                if ((uint32_t)hchanged[0].value() == 0) break;   // nothing moved: the centroids are the means of these labels already
+            }
             if ((rc = m_step.means(st, dX, dC, n_list))) return rc;
+            if (may_be_alone) {
+                if (!before) KTRY(hchanged[0].wait());           // (the means are on their way)
+                P.alone = products_alone((int64_t)(hchanged[0].value() >> 32) * kOpenSample, n, K, d);
+            }
             std::swap(cur, prev);
         }
     }

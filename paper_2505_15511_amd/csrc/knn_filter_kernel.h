@@ -178,7 +178,7 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 //
 // Large products alone: the nearest centroid is usually nearer than the second by more than 2 slack, and then hi hi decides: a third of the
 // products, and half of what is read of the queries.  A step of Lloyd's iterations does without the others where the one before has
-// left (or, with all three products, would have left) fewer than a sixteenth of the queries open (kOpenShare); the first one does not.  What is open goes to
+// left (or, with all three products, would have left) few of the queries open (products_alone); the first one does not.  What is open goes to
 // k_assign_refine as ever, with slack in the margin and in tau.  1,000,000 x 128 and 256 centroids: 227 -> 132 us a step, a call of ten 4.64 -> 3.76 ms.
 // Or, with `open`, a word of bits a tile of queries says which those are, and what goes with them lies at their positions (a list's one counter was what
 // the step waited for: a step of a million points with one in every second wavefront, 150 us for 132).

@@ -72,6 +72,10 @@ int main(int argc, char** argv) {
         for (int g = 0; g < atoi(argv[2]); ++g)
             for (int w = 0; w < 8; ++w)
                 if (open_is_counted((uint32_t)g, (uint32_t)w)) printf("%d %d\n", g % 8, g / 8 * 8 + w);
+    if (!strcmp(argv[1], "line"))                         // n K d n_tiles steps
+        printf("%d\n", (int)products_may_be_alone(atoll(argv[2]), atoll(argv[3]), atoll(argv[4]), atoll(argv[5]), atoll(argv[6])));
+    if (!strcmp(argv[1], "share"))                        // open n K d
+        printf("%d\n", (int)products_alone(atoll(argv[2]), atoll(argv[3]), atoll(argv[4]), atoll(argv[5])));
 }
 """
 
@@ -102,3 +106,16 @@ def test_the_sample_of_open_points_is_fair(ask):
         assert all(abs(c - share) <= 2 for c in per_list) and min(per_list) >= 1
         if groups == 4_096:                                           # every place among 64 equally often: rows with a period
             assert [sum(t % 64 == p for t in tiles) for p in range(64)] == [8] * 64
+
+
+def test_large_products_alone(ask):
+    line = lambda n, K, d, steps=5: ask("line", n, K, d, -(-n // (32 if d <= 256 else 16)), steps) == [1]
+    assert line(1_000_000, 256, 128) and line(100_003, 64, 768) and line(50_000, 2_000, 768)
+    assert not line(1_000_000, 256, 128, 1)                           # a step that no other follows
+    assert not line(1_000_000, 16, 16) and not line(10 ** 9, 4, 8)    # short rows of few centroids
+    assert line(131_072, 128, 64) and not line(131_071, 128, 64)      # products
+    assert line(32_768, 1_000, 250) and not line(32_736, 1_000, 250)  # workgroups of eight wavefronts
+    assert line(16_385, 256, 768) and not line(16_384, 256, 768)      # the open points of few are not refined
+    for K, d, part in ((2_000, 768, 16), (256, 128, 32), (128, 64, 128), (64, 768, 16), (64, 257, 22), (64, 256, 64)):
+        n = 1 << 20
+        assert ask("share", (n - 1) // part, n, K, d) == [1] and ask("share", n // part + 1, n, K, d) == [0]
