@@ -146,7 +146,7 @@ struct MeanStep {
     uint32_t n_tiles = 0;           // tiles of the scan over the 256 n_blocks digit counters
     int32_t* stamp_of = nullptr;    // [K] sort with prev that last saw the cluster change
     int32_t stamp = 0;
-    ChangedClusters clusters{nullptr, 0};   // of the last sort
+    ChangedClusters clusters{nullptr, 0, 0};   // of the last sort
     int32_t *keys[2] = {nullptr, nullptr}, *ids[2] = {nullptr, nullptr};   // a pass reads one pair of arrays and writes the other
     const int32_t *sorted_keys = nullptr, *sorted_ids = nullptr;
 
@@ -182,8 +182,8 @@ struct MeanStep {
         const int32_t* vin = nullptr;   // first pass: the point at position i is i
         int out = 0;
         if (!prev) stamp = 0;
-        const ChangedClusters stamps{stamp_of, prev ? ++stamp : 0};
-        clusters = prev ? stamps : ChangedClusters{nullptr, 0};
+        const ChangedClusters stamps{stamp_of, prev ? ++stamp : 0, K};
+        clusters = prev ? stamps : ChangedClusters{nullptr, 0, 0};
         for (int p = 0; p < passes; ++p) {
             const bool report = p == 0 && host;
             hipLaunchKernelGGL(k_sort_count, dim3(n_blocks), dim3(256), 0, st, kin, n, 8 * p, n_blocks, hist,

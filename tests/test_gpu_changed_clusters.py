@@ -10,8 +10,9 @@ from paper_2505_15511_amd import kmeans_lloyd
 pytestmark = pytest.mark.gpu
 
 
-# sums in parallel (two widths of loads, odd rows), clusters shorter than 128 points, more than 256 centroids (two passes of the sort)
-@pytest.mark.parametrize("n,d,K", [(26000, 20, 24), (20001, 132, 20), (18000, 66, 30), (17001, 7, 160), (40000, 4, 300)])
+# sums in parallel (two widths of loads, odd rows), clusters shorter than 128 points, more than 256 centroids (two passes of the sort), as many as are marked
+# in LDS and one more
+@pytest.mark.parametrize("n,d,K", [(26000, 20, 24), (20001, 132, 20), (18000, 66, 30), (17001, 7, 160), (40000, 4, 300), (17100, 3, 1024), (17100, 3, 1025)])
 def test_clusters_that_do_not_change_keep_their_centroids(n, d, K):
     rng = np.random.default_rng(n)
     centres = 40.0 * rng.normal(size=(K // 2, d))                       # far apart: a cluster with one centroid is settled at once
