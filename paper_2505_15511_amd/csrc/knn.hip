@@ -472,7 +472,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     // inertia of the labels against the centroids they were computed from
     double hinertia = 0.0;
     KTRY(hipMemsetAsync(inertia, 0, sizeof(double), st));
-    hipLaunchKernelGGL(k_kmeans_inertia, dim3(std::min<uint32_t>(kInertiaGrid, blocks_of(n, 64))), dim3(256), 0, st, dX, (const float*)c_used, d, (const int32_t*)dLab, n, inertia);
+    hipLaunchKernelGGL(k_kmeans_inertia, dim3(std::min<uint32_t>(kInertiaGrid, blocks_of(n, kInertiaRows))), dim3(1024), 0, st, dX, (const float*)c_used, d, (const int32_t*)dLab, n, inertia);
     KTRY(hipMemcpyAsync(&hinertia, inertia, sizeof(double), hipMemcpyDeviceToHost, st));
     KTRY(hipGetLastError());
     if (mem == NOMAD_HOST) {

@@ -1463,21 +1463,22 @@ __global__ void __launch_bounds__(256) k_lsh_fallback(const float* __restrict__ 
 }
 
 // sum over the points of the distance to their centroid, in float64, added in no particular order: sixteen lanes a row, four rows of theirs in
-// flight.  Bound by the read of the rows: 1,000,000 x 128 190 -> 109 us (a lane a row, its columns in order, before).
-constexpr int kInertiaGrid = 2048;
-__global__ void __launch_bounds__(256) k_kmeans_inertia(const float* __restrict__ X, const float* __restrict__ C, int32_t d,
+// flight.  Bound by the read of the rows: 1,000,000 x 128 102 us.  The workgroups add to one word, 10 ns each: sixteen wavefronts to a workgroup, few of them
+// (2,048 of four: 130,000 x 16 29 us, now 10).
+constexpr int kInertiaGrid = 512, kInertiaRows = 256;   // workgroups at most, rows of one at a time
+__global__ void __launch_bounds__(1024) k_kmeans_inertia(const float* __restrict__ X, const float* __restrict__ C, int32_t d,
                                                         const int32_t* __restrict__ labels, int64_t n, double* __restrict__ out) {
-    __shared__ double wave_sum[4];
+    __shared__ double wave_sum[16];
     const int part = threadIdx.x % 16;
     const bool vec = rows_by_16(X, d) && rows_by_16(C, d);
     double sum = 0.0;
     const auto add = [&](float a, float b) { const double e = (double)a - (double)b; sum = fma(e, e, sum); };
-    for (int64_t i0 = (int64_t)blockIdx.x * 64 + threadIdx.x / 16; i0 < n; i0 += (int64_t)gridDim.x * 64) {
+    for (int64_t i0 = (int64_t)blockIdx.x * kInertiaRows + threadIdx.x / 16; i0 < n; i0 += (int64_t)gridDim.x * kInertiaRows) {
         const float *x[4], *c[4];
         bool in[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int64_t i = i0 + 16 * u;
+            const int64_t i = i0 + 64 * u;
             in[u] = i < n;
             x[u] = X + (in[u] ? i : i0) * d;
             c[u] = C + (int64_t)labels[in[u] ? i : i0] * d;
@@ -1505,7 +1506,10 @@ __global__ void __launch_bounds__(256) k_kmeans_inertia(const float* __restrict_
     for (int w = 32; w > 0; w >>= 1) sum += __shfl_xor(sum, w, 64);
     if ((threadIdx.x & 63) == 0) wave_sum[threadIdx.x >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(out, (wave_sum[0] + wave_sum[1]) + (wave_sum[2] + wave_sum[3]));
+    if (threadIdx.x >= 64) return;
+    sum = threadIdx.x < 16 ? wave_sum[threadIdx.x] : 0.0;
+    for (int w = 8; w > 0; w >>= 1) sum += __shfl_xor(sum, w, 64);
+    if (threadIdx.x == 0) atomicAdd(out, sum);
 }
 
 }  // namespace nomad_knn
