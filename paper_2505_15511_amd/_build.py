@@ -12,6 +12,7 @@ SOURCES = [os.path.join(_PKG, "csrc", "nomad.hip"), os.path.join(_PKG, "csrc", "
            os.path.join(_PKG, "csrc", "pca.hip"), os.path.join(_PKG, "csrc", "probes.hip")]
 HEADERS = [os.path.join(_PKG, "csrc", "nomad_kernels.h"), os.path.join(_PKG, "csrc", "knn_kernels.h"),
            os.path.join(_PKG, "csrc", "knn_filter.h"), os.path.join(_PKG, "csrc", "knn_filter_kernel.h"), os.path.join(_PKG, "csrc", "filter_scale.h"),
+           os.path.join(_PKG, "csrc", "filter_plan.h"),
            os.path.join(_PKG, "csrc", "rows.h"),
            os.path.join(_PKG, "csrc", "metrics_kernels.h"), os.path.join(_PKG, "csrc", "philox.h"),
            os.path.join(_PKG, "csrc", "pca_kernels.h"), os.path.join(_PKG, "csrc", "host_util.h"),

@@ -8,6 +8,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "filter_plan.h"
 #include "host_util.h"
 #include "kmeans_plan.h"
 #include "knn_filter.h"
@@ -292,7 +293,8 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     }
     PackedSide side;
     side.plan(hstart, d, list_len);
-    const int waves = knn_filter_waves(side.tile, side.n_tiles, knn_most_waves(side.tile, side.steps, knn_list_class(side.tile, list_len)));
+    const int eight = knn_filter_waves(side.tile, side.n_tiles);
+    const int waves = eight == 8 ? filter_waves(side.tstart, knn_most_waves(side.tile, side.steps, knn_list_class(side.tile, list_len))) : eight;
     const std::vector<KnnBlock> hblocks = filter_blocks(side, side, waves);
     HostArrays up;
     const size_t at_start = up.add(hstart), at_tstart = up.add(side.tstart), at_blocks = up.add(hblocks), at_slabs = up.add(hslabs);

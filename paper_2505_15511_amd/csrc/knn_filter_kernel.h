@@ -639,13 +639,13 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     }
 }
 
-// Wavefronts per workgroup of the filter: eight share a staged tile, unless that leaves compute units without work.  Inside clusters as
-// many as the registers allow (`most`): 600,000 x 64 in clusters of 4,000, k = 10, unordered, 2.82 -> 2.40 ms.  Over slices of
+// Wavefronts per workgroup of the filter: eight share a staged tile, unless that leaves compute units without work.  Inside clusters also as
+// many as the registers allow (filter_waves): 600,000 x 64 in clusters of 4,000, k = 10, unordered, 2.82 -> 2.40 ms.  Over slices of
 // the whole set eight: twelve leave fewer workgroups, and fewer of them stage the tiles, which comes out the same (7.7 ms a call).
 __host__ __device__ constexpr int knn_most_waves(int tile, int steps, int L) {
     return tile == 32 ? (L == 16 ? (steps <= 2 ? 16 : steps <= 8 ? 12 : 8) : L > 16 && steps <= 2 ? 12 : 8) : L > 2 && steps <= (L == 12 ? 12 : 8) ? 12 : 8;
 }
-__host__ inline int knn_filter_waves(int tile, int64_t query_tiles, int most = 8) { return query_tiles >= 1024 ? most : tile == 32 ? 2 : 4; }
+__host__ inline int knn_filter_waves(int tile, int64_t query_tiles) { return query_tiles >= 1024 ? 8 : tile == 32 ? 2 : 4; }
 
 // list length per lane for K' = list_len candidates per query: every list longer than k (32-row tiles, two lists per query;
 // a query whose k nearest all fall to one lane must still be certified), or half of K' (16-row tiles, four lists)

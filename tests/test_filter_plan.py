@@ -1,0 +1,77 @@
+"""Wavefronts per workgroup of the neighbour filter inside clusters (csrc/filter_plan.h, compiled on the host): the span against a simulation of the launch, and the rule at
+sets whose workgroups fill the chip once, a little more than once, and many times."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PROGRAM = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "filter_plan.h"
+using namespace nomad_knn;
+int main(int argc, char** argv) {   // most, tiles of every group
+    std::vector<uint32_t> tstart = {0u}, hist;
+    for (int a = 2; a < argc; ++a) {
+        const uint32_t c = (uint32_t)atol(argv[a]);
+        tstart.push_back(tstart.back() + c);
+        if (c >= hist.size()) hist.resize(c + 1, 0u);
+        ++hist[c];
+    }
+    printf("%d %.17g %.17g\n", filter_waves(tstart, atoi(argv[1])), filter_span(hist, 8), filter_span(hist, atoi(argv[1])));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("filter_plan")
+    (d / "plan.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2505_15511_amd", "csrc"), str(d / "plan.cpp"), "-o", str(d / "plan")],
+                   check=True, capture_output=True, text=True)
+
+    def of(most, groups):
+        out = subprocess.run([str(d / "plan"), str(most)] + [str(int(c)) for c in groups], check=True, capture_output=True, text=True).stdout.split()
+        return int(out[0]), float(out[1]), float(out[2])
+    return of
+
+
+def _rounds(groups, waves):
+    """Workgroups, longest first, each to the unit that is free first."""
+    units = np.zeros(256)
+    for c in sorted(groups, reverse=True):
+        for _ in range(-(-int(c) // waves)):
+            units[units.argmin()] += c
+    return units.max()
+
+
+@pytest.mark.parametrize("seed", range(4))
+@pytest.mark.parametrize("groups", [20, 70, 250])
+def test_the_span_is_a_launch(plan, groups, seed):
+    rng = np.random.default_rng(seed)
+    for sizes in (np.full(groups, 125), rng.integers(100, 130, groups), np.ceil(rng.gamma(4.0, 25.0, groups))):
+        for most in (12, 16):
+            _, eight, more = plan(most, sizes)
+            for span, waves in ((eight, 8), (more, most)):
+                launch = _rounds(sizes, waves)
+                assert 0.70 * launch <= span <= 1.25 * launch            # (the last round is not the mean round)
+                if sum(-(-int(c) // waves) for c in sizes) > 1024:       # rounds enough that no single workgroup decides
+                    assert 0.90 * launch <= span
+
+
+def test_the_rule(plan):
+    waves = lambda most, groups: plan(most, groups)[0]
+    assert waves(8, [125] * 250) == 8                                    # registers for no more
+    # clusters of 4,000 rows, tiles of 32: sixteen wavefronts are half as many workgroups
+    assert waves(16, [125] * 8) == 8 and waves(16, [125] * 16) == 8      # one round either way
+    assert waves(16, [125] * 17) == 16                                   # 272 workgroups, 136
+    assert waves(16, [125] * 250) == 16 and waves(12, [125] * 250) == 12
+    assert waves(12, [125] * 25) == 8                                    # 400 and 275: two rounds either way
+    # as many workgroups of twelve as of eight: a cluster's last one has idle wavefronts
+    assert waves(12, [16] * 400) == 8 and waves(12, [16] * 4_000) == 8
+    assert waves(16, [17] * 1_000) == 16 and waves(16, [7] * 5_000) == 8
+    # one cluster ten times as long as the others decides, however many these are
+    assert waves(16, [1_250] + [125] * 10) == 8
+    assert waves(16, [1]) == 8 and waves(16, [0, 0]) == 8

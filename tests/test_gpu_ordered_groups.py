@@ -30,7 +30,11 @@ def _rows(kind, n, d, clusters, seed):
     ("noise", 1700, 127, 1, 32), ("grid", 1200, 200, 1, 15), ("duplicates", 1500, 160, 1, 15), ("components", 780, 512, 2, 5),
     ("components", 772, 517, 2, 24),                     # one row short of the order
     ("components", 34000, 16, 2, 15), ("components", 34000, 61, 7, 9), ("components", 34000, 96, 16, 15), ("noise", 34000, 126, 20, 31),
-    ("components", 17000, 300, 25, 15), ("components", 17000, 190, 16, 25), ("components", 33000, 12, 1, 32)])
+    ("components", 17000, 300, 25, 15), ("components", 17000, 190, 16, 25), ("components", 33000, 12, 1, 32),
+    # twelve and sixteen wavefronts a workgroup, which take a little more than one round of eight to be worth it (tests/test_filter_plan.py), ordered and not
+    ("components", 70000, 16, 17, 15), ("noise", 70000, 30, 17, 8), ("grid", 70000, 15, 17, 15), ("components", 70000, 61, 17, 9), ("components", 70000, 40, 17, 15),
+    ("components", 70000, 90, 17, 15), ("components", 70000, 128, 17, 10), ("components", 70000, 12, 17, 32), ("noise", 70000, 31, 17, 20), ("components", 36000, 300, 9, 15),
+    ("components", 36000, 260, 9, 5), ("components", 36000, 130, 9, 25), ("components", 36000, 200, 9, 20), ("components", 70000, 64, 17, 30), ("components", 65536, 64, 17, 30)])
 def test_the_order_of_the_rows_has_no_part_in_the_answer(kind, n, d, clusters, k):
     X, c = _rows(kind, n, d, clusters, n + d)
     out = knn_in_clusters(torch.from_numpy(X).cuda(), torch.from_numpy(c).cuda(), clusters, k).cpu().numpy()
