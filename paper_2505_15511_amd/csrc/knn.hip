@@ -307,7 +307,7 @@ extern "C" int nomad_knn_in_clusters(const float* X, int64_t n, int32_t d, const
     hipLaunchKernelGGL(k_knn_group, dim3(blocks_of(n, kGroupSpan)), dim3(256), 0, st, dC, n, R, start, cursor, members);
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, members, start, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of((int64_t)R * d, 256)), dim3(256), 0, st, centre, start, R, d);
-    const bool ordered = knn_ordered(n, d, R);   // the order of the rows inside a cluster, and the norms with it
+    const bool ordered = knn_ordered(n, d, R, list_len);   // the order of the rows inside a cluster, and the norms with it
     if (ordered) {
         uint32_t* cells = nullptr;      // [2][R][kCells] counts, cursors
         uint8_t* cell_of = nullptr;

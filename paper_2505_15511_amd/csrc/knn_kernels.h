@@ -259,7 +259,11 @@ constexpr int kCells = 16;
 // 1.18 / 1.26 to 2.13 / 2.27 ms, 500 x 250 2.32 / 2.35 to 3.46 / 3.41, 500 x 400 1.15 / 1.11, 1,500 x 64 1.54 / 1.55 to 2.66 / 2.81,
 // 1,500 x 128 1.63 / 1.55 to 2.80 / 2.84, 4,000 x 30 2.04 / 1.90 to 3.43 / 3.54, 4,000 x 64 2.34 / 2.12 to 3.87 / 3.71, 4,000 x 256 2.72 / 2.29 to 4.28 / 3.59;
 // isotropic rows, which have no cells worth the name: 3,900 x 128 5.86 / 5.99.
-inline bool knn_ordered(int64_t n, int32_t d, int32_t groups) { return n * d >= (int64_t)200000 * groups; }
+// Long lists in 32-row tiles take their longest from the queries' own tiles, which come first: where all workgroups run at once nothing makes up for it.  k = 30, clusters of
+// 4,000 x 64 and 2,000 x 120, unordered / ordered: 33,000 points 0.44 / 0.48 and 0.41 / 0.45 ms, 50,000 0.44 / 0.50 and 0.43 / 0.47, 70,000 0.74 / 0.68 and 0.66 / 0.65, 200,000 1.41 / 1.22 and 1.25 / 1.17.
+inline bool knn_ordered(int64_t n, int32_t d, int32_t groups, int32_t list_len) {
+    return n * d >= (int64_t)200000 * groups && (n > 65536 || list_len <= kShortList || knn_tile(d, list_len) == 16);
+}
 
 // the sum over the sixteen lanes of a row of lanes, in all of them
 template <int CTRL> __device__ __forceinline__ float add_lanes(float v) {
