@@ -31,6 +31,7 @@ hipError_t launch_waves(hipStream_t st, uint32_t n_blocks, int waves, const KnnS
     };
     if constexpr (knn_shares(TILE, KS, L))
         if (P.shared) return way(std::integral_constant<int, kWayShare>());
+    if (P.shared) return hipErrorInvalidValue;   // (knn_shares: the caller asks)
     if constexpr (L > 2 && !knn_both_ways(TILE, KS, 8))
         if (!P.ordered) return way(std::integral_constant<int, kWayBeside>());
     if constexpr (L == 2)
