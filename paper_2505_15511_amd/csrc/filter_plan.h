@@ -1,4 +1,5 @@
-// libnomad: how many wavefronts share a workgroup of the neighbour filter inside clusters, plain C++ (a test compiles it with the host compiler).
+// libnomad: how many wavefronts share a workgroup of the neighbour filter inside clusters, and which slices of one set share their distances, plain C++
+// (a test compiles it with the host compiler).
 #pragma once
 #include <stdint.h>
 
@@ -47,6 +48,16 @@ inline int filter_waves(const std::vector<uint32_t>& tstart, int most) {
     std::vector<uint32_t> hist((size_t)longest + 1, 0u);
     for (size_t g = 0; g + 1 < tstart.size(); ++g) ++hist[tstart[g + 1] - tstart[g]];
     return 7.0 * filter_span(hist, most) < 6.0 * filter_span(hist, 8) ? most : 8;
+}
+
+// Whether slices of one set tell each other how near their candidates are: a wavefront does so some ten times over 4,000 candidates, twenty over 16,000, forty over 166,000, each
+// time reading 16 bytes a slice and lane (four lanes a query in 16-row tiles, two in 32-row ones), and what it saves goes with the candidates.  Calls, shared over not,
+// by slices x candidates: 2 x 5,000 1.07, 4 x 9,661 1.04, 6 x 7,750 1.00, 8 x 14,650 0.93, 8 x 57,546 0.79; 17 x 4,201 1.07, 17 x 11,593 1.07, 17 x 22,513 0.99, 12 x 21,890 0.98,
+// 12 x 36,285 0.94; 25 x 12,000 1.05, 21 x 47,620 0.96; 16-row tiles 2 x 13,007 1.04, 6 x 4,349 1.18, 12 x 15,901 1.06, 6 x 16,668 0.94; long lists in 32-row tiles, whose hits
+// take longer, 4 x 4,523 1.03, 6 x 7,750 1.00, 8 x 12,500 0.95.
+inline bool slices_share(int64_t slices, int64_t candidates, int tile, bool long_list) {
+    constexpr int64_t kMost = 32;
+    return slices > 1 && slices <= kMost && candidates >= (long_list && tile == 32 ? 8192 : 14336) && candidates * tile >= 1280 * 32 * slices;
 }
 
 }  // namespace nomad_knn

@@ -576,9 +576,6 @@ extern "C" int nomad_kmeans_lsh_init(const float* X, int64_t n, int32_t d, int32
 
 namespace {
 
-// Slices up to which they tell each other their distances (every lane of a query reads 16 bytes a slice each time).
-constexpr int64_t kSharingSlices = 32;
-
 // Exact k nearest other points, among all n rows of A, of the rows listed in dQ (m of them; nullptr: every row).
 // out [m * k] on the device.  A workgroup of the filter scans every candidate of its group, so few queries would leave
 // most of the chip idle: the candidates are then cut into slices, every slice is a group of its own with a copy of the
@@ -636,7 +633,7 @@ int neighbours_of_queries(hipStream_t st, Buffers& buf, const float* A, int64_t 
     const int64_t lists = G * (64 / qside.tile);   // lanes that hold candidates of one query
     const int32_t share_rank = (int32_t)((list_len + 2 * lists - 1) / (2 * lists));
     const int lanes_list = knn_list_class(qside.tile, list_len);
-    const bool share = G > 1 && G <= kSharingSlices && knn_shares(qside.tile, qside.steps, lanes_list) && 4 * share_rank <= lanes_list;
+    const bool share = slices_share(G, slice, qside.tile, list_len > kShortList) && knn_shares(qside.tile, qside.steps, lanes_list) && 4 * share_rank <= lanes_list;
     float4* shared = nullptr;
     if (share) {
         KTRY(buf.alloc(&qnorm, (size_t)mq));

@@ -12,7 +12,8 @@ PROGRAM = r"""
 #include <stdlib.h>
 #include "filter_plan.h"
 using namespace nomad_knn;
-int main(int argc, char** argv) {   // most, tiles of every group
+int main(int argc, char** argv) {   // most, tiles of every group; or 0, slices, candidates, tile, long lists
+    if (atoi(argv[1]) == 0) { printf("%d\n", (int)slices_share(atoll(argv[2]), atoll(argv[3]), atoi(argv[4]), atoi(argv[5]))); return 0; }
     std::vector<uint32_t> tstart = {0u}, hist;
     for (int a = 2; a < argc; ++a) {
         const uint32_t c = (uint32_t)atol(argv[a]);
@@ -34,7 +35,7 @@ def plan(tmp_path_factory):
 
     def of(most, groups):
         out = subprocess.run([str(d / "plan"), str(most)] + [str(int(c)) for c in groups], check=True, capture_output=True, text=True).stdout.split()
-        return int(out[0]), float(out[1]), float(out[2])
+        return (int(out[0]), float(out[1]), float(out[2])) if most else int(out[0])
     return of
 
 
@@ -75,3 +76,12 @@ def test_the_rule(plan):
     # one cluster ten times as long as the others decides, however many these are
     assert waves(16, [1_250] + [125] * 10) == 8
     assert waves(16, [1]) == 8 and waves(16, [0, 0]) == 8
+
+
+def test_which_slices_share(plan):
+    share = lambda slices, candidates, tile, long_lists=0: plan(0, [slices, candidates, tile, long_lists]) == 1
+    assert share(2, 14_336, 32) and not share(2, 14_335, 32) and not share(1, 10 ** 6, 32)
+    assert share(20, 25_600, 32) and not share(20, 25_599, 32)
+    assert share(6, 15_360, 16) and not share(6, 15_359, 16)
+    assert share(6, 8_192, 32, 1) and not share(6, 8_191, 32, 1) and not share(7, 8_192, 32, 1) and not share(2, 14_335, 16, 1)
+    assert share(32, 40_960, 32) and not share(33, 10 ** 6, 32)
