@@ -35,7 +35,7 @@ hipError_t launch_waves(hipStream_t st, uint32_t n_blocks, int waves, const KnnS
     if constexpr (L > 2 && !knn_both_ways(TILE, KS, 8))
         if (!P.ordered) return way(std::integral_constant<int, kWayBeside>());
     if constexpr (L == 2)
-        if (P.alone) return way(std::integral_constant<int, kWayAlone>());
+        if (P.alone) return waves == 8 ? launch<TILE, KS, L, 8, kWayAlone>(st, n_blocks, P, blocks, list_len, cand, keys, tau, assign) : hipErrorInvalidValue;   // (products_may_be_alone)
     return way(std::integral_constant<int, kWaySift>());
 }
 
