@@ -242,6 +242,9 @@ struct ExchangePlan {
     int tile_bits = 0;
 };
 inline size_t exchange_rows_lds_bytes(const ExchangePlan& x) { return (size_t)8 << (x.tile_bits + (x.pairs ? 1 : 0)); }
+// k_tile_sums: segments that a wavefront can have queued (8 bytes each), two steps of 64 / lanes and a round of 64; the tile's sums and all queues
+constexpr uint32_t tile_sums_queue(int lanes) { return 2u * (64u / (uint32_t)lanes) + 64u; }
+inline size_t tile_sums_lds_bytes(const ExchangePlan& x) { return ((size_t)16 << x.tile_bits) + (size_t)(kBinBlock / 64) * tile_sums_queue(x.sums_lanes) * 8; }
 constexpr double kExchangeStepReferences = 8e6;
 inline ExchangePlan plan_exchange(const EdgePlanRequest& q, const EdgePlan& p) {
     ExchangePlan x;

@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(kBinBlock) k_tile_sums(const TileSums X, float
     typedef float Forces __attribute__((ext_vector_type(4), aligned(8)));
     typedef uint32_t Indexes __attribute__((aligned(2)));
     extern __shared__ unsigned long long acc[];   // [2 tile]: x, then y
-    __shared__ uint2 queues[WAVES][2 * STEP + 64];
+    __shared__ uint2 queues[WAVES][tile_sums_queue(G)];
     uint32_t b, part;
     if (!exchange_unit(X.n_tiles, b, part)) return;
     const uint32_t blocks = X.n_blocks, mask = X.mask;

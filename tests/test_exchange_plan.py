@@ -26,7 +26,7 @@ int main(int argc, char** argv) {
     printf("{\"use\": %d, \"pairs\": %d, \"rows\": %d, \"sums\": %d, \"parts\": %u, \"tiles\": %u, \"tile_bits\": %d, \"slots\": %zu, \"edges\": %d, "
            "\"deal_lds\": %zu, \"rows_lds\": %zu, \"edges_lds\": %zu, \"sums_lds\": %zu, \"max_lds\": %zu}\n",
            (int)x.use, (int)x.pairs, x.rows_lanes, x.sums_lanes, x.parts, p.n_bins, p.tile_bits, exchange_slots(q.s), exchange_block_edges(q.s),
-           exchange_deal_lds_bytes(q.s, p.n_bins), exchange_rows_lds_bytes(x), exchange_edges_lds_bytes(q.s), (size_t)16 << p.tile_bits, kMaxLdsBytes);
+           exchange_deal_lds_bytes(q.s, p.n_bins), exchange_rows_lds_bytes(x), exchange_edges_lds_bytes(q.s), tile_sums_lds_bytes(x), kMaxLdsBytes);
     return 0;
 }
 """
