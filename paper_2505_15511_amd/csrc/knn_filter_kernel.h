@@ -172,7 +172,7 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // In a launch of several rounds the later slices begin with the bound of the earlier ones: 300,000 x 128, 17,000 queries in 15 slices 5.35 -> 4.80 ms against a bound
 // that needs all lists, 150,000 x 20 among themselves in 3 slices 9.9 -> 9.1.
 // At the end the lists are merged by counting, smallest key first; tau = min(K'-th key of the union, the lists' last keys): every candidate
-// that is not passed on has key >= tau.
+// that is not passed on has key >= tau, or another slice's distances rule it out.
 //
 // L == 2: one neighbour wanted.  Every key goes straight into the lane's best two; at the end a query whose smallest key
 // lies below the second by more than twice the filter's error bound has its answer (out); the others are put on the `todo`

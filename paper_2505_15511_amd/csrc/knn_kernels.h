@@ -6,7 +6,8 @@
 //   k_knn_pack     every row centred, scaled by a power of two and split into two float16 parts, x' = hi + lo to 2^-22 of x',
 //                  laid out tile by tile in the order the matrix instructions read their operands;
 //   k_knn_filter   float16 matrix cores (hi hi + hi lo + lo hi, float32 accumulation): for every query the K' = k + pad
-//                  candidates with the smallest key |c|^2 - 2 q.c, and tau (every point left out has key >= tau);
+//                  candidates with the smallest key |c|^2 - 2 q.c, and tau (every point left out has key >= tau, but for those that
+//                  another slice's distances rule out: these are farther than the K'-th nearest for certain);
 //   k_knn_refine   sorts those candidates by (distance, index), distance = sum_t (x_t - y_t)^2 in float64 in the order
 //                  t = 0..d-1, worked out where the filter's error bound leaves the order open; the first k are the answer
 //                  if the k-th lies below tau by more than that bound -- otherwise the query is flagged;
