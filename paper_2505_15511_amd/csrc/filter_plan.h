@@ -9,45 +9,59 @@
 namespace nomad_knn {
 
 constexpr int64_t kFilterUnits = 256;   // compute units, one workgroup of the filter at a time each
+constexpr int kFilterLists = 8;         // XCDs: workgroups go to them in turn, and each works through a list of its own (filter_blocks)
 
-// How long the filter is at work over groups of hist[c] groups of c tiles each, in tiles of candidates, `waves` tiles of queries to a workgroup: longest groups first, and a
-// workgroup that begins a round of the chip has the mean of those before it ahead of it.
-inline double filter_span(const std::vector<uint32_t>& hist, int waves) {
-    double span = 0.0, before = 0.0;   // candidates' tiles of the workgroups so far
-    int64_t at = 0;                    // workgroups so far
-    for (size_t c = hist.size(); c-- > 1;) {
-        if (hist[c] == 0u) continue;
-        const int64_t count = (int64_t)hist[c] * (int64_t)((c + (size_t)waves - 1) / (size_t)waves);
-        const int64_t last = (at + count - 1) / kFilterUnits * kFilterUnits;   // the last of them that begins a round
-        if (last >= at) span = std::max(span, (before + (double)(last - at) * (double)c) / (double)kFilterUnits + (double)c);
-        before += (double)count * (double)c;
-        at += count;
+// the list that a workgroup goes to when `done` of the work is in the lists already
+inline int filter_list(double done, double total) { return total > 0.0 ? std::min(kFilterLists - 1, (int)(done / total * kFilterLists)) : 0; }
+
+// How long `units` compute units are at work on workgroups of these lengths, longest first: one that begins a round has the mean of those before it ahead of it.
+inline double list_span(std::vector<uint32_t>& list, int64_t units) {
+    std::sort(list.begin(), list.end(), [](uint32_t a, uint32_t b) { return a > b; });
+    double span = 0.0, before = 0.0;
+    for (size_t i = 0; i < list.size(); ++i) {
+        if ((int64_t)i % units == 0) span = std::max(span, before / (double)units + (double)list[i]);
+        before += (double)list[i];
     }
     return span;
 }
 
+// How long the filter is at work over groups of tstart[g + 1] - tstart[g] tiles, in tiles of candidates, `waves` tiles of queries to a workgroup: the mean of the longest list's
+// span and of the whole chip's as if it were one list.  (Few long clusters can leave one XCD with a round more than the others.  Neither says enough alone: 68,277 x 76 in 12 clusters twelve over eight wavefronts 1.00 by the chip, 0.82 by the lists and 1.16 measured, 95,776 x 59 in 11 0.51, 0.97 and 0.89.)
+inline double filter_span(const std::vector<uint32_t>& tstart, int waves) {
+    double total = 0.0, done = 0.0, longest = 0.0;
+    std::vector<uint32_t> all, lists[kFilterLists];
+    for (size_t g = 0; g + 1 < tstart.size(); ++g) {
+        const uint32_t c = tstart[g + 1] - tstart[g], count = (c + (uint32_t)waves - 1u) / (uint32_t)waves;
+        all.insert(all.end(), count, c);
+        total += (double)c * (double)count;
+    }
+    for (const uint32_t c : all) {
+        lists[filter_list(done, total)].push_back(c);
+        done += (double)c;
+    }
+    for (auto& l : lists) longest = std::max(longest, list_span(l, kFilterUnits / kFilterLists));
+    return 0.5 * (longest + list_span(all, kFilterUnits));
+}
+
 // Eight wavefronts share a staged tile, or `most` (twelve or sixteen, as the registers allow).  These are faster by themselves where a workgroup's wavefronts have work, for
 // three or four wavefronts a SIMD hide what two wait for; but workgroups are fewer then and longer, one of sixteen 1.4 to 1.5 times as long as one of eight, one of twelve 1.1 to 1.25.
-// The line is where the span is six sevenths.  Calls, `most` over eight, by span over span (420 sets of 33,000 to 400,000 rows of 16 to 300 columns, clusters of 200
-// to 4,000, equal and Dirichlet): up to 0.6 0.74 to 0.94; 0.65 to 0.75 0.83 to 1.01; 0.8 to 0.85 0.78 to 1.03; 0.86 to 0.96 1.03 to 1.16; 1, where the longest cluster or a
-// last round decides, 0.91 to 1.28 (1.06 to 1.13 in the mean).  By this line 0.3 % above the better of the two in the mean, 10 % at most; always eight 4 and 32 %, always `most` 5 and 28 %.
+// The line is where the span is nine tenths.  Calls, `most` over eight, by span over span (330 sets of 16,400 to 300,000 rows of 4 to 384 columns in 5 to 1,400 clusters, equal
+// and of very different sizes, half of them up to 60): below 0.6 0.86 in the mean, 0.6 to 0.8 0.93, 0.8 to 0.9 0.98 (0.90 to 1.12), 0.9 to 0.95 1.02, 0.95 to 0.99 1.08, 1 1.10
+// (0.97 to 1.24).  By this line 0.2 % above the better of the two in the mean, 12 % at most (220 other sets: 0.6 and 8 %); always eight 4 and 39 %, always `most` 5 and 24 %; by the span of the
+// chip as one list 0.4 and 29 % (46,542 x 180 in eleven clusters, k = 21, 1.18 ms where twelve take 1.01).
 inline int filter_waves(const std::vector<uint32_t>& tstart, int most) {
     if (most <= 8) return 8;
     constexpr int64_t kMany = 16 * kFilterUnits;   // workgroups from which rounds don't count
     int64_t eight = 0;
     double all8 = 0.0, all = 0.0;
-    uint32_t longest = 0u;
     for (size_t g = 0; g + 1 < tstart.size(); ++g) {
         const uint32_t c = tstart[g + 1] - tstart[g];
         eight += (c + 7u) / 8u;
         all8 += (double)c * (double)((c + 7u) / 8u);
         all += (double)c * (double)((c + (uint32_t)most - 1u) / (uint32_t)most);
-        longest = std::max(longest, c);
     }
-    if (eight >= kMany) return 7.0 * all < 6.0 * all8 ? most : 8;
-    std::vector<uint32_t> hist((size_t)longest + 1, 0u);
-    for (size_t g = 0; g + 1 < tstart.size(); ++g) ++hist[tstart[g + 1] - tstart[g]];
-    return 7.0 * filter_span(hist, most) < 6.0 * filter_span(hist, 8) ? most : 8;
+    if (eight < kMany) { all8 = filter_span(tstart, 8); all = filter_span(tstart, most); }
+    return 10.0 * all < 9.0 * all8 ? most : 8;
 }
 
 // Whether slices of one set tell each other how near their candidates are: a wavefront does so some ten times over 4,000 candidates, twenty over 16,000, forty over 166,000, each

@@ -66,16 +66,14 @@ struct PackedSide {
 // most candidates come first: a workgroup's time goes with its group's candidates, and what starts last should be short.
 // Entries without work (cluster -1) fill the shorter lists up.
 std::vector<KnnBlock> filter_blocks(const PackedSide& Q, const PackedSide& C, int waves) {
-    constexpr int kXcds = 8;
     const auto cost_of = [&](int32_t g) { return (double)(C.tstart[g + 1] - C.tstart[g]); };
     double total = 0.0;
     for (int32_t g = 0; g < Q.groups; ++g) total += cost_of(g) * (double)((Q.tstart[g + 1] - Q.tstart[g] + (uint32_t)waves - 1) / (uint32_t)waves);
-    std::vector<KnnBlock> lists[kXcds];
+    std::vector<KnnBlock> lists[kFilterLists];
     double done = 0.0;
     for (int32_t g = 0; g < Q.groups; ++g)
         for (uint32_t t = 0; t < Q.tstart[g + 1] - Q.tstart[g]; t += (uint32_t)waves) {
-            const int x = std::min(kXcds - 1, (int)(total > 0.0 ? done / total * kXcds : 0.0));
-            lists[x].push_back(KnnBlock{g, (int32_t)t});
+            lists[filter_list(done, total)].push_back(KnnBlock{g, (int32_t)t});
             done += cost_of(g);
         }
     size_t longest = 0;
@@ -83,9 +81,9 @@ std::vector<KnnBlock> filter_blocks(const PackedSide& Q, const PackedSide& C, in
         std::stable_sort(l.begin(), l.end(), [&](const KnnBlock& a, const KnnBlock& b) { return cost_of(a.cluster) > cost_of(b.cluster); });
         longest = std::max(longest, l.size());
     }
-    std::vector<KnnBlock> blocks(longest * kXcds, KnnBlock{-1, 0});
-    for (int x = 0; x < kXcds; ++x)
-        for (size_t i = 0; i < lists[x].size(); ++i) blocks[i * kXcds + (size_t)x] = lists[x][i];
+    std::vector<KnnBlock> blocks(longest * kFilterLists, KnnBlock{-1, 0});
+    for (int x = 0; x < kFilterLists; ++x)
+        for (size_t i = 0; i < lists[x].size(); ++i) blocks[i * kFilterLists + (size_t)x] = lists[x][i];
     return blocks;
 }
 

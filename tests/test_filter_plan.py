@@ -14,14 +14,9 @@ PROGRAM = r"""
 using namespace nomad_knn;
 int main(int argc, char** argv) {   // most, tiles of every group; or 0, slices, candidates, tile, long lists
     if (atoi(argv[1]) == 0) { printf("%d\n", (int)slices_share(atoll(argv[2]), atoll(argv[3]), atoi(argv[4]), atoi(argv[5]))); return 0; }
-    std::vector<uint32_t> tstart = {0u}, hist;
-    for (int a = 2; a < argc; ++a) {
-        const uint32_t c = (uint32_t)atol(argv[a]);
-        tstart.push_back(tstart.back() + c);
-        if (c >= hist.size()) hist.resize(c + 1, 0u);
-        ++hist[c];
-    }
-    printf("%d %.17g %.17g\n", filter_waves(tstart, atoi(argv[1])), filter_span(hist, 8), filter_span(hist, atoi(argv[1])));
+    std::vector<uint32_t> tstart = {0u};
+    for (int a = 2; a < argc; ++a) tstart.push_back(tstart.back() + (uint32_t)atol(argv[a]));
+    printf("%d %.17g %.17g\n", filter_waves(tstart, atoi(argv[1])), filter_span(tstart, 8), filter_span(tstart, atoi(argv[1])));
 }
 """
 
@@ -40,12 +35,16 @@ def plan(tmp_path_factory):
 
 
 def _rounds(groups, waves):
-    """Workgroups, longest first, each to the unit that is free first."""
-    units = np.zeros(256)
-    for c in sorted(groups, reverse=True):
-        for _ in range(-(-int(c) // waves)):
-            units[units.argmin()] += c
-    return units.max()
+    """Workgroups, longest first, each to the unit that is free first: the whole chip's, and an eighth of the work after the other on an eighth of the units."""
+    work = [int(c) for c in groups for _ in range(-(-int(c) // waves))]
+    before = np.concatenate([[0.0], np.cumsum(work)[:-1]]) / max(1, sum(work))
+
+    def launch(lengths, units):
+        at = np.zeros(units)
+        for c in sorted(lengths, reverse=True):
+            at[at.argmin()] += c
+        return at.max()
+    return 0.5 * (launch(work, 256) + max(launch([c for c, b in zip(work, before) if int(8 * b) == x], 32) for x in range(8)))
 
 
 @pytest.mark.parametrize("seed", range(4))
@@ -70,6 +69,8 @@ def test_the_rule(plan):
     assert waves(16, [125] * 17) == 16                                   # 272 workgroups, 136
     assert waves(16, [125] * 250) == 16 and waves(12, [125] * 250) == 12
     assert waves(12, [125] * 25) == 8                                    # 400 and 275: two rounds either way
+    # rows of 16: twelve are one round of the chip's; eight are hardly more by the chip, but one XCD has two rounds of long ones
+    assert waves(12, [-(-n // 16) for n in (5340, 3626, 2814, 2538, 9073, 7306, 1443, 4349, 1129, 2430, 6494)]) == 12
     # as many workgroups of twelve as of eight: a cluster's last one has idle wavefronts
     assert waves(12, [16] * 400) == 8 and waves(12, [16] * 4_000) == 8
     assert waves(16, [17] * 1_000) == 16 and waves(16, [7] * 5_000) == 8
