@@ -71,9 +71,10 @@ std::vector<KnnBlock> filter_blocks(const PackedSide& Q, const PackedSide& C, in
     for (int32_t g = 0; g < Q.groups; ++g) total += cost_of(g) * (double)((Q.tstart[g + 1] - Q.tstart[g] + (uint32_t)waves - 1) / (uint32_t)waves);
     std::vector<KnnBlock> lists[kFilterLists];
     double done = 0.0;
+    int list = 0;
     for (int32_t g = 0; g < Q.groups; ++g)
         for (uint32_t t = 0; t < Q.tstart[g + 1] - Q.tstart[g]; t += (uint32_t)waves) {
-            lists[filter_list(done, total)].push_back(KnnBlock{g, (int32_t)t});
+            lists[list = filter_list(list, done, total)].push_back(KnnBlock{g, (int32_t)t});
             done += cost_of(g);
         }
     size_t longest = 0;

@@ -10,13 +10,28 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include <stdio.h>
 #include <stdlib.h>
+#include <chrono>
 #include "filter_plan.h"
 using namespace nomad_knn;
+template <class Fn> double least_us(Fn fn) {
+    double least = 1e30;
+    for (int i = 0; i < 30; ++i) {
+        const auto t0 = std::chrono::steady_clock::now();
+        fn();
+        least = std::min(least, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count());
+    }
+    return least;
+}
 int main(int argc, char** argv) {   // most, tiles of every group; or 0, slices, candidates, tile, long lists
     if (atoi(argv[1]) == 0) { printf("%d\n", (int)slices_share(atoll(argv[2]), atoll(argv[3]), atoi(argv[4]), atoi(argv[5]))); return 0; }
     std::vector<uint32_t> tstart = {0u};
     for (int a = 2; a < argc; ++a) tstart.push_back(tstart.back() + (uint32_t)atol(argv[a]));
-    printf("%d %.17g %.17g\n", filter_waves(tstart, atoi(argv[1])), filter_span(tstart, 8), filter_span(tstart, atoi(argv[1])));
+    const std::vector<uint32_t> order = longest_first(tstart);
+    std::vector<uint32_t> workgroups;
+    for (size_t g = 0; g + 1 < tstart.size(); ++g) workgroups.insert(workgroups.end(), (tstart[g + 1] - tstart[g] + 7) / 8, tstart[g + 1] - tstart[g]);
+    const double rule = least_us([&] { volatile int w = filter_waves(tstart, atoi(argv[1])); (void)w; });
+    const double sorting = least_us([&] { std::vector<uint32_t> w = workgroups; std::sort(w.begin(), w.end()); volatile uint32_t x = w.empty() ? 0u : w[0]; (void)x; });
+    printf("%d %.17g %.17g %g %g\n", filter_waves(tstart, atoi(argv[1])), filter_span(tstart, order, 8), filter_span(tstart, order, atoi(argv[1])), rule, sorting);
 }
 """
 
@@ -30,7 +45,7 @@ def plan(tmp_path_factory):
 
     def of(most, groups):
         out = subprocess.run([str(d / "plan"), str(most)] + [str(int(c)) for c in groups], check=True, capture_output=True, text=True).stdout.split()
-        return (int(out[0]), float(out[1]), float(out[2])) if most else int(out[0])
+        return (int(out[0]),) + tuple(float(x) for x in out[1:]) if most else int(out[0])
     return of
 
 
@@ -53,12 +68,43 @@ def test_the_span_is_a_launch(plan, groups, seed):
     rng = np.random.default_rng(seed)
     for sizes in (np.full(groups, 125), rng.integers(100, 130, groups), np.ceil(rng.gamma(4.0, 25.0, groups))):
         for most in (12, 16):
-            _, eight, more = plan(most, sizes)
+            _, eight, more = plan(most, sizes)[:3]
             for span, waves in ((eight, 8), (more, most)):
                 launch = _rounds(sizes, waves)
                 assert 0.70 * launch <= span <= 1.25 * launch            # (the last round is not the mean round)
                 if sum(-(-int(c) // waves) for c in sizes) > 1024:       # rounds enough that no single workgroup decides
                     assert 0.90 * launch <= span
+
+
+def _span(lengths, units):
+    lengths = sorted(lengths, reverse=True)
+    return max((sum(lengths[:i]) / units + lengths[i] for i in range(0, len(lengths), units)), default=0.0)
+
+
+@pytest.mark.parametrize("seed", range(4))
+@pytest.mark.parametrize("groups", [1, 11, 90, 700])
+def test_the_span_by_groups_is_the_one_by_workgroups(plan, groups, seed):
+    """Counted by groups; here workgroup by workgroup, with gaps (empty groups), groups of one length, groups that several lists share and long ones among many short ones."""
+    rng = np.random.default_rng(seed)
+    gaps = rng.integers(0, 60, groups) * (rng.random(groups) < 0.8)
+    for sizes in (np.full(groups, 40), gaps, np.ceil(rng.gamma(0.4, 60.0, groups)), np.concatenate([rng.integers(1, 4, groups), [1_500 + 16 * groups]])):
+        for most in (12, 16):
+            _, eight, more = plan(most, sizes)[:3]
+            for span, waves in ((eight, 8), (more, most)):
+                work = [int(c) for c in sizes for _ in range(-(-int(c) // waves))]
+                total, done, lists = sum(work), 0, [[] for _ in range(8)]
+                for c in work:
+                    lists[8 * done // total].append(c)
+                    done += c
+                assert span == pytest.approx(0.5 * (_span(work, 256) + max(_span(l, 32) for l in lists)), rel=1e-12)
+
+
+def test_the_rule_takes_less_than_sorting_the_workgroups(plan):
+    """The device waits for it: a million rows in 256 clusters, 4,000 workgroups, among them one sort of these as the measure."""
+    rng = np.random.default_rng(0)
+    sizes = rng.gamma(4.0, 1.0, 256)
+    waves, _, _, rule, sorting = plan(12, np.ceil(31_250 * sizes / sizes.sum()))
+    assert waves == 12 and rule < 0.6 * sorting
 
 
 def test_the_rule(plan):
