@@ -66,8 +66,12 @@ NOMAD_BOTH bool open_is_counted(uint32_t workgroup, uint32_t wave) {
 // (35,000, K = 64, d = 768) 1.072 / 1.033, 3.2e9 (50,000, K = 500, d = 128) 0.827 / 0.793, 1.2e10 (300,000, K = 128, d = 300) 2.21 / 1.82, 7.7e10 (50,000, K = 2,000,
 // d = 768) 3.83 / 3.56; short rows of many points, whose filter the additional operand of a query is as much as: 1,000,000, K = 16, d = 16 0.996 / 1.083.  Fewer than
 // eight wavefronts a workgroup (n_tiles tiles of points) have no such instance.
-inline bool products_may_be_alone(int64_t n, int64_t K, int64_t d, int64_t n_tiles, int64_t steps) {
-    return steps > 1 && n_tiles >= 1024 && K * d >= 8192 && n * K * d >= (int64_t)1 << 30 && !open_points_are_few(n, K);
+// Rows that are not read 16 bytes at a time (by16): what is open, however little, waits for chains of d loads (100,003 x 231, K = 128: filter 39 -> 20 us a step, but refinement
+// 22 -> 33 and exact path 21 -> 54), which a step saves from about n K = 2^26 on.  Calls of ten steps, never / with them, ms, by n K: 1.3e7 (100,003 x 231, 128) 1.92 / 2.27,
+// (100,003 x 129, 128) 1.40 / 1.51, 1.5e7 (60,001 x 255, 256) 1.78 / 2.02, 2.6e7 (200,000 x 127, 128) 1.85 / 1.92, 3.0e7 (150,000 x 230, 200) 2.09 / 2.07, 3.8e7
+// (300,000 x 98, 128) 1.80 / 1.81, 1.3e8 (500,000 x 67, 256) 2.58 / 2.37.
+inline bool products_may_be_alone(int64_t n, int64_t K, int64_t d, int64_t n_tiles, int64_t steps, bool by16) {
+    return (by16 || n * K >= (int64_t)1 << 26) && steps > 1 && n_tiles >= 1024 && K * d >= 8192 && n * K * d >= (int64_t)1 << 30 && !open_points_are_few(n, K);
 }
 // The share of the points, at most, that a step may leave open for the next to do so: what is open costs a row of each of its candidates, and of all centroids where
 // these don't decide, which is as much as the step saves at about K d / 2^20: 300,000, K = 128, d = 64, saved 9 us, paid at a share of 0.016 3, 0.027 18, 0.045 49;

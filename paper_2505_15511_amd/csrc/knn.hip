@@ -406,7 +406,7 @@ extern "C" int nomad_kmeans_lloyd(const float* X, int64_t n, int32_t d, int32_t 
     KTRY(hipMemsetAsync(max_pts, 0, sizeof(uint32_t), st));
     hipLaunchKernelGGL(k_knn_centroid_sums, dim3((uint32_t)hslabs.size()), dim3(256), 0, st, dX, d, (const int32_t*)nullptr, qstart, slabs, slab_rows, centre);
     hipLaunchKernelGGL(k_knn_centroid_finish, dim3(blocks_of(d, 256)), dim3(256), 0, st, centre, qstart, 1, d);
-    const bool few = open_points_are_few(n, K), may_be_alone = products_may_be_alone(n, K, d, points.n_tiles, max_iters);
+    const bool few = open_points_are_few(n, K), may_be_alone = products_may_be_alone(n, K, d, points.n_tiles, max_iters, rows_by_16(dX, d) && rows_by_16(dC, d));
     if (may_be_alone) KTRY(buf.alloc(&xnorm, (size_t)n));
     launch_norms(st, dX, n, d, nullptr, nullptr, centre, xnorm, max_pts);
     points.fill(st, dX, d, nullptr, centre, max_pts, nullptr, nullptr);

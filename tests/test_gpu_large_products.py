@@ -25,7 +25,7 @@ int main(int, char** a) {   // n K d tiles steps M
     const long long n = atoll(a[1]), K = atoll(a[2]), d = atoll(a[3]);
     long long open = 0;
     while (products_alone(open + 64, n, K, d)) open += 64;
-    printf("%d %lld %.17g\n", (int)products_may_be_alone(n, K, d, atoll(a[4]), atoll(a[5])), open, knn_filter_eps((int)d, atof(a[6])));
+    printf("%d %lld %.17g\n", (int)products_may_be_alone(n, K, d, atoll(a[4]), atoll(a[5]), d % 4 == 0), open, knn_filter_eps((int)d, atof(a[6])));
 }
 """
 
@@ -92,9 +92,9 @@ def _blobs(n, d, K, rng, spread=0.02):
     return centres, c, centres[c] + spread * rng.normal(size=(n, d))
 
 
-# 32- and 16-row tiles, every number of steps once; centroids that don't fill their last tile
-INSTANCES = [(112000, 16, 600), (58000, 31, 601), (33000, 64, 521), (33001, 90, 400), (32800, 128, 300), (33000, 190, 200), (32768, 250, 199), (36000, 300, 100), (34000, 500, 65),
-             (22001, 765, 64)]
+# 32- and 16-row tiles, every number of steps once; centroids that don't fill their last tile; rows that are not read 16 bytes at a time
+INSTANCES = [(112000, 16, 600), (112000, 31, 601), (33000, 64, 521), (33001, 92, 400), (32800, 128, 300), (33000, 192, 200), (32768, 252, 199), (36000, 300, 100), (34000, 500, 65),
+             (22001, 764, 64), (66000, 301, 1025), (131072, 67, 520)]
 
 
 @pytest.mark.parametrize("n,d,K", INSTANCES)

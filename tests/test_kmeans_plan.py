@@ -72,8 +72,8 @@ int main(int argc, char** argv) {
         for (int g = 0; g < atoi(argv[2]); ++g)
             for (int w = 0; w < 8; ++w)
                 if (open_is_counted((uint32_t)g, (uint32_t)w)) printf("%d %d\n", g % 8, g / 8 * 8 + w);
-    if (!strcmp(argv[1], "line"))                         // n K d n_tiles steps
-        printf("%d\n", (int)products_may_be_alone(atoll(argv[2]), atoll(argv[3]), atoll(argv[4]), atoll(argv[5]), atoll(argv[6])));
+    if (!strcmp(argv[1], "line"))                         // n K d n_tiles steps, rows that are read 16 bytes at a time
+        printf("%d\n", (int)products_may_be_alone(atoll(argv[2]), atoll(argv[3]), atoll(argv[4]), atoll(argv[5]), atoll(argv[6]), atoi(argv[7])));
     if (!strcmp(argv[1], "share"))                        // open n K d
         printf("%d\n", (int)products_alone(atoll(argv[2]), atoll(argv[3]), atoll(argv[4]), atoll(argv[5])));
 }
@@ -109,10 +109,11 @@ def test_the_sample_of_open_points_is_fair(ask):
 
 
 def test_large_products_alone(ask):
-    line = lambda n, K, d, steps=5: ask("line", n, K, d, -(-n // (32 if d <= 256 else 16)), steps) == [1]
+    line = lambda n, K, d, steps=5, by16=1: ask("line", n, K, d, -(-n // (32 if d <= 256 else 16)), steps, by16) == [1]
     assert line(1_000_000, 256, 128) and line(100_003, 64, 768) and line(50_000, 2_000, 768)
     assert not line(1_000_000, 256, 128, 1)                           # a step that no other follows
     assert not line(1_000_000, 16, 16) and not line(10 ** 9, 4, 8)    # short rows of few centroids
+    assert line(524_288, 128, 67, 5, 0) and not line(524_287, 128, 67, 5, 0) and not line(100_003, 128, 231, 5, 0)   # rows that are read word by word
     assert line(131_072, 128, 64) and not line(131_071, 128, 64)      # products
     assert line(32_768, 1_000, 250) and not line(32_736, 1_000, 250)  # workgroups of eight wavefronts
     assert line(16_385, 256, 768) and not line(16_384, 256, 768)      # the open points of few are not refined
