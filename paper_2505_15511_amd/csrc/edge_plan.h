@@ -64,6 +64,18 @@ NOMAD_HOST_DEVICE constexpr size_t exchange_slots(int s) {   // one per referenc
 NOMAD_HOST_DEVICE constexpr size_t exchange_deal_lds_bytes(int s, uint32_t n_tiles) { return exchange_slots(s) * 2 + (size_t)n_tiles * 4; }
 NOMAD_HOST_DEVICE constexpr size_t exchange_edges_lds_bytes(int s) { return exchange_slots(s) * 8; }
 
+// edge pass that leaves its forces in runs (run_kernels.h): blocks of runs_lanes * runs_edges_per_lane edges.  As many lanes in flight as registers allow with two
+// workgroups and more a compute unit, an edge a lane; up to two negatives three edges a lane, for as long a run: 6 M points in groups, s = 2, edge pass and sums
+// 2.78 + 1.60 ms with 1,024 x 1, 2.74 + 1.02 with 512 x 3, 3.87 + 1.06 with 512 x 4 and 4.73 + 1.02 with 512 x 5 (two workgroups of 61 and 77 KB), 3.24 + 1.40 with 768 x 2.
+NOMAD_HOST_DEVICE constexpr int runs_lanes(int s) { return s > 2 && s <= 6 ? 1024 : 512; }
+NOMAD_HOST_DEVICE constexpr int runs_edges_per_lane(int s) { return s <= 2 ? 3 : 1; }
+NOMAD_HOST_DEVICE constexpr int runs_waves_per_simd(int s) { return runs_lanes(s) == 1024 ? 8 : s <= 2 ? 4 : 6; }
+NOMAD_HOST_DEVICE constexpr int runs_block_edges(int s) { return runs_lanes(s) * runs_edges_per_lane(s); }
+NOMAD_HOST_DEVICE constexpr size_t runs_slots(int s) {   // one per reference, two per wavefront of head sums; a multiple of 64
+    return ((size_t)runs_block_edges(s) * (s + 1) + 2 * (runs_block_edges(s) / 64) + 63) / 64 * 64;
+}
+NOMAD_HOST_DEVICE constexpr size_t runs_lds_bytes(int s, uint32_t n_tiles) { return runs_slots(s) * 10 + (size_t)n_tiles * 4; }
+
 // ---- the plan
 struct EdgePlanRequest {
     int64_t n = 0, E = 0;
@@ -71,6 +83,7 @@ struct EdgePlanRequest {
     // pooled sampler (pool_size 0: none); distinct: picks in different lines (modes 1 and 2)
     int32_t pool_size = 0, pool_block = 0, pool_line = 1;
     bool pool_distinct = false;
+    bool grouped = false;       // some cells are approximated
     bool far = false;           // groups whose far cells are sampled
     int batches = 1;            // sub-steps of an epoch
     // nomad_tune (0 = the library's choice, except pool_kernel: 1 = use the pooled kernels)
@@ -260,6 +273,32 @@ inline ExchangePlan plan_exchange(const EdgePlanRequest& q, const EdgePlan& p) {
     x.sums_lanes = run < 12 ? 8 : 16;
     const uint32_t units = x.pairs ? (p.n_bins + 1) / 2 : p.n_bins;
     x.parts = units >= 512 ? 2 : (1024 + units - 1) / units;   // (four workgroups per compute unit and more at a few hundred tiles)
+    return x;
+}
+
+// Whether a problem takes the edge pass that leaves its forces in runs (run_kernels.h), and the lanes of a segment of k_tile_sums.
+//   Which: all that would otherwise leave records in chains, sorted by tile.  Time of an epoch, runs over chains (symmetrised, 12 to 15 out-neighbours,
+//   numbered cluster by cluster): s = 5 10 k points 0.71, 20 k 0.67, 100 k 0.65, 300 k 0.71, 600 k 0.78, 900 k 0.83; s = 8 0.76 (100 k), 0.86 (900 k); s = 3 0.70 (400 k in
+//   sub-steps), 0.82 (900 k); s = 2 0.71 (100 k), 0.79, 1.4 M 0.90; s = 1 0.79, 0.78 (600 k); none 0.74 (20 k), 0.86 (5 M); 64 sub-steps of 20 k to 5 M 0.57 to 0.85; every cluster its own
+//   group 150 k 0.57, 1 M 0.76, 3 M (s = 2) 0.83, 8 M 0.94.  Graphs of fewer edges than points have: 12 k, 24 k edges, s = 2 1.02 (within what runs differ by), all others
+//   0.75 to 0.8.  The exchange from a million points on (plan_exchange): runs take 0.94 to 1.0 of its time there, 1.03 to 1.09 at 1.3 M and 1.2 to 1.4 at 2.5 M, and in
+//   random order 1.08, 1.11 and 1.5, so its lines stay.
+//   Not with sampled means beyond 256 tiles: what a block's slots are made for are negatives, few of which get a force there, and the tiles look for their runs in many
+//   blocks.  400 k 0.78 to 0.85, 1 M 0.90, 2 M 0.97, 2.5 M (s = 8) 1.03, 3 M (s = 5) 1.01, 5 M (s = 2) 1.02.
+//   Nor where two workgroups do not fit a compute unit's LDS (77 KB a workgroup: 1.5 times as long as 46 KB with the same lanes in flight).
+//   Lanes of a segment (two references each): half of the mean run, us at 100 k points, s = 5, runs of 31 / 24 / 16: 8 lanes 63, 60, 52, 16 lanes 45, 39, 41, 32 lanes 36, 41, 57.
+//   With groups a block's references lie in the tiles of its own clusters, whatever the mean: 6 M points, s = 2, 8 / 16 / 32 lanes 1.41 / 1.09 / 1.02 ms.
+struct RunsPlan {
+    bool use = false;
+    int sums_lanes = 32;
+};
+inline RunsPlan plan_runs(const EdgePlanRequest& q, const EdgePlan& p) {
+    RunsPlan x;
+    const bool records_asked = q.tune_edge_block || q.tune_wg_per_cu || q.tune_record_sort || q.tune_flush_rounds;
+    if (q.s < 0 || q.s > 8 || q.E < 1 || q.pool_size || !p.bin_block || records_asked) return x;
+    x.use = p.sorted && 2 * runs_lds_bytes(q.s, p.n_bins) <= kMaxLdsBytes && !(q.far && p.n_bins > 256);
+    const double run = (double)runs_block_edges(q.s) * (q.s + 1) / p.n_bins;
+    x.sums_lanes = q.grouped ? 32 : run < 12 ? 8 : run < 22 ? 16 : 32;
     return x;
 }
 

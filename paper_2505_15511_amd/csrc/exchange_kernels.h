@@ -62,6 +62,30 @@ __device__ __forceinline__ bool hands_on_head_sum(bool has, int32_t ea, int32_t 
     return row_end && !inside;
 }
 
+// The references that a block has for every tile (`first`, in LDS, complete) become their first slots there, and the block's table of runs; all BS lanes call.  Returns
+// how many there are.
+template <int BS>
+__device__ __forceinline__ uint32_t counts_to_runs(uint32_t* first, uint32_t T, uint32_t (&wave_total)[BS / 64], uint32_t* __restrict__ runs) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t per = (T + BS - 1) / BS, b0 = (uint32_t)tid * per;
+    uint32_t own = 0;
+    for (uint32_t x = 0; x < per; ++x) own += b0 + x < T ? first[b0 + x] : 0u;
+    const uint32_t incl = wave_prefix(own);
+    if (lane == 63) wave_total[wave] = incl;
+    lds_barrier();
+    const uint32_t waves_incl = wave_prefix(lane < BS / 64 ? wave_total[lane] : 0u);
+    uint32_t run = incl - own;
+    if (wave > 0) run += (uint32_t)__builtin_amdgcn_readlane((int)waves_incl, wave - 1);
+    for (uint32_t x = 0; x < per; ++x)
+        if (b0 + x < T) {
+            const uint32_t c = first[b0 + x];
+            first[b0 + x] = run;
+            runs[b0 + x] = run | c << 16;
+            run += c;
+        }
+    return (uint32_t)__builtin_amdgcn_readlane((int)waves_incl, BS / 64 - 1);
+}
+
 template <int S>
 __global__ void __launch_bounds__(kExchangeLanes) k_exchange_deal(const EdgeArgs args, const ExchangeArgs X) {
     using Shape = ExchangeShape<S>;
@@ -110,25 +134,7 @@ __global__ void __launch_bounds__(kExchangeLanes) k_exchange_deal(const EdgeArgs
         }
     }
     lds_barrier();
-    {   // counts to first slots
-        const uint32_t per = (T + BS - 1) / BS, b0 = (uint32_t)tid * per;
-        uint32_t own = 0;
-        for (uint32_t x = 0; x < per; ++x) own += b0 + x < T ? first[b0 + x] : 0u;
-        const uint32_t incl = wave_prefix(own);
-        if (lane == 63) wave_total[wave] = incl;
-        lds_barrier();
-        const uint32_t waves_incl = wave_prefix(lane < BS / 64 ? wave_total[lane] : 0u);
-        uint32_t run = incl - own;
-        if (wave > 0) run += (uint32_t)__builtin_amdgcn_readlane((int)waves_incl, wave - 1);
-        uint32_t* const runs = X.runs + (size_t)blk * T;
-        for (uint32_t x = 0; x < per; ++x)
-            if (b0 + x < T) {
-                const uint32_t c = first[b0 + x];
-                first[b0 + x] = run;
-                runs[b0 + x] = run | c << 16;
-                run += c;
-            }
-    }
+    counts_to_runs<BS>(first, T, wave_total, X.runs + (size_t)blk * T);
     lds_barrier();
 #pragma unroll
     for (int r = 0; r < R; ++r) {

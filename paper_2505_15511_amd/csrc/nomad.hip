@@ -16,6 +16,7 @@
 #include "host_util.h"
 #include "nomad.h"
 #include "exchange_kernels.h"
+#include "run_kernels.h"
 #include "nomad_kernels.h"
 #include "small_kernels.h"
 
@@ -79,6 +80,7 @@ struct nomad_ctx {
     int small_wg = 0;               // > 0: the edge pass sums in LDS (small_kernels.h), at most this many workgroups
     unsigned long long* small_sums = nullptr;
     bool exchange = false;          // the edge pass is the exchanged one (exchange_kernels.h)
+    bool runs = false;              // the edge pass is the one that leaves its forces in runs (run_kernels.h); it shares the arrays of the exchange
     float2* ex_rec = nullptr;
     uint16_t *ex_idx = nullptr, *ex_side = nullptr;
     uint32_t *ex_pos = nullptr, *ex_runs = nullptr;
@@ -146,7 +148,7 @@ void dev_free(nomad_ctx* c, T*& p) {
 
 void free_exchange(nomad_ctx* c) {
     dev_free(c, c->ex_rec); dev_free(c, c->ex_idx); dev_free(c, c->ex_pos); dev_free(c, c->ex_side); dev_free(c, c->ex_runs);
-    c->exchange = false;
+    c->exchange = c->runs = false;
 }
 
 void free_graph(nomad_ctx* c) {
@@ -399,7 +401,7 @@ ExchangeRowsKernel exchange_rows_kernel(const ExchangePlan& p) {
 }
 // the sums of a tile, for the length of this problem's runs
 using TileSumsKernel = void (*)(const TileSums, float2*, int64_t, float2*, float, unsigned long long*, int);
-TileSumsKernel tile_sums_kernel(int lanes) { return lanes == 8 ? k_tile_sums<8> : k_tile_sums<16>; }
+TileSumsKernel tile_sums_kernel(int lanes) { return lanes == 8 ? k_tile_sums<8> : lanes == 16 ? k_tile_sums<16> : k_tile_sums<32>; }
 
 void launch_tile_sums(nomad_ctx* c, int lanes, const TileSums& x, float eta, int phase) {
     hipLaunchKernelGGL(tile_sums_kernel(lanes), dim3(exchange_padded_tiles(x.n_tiles)), dim3(kBinBlock), 16 * (size_t)x.points, c->stream, x, c->g, c->n, c->theta, eta,
@@ -410,7 +412,7 @@ ExchangeArgs exchange_args(const nomad_ctx* c, int64_t e_begin, int64_t e_end) {
     ExchangeArgs x{};
     x.head = c->head; x.rec = c->ex_rec; x.idx = c->ex_idx; x.pos = c->ex_pos; x.side = c->ex_side; x.runs = c->ex_runs; x.ghead = c->ghead;
     x.e_begin = e_begin; x.e_end = e_end;
-    const int eb = exchange_block_edges(c->cfg.n_neg);
+    const int eb = c->runs ? runs_block_edges(c->cfg.n_neg) : exchange_block_edges(c->cfg.n_neg);
     x.n_blocks = (uint32_t)((e_end - e_begin + eb - 1) / eb);
     x.n_tiles = c->n_bins; x.tile_bits = c->tile_bits; x.spare = c->ex_spare;
     return x;
@@ -439,8 +441,33 @@ void launch_exchange_edges(nomad_ctx* c, const EdgeArgs& a, const ExchangeArgs& 
 }
 
 void launch_exchange_sums(nomad_ctx* c, const ExchangeArgs& x, float eta, int phase) {
-    const uint32_t points = 1u << c->tile_bits;
-    launch_tile_sums(c, c->ex.sums_lanes, TileSums{x.rec, x.idx, x.runs, x.ghead, x.n_blocks, (uint32_t)exchange_slots(c->cfg.n_neg), x.n_tiles, points, points - 1u, x.spare}, eta, phase);
+    const uint32_t points = 1u << c->tile_bits, slots = (uint32_t)(c->runs ? runs_slots(c->cfg.n_neg) : exchange_slots(c->cfg.n_neg));
+    launch_tile_sums(c, c->ex.sums_lanes, TileSums{x.rec, x.idx, x.runs, x.ghead, x.n_blocks, slots, x.n_tiles, points, points - 1u, x.spare}, eta, phase);
+}
+
+// ---- the edge pass that leaves its forces in runs
+template <typename Fn>
+void with_runs_kernel(const nomad_ctx* c, Fn fn) {
+    const int kind = edge_kind(c);
+    switch (c->cfg.n_neg) {
+#define NOMAD_CASE(S) case S: fn(kind == kPlainEdges ? k_edges_runs<S, kPlainEdges> : kind == kGroupedEdges ? k_edges_runs<S, kGroupedEdges> : k_edges_runs<S, kFarEdges>); break;
+        NOMAD_CASE(0) NOMAD_CASE(1) NOMAD_CASE(2) NOMAD_CASE(3) NOMAD_CASE(4) NOMAD_CASE(5) NOMAD_CASE(6) NOMAD_CASE(7) NOMAD_CASE(8)
+#undef NOMAD_CASE
+    }
+}
+
+int prepare_runs(nomad_ctx* c) {
+    hipError_t err = hipSuccess;
+    const auto allow = [&](const void* k, size_t lds) { if (err == hipSuccess) err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); };
+    with_runs_kernel(c, [&](auto kernel) { allow((const void*)kernel, runs_lds_bytes(c->cfg.n_neg, c->n_bins)); });
+    allow((const void*)tile_sums_kernel(c->ex.sums_lanes), (size_t)16 << c->tile_bits);
+    HIP_TRY(c, err);
+    return NOMAD_OK;
+}
+
+void launch_runs_edges(nomad_ctx* c, const EdgeArgs& a, const ExchangeArgs& x) {
+    const int s = c->cfg.n_neg;
+    with_runs_kernel(c, [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(x.n_blocks), dim3(runs_lanes(s)), runs_lds_bytes(s, x.n_tiles), c->stream, a, x); });
 }
 
 // cell means of the current embedding -> mu, cinfo
@@ -799,6 +826,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         want_plan.n = n; want_plan.E = E; want_plan.s = s;
         want_plan.pool_size = c->cfg.pool_size; want_plan.pool_block = c->cfg.pool_block; want_plan.pool_line = std::max(1, c->cfg.pool_line);
         want_plan.pool_distinct = c->cfg.pool_mode != NOMAD_POOL_PICKS16;
+        want_plan.grouped = c->grouped;
         want_plan.far = edge_kind(c) == kFarEdges;
         want_plan.batches = c->cfg.batches_per_epoch;
         want_plan.tune_edge_block = c->tune_edge_block; want_plan.tune_wg_per_cu = c->tune_wg_per_cu;
@@ -858,7 +886,33 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 c->phases = 1;
             }
         }
-        if (E > 0 && why.empty() && !c->exchange && !c->small_wg) {
+        const RunsPlan in_runs = edge_kind(c) != kAnyEdges && why.empty() ? plan_runs(want_plan, plan) : RunsPlan{};
+        if (in_runs.use && !c->exchange && !c->small_wg) {
+            c->ex.sums_lanes = in_runs.sums_lanes;
+            c->n_bins = n_bins;
+            c->tile_bits = tile_bits;
+            c->runs = true;
+            const int eb = runs_block_edges(s);
+            c->phases = plan_record_phases(E, s, eb, c->tune_phases);
+            // (sub-steps and phases are cut into blocks of their own: at most one more each than the positions fill)
+            const size_t blocks = (size_t)((E + eb - 1) / eb + c->phases - 1) / c->phases + 1, slots = runs_slots(s) * blocks;
+            c->ex_spare = (uint32_t)slots;
+            bool ok = slots + kExchangeSpare < ((size_t)1 << 32) && dev_alloc(c, &c->ex_rec, slots + kExchangeSpare) == NOMAD_OK &&
+                      dev_alloc(c, &c->ex_idx, slots + kExchangeSpare) == NOMAD_OK && dev_alloc(c, &c->ex_runs, (size_t)n_bins * blocks) == NOMAD_OK &&
+                      dev_alloc(c, &c->head, (size_t)E) == NOMAD_OK && (c->phases == 1 || dev_alloc(c, &c->carry, (size_t)n * 2) == NOMAD_OK);
+            ok = ok && prepare_runs(c) == NOMAD_OK;
+            if (ok) {
+                hipLaunchKernelGGL(k_edge_heads, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, n, c->head);
+                hipLaunchKernelGGL(k_zero_f2, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->ghead, n);
+                c->binned = true;
+            } else {   // chains of records remain
+                (void)hipGetLastError();
+                free_exchange(c);
+                dev_free(c, c->head); dev_free(c, c->carry);
+                c->phases = 1;
+            }
+        }
+        if (E > 0 && why.empty() && !c->exchange && !c->small_wg && !c->runs) {
             c->bin_block = bin_block;
             c->sorted_records = sorted;
             c->flush_rounds = plan.flush_rounds;
@@ -1026,19 +1080,20 @@ int nomad_epoch(nomad_ctx* c, int32_t t) {
         if (c->cfg.scatter_mode == NOMAD_SCATTER_DETERMINISTIC && c->binned) {
             // the positions of this step in `phases` ranges cut at multiples of the workgroup size; every range's
             // records are accumulated before the next range reuses the pool, the last accumulation takes the step
-            const int64_t cut = c->exchange ? exchange_block_edges(c->cfg.n_neg) : c->bin_block;
+            const int64_t cut = c->exchange ? exchange_block_edges(c->cfg.n_neg) : c->runs ? runs_block_edges(c->cfg.n_neg) : c->bin_block;
             const int phases = c->pool_rounds ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(c->phases, (e1 - e0 + cut - 1) / cut));
             for (int ph = 0; ph < phases; ++ph) {
                 const int64_t blocks = (e1 - e0 + cut - 1) / cut;
                 const int64_t p0 = e0 + blocks * ph / phases * cut, p1 = ph + 1 == phases ? e1 : e0 + blocks * (ph + 1) / phases * cut;
                 { Timed tm(c, NOMAD_K_EDGES);
                   if (c->exchange) launch_exchange_edges(c, a, exchange_args(c, p0, p1));
+                  else if (c->runs) launch_runs_edges(c, a, exchange_args(c, p0, p1));
                   else launch_edges_binned(c, a, p0, p1); }
                 const bool last = ph + 1 == phases;
                 if (last) run_mean_gradient(c, r0, r1);
                 const int kind = phases == 1 ? kPhaseOnly : ph == 0 ? kPhaseFirst : last ? kPhaseLast : kPhaseMiddle;
                 Timed tm(c, NOMAD_K_TILES);   // accumulates the records of every tile; the last one takes the SGD step for its points
-                if (c->exchange) launch_exchange_sums(c, exchange_args(c, p0, p1), eta, kind);
+                if (c->exchange || c->runs) launch_exchange_sums(c, exchange_args(c, p0, p1), eta, kind);
                 else hipLaunchKernelGGL(k_tile_accumulate, dim3(c->n_bins), dim3(kBinBlock), sizeof(unsigned long long) * 2 << c->tile_bits,
                                    c->stream, bin_args(c), (uint32_t)c->n_wg, c->g, n, c->theta, eta,
                                    c->through_means ? c->cluster_of : nullptr, c->through_means ? c->gmean : nullptr, c->carry, kind);

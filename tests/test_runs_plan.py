@@ -1,0 +1,61 @@
+"""Which problems take the edge pass that leaves its forces in runs (csrc/edge_plan.h, compiled on the host): the rule's lines, LDS and 16-bit slots."""
+import json
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+DRIVER = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "edge_plan.h"
+using namespace nomad;
+// argv: n s grouped far pool_size tune_record_sort
+int main(int argc, char** argv) {
+    if (argc != 7) return 2;
+    EdgePlanRequest q;
+    q.n = atoll(argv[1]); q.E = 15 * q.n; q.s = atoi(argv[2]); q.grouped = atoi(argv[3]); q.far = atoi(argv[4]);
+    q.pool_size = atoi(argv[5]); q.pool_block = q.pool_size ? 4096 : 0; q.tune_record_sort = atoi(argv[6]);
+    EdgePlan p = plan_edge_pass(q);
+    fit_tiles(p, q, 256, true);
+    const RunsPlan x = plan_runs(q, p);
+    printf("{\"use\": %d, \"sums\": %d, \"tiles\": %u, \"tile_bits\": %d, \"slots\": %zu, \"edges\": %d, \"lds\": %zu, \"sums_lds\": %zu, \"max_lds\": %zu}\n",
+           (int)x.use, x.sums_lanes, p.n_bins, p.tile_bits, runs_slots(q.s), runs_block_edges(q.s), runs_lds_bytes(q.s, p.n_bins),
+           ((size_t)16 << p.tile_bits) + (size_t)(kBinBlock / 64) * tile_sums_queue(x.sums_lanes) * 8, kMaxLdsBytes);
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    d = tmp_path_factory.mktemp("runs_plan")
+    src, exe = d / "plan.cpp", d / "plan"
+    src.write_text(DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2505_15511_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True, capture_output=True, text=True)
+
+    def plan(n, s=5, grouped=0, far=0, pool=0, sort=0):
+        out = subprocess.run([str(exe)] + [str(int(v)) for v in (n, s, grouped, far, pool, sort)], check=True, capture_output=True, text=True)
+        return json.loads(out.stdout)
+    return plan
+
+
+def test_the_lines(planner):
+    assert [planner(n)["use"] for n in (2, 100_000, 900_000)] == [1, 1, 1]
+    assert planner(100_000, s=9)["use"] == 0 and planner(100_000, pool=1024)["use"] == 0 and planner(100_000, sort=1)["use"] == 0
+    assert planner(6_000_000, s=2, grouped=1)["use"] == 1
+    assert [planner(n, grouped=1, far=1)["use"] for n in (256 * 8192, 256 * 8192 + 1)] == [1, 0]
+    assert planner(60_000_000, s=2, grouped=1)["use"] == 0           # records that are not sorted
+
+
+@pytest.mark.parametrize("s", range(9))
+def test_slots_and_lds(planner, s):
+    for n in (2, 5_000, 99_999, 2_000_000, 8_000_000, 30_000_000):
+        p = planner(n, s=s, grouped=1)
+        assert p["slots"] % 64 == 0 and p["slots"] >= p["edges"] * (s + 1) + p["edges"] // 32 and p["slots"] < 65_536
+        assert p["edges"] % 64 == 0 and p["tile_bits"] <= 16
+        if p["use"]:
+            assert 2 * p["lds"] <= p["max_lds"] and p["sums_lds"] <= p["max_lds"] and p["sums"] in (8, 16, 32)
