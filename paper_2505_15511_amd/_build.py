@@ -17,7 +17,7 @@ HEADERS = [os.path.join(_PKG, "csrc", "nomad_kernels.h"), os.path.join(_PKG, "cs
            os.path.join(_PKG, "csrc", "metrics_kernels.h"), os.path.join(_PKG, "csrc", "philox.h"),
            os.path.join(_PKG, "csrc", "pca_kernels.h"), os.path.join(_PKG, "csrc", "host_util.h"),
            os.path.join(_PKG, "csrc", "edge_plan.h"), os.path.join(_PKG, "csrc", "exchange_kernels.h"),
-           os.path.join(_PKG, "csrc", "run_kernels.h"), os.path.join(_PKG, "csrc", "small_kernels.h"), os.path.join(_PKG, "csrc", "kmeans_plan.h"),
+           os.path.join(_PKG, "csrc", "run_kernels.h"), os.path.join(_PKG, "csrc", "field_kernels.h"), os.path.join(_PKG, "csrc", "small_kernels.h"), os.path.join(_PKG, "csrc", "kmeans_plan.h"),
            os.path.join(_ROOT, "include", "nomad.h")]
 
 

@@ -302,4 +302,18 @@ inline RunsPlan plan_runs(const EdgePlanRequest& q, const EdgePlan& p) {
     return x;
 }
 
+// Mean-field sums by interpolation (field_kernels.h) or cell by cell (k_mean_field).
+//   field_may, before anything is known of the embedding: enough work, and few cells in the heads' own groups, which are summed one by one either way.
+//   field_pays, on the device, from the squares that have heads: vector instructions, 16 a cell and node (float64 with its reciprocal), 1,100 a head (three
+//   polynomials of 256 terms, the place of the head in its square's list) against 9.8 a cell and head, with a third to spare.  Trained embeddings lie close: 6 M points in
+//   1,638 clusters after 200 epochs within 10 of the origin, 279 squares.  Mean-field sums, cell by cell -> field, ms: 6 M x 1,638 2.44 -> 0.32; 500 k x 1,050 over 85 squares
+//   0.13 -> 0.10; 1 M x 2,000 over 990 squares 0.50 -> 0.50 (its limit here); with an embedding it cannot use (looked at and left) 0.04 more.
+constexpr int kFieldMost = 1024;        // squares that can have heads
+inline bool field_may(double heads, double cells, double own_cells_of_all_heads) {
+    return cells >= 256 && heads * cells >= 5e8 && own_cells_of_all_heads <= heads * cells / 16;
+}
+NOMAD_HOST_DEVICE inline bool field_pays(double heads, double cells, double squares) {
+    return squares <= kFieldMost && 256.0 * 16.0 * squares * cells + 1100.0 * heads <= 0.67 * 9.8 * heads * cells;
+}
+
 }  // namespace nomad

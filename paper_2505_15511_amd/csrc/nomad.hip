@@ -16,6 +16,7 @@
 #include "host_util.h"
 #include "nomad.h"
 #include "exchange_kernels.h"
+#include "field_kernels.h"
 #include "run_kernels.h"
 #include "nomad_kernels.h"
 #include "small_kernels.h"
@@ -60,6 +61,8 @@ struct nomad_ctx {
     float *cS = nullptr, *chead = nullptr;   // 2 p_e / S_e per edge, its row sums
     unsigned long long* Gfix = nullptr;      // [2 R] fixed-point sums over the heads, per cell
     float2* gmean = nullptr;                 // [R] what every member of a cell adds to its gradient
+    bool may_interpolate = false;            // the mean-field sums may come from the field (field_kernels.h), which looks at the embedding first
+    Field field{};
     // binned deterministic scatter
     bool binned = false;
     int n_wg = 0, bin_block = 1024;
@@ -151,6 +154,12 @@ void free_exchange(nomad_ctx* c) {
     c->exchange = c->runs = false;
 }
 
+void free_field(nomad_ctx* c) {
+    dev_free(c, c->field.state); dev_free(c, c->field.count); dev_free(c, c->field.cursor); dev_free(c, c->field.list); dev_free(c, c->field.place);
+    dev_free(c, c->field.order); dev_free(c, c->field.partial); dev_free(c, c->field.coefs);
+    c->may_interpolate = false;
+}
+
 void free_graph(nomad_ctx* c) {
     // nothing that is given back may still be in use, on any stream: epochs recorded into a graph run where it is replayed
     // (refused while another thread records a graph: then at least what this context's own stream does)
@@ -170,6 +179,7 @@ void free_graph(nomad_ctx* c) {
     dev_free(c, c->pool); dev_free(c, c->chunk_prev); dev_free(c, c->chain_head); dev_free(c, c->chain_fill); dev_free(c, c->wg_pool_begin);
     dev_free(c, c->head); dev_free(c, c->carry); dev_free(c, c->pool_keys);
     free_exchange(c);
+    free_field(c);
     dev_free(c, c->small_sums);
     c->small_wg = 0;
     c->phases = 1;
@@ -486,9 +496,21 @@ int run_means(nomad_ctx* c) {
 int run_mean_field(nomad_ctx* c, int64_t row_begin, int64_t row_end) {
     if (!c->grouped || row_end <= row_begin || c->cfg.far_field == NOMAD_FAR_FIELD_SAMPLED) return NOMAD_OK;
     Timed tm(c, NOMAD_K_MEANFIELD);
+    if (c->may_interpolate) {   // by interpolation, where the embedding is as it has to be for that (k_field_scan): k_mean_field then has nothing to do
+        const int64_t heads = row_end - row_begin;
+        const Field& f = c->field;
+        const dim3 spans(blocks_for(heads, kFieldSpan)), lanes(kFieldBlock), grid(kFieldGrid);
+        hipLaunchKernelGGL(k_field_count, spans, lanes, 0, c->stream, c->theta, row_begin, row_end, f);
+        hipLaunchKernelGGL(k_field_scan, dim3(1), dim3(1024), 0, c->stream, heads, c->R, f);
+        hipLaunchKernelGGL(k_field_place, spans, lanes, 0, c->stream, c->theta, row_begin, row_end, f);
+        hipLaunchKernelGGL(k_field_nodes, dim3(kFieldUnits), grid, 0, c->stream, c->cinfo, c->R, f);
+        hipLaunchKernelGGL(k_field_coefs, dim3(kFieldMost), grid, 0, c->stream, f);
+        hipLaunchKernelGGL(k_field_sums, dim3(blocks_for(heads, 256 * kFieldTurns)), dim3(256), 0, c->stream, c->theta, c->cluster_of, c->group_of_cluster,
+                           c->cinfo, c->group_slots, row_begin, row_end, f, (const double*)f.coefs, c->A, c->B);
+    }
     hipLaunchKernelGGL(k_mean_field, dim3(blocks_for(row_end - row_begin, kMeanFieldBlock * kMeanFieldHeads)), dim3(kMeanFieldBlock), 0,
                        c->stream, c->theta, c->cluster_of, c->group_of_cluster, c->cinfo, c->group_slots, c->R, row_begin, row_end,
-                       c->A, c->B);
+                       c->A, c->B, c->may_interpolate ? &c->field.state->use : nullptr);
     return NOMAD_OK;
 }
 
@@ -798,6 +820,23 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         TRY(dev_alloc(c, &c->group_slots, (size_t)R));
         HTRY(hipMemcpy(c->cell_slot, slot.data(), sizeof(int32_t) * (size_t)R, hipMemcpyHostToDevice));
         HTRY(hipMemcpy(c->group_slots, gslots.data(), sizeof(int2) * (size_t)R, hipMemcpyHostToDevice));
+        double own = 0.0;   // cells of their own group, over all heads
+        for (int32_t r = 0; r < R; ++r) own += (double)hcounts[r] * (double)gcells[hgroup[r]];
+        if (c->cfg.far_field == NOMAD_FAR_FIELD_EXACT && field_may((double)n / c->cfg.batches_per_epoch, (double)R, own / c->cfg.batches_per_epoch)) {
+            Field& f = c->field;
+            c->may_interpolate = dev_alloc(c, &f.state, 1) == NOMAD_OK && dev_alloc(c, &f.count, (size_t)kFieldSquares) == NOMAD_OK &&
+                dev_alloc(c, &f.cursor, (size_t)kFieldSquares) == NOMAD_OK && dev_alloc(c, &f.list, (size_t)kFieldMost) == NOMAD_OK &&
+                dev_alloc(c, &f.place, (size_t)kFieldSquares) == NOMAD_OK && dev_alloc(c, &f.order, (size_t)n) == NOMAD_OK &&
+                dev_alloc(c, &f.partial, (size_t)kFieldUnits * 3 * kFieldGrid) == NOMAD_OK && dev_alloc(c, &f.coefs, (size_t)kFieldMost * 3 * kFieldGrid) == NOMAD_OK;
+            if (c->may_interpolate) {
+                HTRY(hipMemset(f.state, 0, sizeof(FieldState)));
+                HTRY(hipMemset(f.count, 0, sizeof(uint32_t) * kFieldSquares));
+                HTRY(hipStreamSynchronize(nullptr));
+            } else {   // cell by cell
+                (void)hipGetLastError();
+                free_field(c);
+            }
+        }
     }
 
     c->pool_blocks = 1;

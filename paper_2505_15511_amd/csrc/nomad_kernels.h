@@ -312,7 +312,8 @@ __global__ void __launch_bounds__(kMeanFieldBlock) k_mean_field(const float2* __
                                                                 const int32_t* __restrict__ group_of_cluster,
                                                                 const float4* __restrict__ cinfo, const int2* __restrict__ group_slots,
                                                                 int32_t R, int64_t i_begin, int64_t n, float* __restrict__ A,
-                                                                float2* __restrict__ B) {
+                                                                float2* __restrict__ B, const uint32_t* __restrict__ done) {
+    if (done && *done) return;   // the sums are there already (field_kernels.h)
     // Every wavefront needs the whole cell table.  Reading it straight from memory with wave-uniform loads makes
     // each of the n/64 wavefronts pull all |R| x 16 bytes through the scalar cache (240 GB per launch at 60 M points
     // and 16,384 cells); staged through LDS the table is read once per workgroup and broadcast to the lanes.
