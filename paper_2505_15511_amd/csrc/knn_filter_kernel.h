@@ -181,7 +181,7 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // Large products alone: the nearest centroid is usually nearer than the second by more than 2 slack, and then hi hi decides: a third of the
 // products, and half of what is read of the queries.  A step of Lloyd's iterations does without the others where the one before has
 // left (or, with all three products, would have left) few of the queries open (products_alone); the first one does not.  What is open goes to
-// k_assign_refine as ever, with slack in the margin and in tau.  1,000,000 x 128 and 256 centroids: 227 -> 132 us a step, a call of ten 4.64 -> 3.76 ms.
+// k_assign_refine as ever, with slack in the margin and in tau.  1,000,000 x 128 and 256 centroids: 227 -> 132 us a step, a call of ten 4.64 -> 3.76 ms (before keys were numbered: 196 and 104).
 // Or, with `open`, a word of bits a tile of queries says which those are, and what goes with them lies at their positions (a list's one counter was what
 // the step waited for: a step of a million points with one in every second wavefront, 150 us for 132).
 struct KnnAssign { int32_t* out; int32_t* todo; uint32_t* n_todo; uint32_t* open; };
@@ -438,6 +438,13 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
         }
         if (s == KS - 1) big += chunk;
     };
+    // One neighbour, in 32-row tiles: the element v of the accumulator goes into the last four bits of the key, so that the two smallest of a tile's sixteen take three instructions a key instead of
+    // eight; those keys differ from their own by less than 2^-19 of them, which the margin and tau carry.  A group's last tile, if padded, is done key by key
+    // (infinity with a number in it is none).  Large products alone, 1,000,000 x 128 on 256 centroids: 132 -> 104 us a step, with all three products 222 -> 196.
+    constexpr bool kNumbered = L == 2 && TILE == 32;
+    // positions there: 16 times the tile and the element, which is candidate 8 (v / 4) + 4 part + v % 4 of the tile
+    const auto place_of = [&](int32_t p) { return p < 0 || !kNumbered ? p : (p >> 4) * TILE + 8 * (p >> 2 & 3) + 4 * part + (p & 3); };
+    const int32_t n_cands = (int32_t)(P.cstart[grp + 1] - c0);
     const int32_t sift_from = !kSift ? n_tiles : !kTogether || P.ordered ? 0 : (WAVES == 8 ? list_len * TILE / 2 : list_len * TILE * 2) / (kShares ? P.slices : 1);
     float slack = 0.f;             // >= |hi lo + lo hi| of this query with any candidate, as summed below
     // |hi| <= |c| (1 + 2^-11), |lo| <= 2^-11 |c|, below float16's normal numbers 2^-25 an element; one part in a hundred for
@@ -530,6 +537,25 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
             }
             if (L == 2) big += small;
         }
+        if (kNumbered && (t + 1) * TILE <= n_cands) {
+            float k0 = __builtin_inff(), k1 = k0;   // the two smallest of the tile's keys, numbered
+#pragma unroll
+            for (int v = 0; v < kKeys; ++v) {
+                const float key = __uint_as_float((__float_as_uint(big[v]) & 0xFFFFFFF0u) | (uint32_t)v);
+                k1 = __builtin_amdgcn_fmed3f(k0, key, k1);
+                asm("v_min_f32_e32 %0, %1, %2" : "=v"(k0) : "v"(key), "v"(k0));   // (fminf would make sure first that neither is a signalling NaN)
+            }
+            const int32_t p0 = t << 4 | (int32_t)(__float_as_uint(k0) & 15u), p1 = t << 4 | (int32_t)(__float_as_uint(k1) & 15u);
+            const bool lt0 = k0 < lk[0], lt1 = k0 < lk[L - 1];
+            lp[L - 1] = lt0 ? lp[0] : (lt1 ? p0 : lp[L - 1]);
+            lk[L - 1] = __builtin_amdgcn_fmed3f(lk[0], k0, lk[L - 1]);
+            lp[0] = lt0 ? p0 : lp[0];
+            lk[0] = lt0 ? k0 : lk[0];
+            const bool second = k1 < lk[L - 1];     // (not below the first: k0 is not)
+            lp[L - 1] = second ? p1 : lp[L - 1];
+            lk[L - 1] = second ? k1 : lk[L - 1];
+            return;
+        }
 #pragma unroll
         for (int g = 0; g < kKeys / 4; ++g) {
             float key[4];
@@ -539,10 +565,11 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
             if (L == 2) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
+                    const int32_t at_v = kNumbered ? t << 4 | (4 * g + v) : pos0 + v;   // (see place_of)
                     const bool lt0 = key[v] < lk[0], lt1 = key[v] < lk[L - 1];
-                    lp[L - 1] = lt0 ? lp[0] : (lt1 ? pos0 + v : lp[L - 1]);
+                    lp[L - 1] = lt0 ? lp[0] : (lt1 ? at_v : lp[L - 1]);
                     lk[L - 1] = __builtin_amdgcn_fmed3f(lk[0], key[v], lk[L - 1]);
-                    lp[0] = lt0 ? pos0 + v : lp[0];
+                    lp[0] = lt0 ? at_v : lp[0];
                     lk[0] = lt0 ? key[v] : lk[0];
                 }
             } else if (__any(fminf(fminf(key[0], key[1]), fminf(key[2], key[3])) < thr)) {
@@ -606,6 +633,8 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     const int64_t p = (int64_t)q0g + qpos;
     if (L == 2) {
         // (key of rank 0 and 1 are among the lanes' entries: the second is the smallest of what is not rank 0)
+#pragma unroll
+        for (int x = 0; x < L; ++x) lp[x] = place_of(lp[x]);
         float best = lk[0], second = rank[0] == 0 ? lk[L - 1] : lk[0];
         int32_t bp = lp[0];
 #pragma unroll
@@ -623,8 +652,10 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
             const float length = ldexpf(sqrtf(P.q_norm[max(qpt, 0)]), knn_scale_exponent(P.Q.max_bits[grp])), lo = fmaf(length, 0x1p-11f, least);
             slack = 1.01f * (lo * (1.001f * longest + least) + (1.001f * length + least) * (0x1p-11f * longest + least));
         }
-        const double gap = ((double)second - (double)best) * (double)key_unit, unsure = 2.0 * (double)slack * (double)key_unit;
+        const double numbers = kNumbered ? 0x1p-19 * (fabs((double)best) + fmin(fabs((double)second), 3e38)) : 0.0;   // (no second: infinity)
+        const double gap = ((double)second - (double)best - numbers) * (double)key_unit, unsure = 2.0 * (double)slack * (double)key_unit;
         const bool open = qpt >= 0 && !(gap > 2.0 * eps + (kAlone ? unsure : 0.0));
+        if (kNumbered && last < __builtin_inff()) last = fmaf(-0x1p-18f, fabsf(last), last);
         if (counted) {
             const unsigned long long left = __ballot(qpt >= 0 && part == 0 && !(gap > 2.0 * eps + unsure));
             if (lane == 0 && left) atomicAdd(P.open_count, (uint32_t)__popcll(left));
