@@ -77,7 +77,6 @@ struct nomad_ctx {
     HostWord overflow, loss_out;    // written by kernels, read once the stream has been waited for
     double* loss_partial = nullptr;
     uint32_t edge_grid = 0;
-    int* flags = nullptr;
     // launch-shape knobs (nomad_tune) and what set_graph made of them
     int tune_edge_block = 0, tune_wg_per_cu = 0, tune_path = 0, tune_pool_kernel = 1, tune_phases = 0, tune_record_sort = 0, tune_flush_rounds = 0, tune_exchange = 0;
     int small_wg = 0;               // > 0: the edge pass sums in LDS (small_kernels.h), at most this many workgroups
@@ -168,14 +167,13 @@ void free_graph(nomad_ctx* c) {
         (void)hipStreamSynchronize(c->stream);
     }
     dev_free(c, c->row_ptr); dev_free(c, c->col); dev_free(c, c->cluster_of); dev_free(c, c->group_of_cluster);
-    dev_free(c, c->pe); dev_free(c, c->counts); dev_free(c, c->gbase); dev_free(c, c->gcount); dev_free(c, c->chunk_start);
+    dev_free(c, c->pe); dev_free(c, c->counts); dev_free(c, c->gbase); dev_free(c, c->gcount); c->chunk_start = nullptr;   // (in the array of the chunks)
     dev_free(c, c->gomega); dev_free(c, c->hinfo); dev_free(c, c->gmembers); dev_free(c, c->cmembers); dev_free(c, c->chunks); dev_free(c, c->mean_partial);
     dev_free(c, c->theta); dev_free(c, c->g); dev_free(c, c->ghead); dev_free(c, c->mu); dev_free(c, c->B); dev_free(c, c->cinfo);
     dev_free(c, c->cell_slot); dev_free(c, c->group_slots);
     dev_free(c, c->A); dev_free(c, c->gfix); dev_free(c, c->loss_partial);
     dev_free(c, c->cS); dev_free(c, c->chead); dev_free(c, c->Gfix); dev_free(c, c->gmean);
     c->through_means = false;
-    dev_free(c, c->flags);
     dev_free(c, c->pool); dev_free(c, c->chunk_prev); dev_free(c, c->chain_head); dev_free(c, c->chain_fill); dev_free(c, c->wg_pool_begin);
     dev_free(c, c->head); dev_free(c, c->carry); dev_free(c, c->pool_keys);
     free_exchange(c);
@@ -644,8 +642,8 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         c->batch_edge.assign((size_t)B + 1, 0);
         for (int b = 0; b <= B; ++b) {
             c->batch_row[b] = n * (int64_t)b / B;
-            int32_t off = 0;
-            HTRY(hipMemcpy(&off, c->row_ptr + c->batch_row[b], sizeof(int32_t), hipMemcpyDeviceToHost));
+            int32_t off = b == 0 ? 0 : E32;   // (row_ptr[0] is checked below)
+            if (b > 0 && b < B) HTRY(hipMemcpy(&off, c->row_ptr + c->batch_row[b], sizeof(int32_t), hipMemcpyDeviceToHost));
             c->batch_edge[b] = off;
         }
     }
@@ -683,30 +681,32 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
     }
 
     // ---- validate on the device
-    rc = dev_alloc(c, &c->flags, kFlagCount);
-    uint32_t* first = nullptr;
-    unsigned long long* boundaries = nullptr;
-    if (rc == NOMAD_OK) rc = dev_alloc(c, &c->counts, (size_t)R);
-    if (rc == NOMAD_OK) rc = dev_alloc(c, &first, (size_t)R);
-    if (rc == NOMAD_OK) rc = dev_alloc(c, &boundaries, 2);
-    auto cleanup_tmp = [&]() { (void)hipStreamSynchronize(st); dev_free(c, wdev); dev_free(c, first); dev_free(c, boundaries); };
+    // what the checks find, in one block and one copy: [2] boundaries, [kFlagCount] flags, [R] counts, [R] first
+    constexpr size_t kFlagsAt = 4, kCountsAt = kFlagsAt + kFlagCount;
+    const size_t first_at = kCountsAt + (size_t)R, found_words = first_at + (size_t)R;
+    uint32_t* found = nullptr;
+    rc = dev_alloc(c, &c->counts, (size_t)R);
+    if (rc == NOMAD_OK) rc = dev_alloc(c, &found, found_words);
+    auto cleanup_tmp = [&]() { (void)hipStreamSynchronize(st); dev_free(c, wdev); dev_free(c, found); };
     if (rc != NOMAD_OK) { cleanup_tmp(); free_graph(c); return rc; }
+    int* const flags = (int*)(found + kFlagsAt);
 #define HTRY2(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) { cleanup_tmp(); free_graph(c); return fail(c, e_ == hipErrorOutOfMemory ? NOMAD_E_OOM : NOMAD_E_HIP, "%s: %s", #call, hipGetErrorString(e_)); } } while (0)
     HTRY2(hipStreamSynchronize(nullptr));   // the copies above: between device buffers they may still be on their way on the null stream
-    HTRY2(hipMemsetAsync(c->flags, 0, sizeof(int) * kFlagCount, st));
-    HTRY2(hipMemsetAsync(c->counts, 0, sizeof(uint32_t) * (size_t)R, st));
-    HTRY2(hipMemsetAsync(first, 0xFF, sizeof(uint32_t) * (size_t)R, st));
-    HTRY2(hipMemsetAsync(boundaries, 0, sizeof(unsigned long long) * 2, st));
-    hipLaunchKernelGGL(k_check_row_ptr, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, n, c->flags);
+    HTRY2(hipMemsetAsync(found, 0, sizeof(uint32_t) * first_at, st));
+    HTRY2(hipMemsetAsync(found + first_at, 0xFF, sizeof(uint32_t) * (size_t)R, st));
+    hipLaunchKernelGGL(k_check_row_ptr, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, n, flags);
     int hflags[kFlagCount];
-    HTRY2(hipMemcpyAsync(hflags, c->flags, sizeof(hflags), hipMemcpyDeviceToHost, st));
+    HTRY2(hipMemcpyAsync(hflags, flags, sizeof(hflags), hipMemcpyDeviceToHost, st));
     HTRY2(hipStreamSynchronize(st));
     if (hflags[kFlagRowPtr]) { cleanup_tmp(); free_graph(c); return fail(c, NOMAD_E_BAD_GRAPH, "row_ptr must start at 0 and be non-decreasing"); }
-    hipLaunchKernelGGL(k_check_rows, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, c->col, wdev, c->pe, n, by_rank ? 1 : 0, c->flags);
+    hipLaunchKernelGGL(k_check_rows, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, c->col, wdev, c->pe, n, by_rank ? 1 : 0, flags);
     hipLaunchKernelGGL(k_cluster_census, dim3(blocks_for(n, kCensusSpan)), dim3(kBlock), 0, st, c->cluster_of,
-                       c->grouped ? c->group_of_cluster : nullptr, n, R, c->counts, first, boundaries, c->flags);
-    HTRY2(hipMemcpyAsync(hflags, c->flags, sizeof(hflags), hipMemcpyDeviceToHost, st));
+                       c->grouped ? c->group_of_cluster : nullptr, n, R, found + kCountsAt, found + first_at, (unsigned long long*)found, flags);
+    std::vector<uint32_t> hfound(found_words);
+    HTRY2(hipMemcpyAsync(c->counts, found + kCountsAt, sizeof(uint32_t) * (size_t)R, hipMemcpyDeviceToDevice, st));
+    HTRY2(hipMemcpyAsync(hfound.data(), found, sizeof(uint32_t) * found_words, hipMemcpyDeviceToHost, st));
     HTRY2(hipStreamSynchronize(st));
+    memcpy(hflags, hfound.data() + kFlagsAt, sizeof(hflags));
     const char* what = hflags[kFlagCol] ? "col_idx entry outside 0..n-1" : hflags[kFlagSelfLoop] ? "self loop in the graph"
                      : hflags[kFlagWeight] ? "weights must be finite, >= 0, with a positive sum on every non-empty row"
                      : hflags[kFlagCluster] ? "cluster_of entry outside 0..|R|-1" : nullptr;
@@ -714,12 +714,11 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
     dev_free(c, wdev);   // (the check has been waited for)
 
     // ---- partition tables (host arithmetic on |R|-sized arrays only)
-    std::vector<uint32_t> hcounts(R), hfirst(R), hgfirst(R, 0xFFFFFFFFu);
+    const std::vector<uint32_t> hcounts(hfound.begin() + kCountsAt, hfound.begin() + (long)first_at), hfirst(hfound.begin() + (long)first_at, hfound.end());
+    std::vector<uint32_t> hgfirst(R, 0xFFFFFFFFu);
     unsigned long long hb[2];
-    HTRY2(hipMemcpy(hcounts.data(), c->counts, sizeof(uint32_t) * (size_t)R, hipMemcpyDeviceToHost));
-    HTRY2(hipMemcpy(hfirst.data(), first, sizeof(uint32_t) * (size_t)R, hipMemcpyDeviceToHost));
-    HTRY2(hipMemcpy(hb, boundaries, sizeof(hb), hipMemcpyDeviceToHost));
-    cleanup_tmp();
+    memcpy(hb, hfound.data(), sizeof(hb));
+    dev_free(c, found);   // (waited for)
     if (c->grouped)
         for (int32_t r = 0; r < R; ++r) hgfirst[hgroup[r]] = std::min(hgfirst[hgroup[r]], hfirst[r]);
     int64_t nonempty = 0;
@@ -756,11 +755,17 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         }
         chunk_start[R] = (uint32_t)chunks.size();
         c->n_chunks = (uint32_t)chunks.size();
-        TRY(dev_alloc(c, &c->chunks, chunks.size()));
-        TRY(dev_alloc(c, &c->chunk_start, (size_t)R + 1));
+        // one array and one copy: the first chunk of every cell follows the chunks
+        static_assert(sizeof(MeanChunk) % sizeof(uint32_t) == 0, "");
+        std::vector<uint32_t> both(chunks.size() * (sizeof(MeanChunk) / 4) + (size_t)R + 1);
+        if (!chunks.empty()) memcpy(both.data(), chunks.data(), sizeof(MeanChunk) * chunks.size());
+        std::copy(chunk_start.begin(), chunk_start.end(), both.end() - (R + 1));
+        uint32_t* both_dev = nullptr;
+        TRY(dev_alloc(c, &both_dev, both.size()));
+        c->chunks = (MeanChunk*)both_dev;
+        c->chunk_start = both_dev + (both.size() - ((size_t)R + 1));
         TRY(dev_alloc(c, &c->mean_partial, chunks.size()));
-        HTRY(hipMemcpy(c->chunks, chunks.data(), sizeof(MeanChunk) * chunks.size(), hipMemcpyHostToDevice));
-        HTRY(hipMemcpy(c->chunk_start, chunk_start.data(), sizeof(uint32_t) * ((size_t)R + 1), hipMemcpyHostToDevice));
+        HTRY(hipMemcpy(both_dev, both.data(), sizeof(uint32_t) * both.size(), hipMemcpyHostToDevice));
     }
     // sampling populations
     const double Mn = (double)c->noise_count;

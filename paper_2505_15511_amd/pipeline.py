@@ -20,6 +20,8 @@ def neighbour_lists_to_csr(nbrs: torch.Tensor, graph: str = "directed"):
     ranks, Eq. 7, when asked to: inverse_rank_weights); "symmetric": union with the transposed edges, unit weights.
     Returns (row_ptr, col_idx, None)."""
     n, k = nbrs.shape
+    if graph not in ("directed", "symmetric"):
+        raise ValueError("graph must be 'directed' or 'symmetric'")
     valid = nbrs >= 0
     if graph == "symmetric":
         src = torch.arange(n, device=nbrs.device, dtype=torch.int64)[:, None].expand(n, k)[valid]
@@ -28,16 +30,16 @@ def neighbour_lists_to_csr(nbrs: torch.Tensor, graph: str = "directed"):
         rows = torch.div(key, n, rounding_mode="floor")
         counts = torch.bincount(rows, minlength=n)
         col, w = (key - rows * n).to(torch.int32), None
-    elif graph == "directed":
-        counts = valid.sum(dim=1)
-        col = nbrs[valid].to(torch.int32).contiguous()
-        w = None                                                   # rows stay in rank order: the library weighs them (Eq. 7)
     else:
-        raise ValueError("graph must be 'directed' or 'symmetric'")
+        counts = valid.sum(dim=1)
+        w = None                                                   # rows stay in rank order: the library weighs them (Eq. 7)
     row_ptr = torch.zeros(n + 1, dtype=torch.int64, device=nbrs.device)
     torch.cumsum(counts, 0, out=row_ptr[1:])
-    if int(row_ptr[-1]) >= 2 ** 31:
+    edges = int(row_ptr[-1])
+    if edges >= 2 ** 31:
         raise ValueError("edge count does not fit int32 offsets")
+    if graph == "directed":                                        # (whole lists, the usual case, need no picking)
+        col = nbrs.to(torch.int32, copy=True).reshape(-1) if edges == n * k else nbrs[valid].to(torch.int32).contiguous()
     return row_ptr.to(torch.int32), col, w
 
 
@@ -74,9 +76,13 @@ def project(X: torch.Tensor, n_clusters: int, k: int = 15, n_epochs: int = 200, 
     else:
         raise ValueError("kmeans_start must be 'lsh' or 'sample'")
     _, labels, km_iters, inertia = timed("kmeans", lambda: kmeans_lloyd(X, start, kmeans_iters, device=device))
-    used, labels = torch.unique(labels, return_inverse=True)
-    labels = labels.to(torch.int32)
-    R = int(used.numel())
+    # clusters in use, numbered in order (a mark a cluster and a running count: no sort of the labels)
+    used = torch.zeros(n_clusters, dtype=torch.int32, device=X.device)
+    used.index_fill_(0, labels.long(), 1)
+    number = torch.cumsum(used, 0, dtype=torch.int32)
+    R = int(number[-1])
+    if R < n_clusters:
+        labels = (number - 1)[labels.long()]
     nbrs = timed("knn", lambda: knn_in_clusters(X, labels, R, k, device=device))
     row_ptr, col, w = timed("graph", lambda: neighbour_lists_to_csr(nbrs, graph))
     if init == "pca":
