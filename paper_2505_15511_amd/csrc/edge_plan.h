@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #if defined(__HIPCC__)
 #define NOMAD_HOST_DEVICE __host__ __device__
 #else
@@ -286,18 +288,42 @@ inline ExchangePlan plan_exchange(const EdgePlanRequest& q, const EdgePlan& p) {
 //   Not with sampled means beyond 256 tiles: what a block's slots are made for are negatives, few of which get a force there, and the tiles look for their runs in many
 //   blocks.  400 k 0.78 to 0.85, 1 M 0.90, 2 M 0.97, 2.5 M (s = 8) 1.03, 3 M (s = 5) 1.01, 5 M (s = 2) 1.02.
 //   Nor where two workgroups do not fit a compute unit's LDS (77 KB a workgroup: 1.5 times as long as 46 KB with the same lanes in flight).
+//   Tiles: one workgroup of k_tile_sums each, so as many as fill the compute units, of any number of points of eight bits (powers of two are tried first: kept where the
+//   last round is 84 % full).  Whole epochs, powers of two over that: 147 tiles of 256 (300 k points) 1.04, 159 1.04, 196 1.03, in 64 sub-steps 306 of 512 1.06, groups of 150 k 1.07,
+//   367 of 512 1.06; 220 of 256 0.99, 733 of 768 0.99.  Twice as many tiles: 0.87 to 1.02 (runs half as long), but 1.15 in short sub-steps.
 //   Lanes of a segment (two references each): half of the mean run, us at 100 k points, s = 5, runs of 31 / 24 / 16: 8 lanes 63, 60, 52, 16 lanes 45, 39, 41, 32 lanes 36, 41, 57.
 //   With groups a block's references lie in the tiles of its own clusters, whatever the mean: 6 M points, s = 2, 8 / 16 / 32 lanes 1.41 / 1.09 / 1.02 ms.
 struct RunsPlan {
     bool use = false;
     int sums_lanes = 32;
+    uint32_t n_tiles = 0, points = 0;   // of a tile: factor << shift
+    uint32_t factor = 0, magic = 0;     // points / factor = 2^shift; x / factor = the high word of x magic, where x factor < 2^32
+    int shift = 0;
 };
-inline RunsPlan plan_runs(const EdgePlanRequest& q, const EdgePlan& p) {
+NOMAD_HOST_DEVICE inline uint32_t runs_tile_of(uint32_t pt, int shift, uint32_t magic) {
+    const uint32_t x = pt >> shift;
+    return magic ? (uint32_t)(((uint64_t)x * magic) >> 32) : x;
+}
+inline RunsPlan plan_runs(const EdgePlanRequest& q, const EdgePlan& p, int compute_units = 256) {
     RunsPlan x;
     const bool records_asked = q.tune_edge_block || q.tune_wg_per_cu || q.tune_record_sort || q.tune_flush_rounds;
     if (q.s < 0 || q.s > 8 || q.E < 1 || q.pool_size || !p.bin_block || records_asked) return x;
-    x.use = p.sorted && 2 * runs_lds_bytes(q.s, p.n_bins) <= kMaxLdsBytes && !(q.far && p.n_bins > 256);
-    const double run = (double)runs_block_edges(q.s) * (q.s + 1) / p.n_bins;
+    const int64_t most = (int64_t)1 << kMaxTileBits, rounds = ((int64_t)p.n_bins + compute_units - 1) / compute_units;
+    const auto tiles_of = [&](int64_t points, uint32_t factor, int shift) {
+        x.points = (uint32_t)points; x.factor = factor; x.shift = shift;
+        x.magic = factor > 1 ? (uint32_t)(((uint64_t)1 << 32) / factor) + 1u : 0u;
+        x.n_tiles = (uint32_t)((q.n + points - 1) / points);
+    };
+    tiles_of((int64_t)1 << p.tile_bits, 1, p.tile_bits);
+    if (x.n_tiles < 0.84 * (double)(rounds * compute_units)) {   // the last round leaves many units without work: about as many tiles as there is room for
+        const int64_t want = std::min<int64_t>(most, (q.n + rounds * compute_units - 1) / (rounds * compute_units));
+        int shift = 0;
+        while ((want + ((int64_t)1 << shift) - 1) >> shift > 255) ++shift;
+        const int64_t factor = (want + ((int64_t)1 << shift) - 1) >> shift;
+        if (factor << shift <= most) tiles_of(factor << shift, (uint32_t)factor, shift);
+    }
+    x.use = p.sorted && 2 * runs_lds_bytes(q.s, x.n_tiles) <= kMaxLdsBytes && !(q.far && q.n > 256 * most);
+    const double run = (double)runs_block_edges(q.s) * (q.s + 1) / x.n_tiles;
     x.sums_lanes = q.grouped ? 32 : run < 12 ? 8 : run < 22 ? 16 : 32;
     return x;
 }

@@ -42,6 +42,8 @@ struct ExchangeArgs {
     uint32_t n_blocks, n_tiles;
     int tile_bits;
     uint32_t spare;          // first of the kExchangeSpare slots behind the last block's
+    uint32_t points, magic;  // k_edges_runs: points of a tile, runs_tile_of's numbers
+    int shift;
 };
 
 template <int S>

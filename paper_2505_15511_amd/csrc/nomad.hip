@@ -83,6 +83,7 @@ struct nomad_ctx {
     unsigned long long* small_sums = nullptr;
     bool exchange = false;          // the edge pass is the exchanged one (exchange_kernels.h)
     bool runs = false;              // the edge pass is the one that leaves its forces in runs (run_kernels.h); it shares the arrays of the exchange
+    RunsPlan run_tiles;
     float2* ex_rec = nullptr;
     uint16_t *ex_idx = nullptr, *ex_side = nullptr;
     uint32_t *ex_pos = nullptr, *ex_runs = nullptr;
@@ -423,6 +424,7 @@ ExchangeArgs exchange_args(const nomad_ctx* c, int64_t e_begin, int64_t e_end) {
     const int eb = c->runs ? runs_block_edges(c->cfg.n_neg) : exchange_block_edges(c->cfg.n_neg);
     x.n_blocks = (uint32_t)((e_end - e_begin + eb - 1) / eb);
     x.n_tiles = c->n_bins; x.tile_bits = c->tile_bits; x.spare = c->ex_spare;
+    x.points = c->run_tiles.points; x.magic = c->run_tiles.magic; x.shift = c->run_tiles.shift;
     return x;
 }
 
@@ -449,8 +451,8 @@ void launch_exchange_edges(nomad_ctx* c, const EdgeArgs& a, const ExchangeArgs& 
 }
 
 void launch_exchange_sums(nomad_ctx* c, const ExchangeArgs& x, float eta, int phase) {
-    const uint32_t points = 1u << c->tile_bits, slots = (uint32_t)(c->runs ? runs_slots(c->cfg.n_neg) : exchange_slots(c->cfg.n_neg));
-    launch_tile_sums(c, c->ex.sums_lanes, TileSums{x.rec, x.idx, x.runs, x.ghead, x.n_blocks, slots, x.n_tiles, points, points - 1u, x.spare}, eta, phase);
+    const uint32_t points = c->runs ? c->run_tiles.points : 1u << c->tile_bits, slots = (uint32_t)(c->runs ? runs_slots(c->cfg.n_neg) : exchange_slots(c->cfg.n_neg));
+    launch_tile_sums(c, c->ex.sums_lanes, TileSums{x.rec, x.idx, x.runs, x.ghead, x.n_blocks, slots, x.n_tiles, points, c->runs ? 0xFFFFu : points - 1u, x.spare}, eta, phase);
 }
 
 // ---- the edge pass that leaves its forces in runs
@@ -468,7 +470,7 @@ int prepare_runs(nomad_ctx* c) {
     hipError_t err = hipSuccess;
     const auto allow = [&](const void* k, size_t lds) { if (err == hipSuccess) err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); };
     with_runs_kernel(c, [&](auto kernel) { allow((const void*)kernel, runs_lds_bytes(c->cfg.n_neg, c->n_bins)); });
-    allow((const void*)tile_sums_kernel(c->ex.sums_lanes), (size_t)16 << c->tile_bits);
+    allow((const void*)tile_sums_kernel(c->ex.sums_lanes), (size_t)16 * c->run_tiles.points);
     HIP_TRY(c, err);
     return NOMAD_OK;
 }
@@ -930,11 +932,11 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 c->phases = 1;
             }
         }
-        const RunsPlan in_runs = edge_kind(c) != kAnyEdges && why.empty() ? plan_runs(want_plan, plan) : RunsPlan{};
+        const RunsPlan in_runs = edge_kind(c) != kAnyEdges && why.empty() ? plan_runs(want_plan, plan, compute_units) : RunsPlan{};
         if (in_runs.use && !c->exchange && !c->small_wg) {
             c->ex.sums_lanes = in_runs.sums_lanes;
-            c->n_bins = n_bins;
-            c->tile_bits = tile_bits;
+            c->n_bins = in_runs.n_tiles;
+            c->run_tiles = in_runs;
             c->runs = true;
             const int eb = runs_block_edges(s);
             c->phases = plan_record_phases(E, s, eb, c->tune_phases);
@@ -942,7 +944,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
             const size_t blocks = (size_t)((E + eb - 1) / eb + c->phases - 1) / c->phases + 1, slots = runs_slots(s) * blocks;
             c->ex_spare = (uint32_t)slots;
             bool ok = slots + kExchangeSpare < ((size_t)1 << 32) && dev_alloc(c, &c->ex_rec, slots + kExchangeSpare) == NOMAD_OK &&
-                      dev_alloc(c, &c->ex_idx, slots + kExchangeSpare) == NOMAD_OK && dev_alloc(c, &c->ex_runs, (size_t)n_bins * blocks) == NOMAD_OK &&
+                      dev_alloc(c, &c->ex_idx, slots + kExchangeSpare) == NOMAD_OK && dev_alloc(c, &c->ex_runs, (size_t)c->n_bins * blocks) == NOMAD_OK &&
                       dev_alloc(c, &c->head, (size_t)E) == NOMAD_OK && (c->phases == 1 || dev_alloc(c, &c->carry, (size_t)n * 2) == NOMAD_OK);
             ok = ok && prepare_runs(c) == NOMAD_OK;
             if (ok) {

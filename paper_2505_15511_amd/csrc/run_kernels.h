@@ -35,7 +35,6 @@ __global__ void __launch_bounds__(runs_lanes(S), runs_waves_per_simd(S)) k_edges
     __shared__ uint32_t wave_total[BS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t blk = blockIdx.x, T = X.n_tiles;
-    const int tb = X.tile_bits;
     const int64_t e0 = X.e_begin + (int64_t)blk * Shape::EB;
     EdgeFetch<S> f[R];
 #pragma unroll
@@ -77,7 +76,7 @@ __global__ void __launch_bounds__(runs_lanes(S), runs_waves_per_simd(S)) k_edges
     }
     lds_barrier();
     const auto point = [&](int r, int k) { return (uint32_t)(k == 0 ? f[r].j : k <= S ? f[r].m[k > 0 && k <= S ? k - 1 : 0] : f[r].i); };
-    uint32_t rank[R][S + 2];
+    uint32_t place[R][S + 2];   // tile | references of the block before it there << 16
     bool valid[R][S + 2];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -85,8 +84,11 @@ __global__ void __launch_bounds__(runs_lanes(S), runs_waves_per_simd(S)) k_edges
 #pragma unroll
         for (int k = 0; k < S + 2; ++k) {
             valid[r][k] = k > S ? on : f[r].has && (KIND != kFarEdges || k == 0 || f[r].m[k > 0 ? k - 1 : 0] >= 0);
-            rank[r][k] = 0u;
-            if (valid[r][k]) rank[r][k] = atomicAdd(&first[point(r, k) >> tb], 1u);
+            place[r][k] = 0u;
+            if (valid[r][k]) {
+                const uint32_t tile = runs_tile_of(point(r, k), X.shift, X.magic);
+                place[r][k] = tile | atomicAdd(&first[tile], 1u) << 16;
+            }
         }
     }
     lds_barrier();
@@ -94,10 +96,10 @@ __global__ void __launch_bounds__(runs_lanes(S), runs_waves_per_simd(S)) k_edges
     lds_barrier();
     BinArgs Q{};
     Q.ghead = X.ghead;
-    const auto put = [&](uint32_t pt, uint32_t behind, float x, float y) {
-        const uint32_t at = first[pt >> tb] + behind;
+    const auto put = [&](uint32_t pt, uint32_t where, float x, float y) {
+        const uint32_t tile = where & 0xFFFFu, at = first[tile] + (where >> 16);
         rec[at] = make_float2(x, y);
-        pts[at] = (uint16_t)pt;
+        pts[at] = (uint16_t)(pt - tile * X.points);
     };
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -108,12 +110,12 @@ __global__ void __launch_bounds__(runs_lanes(S), runs_waves_per_simd(S)) k_edges
             edge_math<S, false>(h, P.pe ? f[r].pe : h.inv_deg, f[r].tj, f[r].tm, o);
             hx = o.hx;
             hy = o.hy;
-            put((uint32_t)f[r].j, rank[r][0], -o.a * o.dx, -o.a * o.dy);
+            put((uint32_t)f[r].j, place[r][0], -o.a * o.dx, -o.a * o.dy);
 #pragma unroll
             for (int k = 0; k < S; ++k)
-                if (KIND != kFarEdges || valid[r][k + 1]) put((uint32_t)f[r].m[k], rank[r][k + 1], o.rx[k], o.ry[k]);
+                if (KIND != kFarEdges || valid[r][k + 1]) put((uint32_t)f[r].m[k], place[r][k + 1], o.rx[k], o.ry[k]);
         }
-        if (reduce_head_sums(Q, f[r].has, f[r].i, f[r].row.x, f[r].row.y, e0 + r * BS + tid, X.e_end, hx, hy)) put((uint32_t)f[r].i, rank[r][S + 1], hx, hy);
+        if (reduce_head_sums(Q, f[r].has, f[r].i, f[r].row.x, f[r].row.y, e0 + r * BS + tid, X.e_end, hx, hy)) put((uint32_t)f[r].i, place[r][S + 1], hx, hy);
     }
     lds_barrier();
     float4* const out_rec = (float4*)(X.rec + (size_t)blk * Shape::SLOTS);

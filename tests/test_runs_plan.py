@@ -21,9 +21,14 @@ int main(int argc, char** argv) {
     EdgePlan p = plan_edge_pass(q);
     fit_tiles(p, q, 256, true);
     const RunsPlan x = plan_runs(q, p);
-    printf("{\"use\": %d, \"sums\": %d, \"tiles\": %u, \"tile_bits\": %d, \"slots\": %zu, \"edges\": %d, \"lds\": %zu, \"sums_lds\": %zu, \"max_lds\": %zu}\n",
-           (int)x.use, x.sums_lanes, p.n_bins, p.tile_bits, runs_slots(q.s), runs_block_edges(q.s), runs_lds_bytes(q.s, p.n_bins),
-           ((size_t)16 << p.tile_bits) + (size_t)(kBinBlock / 64) * tile_sums_queue(x.sums_lanes) * 8, kMaxLdsBytes);
+    int split = (uint32_t)x.factor << x.shift == x.points && (int64_t)x.points * x.n_tiles >= q.n && (int64_t)x.points * (x.n_tiles - 1) < q.n;   // and every point in its tile
+    const int64_t step = q.n > 3000000 ? 997 : 1;
+    for (int64_t i = 0; i < q.n; i += step) split = split && runs_tile_of((uint32_t)i, x.shift, x.magic) == (uint32_t)(i / x.points);
+    for (int64_t t = 1; t < x.n_tiles; ++t)
+        split = split && runs_tile_of((uint32_t)(t * x.points), x.shift, x.magic) == (uint32_t)t && runs_tile_of((uint32_t)(t * x.points - 1), x.shift, x.magic) == (uint32_t)(t - 1);
+    printf("{\"use\": %d, \"sums\": %d, \"tiles\": %u, \"points\": %u, \"split\": %d, \"slots\": %zu, \"edges\": %d, \"lds\": %zu, \"sums_lds\": %zu, \"max_lds\": %zu}\n",
+           (int)x.use, x.sums_lanes, x.n_tiles, x.points, split, runs_slots(q.s), runs_block_edges(q.s), runs_lds_bytes(q.s, x.n_tiles),
+           (size_t)16 * x.points + (size_t)(kBinBlock / 64) * tile_sums_queue(x.sums_lanes) * 8, kMaxLdsBytes);
     return 0;
 }
 """
@@ -43,6 +48,11 @@ def planner(tmp_path_factory):
     return plan
 
 
+def test_tiles_fill_the_compute_units(planner):
+    assert [planner(n)["tiles"] for n in (100_000, 300_000, 600_000, 900_000)] == [256, 256, 256, 220]
+    assert [planner(n, s=2, grouped=1)["tiles"] for n in (3_000_000, 6_000_011)] == [510, 733]   # 184 x 32 points; 8,192
+
+
 def test_the_lines(planner):
     assert [planner(n)["use"] for n in (2, 100_000, 900_000)] == [1, 1, 1]
     assert planner(100_000, s=9)["use"] == 0 and planner(100_000, pool=1024)["use"] == 0 and planner(100_000, sort=1)["use"] == 0
@@ -53,9 +63,10 @@ def test_the_lines(planner):
 
 @pytest.mark.parametrize("s", range(9))
 def test_slots_and_lds(planner, s):
-    for n in (2, 5_000, 99_999, 2_000_000, 8_000_000, 30_000_000):
+    for n in (2, 257, 5_000, 40_961, 99_999, 300_000, 600_001, 1_400_000, 2_000_000, 2_200_000, 8_000_000, 30_000_000):
         p = planner(n, s=s, grouped=1)
         assert p["slots"] % 64 == 0 and p["slots"] >= p["edges"] * (s + 1) + p["edges"] // 32 and p["slots"] < 65_536
-        assert p["edges"] % 64 == 0 and p["tile_bits"] <= 16
+        assert p["edges"] % 64 == 0
         if p["use"]:
+            assert p["points"] <= 8192 and p["tiles"] < 65_536 and p["split"]
             assert 2 * p["lds"] <= p["max_lds"] and p["sums_lds"] <= p["max_lds"] and p["sums"] in (8, 16, 32)
