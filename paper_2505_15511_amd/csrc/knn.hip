@@ -547,7 +547,7 @@ extern "C" int nomad_kmeans_lsh_init(const float* X, int64_t n, int32_t d, int32
         constexpr int P = decltype(planes_of)::value;
         double* offset = table + (size_t)P * d;
         hipLaunchKernelGGL(k_lsh_table<P>, dim3(P), dim3(256), 0, st, dX, d, dP, dA, n_planes, table, offset);
-        hipLaunchKernelGGL(k_lsh_buckets<P>, dim3(blocks_of(n, 256)), dim3(256), 0, st, dX, n, d, dP, dA, (const double*)table, (const double*)offset,
+        hipLaunchKernelGGL(k_lsh_buckets<P>, dim3(blocks_of(n, 64)), dim3(256), 0, st, dX, n, d, dP, dA, (const double*)table, (const double*)offset,
                            n_planes, K, dB);
     };
     if (n_planes <= 8) buckets(std::integral_constant<int, 8>());

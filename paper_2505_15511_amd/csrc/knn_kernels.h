@@ -1311,12 +1311,12 @@ __global__ void __launch_bounds__(256) k_mean_ordered(const float* __restrict__ 
 
 // The start from a locality-sensitive hash: bit j of a point = [ sum_t h_{j,t} (x_t - a_{j,t}) > 0 ], a_j the anchor row of
 // plane j, the sum over t = 0..d-1 in order with difference, product and running sum each rounded once in float64;
-// bucket = floor(code K / 2^b).  One thread per point, one accumulator per plane.
+// bucket = floor(code K / 2^b).  Four threads per point, one accumulator per plane each.
 //
 // Only the sign of the sum counts, so it is taken from sum_t h_t x_t - sum_t h_t a_t with fused multiply-adds (a third of the
 // operations) wherever that lies outside both sums' roundings, (d + 4) 2^-53 (sum |h_t| |x_t| + sum |h_t| |a_t|) each at most; a point
-// on a plane or nearly so (its anchor) walks its row in the order above.  A workgroup's 256 rows come through LDS kLshCols
-// columns at a time: whole lines from memory, where a thread walking its own row took 2.1 ms for a million rows of 128.
+// on a plane or nearly so (its anchor) walks its row in the order above.  A workgroup's 64 rows come through LDS kLshCols
+// columns a wavefront at a time: whole lines from memory, where a thread walking its own row took 2.1 ms for a million rows of 128.
 // P: planes this instance has accumulators for.
 constexpr int kMaxPlanes = 30;
 constexpr int kLshCols = 16;
@@ -1347,9 +1347,14 @@ template <int P>
 __global__ void __launch_bounds__(256) k_lsh_buckets(const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ planes,
                                                      const int32_t* __restrict__ anchors, const double* __restrict__ normals,
                                                      const double* __restrict__ offset, int32_t b, int32_t K, int32_t* __restrict__ bucket) {
-    __shared__ float rows[256][kLshCols + 1];
-    const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + threadIdx.x;
-    const int lr = (int)threadIdx.x / kLshCols, lc = (int)threadIdx.x % kLshCols;   // loads: column lc of rows lr + 16 u
+    // 64 rows a workgroup; a wavefront takes sixteen columns of every 64 of them, and the four's sums are added at the end (they stand in any order: the bound is for
+    // that).  With 256 rows and all columns a workgroup, rows of 768 columns were 48 loads of a chain: 100,003 x 768 225 us, now 125; 1,000,000 x 128 142, now 112.
+    __shared__ float rows[4][64][kLshCols + 1];
+    __shared__ double sums[P][64];
+    __shared__ float bigs[64];
+    const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
+    const int lr = lane / kLshCols, lc = lane % kLshCols;   // loads: column lc of rows lr + 4 u
     double acc[P];
     float big = 0.f;
 #pragma unroll
@@ -1358,27 +1363,39 @@ __global__ void __launch_bounds__(256) k_lsh_buckets(const float* __restrict__ X
     const auto load = [&](int t0) {
 #pragma unroll
         for (int u = 0; u < kLshCols; ++u) {
-            const int64_t r = i0 + lr + (256 / kLshCols) * u;
+            const int64_t r = i0 + lr + (64 / kLshCols) * u;
             next[u] = r < n && t0 + lc < d ? X[r * d + t0 + lc] : 0.f;
         }
     };
-    load(0);
-    for (int t0 = 0; t0 < d; t0 += kLshCols) {
+    load(wave * kLshCols);
+    for (int t0 = wave * kLshCols; t0 < d; t0 += 4 * kLshCols) {
         const int cols = min(kLshCols, d - t0);
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");   // (the rows are the wavefront's own)
 #pragma unroll
-        for (int u = 0; u < kLshCols; ++u) rows[lr + (256 / kLshCols) * u][lc] = next[u];
-        __syncthreads();
-        if (t0 + kLshCols < d) load(t0 + kLshCols);
+        for (int u = 0; u < kLshCols; ++u) rows[wave][lr + (64 / kLshCols) * u][lc] = next[u];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        if (t0 + 4 * kLshCols < d) load(t0 + 4 * kLshCols);
 #pragma unroll 2
         for (int t = 0; t < cols; ++t) {
-            const float x = rows[threadIdx.x][t];
+            const float x = rows[wave][lane][t];
             const double* h = normals + (size_t)(t0 + t) * P;
             big = fmaxf(big, fabsf(x));
 #pragma unroll
             for (int j = 0; j < P; ++j) acc[j] = fma(h[j], (double)x, acc[j]);
         }
     }
+    for (int w = 3; w > 0; --w) {   // one wavefront after the other, the first one last
+        if (wave == w) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) sums[j][lane] = w == 3 ? acc[j] : sums[j][lane] + acc[j];
+            bigs[lane] = w == 3 ? big : fmaxf(bigs[lane], big);
+        }
+        __syncthreads();
+    }
+    if (wave > 0) return;
+#pragma unroll
+    for (int j = 0; j < P; ++j) acc[j] += sums[j][lane];
+    big = fmaxf(big, bigs[lane]);
     if (i >= n) return;
     uint64_t code = 0;
     uint32_t open = 0;
