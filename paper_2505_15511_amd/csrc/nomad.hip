@@ -308,6 +308,28 @@ int edge_kind(const nomad_ctx* c) {
     return c->gmembers ? kAnyEdges : kGroupedEdges;
 }
 
+// The loss terms; returns how many partial sums they leave.  A position a lane where the heads of positions are kept, the negatives are drawn one by one and the
+// embedding fits one L2: beyond that the gathers bound either kernel and the heads are four bytes a position more.  Whole calls, sixteen lanes a row -> a position a
+// lane, us: 2,000 points 19.2 -> 17.5, 100,000 92.9 -> 86 (s = 2 56.5 -> 52.0, s = 8 124.5 -> 117.8), 300,000 (s = 2) 89.4 -> 76.1, 500,000 in groups 338 -> 339, with sampled
+// means 384 -> 372; not taken there: 1,000,000 687 -> 711, 3,000,000 (s = 8) 8,583 -> 8,721, 5,000,000 13,093 -> 13,578.  As many workgroups as fit at once.
+constexpr int64_t kLossPoints = (int64_t)1 << 19;   // 4 MB of embedding
+uint32_t launch_loss(nomad_ctx* c, const EdgeArgs& a) {
+    const int kind = edge_kind(c);
+    const int64_t blocks = (c->E + kLossLanes - 1) / kLossLanes;
+    if (!c->head || c->n > kLossPoints || kind == kAnyEdges || c->cfg.n_neg < 1 || c->cfg.n_neg > 8 || c->E < 1) {
+        launch_edges<kModeLoss>(c, a);
+        return c->edge_grid;
+    }
+    const uint32_t grid = (uint32_t)std::min<int64_t>(std::min<int64_t>(c->edge_grid, 2048), (blocks + 7) & ~(int64_t)7);   // (edge_grid: a multiple of eight)
+    const auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kLossLanes), 0, c->stream, a, c->head, c->E); };
+    switch (c->cfg.n_neg) {
+#define NOMAD_CASE(S) case S: launch(kind == kPlainEdges ? k_edges_loss<S, kPlainEdges> : kind == kGroupedEdges ? k_edges_loss<S, kGroupedEdges> : k_edges_loss<S, kFarEdges>); break;
+        NOMAD_CASE(1) NOMAD_CASE(2) NOMAD_CASE(3) NOMAD_CASE(4) NOMAD_CASE(5) NOMAD_CASE(6) NOMAD_CASE(7) NOMAD_CASE(8)
+#undef NOMAD_CASE
+    }
+    return grid;
+}
+
 // Calls `fn(kernel)` with the edge-pass kernel that matches the context: number of negatives, sampler, launch shape.
 using EdgePassKernel = void (*)(const EdgeArgs, const BinArgs);
 
@@ -1179,8 +1201,8 @@ int nomad_loss(nomad_ctx* c, int32_t t_sample, double* out_host) {
     run_mean_field(c, 0, c->n);
     const EdgeArgs a = edge_args(c, (uint32_t)t_sample);
     { Timed tm(c, NOMAD_K_LOSS);
-      launch_edges<kModeLoss>(c, a);
-      hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(kLossBlock), 0, c->stream, c->loss_partial, c->edge_grid, 1.0 / (double)c->n,
+      const uint32_t partials = launch_loss(c, a);
+      hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(kLossBlock), 0, c->stream, c->loss_partial, partials, 1.0 / (double)c->n,
                          (double*)c->loss_out.word()); }
     HIP_TRY(c, hipGetLastError());
     rc = finish(c);
