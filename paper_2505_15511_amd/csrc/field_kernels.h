@@ -1,13 +1,17 @@
 // Device kernels of the mean-field sums (K2) by interpolation, for problems of many heads and cells.
 //
 // A(theta) = sum_r p_r q(theta, mu_r) and B(theta) = sum_r p_r q^2 (theta - mu_r) over all cells are smooth functions of the plane: q = 1 / (1 + d^2) has no pole
-// nearer than 1 to any point, wherever the cells lie.  On a square of side 1 the interpolant of degree 15 in either coordinate at the Chebyshev nodes is within
-// 4e-10 (A) and 2e-9 (B) of every term of unit mass, a hundredth of float32's rounding, so the sums need the n |R| kernels of k_mean_field only at 256 nodes of every
-// square that has heads in it, and of a head's own group.  Everything here is float64 (its rate is float32's): the results are the float64 sums to within
-// that bound, rounded once, where sums in float32 carry three to five roundings.
+// nearer than 1 to any point, wherever the cells lie.  On a square of side 5/8 the interpolant of degree 15 in either coordinate at the Chebyshev nodes is within
+// 3.3e-13 (A) and 1.5e-12 (B) of every term of unit mass, so the sums need the n |R| kernels of k_mean_field only at 256 nodes of every square that has heads in it, and of a
+// head's own group.  Everything here is float64 (its rate is float32's).
 //
-//   k_field_count   heads of every square (squares are centred on whole numbers, so that an embedding about the origin begins inside one)
-//   k_field_scan    first position of every square, the squares that have heads; whether the field is worth it, or k_mean_field does the work
+// The own group is in what is interpolated and is taken out at the head, so the interpolant's error on it stays: absolute in the own group's mass, while what is left can be as small as
+// the others are far.  Hence squares of 5/8 (sides of 1: 3.2e-10 and 1.5e-9, which for half of the mass 20 away from the rest is 1e-5 of B where sums in float32 keep 3e-7; of 1/2: 5e-14,
+// and half as many squares again), and field_sound, which k_field_scan asks with the embedding's extent: where the error could be more than float32's rounding of any head's sum, k_mean_field
+// does the work.  The results are the float64 sums to within that, rounded once, where sums in float32 carry three to five roundings.
+//
+//   k_field_count   heads of every square (squares are centred on multiples of their side, so that an embedding about the origin begins inside one)
+//   k_field_scan    first position of every square, the squares that have heads; whether the field is exact enough and worth it, or k_mean_field does the work
 //   k_field_place   the heads in the order of their squares
 //   k_field_nodes   the sums at the nodes, the cells of a square cut among workgroups
 //   k_field_coefs   added up in a fixed order, to coefficients of Chebyshev polynomials
@@ -20,7 +24,7 @@
 
 namespace nomad {
 
-constexpr int kFieldSide = 64, kFieldSquares = kFieldSide * kFieldSide;   // coordinates from -32.5 to 31.5 (6 M points after 200 epochs: within 10, 279 squares)
+constexpr int kFieldSide = 102, kFieldSquares = kFieldSide * kFieldSide;   // coordinates within 31 (6 M points after 200 epochs: within 10)
 constexpr int kFieldNodes = 16, kFieldGrid = kFieldNodes * kFieldNodes;
 constexpr int kFieldUnits = kFieldMost;            // workgroups of k_field_nodes
 constexpr int kFieldBlock = 1024, kFieldPerLane = 16, kFieldSpan = kFieldBlock * kFieldPerLane;
@@ -42,8 +46,11 @@ struct Field {
 // the square of a point, or -1 outside of them (and for what is no number)
 __device__ __forceinline__ int32_t field_square(float2 t) {
     if (!(fabsf(t.x) < 31.0f && fabsf(t.y) < 31.0f)) return -1;
-    return ((int32_t)floorf(t.y + 0.5f) + kFieldSide / 2) * kFieldSide + (int32_t)floorf(t.x + 0.5f) + kFieldSide / 2;
+    constexpr float per = (float)(1.0 / kFieldEdge);   // (a point within a rounding of an edge may count to either square)
+    return ((int32_t)floorf(fmaf(t.y, per, 0.5f)) + kFieldSide / 2) * kFieldSide + (int32_t)floorf(fmaf(t.x, per, 0.5f)) + kFieldSide / 2;
 }
+// the coordinate of its centre, in either direction
+__device__ __forceinline__ double field_centre(int32_t k) { return kFieldEdge * (double)(k - kFieldSide / 2); }
 
 // one more of every lane's square in the workgroup's counters: the lane's rank; wavefronts that lie in one square (most do) add once
 __device__ __forceinline__ uint32_t field_rank(uint32_t* counts, int32_t sq, bool has) {
@@ -82,19 +89,51 @@ __global__ void __launch_bounds__(kFieldBlock) k_field_count(const float2* __res
 }
 
 // (one workgroup)
-__global__ void __launch_bounds__(1024) k_field_scan(int64_t heads, int32_t R, Field F) {
-    constexpr int kPer = kFieldSquares / 1024;
+__global__ void __launch_bounds__(1024) k_field_scan(const float4* __restrict__ cinfo, int64_t heads, int32_t R, double heaviest, Field F) {
+    constexpr int kPer = (kFieldSquares + 1023) / 1024;
     __shared__ uint32_t total[16], some[16];
+    __shared__ float box[16][4];
+    __shared__ int strays;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t c[kPer], own = 0u, has = 0u;
 #pragma unroll
     for (int x = 0; x < kPer; ++x) {
-        c[x] = F.count[tid * kPer + x];
+        c[x] = tid * kPer + x < kFieldSquares ? F.count[tid * kPer + x] : 0u;
         own += c[x];
         has += c[x] ? 1u : 0u;
     }
+    // how far apart a head and a cell can be: a box of all squares that have heads and of all cells
+    constexpr float kFar = 1e18f;
+    float most[4] = {-kFar, -kFar, -kFar, -kFar};   // -x, -y, x, y
+    bool stray = false;                             // a cell that is nowhere
+#pragma unroll
+    for (int x = 0; x < kPer; ++x) {
+        const float cx = (float)field_centre((tid * kPer + x) % kFieldSide), cy = (float)field_centre((tid * kPer + x) / kFieldSide), half = 0.5f * (float)kFieldEdge;
+        most[0] = c[x] ? fmaxf(most[0], half - cx) : most[0];
+        most[1] = c[x] ? fmaxf(most[1], half - cy) : most[1];
+        most[2] = c[x] ? fmaxf(most[2], half + cx) : most[2];
+        most[3] = c[x] ? fmaxf(most[3], half + cy) : most[3];
+    }
+    for (int32_t r = tid; r < R; r += 1024) {
+        const float4 cell = cinfo[r];
+        if (cell.z > 0.f) {
+            stray = stray || !(fabsf(cell.x) < kFar && fabsf(cell.y) < kFar);
+            most[0] = fmaxf(most[0], -cell.x);
+            most[1] = fmaxf(most[1], -cell.y);
+            most[2] = fmaxf(most[2], cell.x);
+            most[3] = fmaxf(most[3], cell.y);
+        }
+    }
+#pragma unroll
+    for (int w = 1; w < 64; w <<= 1)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) most[v] = fmaxf(most[v], __shfl_xor(most[v], w, 64));
+    if (tid == 0) strays = 0;
+    if (lane < 4) box[wave][lane] = lane == 0 ? most[0] : lane == 1 ? most[1] : lane == 2 ? most[2] : most[3];
     const uint32_t incl = wave_prefix(own), incl_some = wave_prefix(has);
     if (lane == 63) { total[wave] = incl; some[wave] = incl_some; }
+    __syncthreads();
+    if (stray) strays = 1;
     __syncthreads();
     uint32_t at = incl - own, k = incl_some - has, n_squares = 0u;
     for (int w = 0; w < 16; ++w) {
@@ -104,6 +143,7 @@ __global__ void __launch_bounds__(1024) k_field_scan(int64_t heads, int32_t R, F
 #pragma unroll
     for (int x = 0; x < kPer; ++x) {
         const uint32_t sq = (uint32_t)(tid * kPer + x);
+        if (sq >= (uint32_t)kFieldSquares) break;
         F.count[sq] = 0u;
         F.cursor[sq] = at;
         F.place[sq] = k;
@@ -112,7 +152,11 @@ __global__ void __launch_bounds__(1024) k_field_scan(int64_t heads, int32_t R, F
         k += c[x] ? 1u : 0u;
     }
     if (tid == 0) {
-        F.state->use = !F.state->outside && field_pays((double)heads, (double)R, (double)n_squares) ? 1u : 0u;
+        for (int w = 1; w < 16; ++w)
+            for (int v = 0; v < 4; ++v) box[0][v] = fmaxf(box[0][v], box[w][v]);
+        const double dx = (double)box[0][0] + (double)box[0][2], dy = (double)box[0][1] + (double)box[0][3];
+        const bool sound = !F.state->outside && !strays && field_sound(heaviest, sqrt(dx * dx + dy * dy));
+        F.state->use = sound && field_pays((double)heads, (double)R, (double)n_squares) ? 1u : 0u;
         F.state->n_squares = n_squares;
         F.state->chunks = max(1u, min((uint32_t)kFieldUnits / max(n_squares, 1u), (uint32_t)(R + 31) / 32u));
         F.state->outside = 0u;
@@ -156,10 +200,11 @@ __global__ void __launch_bounds__(kFieldGrid) k_field_nodes(const float4* __rest
     __shared__ float4 cells[kFieldGrid];
     const uint32_t chunks = F.state->chunks, units = F.state->n_squares * chunks;
     const int tid = threadIdx.x;
-    const double nx = 0.5 * cospi(((tid % kFieldNodes) + 0.5) / kFieldNodes), ny = 0.5 * cospi(((tid / kFieldNodes) + 0.5) / kFieldNodes);
+    const double nx = 0.5 * kFieldEdge * cospi(((tid % kFieldNodes) + 0.5) / kFieldNodes),
+                 ny = 0.5 * kFieldEdge * cospi(((tid / kFieldNodes) + 0.5) / kFieldNodes);
     for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
         const uint32_t sq = F.list[u / chunks], part = u % chunks;
-        const double x = nx + (double)((int32_t)(sq % kFieldSide) - kFieldSide / 2), y = ny + (double)((int32_t)(sq / kFieldSide) - kFieldSide / 2);
+        const double x = nx + field_centre((int32_t)(sq % kFieldSide)), y = ny + field_centre((int32_t)(sq / kFieldSide));
         const int32_t r0 = (int32_t)((int64_t)R * part / chunks), r1 = (int32_t)((int64_t)R * (part + 1) / chunks);
         double a = 0.0, bx = 0.0, by = 0.0;
         for (int32_t c0 = r0; c0 < r1; c0 += kFieldGrid) {
@@ -256,8 +301,8 @@ __global__ void __launch_bounds__(256) k_field_sums(const float2* __restrict__ t
             const float px = __shfl(t.x, from, 64), py = __shfl(t.y, from, 64);
             const int32_t psq = __shfl(sq, from, 64), pk = __shfl(k, from, 64);
             double tx[4], ty[4], sum[3] = {0.0, 0.0, 0.0};
-            field_chebyshev(2.0 * ((double)px - (double)(psq % kFieldSide - kFieldSide / 2)), g, tx);
-            field_chebyshev(2.0 * ((double)py - (double)(psq / kFieldSide - kFieldSide / 2)), g, ty);
+            field_chebyshev(2.0 / kFieldEdge * ((double)px - field_centre(psq % kFieldSide)), g, tx);
+            field_chebyshev(2.0 / kFieldEdge * ((double)py - field_centre(psq / kFieldSide)), g, ty);
             unsigned long long left = __ballot(true);
             while (left) {   // the squares of these heads, one after the other
                 const int32_t now = __builtin_amdgcn_readlane(pk, __ffsll((long long)left) - 1);

@@ -63,6 +63,7 @@ struct nomad_ctx {
     float2* gmean = nullptr;                 // [R] what every member of a cell adds to its gradient
     bool may_interpolate = false;            // the mean-field sums may come from the field (field_kernels.h), which looks at the embedding first
     Field field{};
+    double heaviest_group = 0.0;             // mass of the heaviest group, of 1
     // binned deterministic scatter
     bool binned = false;
     int n_wg = 0, bin_block = 1024;
@@ -523,7 +524,7 @@ int run_mean_field(nomad_ctx* c, int64_t row_begin, int64_t row_end) {
         const Field& f = c->field;
         const dim3 spans(blocks_for(heads, kFieldSpan)), lanes(kFieldBlock), grid(kFieldGrid);
         hipLaunchKernelGGL(k_field_count, spans, lanes, 0, c->stream, c->theta, row_begin, row_end, f);
-        hipLaunchKernelGGL(k_field_scan, dim3(1), dim3(1024), 0, c->stream, heads, c->R, f);
+        hipLaunchKernelGGL(k_field_scan, dim3(1), dim3(1024), 0, c->stream, c->cinfo, heads, c->R, c->heaviest_group, f);
         hipLaunchKernelGGL(k_field_place, spans, lanes, 0, c->stream, c->theta, row_begin, row_end, f);
         hipLaunchKernelGGL(k_field_nodes, dim3(kFieldUnits), grid, 0, c->stream, c->cinfo, c->R, f);
         hipLaunchKernelGGL(k_field_coefs, dim3(kFieldMost), grid, 0, c->stream, f);
@@ -851,7 +852,8 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         HTRY(hipMemcpy(c->group_slots, gslots.data(), sizeof(int2) * (size_t)R, hipMemcpyHostToDevice));
         double own = 0.0;   // cells of their own group, over all heads
         for (int32_t r = 0; r < R; ++r) own += (double)hcounts[r] * (double)gcells[hgroup[r]];
-        if (c->cfg.far_field == NOMAD_FAR_FIELD_EXACT && field_may((double)n / c->cfg.batches_per_epoch, (double)R, own / c->cfg.batches_per_epoch)) {
+        c->heaviest_group = (double)*std::max_element(gcount.begin(), gcount.end()) / (double)n;
+        if (c->cfg.far_field == NOMAD_FAR_FIELD_EXACT && field_may((double)n / c->cfg.batches_per_epoch, (double)R, own / c->cfg.batches_per_epoch, c->heaviest_group)) {
             Field& f = c->field;
             c->may_interpolate = dev_alloc(c, &f.state, 1) == NOMAD_OK && dev_alloc(c, &f.count, (size_t)kFieldSquares) == NOMAD_OK &&
                 dev_alloc(c, &f.cursor, (size_t)kFieldSquares) == NOMAD_OK && dev_alloc(c, &f.list, (size_t)kFieldMost) == NOMAD_OK &&
