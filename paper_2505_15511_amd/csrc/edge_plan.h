@@ -330,10 +330,10 @@ inline RunsPlan plan_runs(const EdgePlanRequest& q, const EdgePlan& p, int compu
 
 // Mean-field sums by interpolation (field_kernels.h) or cell by cell (k_mean_field).
 //   field_may, before anything is known of the embedding: enough work, and few cells in the heads' own groups, which are summed one by one either way.
-//   field_pays, on the device, from the squares that have heads: vector instructions, 16 a cell and node (float64 with its reciprocal), 1,100 a head (three
-//   polynomials of 256 terms, the place of the head in its square's list) against 9.8 a cell and head, with a third to spare.  Trained embeddings lie close: 6 M points in
-//   1,638 clusters after 200 epochs within 10 of the origin.  Mean-field sums, cell by cell -> field, ms: 6 M x 1,638 2.44 -> 0.32; 500 k x 1,050 over 85 squares
-//   0.13 -> 0.10; 1 M x 2,000 over 990 squares 0.50 -> 0.50 (its limit here); with an embedding it cannot use (looked at and left) 0.04 more.
+//   field_pays, on the device, from the squares that have heads: us, 1.4e-4 a square and cell (256 nodes), 4.5e-5 a head (three polynomials of 256 terms, the place of the head
+//   in its square's list) and 28 of launches against 2.45e-7 a cell and head, with a tenth to spare.  Mean-field sums, cell by cell -> field, us: 6 M x 1,638 in one square 2,364 -> 283, in
+//   1,290 2,356 -> 593; 1 M x 2,000 in 460 518 -> 194; 500 k x 1,050 in one 142 -> 60, in 275 142 -> 101; 250 k x 2,100 in 221 156 -> 117.  Trained embeddings lie close: 6 M points in 1,638
+//   clusters after 200 epochs within 10 of the origin.  An embedding it cannot use (looked at and left): 500 k x 1,050 145 -> 173.
 //   field_sound: whether interpolation is as exact as float32, whatever the place of a head.  heaviest: the mass of the heaviest group; diameter: the largest distance
 //   of a head and a cell.  The interpolant is off by up to kFieldError of a head's own group's mass, and what is left when that group is taken out is, in magnitudes,
 //   at least D / (1 + D^2)^2 of the others' mass; the error may be 2^-24 of that.  Half of the mass in one group: extents up to 31; nine tenths: 15; a tenth: 64; a
@@ -349,7 +349,7 @@ inline bool field_may(double heads, double cells, double own_cells_of_all_heads,
     return field_sound(heaviest, 2.0 * kFieldEdge) && cells >= 256 && heads * cells >= 5e8 && own_cells_of_all_heads <= heads * cells / 16;
 }
 NOMAD_HOST_DEVICE inline bool field_pays(double heads, double cells, double squares) {
-    return squares <= kFieldMost && 256.0 * 16.0 * squares * cells + 1100.0 * heads <= 0.67 * 9.8 * heads * cells;
+    return squares <= kFieldMost && 1.4e-4 * squares * cells + 4.5e-5 * heads + 28.0 <= 0.9 * 2.45e-7 * heads * cells;
 }
 
 }  // namespace nomad

@@ -12,12 +12,13 @@
 //
 //   k_field_count   heads of every square (squares are centred on multiples of their side, so that an embedding about the origin begins inside one)
 //   k_field_scan    first position of every square, the squares that have heads; whether the field is exact enough and worth it, or k_mean_field does the work
-//   k_field_place   the heads in the order of their squares
-//   k_field_nodes   the sums at the nodes, the cells of a square cut among workgroups
-//   k_field_coefs   added up in a fixed order, to coefficients of Chebyshev polynomials
+//   k_field_lay     the sums at the nodes, a square's cells cut among workgroups; the heads in the order of their squares
+//   k_field_coefs   added up, to coefficients of Chebyshev polynomials
 //   k_field_sums    the polynomials at the heads, less what the own group's cells have in them
 //
-// 6,000,011 heads and 1,638 cells: 2.44 -> 0.32 ms (250 us of it at the heads).  Largest error of A over its value, 1,000 cells, against float64: 5.3e-7 -> 6.0e-8, of B as a whole
+// An embedding that the field cannot use pays for the launches all the same: 500,000 heads and 1,050 cells 145 -> 173 us (178 with a launch for nodes and places each and longer spans of heads).
+//
+// 6,000,011 heads and 1,638 cells: 2.36 -> 0.28 ms in one square (220 us of it at the heads), 0.59 in 1,290.  Largest error of A over its value, 1,000 cells, against float64: 5.3e-7 -> 6.0e-8, of B as a whole
 // 1.4e-7 -> 2.6e-8.  The order of the heads within a square changes from run to run, what each gets does not.
 #pragma once
 #include "nomad_kernels.h"
@@ -25,21 +26,28 @@
 namespace nomad {
 
 constexpr int kFieldSide = 102, kFieldSquares = kFieldSide * kFieldSide;   // coordinates within 31 (6 M points after 200 epochs: within 10)
+constexpr int kFieldTable = 12 * 1024;             // entries of a table of squares: twelve a lane of k_field_scan
+static_assert(kFieldSquares <= kFieldTable, "");
 constexpr int kFieldNodes = 16, kFieldGrid = kFieldNodes * kFieldNodes;
-constexpr int kFieldUnits = kFieldMost;            // workgroups of k_field_nodes
-constexpr int kFieldBlock = 1024, kFieldPerLane = 16, kFieldSpan = kFieldBlock * kFieldPerLane;
+constexpr int kFieldParts = 2048;                  // workgroups' worth of nodes: parts of the cells of every square, where the squares are fewer (eight for every unit: they are not all as long)
+constexpr int kFieldUnits = kFieldMost > kFieldParts ? kFieldMost : kFieldParts;   // (square, part of the cells) pairs
+constexpr int kFieldPartCells = 256;               // cells a part has at least, where it is not all
+constexpr int kFieldCountBlock = 1024, kFieldLayBlock = 512, kFieldLayWaves = kFieldLayBlock / 64, kFieldNodeBlocks = 512;
+constexpr int kFieldFewHeads = 2 << 20, kFieldFew = 4, kFieldMany = 16;   // heads a lane of the counting pass has, below and above: workgroups for all units below
+inline int64_t field_count_span(int64_t heads) { return kFieldCountBlock * (heads < kFieldFewHeads ? kFieldFew : kFieldMany); }
+inline int64_t field_place_span(int64_t heads) { return kFieldLayBlock * (heads < kFieldFewHeads ? kFieldFew : kFieldMany); }
 constexpr int kFieldTurns = 4;                     // heads a lane of k_field_sums takes, one after the other
 
-struct FieldState { uint32_t use, n_squares, chunks, outside; };
+struct FieldState { uint32_t use, n_squares, chunks, outside; };   // outside: zero between epochs
 
 struct Field {
     FieldState* state;
-    uint32_t* count;       // [squares] heads; zero between epochs
-    uint32_t* cursor;      // [squares] next position of the square in `order`
+    uint32_t* count;       // [kFieldTable] heads of a square; zero between epochs
+    uint32_t* cursor;      // [kFieldTable] next position of the square in `order`
     uint32_t* list;        // [kFieldMost] squares that have heads, ascending
-    uint32_t* place;       // [squares] where a square is in the list
+    uint32_t* place;       // [kFieldTable] where a square is in the list
     uint32_t* order;       // [n] heads, square by square
-    double* partial;       // [kFieldUnits][3][kFieldGrid] sums of a part of the cells at the nodes
+    double* partial;       // [kFieldUnits][3][kFieldGrid] sums of a part of the cells at the nodes, (x, y) at 64 (x / 4) + 16 (x % 4) + y
     double* coefs;         // [kFieldMost][3][kFieldGrid] of T_l(x) T_m(y), at 64 (l / 4) + 16 (l % 4) + m: as the matrix instructions take them
 };
 
@@ -69,36 +77,43 @@ __device__ __forceinline__ uint32_t field_rank(uint32_t* counts, int32_t sq, boo
     return rank;
 }
 
-__global__ void __launch_bounds__(kFieldBlock) k_field_count(const float2* __restrict__ theta, int64_t i_begin, int64_t i_end, Field F) {
+template <int PER>
+__global__ void __launch_bounds__(kFieldCountBlock, 8) k_field_count(const float2* __restrict__ theta, int64_t i_begin, int64_t i_end, Field F) {
     __shared__ uint32_t counts[kFieldSquares];
-    for (int x = threadIdx.x; x < kFieldSquares; x += kFieldBlock) counts[x] = 0u;
+    for (int x = threadIdx.x; x < kFieldSquares; x += kFieldCountBlock) counts[x] = 0u;
     __syncthreads();
-    const int64_t i0 = i_begin + (int64_t)blockIdx.x * kFieldSpan;
+    const int64_t i0 = i_begin + (int64_t)blockIdx.x * (kFieldCountBlock * PER);
     bool outside = false;
 #pragma unroll 4
-    for (int u = 0; u < kFieldPerLane; ++u) {
-        const int64_t i = i0 + u * kFieldBlock + threadIdx.x;
+    for (int u = 0; u < PER; ++u) {
+        const int64_t i = i0 + u * kFieldCountBlock + threadIdx.x;
         const int32_t sq = i < i_end ? field_square(theta[i]) : -1;
         outside = outside || (i < i_end && sq < 0);
         field_rank(counts, sq, sq >= 0);
     }
     if (__any(outside) && (threadIdx.x & 63) == 0) F.state->outside = 1u;
     __syncthreads();
-    for (int x = threadIdx.x; x < kFieldSquares; x += kFieldBlock)
+    for (int x = threadIdx.x; x < kFieldSquares; x += kFieldCountBlock)
         if (counts[x]) atomicAdd(&F.count[x], counts[x]);
 }
 
 // (one workgroup)
 __global__ void __launch_bounds__(1024) k_field_scan(const float4* __restrict__ cinfo, int64_t heads, int32_t R, double heaviest, Field F) {
-    constexpr int kPer = (kFieldSquares + 1023) / 1024;
+    constexpr int kPer = kFieldTable / 1024;
     __shared__ uint32_t total[16], some[16];
     __shared__ float box[16][4];
     __shared__ int strays;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t c[kPer], own = 0u, has = 0u;
+    uint4* const mine = (uint4*)F.count + tid * (kPer / 4);
+#pragma unroll
+    for (int x = 0; x < kPer; x += 4) {
+        const uint4 four = mine[x / 4];
+        mine[x / 4] = make_uint4(0u, 0u, 0u, 0u);
+        c[x] = four.x; c[x + 1] = four.y; c[x + 2] = four.z; c[x + 3] = four.w;
+    }
 #pragma unroll
     for (int x = 0; x < kPer; ++x) {
-        c[x] = tid * kPer + x < kFieldSquares ? F.count[tid * kPer + x] : 0u;
         own += c[x];
         has += c[x] ? 1u : 0u;
     }
@@ -140,16 +155,19 @@ __global__ void __launch_bounds__(1024) k_field_scan(const float4* __restrict__ 
         if (w < wave) { at += total[w]; k += some[w]; }
         n_squares += some[w];
     }
+    uint32_t first[kPer], place[kPer];
 #pragma unroll
     for (int x = 0; x < kPer; ++x) {
-        const uint32_t sq = (uint32_t)(tid * kPer + x);
-        if (sq >= (uint32_t)kFieldSquares) break;
-        F.count[sq] = 0u;
-        F.cursor[sq] = at;
-        F.place[sq] = k;
-        if (c[x] && k < (uint32_t)kFieldMost) F.list[k] = sq;
+        first[x] = at;
+        place[x] = k;
+        if (c[x] && k < (uint32_t)kFieldMost) F.list[k] = (uint32_t)(tid * kPer + x);
         at += c[x];
         k += c[x] ? 1u : 0u;
+    }
+#pragma unroll
+    for (int x = 0; x < kPer; x += 4) {
+        ((uint4*)F.cursor)[tid * (kPer / 4) + x / 4] = make_uint4(first[x], first[x + 1], first[x + 2], first[x + 3]);
+        ((uint4*)F.place)[tid * (kPer / 4) + x / 4] = make_uint4(place[x], place[x + 1], place[x + 2], place[x + 3]);
     }
     if (tid == 0) {
         for (int w = 1; w < 16; ++w)
@@ -158,107 +176,132 @@ __global__ void __launch_bounds__(1024) k_field_scan(const float4* __restrict__ 
         const bool sound = !F.state->outside && !strays && field_sound(heaviest, sqrt(dx * dx + dy * dy));
         F.state->use = sound && field_pays((double)heads, (double)R, (double)n_squares) ? 1u : 0u;
         F.state->n_squares = n_squares;
-        F.state->chunks = max(1u, min((uint32_t)kFieldUnits / max(n_squares, 1u), (uint32_t)(R + 31) / 32u));
+        F.state->chunks = max(1u, min((uint32_t)kFieldParts / max(n_squares, 1u), (uint32_t)(R + kFieldPartCells - 1) / kFieldPartCells));
         F.state->outside = 0u;
     }
 }
 
-__global__ void __launch_bounds__(kFieldBlock) k_field_place(const float2* __restrict__ theta, int64_t i_begin, int64_t i_end, Field F) {
-    if (!F.state->use || F.state->n_squares == 1u) return;   // (one square: any order is the order)
-    __shared__ uint32_t counts[kFieldSquares];
-    for (int x = threadIdx.x; x < kFieldSquares; x += kFieldBlock) counts[x] = 0u;
-    __syncthreads();
-    const int64_t i0 = i_begin + (int64_t)blockIdx.x * kFieldSpan;
-    int32_t sq[kFieldPerLane];
-    uint32_t rank[kFieldPerLane];
+// 1 / t, to a unit in the last place or two of float64: the approximation of 2^-23 and better, refined once by a cubic step
+__device__ __forceinline__ double field_reciprocal(double t) {
+    const double q = __builtin_amdgcn_rcp(t), e = fma(-t, q, 1.0);
+    return fma(q, fma(e, e, e), q);
+}
+
+// The sums at the nodes: a workgroup takes a part of the cells for one square, a wavefront an eighth of those for all 256 nodes, four a lane ((x, y) with x = lane / 16
+// + 0, 4, 8, 12 and y = lane % 16), whose differences in y and whose reciprocal it shares: 13 float64 instructions a cell and node where a lane for each node had 20, and no barrier among the
+// cells.  Eight wavefronts' sums are added in LDS, in a fixed order.  250,003 heads in 221 squares, 2,100 cells: 61 us with the places, 1.9 times
+// what the instructions take (a lane for each node, with barriers: 85, and 18 for the places); 6 M heads in 1,290 squares, 1,638 cells 256.
+__device__ __forceinline__ void field_nodes(const float4* __restrict__ cinfo, int32_t R, const Field& F, double (&sums)[kFieldLayWaves / 2][12][64]) {
+    constexpr int N = kFieldNodes;
+    const uint32_t chunks = F.state->chunks, units = F.state->n_squares * chunks;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 15, g = lane >> 4;
+    double nx[4];
+    const double ny = 0.5 * kFieldEdge * cospi((col + 0.5) / N);
 #pragma unroll
-    for (int u = 0; u < kFieldPerLane; ++u) {
-        const int64_t i = i0 + u * kFieldBlock + threadIdx.x;
+    for (int s = 0; s < 4; ++s) nx[s] = 0.5 * kFieldEdge * cospi((4 * s + g + 0.5) / N);
+    for (uint32_t u = blockIdx.x; u < units; u += kFieldNodeBlocks) {
+        const uint32_t k = u / chunks, part = u % chunks, sq = F.list[k];
+        const double y = ny + field_centre((int32_t)(sq / kFieldSide)), x0 = field_centre((int32_t)(sq % kFieldSide));
+        const int64_t cuts = (int64_t)chunks * kFieldLayWaves, cut = (int64_t)part * kFieldLayWaves + wave;
+        const int32_t r0 = (int32_t)(R * cut / cuts), r1 = (int32_t)(R * (cut + 1) / cuts);
+        double v[3][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) v[0][s] = v[1][s] = v[2][s] = 0.0;
+#pragma unroll 2
+        for (int32_t r = r0; r < r1; ++r) {
+            const float4 c = cinfo[r];
+            const double dy = y - (double)c.y, y2 = fma(dy, dy, 1.0), from = x0 - (double)c.x, p = (double)c.z;
+            double dx[4], t[4], q[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) { dx[s] = nx[s] + from; t[s] = fma(dx[s], dx[s], y2); }
+            const double t01 = t[0] * t[1], t23 = t[2] * t[3], i = field_reciprocal(t01 * t23), i01 = i * t23, i23 = i * t01;
+            q[0] = i01 * t[1]; q[1] = i01 * t[0]; q[2] = i23 * t[3]; q[3] = i23 * t[2];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double w = p * q[s], w2 = w * q[s];
+                v[0][s] += w;
+                v[1][s] = fma(w2, dx[s], v[1][s]);
+                v[2][s] = fma(w2, dy, v[2][s]);
+            }
+        }
+#pragma unroll
+        for (int half = kFieldLayWaves / 2; half > 0; half >>= 1) {
+            if (wave >= half && wave < 2 * half)
+#pragma unroll
+                for (int m = 0; m < 12; ++m) sums[wave - half][m][lane] = v[m / 4][m % 4];
+            __syncthreads();
+            if (wave < half)
+#pragma unroll
+                for (int m = 0; m < 12; ++m) v[m / 4][m % 4] += sums[wave][m][lane];
+            __syncthreads();
+        }
+        if (wave > 0) continue;
+        double* const out = F.partial + (size_t)u * 3 * kFieldGrid + lane;
+#pragma unroll
+        for (int m = 0; m < 12; ++m) out[64 * m] = v[m / 4][m % 4];
+    }
+}
+
+template <int PER>
+__device__ __forceinline__ void field_place(const float2* __restrict__ theta, int64_t i_begin, int64_t i_end, uint32_t block, const Field& F, uint32_t (&counts)[kFieldSquares]) {
+    for (int x = threadIdx.x; x < kFieldSquares; x += kFieldLayBlock) counts[x] = 0u;
+    __syncthreads();
+    const int64_t i0 = i_begin + (int64_t)block * (kFieldLayBlock * PER);
+    int32_t sq[PER];
+    uint32_t rank[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t i = i0 + u * kFieldLayBlock + threadIdx.x;
         sq[u] = i < i_end ? field_square(theta[i]) : -1;
     }
 #pragma unroll
-    for (int u = 0; u < kFieldPerLane; ++u) rank[u] = field_rank(counts, sq[u], sq[u] >= 0);
+    for (int u = 0; u < PER; ++u) rank[u] = field_rank(counts, sq[u], sq[u] >= 0);
     __syncthreads();
-    for (int x = threadIdx.x; x < kFieldSquares; x += kFieldBlock)
+    for (int x = threadIdx.x; x < kFieldSquares; x += kFieldLayBlock)
         if (counts[x]) counts[x] = atomicAdd(&F.cursor[x], counts[x]);
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kFieldPerLane; ++u)
-        if (sq[u] >= 0) F.order[counts[sq[u]] + rank[u]] = (uint32_t)(i0 + u * kFieldBlock + threadIdx.x);
+    for (int u = 0; u < PER; ++u)
+        if (sq[u] >= 0) F.order[counts[sq[u]] + rank[u]] = (uint32_t)(i0 + u * kFieldLayBlock + threadIdx.x);
 }
 
-// q, to a unit in the last place or two of float64: the approximation of 2^-26, refined twice
-__device__ __forceinline__ double field_cauchy(double dx, double dy) {
-    const double t = fma(dx, dx, fma(dy, dy, 1.0));
-    double q = __builtin_amdgcn_rcp(t);
-    q = fma(q, fma(-t, q, 1.0), q);
-    return fma(q, fma(-t, q, 1.0), q);
-}
-
-__global__ void __launch_bounds__(kFieldGrid) k_field_nodes(const float4* __restrict__ cinfo, int32_t R, Field F) {
+// workgroups: kFieldNodeBlocks for the nodes, then one a span of heads to be placed
+template <int PER>
+__global__ void __launch_bounds__(kFieldLayBlock) k_field_lay(const float2* __restrict__ theta, const float4* __restrict__ cinfo, int64_t i_begin, int64_t i_end, int32_t R,
+                                                              Field F) {
     if (!F.state->use) return;
-    __shared__ float4 cells[kFieldGrid];
-    const uint32_t chunks = F.state->chunks, units = F.state->n_squares * chunks;
-    const int tid = threadIdx.x;
-    const double nx = 0.5 * kFieldEdge * cospi(((tid % kFieldNodes) + 0.5) / kFieldNodes),
-                 ny = 0.5 * kFieldEdge * cospi(((tid / kFieldNodes) + 0.5) / kFieldNodes);
-    for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
-        const uint32_t sq = F.list[u / chunks], part = u % chunks;
-        const double x = nx + field_centre((int32_t)(sq % kFieldSide)), y = ny + field_centre((int32_t)(sq / kFieldSide));
-        const int32_t r0 = (int32_t)((int64_t)R * part / chunks), r1 = (int32_t)((int64_t)R * (part + 1) / chunks);
-        double a = 0.0, bx = 0.0, by = 0.0;
-        for (int32_t c0 = r0; c0 < r1; c0 += kFieldGrid) {
-            __syncthreads();
-            if (c0 + tid < r1) cells[tid] = cinfo[c0 + tid];
-            __syncthreads();
-            const int32_t m = min(kFieldGrid, r1 - c0);
-#pragma unroll 4
-            for (int32_t r = 0; r < m; ++r) {
-                const float4 c = cells[r];
-                const double dx = x - (double)c.x, dy = y - (double)c.y, q = field_cauchy(dx, dy), w = (double)c.z * q, w2 = w * q;
-                a += w;
-                bx = fma(w2, dx, bx);
-                by = fma(w2, dy, by);
-            }
-        }
-        double* const out = F.partial + (size_t)u * 3 * kFieldGrid + tid;
-        out[0] = a;
-        out[kFieldGrid] = bx;
-        out[2 * kFieldGrid] = by;
+    __shared__ union { double sums[kFieldLayWaves / 2][12][64]; uint32_t counts[kFieldSquares]; } lds;
+    if (blockIdx.x < (uint32_t)kFieldNodeBlocks) field_nodes(cinfo, R, F, lds.sums);
+    else if (F.state->n_squares > 1u) field_place<PER>(theta, i_begin, i_end, blockIdx.x - (uint32_t)kFieldNodeBlocks, F, lds.counts);   // (one square: any order is the order)
+}
+
+// The parts of a square added up in a fixed order and turned to coefficients on the matrix cores, a square a wavefront: the operands lie as the lanes hold the sums, and the product
+// along x is the operand of the one along y.
+__global__ void __launch_bounds__(256) k_field_coefs(Field F) {
+    typedef double Acc __attribute__((ext_vector_type(4)));
+    const uint32_t chunks = F.state->chunks, k = blockIdx.x * 4u + (threadIdx.x >> 6);
+    if (!F.state->use || k >= F.state->n_squares) return;
+    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    double dct[4], v[3][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        dct[s] = (col ? 2.0 : 1.0) / kFieldNodes * cospi(col * (4 * s + g + 0.5) / kFieldNodes);
+        v[0][s] = v[1][s] = v[2][s] = 0.0;
     }
-}
-
-__global__ void __launch_bounds__(kFieldGrid) k_field_coefs(Field F) {
-    if (!F.state->use) return;
-    constexpr int N = kFieldNodes;
-    __shared__ double dct[N][N + 1], at_node[3][N][N + 1], half[3][N][N + 1];
-    const uint32_t chunks = F.state->chunks, n_squares = F.state->n_squares;
-    const int tid = threadIdx.x, row = tid / N, col = tid % N;
-    dct[row][col] = (row ? 2.0 : 1.0) / N * cospi(row * (col + 0.5) / N);
-    for (uint32_t k = blockIdx.x; k < n_squares; k += gridDim.x) {
-        __syncthreads();
+    const double* const from = F.partial + (size_t)k * chunks * 3 * kFieldGrid + lane;
+#pragma unroll 2
+    for (uint32_t c = 0; c < chunks; ++c)
 #pragma unroll
-        for (int v = 0; v < 3; ++v) {
-            const double* const from = F.partial + ((size_t)k * chunks * 3 + v) * kFieldGrid + tid;
-            double s = 0.0;
-#pragma unroll 8
-            for (uint32_t c = 0; c < chunks; ++c) s += from[(size_t)c * 3 * kFieldGrid];
-            at_node[v][row][col] = s;
-        }
-        __syncthreads();
+        for (int m = 0; m < 12; ++m) v[m / 4][m % 4] += from[(size_t)c * 3 * kFieldGrid + 64 * m];
 #pragma unroll
-        for (int v = 0; v < 3; ++v) {   // along x
-            double s = 0.0;
-            for (int j = 0; j < N; ++j) s = fma(dct[col][j], at_node[v][row][j], s);
-            half[v][row][col] = s;
-        }
-        __syncthreads();
+    for (int m = 0; m < 3; ++m) {
+        Acc h = {0.0, 0.0, 0.0, 0.0}, d = h;
 #pragma unroll
-        for (int v = 0; v < 3; ++v) {   // along y
-            double s = 0.0;
-            for (int j = 0; j < N; ++j) s = fma(dct[row][j], half[v][j][col], s);
-            F.coefs[((size_t)k * 3 + v) * kFieldGrid + 64 * (col / 4) + 16 * (col % 4) + row] = s;
-        }
+        for (int s = 0; s < 4; ++s) h = __builtin_amdgcn_mfma_f64_16x16x4f64(v[m][s], dct[s], h, 0, 0, 0);   // [y][T of x]
+#pragma unroll
+        for (int s = 0; s < 4; ++s) d = __builtin_amdgcn_mfma_f64_16x16x4f64(h[s], dct[s], d, 0, 0, 0);      // [T of x][T of y]
+#pragma unroll
+        for (int s = 0; s < 4; ++s) F.coefs[((size_t)k * 3 + m) * kFieldGrid + 64 * s + lane] = d[s];
     }
 }
 
@@ -335,7 +378,8 @@ __global__ void __launch_bounds__(256) k_field_sums(const float2* __restrict__ t
         }
         for (int32_t r = own.x; r < own.y; ++r) {   // less the own group's cells
             const float4 cell = cinfo[r];
-            const double dx = (double)t.x - (double)cell.x, dy = (double)t.y - (double)cell.y, q = field_cauchy(dx, dy), w = (double)cell.z * q, w2 = w * q;
+            const double dx = (double)t.x - (double)cell.x, dy = (double)t.y - (double)cell.y, q = field_reciprocal(fma(dx, dx, fma(dy, dy, 1.0))), w = (double)cell.z * q,
+                         w2 = w * q;
             a -= w;
             bx = fma(-w2, dx, bx);
             by = fma(-w2, dy, by);

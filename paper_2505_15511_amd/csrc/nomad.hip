@@ -522,12 +522,15 @@ int run_mean_field(nomad_ctx* c, int64_t row_begin, int64_t row_end) {
     if (c->may_interpolate) {   // by interpolation, where the embedding is as it has to be for that (k_field_scan): k_mean_field then has nothing to do
         const int64_t heads = row_end - row_begin;
         const Field& f = c->field;
-        const dim3 spans(blocks_for(heads, kFieldSpan)), lanes(kFieldBlock), grid(kFieldGrid);
-        hipLaunchKernelGGL(k_field_count, spans, lanes, 0, c->stream, c->theta, row_begin, row_end, f);
-        hipLaunchKernelGGL(k_field_scan, dim3(1), dim3(1024), 0, c->stream, c->cinfo, heads, c->R, c->heaviest_group, f);
-        hipLaunchKernelGGL(k_field_place, spans, lanes, 0, c->stream, c->theta, row_begin, row_end, f);
-        hipLaunchKernelGGL(k_field_nodes, dim3(kFieldUnits), grid, 0, c->stream, c->cinfo, c->R, f);
-        hipLaunchKernelGGL(k_field_coefs, dim3(kFieldMost), grid, 0, c->stream, f);
+        const uint32_t counting = blocks_for(heads, (int)field_count_span(heads)), placing = blocks_for(heads, (int)field_place_span(heads));
+        const auto launch = [&](auto count, auto lay) {
+            hipLaunchKernelGGL(count, dim3(counting), dim3(kFieldCountBlock), 0, c->stream, c->theta, row_begin, row_end, f);
+            hipLaunchKernelGGL(k_field_scan, dim3(1), dim3(1024), 0, c->stream, c->cinfo, heads, c->R, c->heaviest_group, f);
+            hipLaunchKernelGGL(lay, dim3(kFieldNodeBlocks + placing), dim3(kFieldLayBlock), 0, c->stream, c->theta, c->cinfo, row_begin, row_end, c->R, f);
+        };
+        if (heads < kFieldFewHeads) launch(k_field_count<kFieldFew>, k_field_lay<kFieldFew>);
+        else launch(k_field_count<kFieldMany>, k_field_lay<kFieldMany>);
+        hipLaunchKernelGGL(k_field_coefs, dim3((kFieldMost + 3) / 4), dim3(256), 0, c->stream, f);
         hipLaunchKernelGGL(k_field_sums, dim3(blocks_for(heads, 256 * kFieldTurns)), dim3(256), 0, c->stream, c->theta, c->cluster_of, c->group_of_cluster,
                            c->cinfo, c->group_slots, row_begin, row_end, f, (const double*)f.coefs, c->A, c->B);
     }
@@ -855,13 +858,13 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
         c->heaviest_group = (double)*std::max_element(gcount.begin(), gcount.end()) / (double)n;
         if (c->cfg.far_field == NOMAD_FAR_FIELD_EXACT && field_may((double)n / c->cfg.batches_per_epoch, (double)R, own / c->cfg.batches_per_epoch, c->heaviest_group)) {
             Field& f = c->field;
-            c->may_interpolate = dev_alloc(c, &f.state, 1) == NOMAD_OK && dev_alloc(c, &f.count, (size_t)kFieldSquares) == NOMAD_OK &&
-                dev_alloc(c, &f.cursor, (size_t)kFieldSquares) == NOMAD_OK && dev_alloc(c, &f.list, (size_t)kFieldMost) == NOMAD_OK &&
-                dev_alloc(c, &f.place, (size_t)kFieldSquares) == NOMAD_OK && dev_alloc(c, &f.order, (size_t)n) == NOMAD_OK &&
+            c->may_interpolate = dev_alloc(c, &f.state, 1) == NOMAD_OK && dev_alloc(c, &f.count, (size_t)kFieldTable) == NOMAD_OK &&
+                dev_alloc(c, &f.cursor, (size_t)kFieldTable) == NOMAD_OK && dev_alloc(c, &f.list, (size_t)kFieldMost) == NOMAD_OK &&
+                dev_alloc(c, &f.place, (size_t)kFieldTable) == NOMAD_OK && dev_alloc(c, &f.order, (size_t)n) == NOMAD_OK &&
                 dev_alloc(c, &f.partial, (size_t)kFieldUnits * 3 * kFieldGrid) == NOMAD_OK && dev_alloc(c, &f.coefs, (size_t)kFieldMost * 3 * kFieldGrid) == NOMAD_OK;
             if (c->may_interpolate) {
                 HTRY(hipMemset(f.state, 0, sizeof(FieldState)));
-                HTRY(hipMemset(f.count, 0, sizeof(uint32_t) * kFieldSquares));
+                HTRY(hipMemset(f.count, 0, sizeof(uint32_t) * kFieldTable));
                 HTRY(hipStreamSynchronize(nullptr));
             } else {   // cell by cell
                 (void)hipGetLastError();

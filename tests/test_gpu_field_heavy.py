@@ -5,7 +5,7 @@ import torch
 
 from paper_2505_15511_amd import Nomad
 from tests.test_gpu_exchange import graph
-from tests.test_gpu_field import in_float64
+from tests.test_gpu_field import in_float64, spread
 
 pytestmark = pytest.mark.gpu
 N, R = 1_000_003, 701
@@ -48,3 +48,24 @@ def test_errors_are_relative_to_what_is_summed(share, cells, away, corner, field
     assert ((A - wantA).abs() <= tol * wantA).all(), float(((A - wantA).abs() / wantA).max())
     assert ((B - wantB).norm(dim=1) <= tol * 2 ** 0.5 * sizeB).all(), float(((B - wantB).norm(dim=1) / sizeB).max())
     nm.close()
+
+
+def test_sub_steps_over_many_squares():
+    """Only points of the second half have edges: the second of two sub-steps, whose heads they are, has the gradient of one step over all heads."""
+    n, cells, E = 600_001, 4_000, 60_000
+    g = torch.Generator(device="cuda").manual_seed(1)
+    head = (n // 2 + torch.randint(0, n - n // 2, (E,), generator=g, device="cuda")).sort().values
+    col = ((head + 1 + torch.randint(0, n - 1, (E,), generator=g, device="cuda")) % n).to(torch.int32)
+    row_ptr = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    row_ptr[1:] = torch.cumsum(torch.bincount(head, minlength=n), 0).to(torch.int32)
+    cluster_of = (torch.arange(n, device="cuda") * cells // n).to(torch.int32)
+    th = spread(n, cluster_of.long(), cells, "clusters", 7)
+    got = []
+    for batches in (1, 2):
+        nm = Nomad(n, cells, 2, 5.0, 10, 0.0, 5, batches_per_epoch=batches)
+        nm.set_graph(row_ptr, col, None, cluster_of, torch.arange(cells, dtype=torch.int32, device="cuda"))
+        nm.set_embedding(th)
+        nm.epoch(0)
+        got.append(nm.get_gradient(device=True))
+        nm.close()
+    assert (got[0] - got[1]).abs().max() <= 2.0 ** -21 * got[0].abs().max()
