@@ -547,8 +547,13 @@ extern "C" int nomad_kmeans_lsh_init(const float* X, int64_t n, int32_t d, int32
         constexpr int P = decltype(planes_of)::value;
         double* offset = table + (size_t)P * d;
         hipLaunchKernelGGL(k_lsh_table<P>, dim3(P), dim3(256), 0, st, dX, d, dP, dA, n_planes, table, offset);
-        hipLaunchKernelGGL(k_lsh_buckets<P>, dim3(blocks_of(n, 64)), dim3(256), 0, st, dX, n, d, dP, dA, (const double*)table, (const double*)offset,
-                           n_planes, K, dB);
+        const auto launch = [&](auto kernel, int shared) {
+            hipLaunchKernelGGL(kernel, dim3(blocks_of(n, 256 / shared)), dim3(256), 0, st, dX, n, d, dP, dA, (const double*)table, (const double*)offset, n_planes, K, dB);
+        };
+        const int shared = lsh_shared(n, d, P);
+        if (shared == 1) launch(k_lsh_buckets<P, 1>, shared);
+        else if (shared == 2) launch(k_lsh_buckets<P, 2>, shared);
+        else launch(k_lsh_buckets<P, 4>, shared);
     };
     if (n_planes <= 8) buckets(std::integral_constant<int, 8>());
     else if (n_planes <= 16) buckets(std::integral_constant<int, 16>());

@@ -1311,13 +1311,15 @@ __global__ void __launch_bounds__(256) k_mean_ordered(const float* __restrict__ 
 
 // The start from a locality-sensitive hash: bit j of a point = [ sum_t h_{j,t} (x_t - a_{j,t}) > 0 ], a_j the anchor row of
 // plane j, the sum over t = 0..d-1 in order with difference, product and running sum each rounded once in float64;
-// bucket = floor(code K / 2^b).  Four threads per point, one accumulator per plane each.
+// bucket = floor(code K / 2^b).  One, two or four threads per point, one accumulator per plane each.
 //
 // Only the sign of the sum counts, so it is taken from sum_t h_t x_t - sum_t h_t a_t with fused multiply-adds (a third of the
 // operations) wherever that lies outside both sums' roundings, (d + 4) 2^-53 (sum |h_t| |x_t| + sum |h_t| |a_t|) each at most; a point
-// on a plane or nearly so (its anchor) walks its row in the order above.  A workgroup's 64 rows come through LDS kLshCols
-// columns a wavefront at a time: whole lines from memory, where a thread walking its own row took 2.1 ms for a million rows of 128.
+// on a plane or nearly so (its anchor) walks its row in the order above.  A wavefront's 64 rows come through LDS kLshCols
+// columns at a time: whole lines from memory, where a thread walking its own row took 2.1 ms for a million rows of 128.
 // P: planes this instance has accumulators for.
+// W: wavefronts of a workgroup that share 64 rows, each with kLshCols columns of every W kLshCols; their sums are added at the end (they stand in any order: the bound is
+// for that).
 constexpr int kMaxPlanes = 30;
 constexpr int kLshCols = 16;
 // Of every plane j: normals [d][P] as float64 (0 beyond the b planes), and offset [P][3] = sum h a, sum |h| |a|, sum |h|
@@ -1343,17 +1345,26 @@ __global__ void __launch_bounds__(256) k_lsh_table(const float* __restrict__ X, 
     __syncthreads();
     if (threadIdx.x < 3) offset[3 * j + threadIdx.x] = part[0][threadIdx.x] + part[1][threadIdx.x] + part[2][threadIdx.x] + part[3][threadIdx.x];
 }
-template <int P>
+// How many share.  A row is a chain of d / 16 loads to one wavefront, which few rows wait for; where the rows fill the chip, adding up a row's P sums costs more than it
+// saves, and of up to 16 columns there is nothing to share.  us, 1 / 2 / 4 wavefronts, P = 8: 100,000 rows of 32 11 / 9 / 9, of 64 22 / 14 / 12, of 768 210 / 134 / 112; 300,000 of 17
+// 10 / 11 / 15, of 32 15 / 14 / 17, of 256 90 / 70 / 66; 1,000,000 of 16 18 / 24 / 36, of 17 21 / 26 / 38, of 32 34 / 32 / 43, of 128 127 / 91 / 91.  P = 16: 100,000 of 64 23 / 18 / 17, of
+// 768 226 / 156 / 149, 300,000 of 17 15 / 18 / 26, of 64 32 / 29 / 32, of 256 121 / 95 / 93, 1,000,000 of 64 70 / 76 / 95, of 128 130 / 128 / 149.  P = 32: 100,000 of 17
+// 15 / 18 / 22, of 128 66 / 57 / 51, 300,000 of 64 53 / 51 / 58, of 256 224 / 191 / 175, 1,000,000 of 64 119 / 130 / 172, of 128 296 / 288 / 287.
+inline int lsh_shared(int64_t n, int32_t d, int P) {
+    const double fill = (double)n * P / (double)(1 << 21);
+    const int two = fill <= 1.0 ? kLshCols + 1 : fill <= 4.0 ? 2 * kLshCols : 7 * kLshCols, four = fill <= 0.5 ? 2 * kLshCols + 1 : fill <= 1.0 ? 4 * kLshCols : 10 * kLshCols;
+    return d < two ? 1 : d < four ? 2 : 4;
+}
+template <int P, int W>
 __global__ void __launch_bounds__(256) k_lsh_buckets(const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ planes,
                                                      const int32_t* __restrict__ anchors, const double* __restrict__ normals,
                                                      const double* __restrict__ offset, int32_t b, int32_t K, int32_t* __restrict__ bucket) {
-    // 64 rows a workgroup; a wavefront takes sixteen columns of every 64 of them, and the four's sums are added at the end (they stand in any order: the bound is for
-    // that).  With 256 rows and all columns a workgroup, rows of 768 columns were 48 loads of a chain: 100,003 x 768 225 us, now 125; 1,000,000 x 128 142, now 112.
+    constexpr int kSets = 4 / W;
     __shared__ float rows[4][64][kLshCols + 1];
-    __shared__ double sums[P][64];
-    __shared__ float bigs[64];
-    const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
+    __shared__ double sums[kSets][W > 1 ? P : 1][64];
+    __shared__ float bigs[kSets][64];
+    const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), part = wave % W, set = wave / W;
+    const int64_t i0 = ((int64_t)blockIdx.x * kSets + set) * 64, i = i0 + lane;
     const int lr = lane / kLshCols, lc = lane % kLshCols;   // loads: column lc of rows lr + 4 u
     double acc[P];
     float big = 0.f;
@@ -1367,14 +1378,14 @@ __global__ void __launch_bounds__(256) k_lsh_buckets(const float* __restrict__ X
             next[u] = r < n && t0 + lc < d ? X[r * d + t0 + lc] : 0.f;
         }
     };
-    load(wave * kLshCols);
-    for (int t0 = wave * kLshCols; t0 < d; t0 += 4 * kLshCols) {
+    load(part * kLshCols);
+    for (int t0 = part * kLshCols; t0 < d; t0 += W * kLshCols) {
         const int cols = min(kLshCols, d - t0);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");   // (the rows are the wavefront's own)
 #pragma unroll
         for (int u = 0; u < kLshCols; ++u) rows[wave][lr + (64 / kLshCols) * u][lc] = next[u];
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-        if (t0 + 4 * kLshCols < d) load(t0 + 4 * kLshCols);
+        if (t0 + W * kLshCols < d) load(t0 + W * kLshCols);
 #pragma unroll 2
         for (int t = 0; t < cols; ++t) {
             const float x = rows[wave][lane][t];
@@ -1384,18 +1395,20 @@ __global__ void __launch_bounds__(256) k_lsh_buckets(const float* __restrict__ X
             for (int j = 0; j < P; ++j) acc[j] = fma(h[j], (double)x, acc[j]);
         }
     }
-    for (int w = 3; w > 0; --w) {   // one wavefront after the other, the first one last
-        if (wave == w) {
+    if constexpr (W > 1) {
+        for (int w = W - 1; w > 0; --w) {   // one wavefront after the other, the first one last
+            if (part == w) {
 #pragma unroll
-            for (int j = 0; j < P; ++j) sums[j][lane] = w == 3 ? acc[j] : sums[j][lane] + acc[j];
-            bigs[lane] = w == 3 ? big : fmaxf(bigs[lane], big);
+                for (int j = 0; j < P; ++j) sums[set][j][lane] = w == W - 1 ? acc[j] : sums[set][j][lane] + acc[j];
+                bigs[set][lane] = w == W - 1 ? big : fmaxf(bigs[set][lane], big);
+            }
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    if (wave > 0) return;
+        if (part > 0) return;
 #pragma unroll
-    for (int j = 0; j < P; ++j) acc[j] += sums[j][lane];
-    big = fmaxf(big, bigs[lane]);
+        for (int j = 0; j < P; ++j) acc[j] += sums[set][j][lane];
+        big = fmaxf(big, bigs[set][lane]);
+    }
     if (i >= n) return;
     uint64_t code = 0;
     uint32_t open = 0;
