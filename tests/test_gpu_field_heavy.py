@@ -69,3 +69,26 @@ def test_sub_steps_over_many_squares():
         got.append(nm.get_gradient(device=True))
         nm.close()
     assert (got[0] - got[1]).abs().max() <= 2.0 ** -21 * got[0].abs().max()
+
+
+@pytest.mark.parametrize("size", [1e-4, 1e-3, 1e-2])
+def test_a_small_embedding_off_the_centre_of_its_square(size):
+    """Heads and cells so close that every B is a difference of nearby points: as exact as the sums cell by cell."""
+    n, cells = 1_000_003, 600
+    g = torch.Generator(device="cuda").manual_seed(4)
+    cluster_of = (torch.arange(n, device="cuda") * cells // n).to(torch.int32)
+    groups = torch.arange(cells, device="cuda")
+    th = size * (torch.randn(n, 2, generator=g, device="cuda") + torch.randn(cells, 2, generator=g, device="cuda")[cluster_of.long()]) + torch.tensor([0.21, 2.9], device="cuda")
+    nm = Nomad(n, cells, 2, 5.0, 10, 1.0, 5)
+    row_ptr, col, _ = graph(n, 60_000, 7)
+    nm.set_graph(row_ptr, col, None, cluster_of, groups.to(torch.int32))
+    nm.set_embedding(th)
+    heads = torch.randint(0, n, (3_000,), generator=torch.Generator().manual_seed(3)).cuda()
+    mu, counts = (torch.as_tensor(v).cuda() for v in nm.get_means())
+    B = torch.as_tensor(nm.get_mean_field()[1]).cuda()[heads].double()
+    _, wantB = in_float64(th, mu, counts, cluster_of.long(), groups, heads)
+    d = th[heads].double()[:, None, :] - mu.double()[None]
+    p = (counts.double() / n).float().double() * (cluster_of.long()[heads][:, None] != groups[None])
+    sizeB = (p * d.norm(dim=-1) / (1.0 + (d ** 2).sum(-1)) ** 2).sum(1)
+    assert ((B - wantB).norm(dim=1) <= 2.0 ** -23 * 2 ** 0.5 * sizeB).all(), float(((B - wantB).norm(dim=1) / sizeB).max())
+    nm.close()
