@@ -264,7 +264,8 @@ int nomad_scatter_path(const nomad_ctx* ctx);
 
 /* Which edge pass nomad_epoch runs after nomad_set_graph (0 before it):
  *   NOMAD_EDGES_ROWS      a group of lanes per row, global atomics (NOMAD_PATH_ATOMIC_FP32, NOMAD_PATH_FIXED_ATOMICS)
- *   NOMAD_EDGES_RECORDS   an edge per lane, forces as records by tile (NOMAD_PATH_BINNED)
+ *   NOMAD_EDGES_RECORDS   an edge per lane, forces sorted by tile (NOMAD_PATH_BINNED): in runs, a block's of edges by tile, or as records
+ *                         in chains; nomad_edges_in_runs tells which, the bits are the same
  *   NOMAD_EDGES_POOLED    the pooled samplers' own (NOMAD_PATH_BINNED_POOLED)
  *   NOMAD_EDGES_EXCHANGED embedding rows and forces exchanged tile by tile (NOMAD_PATH_BINNED, the same bits as records)
  *   NOMAD_EDGES_LDS_SUMS  the forces of a small embedding summed in LDS (NOMAD_PATH_BINNED, the same bits as records)
@@ -276,6 +277,10 @@ int nomad_scatter_path(const nomad_ctx* ctx);
 #define NOMAD_EDGES_EXCHANGED 4
 #define NOMAD_EDGES_LDS_SUMS 5
 int nomad_edge_pass(const nomad_ctx* ctx);
+
+/* 1 if the edge pass leaves its forces in runs (the library's choice for sorted forces without a knob of nomad_tune that shapes
+ * records), 0 if not, and before nomad_set_graph. */
+int nomad_edges_in_runs(const nomad_ctx* ctx);
 
 /* Device memory the context holds, in bytes (graph, embedding, work space; 0 before nomad_set_graph).  Blocks taken over
  * from earlier contexts and calls count at their full size, up to half as large again (and 64 KB) as what was needed. */
@@ -290,16 +295,18 @@ int nomad_release_memory(void);
 /*
  * Launch-shape knobs for experiments and tests; results do not depend on them beyond rounding order (every setting
  * is reproducible run to run).  Call between nomad_create and nomad_set_graph (NOMAD_E_ORDER afterwards).
- *   NOMAD_TUNE_EDGE_BLOCK      lanes per workgroup of the binned edge pass: 1024 (default) or 512
- *   NOMAD_TUNE_WORKGROUPS_PER_CU persistent workgroups per compute unit, 1..8 (default 1; 2 with 512 lanes)
+ * EDGE_BLOCK, WORKGROUPS_PER_CU, RECORD_SORT and FLUSH_ROUNDS shape the edge pass that leaves records in chains and choose it over the
+ * faster ones (sums in LDS, runs, exchange): any value asks for it, 0 (where it is allowed) or no call leaves the choice to the library.
+ *   NOMAD_TUNE_EDGE_BLOCK      lanes per workgroup of the binned edge pass: 1024 or 512
+ *   NOMAD_TUNE_WORKGROUPS_PER_CU persistent workgroups per compute unit, 1..8 (unless set: 1; 2 with 512 lanes)
  *   NOMAD_TUNE_SCATTER_PATH    0 (default: the fastest path that fits) or NOMAD_PATH_FIXED_ATOMICS to force the fallback
  *   NOMAD_TUNE_POOL_KERNEL     1 (default) or 0: run the pooled samplers on the general kernels
  *   NOMAD_TUNE_RECORD_PHASES   0 (default: chosen from the record volume) or 1..64: the edge pass of an epoch runs in
  *                              this many phases over ranges of CSR positions, each followed by the accumulation of its
  *                              records, so that the record pool holds one phase at a time
- *   NOMAD_TUNE_RECORD_SORT     0 (default: sorted unless there are more tiles than a round has records), 1: a round's
- *                              records are counting-sorted by tile in LDS and written by consecutive lanes, 2: every
- *                              lane writes its own records
+ *   NOMAD_TUNE_RECORD_SORT     0 (default: the library's choice; records are sorted unless there are more tiles than a round has
+ *                              records), 1: a round's records are counting-sorted by tile in LDS and written by consecutive
+ *                              lanes, 2: every lane writes its own records
  *   NOMAD_TUNE_FLUSH_ROUNDS    0 (default: 2), 1 or 2: rounds of 1024 positions the unsorted form takes between two
  *                              flushes of its records (1024-lane workgroups only)
  *   NOMAD_TUNE_EXCHANGE        0 (default: large embeddings of one population with i.i.d. negatives and no short sub-steps, unless a

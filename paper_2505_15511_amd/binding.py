@@ -23,7 +23,7 @@ ERRORS = {-1: "NOMAD_E_INVALID_ARG", -2: "NOMAD_E_BAD_GRAPH", -3: "NOMAD_E_ORDER
 
 EXPORTS = ["nomad_create", "nomad_destroy", "nomad_set_graph", "nomad_set_embedding", "nomad_epoch", "nomad_loss",
            "nomad_get_embedding", "nomad_get_gradient", "nomad_get_negatives", "nomad_get_means",
-           "nomad_get_mean_field", "nomad_num_edges", "nomad_scatter_path", "nomad_edge_pass", "nomad_device_bytes", "nomad_release_memory", "nomad_tune", "nomad_profile", "nomad_profile_read", "nomad_last_error",
+           "nomad_get_mean_field", "nomad_num_edges", "nomad_scatter_path", "nomad_edge_pass", "nomad_edges_in_runs", "nomad_device_bytes", "nomad_release_memory", "nomad_tune", "nomad_profile", "nomad_profile_read", "nomad_last_error",
            "nomad_copy_probe", "nomad_gather_probe", "nomad_scatter_probe", "nomad_knn_in_clusters", "nomad_kmeans_lloyd", "nomad_neighbourhood_preservation",
            "nomad_random_triplet_accuracy", "nomad_random_triplet_accuracy_noalloc", "nomad_pca_init", "nomad_kmeans_lsh_init"]
 
@@ -82,6 +82,7 @@ def load_library():
     lib.nomad_num_edges.restype = i64
     lib.nomad_scatter_path.argtypes = [vp]
     lib.nomad_edge_pass.argtypes = [vp]
+    lib.nomad_edges_in_runs.argtypes = [vp]
     lib.nomad_device_bytes.argtypes = [vp]
     lib.nomad_device_bytes.restype = i64
     lib.nomad_release_memory.argtypes = []
@@ -488,6 +489,10 @@ class Nomad:
     def edge_pass(self):
         """nomad_edge_pass: one of the EDGES_* constants."""
         return int(self.lib.nomad_edge_pass(self.ctx))
+
+    def edges_in_runs(self):
+        """nomad_edges_in_runs: whether the edge pass (EDGES_RECORDS) leaves its forces in runs, not in chains of records."""
+        return bool(self.lib.nomad_edges_in_runs(self.ctx))
 
     def device_bytes(self):
         return int(self.lib.nomad_device_bytes(self.ctx))

@@ -1074,6 +1074,8 @@ int nomad_edge_pass(const nomad_ctx* c) {
            : c->pool_rounds ? NOMAD_EDGES_POOLED : NOMAD_EDGES_RECORDS;
 }
 
+int nomad_edges_in_runs(const nomad_ctx* c) { return c && c->path && c->runs; }
+
 int64_t nomad_device_bytes(const nomad_ctx* c) { return c ? c->device_bytes : 0; }
 
 int nomad_release_memory(void) {
