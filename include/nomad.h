@@ -269,7 +269,8 @@ int nomad_scatter_path(const nomad_ctx* ctx);
  *   NOMAD_EDGES_POOLED    the pooled samplers' own (NOMAD_PATH_BINNED_POOLED)
  *   NOMAD_EDGES_EXCHANGED embedding rows and forces exchanged tile by tile (NOMAD_PATH_BINNED, the same bits as records)
  *   NOMAD_EDGES_LDS_SUMS  the forces of a small embedding summed in LDS (NOMAD_PATH_BINNED, the same bits as records)
- * Where one of the last two could not get its memory, nomad_set_graph goes on with records and nomad_last_error says so.
+ * Where one of the last two, or the forces in runs, could not get its memory, nomad_set_graph goes on with the next that can (runs, then
+ * records in chains) and nomad_last_error says so; likewise where sums over the means by interpolation could not.
  */
 #define NOMAD_EDGES_ROWS 1
 #define NOMAD_EDGES_RECORDS 2

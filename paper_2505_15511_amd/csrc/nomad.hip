@@ -651,7 +651,13 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
     const int32_t R = c->R;
     hipStream_t st = c->stream;
     int rc;
-    std::string fallback_note;
+    std::string fallback_note;       // what could not be set up, and why
+    c->err.clear();
+    const auto missed = [&](const char* what) {
+        fallback_note += (fallback_note.empty() ? "" : "; ") + std::string(what) + " could not be set up (" + (c->err.empty() ? "size out of range" : c->err) + ")";
+        c->err.clear();
+        (void)hipGetLastError();
+    };
 #define TRY(x) do { rc = (x); if (rc != NOMAD_OK) { free_graph(c); return rc; } } while (0)
 #define HTRY(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) { free_graph(c); return fail(c, e_ == hipErrorOutOfMemory ? NOMAD_E_OOM : NOMAD_E_HIP, "%s: %s", #call, hipGetErrorString(e_)); } } while (0)
 
@@ -867,7 +873,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 HTRY(hipMemset(f.count, 0, sizeof(uint32_t) * kFieldTable));
                 HTRY(hipStreamSynchronize(nullptr));
             } else {   // cell by cell
-                (void)hipGetLastError();
+                missed("mean-field sums by interpolation");
                 free_field(c);
             }
         }
@@ -926,9 +932,8 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
             hipLaunchKernelGGL(k_zero_f2, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->ghead, n);
             c->small_wg = small_wg;
             c->binned = true;
-        } else if (small_wg) {   // records remain
-            (void)hipGetLastError();
-            fallback_note = "records in place of sums in LDS, whose work space could not be allocated: " + c->err;
+        } else if (small_wg) {   // runs or records remain
+            missed("the edge pass with sums in LDS");
             dev_free(c, c->small_sums);
             dev_free(c, c->head);
         }
@@ -951,9 +956,8 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 hipLaunchKernelGGL(k_edge_heads, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->row_ptr, n, c->head);
                 hipLaunchKernelGGL(k_zero_f2, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->ghead, n);
                 c->binned = c->exchange = true;
-            } else {   // the sorted edge pass remains
-                (void)hipGetLastError();
-                fallback_note = "the sorted edge pass in place of the exchanged one, whose work space could not be set up: " + (c->err.empty() ? "size out of range" : c->err);
+            } else {   // runs or records remain
+                missed("the exchanged edge pass");
                 free_exchange(c);
                 dev_free(c, c->head); dev_free(c, c->carry);
                 c->phases = 1;
@@ -979,7 +983,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 hipLaunchKernelGGL(k_zero_f2, dim3(blocks_for(n)), dim3(kBlock), 0, st, c->ghead, n);
                 c->binned = true;
             } else {   // chains of records remain
-                (void)hipGetLastError();
+                missed("the edge pass with forces in runs");
                 free_exchange(c);
                 dev_free(c, c->head); dev_free(c, c->carry);
                 c->phases = 1;
@@ -1047,7 +1051,7 @@ int nomad_set_graph(nomad_ctx* c, const int32_t* row_ptr, const int32_t* col_idx
                 c->distinct_kernel = false;
             }
         }
-        if (!c->binned && E > 0) fallback_note = "deterministic scatter on the fixed-point atomics path: " + why;
+        if (!c->binned && E > 0) fallback_note += (fallback_note.empty() ? "" : "; ") + std::string("deterministic scatter on the fixed-point atomics path: ") + why;
         if (!c->binned) {
             TRY(dev_alloc(c, &c->gfix, (size_t)n * 2));
             hipLaunchKernelGGL(k_zero_u64, dim3(blocks_for(n * 2)), dim3(kBlock), 0, st, c->gfix, n * 2);

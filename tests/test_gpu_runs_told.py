@@ -1,9 +1,10 @@
-"""Which of the two edge passes of sorted forces runs (nomad_edges_in_runs): the comparison of forces in runs with records in chains is one of two different passes."""
+"""Which of the two edge passes of sorted forces runs (nomad_edges_in_runs): the comparison of forces in runs with records in chains is one of two different passes, and a
+pass that could not be set up is named."""
 import pytest
 import torch
 
 import tests.test_gpu_runs as runs
-from paper_2505_15511_amd import EDGES_EXCHANGED, EDGES_LDS_SUMS, EDGES_RECORDS, SCATTER_ATOMIC, Nomad
+from paper_2505_15511_amd import EDGES_EXCHANGED, EDGES_LDS_SUMS, EDGES_RECORDS, SCATTER_ATOMIC, Nomad, release_memory
 from tests.test_gpu_exchange import graph
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +52,18 @@ def test_other_passes_are_not_in_runs(n, want, kw):
     with Nomad(n, 1, 5, 5.0, 10, 1.0, 7, **kw) as nm:
         nm.set_graph(row_ptr, col, None, torch.zeros(n, dtype=torch.int32, device="cuda"))
         assert nm.edges_in_runs() == (want == EDGES_RECORDS) and (want is None or nm.edge_pass() == want) and nm.note() == ""
+
+
+def test_a_pass_that_could_not_be_set_up_is_named():
+    """Forces in runs count their slots in 32 bits: 712 M edges in one phase have more.  (Only set up: nothing of this runs.)"""
+    n, degree = 300_000, 2_375
+    col = torch.arange(n, dtype=torch.int32, device="cuda")[:, None] + torch.arange(1, degree + 1, dtype=torch.int32, device="cuda")[None]
+    col = col.remainder_(n).reshape(-1)
+    row_ptr = torch.arange(n + 1, dtype=torch.int32, device="cuda") * degree
+    with Nomad(n, 1, 5, 5.0, 10, 1.0, 7, tune={"record_phases": 1}) as nm:
+        nm.set_graph(row_ptr, col, None, torch.zeros(n, dtype=torch.int32, device="cuda"))
+        assert not nm.edges_in_runs() and nm.edge_pass() == EDGES_RECORDS
+        assert "forces in runs could not be set up (size out of range)" in nm.note()
+    del col, row_ptr
+    release_memory()
+    torch.cuda.empty_cache()
