@@ -147,11 +147,11 @@ inline EdgePlan plan_edge_pass(const EdgePlanRequest& q) {
 //   and runs of 25 records instead of six end in fewer partial lines (1 M points, s = 5, a thousand tiles -> 245: edge pass
 //   1.26 -> 1.12 ms, tile pass 0.32 -> 0.24; 123 tiles: tile pass 0.31).
 // special_kernel: the edge pass is one of the kernels that know their options.  Those also come
-//   with two rounds to a flush, where the records fit LDS (half the barriers and table passes: 100 k points 0.149 -> 0.142 ms,
+//   with two rounds to a flush, where the records fit LDS (where chains are asked for, or runs do not fit; half the barriers and table passes: 100 k points 0.149 -> 0.142 ms,
 //   6 M points in groups, s = 2, 4.26 -> 4.06);
-//   with 256 lanes, for graphs of no more positions than give every compute unit one such workgroup (few now: most embeddings of
-//   up to 10,224 points take plan_small's pass): one round is all there is, and its length goes with the lanes that share its
-//   barriers and LDS (whole epoch, 14 k edges: 22.0 -> 12.7 us, 58 k: 22.4 -> 18.8; with two such workgroups per compute unit 87 k: 24.0 -> 25.8, 116 k: 25.7 -> 29.9).
+//   with 256 lanes, for graphs of no more positions than give every compute unit one such workgroup (embeddings of
+//   up to 10,224 points take plan_small's pass, and plan_runs leaves the sparsest graphs of the others to chains: those are what comes here, and what asks for chains):
+//   one round is all there is, and its length goes with the lanes that share its barriers and LDS (whole epoch, 14 k edges: 22.0 -> 12.7 us, 58 k: 22.4 -> 18.8; with two such workgroups per compute unit 87 k: 24.0 -> 25.8, 116 k: 25.7 -> 29.9).
 inline bool edge_tables_fit(const EdgePlan& p, const EdgePlanRequest& q) {
     const size_t lds = p.distinct_kernel ? distinct_lds_bytes(p.n_bins, (uint32_t)q.pool_size, (uint32_t)(q.pool_size / q.pool_line), p.pool_rounds)
                        : p.pool_rounds  ? pooled_lds_bytes(p.n_bins, q.pool_block, (uint32_t)q.pool_size)
@@ -282,8 +282,13 @@ inline ExchangePlan plan_exchange(const EdgePlanRequest& q, const EdgePlan& p) {
 //   Which: all that would otherwise leave records in chains, sorted by tile.  Time of an epoch, runs over chains (symmetrised, 12 to 15 out-neighbours,
 //   numbered cluster by cluster): s = 5 10 k points 0.71, 20 k 0.67, 100 k 0.65, 300 k 0.71, 600 k 0.78, 900 k 0.83; s = 8 0.76 (100 k), 0.86 (900 k); s = 3 0.70 (400 k in
 //   sub-steps), 0.82 (900 k); s = 2 0.71 (100 k), 0.79, 1.4 M 0.90; s = 1 0.79, 0.78 (600 k); none 0.74 (20 k), 0.86 (5 M); 64 sub-steps of 20 k to 5 M 0.57 to 0.85; every cluster its own
-//   group 150 k 0.57, 1 M 0.76, 3 M (s = 2) 0.83, 8 M 0.94.  Graphs of fewer edges than points have: 12 k, 24 k edges, s = 2 1.02 (within what runs differ by), all others
-//   0.75 to 0.8.  The exchange from a million points on (plan_exchange): runs take 0.94 to 1.0 of its time there, 1.03 to 1.09 at 1.3 M and 1.2 to 1.4 at 2.5 M, and in
+//   group 150 k 0.57, 1 M 0.76, 3 M (s = 2) 0.83, 8 M 0.94.
+//   Not for graphs of so few edges that they are a few blocks (runs_sparse): a workgroup of chains then has 256 positions, a block of runs up to 1,536, and both are one chain of
+//   loads.  Runs over chains at 4 k, 16 k, 32 k, 48 k edges, s = 2: 20 k points 1.26, 1.20, 1.09, 0.85, 900 k 1.35, 1.24, 1.13, 0.99 (in groups 1.21, 1.19, 1.14, 1.05; sampled means 1.32, 1.31,
+//   1.22, 1.08); s = 1: 20 k 1.14, 1.07, 1.00, 0.82, 2 M 1.24, 1.19, 1.12, 0.97; s = 5: 20 k 1.09, 1.02, 0.90, 200 k 1.24, 1.12, 1.03, 0.89, 900 k 1.21, 1.10, 1.07, 0.94; s = 3: 20 k 1.02, 0.97, 0.87,
+//   200 k 1.14, 1.04, 0.97, 900 k 1.12, 1.04, 0.99; none: 20 k 0.99, 0.95, 200 k 1.09, 1.02, 0.95, 2 M 1.19, 1.12, 1.07, 0.93.  s = 7 and 8 (blocks of 512): 0.60 to 1.0, two million points up to 1.06.  (Smaller
+//   embeddings take sums in LDS.)
+//   The exchange from a million points on (plan_exchange): runs take 0.94 to 1.0 of its time there, 1.03 to 1.09 at 1.3 M and 1.2 to 1.4 at 2.5 M, and in
 //   random order 1.08, 1.11 and 1.5, so its lines stay.
 //   Not with sampled means beyond 256 tiles: what a block's slots are made for are negatives, few of which get a force there, and the tiles look for their runs in many
 //   blocks.  400 k 0.78 to 0.85, 1 M 0.90, 2 M 0.97, 2.5 M (s = 8) 1.03, 3 M (s = 5) 1.01, 5 M (s = 2) 1.02.
@@ -304,6 +309,10 @@ NOMAD_HOST_DEVICE inline uint32_t runs_tile_of(uint32_t pt, int shift, uint32_t 
     const uint32_t x = pt >> shift;
     return magic ? (uint32_t)(((uint64_t)x * magic) >> 32) : x;
 }
+inline bool runs_sparse(const EdgePlanRequest& q, int compute_units) {
+    const int64_t few = q.s == 1 || q.s == 2 || q.n >= (1 << 19) ? 128 : q.n >= (1 << 17) ? 64 : 32;   // positions a compute unit
+    return q.s <= 6 && small_lds_bytes(q.n) > kMaxLdsBytes && q.E <= few * compute_units;
+}
 inline RunsPlan plan_runs(const EdgePlanRequest& q, const EdgePlan& p, int compute_units = 256) {
     RunsPlan x;
     const bool records_asked = q.tune_edge_block || q.tune_wg_per_cu || q.tune_record_sort || q.tune_flush_rounds;
@@ -322,7 +331,7 @@ inline RunsPlan plan_runs(const EdgePlanRequest& q, const EdgePlan& p, int compu
         const int64_t factor = (want + ((int64_t)1 << shift) - 1) >> shift;
         if (factor << shift <= most) tiles_of(factor << shift, (uint32_t)factor, shift);
     }
-    x.use = p.sorted && 2 * runs_lds_bytes(q.s, x.n_tiles) <= kMaxLdsBytes && !(q.far && q.n > 256 * most);
+    x.use = p.sorted && !runs_sparse(q, compute_units) && 2 * runs_lds_bytes(q.s, x.n_tiles) <= kMaxLdsBytes && !(q.far && q.n > 256 * most);
     const double run = (double)runs_block_edges(q.s) * (q.s + 1) / x.n_tiles;
     x.sums_lanes = q.grouped ? 32 : run < 12 ? 8 : run < 22 ? 16 : 32;
     return x;

@@ -46,6 +46,21 @@ def test_lanes(n, s, E, lanes, told):
     assert told == {False, True}
 
 
+@pytest.mark.parametrize("n,E,s,kind", [(12_000, 3_000, 2, "plain"), (20_000, 32_768, 1, "groups"), (200_000, 5_000, 5, "plain"), (900_001, 20_000, 0, "far")])
+def test_sparse_graphs_are_left_to_chains(n, E, s, kind):
+    cluster_of = (torch.arange(n, device="cuda") * 7 // n).to(torch.int32)
+    row_ptr, col, theta = graph(n, E, s)
+    got = []
+    for tune in ({}, {"exchange": 2}, {"record_sort": 1}):
+        with Nomad(n, 7, s, 5.0, 10, 1.0, 7, sampled_far_field=kind == "far", tune=tune) as nm:
+            nm.set_graph(row_ptr, col, None, cluster_of, None if kind == "plain" else torch.arange(7, dtype=torch.int32, device="cuda"))
+            assert not nm.edges_in_runs() and nm.edge_pass() == EDGES_RECORDS and nm.note() == ""
+            nm.set_embedding(theta)
+            nm.epoch(0)
+            got.append((nm.get_gradient(device=True), nm.get_embedding(device=True)))
+    runs.same(got[0], got[2]), runs.same(got[1], got[2])
+
+
 @pytest.mark.parametrize("n,want,kw", [(2_000, EDGES_LDS_SUMS, {}), (20_000, EDGES_RECORDS, {}), (1_000_000, EDGES_EXCHANGED, {}), (20_000, None, {"scatter_mode": SCATTER_ATOMIC})])
 def test_other_passes_are_not_in_runs(n, want, kw):
     row_ptr, col, _ = graph(n, 50_000, 3)
