@@ -440,7 +440,8 @@ __global__ void __launch_bounds__(64 * WAVES, knn_waves_per_simd(TILE, KS, L, WA
     };
     // One neighbour, in 32-row tiles: the element v of the accumulator goes into the last four bits of the key, so that the two smallest of a tile's sixteen take three instructions a key instead of
     // eight; those keys differ from their own by less than 2^-19 of them, which the margin and tau carry.  A group's last tile, if padded, is done key by key
-    // (infinity with a number in it is none).  Large products alone, 1,000,000 x 128 on 256 centroids: 132 -> 104 us a step, with all three products 222 -> 196.
+    // (infinity with a number in it is none; keys of a full tile are finite, knn_filter_usable).  Points that this leaves open besides, simulated on mixtures and noise of 8 to 768 columns: with all
+    // three products up to 70 of a million (750 to 1,800 are), with the large ones alone, whose margin is a hundred times as wide, up to 30 (33,000 to 70,000 are).  Large products alone, 1,000,000 x 128 on 256 centroids: 132 -> 104 us a step, with all three products 222 -> 196.
     constexpr bool kNumbered = L == 2 && TILE == 32;
     // positions there: 16 times the tile and the element, which is candidate 8 (v / 4) + 4 part + v % 4 of the tile
     const auto place_of = [&](int32_t p) { return p < 0 || !kNumbered ? p : (p >> 4) * TILE + 8 * (p >> 2 & 3) + 4 * part + (p & 3); };

@@ -16,7 +16,7 @@ struct RunsShape {
 //
 // Bound by the gathers out of L2 (2.6 M edges of 100,000 points, s = 5: 78 us, the 15.6 M gathers alone 58 at 270 G/s).  k_edges_binned does the same work in 141 us:
 // one persistent workgroup a compute unit, whose rounds are a chain of phases with barriers between them, and records of 12 bytes in chains of chunks.  Here a
-// compute unit has two workgroups of 1,024 lanes (or three of 512), each in a phase of its own, a block's forces leave as whole lines, 10 bytes a reference,
+// compute unit has two workgroups of 1,024 lanes (s = 7 and 8: three of 512; up to two negatives two of 512 with three edges a lane), each in a phase of its own, a block's forces leave as whole lines, 10 bytes a reference,
 // and the tile's workgroup finds its runs by a table (the tile pass 54 -> 36 us).  300,000 points, 9 M edges: 285 + 165 us.  6 M points in groups, s = 2: 3.92 + 0.94 -> 2.74 + 1.02 ms.
 // Same lanes for the same edges, same products, integer sums: the same bits.
 template <int S, int KIND>
